@@ -99,7 +99,7 @@ extern "C" int epp_path_info(const epp_path_t* p, epp_path_info_t* info) {
     info->max_len = p->max_len;
     for (int c = 0; c < EPP_NCLASS; ++c) info->len_hist[c] = p->len_hist[c];
     size_t bytes = p->row_ids.bytes + p->rowptr.bytes + p->cv.bytes + p->full_rowptr.bytes + p->empty_rows.bytes;
-    bytes += p->zero_block.bytes;
+    bytes += p->zero_block.bytes + p->inner_pos.bytes;
     for (const Schedule* s : p->scheds) bytes += s->bytes();
     for (const auto& w : p->widths)
         if (w.part) bytes += w.part->bytes();

@@ -239,6 +239,7 @@ struct epp_path {
     const unsigned int* inner_rows = nullptr;  // set on the inner path: bitmap of its rows (owned by the handle)
     bool has_inner = false;               // set on the outer path: kEntOuterOnly marks are in place
     DevBuf zero_block;                    // outer path: 256 zero bytes, what a skipped entry gathers
+    DevBuf inner_pos;                     // outer path: int32[ceil(nnz / 64)] entries of the inner path before every 64th entry
     int cold_thr = 0;            // entries whose source is referenced fewer times than this carry the cold flag
     int cold_F = 0;              // width the cold flags were chosen for (the largest prepared width that marks)
     epp_alloc_t alloc = {nullptr, nullptr, nullptr};  // the caller's allocator (alloc == NULL: hipMalloc)
