@@ -269,7 +269,7 @@ struct epp_paths {
     std::vector<int64_t> set_size;  // |N^k|
     std::vector<epp_path*> path;    // index l; once the sets stop growing, deeper layers share one object
     DevBuf set0_ids;                // ascending ids of N^0 (the other sets are path rows)
-    DevBuf small_store;             // small graphs: the one allocation that all arrays above are views of
+    DevBuf store;                   // the allocation that the bitmaps (small graphs: all arrays) are views of
     ScratchPool pool;               // launch scratch shared by the paths
     epp_alloc_t alloc = {nullptr, nullptr, nullptr};
     ~epp_paths() {
@@ -281,13 +281,21 @@ struct epp_paths {
     }
 };
 
+// Pinned host words that the device writes and the host reads after a wait; a lease on a block of a
+// process-wide list (prepare.hip).
+struct PinnedWords {
+    long long* p = nullptr;
+    size_t count = 0;
+    PinnedWords() = default;
+    PinnedWords(const PinnedWords&) = delete;
+    PinnedWords& operator=(const PinnedWords&) = delete;
+    int get(size_t need);
+    ~PinnedWords();
+};
+
 // prepare.hip
-// histogram + max length of a built path; `stats_scratch`: (EPP_NCLASS + 1) * 8 device bytes, or NULL
-// `host_later` (pinned host memory, EPP_NCLASS + 1 words): the statistics are copied there
-// without waiting; the caller hands them to epp_path_set_stats after it has synchronised
-// mark_row_ends = false: the entry array is not there yet (the caller marks the row ends itself)
-int epp_path_finish(epp_path* p, hipStream_t s, void* stats_scratch = nullptr, unsigned long long* host_later = nullptr,
-                    bool mark_row_ends = true);
+// histogram + max length of a built path (waits for them), row-end flags
+int epp_path_finish(epp_path* p, hipStream_t s);
 void epp_path_set_stats(epp_path* p, const unsigned long long* host);
 // ascending vertex ids of N^k (device, owned by `p`); allocates nothing, never waits
 int epp_active_ids(const epp_paths* p, int k, const int32_t** ids, int64_t* count);

@@ -3,27 +3,35 @@
 // renumbering and prefix-sum compaction into compact CSR.  Hand-written for gfx950, wave64.
 //
 // One level k -> k+1 is two streaming passes over the edge array and two over the rows:
-//   edge_mask     keep[j] = (col[j] in N^k) as one 64-bit ballot per 64 edges + tile counts
-//   scan          exclusive scan of the tile counts (one readback: nnz of the path)
-//   edge_extract  stable compaction of (col, val) through the ballots; also stores the
-//                 running count at every 64-edge boundary
+//   edge_mask     keep[j] = (col[j] in N^k) as one 64-bit ballot per 64 edges, the kept edges before
+//                 each of them in its tile of 2048, and the tile's count
+//   scan          exclusive scan of the tile counts
 //   row_flags     filtered row pointer of every vertex from those counts; a vertex is in
-//                 N^{k+1} iff its filtered list is non-empty -> next bitmap
-//   bitmap_count / scan / bitmap_compact   ascending ids of N^{k+1} + compact row pointer
+//                 N^{k+1} iff its filtered list is non-empty -> next bitmap, members per 256 vertices
+//   scan          exclusive scan of the member counts; its last act is to hand the level's five
+//                 numbers (kept edges, members, errors, relation of N^k to N^{k+1}) to the host
+//   rows_compact  ascending ids of N^{k+1}, compact row pointer, row-length statistics
+//   edge_extract  stable compaction of (col, val) through the ballots
+// The host waits once per level, for those numbers, and then allocates the level's arrays.
 // All kept entries belong to rows of N^{k+1} by definition, so compacting the edge array
 // alone yields the path's entries in canonical order.
 
 #include <algorithm>
 #include <cstdlib>
 #include <cstring>
+#include <mutex>
 
 #include "epp_internal.h"
 
 namespace {
 
 constexpr int kBlock = 256;
-constexpr int kSegsPerTile = 32;  // 32 ballots of 64 edges = 2048 edges per workgroup
-constexpr int kWordsPerTile = 256;
+constexpr int kSegsPerTile = 32;  // 32 ballots of 64 edges = 2048 edges
+constexpr int kWordsPerTile = 64;  // bitmap words per workgroup (at most kBlock)
+// Numbers of one level: [0] kept entries, [1] rows, [2] input errors (below), [3] N^k is not inside
+// N^{k+1}, [4] N^k differs from N^{k+1}, [5] |N^0| (first level)
+constexpr int kLevelWords = 8;
+constexpr int kErrRowptr = 1, kErrCol = 2, kErrTrain = 4;
 
 __device__ __forceinline__ int lane_id() { return threadIdx.x & 63; }
 __device__ __forceinline__ unsigned long long low_mask(int lane) { return (1ull << lane) - 1ull; }
@@ -64,66 +72,124 @@ __global__ __launch_bounds__(kBlock) void k_mark_training(const int32_t* __restr
     int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
     if (i >= n_ids) return;
     int32_t v = ids[i];
-    if (v < 0 || v >= n) { atomicOr(err, 1); return; }
+    if (v < 0 || v >= n) { atomicOr(err, kErrTrain); return; }
     atomicOr(&bitmap32[v >> 5], 1u << (v & 31));
 }
 
-// keep-mask of every 64-edge segment and kept entries per tile.
+struct MaskArgs {
+    const int32_t* col;
+    int64_t nnz, n_seg, n_tiles;
+    int n;
+    const unsigned int* bitmap;     // N^k
+    int first_id, n_ids;            // ids looked up by this pass (all of them without the LDS window)
+    const unsigned long long* known;  // entries kept without a lookup (NULL: none; may be `mask` itself)
+    int all;                        // N^k holds every vertex: every entry is kept, nothing is looked up
+    int check;                      // range-check the columns (the first pass over the array)
+    int count;                      // last pass of the level: write the counts
+    unsigned long long* mask;
+    uint16_t* seg_off;              // kept entries of the tile before each segment
+    int* tile_count;
+    int* err;
+};
+
+// keep-mask of every 64-edge segment, kept entries per tile and before each segment of a tile.  A
+// wavefront owns a tile of 2048 entries and takes it in two halves: 16 column loads, then 16
+// lookups, each back to back, so that the dependent latencies are paid once per half.
 //
-// `prev` is the keep-mask of the previous level, or NULL.  If N^{k-1} is a
-// subset of N^k (*not_subset == 0; always the case when every vertex has a self-loop), an entry
-// kept at the previous level has its column in N^{k-1}, hence in N^k, and is kept again: only
-// the other entries are loaded and looked up.  Once the sets are close to saturation this
-// turns a pass bound by the rate of random bitmap lookups into a scan of the previous mask.
+// What bounds it: the lookups.  64 lanes look 64 different words up, which from L2 costs the address
+// unit one cycle and more per lane: 250 G lookups/s on the whole chip, 0.52 ms for the 140 M
+// entries of a co-purchase graph whose columns stream in 0.12 ms.  LDS serves a wavefront's 64
+// words in a few cycles.  So a workgroup first copies a window of the bitmap into LDS (LDS_WORDS
+// words: 1.28 M ids fit) and streams its tiles past it; where the graph has more vertices, one
+// pass per window, each adding its finds to the mask.  A pass re-reads the columns, so past three
+// windows the lookups through L2 (LDS_WORDS = 0) are no slower.  Same graph: 0.28 ms in two passes.
 //
-// Columns are range-checked where they are loaded (every entry at the first level): an id outside
-// [0, n) raises bit 1 of *err and is treated as not kept, so it is never used as an index.
-__global__ __launch_bounds__(kBlock) void k_edge_mask(const int32_t* __restrict__ col, int64_t nnz, int64_t n_seg,
-                                                      int64_t n, const unsigned int* __restrict__ bitmap32,
-                                                      const unsigned long long* __restrict__ prev,
-                                                      const int* __restrict__ not_subset,
-                                                      unsigned long long* __restrict__ mask,
-                                                      int* __restrict__ tile_count, int* __restrict__ err) {
-    __shared__ int wave_cnt[4];
+// `known`: if N^{k-1} is a subset of N^k (always the case when every vertex has a self-loop), an
+// entry kept at the previous level has its column in N^{k-1}, hence in N^k, and is kept again: only
+// the other entries are loaded and looked up.  The next window of a level is handed the mask so far
+// in the same way.
+//
+// Columns are range-checked by the first pass: an id outside [0, n) raises an error bit; it is
+// never used as an index.
+template <int THREADS, int LDS_WORDS>
+__global__ __launch_bounds__(THREADS) void k_edge_mask(MaskArgs a) {
+    __shared__ __attribute__((aligned(16))) unsigned int bits[LDS_WORDS > 0 ? LDS_WORDS : 4];
     const int wave = threadIdx.x >> 6, lane = lane_id();
-    int cnt = 0;
-    // a wavefront owns 8 consecutive segments; all column loads, then all bitmap lookups, are
-    // issued back to back so that the two dependent memory latencies are paid once per tile
-    constexpr int kPerWave = kSegsPerTile / 4;
-    const int64_t seg0 = (int64_t)blockIdx.x * kSegsPerTile + wave * kPerWave;
-    const bool use_prev = prev && *not_subset == 0;
-    bool known[kPerWave];
-    int32_t c[kPerWave];
-    unsigned int w[kPerWave];
-#pragma unroll
-    for (int i = 0; i < kPerWave; ++i) {
-        const unsigned long long pm = (use_prev && seg0 + i < n_seg) ? prev[seg0 + i] : 0ull;
-        known[i] = (pm >> lane) & 1ull;
+    if constexpr (LDS_WORDS > 0) {
+        if (!a.all) {
+            const int words = (a.n_ids + 31) >> 5, total = ((a.n + 63) >> 6) * 2 - (a.first_id >> 5);
+            const unsigned int* __restrict__ src = a.bitmap + (a.first_id >> 5);
+            for (int i = 4 * (int)threadIdx.x; i < words; i += 4 * THREADS) {
+                uint4 x = make_uint4(0, 0, 0, 0);
+                if (i + 4 <= total) {
+                    x = *reinterpret_cast<const uint4*>(src + i);
+                } else {
+                    if (i < total) x.x = src[i];
+                    if (i + 1 < total) x.y = src[i + 1];
+                    if (i + 2 < total) x.z = src[i + 2];
+                }
+                *reinterpret_cast<uint4*>(bits + i) = x;
+            }
+            __syncthreads();
+        }
     }
+    constexpr int kHalf = kSegsPerTile / 2;
+    const int64_t step = (int64_t)gridDim.x * (THREADS / 64);
+    for (int64_t tile = (int64_t)blockIdx.x * (THREADS / 64) + wave; tile < a.n_tiles; tile += step) {
+        const int64_t seg0 = tile * kSegsPerTile;
+        const bool mine = lane < kSegsPerTile && seg0 + lane < a.n_seg;
+        const unsigned long long pm = (a.known && mine) ? a.known[seg0 + lane] : 0ull;
+        unsigned long long out = 0ull;
+        int off = 0, run = 0;
+        bool bad = false;
 #pragma unroll
-    for (int i = 0; i < kPerWave; ++i) {
-        const int64_t e = (seg0 + i) * 64 + lane;
-        c[i] = (e < nnz && !known[i]) ? col[e] : -1;
+        for (int h = 0; h < 2; ++h) {
+            int c[kHalf];
+            unsigned long long km[kHalf];
+#pragma unroll
+            for (int i = 0; i < kHalf; ++i) {
+                const int sg = h * kHalf + i;
+                const int64_t e = (seg0 + sg) * 64 + lane;
+                km[i] = (unsigned int)__builtin_amdgcn_readlane((int)pm, sg) |
+                        ((unsigned long long)(unsigned int)__builtin_amdgcn_readlane((int)(pm >> 32), sg) << 32);
+                c[i] = (e < a.nnz && !a.all && !((km[i] >> lane) & 1ull)) ? __builtin_nontemporal_load(a.col + e) : -1;
+            }
+            if (a.check) {
+#pragma unroll
+                for (int i = 0; i < kHalf; ++i) {
+                    const int64_t e = (seg0 + h * kHalf + i) * 64 + lane;
+                    bad |= e < a.nnz && (c[i] < 0 || c[i] >= a.n) && !a.all && !((km[i] >> lane) & 1ull);
+                }
+            }
+            unsigned int w[kHalf];
+#pragma unroll
+            for (int i = 0; i < kHalf; ++i) {
+                const int x = c[i] - a.first_id;
+                const bool in = c[i] >= 0 && (unsigned int)x < (unsigned int)a.n_ids;
+                if constexpr (LDS_WORDS > 0) w[i] = in ? bits[x >> 5] : 0u;
+                else w[i] = in ? a.bitmap[x >> 5] : 0u;
+                c[i] = x;
+            }
+#pragma unroll
+            for (int i = 0; i < kHalf; ++i) {
+                const int sg = h * kHalf + i;
+                const bool keep = a.all ? (seg0 + sg) * 64 + lane < a.nnz
+                                        : ((km[i] >> lane) & 1ull) || ((w[i] >> (c[i] & 31)) & 1u);
+                const unsigned long long m = __ballot(keep);
+                if (lane == sg) {
+                    out = m;
+                    off = run;
+                }
+                run += __popcll(m);
+            }
+        }
+        if (bad) atomicOr(a.err, kErrCol);
+        if (mine) {
+            a.mask[seg0 + lane] = out;
+            if (a.count) a.seg_off[seg0 + lane] = (uint16_t)off;
+        }
+        if (a.count && lane == 0) a.tile_count[tile] = run;
     }
-    bool bad = false;
-#pragma unroll
-    for (int i = 0; i < kPerWave; ++i) {
-        const int64_t e = (seg0 + i) * 64 + lane;
-        if (e < nnz && !known[i] && (c[i] < 0 || c[i] >= n)) { bad = true; c[i] = -1; }
-    }
-    if (bad) atomicOr(err, 2);
-#pragma unroll
-    for (int i = 0; i < kPerWave; ++i) w[i] = c[i] >= 0 ? bitmap32[c[i] >> 5] : 0u;
-#pragma unroll
-    for (int i = 0; i < kPerWave; ++i) {
-        const bool keep = known[i] || (c[i] >= 0 && ((w[i] >> (c[i] & 31)) & 1u));
-        const unsigned long long m = __ballot(keep);
-        if (lane == 0 && seg0 + i < n_seg) mask[seg0 + i] = m;
-        cnt += __popcll(m);
-    }
-    if (lane == 0) wave_cnt[wave] = cnt;
-    __syncthreads();
-    if (threadIdx.x == 0) tile_count[blockIdx.x] = wave_cnt[0] + wave_cnt[1] + wave_cnt[2] + wave_cnt[3];
 }
 
 // Exclusive scan of `n` counts (per-tile numbers of kept entries or set bits).  A workgroup of
@@ -134,19 +200,27 @@ constexpr int kScanPerThread = 8;
 constexpr int kScanChunk = 1024 * kScanPerThread;
 
 // Scans in[base .. base + kScanChunk) into out, starting from `carry`; returns the chunk's sum
-// to every thread.  Called by all 1024 threads of the workgroup.
+// to every thread.  Called by all 1024 threads of the workgroup.  (The arrays are 16-byte aligned.)
 __device__ __forceinline__ int scan_chunk(const int* __restrict__ in, int* __restrict__ out, int64_t n, int64_t base,
                                           int carry) {
     __shared__ int wave_sum[16];
     const int wave = threadIdx.x >> 6, lane = lane_id();
     const int64_t i0 = base + (int64_t)threadIdx.x * kScanPerThread;
+    const bool whole = i0 + kScanPerThread <= n;
     int x[kScanPerThread];
     int mine = 0;
+    if (whole) {
 #pragma unroll
-    for (int j = 0; j < kScanPerThread; ++j) {
-        x[j] = i0 + j < n ? in[i0 + j] : 0;
-        mine += x[j];
+        for (int j = 0; j < kScanPerThread; j += 4) {
+            const int4 v = *reinterpret_cast<const int4*>(in + i0 + j);
+            x[j] = v.x; x[j + 1] = v.y; x[j + 2] = v.z; x[j + 3] = v.w;
+        }
+    } else {
+#pragma unroll
+        for (int j = 0; j < kScanPerThread; ++j) x[j] = i0 + j < n ? in[i0 + j] : 0;
     }
+#pragma unroll
+    for (int j = 0; j < kScanPerThread; ++j) mine += x[j];
     const int incl = wave_inclusive_scan(mine);
     if (lane == 63) wave_sum[wave] = incl;
     __syncthreads();
@@ -159,17 +233,34 @@ __device__ __forceinline__ int scan_chunk(const int* __restrict__ in, int* __res
     off += incl - mine;
 #pragma unroll
     for (int j = 0; j < kScanPerThread; ++j) {
-        if (i0 + j < n) out[i0 + j] = off;
-        off += x[j];
+        const int v = x[j];
+        x[j] = off;
+        off += v;
+    }
+    if (whole) {
+#pragma unroll
+        for (int j = 0; j < kScanPerThread; j += 4)
+            *reinterpret_cast<int4*>(out + i0 + j) = make_int4(x[j], x[j + 1], x[j + 2], x[j + 3]);
+    } else {
+#pragma unroll
+        for (int j = 0; j < kScanPerThread; ++j)
+            if (i0 + j < n) out[i0 + j] = x[j];
     }
     return all;
 }
 
+// With `level` (the numbers of a level, of which *total is one) and `host` (pinned): all of them are
+// handed to the host.
 __global__ __launch_bounds__(1024) void k_scan_counts(const int* __restrict__ in, int* __restrict__ out, int64_t n,
-                                                      long long* __restrict__ total) {
+                                                      long long* total, const long long* level, long long* host) {
     int carry = 0;
     for (int64_t base = 0; base < n; base += kScanChunk) carry += scan_chunk(in, out, n, base, carry);
-    if (threadIdx.x == 0) *total = carry;
+    if (threadIdx.x == 0) {
+        *total = carry;
+        if (host) {
+            for (int i = 0; i < kLevelWords; ++i) host[i] = level + i == total ? (long long)carry : level[i];
+        }
+    }
 }
 
 __global__ __launch_bounds__(1024) void k_scan_chunks(const int* __restrict__ in, int* __restrict__ out, int64_t n,
@@ -187,27 +278,21 @@ __global__ __launch_bounds__(1024) void k_scan_add_offsets(int* __restrict__ out
         if (i0 + j < n) out[i0 + j] += off;
 }
 
-// seg_base[s] = number of kept entries before segment s: the tile's offset plus the kept
-// entries of the tile's earlier segments.  One wavefront per tile.
-__global__ __launch_bounds__(64) void k_seg_base(const unsigned long long* __restrict__ mask, int64_t n_seg,
-                                                 const int* __restrict__ tile_base, int* __restrict__ seg_base) {
-    const int lane = lane_id();
-    const int64_t seg = (int64_t)blockIdx.x * kSegsPerTile + lane;
-    const int c = (lane < kSegsPerTile && seg < n_seg) ? __popcll(mask[seg]) : 0;
-    const int incl = wave_inclusive_scan(c);
-    if (lane < kSegsPerTile && seg < n_seg) seg_base[seg] = tile_base[blockIdx.x] + incl - c;
-}
+// Where the kept entries of a level go: mask, and the counts before a tile and inside it.
+struct Kept {
+    const unsigned long long* mask;
+    const uint16_t* seg_off;
+    const int* tile_base;
+    __device__ __forceinline__ int before_seg(int64_t seg) const { return tile_base[seg / kSegsPerTile] + seg_off[seg]; }
+};
 
 // Stable compaction of the kept entries into interleaved (col, val) pairs: a kept entry of
-// segment s goes to seg_base[s] + (kept entries before it in the segment).  With `inner` (the
-// keep-mask of the level before, a subset of `mask`) the entries that level did not keep get
-// the kEntOuterOnly mark: the path of the level before will run on this array; inner_pos[q / 64]
-// then receives, for every 64th entry q, how many entries before it that level kept.
+// segment s goes to (kept entries before s) + (kept entries before it in the segment).  With
+// `inner.mask` (the keep-mask of the level before, a subset of this one) the entries that level did
+// not keep get the kEntOuterOnly mark: the path of the level before will run on this array;
+// inner_pos[q / 64] then receives, for every 64th entry q, how many entries before it that level kept.
 __global__ __launch_bounds__(kBlock) void k_edge_extract(const int32_t* __restrict__ col, const float* __restrict__ val,
-                                                         int64_t n_seg, const unsigned long long* __restrict__ mask,
-                                                         const unsigned long long* __restrict__ inner,
-                                                         const int* __restrict__ seg_base,
-                                                         const int* __restrict__ inner_base,
+                                                         int64_t n_seg, Kept outer, Kept inner,
                                                          int* __restrict__ inner_pos, int2* __restrict__ cv) {
     const int wave = threadIdx.x >> 6, lane = lane_id();
     constexpr int kPerWave = kSegsPerTile / 4;
@@ -217,62 +302,145 @@ __global__ __launch_bounds__(kBlock) void k_edge_extract(const int32_t* __restri
 #pragma unroll
     for (int i = 0; i < kPerWave; ++i) {
         const int64_t seg = (int64_t)blockIdx.x * kSegsPerTile + wave * kPerWave + i;
-        m[i] = seg < n_seg ? mask[seg] : 0ull;
-        fr[i] = (inner && seg < n_seg) ? (m[i] & ~inner[seg]) : 0ull;
-        sb[i] = seg < n_seg ? seg_base[seg] : 0;
+        m[i] = seg < n_seg ? outer.mask[seg] : 0ull;
+        fr[i] = (inner.mask && seg < n_seg) ? (m[i] & ~inner.mask[seg]) : 0ull;
+        sb[i] = seg < n_seg ? outer.before_seg(seg) : 0;
     }
 #pragma unroll
     for (int i = 0; i < kPerWave; ++i) {
         const int64_t e = ((int64_t)blockIdx.x * kSegsPerTile + wave * kPerWave + i) * 64 + lane;
         if ((m[i] >> lane) & 1ull)
-            x[i] = make_int2(col[e] | (((fr[i] >> lane) & 1ull) ? kEntOuterOnly : 0), __float_as_int(val[e]));
+            x[i] = make_int2(__builtin_nontemporal_load(col + e) | (((fr[i] >> lane) & 1ull) ? kEntOuterOnly : 0),
+                             __float_as_int(__builtin_nontemporal_load(val + e)));
     }
 #pragma unroll
     for (int i = 0; i < kPerWave; ++i) {
         if ((m[i] >> lane) & 1ull) {
             const int q = sb[i] + __popcll(m[i] & low_mask(lane));
             cv[q] = x[i];
-            if (inner && (q & 63) == 0) {
+            if (inner.mask && (q & 63) == 0) {
                 const int64_t seg = (int64_t)blockIdx.x * kSegsPerTile + wave * kPerWave + i;
-                inner_pos[q >> 6] = inner_base[seg] + __popcll(m[i] & ~fr[i] & low_mask(lane));
+                inner_pos[q >> 6] = inner.before_seg(seg) + __popcll(m[i] & ~fr[i] & low_mask(lane));
             }
         }
     }
 }
 
-// Filtered row pointer of every vertex and membership of N^{k+1}.  A row pointer that does not
-// rise from 0 to nnz raises bit 0 of *err; the offending row is treated as empty, so no index
-// outside the mask arrays is formed.
-__global__ __launch_bounds__(kBlock) void k_row_flags(const int32_t* __restrict__ rowptr, int64_t n, int64_t nnz,
-                                                      const unsigned long long* __restrict__ mask,
-                                                      const int* __restrict__ seg_base,
-                                                      const long long* __restrict__ total_p,
-                                                      int* __restrict__ newptr,
+// Filtered row pointer of every vertex, membership of N^{k+1}, members per 256 vertices, and how
+// N^{k+1} relates to N^k.  A row pointer that does not rise from 0 to nnz raises an error bit; no
+// index outside the mask arrays is formed.
+__global__ __launch_bounds__(kBlock) void k_row_flags(const int32_t* __restrict__ rowptr, int64_t n, int64_t nnz, Kept kept,
+                                                      long long* level, int* __restrict__ newptr,
+                                                      const unsigned long long* __restrict__ bitmap_cur,
                                                       unsigned long long* __restrict__ bitmap_next,
-                                                      int* __restrict__ err) {
-    int64_t v = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+                                                      int* __restrict__ row_count) {
+    __shared__ int wave_cnt[kBlock / 64], wave_rel[kBlock / 64];
+    const int lane = lane_id(), wave = threadIdx.x >> 6;
+    const int64_t v = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+    const int total = (int)level[0];  // kept entries of the level (the host has not read it yet)
+    auto kept_before = [&](int64_t p) -> int {
+        if (p < 0 || p >= nnz) return total;
+        return kept.before_seg(p >> 6) + __popcll(kept.mask[p >> 6] & low_mask((int)(p & 63)));
+    };
+    const int p0 = v < n ? rowptr[v] : (int)nnz;
+    int p1 = __shfl_down(p0, 1, 64);
+    if (lane == 63) p1 = v + 1 <= n ? rowptr[v + 1] : (int)nnz;
+    const int a = kept_before(p0);
+    int b = __shfl_down(a, 1, 64);
+    if (lane == 63) b = kept_before(p1);
     bool flag = false;
     if (v < n) {
-        const int total = (int)*total_p;  // kept entries of the level (the host has not read it yet)
-        int64_t p0 = rowptr[v], p1 = rowptr[v + 1];
-        if (p0 < 0 || p1 < p0 || p1 > nnz || (v == 0 && p0 != 0) || (v == n - 1 && p1 != nnz)) {
-            atomicOr(err, 1);
-            p0 = p1 = nnz;
-        }
-        int a = p0 >= nnz ? total : seg_base[p0 >> 6] + __popcll(mask[p0 >> 6] & low_mask((int)(p0 & 63)));
-        int b = p1 >= nnz ? total : seg_base[p1 >> 6] + __popcll(mask[p1 >> 6] & low_mask((int)(p1 & 63)));
+        if (v == n - 1) p1 = rowptr[n];
+        if (p0 < 0 || p1 < p0 || p1 > nnz || (v == 0 && p0 != 0) || (v == n - 1 && p1 != nnz))
+            atomicOr(reinterpret_cast<int*>(level + 2), kErrRowptr);
         newptr[v] = a;
-        if (v == n - 1) newptr[n] = b;
+        if (v == n - 1) newptr[n] = total;
         flag = b > a;
     }
-    unsigned long long bal = __ballot(flag);
-    if (lane_id() == 0 && (v >> 6) < ((n + 63) >> 6)) bitmap_next[v >> 6] = bal;
+    const unsigned long long bal = __ballot(flag);
+    if (lane == 0) {
+        const bool in = v < n;
+        if (in) bitmap_next[v >> 6] = bal;
+        const unsigned long long cur = in ? bitmap_cur[v >> 6] : 0ull;
+        wave_cnt[wave] = __popcll(bal);
+        wave_rel[wave] = ((cur & ~bal) ? 1 : 0) | (cur != bal ? 2 : 0);
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        int cnt = 0, rel = 0;
+#pragma unroll
+        for (int w = 0; w < kBlock / 64; ++w) {
+            cnt += wave_cnt[w];
+            rel |= wave_rel[w];
+        }
+        row_count[blockIdx.x] = cnt;
+        if (rel & 1) level[3] = 1;  // (plain stores: every writer stores the same value)
+        if (rel & 2) level[4] = 1;
+    }
+}
+
+__device__ __forceinline__ int length_class(int len) { return len <= 1 ? 0 : 32 - __clz(len - 1); }
+
+// Adds the rows of a wavefront (len > 0 where `row`) to the workgroup's histogram: one count per
+// distinct class among its 64 rows.
+__device__ __forceinline__ void add_lengths(int* __restrict__ h, bool row, int len) {
+    const int cls = row ? length_class(len) : -1;
+    unsigned long long todo = __ballot(cls >= 0);
+    while (todo) {
+        const int leader = __ffsll((long long)todo) - 1;
+        const unsigned long long same = __ballot(cls == __shfl(cls, leader));
+        if (lane_id() == leader) atomicAdd(&h[cls], __popcll(same));
+        todo &= ~same;
+    }
+}
+
+// Ascending ids of N^{k+1}, compact row pointer and row-length statistics (EPP_NCLASS counts, then
+// the longest row); a workgroup takes 256 vertices at a time.
+__global__ __launch_bounds__(kBlock) void k_rows_compact(const unsigned long long* __restrict__ bitmap, int64_t n,
+                                                         const int* __restrict__ row_base, const int* __restrict__ newptr,
+                                                         int32_t* __restrict__ ids, int32_t* __restrict__ ptr_out,
+                                                         int64_t n_set, int total_nnz,
+                                                         unsigned long long* __restrict__ stats) {
+    __shared__ int h[EPP_NCLASS];
+    __shared__ int mx;
+    const int lane = lane_id(), wave = threadIdx.x >> 6;
+    if (threadIdx.x < EPP_NCLASS) h[threadIdx.x] = 0;
+    if (threadIdx.x == 0) mx = 0;
+    __syncthreads();
+    int my_max = 0;
+    const int64_t tiles = (n + kBlock - 1) / kBlock, n_words = (n + 63) >> 6;
+    for (int64_t t = blockIdx.x; t < tiles; t += gridDim.x) {
+        int at = row_base[t];
+        unsigned long long m = 0ull;
+#pragma unroll
+        for (int w = 0; w < kBlock / 64; ++w) {
+            const unsigned long long x = t * 4 + w < n_words ? bitmap[t * 4 + w] : 0ull;
+            if (w < wave) at += __popcll(x);
+            if (w == wave) m = x;
+        }
+        const int64_t v = t * kBlock + threadIdx.x;
+        const bool member = (m >> lane) & 1ull;
+        int len = 0;
+        if (member) {
+            const int r = at + __popcll(m & low_mask(lane)), p = newptr[v];
+            len = newptr[v + 1] - p;
+            ids[r] = (int32_t)v;
+            ptr_out[r] = p;
+            my_max = max(my_max, len);
+        }
+        add_lengths(h, member, len);
+    }
+    if (my_max) atomicMax(&mx, my_max);
+    __syncthreads();
+    if (threadIdx.x < EPP_NCLASS && h[threadIdx.x]) atomicAdd(&stats[threadIdx.x], (unsigned long long)h[threadIdx.x]);
+    if (threadIdx.x == 0 && mx) atomicMax(reinterpret_cast<int*>(stats + EPP_NCLASS), mx);
+    if (blockIdx.x == 0 && threadIdx.x == 0) ptr_out[n_set] = total_nnz;
 }
 
 __global__ __launch_bounds__(kBlock) void k_bitmap_count(const unsigned long long* __restrict__ bitmap, int64_t n_words,
                                                          int* __restrict__ tile_count) {
     int64_t w = (int64_t)blockIdx.x * kWordsPerTile + threadIdx.x;
-    int c = w < n_words ? __popcll(bitmap[w]) : 0;
+    int c = threadIdx.x < kWordsPerTile && w < n_words ? __popcll(bitmap[w]) : 0;
     int total;
     (void)block_exclusive_scan(c, &total);
     if (threadIdx.x == 0) tile_count[blockIdx.x] = total;
@@ -286,9 +454,10 @@ __global__ __launch_bounds__(kBlock) void k_bitmap_compact(const unsigned long l
                                                            int total_nnz) {
     __shared__ int wbase[kWordsPerTile];
     int64_t w = (int64_t)blockIdx.x * kWordsPerTile + threadIdx.x;
-    int c = w < n_words ? __popcll(bitmap[w]) : 0;
+    int c = threadIdx.x < kWordsPerTile && w < n_words ? __popcll(bitmap[w]) : 0;
     int total;
-    wbase[threadIdx.x] = block_exclusive_scan(c, &total);
+    const int before = block_exclusive_scan(c, &total);
+    if (threadIdx.x < kWordsPerTile) wbase[threadIdx.x] = before;
     __syncthreads();
     const int wave = threadIdx.x >> 6, lane = lane_id();
     const int tb = tile_base[blockIdx.x];
@@ -306,8 +475,6 @@ __global__ __launch_bounds__(kBlock) void k_bitmap_compact(const unsigned long l
     if (ptr_out && blockIdx.x == 0 && threadIdx.x == 0) ptr_out[n_set] = total_nnz;
 }
 
-__device__ __forceinline__ int length_class(int len) { return len <= 1 ? 0 : 32 - __clz(len - 1); }
-
 // Row-length histogram by class and the maximal length.  Grid-stride; a wavefront adds one
 // count per distinct class among its 64 rows (ballots), a workgroup 33 global atomics in all.
 __global__ __launch_bounds__(kBlock) void k_len_hist(const int32_t* __restrict__ rowptr, int64_t n_rows,
@@ -323,19 +490,9 @@ __global__ __launch_bounds__(kBlock) void k_len_hist(const int32_t* __restrict__
     // whole wavefronts enter every iteration, so the ballots below see all 64 lanes
     for (int64_t base = (int64_t)blockIdx.x * kBlock + (threadIdx.x & ~63); base < n_rows; base += span) {
         const int64_t r = base + lane;
-        int cls = -1;
-        if (r < n_rows) {
-            const int len = rowptr[r + 1] - rowptr[r];
-            my_max = max(my_max, len);
-            cls = length_class(len);
-        }
-        unsigned long long todo = __ballot(cls >= 0);
-        while (todo) {
-            const int c = __shfl(cls, __ffsll((long long)todo) - 1);
-            const unsigned long long same = __ballot(cls == c);
-            if (lane == __ffsll((long long)same) - 1) atomicAdd(&h[c], __popcll(same));
-            todo &= ~same;
-        }
+        const int len = r < n_rows ? rowptr[r + 1] - rowptr[r] : 0;
+        my_max = max(my_max, len);
+        add_lengths(h, r < n_rows, len);
     }
     if (my_max) atomicMax(&mx, my_max);
     __syncthreads();
@@ -414,13 +571,14 @@ __global__ __launch_bounds__(kBlock) void k_iota(int32_t* __restrict__ out, int6
     if (i < n) out[i] = (int32_t)i;
 }
 
-// Flag the last entry of every (non-empty) row in bit 31 of its column id.
-__global__ __launch_bounds__(kBlock) void k_mark_row_ends(const int32_t* __restrict__ rowptr, int64_t n_rows,
+// Flag the last entry of every (non-empty) row in bit 31 of its column id.  (The bounds only matter
+// for imported arrays, which are checked in the same stream of work.)
+__global__ __launch_bounds__(kBlock) void k_mark_row_ends(const int32_t* __restrict__ rowptr, int64_t n_rows, int64_t nnz,
                                                           int2* __restrict__ cv) {
     int64_t r = (int64_t)blockIdx.x * kBlock + threadIdx.x;
     if (r >= n_rows) return;
-    int32_t end = rowptr[r + 1];
-    if (end > rowptr[r]) cv[end - 1].x |= (int)0x80000000u;
+    const int32_t end = rowptr[r + 1];
+    if (end > rowptr[r] && end > 0 && end <= nnz) cv[end - 1].x |= kEntRowEnd;
 }
 
 // Bitmap of the vertices with a non-empty (invert = 0) or empty (invert = 1) list.
@@ -433,52 +591,26 @@ __global__ __launch_bounds__(kBlock) void k_nonempty_bitmap(const int32_t* __res
     if (lane_id() == 0 && (v >> 6) < ((n + 63) >> 6)) bitmap[v >> 6] = bal;
 }
 
-// flag |= 1 if the two bitmaps differ anywhere.
-__global__ __launch_bounds__(kBlock) void k_bitmap_differs(const unsigned long long* __restrict__ a,
-                                                           const unsigned long long* __restrict__ b, int64_t n_words,
-                                                           int* __restrict__ flag) {
-    int64_t w = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (w < n_words && a[w] != b[w]) atomicOr(flag, 1);
-}
-
-// flag |= 1 if some member of set a is not in set b.
-__global__ __launch_bounds__(kBlock) void k_bitmap_not_subset(const unsigned long long* __restrict__ a,
-                                                              const unsigned long long* __restrict__ b, int64_t n_words,
-                                                              int* __restrict__ flag) {
-    int64_t w = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (w < n_words && (a[w] & ~b[w]) != 0ull) atomicOr(flag, 1);
-}
-
 inline unsigned grid_for(int64_t n, int per_block) { return (unsigned)((n + per_block - 1) / per_block); }
 
-// out = exclusive scan of in[0 .. n), *total = sum.  `tmp` holds 2 * ceil(n / kScanChunk) ints.
-inline size_t scan_tmp_bytes(int64_t n) { return (size_t)(2 * ((n + kScanChunk - 1) / kScanChunk) + 2) * sizeof(int); }
-void scan_counts(const int* in, int* out, int64_t n, long long* total, int* tmp, hipStream_t s) {
+// out = exclusive scan of in[0 .. n), *total = sum.  `tmp` holds two arrays of a number per chunk.
+inline int64_t scan_tmp_stride(int64_t n) { return ((n + kScanChunk - 1) / kScanChunk + 3) & ~(int64_t)3; }
+inline size_t scan_tmp_bytes(int64_t n) { return (size_t)(2 * scan_tmp_stride(n)) * sizeof(int); }
+// `level`, `host`: see k_scan_counts.
+void scan_counts(const int* in, int* out, int64_t n, long long* total, int* tmp, hipStream_t s,
+                 const long long* level = nullptr, long long* host = nullptr) {
     const int64_t chunks = (n + kScanChunk - 1) / kScanChunk;
-    if (chunks <= 2) {
-        hipLaunchKernelGGL(k_scan_counts, dim3(1), dim3(1024), 0, s, in, out, n, total);
+    if (chunks <= 4) {
+        hipLaunchKernelGGL(k_scan_counts, dim3(1), dim3(1024), 0, s, in, out, n, total, (const long long*)level, host);
         return;
     }
     int* chunk_sum = tmp;
-    int* chunk_base = tmp + chunks;
+    int* chunk_base = tmp + scan_tmp_stride(n);
     hipLaunchKernelGGL(k_scan_chunks, dim3((unsigned)chunks), dim3(1024), 0, s, in, out, n, chunk_sum);
-    hipLaunchKernelGGL(k_scan_counts, dim3(1), dim3(1024), 0, s, (const int*)chunk_sum, chunk_base, chunks, total);
+    hipLaunchKernelGGL(k_scan_counts, dim3(1), dim3(1024), 0, s, (const int*)chunk_sum, chunk_base, chunks, total,
+                       level, host);
     hipLaunchKernelGGL(k_scan_add_offsets, dim3((unsigned)chunks), dim3(1024), 0, s, out, n, (const int*)chunk_base);
 }
-
-// Pinned host staging for the few scalars read back per level.
-struct HostScalars {
-    long long* p = nullptr;
-    int init(size_t count = 64) {
-        if (hipHostMalloc((void**)&p, count * sizeof(long long), hipHostMallocDefault) != hipSuccess) {
-            (void)hipGetLastError();
-            epp_set_error("pinned host allocation failed");
-            return EPP_ERR_ALLOC;
-        }
-        return EPP_OK;
-    }
-    ~HostScalars() { if (p) (void)hipHostFree(p); }
-};
 
 int validate_csr(const epp_csr_t* g) {
     if (!g) { epp_set_error("graph is NULL"); return EPP_ERR_INVALID_ARG; }
@@ -497,7 +629,7 @@ int validate_csr(const epp_csr_t* g) {
 
 // Ascending ids of a bitmap (and optionally the compact row pointer).  Returns the count.
 int compact_bitmap(const DevBuf& bitmap, int64_t n, const int* newptr, int total_nnz, DevBuf* ids, DevBuf* ptr_out,
-                   int64_t* count, DevBuf& tile_cnt, DevBuf& tile_base, DevBuf& dev_total, HostScalars& hs,
+                   int64_t* count, DevBuf& tile_cnt, DevBuf& tile_base, DevBuf& dev_total, PinnedWords& hs,
                    const epp_alloc_t* al, hipStream_t s) {
     const int64_t n_words = (n + 63) / 64;
     const unsigned tiles = grid_for(n_words, kWordsPerTile);
@@ -506,7 +638,7 @@ int compact_bitmap(const DevBuf& bitmap, int64_t n, const int* newptr, int total
         hipLaunchKernelGGL(k_bitmap_count, dim3(tiles), dim3(kBlock), 0, s, bitmap.as<unsigned long long>(), n_words,
                            tile_cnt.as<int>());
         hipLaunchKernelGGL(k_scan_counts, dim3(1), dim3(1024), 0, s, tile_cnt.as<int>(), tile_base.as<int>(),
-                           (int64_t)tiles, dev_total.as<long long>());
+                           (int64_t)tiles, dev_total.as<long long>(), (const long long*)nullptr, (long long*)nullptr);
         EPP_HIP_TRY(hipMemcpyAsync(hs.p, dev_total.p, sizeof(long long), hipMemcpyDeviceToHost, s));
         EPP_HIP_TRY(hipStreamSynchronize(s));
         R = hs.p[0];
@@ -526,26 +658,100 @@ int compact_bitmap(const DevBuf& bitmap, int64_t n, const int* newptr, int total
     return EPP_OK;
 }
 
-// Checks of imported path arrays: bit 0 structure (ids not ascending, pointer decreasing, empty
-// row, wrong end points), bit 1 an id outside [0, n).  Also sets the bitmap of the row set.
-__global__ __launch_bounds__(kBlock) void k_check_rows(const int32_t* __restrict__ row_ids,
-                                                       const int32_t* __restrict__ rowptr, int64_t n_rows, int64_t nnz,
-                                                       int64_t n, unsigned int* __restrict__ bitmap32,
-                                                       int* __restrict__ err) {
-    const int64_t r = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (r == 0 && (rowptr[0] != 0 || rowptr[n_rows] != nnz)) atomicOr(err, 1);
-    if (r >= n_rows) return;
-    const int32_t v = row_ids[r];
-    if (v < 0 || v >= n) { atomicOr(err, 2); return; }
-    if (r > 0 && row_ids[r - 1] >= v) atomicOr(err, 1);
-    if (rowptr[r + 1] <= rowptr[r]) atomicOr(err, 1);
-    atomicOr(&bitmap32[v >> 5], 1u << (v & 31));
+// keep-mask of one level: windows of the bitmap in LDS, or lookups through L2 (see k_edge_mask).
+void launch_edge_mask(const epp_csr_t* g, int64_t n_seg, unsigned n_tiles, const unsigned int* bitmap,
+                      const unsigned long long* known, bool all, bool check, unsigned long long* mask, uint16_t* seg_off,
+                      int* tile_count, int* err, hipStream_t s) {
+    constexpr int kSmall = 8192, kLarge = 39936;  // words: 32 KB (two workgroups per CU), 156 KB
+    MaskArgs a;
+    a.col = g->col;
+    a.nnz = g->nnz;
+    a.n_seg = n_seg;
+    a.n_tiles = n_tiles;
+    a.n = (int)g->n;
+    a.bitmap = bitmap;
+    a.known = known;
+    a.all = all;
+    a.mask = mask;
+    a.seg_off = seg_off;
+    a.tile_count = tile_count;
+    a.err = err;
+    const int64_t window = g->n <= kSmall * 32 ? kSmall * 32 : kLarge * 32;
+    const int64_t passes = (g->n + window - 1) / window;
+    if (all || passes > 3) {
+        a.first_id = 0;
+        a.n_ids = a.n;
+        a.check = check;
+        a.count = 1;
+        hipLaunchKernelGGL((k_edge_mask<kBlock, 0>), dim3(std::min(grid_for(n_tiles, kBlock / 64), 16384u)), dim3(kBlock), 0, s, a);
+        return;
+    }
+    for (int64_t w = 0; w < passes; ++w) {
+        a.first_id = (int)(w * window);
+        a.n_ids = (int)std::min(window, g->n - w * window);
+        a.check = check && w == 0;
+        a.count = w == passes - 1;
+        if (w > 0) a.known = mask;
+        if (window == kSmall * 32)
+            hipLaunchKernelGGL((k_edge_mask<1024, kSmall>), dim3(std::min(grid_for(n_tiles, 16), 512u)), dim3(1024), 0, s, a);
+        else
+            hipLaunchKernelGGL((k_edge_mask<1024, kLarge>), dim3(std::min(grid_for(n_tiles, 16), 256u)), dim3(1024), 0, s, a);
+    }
 }
 
-__global__ __launch_bounds__(kBlock) void k_check_cols(const int32_t* __restrict__ col, int64_t nnz, int64_t n,
-                                                       int* __restrict__ err) {
-    const int64_t e = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (e < nnz && (col[e] < 0 || col[e] >= n)) atomicOr(err, 2);
+// Row arrays of an imported path: copied, checked (an error bit if ids do not ascend, the pointer
+// decreases, a row is empty or the end points are wrong; another for an id outside [0, n)), counted
+// into the row-length statistics, and set in the bitmap of the row set.  Ids ascend, so neighbouring
+// lanes share bitmap words: the bits of a word are gathered by a segmented scan across the
+// wavefront and set by its last lane, one atomic per word instead of one per row.
+__global__ __launch_bounds__(kBlock) void k_import_rows(const int32_t* __restrict__ row_ids,
+                                                        const int32_t* __restrict__ rowptr, int64_t n_rows, int64_t nnz,
+                                                        int64_t n, int32_t* __restrict__ ids_out,
+                                                        int32_t* __restrict__ ptr_out, unsigned int* __restrict__ bitmap32,
+                                                        unsigned long long* __restrict__ stats, int* __restrict__ err) {
+    __shared__ int h[EPP_NCLASS];
+    __shared__ int mx;
+    if (threadIdx.x < EPP_NCLASS) h[threadIdx.x] = 0;
+    if (threadIdx.x == 0) mx = 0;
+    __syncthreads();
+    const int lane = lane_id();
+    int my_max = 0, bad = 0;
+    const int64_t span = (int64_t)gridDim.x * kBlock;
+    // (one index past the rows, for the end of the pointer; whole wavefronts enter every iteration)
+    for (int64_t base = (int64_t)blockIdx.x * kBlock + (threadIdx.x & ~63); base <= n_rows; base += span) {
+        const int64_t r = base + lane;
+        const bool row = r < n_rows;
+        const int p = r <= n_rows ? rowptr[r] : 0;
+        const int v = row ? row_ids[r] : -1;
+        const int prev = row && r > 0 ? row_ids[r - 1] : -1;
+        const int len = row ? rowptr[r + 1] - p : 0;
+        if (r <= n_rows) ptr_out[r] = p;
+        if ((r == 0 && p != 0) || (r == n_rows && p != nnz)) bad |= kErrRowptr;
+        bool in = false;
+        if (row) {
+            ids_out[r] = v;
+            in = v >= 0 && v < n;
+            if (!in) bad |= kErrCol;
+            if (prev >= v || len <= 0) bad |= kErrRowptr;
+            my_max = max(my_max, len);
+        }
+        const int word = in ? v >> 5 : -1;
+        unsigned int b = in ? 1u << (v & 31) : 0u;
+#pragma unroll
+        for (int d = 1; d < 64; d <<= 1) {
+            const unsigned int other = __shfl_up(b, d, 64);
+            const int other_word = __shfl_up(word, d, 64);
+            if (lane >= d && other_word == word) b |= other;
+        }
+        const int next_word = __shfl_down(word, 1, 64);
+        if (in && (lane == 63 || next_word != word)) atomicOr(&bitmap32[word], b);
+        add_lengths(h, row && len > 0, len);
+    }
+    if (bad) atomicOr(err, bad);
+    if (my_max) atomicMax(&mx, my_max);
+    __syncthreads();
+    if (threadIdx.x < EPP_NCLASS && h[threadIdx.x]) atomicAdd(&stats[threadIdx.x], (unsigned long long)h[threadIdx.x]);
+    if (threadIdx.x == 0 && mx) atomicMax(reinterpret_cast<int*>(stats + EPP_NCLASS), mx);
 }
 
 // Message and code for the error bits raised by the input checks (bit 0 row pointer, bit 1 ids).
@@ -562,6 +768,43 @@ int input_error(int bits, int64_t n) {
 
 }  // namespace
 
+// Pinned blocks of every host thread that is inside a call: a list of idle ones, so that calls do
+// not each pay for a pinned allocation and its release (together 0.1 ms).  At most kIdlePinned stay
+// in the list; the rest goes back to the runtime.
+namespace {
+constexpr size_t kPinnedBlock = 4096, kIdlePinned = 16;
+std::mutex g_pinned_lock;
+long long* g_pinned_idle[kIdlePinned];
+size_t g_pinned_count = 0;
+}  // namespace
+
+int PinnedWords::get(size_t need) {
+    if (need <= kPinnedBlock) {
+        std::lock_guard<std::mutex> hold(g_pinned_lock);
+        if (g_pinned_count) p = g_pinned_idle[--g_pinned_count];
+    }
+    count = std::max(need, kPinnedBlock);
+    if (!p && hipHostMalloc((void**)&p, count * sizeof(long long), hipHostMallocPortable) != hipSuccess) {
+        (void)hipGetLastError();
+        p = nullptr;
+        epp_set_error("pinned host allocation failed");
+        return EPP_ERR_ALLOC;
+    }
+    return EPP_OK;
+}
+
+PinnedWords::~PinnedWords() {
+    if (!p) return;
+    if (count == kPinnedBlock) {
+        std::lock_guard<std::mutex> hold(g_pinned_lock);
+        if (g_pinned_count < kIdlePinned) {
+            g_pinned_idle[g_pinned_count++] = p;
+            return;
+        }
+    }
+    (void)hipHostFree(p);
+}
+
 size_t epp_scan_tmp_bytes(int64_t n) { return scan_tmp_bytes(n); }
 void epp_scan_exclusive(const int* in, int* out, int64_t n, long long* total, int* tmp, hipStream_t s) {
     scan_counts(in, out, n, total, tmp, s);
@@ -574,11 +817,9 @@ void epp_path_set_stats(epp_path* p, const unsigned long long* host) {
     p->max_len = mx;
 }
 
-int epp_path_finish(epp_path* p, hipStream_t s, void* stats_scratch, unsigned long long* host_later,
-                    bool mark_row_ends) {
+int epp_path_finish(epp_path* p, hipStream_t s) {
     DevBuf stats;
-    if (stats_scratch) stats.view(stats_scratch, (EPP_NCLASS + 1) * sizeof(unsigned long long));
-    else EPP_TRY(stats.alloc((EPP_NCLASS + 1) * sizeof(unsigned long long), epp_alloc_of(p)));
+    EPP_TRY(stats.alloc((EPP_NCLASS + 1) * sizeof(unsigned long long), epp_alloc_of(p)));
     EPP_HIP_TRY(hipMemsetAsync(stats.p, 0, stats.bytes, s));
     if (p->n_rows > 0) {
         // canonical rows: the all-active graph counts its empty rows too
@@ -588,19 +829,13 @@ int epp_path_finish(epp_path* p, hipStream_t s, void* stats_scratch, unsigned lo
                            reinterpret_cast<int*>(stats.as<unsigned long long>() + EPP_NCLASS));
         EPP_HIP_TRY(hipGetLastError());
     }
-    if (host_later) {
-        // pinned destination: the caller reads it (epp_path_set_stats) after its own synchronisation
-        EPP_HIP_TRY(hipMemcpyAsync(host_later, stats.p, (EPP_NCLASS + 1) * sizeof(unsigned long long),
-                                   hipMemcpyDeviceToHost, s));
-    } else {
-        unsigned long long host[EPP_NCLASS + 1];
-        EPP_HIP_TRY(hipMemcpyAsync(host, stats.p, sizeof(host), hipMemcpyDeviceToHost, s));
-        EPP_HIP_TRY(hipStreamSynchronize(s));
-        epp_path_set_stats(p, host);
-    }
-    if (mark_row_ends && p->n_stream_rows > 0) {
+    unsigned long long host[EPP_NCLASS + 1];
+    EPP_HIP_TRY(hipMemcpyAsync(host, stats.p, sizeof(host), hipMemcpyDeviceToHost, s));
+    EPP_HIP_TRY(hipStreamSynchronize(s));
+    epp_path_set_stats(p, host);
+    if (p->n_stream_rows > 0) {
         hipLaunchKernelGGL(k_mark_row_ends, dim3(grid_for(p->n_stream_rows, kBlock)), dim3(kBlock), 0, s,
-                           p->rowptr.as<int32_t>(), p->n_stream_rows, p->cv.as<int2>());
+                           p->rowptr.as<int32_t>(), p->n_stream_rows, p->nnz, p->cv.as<int2>());
         EPP_HIP_TRY(hipGetLastError());
     }
     return EPP_OK;  // the callers synchronise once, before they return the handle
@@ -624,18 +859,27 @@ extern "C" int epp_prepare(const epp_csr_t* g, const int32_t* train_ids, int64_t
         if (!(e && e[0] == '0')) return epp_prepare_small(g, train_ids, n_train, L, alloc, s, out);
     }
     const int64_t n = g->n, nnz = g->nnz;
+    if (n == 0 && nnz > 0) return input_error(kErrCol, n);
     const int64_t n_words = (n + 63) / 64;
     const int64_t n_seg = (nnz + 63) / 64;
     const unsigned edge_tiles = grid_for(n_seg, kSegsPerTile);
     const unsigned word_tiles = grid_for(n_words, kWordsPerTile);
+    const unsigned row_tiles = grid_for(n, kBlock);
 
-    // pinned words read back from the device: [0] kept entries, [1] |N^{k+1}| (also the scratch of
-    // compact_bitmap), then EPP_NCLASS + 1 statistics words per level
+    // pinned words: the numbers of the level being built, then every level's statistics
     constexpr int kStatWords = EPP_NCLASS + 1;
-    HostScalars hs;
-    EPP_TRY(hs.init(8 + (size_t)L * kStatWords));
+    PinnedWords hs;
+    EPP_TRY(hs.get(kLevelWords + (size_t)L * kStatWords));
     epp_paths* P = new epp_paths();
-    struct Guard { epp_paths* p; ~Guard() { delete p; } } guard{P};
+    struct Guard {  // (on an error: nothing may still be writing to what is given back)
+        epp_paths* p;
+        hipStream_t s;
+        ~Guard() {
+            if (!p) return;
+            (void)hipStreamSynchronize(s);
+            delete p;
+        }
+    } guard{P, s};
     P->L = L;
     P->n = n;
     if (alloc && alloc->alloc && alloc->free) P->alloc = *alloc;
@@ -643,59 +887,57 @@ extern "C" int epp_prepare(const epp_csr_t* g, const int32_t* train_ids, int64_t
     P->bitmaps.resize(L + 1);
     P->set_size.assign(L + 1, 0);
     P->path.assign(L, nullptr);
-    for (int k = 0; k <= L; ++k) {
-        EPP_TRY(P->bitmaps[k].alloc((size_t)n_words * 8, al));
-        EPP_HIP_TRY(hipMemsetAsync(P->bitmaps[k].p, 0, P->bitmaps[k].bytes, s));
-    }
+    // bitmaps of all sets and the ids of N^0 (at most one per training id) in one allocation
+    const size_t bm_bytes = (size_t)n_words * 8;
+    const size_t set0_bytes = (size_t)std::min(n_train, n) * 4;
+    EPP_TRY(P->store.alloc((size_t)(L + 1) * DevArena::rounded(bm_bytes) + DevArena::rounded(set0_bytes), al));
+    for (int k = 0; k <= L; ++k) P->bitmaps[k].view(P->store.as<char>() + (size_t)k * DevArena::rounded(bm_bytes), bm_bytes);
+    void* set0 = P->store.as<char>() + (size_t)(L + 1) * DevArena::rounded(bm_bytes);
+    EPP_HIP_TRY(hipMemsetAsync(P->bitmaps[0].p, 0, bm_bytes, s));  // (the others are written whole)
 
     // all temporaries of the construction come from one allocation
-    // (keep-mask and segment offsets twice: the entries of a level are extracted once the next
+    // (keep-mask and its counts twice: the entries of a level are extracted once the next
     // level has shown whether the two paths share them, so two levels' masks are alive at a time)
-    DevBuf mask[2], seg_base[2], tile_cnt, tile_base, scan_tmp, newptr, dev_total, err, stats;
-    const size_t max_tiles = std::max<size_t>(std::max(edge_tiles, word_tiles), 1);
-    const size_t stats_bytes = kStatWords * sizeof(unsigned long long);
+    DevBuf mask[2], seg_off[2], tile_base[2], tile_cnt, row_cnt, row_base, scan_tmp, newptr, levels;
+    const size_t cnt_bytes = (size_t)std::max(std::max(edge_tiles, word_tiles), 1u) * 4;
+    const size_t row_bytes = (size_t)std::max(row_tiles, 1u) * 4;
+    const size_t tmp_bytes = scan_tmp_bytes(std::max<int64_t>(edge_tiles, row_tiles));
+    const size_t level_bytes = (size_t)L * (kLevelWords + kStatWords) * 8;
     DevArena arena;
-    EPP_TRY(arena.reserve(2 * DevArena::rounded((size_t)n_seg * 8) + 2 * DevArena::rounded((size_t)n_seg * 4) +
-                          2 * DevArena::rounded(max_tiles * 4) + DevArena::rounded(scan_tmp_bytes(edge_tiles)) +
-                          DevArena::rounded((size_t)(n + 1) * 4) +
-                          2 * DevArena::rounded(32) + DevArena::rounded(stats_bytes), al));
+    EPP_TRY(arena.reserve(2 * (DevArena::rounded((size_t)n_seg * 8) + DevArena::rounded((size_t)n_seg * 2) +
+                               DevArena::rounded(cnt_bytes)) +
+                          DevArena::rounded(cnt_bytes) + 2 * DevArena::rounded(row_bytes) + DevArena::rounded(tmp_bytes) +
+                          DevArena::rounded((size_t)(n + 1) * 4) + DevArena::rounded(level_bytes), al));
     for (int i = 0; i < 2; ++i) {
         arena.take(&mask[i], (size_t)n_seg * 8);
-        arena.take(&seg_base[i], (size_t)n_seg * 4);
+        arena.take(&seg_off[i], (size_t)n_seg * 2);
+        arena.take(&tile_base[i], cnt_bytes);
     }
-    arena.take(&tile_cnt, max_tiles * 4);
-    arena.take(&tile_base, max_tiles * 4);
-    arena.take(&scan_tmp, scan_tmp_bytes(edge_tiles));
+    arena.take(&tile_cnt, cnt_bytes);
+    arena.take(&row_cnt, row_bytes);
+    arena.take(&row_base, row_bytes);
+    arena.take(&scan_tmp, tmp_bytes);
     arena.take(&newptr, (size_t)(n + 1) * 4);
-    // [0] kept entries, [1] rows of the level, [2] input error bits, [3] "N^{k-1} is not inside N^k"
-    arena.take(&dev_total, 4 * sizeof(long long));
-    arena.take(&err, sizeof(int));
-    arena.take(&stats, stats_bytes);
-    EPP_HIP_TRY(hipMemsetAsync(err.p, 0, sizeof(int), s));
-    EPP_HIP_TRY(hipMemsetAsync(newptr.p, 0, newptr.bytes, s));
+    arena.take(&levels, level_bytes);
+    long long* const d_levels = levels.as<long long>();
+    unsigned long long* const d_stats = reinterpret_cast<unsigned long long*>(d_levels + (size_t)L * kLevelWords);
+    EPP_HIP_TRY(hipMemsetAsync(levels.p, 0, level_bytes, s));
 
-    // N^0 = V_t (Property 1)
+    // N^0 = V_t (Property 1) and its ascending ids (the other sets are the row ids of the paths)
     if (n_train > 0) {
         hipLaunchKernelGGL(k_mark_training, dim3(grid_for(n_train, kBlock)), dim3(kBlock), 0, s, train_ids, n_train, n,
-                           P->bitmaps[0].as<unsigned int>(), err.as<int>());
-        EPP_HIP_TRY(hipGetLastError());
-        int herr = 0;
-        EPP_HIP_TRY(hipMemcpyAsync(&herr, err.p, sizeof(int), hipMemcpyDeviceToHost, s));
-        EPP_HIP_TRY(hipStreamSynchronize(s));
-        if (herr) {
-            epp_set_error("training id outside [0, %lld)", (long long)n);
-            return EPP_ERR_OUT_OF_RANGE_ID;
+                           P->bitmaps[0].as<unsigned int>(), reinterpret_cast<int*>(d_levels + 2));
+        if (n > 0) {
+            hipLaunchKernelGGL(k_bitmap_count, dim3(word_tiles), dim3(kBlock), 0, s, P->bitmaps[0].as<unsigned long long>(),
+                               n_words, tile_cnt.as<int>());
+            scan_counts(tile_cnt.as<int>(), tile_base[0].as<int>(), word_tiles, d_levels + 5, scan_tmp.as<int>(), s);
+            hipLaunchKernelGGL(k_bitmap_compact, dim3(word_tiles), dim3(kBlock), 0, s,
+                               P->bitmaps[0].as<unsigned long long>(), n_words, tile_base[0].as<int>(), (const int*)nullptr,
+                               static_cast<int32_t*>(set0), (int32_t*)nullptr, (int64_t)0, 0);
         }
+        EPP_HIP_TRY(hipGetLastError());
     }
-    // ascending ids of N^0 (the other sets are the row ids of the paths)
-    EPP_TRY(compact_bitmap(P->bitmaps[0], n, nullptr, 0, &P->set0_ids, nullptr, &P->set_size[0], tile_cnt, tile_base,
-                           dev_total, hs, al, s));
 
-    // One level: everything that only needs the two counts (kept entries, rows) on the device is
-    // enqueued first, the host waits once for both, allocates the level's arrays, and enqueues
-    // the passes that fill them.  The row-length statistics come back through pinned memory and
-    // are read after the last level.
-    //
     // Shared entries: the path of a level runs on the arrays of the next level's path if nearly
     // all of that path's entries are its own too (the extra entries are skipped one by one at
     // run time, so the inner layer pays for them; EPP_TUNE_SHARE_PCT, default 95, 0: never).
@@ -705,26 +947,28 @@ extern "C" int epp_prepare(const epp_csr_t* g, const int32_t* train_ids, int64_t
     // keeps its own arrays.
     std::vector<epp_path*> built;  // in level order, for the statistics
     struct { epp_path* p = nullptr; int slot = 0; } pending;  // path whose entries are not extracted yet
+    auto kept_of = [&](int slot) {
+        return Kept{mask[slot].as<unsigned long long>(), seg_off[slot].as<uint16_t>(), tile_base[slot].as<int>()};
+    };
     auto extract = [&](epp_path* q, int slot, bool marks_inner) -> int {
         // the entries in an allocation of their own (it can be given back once every prepared width
         // runs on a reconstructed copy)
         EPP_TRY(q->cv.alloc((size_t)q->nnz * sizeof(int2), al));
         if (marks_inner) EPP_TRY(q->inner_pos.alloc((size_t)((q->nnz + 63) / 64) * 4, al));
         if (edge_tiles) {
-            hipLaunchKernelGGL(k_edge_extract, dim3(edge_tiles), dim3(kBlock), 0, s, g->col, g->val, n_seg,
-                               mask[slot].as<unsigned long long>(),
-                               marks_inner ? mask[slot ^ 1].as<unsigned long long>() : (const unsigned long long*)nullptr,
-                               seg_base[slot].as<int>(), seg_base[slot ^ 1].as<int>(), q->inner_pos.as<int>(),
+            hipLaunchKernelGGL(k_edge_extract, dim3(edge_tiles), dim3(kBlock), 0, s, g->col, g->val, n_seg, kept_of(slot),
+                               marks_inner ? kept_of(slot ^ 1) : Kept{nullptr, nullptr, nullptr}, q->inner_pos.as<int>(),
                                q->cv.as<int2>());
         }
         if (q->n_stream_rows > 0) {
             hipLaunchKernelGGL(k_mark_row_ends, dim3(grid_for(q->n_stream_rows, kBlock)), dim3(kBlock), 0, s,
-                               q->rowptr.as<int32_t>(), q->n_stream_rows, q->cv.as<int2>());
+                               q->rowptr.as<int32_t>(), q->n_stream_rows, q->nnz, q->cv.as<int2>());
         }
         EPP_HIP_TRY(hipGetLastError());
         return EPP_OK;
     };
     const long long share_pct = env_share_pct();
+    bool nested = false;  // N^{k-1} lies in N^k
     for (int k = 0; k < L; ++k) {
         const int l = L - 1 - k;  // rows N^{k+1} = N^{L-l}, sources N^k = N^{L-l-1}
         const int slot = k & 1;
@@ -734,45 +978,38 @@ extern "C" int epp_prepare(const epp_csr_t* g, const int32_t* train_ids, int64_t
         p->n = n;
         p->alloc = P->alloc;
         p->pool = &P->pool;
-        p->n_src = P->set_size[k];
-        long long* d_total = dev_total.as<long long>();
-        int* d_err = reinterpret_cast<int*>(d_total + 2);
-        int* d_not_subset = reinterpret_cast<int*>(d_total + 3);
-        EPP_HIP_TRY(hipMemsetAsync(d_total, 0, 4 * sizeof(long long), s));
+        long long* d_level = d_levels + (size_t)k * kLevelWords;
         if (edge_tiles) {
-            // from the second level on the mask of the level before is reused where N^{k-1} lies in N^k
-            if (k > 0) {
-                hipLaunchKernelGGL(k_bitmap_not_subset, dim3(grid_for(n_words, kBlock)), dim3(kBlock), 0, s,
-                                   P->bitmaps[k - 1].as<unsigned long long>(), P->bitmaps[k].as<unsigned long long>(),
-                                   n_words, d_not_subset);
-            }
-            hipLaunchKernelGGL(k_edge_mask, dim3(edge_tiles), dim3(kBlock), 0, s, g->col, nnz, n_seg, n,
-                               P->bitmaps[k].as<unsigned int>(),
-                               k > 0 ? mask[slot ^ 1].as<unsigned long long>() : (const unsigned long long*)nullptr,
-                               (const int*)d_not_subset, mask[slot].as<unsigned long long>(), tile_cnt.as<int>(), d_err);
-            scan_counts(tile_cnt.as<int>(), tile_base.as<int>(), (int64_t)edge_tiles, d_total, scan_tmp.as<int>(), s);
-            hipLaunchKernelGGL(k_seg_base, dim3(edge_tiles), dim3(64), 0, s, mask[slot].as<unsigned long long>(), n_seg,
-                               tile_base.as<int>(), seg_base[slot].as<int>());
-            EPP_HIP_TRY(hipGetLastError());
+            const bool all = k > 0 && P->set_size[k] == n;
+            launch_edge_mask(g, n_seg, edge_tiles, P->bitmaps[k].as<unsigned int>(),
+                             k > 0 && nested ? mask[slot ^ 1].as<unsigned long long>() : nullptr, all, k == 0,
+                             mask[slot].as<unsigned long long>(), seg_off[slot].as<uint16_t>(), tile_cnt.as<int>(),
+                             reinterpret_cast<int*>(d_level + 2), s);
+            scan_counts(tile_cnt.as<int>(), tile_base[slot].as<int>(), (int64_t)edge_tiles, d_level, scan_tmp.as<int>(), s);
         }
         if (n > 0) {
-            hipLaunchKernelGGL(k_row_flags, dim3(grid_for(n, kBlock)), dim3(kBlock), 0, s, g->rowptr, n, nnz,
-                               mask[slot].as<unsigned long long>(), seg_base[slot].as<int>(), (const long long*)d_total,
-                               newptr.as<int>(), P->bitmaps[k + 1].as<unsigned long long>(), d_err);
-            // rows of the level: set bits of the new bitmap, counted per tile of words and scanned
-            // (the edge-tile offsets are no longer needed: seg_base holds them)
-            hipLaunchKernelGGL(k_bitmap_count, dim3(word_tiles), dim3(kBlock), 0, s,
-                               P->bitmaps[k + 1].as<unsigned long long>(), n_words, tile_cnt.as<int>());
-            hipLaunchKernelGGL(k_scan_counts, dim3(1), dim3(1024), 0, s, tile_cnt.as<int>(), tile_base.as<int>(),
-                               (int64_t)word_tiles, d_total + 1);
-            EPP_HIP_TRY(hipGetLastError());
+            hipLaunchKernelGGL(k_row_flags, dim3(row_tiles), dim3(kBlock), 0, s, g->rowptr, n, nnz, kept_of(slot), d_level,
+                               newptr.as<int>(), P->bitmaps[k].as<unsigned long long>(),
+                               P->bitmaps[k + 1].as<unsigned long long>(), row_cnt.as<int>());
+            scan_counts(row_cnt.as<int>(), row_base.as<int>(), (int64_t)row_tiles, d_level + 1, scan_tmp.as<int>(), s, d_level,
+                        hs.p);
+        } else {
+            EPP_HIP_TRY(hipMemcpyAsync(hs.p, d_level, kLevelWords * sizeof(long long), hipMemcpyDeviceToHost, s));
         }
-        EPP_HIP_TRY(hipMemcpyAsync(hs.p, d_total, 4 * sizeof(long long), hipMemcpyDeviceToHost, s));
+        EPP_HIP_TRY(hipGetLastError());
         EPP_HIP_TRY(hipStreamSynchronize(s));
+        if (hs.p[2] & kErrTrain) {
+            epp_set_error("training id outside [0, %lld)", (long long)n);
+            return EPP_ERR_OUT_OF_RANGE_ID;
+        }
         if (hs.p[2] != 0) return input_error((int)hs.p[2], n);
-        if (n == 0 && nnz > 0) return input_error(2, n);
+        if (k == 0) {
+            P->set_size[0] = hs.p[5];
+            P->set0_ids.view(set0, (size_t)hs.p[5] * 4);
+        }
         const long long kept = hs.p[0], R = hs.p[1];
-        const bool nested = (int)hs.p[3] == 0;
+        const bool next_nested = hs.p[3] == 0, fixed_point = hs.p[4] == 0;
+        p->n_src = P->set_size[k];
         p->nnz = kept;
         p->n_rows = R;
         p->n_stream_rows = R;  // every row of a path has at least one entry
@@ -784,15 +1021,14 @@ extern "C" int epp_prepare(const epp_csr_t* g, const int32_t* train_ids, int64_t
         p->row_ids.view(base, ids_bytes);
         p->rowptr.view(base + DevArena::rounded(ids_bytes), ptr_bytes);
         if (n > 0) {
-            hipLaunchKernelGGL(k_bitmap_compact, dim3(word_tiles), dim3(kBlock), 0, s,
-                               P->bitmaps[k + 1].as<unsigned long long>(), n_words, tile_base.as<int>(), newptr.as<int>(),
-                               p->row_ids.as<int32_t>(), p->rowptr.as<int32_t>(), (int64_t)R, (int)kept);
+            hipLaunchKernelGGL(k_rows_compact, dim3(std::min(row_tiles, 2048u)), dim3(kBlock), 0, s,
+                               P->bitmaps[k + 1].as<unsigned long long>(), n, row_base.as<int>(), newptr.as<int>(),
+                               p->row_ids.as<int32_t>(), p->rowptr.as<int32_t>(), (int64_t)R, (int)kept,
+                               d_stats + (size_t)k * kStatWords);
+            EPP_HIP_TRY(hipGetLastError());
         } else {
             EPP_HIP_TRY(hipMemsetAsync(p->rowptr.p, 0, sizeof(int32_t), s));
         }
-        EPP_HIP_TRY(hipGetLastError());
-        EPP_TRY(epp_path_finish(p, s, stats.p, reinterpret_cast<unsigned long long*>(hs.p) + 8 + (size_t)k * kStatWords,
-                                /*mark_row_ends=*/false));
         epp_path* q = pending.p;  // the path of the level before, if its entries still wait
         if (q && nested && share_pct > 0 && q->nnz > 0 && q->nnz * 100 >= kept * share_pct) {
             EPP_TRY(p->zero_block.alloc(256, al));
@@ -807,34 +1043,24 @@ extern "C" int epp_prepare(const epp_csr_t* g, const int32_t* train_ids, int64_t
             pending.p = p;
             pending.slot = slot;
         }
+        nested = next_nested;
         // Fixed point: N^{k+1} == N^k means every further set is the same set, so every deeper
         // layer (rows and sources both equal to it) has exactly this path; share it.
-        if (k + 1 < L && P->set_size[k + 1] == P->set_size[k]) {
-            int differs = 0;
-            EPP_HIP_TRY(hipMemsetAsync(err.p, 0, sizeof(int), s));
-            if (n_words > 0) {
-                hipLaunchKernelGGL(k_bitmap_differs, dim3(grid_for(n_words, kBlock)), dim3(kBlock), 0, s,
-                                   P->bitmaps[k].as<unsigned long long>(), P->bitmaps[k + 1].as<unsigned long long>(),
-                                   n_words, err.as<int>());
-                EPP_HIP_TRY(hipGetLastError());
+        if (k + 1 < L && fixed_point) {
+            for (int j = k + 1; j < L; ++j) {
+                EPP_HIP_TRY(hipMemcpyAsync(P->bitmaps[j + 1].p, P->bitmaps[k + 1].p, P->bitmaps[k + 1].bytes,
+                                           hipMemcpyDeviceToDevice, s));
+                P->set_size[j + 1] = P->set_size[k + 1];
+                P->path[L - 1 - j] = p;
             }
-            EPP_HIP_TRY(hipMemcpyAsync(&differs, err.p, sizeof(int), hipMemcpyDeviceToHost, s));
-            EPP_HIP_TRY(hipStreamSynchronize(s));
-            if (!differs) {
-                for (int j = k + 1; j < L; ++j) {
-                    EPP_HIP_TRY(hipMemcpyAsync(P->bitmaps[j + 1].p, P->bitmaps[k + 1].p, P->bitmaps[k + 1].bytes,
-                                               hipMemcpyDeviceToDevice, s));
-                    P->set_size[j + 1] = P->set_size[k + 1];
-                    P->path[L - 1 - j] = p;
-                }
-                break;
-            }
+            break;
         }
     }
     if (pending.p) EPP_TRY(extract(pending.p, pending.slot, false));
+    EPP_HIP_TRY(hipMemcpyAsync(hs.p + kLevelWords, d_stats, (size_t)L * kStatWords * 8, hipMemcpyDeviceToHost, s));
     EPP_HIP_TRY(hipStreamSynchronize(s));
     for (size_t k = 0; k < built.size(); ++k)
-        epp_path_set_stats(built[k], reinterpret_cast<const unsigned long long*>(hs.p) + 8 + k * kStatWords);
+        epp_path_set_stats(built[k], reinterpret_cast<const unsigned long long*>(hs.p) + kLevelWords + k * kStatWords);
     guard.p = nullptr;
     *out = P;
     return EPP_OK;
@@ -858,8 +1084,8 @@ extern "C" int epp_prepare_full(const epp_csr_t* g, const epp_alloc_t* alloc, ep
     EPP_TRY(p->full_rowptr.alloc((size_t)(g->n + 1) * 4, al));
     EPP_TRY(p->cv.alloc((size_t)g->nnz * sizeof(int2), al));
     {   // streamed form: the vertices with non-empty lists, ascending, with a compact row pointer
-        HostScalars hs;
-        EPP_TRY(hs.init());
+        PinnedWords hs;
+        EPP_TRY(hs.get(64));
         DevBuf bitmap, tile_cnt, tile_base, dev_total, err;
         const int64_t n_words = (g->n + 63) / 64;
         const size_t tiles = std::max<size_t>(grid_for(n_words, kWordsPerTile), 1);
@@ -938,10 +1164,21 @@ extern "C" int epp_paths_import(int64_t n, int L, const int32_t* train_ids, int6
         EPP_TRY(epp_static_scratch(&unused));
     }
     const int64_t n_words = (n + 63) / 64;
-    HostScalars hs;
-    EPP_TRY(hs.init());
+    constexpr int kStatWords = EPP_NCLASS + 1;
+    // words: [0] errors, [1] |N^0|, then every layer's statistics
+    const size_t res_words = 2 + (size_t)L * kStatWords;
+    PinnedWords hs;
+    EPP_TRY(hs.get(res_words));
     epp_paths* P = new epp_paths();
-    struct Guard { epp_paths* p; ~Guard() { delete p; } } guard{P};
+    struct Guard {  // (on an error: nothing may still be writing to what is given back)
+        epp_paths* p;
+        hipStream_t s;
+        ~Guard() {
+            if (!p) return;
+            (void)hipStreamSynchronize(s);
+            delete p;
+        }
+    } guard{P, s};
     P->L = L;
     P->n = n;
     if (alloc && alloc->alloc && alloc->free) P->alloc = *alloc;
@@ -949,37 +1186,34 @@ extern "C" int epp_paths_import(int64_t n, int L, const int32_t* train_ids, int6
     P->bitmaps.resize(L + 1);
     P->set_size.assign(L + 1, 0);
     P->path.assign(L, nullptr);
-    for (int k = 0; k <= L; ++k) {
-        EPP_TRY(P->bitmaps[k].alloc((size_t)n_words * 8, al));
-        EPP_HIP_TRY(hipMemsetAsync(P->bitmaps[k].p, 0, P->bitmaps[k].bytes, s));
-    }
-    DevBuf tile_cnt, tile_base, dev_total, err;
+    // bitmaps (cleared), ids of N^0 (at most one per training id), results (cleared)
+    const size_t bm_bytes = (size_t)n_words * 8, set0_bytes = (size_t)std::min(n_train, n) * 4;
     const size_t tiles = std::max<size_t>(grid_for(n_words, kWordsPerTile), 1);
-    EPP_TRY(tile_cnt.alloc(tiles * 4, al));
-    EPP_TRY(tile_base.alloc(tiles * 4, al));
-    EPP_TRY(dev_total.alloc(sizeof(long long), al));
-    EPP_TRY(err.alloc(2 * sizeof(int), al));  // [0]: path arrays, [1]: training ids
-    EPP_HIP_TRY(hipMemsetAsync(err.p, 0, 2 * sizeof(int), s));
-    if (n_train > 0)
+    const size_t clear_bytes = (size_t)(L + 1) * DevArena::rounded(bm_bytes) + DevArena::rounded(res_words * 8);
+    EPP_TRY(P->store.alloc(clear_bytes + DevArena::rounded(set0_bytes), al));
+    EPP_HIP_TRY(hipMemsetAsync(P->store.p, 0, clear_bytes, s));
+    for (int k = 0; k <= L; ++k) P->bitmaps[k].view(P->store.as<char>() + (size_t)k * DevArena::rounded(bm_bytes), bm_bytes);
+    long long* d_res = reinterpret_cast<long long*>(P->store.as<char>() + (size_t)(L + 1) * DevArena::rounded(bm_bytes));
+    void* set0 = P->store.as<char>() + clear_bytes;
+    int* d_err = reinterpret_cast<int*>(d_res);
+    DevArena arena;
+    DevBuf tile_cnt, tile_base, scan_tmp;
+    EPP_TRY(arena.reserve(2 * DevArena::rounded(tiles * 4) + DevArena::rounded(scan_tmp_bytes(tiles)), al));
+    arena.take(&tile_cnt, tiles * 4);
+    arena.take(&tile_base, tiles * 4);
+    arena.take(&scan_tmp, scan_tmp_bytes(tiles));
+    if (n_train > 0) {
         hipLaunchKernelGGL(k_mark_training, dim3(grid_for(n_train, kBlock)), dim3(kBlock), 0, s, train_ids, n_train, n,
-                           P->bitmaps[0].as<unsigned int>(), err.as<int>() + 1);
-    for (int l = 0; l < L; ++l) {
-        const epp_path_arrays_t& a = layers[l];
-        hipLaunchKernelGGL(k_check_rows, dim3(std::max(grid_for(a.n_rows, kBlock), 1u)), dim3(kBlock), 0, s, a.row_ids,
-                           a.rowptr, a.n_rows, a.nnz, n, P->bitmaps[L - l].as<unsigned int>(), err.as<int>());
-        if (a.nnz > 0)
-            hipLaunchKernelGGL(k_check_cols, dim3(grid_for(a.nnz, kBlock)), dim3(kBlock), 0, s, a.col, a.nnz, n,
-                               err.as<int>());
+                           P->bitmaps[0].as<unsigned int>(), d_err);
+        if (n > 0) {
+            hipLaunchKernelGGL(k_bitmap_count, dim3((unsigned)tiles), dim3(kBlock), 0, s, P->bitmaps[0].as<unsigned long long>(),
+                               n_words, tile_cnt.as<int>());
+            scan_counts(tile_cnt.as<int>(), tile_base.as<int>(), (int64_t)tiles, d_res + 1, scan_tmp.as<int>(), s);
+            hipLaunchKernelGGL(k_bitmap_compact, dim3((unsigned)tiles), dim3(kBlock), 0, s,
+                               P->bitmaps[0].as<unsigned long long>(), n_words, tile_base.as<int>(), (const int*)nullptr,
+                               static_cast<int32_t*>(set0), (int32_t*)nullptr, (int64_t)0, 0);
+        }
     }
-    EPP_HIP_TRY(hipGetLastError());
-    int herr2[2] = {0, 0};
-    EPP_HIP_TRY(hipMemcpyAsync(herr2, err.p, sizeof(herr2), hipMemcpyDeviceToHost, s));
-    EPP_HIP_TRY(hipStreamSynchronize(s));
-    const int herr = herr2[0] | (herr2[1] ? 2 : 0);
-    if (herr & 2) { epp_set_error("an id lies outside [0, %lld)", (long long)n); return EPP_ERR_OUT_OF_RANGE_ID; }
-    if (herr & 1) { epp_set_error("path arrays are not in canonical form"); return EPP_ERR_INVALID_ARG; }
-    EPP_TRY(compact_bitmap(P->bitmaps[0], n, nullptr, 0, &P->set0_ids, nullptr, &P->set_size[0], tile_cnt, tile_base,
-                           dev_total, hs, al, s));
     for (int l = L - 1; l >= 0; --l) {
         const epp_path_arrays_t& a = layers[l];
         const int k = L - l - 1;
@@ -990,22 +1224,36 @@ extern "C" int epp_paths_import(int64_t n, int L, const int32_t* train_ids, int6
         p->pool = &P->pool;
         p->n_rows = p->n_stream_rows = a.n_rows;
         p->nnz = a.nnz;
-        p->n_src = P->set_size[k];
         P->set_size[k + 1] = a.n_rows;
-        EPP_TRY(p->row_ids.alloc((size_t)a.n_rows * 4, al));
-        EPP_TRY(p->rowptr.alloc((size_t)(a.n_rows + 1) * 4, al));
+        // row ids | row pointer in one allocation, the entries in one of their own (see epp_prepare)
+        const size_t ids_bytes = (size_t)a.n_rows * 4, ptr_bytes = (size_t)(a.n_rows + 1) * 4;
+        EPP_TRY(p->store.alloc(DevArena::rounded(ids_bytes) + DevArena::rounded(ptr_bytes), al));
+        p->row_ids.view(p->store.p, ids_bytes);
+        p->rowptr.view(p->store.as<char>() + DevArena::rounded(ids_bytes), ptr_bytes);
         EPP_TRY(p->cv.alloc((size_t)a.nnz * sizeof(int2), al));
-        if (a.n_rows > 0)
-            EPP_HIP_TRY(hipMemcpyAsync(p->row_ids.p, a.row_ids, (size_t)a.n_rows * 4, hipMemcpyDeviceToDevice, s));
-        EPP_HIP_TRY(hipMemcpyAsync(p->rowptr.p, a.rowptr, (size_t)(a.n_rows + 1) * 4, hipMemcpyDeviceToDevice, s));
+        hipLaunchKernelGGL(k_import_rows, dim3(std::min(grid_for(a.n_rows + 1, kBlock), 2048u)), dim3(kBlock), 0, s, a.row_ids,
+                           a.rowptr, a.n_rows, a.nnz, n, p->row_ids.as<int32_t>(), p->rowptr.as<int32_t>(),
+                           P->bitmaps[k + 1].as<unsigned int>(),
+                           reinterpret_cast<unsigned long long*>(d_res + 2 + (size_t)l * kStatWords), d_err);
         if (a.nnz > 0) {
             hipLaunchKernelGGL(k_interleave, dim3(grid_for(a.nnz, kBlock)), dim3(kBlock), 0, s, a.col, a.val, a.nnz, n,
-                               p->cv.as<int2>(), (int*)nullptr);
-            EPP_HIP_TRY(hipGetLastError());
+                               p->cv.as<int2>(), d_err);
+            hipLaunchKernelGGL(k_mark_row_ends, dim3(grid_for(a.n_rows, kBlock)), dim3(kBlock), 0, s,
+                               p->rowptr.as<int32_t>(), a.n_rows, a.nnz, p->cv.as<int2>());
         }
-        EPP_TRY(epp_path_finish(p, s));
+        EPP_HIP_TRY(hipGetLastError());
     }
+    EPP_HIP_TRY(hipMemcpyAsync(hs.p, d_res, res_words * 8, hipMemcpyDeviceToHost, s));
     EPP_HIP_TRY(hipStreamSynchronize(s));
+    const int herr = (int)hs.p[0];
+    if (herr & (kErrCol | kErrTrain)) { epp_set_error("an id lies outside [0, %lld)", (long long)n); return EPP_ERR_OUT_OF_RANGE_ID; }
+    if (herr) { epp_set_error("path arrays are not in canonical form"); return EPP_ERR_INVALID_ARG; }
+    P->set_size[0] = hs.p[1];
+    P->set0_ids.view(set0, (size_t)hs.p[1] * 4);
+    for (int l = 0; l < L; ++l) {
+        P->path[l]->n_src = P->set_size[L - l - 1];
+        epp_path_set_stats(P->path[l], reinterpret_cast<const unsigned long long*>(hs.p) + 2 + (size_t)l * kStatWords);
+    }
     guard.p = nullptr;
     *out = P;
     return EPP_OK;
@@ -1064,8 +1312,8 @@ extern "C" int epp_active_set_export(const epp_paths_t* p, int k, int32_t* ids, 
         epp_set_error("ids buffer holds %lld entries, need %lld", (long long)*count, (long long)p->set_size[k]);
         return EPP_ERR_INVALID_ARG;
     }
-    HostScalars hs;
-    EPP_TRY(hs.init());
+    PinnedWords hs;
+    EPP_TRY(hs.get(64));
     DevBuf tile_cnt, tile_base, dev_total, tmp;
     const size_t tiles = std::max<size_t>(grid_for((p->n + 63) / 64, kWordsPerTile), 1);
     const epp_alloc_t* al = epp_alloc_of(p);

@@ -268,28 +268,6 @@ __global__ __launch_bounds__(kThreads) void k_prepare_small(SmallArgs a) {
     }
 }
 
-// Pinned host words for the read-back, one buffer per host thread, kept until the process ends (a
-// few kilobytes; freeing them from a thread-exit handler could run after the HIP runtime is gone).
-struct PinnedWords {
-    long long* p = nullptr;
-    size_t count = 0;
-    long long* get(size_t need) {
-        if (count < need) {
-            if (p) (void)hipHostFree(p);  // (grown while the runtime is certainly alive)
-            p = nullptr;
-            count = 0;
-            if (hipHostMalloc((void**)&p, need * sizeof(long long), hipHostMallocDefault) != hipSuccess) {
-                (void)hipGetLastError();
-                p = nullptr;
-                return nullptr;
-            }
-            count = need;
-        }
-        return p;
-    }
-};
-thread_local PinnedWords g_pinned;
-
 }  // namespace
 
 bool epp_prepare_small_fits(const epp_csr_t* g, int64_t n_train, int L) {
@@ -326,8 +304,9 @@ int epp_prepare_small(const epp_csr_t* g, const int32_t* train_ids, int64_t n_tr
     arena.take(&ptr_all, (size_t)L * DevArena::rounded(ptr_bytes));
     arena.take(&newptr, ptr_bytes);
     arena.take(&result, result_words * 8);
-    long long* host = g_pinned.get(result_words);
-    if (!host) { epp_set_error("pinned host allocation failed"); return EPP_ERR_ALLOC; }
+    PinnedWords pinned;
+    EPP_TRY(pinned.get(result_words));
+    long long* host = pinned.p;
 
     SmallArgs a;
     a.n = (int)n;
@@ -388,7 +367,7 @@ int epp_prepare_small(const epp_csr_t* g, const int32_t* train_ids, int64_t n_tr
             break;
         }
     }
-    P->small_store = std::move(arena.store);
+    P->store = std::move(arena.store);
     guard.p = nullptr;
     *out = P;
     return EPP_OK;
