@@ -81,7 +81,7 @@ struct MaskArgs {
     int64_t nnz, n_seg, n_tiles;
     int n;
     const unsigned int* bitmap;     // N^k
-    int first_id, n_ids;            // ids looked up by this pass (all of them without the LDS window)
+    int first_id, n_ids;            // ids looked up by this pass
     const unsigned long long* known;  // entries kept without a lookup (NULL: none; may be `mask` itself)
     int all;                        // N^k holds every vertex: every entry is kept, nothing is looked up
     int check;                      // range-check the columns (the first pass over the array)
@@ -93,89 +93,138 @@ struct MaskArgs {
 };
 
 // keep-mask of every 64-edge segment, kept entries per tile and before each segment of a tile.  A
-// wavefront owns a tile of 2048 entries and takes it in two halves: 16 column loads, then 16
-// lookups, each back to back, so that the dependent latencies are paid once per half.
+// wavefront owns a tile of 2048 entries and issues all its column loads, then all lookups, back to
+// back, so that the dependent latencies are paid once.
 //
 // What bounds it: the lookups.  64 lanes look 64 different words up, which from L2 costs the address
 // unit one cycle and more per lane: 250 G lookups/s on the whole chip, 0.52 ms for the 140 M
 // entries of a co-purchase graph whose columns stream in 0.12 ms.  LDS serves a wavefront's 64
-// words in a few cycles.  So a workgroup first copies a window of the bitmap into LDS (LDS_WORDS
-// words: 1.28 M ids fit) and streams its tiles past it; where the graph has more vertices, one
-// pass per window, each adding its finds to the mask.  A pass re-reads the columns, so past three
-// windows the lookups through L2 (LDS_WORDS = 0) are no slower.  Same graph: 0.28 ms in two passes.
+// words in a few cycles.  So a workgroup first copies a window of the bitmap into LDS (WORDS words:
+// 1.28 M ids fit) and streams its tiles past it; where the graph has more vertices, one pass per
+// window, each adding its finds to the mask.  A pass re-reads the columns, so past three windows
+// the lookups through L2 (k_edge_mask_far) are no slower.  Same graph: 0.12 ms per pass.
 //
 // `known`: if N^{k-1} is a subset of N^k (always the case when every vertex has a self-loop), an
-// entry kept at the previous level has its column in N^{k-1}, hence in N^k, and is kept again: only
-// the other entries are loaded and looked up.  The next window of a level is handed the mask so far
-// in the same way.
+// entry kept at the previous level has its column in N^{k-1}, hence in N^k, and is kept again.  The
+// next window of a level is handed the mask so far in the same way.
 //
 // Columns are range-checked by the first pass: an id outside [0, n) raises an error bit; it is
 // never used as an index.
-template <int THREADS, int LDS_WORDS>
-__global__ __launch_bounds__(THREADS) void k_edge_mask(MaskArgs a) {
-    __shared__ __attribute__((aligned(16))) unsigned int bits[LDS_WORDS > 0 ? LDS_WORDS : 4];
-    const int wave = threadIdx.x >> 6, lane = lane_id();
-    if constexpr (LDS_WORDS > 0) {
-        if (!a.all) {
-            const int words = (a.n_ids + 31) >> 5, total = ((a.n + 63) >> 6) * 2 - (a.first_id >> 5);
-            const unsigned int* __restrict__ src = a.bitmap + (a.first_id >> 5);
-            for (int i = 4 * (int)threadIdx.x; i < words; i += 4 * THREADS) {
-                uint4 x = make_uint4(0, 0, 0, 0);
-                if (i + 4 <= total) {
-                    x = *reinterpret_cast<const uint4*>(src + i);
-                } else {
-                    if (i < total) x.x = src[i];
-                    if (i + 1 < total) x.y = src[i + 1];
-                    if (i + 2 < total) x.z = src[i + 2];
-                }
-                *reinterpret_cast<uint4*>(bits + i) = x;
-            }
-            __syncthreads();
-        }
+__device__ __forceinline__ unsigned long long lane_word(unsigned long long x, int i) {
+    return (unsigned int)__builtin_amdgcn_readlane((int)x, i) |
+           ((unsigned long long)(unsigned int)__builtin_amdgcn_readlane((int)(x >> 32), i) << 32);
+}
+
+// Mask words and counts of a tile (lane i holds segment i's) to memory.
+__device__ __forceinline__ void store_tile(const MaskArgs& a, int64_t tile, bool mine, unsigned long long out, int off, int run) {
+    const int lane = lane_id();
+    const int64_t seg = tile * kSegsPerTile + lane;
+    if (mine) {
+        a.mask[seg] = out;
+        if (a.count) a.seg_off[seg] = (uint16_t)off;
     }
-    constexpr int kHalf = kSegsPerTile / 2;
-    const int64_t step = (int64_t)gridDim.x * (THREADS / 64);
-    for (int64_t tile = (int64_t)blockIdx.x * (THREADS / 64) + wave; tile < a.n_tiles; tile += step) {
+    if (a.count && lane == 0) a.tile_count[tile] = run;
+}
+
+template <int WORDS>
+__global__ __launch_bounds__(1024) void k_edge_mask(MaskArgs a) {
+    __shared__ __attribute__((aligned(16))) unsigned int bits[WORDS + 4];
+    const int wave = threadIdx.x >> 6, lane = lane_id();
+    {
+        const int words = (a.n_ids + 31) >> 5, total = ((a.n + 63) >> 6) * 2 - (a.first_id >> 5);
+        const unsigned int* __restrict__ src = a.bitmap + (a.first_id >> 5);
+        for (int i = 4 * (int)threadIdx.x; i < words; i += 4 * 1024) {
+            uint4 x = make_uint4(0, 0, 0, 0);
+            if (i + 4 <= total) {
+                x = *reinterpret_cast<const uint4*>(src + i);
+            } else {
+                if (i < total) x.x = src[i];
+                if (i + 1 < total) x.y = src[i + 1];
+                if (i + 2 < total) x.z = src[i + 2];
+            }
+            *reinterpret_cast<uint4*>(bits + i) = x;
+        }
+        if (threadIdx.x == 0) bits[WORDS] = 0u;  // what every id outside the window looks up
+        __syncthreads();
+    }
+    const int64_t step = (int64_t)gridDim.x * 16;
+    for (int64_t tile = (int64_t)blockIdx.x * 16 + wave; tile < a.n_tiles; tile += step) {
         const int64_t seg0 = tile * kSegsPerTile;
         const bool mine = lane < kSegsPerTile && seg0 + lane < a.n_seg;
-        const unsigned long long pm = (a.known && mine) ? a.known[seg0 + lane] : 0ull;
+        const unsigned long long known = (a.known && mine) ? a.known[seg0 + lane] : 0ull;
+        int c[kSegsPerTile];
+        const int32_t* __restrict__ col = a.col + seg0 * 64 + lane;
+        if ((seg0 + kSegsPerTile) * 64 <= a.nnz) {
+#pragma unroll
+            for (int i = 0; i < kSegsPerTile; ++i) c[i] = __builtin_nontemporal_load(col + i * 64);
+        } else {
+#pragma unroll
+            for (int i = 0; i < kSegsPerTile; ++i) c[i] = (seg0 + i) * 64 + lane < a.nnz ? col[i * 64] : -1;
+        }
+        if (a.check) {
+            unsigned int top = 0;  // (a negative id is a large unsigned one; so is the filler past the end)
+#pragma unroll
+            for (int i = 0; i < kSegsPerTile; ++i)
+                top = max(top, (seg0 + i) * 64 + lane < a.nnz ? (unsigned int)c[i] : 0u);
+            if (top >= (unsigned int)a.n) atomicOr(a.err, kErrCol);
+        }
+        unsigned int w[kSegsPerTile];
+#pragma unroll
+        for (int i = 0; i < kSegsPerTile; ++i) {
+            c[i] -= a.first_id;
+            w[i] = bits[(unsigned int)c[i] < (unsigned int)a.n_ids ? (unsigned int)c[i] >> 5 : WORDS];
+        }
+        unsigned long long out = 0ull;
+        int off = 0, run = 0;
+#pragma unroll
+        for (int i = 0; i < kSegsPerTile; ++i) {
+            const unsigned long long m = __ballot((w[i] >> (c[i] & 31)) & 1u) | lane_word(known, i);
+            if (lane == i) {
+                out = m;
+                off = run;
+            }
+            run += __popcll(m);
+        }
+        store_tile(a, tile, mine, out, off, run);
+    }
+}
+
+// The same with the lookups through L2, where known entries are neither loaded nor looked up; and, with
+// `all`, the mask of a set that holds every vertex.
+__global__ __launch_bounds__(kBlock) void k_edge_mask_far(MaskArgs a) {
+    constexpr int kHalf = kSegsPerTile / 2;
+    const int lane = lane_id();
+    const int64_t step = (int64_t)gridDim.x * (kBlock / 64);
+    for (int64_t tile = (int64_t)blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6); tile < a.n_tiles; tile += step) {
+        const int64_t seg0 = tile * kSegsPerTile;
+        const bool mine = lane < kSegsPerTile && seg0 + lane < a.n_seg;
+        if (a.all) {
+            const int64_t left = a.nnz - (seg0 + lane) * 64;
+            store_tile(a, tile, mine, left >= 64 ? ~0ull : low_mask((int)max(left, (int64_t)0)), lane * 64,
+                       (int)min(a.nnz - seg0 * 64, (int64_t)kSegsPerTile * 64));
+            continue;
+        }
+        const unsigned long long known = (a.known && mine) ? a.known[seg0 + lane] : 0ull;
         unsigned long long out = 0ull;
         int off = 0, run = 0;
         bool bad = false;
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
             int c[kHalf];
-            unsigned long long km[kHalf];
 #pragma unroll
             for (int i = 0; i < kHalf; ++i) {
-                const int sg = h * kHalf + i;
-                const int64_t e = (seg0 + sg) * 64 + lane;
-                km[i] = (unsigned int)__builtin_amdgcn_readlane((int)pm, sg) |
-                        ((unsigned long long)(unsigned int)__builtin_amdgcn_readlane((int)(pm >> 32), sg) << 32);
-                c[i] = (e < a.nnz && !a.all && !((km[i] >> lane) & 1ull)) ? __builtin_nontemporal_load(a.col + e) : -1;
-            }
-            if (a.check) {
-#pragma unroll
-                for (int i = 0; i < kHalf; ++i) {
-                    const int64_t e = (seg0 + h * kHalf + i) * 64 + lane;
-                    bad |= e < a.nnz && (c[i] < 0 || c[i] >= a.n) && !a.all && !((km[i] >> lane) & 1ull);
-                }
+                const int64_t e = (seg0 + h * kHalf + i) * 64 + lane;
+                const bool want = e < a.nnz && !((lane_word(known, h * kHalf + i) >> lane) & 1ull);
+                c[i] = want ? __builtin_nontemporal_load(a.col + e) : -1;
+                bad |= want && (c[i] < 0 || c[i] >= a.n);
             }
             unsigned int w[kHalf];
 #pragma unroll
-            for (int i = 0; i < kHalf; ++i) {
-                const int x = c[i] - a.first_id;
-                const bool in = c[i] >= 0 && (unsigned int)x < (unsigned int)a.n_ids;
-                if constexpr (LDS_WORDS > 0) w[i] = in ? bits[x >> 5] : 0u;
-                else w[i] = in ? a.bitmap[x >> 5] : 0u;
-                c[i] = x;
-            }
+            for (int i = 0; i < kHalf; ++i) w[i] = (c[i] >= 0 && c[i] < a.n) ? a.bitmap[c[i] >> 5] : 0u;
 #pragma unroll
             for (int i = 0; i < kHalf; ++i) {
                 const int sg = h * kHalf + i;
-                const bool keep = a.all ? (seg0 + sg) * 64 + lane < a.nnz
-                                        : ((km[i] >> lane) & 1ull) || ((w[i] >> (c[i] & 31)) & 1u);
-                const unsigned long long m = __ballot(keep);
+                const unsigned long long m = __ballot((w[i] >> (c[i] & 31)) & 1u) | lane_word(known, sg);
                 if (lane == sg) {
                     out = m;
                     off = run;
@@ -183,12 +232,8 @@ __global__ __launch_bounds__(THREADS) void k_edge_mask(MaskArgs a) {
                 run += __popcll(m);
             }
         }
-        if (bad) atomicOr(a.err, kErrCol);
-        if (mine) {
-            a.mask[seg0 + lane] = out;
-            if (a.count) a.seg_off[seg0 + lane] = (uint16_t)off;
-        }
-        if (a.count && lane == 0) a.tile_count[tile] = run;
+        if (a.check && bad) atomicOr(a.err, kErrCol);
+        store_tile(a, tile, mine, out, off, run);
     }
 }
 
@@ -291,49 +336,77 @@ struct Kept {
 // `inner.mask` (the keep-mask of the level before, a subset of this one) the entries that level did
 // not keep get the kEntOuterOnly mark: the path of the level before will run on this array;
 // inner_pos[q / 64] then receives, for every 64th entry q, how many entries before it that level kept.
+//
+// The last kept entry of every row gets the row-end flag: a workgroup looks through the rows that
+// overlap its tile (tile_row[t]: the row of the tile's first entry) for those whose filtered list
+// ends in it, while its entries are in flight.  (A kernel of its own that set the flags in the
+// finished array took 0.1 ms for 2.4 M rows: a read and a write of 128 bytes for each.)
+//
+// Runs at the rate of a copy: 140 M entries in 0.42 ms.  (What concerns a segment is fetched by one lane
+// and read from there as a scalar; vector loads of it cost 0.45 ms more.)
 __global__ __launch_bounds__(kBlock) void k_edge_extract(const int32_t* __restrict__ col, const float* __restrict__ val,
                                                          int64_t n_seg, Kept outer, Kept inner,
-                                                         int* __restrict__ inner_pos, int2* __restrict__ cv) {
-    const int wave = threadIdx.x >> 6, lane = lane_id();
+                                                         int* __restrict__ inner_pos, const int* __restrict__ tile_row,
+                                                         const int* __restrict__ newptr, int n, int total,
+                                                         int2* __restrict__ cv) {
     constexpr int kPerWave = kSegsPerTile / 4;
-    unsigned long long m[kPerWave], fr[kPerWave];
-    int sb[kPerWave];
+    __shared__ unsigned int row_end[kSegsPerTile * 2];  // one bit per kept entry of the tile
+    if (threadIdx.x < kSegsPerTile * 2) row_end[threadIdx.x] = 0u;
+    const int lane = lane_id();
+    const int64_t seg0 = (int64_t)blockIdx.x * kSegsPerTile + (threadIdx.x >> 6) * kPerWave;
+    // lane i fetches what concerns segment i; it is read from there as a scalar below
+    unsigned long long om = 0ull, im = 0ull;
+    int ob = 0, ib = 0;
+    if (lane < kPerWave && seg0 + lane < n_seg) {
+        om = outer.mask[seg0 + lane];
+        ob = outer.before_seg(seg0 + lane);
+        if (inner.mask) {
+            im = inner.mask[seg0 + lane];
+            ib = inner.before_seg(seg0 + lane);
+        }
+    }
     int2 x[kPerWave];
 #pragma unroll
     for (int i = 0; i < kPerWave; ++i) {
-        const int64_t seg = (int64_t)blockIdx.x * kSegsPerTile + wave * kPerWave + i;
-        m[i] = seg < n_seg ? outer.mask[seg] : 0ull;
-        fr[i] = (inner.mask && seg < n_seg) ? (m[i] & ~inner.mask[seg]) : 0ull;
-        sb[i] = seg < n_seg ? outer.before_seg(seg) : 0;
+        const int64_t e = (seg0 + i) * 64 + lane;
+        if ((lane_word(om, i) >> lane) & 1ull) x[i] = make_int2(col[e], __float_as_int(val[e]));
     }
+    const bool last_tile = blockIdx.x + 1 == gridDim.x;
+    const int base = outer.tile_base[blockIdx.x], limit = last_tile ? total : outer.tile_base[blockIdx.x + 1];
+    const int v_last = last_tile ? n - 1 : tile_row[blockIdx.x + 1];
+    __syncthreads();
+    if (limit > base) {
+        for (int v = tile_row[blockIdx.x] + (int)threadIdx.x; v <= v_last; v += kBlock) {
+            const int a = newptr[v], b = newptr[v + 1];
+            if (b > a && b > base && b <= limit) atomicOr(&row_end[(b - 1 - base) >> 5], 1u << ((b - 1 - base) & 31));
+        }
+    }
+    __syncthreads();
 #pragma unroll
     for (int i = 0; i < kPerWave; ++i) {
-        const int64_t e = ((int64_t)blockIdx.x * kSegsPerTile + wave * kPerWave + i) * 64 + lane;
-        if ((m[i] >> lane) & 1ull)
-            x[i] = make_int2(__builtin_nontemporal_load(col + e) | (((fr[i] >> lane) & 1ull) ? kEntOuterOnly : 0),
-                             __float_as_int(__builtin_nontemporal_load(val + e)));
-    }
-#pragma unroll
-    for (int i = 0; i < kPerWave; ++i) {
-        if ((m[i] >> lane) & 1ull) {
-            const int q = sb[i] + __popcll(m[i] & low_mask(lane));
+        const unsigned long long m = lane_word(om, i);
+        const int q = __builtin_amdgcn_readlane(ob, i) + __popcll(m & low_mask(lane));
+        if (inner.mask) {  // (uniform)
+            const unsigned long long in = lane_word(im, i);
+            if (!((in >> lane) & 1ull)) x[i].x |= kEntOuterOnly;
+            if (((m >> lane) & 1ull) && (q & 63) == 0)
+                inner_pos[q >> 6] = __builtin_amdgcn_readlane(ib, i) + __popcll(in & low_mask(lane));
+        }
+        if ((m >> lane) & 1ull) {
+            if ((row_end[(q - base) >> 5] >> ((q - base) & 31)) & 1u) x[i].x |= kEntRowEnd;
             cv[q] = x[i];
-            if (inner.mask && (q & 63) == 0) {
-                const int64_t seg = (int64_t)blockIdx.x * kSegsPerTile + wave * kPerWave + i;
-                inner_pos[q >> 6] = inner.before_seg(seg) + __popcll(m[i] & ~fr[i] & low_mask(lane));
-            }
         }
     }
 }
 
 // Filtered row pointer of every vertex, membership of N^{k+1}, members per 256 vertices, and how
-// N^{k+1} relates to N^k.  A row pointer that does not rise from 0 to nnz raises an error bit; no
+// N^{k+1} relates to N^k; with `tile_row`, also the row of every tile's first entry.  A row pointer that does not rise from 0 to nnz raises an error bit; no
 // index outside the mask arrays is formed.
 __global__ __launch_bounds__(kBlock) void k_row_flags(const int32_t* __restrict__ rowptr, int64_t n, int64_t nnz, Kept kept,
                                                       long long* level, int* __restrict__ newptr,
                                                       const unsigned long long* __restrict__ bitmap_cur,
                                                       unsigned long long* __restrict__ bitmap_next,
-                                                      int* __restrict__ row_count) {
+                                                      int* __restrict__ row_count, int* __restrict__ tile_row) {
     __shared__ int wave_cnt[kBlock / 64], wave_rel[kBlock / 64];
     const int lane = lane_id(), wave = threadIdx.x >> 6;
     const int64_t v = (int64_t)blockIdx.x * kBlock + threadIdx.x;
@@ -356,6 +429,10 @@ __global__ __launch_bounds__(kBlock) void k_row_flags(const int32_t* __restrict_
         newptr[v] = a;
         if (v == n - 1) newptr[n] = total;
         flag = b > a;
+        if (tile_row && p0 >= 0 && p1 > p0 && p1 <= nnz) {  // (first level: the rows of the tiles' first entries)
+            constexpr int kTile = kSegsPerTile * 64;
+            for (int64_t t = ((int64_t)p0 + kTile - 1) / kTile; t * kTile < p1; ++t) tile_row[t] = (int)v;
+        }
     }
     const unsigned long long bal = __ballot(flag);
     if (lane == 0) {
@@ -381,18 +458,32 @@ __global__ __launch_bounds__(kBlock) void k_row_flags(const int32_t* __restrict_
 
 __device__ __forceinline__ int length_class(int len) { return len <= 1 ? 0 : 32 - __clz(len - 1); }
 
-// Adds the rows of a wavefront (len > 0 where `row`) to the workgroup's histogram: one count per
-// distinct class among its 64 rows.
-__device__ __forceinline__ void add_lengths(int* __restrict__ h, bool row, int len) {
-    const int cls = row ? length_class(len) : -1;
-    unsigned long long todo = __ballot(cls >= 0);
-    while (todo) {
-        const int leader = __ffsll((long long)todo) - 1;
-        const unsigned long long same = __ballot(cls == __shfl(cls, leader));
-        if (lane_id() == leader) atomicAdd(&h[cls], __popcll(same));
-        todo &= ~same;
-    }
+// Adds a row to the workgroup's histogram (one copy per wavefront, so that at most 64 lanes queue at
+// a counter).
+constexpr int kHists = kBlock / 64;
+__device__ __forceinline__ void add_length(int* __restrict__ h, int len) {
+    atomicAdd(&h[(threadIdx.x >> 6) * EPP_NCLASS + length_class(len)], 1);
 }
+__device__ __forceinline__ void clear_lengths(int* __restrict__ h, int* __restrict__ mx) {
+    for (int i = threadIdx.x; i < kHists * EPP_NCLASS; i += kBlock) h[i] = 0;
+    if (threadIdx.x == 0) *mx = 0;
+    __syncthreads();
+}
+// The workgroup's counts and longest row to the statistics in memory (few workgroups: their atomics
+// meet at the same 33 words).
+__device__ __forceinline__ void flush_lengths(const int* __restrict__ h, int* __restrict__ mx, int my_max,
+                                              unsigned long long* __restrict__ hist, int* __restrict__ max_len) {
+    if (my_max) atomicMax(mx, my_max);
+    __syncthreads();
+    if (threadIdx.x < EPP_NCLASS) {
+        int c = 0;
+#pragma unroll
+        for (int w = 0; w < kHists; ++w) c += h[w * EPP_NCLASS + threadIdx.x];
+        if (c) atomicAdd(&hist[threadIdx.x], (unsigned long long)c);
+    }
+    if (threadIdx.x == 0 && *mx) atomicMax(max_len, *mx);
+}
+constexpr unsigned kStatBlocks = 512;
 
 // Ascending ids of N^{k+1}, compact row pointer and row-length statistics (EPP_NCLASS counts, then
 // the longest row); a workgroup takes 256 vertices at a time.
@@ -401,12 +492,10 @@ __global__ __launch_bounds__(kBlock) void k_rows_compact(const unsigned long lon
                                                          int32_t* __restrict__ ids, int32_t* __restrict__ ptr_out,
                                                          int64_t n_set, int total_nnz,
                                                          unsigned long long* __restrict__ stats) {
-    __shared__ int h[EPP_NCLASS];
+    __shared__ int h[kHists * EPP_NCLASS];
     __shared__ int mx;
     const int lane = lane_id(), wave = threadIdx.x >> 6;
-    if (threadIdx.x < EPP_NCLASS) h[threadIdx.x] = 0;
-    if (threadIdx.x == 0) mx = 0;
-    __syncthreads();
+    clear_lengths(h, &mx);
     int my_max = 0;
     const int64_t tiles = (n + kBlock - 1) / kBlock, n_words = (n + 63) >> 6;
     for (int64_t t = blockIdx.x; t < tiles; t += gridDim.x) {
@@ -419,21 +508,15 @@ __global__ __launch_bounds__(kBlock) void k_rows_compact(const unsigned long lon
             if (w == wave) m = x;
         }
         const int64_t v = t * kBlock + threadIdx.x;
-        const bool member = (m >> lane) & 1ull;
-        int len = 0;
-        if (member) {
-            const int r = at + __popcll(m & low_mask(lane)), p = newptr[v];
-            len = newptr[v + 1] - p;
+        if ((m >> lane) & 1ull) {
+            const int r = at + __popcll(m & low_mask(lane)), p = newptr[v], len = newptr[v + 1] - p;
             ids[r] = (int32_t)v;
             ptr_out[r] = p;
             my_max = max(my_max, len);
+            add_length(h, len);
         }
-        add_lengths(h, member, len);
     }
-    if (my_max) atomicMax(&mx, my_max);
-    __syncthreads();
-    if (threadIdx.x < EPP_NCLASS && h[threadIdx.x]) atomicAdd(&stats[threadIdx.x], (unsigned long long)h[threadIdx.x]);
-    if (threadIdx.x == 0 && mx) atomicMax(reinterpret_cast<int*>(stats + EPP_NCLASS), mx);
+    flush_lengths(h, &mx, my_max, stats, reinterpret_cast<int*>(stats + EPP_NCLASS));
     if (blockIdx.x == 0 && threadIdx.x == 0) ptr_out[n_set] = total_nnz;
 }
 
@@ -475,29 +558,20 @@ __global__ __launch_bounds__(kBlock) void k_bitmap_compact(const unsigned long l
     if (ptr_out && blockIdx.x == 0 && threadIdx.x == 0) ptr_out[n_set] = total_nnz;
 }
 
-// Row-length histogram by class and the maximal length.  Grid-stride; a wavefront adds one
-// count per distinct class among its 64 rows (ballots), a workgroup 33 global atomics in all.
+// Row-length histogram by class and the maximal length.
 __global__ __launch_bounds__(kBlock) void k_len_hist(const int32_t* __restrict__ rowptr, int64_t n_rows,
                                                      unsigned long long* __restrict__ hist, int* __restrict__ max_len) {
-    __shared__ int h[EPP_NCLASS];
+    __shared__ int h[kHists * EPP_NCLASS];
     __shared__ int mx;
-    if (threadIdx.x < EPP_NCLASS) h[threadIdx.x] = 0;
-    if (threadIdx.x == 0) mx = 0;
-    __syncthreads();
-    const int lane = threadIdx.x & 63;
+    clear_lengths(h, &mx);
     int my_max = 0;
     const int64_t span = (int64_t)gridDim.x * kBlock;
-    // whole wavefronts enter every iteration, so the ballots below see all 64 lanes
-    for (int64_t base = (int64_t)blockIdx.x * kBlock + (threadIdx.x & ~63); base < n_rows; base += span) {
-        const int64_t r = base + lane;
-        const int len = r < n_rows ? rowptr[r + 1] - rowptr[r] : 0;
+    for (int64_t r = (int64_t)blockIdx.x * kBlock + threadIdx.x; r < n_rows; r += span) {
+        const int len = rowptr[r + 1] - rowptr[r];
         my_max = max(my_max, len);
-        add_lengths(h, r < n_rows, len);
+        add_length(h, len);
     }
-    if (my_max) atomicMax(&mx, my_max);
-    __syncthreads();
-    if (threadIdx.x < EPP_NCLASS && h[threadIdx.x]) atomicAdd(&hist[threadIdx.x], (unsigned long long)h[threadIdx.x]);
-    if (threadIdx.x == 0 && mx) atomicMax(max_len, mx);
+    flush_lengths(h, &mx, my_max, hist, max_len);
 }
 
 // Interleave a plain CSR's (col, val) into pairs (all-active graph).
@@ -524,26 +598,30 @@ __global__ __launch_bounds__(kBlock) void k_check_rowptr(const int32_t* __restri
     if (p0 < 0 || p1 < p0 || p1 > nnz || (v == 0 && p0 != 0) || (v == n - 1 && p1 != nnz)) atomicOr(err, 1);
 }
 
-__global__ __launch_bounds__(kBlock) void k_deinterleave(const int2* __restrict__ cv, int64_t nnz, int32_t* __restrict__ col,
-                                                         float* __restrict__ val) {
-    int64_t e = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (e < nnz) {
-        int2 x = cv[e];
-        if (col) col[e] = x.x & kEntCol;  // (the high bits are flags)
-        if (val) val[e] = __int_as_float(x.y);
-    }
-}
-
-// Entries of an inner path that shares the arrays of its outer path (canonical form, for export): the
-// outer path's entries without those that carry the kEntOuterOnly mark, in the same order.  A
-// wavefront takes kExportSegs segments of 64 entries; inner_pos (recorded when the array was extracted)
-// says where a segment's entries go, so one pass over the array is enough.  It runs at the rate of
-// a copy: 140 M entries (1.1 GB read, 1.1 GB written) in 0.48 ms.  (A wavefront per row, with a search
-// for the row, took 6.3 ms: rows of a few dozen entries leave most lanes idle.)
+// A path in canonical form, into the caller's arrays (any of which may be NULL), in one launch: the
+// first entry_blocks workgroups write the entries without their flags, kExportSegs segments of 64
+// per wavefront, the others the row ids (NULL: 0 .. n_rows - 1) and the row pointer.
+//
+// INNER: the path is an inner one that shares these entries.  Its entries are those without the
+// kEntOuterOnly mark, in the same order; inner_pos (recorded when the array was extracted) says
+// where a segment's entries go, so one pass over the array is enough.
+//
+// Runs at the rate of a copy: 140 M entries (1.1 GB read, 1.1 GB written) in 0.4 to 0.47 ms.  (A
+// wavefront per inner row, with a search for the row, took 6.3 ms.)
 constexpr int kExportSegs = 4;
-__global__ __launch_bounds__(kBlock) void k_export_inner(const int2* __restrict__ cv, int64_t nnz,
-                                                         const int* __restrict__ inner_pos, int64_t inner_nnz,
-                                                         int32_t* __restrict__ col, float* __restrict__ val) {
+template <bool INNER>
+__global__ __launch_bounds__(kBlock) void k_export(const int2* __restrict__ cv, int64_t nnz,
+                                                   const int* __restrict__ inner_pos, int64_t out_nnz, unsigned entry_blocks,
+                                                   int32_t* __restrict__ col, float* __restrict__ val,
+                                                   const int32_t* __restrict__ row_ids, const int32_t* __restrict__ rowptr,
+                                                   int64_t n_rows, int32_t* __restrict__ ids_out,
+                                                   int32_t* __restrict__ ptr_out) {
+    if (blockIdx.x >= entry_blocks) {
+        const int64_t r = (int64_t)(blockIdx.x - entry_blocks) * kBlock + threadIdx.x;
+        if (ids_out && r < n_rows) ids_out[r] = row_ids ? row_ids[r] : (int32_t)r;
+        if (ptr_out && r <= n_rows) ptr_out[r] = rowptr[r];
+        return;
+    }
     const int64_t seg0 = ((int64_t)blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6)) * kExportSegs;
     const int lane = lane_id();
     int2 x[kExportSegs];
@@ -552,23 +630,22 @@ __global__ __launch_bounds__(kBlock) void k_export_inner(const int2* __restrict_
     for (int i = 0; i < kExportSegs; ++i) {
         const int64_t e = (seg0 + i) * 64 + lane;
         x[i] = e < nnz ? cv[e] : make_int2(kEntOuterOnly, 0);
-        at[i] = (seg0 + i) * 64 < nnz ? inner_pos[seg0 + i] : 0;
+        if constexpr (INNER) at[i] = (seg0 + i) * 64 < nnz ? inner_pos[seg0 + i] : 0;
     }
 #pragma unroll
     for (int i = 0; i < kExportSegs; ++i) {
-        const bool keep = !(x[i].x & kEntOuterOnly);
-        const unsigned long long m = __ballot(keep);
-        const int64_t j = at[i] + __popcll(m & low_mask(lane));
-        if (keep && j < inner_nnz) {  // (the bound only guards against arrays that do not belong together)
+        int64_t j = (seg0 + i) * 64 + lane;
+        bool keep = j < nnz;
+        if constexpr (INNER) {
+            keep = !(x[i].x & kEntOuterOnly);
+            j = at[i] + __popcll(__ballot(keep) & low_mask(lane));
+            keep &= j < out_nnz;  // (only guards against arrays that do not belong together)
+        }
+        if (keep) {
             if (col) col[j] = x[i].x & kEntCol;
             if (val) val[j] = __int_as_float(x[i].y);
         }
     }
-}
-
-__global__ __launch_bounds__(kBlock) void k_iota(int32_t* __restrict__ out, int64_t n) {
-    int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (i < n) out[i] = (int32_t)i;
 }
 
 // Flag the last entry of every (non-empty) row in bit 31 of its column id.  (The bounds only matter
@@ -662,7 +739,7 @@ int compact_bitmap(const DevBuf& bitmap, int64_t n, const int* newptr, int total
 void launch_edge_mask(const epp_csr_t* g, int64_t n_seg, unsigned n_tiles, const unsigned int* bitmap,
                       const unsigned long long* known, bool all, bool check, unsigned long long* mask, uint16_t* seg_off,
                       int* tile_count, int* err, hipStream_t s) {
-    constexpr int kSmall = 8192, kLarge = 39936;  // words: 32 KB (two workgroups per CU), 156 KB
+    constexpr int kSmall = 8192, kLarge = 39936;  // words: 32 KB (two workgroups per CU), 156 KB (one)
     MaskArgs a;
     a.col = g->col;
     a.nnz = g->nnz;
@@ -683,7 +760,7 @@ void launch_edge_mask(const epp_csr_t* g, int64_t n_seg, unsigned n_tiles, const
         a.n_ids = a.n;
         a.check = check;
         a.count = 1;
-        hipLaunchKernelGGL((k_edge_mask<kBlock, 0>), dim3(std::min(grid_for(n_tiles, kBlock / 64), 16384u)), dim3(kBlock), 0, s, a);
+        hipLaunchKernelGGL(k_edge_mask_far, dim3(std::min(grid_for(n_tiles, kBlock / 64), 16384u)), dim3(kBlock), 0, s, a);
         return;
     }
     for (int64_t w = 0; w < passes; ++w) {
@@ -693,9 +770,9 @@ void launch_edge_mask(const epp_csr_t* g, int64_t n_seg, unsigned n_tiles, const
         a.count = w == passes - 1;
         if (w > 0) a.known = mask;
         if (window == kSmall * 32)
-            hipLaunchKernelGGL((k_edge_mask<1024, kSmall>), dim3(std::min(grid_for(n_tiles, 16), 512u)), dim3(1024), 0, s, a);
+            hipLaunchKernelGGL((k_edge_mask<kSmall>), dim3(std::min(grid_for(n_tiles, 16), 512u)), dim3(1024), 0, s, a);
         else
-            hipLaunchKernelGGL((k_edge_mask<1024, kLarge>), dim3(std::min(grid_for(n_tiles, 16), 256u)), dim3(1024), 0, s, a);
+            hipLaunchKernelGGL((k_edge_mask<kLarge>), dim3(std::min(grid_for(n_tiles, 16), 256u)), dim3(1024), 0, s, a);
     }
 }
 
@@ -709,11 +786,9 @@ __global__ __launch_bounds__(kBlock) void k_import_rows(const int32_t* __restric
                                                         int64_t n, int32_t* __restrict__ ids_out,
                                                         int32_t* __restrict__ ptr_out, unsigned int* __restrict__ bitmap32,
                                                         unsigned long long* __restrict__ stats, int* __restrict__ err) {
-    __shared__ int h[EPP_NCLASS];
+    __shared__ int h[kHists * EPP_NCLASS];
     __shared__ int mx;
-    if (threadIdx.x < EPP_NCLASS) h[threadIdx.x] = 0;
-    if (threadIdx.x == 0) mx = 0;
-    __syncthreads();
+    clear_lengths(h, &mx);
     const int lane = lane_id();
     int my_max = 0, bad = 0;
     const int64_t span = (int64_t)gridDim.x * kBlock;
@@ -745,13 +820,10 @@ __global__ __launch_bounds__(kBlock) void k_import_rows(const int32_t* __restric
         }
         const int next_word = __shfl_down(word, 1, 64);
         if (in && (lane == 63 || next_word != word)) atomicOr(&bitmap32[word], b);
-        add_lengths(h, row && len > 0, len);
+        if (row && len > 0) add_length(h, len);
     }
     if (bad) atomicOr(err, bad);
-    if (my_max) atomicMax(&mx, my_max);
-    __syncthreads();
-    if (threadIdx.x < EPP_NCLASS && h[threadIdx.x]) atomicAdd(&stats[threadIdx.x], (unsigned long long)h[threadIdx.x]);
-    if (threadIdx.x == 0 && mx) atomicMax(reinterpret_cast<int*>(stats + EPP_NCLASS), mx);
+    flush_lengths(h, &mx, my_max, stats, reinterpret_cast<int*>(stats + EPP_NCLASS));
 }
 
 // Message and code for the error bits raised by the input checks (bit 0 row pointer, bit 1 ids).
@@ -824,7 +896,7 @@ int epp_path_finish(epp_path* p, hipStream_t s) {
     if (p->n_rows > 0) {
         // canonical rows: the all-active graph counts its empty rows too
         const int32_t* ptr = p->all_rows ? p->full_rowptr.as<int32_t>() : p->rowptr.as<int32_t>();
-        hipLaunchKernelGGL(k_len_hist, dim3(std::min(grid_for(p->n_rows, kBlock), 2048u)), dim3(kBlock), 0, s, ptr,
+        hipLaunchKernelGGL(k_len_hist, dim3(std::min(grid_for(p->n_rows, kBlock), kStatBlocks)), dim3(kBlock), 0, s, ptr,
                            p->n_rows, stats.as<unsigned long long>(),
                            reinterpret_cast<int*>(stats.as<unsigned long long>() + EPP_NCLASS));
         EPP_HIP_TRY(hipGetLastError());
@@ -896,9 +968,9 @@ extern "C" int epp_prepare(const epp_csr_t* g, const int32_t* train_ids, int64_t
     EPP_HIP_TRY(hipMemsetAsync(P->bitmaps[0].p, 0, bm_bytes, s));  // (the others are written whole)
 
     // all temporaries of the construction come from one allocation
-    // (keep-mask and its counts twice: the entries of a level are extracted once the next
+    // (keep-mask, its counts and the filtered row pointer twice: the entries of a level are extracted once the next
     // level has shown whether the two paths share them, so two levels' masks are alive at a time)
-    DevBuf mask[2], seg_off[2], tile_base[2], tile_cnt, row_cnt, row_base, scan_tmp, newptr, levels;
+    DevBuf mask[2], seg_off[2], tile_base[2], tile_cnt, row_cnt, row_base, scan_tmp, newptr[2], tile_row, levels;
     const size_t cnt_bytes = (size_t)std::max(std::max(edge_tiles, word_tiles), 1u) * 4;
     const size_t row_bytes = (size_t)std::max(row_tiles, 1u) * 4;
     const size_t tmp_bytes = scan_tmp_bytes(std::max<int64_t>(edge_tiles, row_tiles));
@@ -906,18 +978,19 @@ extern "C" int epp_prepare(const epp_csr_t* g, const int32_t* train_ids, int64_t
     DevArena arena;
     EPP_TRY(arena.reserve(2 * (DevArena::rounded((size_t)n_seg * 8) + DevArena::rounded((size_t)n_seg * 2) +
                                DevArena::rounded(cnt_bytes)) +
-                          DevArena::rounded(cnt_bytes) + 2 * DevArena::rounded(row_bytes) + DevArena::rounded(tmp_bytes) +
-                          DevArena::rounded((size_t)(n + 1) * 4) + DevArena::rounded(level_bytes), al));
+                          2 * DevArena::rounded(cnt_bytes) + 2 * DevArena::rounded(row_bytes) + DevArena::rounded(tmp_bytes) +
+                          2 * DevArena::rounded((size_t)(n + 1) * 4) + DevArena::rounded(level_bytes), al));
     for (int i = 0; i < 2; ++i) {
         arena.take(&mask[i], (size_t)n_seg * 8);
         arena.take(&seg_off[i], (size_t)n_seg * 2);
         arena.take(&tile_base[i], cnt_bytes);
+        arena.take(&newptr[i], (size_t)(n + 1) * 4);
     }
     arena.take(&tile_cnt, cnt_bytes);
     arena.take(&row_cnt, row_bytes);
     arena.take(&row_base, row_bytes);
     arena.take(&scan_tmp, tmp_bytes);
-    arena.take(&newptr, (size_t)(n + 1) * 4);
+    arena.take(&tile_row, cnt_bytes);
     arena.take(&levels, level_bytes);
     long long* const d_levels = levels.as<long long>();
     unsigned long long* const d_stats = reinterpret_cast<unsigned long long*>(d_levels + (size_t)L * kLevelWords);
@@ -958,11 +1031,7 @@ extern "C" int epp_prepare(const epp_csr_t* g, const int32_t* train_ids, int64_t
         if (edge_tiles) {
             hipLaunchKernelGGL(k_edge_extract, dim3(edge_tiles), dim3(kBlock), 0, s, g->col, g->val, n_seg, kept_of(slot),
                                marks_inner ? kept_of(slot ^ 1) : Kept{nullptr, nullptr, nullptr}, q->inner_pos.as<int>(),
-                               q->cv.as<int2>());
-        }
-        if (q->n_stream_rows > 0) {
-            hipLaunchKernelGGL(k_mark_row_ends, dim3(grid_for(q->n_stream_rows, kBlock)), dim3(kBlock), 0, s,
-                               q->rowptr.as<int32_t>(), q->n_stream_rows, q->nnz, q->cv.as<int2>());
+                               tile_row.as<int>(), newptr[slot].as<int>(), (int)n, (int)q->nnz, q->cv.as<int2>());
         }
         EPP_HIP_TRY(hipGetLastError());
         return EPP_OK;
@@ -989,8 +1058,9 @@ extern "C" int epp_prepare(const epp_csr_t* g, const int32_t* train_ids, int64_t
         }
         if (n > 0) {
             hipLaunchKernelGGL(k_row_flags, dim3(row_tiles), dim3(kBlock), 0, s, g->rowptr, n, nnz, kept_of(slot), d_level,
-                               newptr.as<int>(), P->bitmaps[k].as<unsigned long long>(),
-                               P->bitmaps[k + 1].as<unsigned long long>(), row_cnt.as<int>());
+                               newptr[slot].as<int>(), P->bitmaps[k].as<unsigned long long>(),
+                               P->bitmaps[k + 1].as<unsigned long long>(), row_cnt.as<int>(),
+                               k == 0 ? tile_row.as<int>() : (int*)nullptr);
             scan_counts(row_cnt.as<int>(), row_base.as<int>(), (int64_t)row_tiles, d_level + 1, scan_tmp.as<int>(), s, d_level,
                         hs.p);
         } else {
@@ -1021,8 +1091,8 @@ extern "C" int epp_prepare(const epp_csr_t* g, const int32_t* train_ids, int64_t
         p->row_ids.view(base, ids_bytes);
         p->rowptr.view(base + DevArena::rounded(ids_bytes), ptr_bytes);
         if (n > 0) {
-            hipLaunchKernelGGL(k_rows_compact, dim3(std::min(row_tiles, 2048u)), dim3(kBlock), 0, s,
-                               P->bitmaps[k + 1].as<unsigned long long>(), n, row_base.as<int>(), newptr.as<int>(),
+            hipLaunchKernelGGL(k_rows_compact, dim3(std::min(row_tiles, kStatBlocks)), dim3(kBlock), 0, s,
+                               P->bitmaps[k + 1].as<unsigned long long>(), n, row_base.as<int>(), newptr[slot].as<int>(),
                                p->row_ids.as<int32_t>(), p->rowptr.as<int32_t>(), (int64_t)R, (int)kept,
                                d_stats + (size_t)k * kStatWords);
             EPP_HIP_TRY(hipGetLastError());
@@ -1231,7 +1301,7 @@ extern "C" int epp_paths_import(int64_t n, int L, const int32_t* train_ids, int6
         p->row_ids.view(p->store.p, ids_bytes);
         p->rowptr.view(p->store.as<char>() + DevArena::rounded(ids_bytes), ptr_bytes);
         EPP_TRY(p->cv.alloc((size_t)a.nnz * sizeof(int2), al));
-        hipLaunchKernelGGL(k_import_rows, dim3(std::min(grid_for(a.n_rows + 1, kBlock), 2048u)), dim3(kBlock), 0, s, a.row_ids,
+        hipLaunchKernelGGL(k_import_rows, dim3(std::min(grid_for(a.n_rows + 1, kBlock), kStatBlocks)), dim3(kBlock), 0, s, a.row_ids,
                            a.rowptr, a.n_rows, a.nnz, n, p->row_ids.as<int32_t>(), p->rowptr.as<int32_t>(),
                            P->bitmaps[k + 1].as<unsigned int>(),
                            reinterpret_cast<unsigned long long*>(d_res + 2 + (size_t)l * kStatWords), d_err);
@@ -1273,28 +1343,20 @@ extern "C" int epp_path_export(const epp_path_t* p, int32_t* row_ids, int32_t* r
                                epp_stream_t stream) {
     if (!p) { epp_set_error("path is NULL"); return EPP_ERR_INVALID_ARG; }
     hipStream_t s = (hipStream_t)stream;
-    if (row_ids && p->n_rows > 0) {
-        if (p->all_rows) {
-            hipLaunchKernelGGL(k_iota, dim3(grid_for(p->n_rows, kBlock)), dim3(kBlock), 0, s, row_ids, p->n_rows);
-        } else {
-            EPP_HIP_TRY(hipMemcpyAsync(row_ids, p->row_ids.p, (size_t)p->n_rows * 4, hipMemcpyDeviceToDevice, s));
-        }
-    }
-    if (rowptr) {
-        const void* ptr = p->all_rows ? p->full_rowptr.p : p->rowptr.p;
-        EPP_HIP_TRY(hipMemcpyAsync(rowptr, ptr, (size_t)(p->n_rows + 1) * 4, hipMemcpyDeviceToDevice, s));
-    }
-    if ((col || val) && p->nnz > 0) {
-        if (p->outer) {  // the entries live in the outer path's array
-            epp_path* o = p->outer;
-            EPP_TRY(epp_ensure_canonical(o, s));
-            hipLaunchKernelGGL(k_export_inner, dim3(grid_for(o->nnz, kBlock * kExportSegs)), dim3(kBlock), 0, s,
-                               o->cv.as<int2>(), o->nnz, o->inner_pos.as<int>(), p->nnz, col, val);
-        } else {
-            EPP_TRY(epp_ensure_canonical(const_cast<epp_path*>(p), s));
-            hipLaunchKernelGGL(k_deinterleave, dim3(grid_for(p->nnz, kBlock)), dim3(kBlock), 0, s, p->cv.as<int2>(),
-                               p->nnz, col, val);
-        }
+    epp_path* o = p->outer ? p->outer : const_cast<epp_path*>(p);  // the path whose array holds the entries
+    const bool entries = (col || val) && p->nnz > 0;
+    if (entries) EPP_TRY(epp_ensure_canonical(o, s));
+    const unsigned eb = entries ? grid_for(o->nnz, kBlock * kExportSegs) : 0;
+    const unsigned rb = (row_ids || rowptr) ? grid_for(p->n_rows + 1, kBlock) : 0;
+    if (eb + rb > 0) {
+        const int32_t* ids = p->all_rows ? nullptr : p->row_ids.as<int32_t>();
+        const int32_t* ptr = p->all_rows ? p->full_rowptr.as<int32_t>() : p->rowptr.as<int32_t>();
+        if (p->outer)
+            hipLaunchKernelGGL(k_export<true>, dim3(eb + rb), dim3(kBlock), 0, s, o->cv.as<int2>(), o->nnz,
+                               o->inner_pos.as<int>(), p->nnz, eb, col, val, ids, ptr, p->n_rows, row_ids, rowptr);
+        else
+            hipLaunchKernelGGL(k_export<false>, dim3(eb + rb), dim3(kBlock), 0, s, o->cv.as<int2>(), o->nnz,
+                               (const int*)nullptr, p->nnz, eb, col, val, ids, ptr, p->n_rows, row_ids, rowptr);
     }
     EPP_HIP_TRY(hipGetLastError());
     EPP_HIP_TRY(hipStreamSynchronize(s));
