@@ -2,7 +2,10 @@
 
 Argument marshalling only: every step of the path runs inside the HIP library.  PyTorch
 supplies device memory (tensors) and the current stream.  There is no CPU fallback: if the
-shared library is missing or cannot be loaded, importing the functions below raises.
+shared library is missing or cannot be loaded, calling the functions below raises.
+
+The calls that a training loop makes on every layer of every pass come from the extension module
+`_binding` (csrc/epp_binding.cpp); everything else goes through ctypes.
 """
 from __future__ import annotations
 
@@ -145,8 +148,11 @@ def _check(rc: int) -> int:
     return rc
 
 
+_raw_stream = torch._C._cuda_getCurrentRawStream  # (without the Stream object around it)
+
+
 def _stream() -> int:
-    return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(torch.cuda.current_device())
 
 
 def _dev(t: torch.Tensor, dtype) -> torch.Tensor:
@@ -239,6 +245,7 @@ class Paths:
 
     def __init__(self, handle: int):
         self._h = handle
+        self._n = None
 
     @property
     def num_layers(self) -> int:
@@ -247,7 +254,9 @@ class Paths:
     @property
     def n(self) -> int:
         """Vertices of the input graph."""
-        return self.path(0).info().n
+        if self._n is None:
+            self._n = self.path(0).info().n
+        return self._n
 
     def path(self, l: int) -> Path_:
         h = load_library().epp_get_path(self._h, l)
@@ -306,16 +315,6 @@ def _grads(path: Path_, grad_in: torch.Tensor, grad_out: torch.Tensor) -> int:
     return grad_in.shape[1]
 
 
-def epp_backward_aggregate(path: Path_, grad_in: torch.Tensor, grad_out: torch.Tensor) -> None:
-    F = _grads(path, grad_in, grad_out)
-    _check(load_library().epp_backward_aggregate(path._h, grad_in.data_ptr(), grad_out.data_ptr(), F, _stream()))
-
-
-def epp_full_aggregate(full: Path_, grad_in: torch.Tensor, grad_out: torch.Tensor) -> None:
-    F = _grads(full, grad_in, grad_out)
-    _check(load_library().epp_full_aggregate(full._h, grad_in.data_ptr(), grad_out.data_ptr(), F, _stream()))
-
-
 def epp_ifelse_aggregate(full: Path_, paths: Paths, l: int, grad_in: torch.Tensor, grad_out: torch.Tensor) -> None:
     """If-else selective scheduling baseline (Sec. 4): all-active traversal with activity tests."""
     F = _grads(full, grad_in, grad_out)
@@ -323,48 +322,19 @@ def epp_ifelse_aggregate(full: Path_, paths: Paths, l: int, grad_in: torch.Tenso
                                                _stream()))
 
 
-def _matrix(t: torch.Tensor, what: str) -> torch.Tensor:
-    _dev(t, torch.float32)
-    if t.dim() != 2:
-        raise ValueError(f"{what} must be a matrix")
-    return t
-
-
 def epp_weight_gradient_workspace(paths: Paths, k: int, F_in: int, F_out: int) -> int:
     return _check(load_library().epp_weight_gradient_workspace(paths._h, k, F_in, F_out))
 
 
-def epp_weight_gradient(paths: Paths, k: int, Y: torch.Tensor, grad_X: torch.Tensor, grad_W: torch.Tensor,
-                        workspace: torch.Tensor) -> None:
-    """W' = Y^T (x) X' over the rows of N^k (k = -1: all rows); `workspace` is a CUDA uint8 tensor of
-    at least epp_weight_gradient_workspace(...) bytes."""
-    _matrix(Y, "Y"), _matrix(grad_X, "grad_X"), _matrix(grad_W, "grad_W")
-    if Y.shape[0] != paths.n or grad_X.shape[0] != paths.n or grad_W.shape != (Y.shape[1], grad_X.shape[1]):
-        raise ValueError("shapes: Y n x F_in, grad_X n x F_out, grad_W F_in x F_out")
-    if not workspace.is_cuda or workspace.dtype != torch.uint8 or not workspace.is_contiguous():
-        raise ValueError("workspace must be a contiguous CUDA uint8 tensor")
-    _check(load_library().epp_weight_gradient(paths._h, k, Y.data_ptr(), Y.shape[1], grad_X.data_ptr(), grad_X.shape[1],
-                                              grad_W.data_ptr(), workspace.data_ptr(), workspace.numel(), _stream()))
-
-
-def epp_weight_gradient_static(paths: Paths, k: int, Y: torch.Tensor, grad_X: torch.Tensor,
-                               grad_W: torch.Tensor) -> None:
-    """epp_weight_gradient without a workspace: the partial sums use the library's static device array
-    (no allocation anywhere; F_in * F_out <= 8,388,608; calls on one GPU must not overlap)."""
-    _matrix(Y, "Y"), _matrix(grad_X, "grad_X"), _matrix(grad_W, "grad_W")
-    if Y.shape[0] != paths.n or grad_X.shape[0] != paths.n or grad_W.shape != (Y.shape[1], grad_X.shape[1]):
-        raise ValueError("shapes: Y n x F_in, grad_X n x F_out, grad_W F_in x F_out")
-    _check(load_library().epp_weight_gradient_static(paths._h, k, Y.data_ptr(), Y.shape[1], grad_X.data_ptr(),
-                                                     grad_X.shape[1], grad_W.data_ptr(), _stream()))
-
-
-def epp_input_gradient(paths: Paths, k: int, grad_X: torch.Tensor, W: torch.Tensor, grad_Y: torch.Tensor) -> None:
-    """Y' = X' (x) W^T on the rows of N^k (k = -1: all rows); other rows of grad_Y are not touched."""
-    _matrix(grad_X, "grad_X"), _matrix(W, "W"), _matrix(grad_Y, "grad_Y")
-    if grad_X.shape[0] != paths.n or W.shape[1] != grad_X.shape[1] or grad_Y.shape != (grad_X.shape[0], W.shape[0]):
-        raise ValueError("shapes: grad_X n x F_out, W F_in x F_out, grad_Y n x F_in")
-    _check(load_library().epp_input_gradient(paths._h, k, grad_X.data_ptr(), grad_X.shape[1], W.data_ptr(), W.shape[0],
-                                             grad_Y.data_ptr(), _stream()))
+try:
+    from ._binding import (epp_backward_aggregate, epp_full_aggregate, epp_input_gradient, epp_weight_gradient,
+                           epp_weight_gradient_static, init as _init_binding)
+    _init_binding(EppError, _raw_stream)
+except ImportError as _e:  # not built yet: the package can be imported (to build it), these calls raise
+    def _not_built(*_args, _why=str(_e), **_kw):
+        raise FileNotFoundError(f"{PKG}/_binding is not usable ({_why}): run `python -m paper_2204_02662_amd.build`")
+    epp_backward_aggregate = epp_full_aggregate = epp_input_gradient = _not_built
+    epp_weight_gradient = epp_weight_gradient_static = _not_built
 
 
 def epp_paths_import(n: int, train_ids: torch.Tensor, layers, torch_allocator: bool = True) -> Paths:

@@ -69,18 +69,13 @@ __global__ __launch_bounds__(kBlock) void k_sched_groups(const int32_t* __restri
 
 // ------------------------------------------------------------------------- aggregation
 // Zero the given rows (all-active graph: the vertices whose lists are empty).
-__global__ __launch_bounds__(kBlock) void k_zero_rows(const int32_t* __restrict__ rows, int64_t n_rows,
-                                                      const int32_t* __restrict__ row_ids, int F,
-                                                      const unsigned int* __restrict__ only_bits,
+__global__ __launch_bounds__(kBlock) void k_zero_rows(const int32_t* __restrict__ rows, int64_t n_rows, int F,
                                                       float* __restrict__ out) {
     int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
     if (i >= n_rows * F) return;
     int64_t r = i / F;
     int f = (int)(i - r * F);
-    int32_t v = rows[r];
-    if (row_ids) v = row_ids[v];
-    if (only_bits && !((only_bits[v >> 5] >> (v & 31)) & 1u)) return;
-    out[(size_t)v * F + f] = 0.0f;
+    out[(size_t)rows[r] * F + f] = 0.0f;
 }
 
 struct AggArgs {
@@ -127,11 +122,15 @@ __device__ __forceinline__ void write_row(float* __restrict__ o, const float (&a
     __builtin_nontemporal_store(r, reinterpret_cast<typename VecT<VEC>::type*>(o));
 }
 
-// out[vertex(r), :] = sum of the partial rows of cut row r, in group order: the row starts in
-// group g0 (whose end-of-group slot holds its head), runs through whole groups (end-of-group
-// slots) and ends in group g1 (whose start-of-group slot holds its tail).  Fp lanes (a power of
-// two >= min(F, 64)) work on one row, eight independent loads at a time; the additions stay in
-// group order, so the result does not depend on the launch shape.
+// out[vertex(r), :] = sum of the partial rows of cut row r: the row starts in group g0 (whose
+// end-of-group slot holds its head), runs through whole groups (end-of-group slots) and ends in
+// group g1 (whose start-of-group slot holds its tail).  Fp lanes (a power of two >= min(F, 64)) add a
+// row's pieces in group order, eight loads in flight.  A row of more than kManyPieces is left to
+// the workgroup, whose 256 / Fp teams of lanes each take every so-manieth piece and are added in team
+// order: one team alone makes the longest row a chain of loads that nothing hides (340 pieces of a
+// 43,000-entry row: 24 of the launch's 24 us at F = 16; 7 us with the teams).  The order depends on
+// the table and the width only, never on timing.
+constexpr int kManyPieces = 24;
 __global__ __launch_bounds__(kBlock) void k_combine_cut_rows(const int32_t* __restrict__ cut_rows, int64_t n_cut,
                                                              const int32_t* __restrict__ rowptr,
                                                              const int32_t* __restrict__ row_ids, int gs, int F,
@@ -139,31 +138,67 @@ __global__ __launch_bounds__(kBlock) void k_combine_cut_rows(const int32_t* __re
                                                              const unsigned int* __restrict__ only_bits,
                                                              float* __restrict__ out, int n,
                                                              float* __restrict__ vpart) {
-    const int Fp = 1 << log2Fp;
+    __shared__ int32_t list[kBlock];
+    __shared__ int count;
+    __shared__ float part[kBlock];
+    const int Fp = 1 << log2Fp, lane = threadIdx.x & (Fp - 1), team = threadIdx.x >> log2Fp;
+    if (threadIdx.x == 0) count = 0;
+    __syncthreads();
+    // where cut row r goes (NULL: it is not a row of this launch -- if-else baseline, inner path on shared arrays)
+    auto target = [&](int32_t r) -> float* {
+        const int32_t v = row_ids ? row_ids[r] : r;
+        if (vpart && v >= n) return vpart + (size_t)(v - n) * F;  // one section's share of a vertex's list
+        if (only_bits && !((only_bits[v >> 5] >> (v & 31)) & 1u)) return nullptr;
+        return out + (size_t)v * F;
+    };
     const int64_t k = ((int64_t)blockIdx.x * kBlock + threadIdx.x) >> log2Fp;
-    if (k >= n_cut) return;
-    const int32_t r = cut_rows[k];
-    int32_t v = row_ids ? row_ids[r] : r;
-    if (vpart && v >= n) {  // partitioned layout: the row is one section's share of a vertex's list
-        out = vpart;
-        v -= n;
-    } else if (only_bits && !((only_bits[v >> 5] >> (v & 31)) & 1u)) {
-        return;  // not a row of this launch (if-else baseline; inner path on shared arrays)
-    }
-    const int64_t g0 = rowptr[r] / gs, g1 = ((int64_t)rowptr[r + 1] - 1) / gs;
-    for (int f = threadIdx.x & (Fp - 1); f < F; f += Fp) {
-        float sum = 0.0f;
-        int64_t g = g0;
-        for (; g + 8 <= g1; g += 8) {
-            float x[8];
+    if (k < n_cut) {
+        const int32_t r = cut_rows[k];
+        float* __restrict__ o = target(r);
+        const int64_t g0 = rowptr[r] / gs, g1 = ((int64_t)rowptr[r + 1] - 1) / gs;
+        if (g1 - g0 >= kManyPieces) {
+            if (o && lane == 0) list[atomicAdd(&count, 1)] = r;
+        } else if (o) {
+            for (int f = lane; f < F; f += Fp) {
+                float sum = 0.0f;
+                int64_t g = g0;
+                for (; g + 8 <= g1; g += 8) {
+                    float x[8];
 #pragma unroll
-            for (int i = 0; i < 8; ++i) x[i] = pieces[((g + i) * 2 + 1) * F + f];
+                    for (int i = 0; i < 8; ++i) x[i] = pieces[((g + i) * 2 + 1) * F + f];
 #pragma unroll
-            for (int i = 0; i < 8; ++i) sum += x[i];
+                    for (int i = 0; i < 8; ++i) sum += x[i];
+                }
+                for (; g < g1; ++g) sum += pieces[(g * 2 + 1) * F + f];
+                sum += pieces[(g1 * 2) * F + f];
+                o[f] = sum;
+            }
         }
-        for (; g < g1; ++g) sum += pieces[(g * 2 + 1) * F + f];
-        sum += pieces[(g1 * 2) * F + f];
-        out[(size_t)v * F + f] = sum;
+    }
+    __syncthreads();
+    const int n_long = count, teams = kBlock >> log2Fp;
+    for (int i = 0; i < n_long; ++i) {
+        const int32_t r = list[i];
+        float* __restrict__ o = target(r);
+        const int64_t g0 = rowptr[r] / gs, g1 = ((int64_t)rowptr[r + 1] - 1) / gs;
+        for (int f0 = 0; f0 < F; f0 += Fp) {
+            const int f = f0 + lane;
+            float sum = 0.0f;
+            for (int64_t g = g0 + team; g < g1; g += 8 * teams) {
+                float x[8];
+#pragma unroll
+                for (int j = 0; j < 8; ++j) x[j] = f < F && g + j * teams < g1 ? pieces[((g + j * teams) * 2 + 1) * F + f] : 0.0f;
+#pragma unroll
+                for (int j = 0; j < 8; ++j) sum += x[j];
+            }
+            part[threadIdx.x] = sum;
+            __syncthreads();
+            if (team == 0 && f < F) {
+                for (int j = 1; j < teams; ++j) sum += part[(j << log2Fp) + lane];
+                o[f] = sum + pieces[(g1 * 2) * F + f];
+            }
+            __syncthreads();  // `part` is written again
+        }
     }
 }
 
@@ -641,6 +676,16 @@ int epp_build_schedule(epp_path* p, int gs, hipStream_t s, Schedule** out) {
     return EPP_OK;
 }
 
+// all-active graph: vertices without any entry become zero
+int epp_zero_empty_rows(const epp_path* p, float* out, int F, hipStream_t s) {
+    if (p->n_empty_rows == 0) return EPP_OK;
+    const int64_t total = p->n_empty_rows * F;
+    hipLaunchKernelGGL(k_zero_rows, dim3((unsigned)((total + kBlock - 1) / kBlock)), dim3(kBlock), 0, s,
+                       p->empty_rows.as<int32_t>(), p->n_empty_rows, F, out);
+    EPP_HIP_TRY(hipGetLastError());
+    return EPP_OK;
+}
+
 int epp_launch_aggregate(epp_path* p, Schedule* sc, int log2_slices, const float* in, float* out, int F, hipStream_t s,
                          const unsigned int* row_bits, const unsigned int* src_bits, const Partition* part,
                          const unsigned int* inner_rows) {
@@ -660,12 +705,7 @@ int epp_launch_aggregate(epp_path* p, Schedule* sc, int log2_slices, const float
     const int32_t* rowptr = part ? part->vptr.as<int32_t>() : p->rowptr.as<int32_t>();
     float* pieces = sc->pieces_for(F);
     if (sc->n_split_rows > 0 && !pieces) { epp_set_error("no partial-row buffer for F=%d", F); return EPP_ERR_INVALID_ARG; }
-    if (p->n_empty_rows > 0 && !row_bits) {  // all-active graph: vertices without any entry become zero
-        const int64_t total = p->n_empty_rows * F;
-        hipLaunchKernelGGL(k_zero_rows, dim3((unsigned)((total + kBlock - 1) / kBlock)), dim3(kBlock), 0, s,
-                           p->empty_rows.as<int32_t>(), p->n_empty_rows, (const int32_t*)nullptr, F,
-                           (const unsigned int*)nullptr, out);
-    }
+    if (!row_bits) EPP_TRY(epp_zero_empty_rows(p, out, F, s));
     if (sc->n_groups > 0) {
         AggArgs a;
         a.cv = reinterpret_cast<const int2v*>(part ? part->cv2.p : p->cv.p);

@@ -12,7 +12,8 @@ thread_local char g_err[512] = "";
 epp_path::WidthCfg* width_cfg(epp_path* p, int F) {
     for (auto& w : p->widths)
         if (w.F == F) return &w;
-    p->widths.push_back(epp_path::WidthCfg{F, 0, nullptr, 0, nullptr});
+    p->widths.emplace_back();
+    p->widths.back().F = F;
     return &p->widths.back();
 }
 
@@ -33,8 +34,17 @@ int prepare_width(epp_path* self, int F, hipStream_t s, epp_path::WidthCfg** out
     epp_path* p = entries_of(self);
     self->last_F = F;
     epp_path::WidthCfg* w = width_cfg(p, F);
-    if (!w->sched) {
+    if (!w->prepared) {
         EPP_TRY(epp_ensure_canonical(p, s));  // (given back while all widths ran on reconstructed copies)
+        // small paths run without tables; a group size asked for is a group table asked for, and so is the
+        // if-else baseline, which only the all-active handle serves
+        w->rows = w->forced_gs <= 0 && epp_rows_kernel_fits(p, F);
+        if (w->rows) EPP_TRY(epp_build_rows_plan(p, F, s, &w->plan));
+        if (w->rows && !p->all_rows) {
+            w->prepared = true;
+            if (out) *out = w;
+            return EPP_OK;
+        }
         const int gs = w->forced_gs > 0 ? w->forced_gs : epp_default_group_size(p, F);
         Schedule* sc = find_schedule(p, gs);
         if (!sc) EPP_TRY(epp_build_schedule(p, gs, s, &sc));
@@ -45,6 +55,7 @@ int prepare_width(epp_path* self, int F, hipStream_t s, epp_path::WidthCfg** out
         // layout (the all-active handle also serves the if-else baseline, which never does)
         if (!w->part || p->all_rows) EPP_TRY(sc->ensure_pieces(F, epp_alloc_of(p)));
         w->sched = sc;
+        w->prepared = true;
         EPP_HIP_TRY(hipStreamSynchronize(s));
         epp_release_canonical_if_unused(p);
     }
@@ -67,12 +78,16 @@ int aggregate(epp_path* self, const float* in, float* out, int F, hipStream_t s,
     if (in == out) { epp_set_error("grad_in and grad_out must not alias"); return EPP_ERR_INVALID_ARG; }
     const epp_path::WidthCfg* w = nullptr;
     for (const auto& x : p->widths)
-        if (x.F == F && x.sched) w = &x;
+        if (x.F == F && x.prepared) w = &x;
     if (!w) {
         epp_set_error("width F=%d has not been prepared on this path: call epp_path_prepare_width first", F);
         return EPP_ERR_INVALID_ARG;
     }
     self->last_F = F;
+    if (w->rows && !row_bits) {
+        EPP_TRY(epp_zero_empty_rows(p, out, F, s));
+        return epp_launch_rows(p, w->plan, in, out, F, s, self->outer ? self->inner_rows : nullptr);
+    }
     // (the if-else baseline walks the whole graph in its given order: no partitioned layout)
     return epp_launch_aggregate(p, w->sched, w->log2_slices, in, out, F, s, row_bits, src_bits,
                                 row_bits ? nullptr : w->part, self->outer ? self->inner_rows : nullptr);
@@ -102,14 +117,18 @@ extern "C" int epp_path_info(const epp_path_t* p, epp_path_info_t* info) {
     bytes += p->zero_block.bytes + p->inner_pos.bytes;
     for (const Schedule* s : p->scheds) bytes += s->bytes();
     for (const auto& w : p->widths)
-        if (w.part) bytes += w.part->bytes();
+        bytes += (w.part ? w.part->bytes() : 0) + (w.plan ? w.plan->store.bytes : 0);
     if (p->pool->accounted_by == p) bytes += p->pool->bytes();  // shared by the handle's paths: reported once
     info->bytes = (int64_t)bytes;
     info->shares_entries = p->outer ? 1 : 0;
     // (a path that runs on the next outer path's arrays reports that path's tables as what it uses;
     // their bytes are part of the outer path's footprint)
     for (const auto& w : entries_of(p)->widths) {
-        if (w.F == p->last_F && w.sched) {
+        if (w.F == p->last_F && w.rows) {  // (no table: no row is cut; the group size is the one the selector names)
+            info->sched_F = w.F;
+            info->group_size = epp_default_group_size(entries_of(p), w.F);
+            info->n_groups = (entries_of(p)->nnz + info->group_size - 1) / info->group_size;
+        } else if (w.F == p->last_F && w.sched) {
             const Schedule* used = w.part ? w.part->sched : w.sched;
             info->sched_F = w.F;
             info->group_size = used->gs;
@@ -152,6 +171,9 @@ extern "C" int epp_path_set_group_size(epp_path_t* self, int F, int gs, epp_stre
     w->forced_gs = gs > 0 ? gs : 0;
     if (w->sched) w->sched->drop_pieces(F);  // a table shared with other widths keeps theirs
     w->sched = nullptr;
+    w->prepared = w->rows = false;
+    delete w->plan;
+    w->plan = nullptr;
     delete w->part;
     w->part = nullptr;
     // drop cached tables that no width refers to any more

@@ -215,6 +215,17 @@ struct Partition {
     }
 };
 
+// What the row kernel (epp_rows.hip) needs to know of the rows that one workgroup should not take alone:
+// they are cut into chunks, whose sums a second kernel adds.
+struct HugeRow { int v, first, count; };  // vertex, its first chunk and their number
+struct RowsPlan {
+    DevBuf store;
+    void* chunks = nullptr;   // entry range of every chunk
+    HugeRow* rows = nullptr;
+    float* pieces = nullptr;  // float[n_chunks][F]
+    int n_huge = 0, n_chunks = 0;
+};
+
 struct epp_path {
     int64_t n = 0;       // vertices of the input graph
     int64_t n_rows = 0;  // R: rows of the path in canonical form (all-active graph: n)
@@ -251,14 +262,23 @@ struct epp_path {
     DevBuf empty_rows;           // int32[n_empty_rows] vertices with empty lists
     std::vector<Schedule*> scheds;
     // per-width choices
-    // sched == NULL: the width has not been prepared (epp_path_prepare_width); slices: XCD feature slicing
-    // part: source-partitioned layout of this width, if it pays (owned by the path)
-    struct WidthCfg { int F; int forced_gs; Schedule* sched; int log2_slices; Partition* part; };
+    // prepared: epp_path_prepare_width has been called; rows: launches run the row kernel, which needs no
+    // group table (sched may be NULL then) and a plan only where some row is very long; slices: XCD feature slicing; part: source-partitioned layout
+    // of this width, if it pays (owned by the path)
+    struct WidthCfg {
+        int F;
+        int forced_gs = 0;
+        bool prepared = false, rows = false;
+        RowsPlan* plan = nullptr;
+        Schedule* sched = nullptr;
+        int log2_slices = 0;
+        Partition* part = nullptr;
+    };
     std::vector<WidthCfg> widths;
     int last_F = 0;
     ~epp_path() {
         for (Schedule* s : scheds) delete s;
-        for (auto& w : widths) delete w.part;
+        for (auto& w : widths) { delete w.part; delete w.plan; }
     }
 };
 
@@ -316,10 +336,15 @@ int epp_build_schedule(epp_path* p, int gs, hipStream_t s, Schedule** out);
 int epp_launch_aggregate(epp_path* p, Schedule* sc, int log2_slices, const float* in, float* out, int F, hipStream_t s,
                          const unsigned int* row_bits = nullptr, const unsigned int* src_bits = nullptr,
                          const Partition* part = nullptr, const unsigned int* inner_rows = nullptr);
+// rows.hip: one launch that processes rows whole, for small paths
+bool epp_rows_kernel_fits(const epp_path* p, int F);
+int epp_build_rows_plan(epp_path* p, int F, hipStream_t s, RowsPlan** out);  // *out = NULL: none needed
+int epp_launch_rows(const epp_path* p, const RowsPlan* plan, const float* in, float* out, int F, hipStream_t s, const unsigned int* inner_rows);
 // group table over any (row pointer, entry count); not registered with the path
 int epp_build_schedule_over(const epp_path* p, const int32_t* rowptr, int64_t n_rows, int64_t nnz, int gs, hipStream_t s,
                             Schedule** out);
 int epp_default_group_size(const epp_path* p, int F);
+int epp_zero_empty_rows(const epp_path* p, float* out, int F, hipStream_t s);
 int epp_tune_locality(epp_path* p, int F, int gs, hipStream_t s, int* log2_slices, Partition** part);
 
 // partition.hip

@@ -556,7 +556,7 @@ bool epp_canonical_unused(const epp_path* p, int F_with_copy) {
     bool any = F_with_copy > 0;
     for (const auto& w : p->widths) {
         if (w.F == F_with_copy) continue;
-        if (w.sched && !w.part) return false;  // a width that launches on the canonical array
+        if (w.prepared && !w.part) return false;  // a width that launches on the canonical array
         any |= (w.part != nullptr);
     }
     return any;

@@ -91,7 +91,7 @@ struct SmallArgs {
     int32_t* row_ids;             // L x n
     int32_t* out_rowptr;          // L x (n + 1)
     int* newptr;                  // n + 1 (scratch)
-    long long* result;            // [0] error bits, [1] |N^0|, then kLevelWords per level
+    long long* result;            // pinned host words: [0] error bits, [1] |N^0|, then kLevelWords per level
 };
 
 __global__ __launch_bounds__(kThreads) void k_prepare_small(SmallArgs a) {
@@ -294,16 +294,15 @@ int epp_prepare_small(const epp_csr_t* g, const int32_t* train_ids, int64_t n_tr
     DevArena arena;
     EPP_TRY(arena.reserve((size_t)(L + 1) * DevArena::rounded(bm_bytes) + DevArena::rounded(ids_bytes) +
                           (size_t)L * (DevArena::rounded(cv_bytes) + DevArena::rounded(ids_bytes) + DevArena::rounded(ptr_bytes)) +
-                          DevArena::rounded(ptr_bytes) + DevArena::rounded(result_words * 8), al));
+                          DevArena::rounded(ptr_bytes), al));
     // (every level's arrays start 256-byte aligned: the strides are the rounded sizes)
-    DevBuf bm_all, set0, cv_all, ids_all, ptr_all, newptr, result;
+    DevBuf bm_all, set0, cv_all, ids_all, ptr_all, newptr;
     arena.take(&bm_all, (size_t)(L + 1) * DevArena::rounded(bm_bytes));
     arena.take(&set0, ids_bytes);
     arena.take(&cv_all, (size_t)L * DevArena::rounded(cv_bytes));
     arena.take(&ids_all, (size_t)L * DevArena::rounded(ids_bytes));
     arena.take(&ptr_all, (size_t)L * DevArena::rounded(ptr_bytes));
     arena.take(&newptr, ptr_bytes);
-    arena.take(&result, result_words * 8);
     PinnedWords pinned;
     EPP_TRY(pinned.get(result_words));
     long long* host = pinned.p;
@@ -327,10 +326,9 @@ int epp_prepare_small(const epp_csr_t* g, const int32_t* train_ids, int64_t n_tr
     a.row_ids = ids_all.as<int32_t>();
     a.out_rowptr = ptr_all.as<int32_t>();
     a.newptr = newptr.as<int>();
-    a.result = result.as<long long>();
+    a.result = host;  // (the kernel writes a few dozen words there itself: a copy would be a launch of its own)
     hipLaunchKernelGGL(k_prepare_small, dim3(1), dim3(kThreads), 0, s, a);
     EPP_HIP_TRY(hipGetLastError());
-    EPP_HIP_TRY(hipMemcpyAsync(host, result.p, result_words * 8, hipMemcpyDeviceToHost, s));
     EPP_HIP_TRY(hipStreamSynchronize(s));
     if (host[0] != 0) {
         if (host[0] & 2) { epp_set_error("training id outside [0, %lld)", (long long)n); return EPP_ERR_OUT_OF_RANGE_ID; }

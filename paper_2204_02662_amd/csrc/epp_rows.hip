@@ -1,0 +1,362 @@
+// Gather-reduce over whole rows (Alg. 2, aggregation loop): small paths, and very narrow rows.
+//
+// On a small path the group kernel (epp_aggregate.hip) is bound by launches and dependent loads, not by
+// what it moves: two kernels of about 5 us each (groups, then the rows cut by their boundaries), and in
+// the first a chain of group table -> row id and pairs -> LDS -> gathers.  Here a row is processed
+// whole, so that nothing is left to add up afterwards and no table has to be built beforehand:
+//   * T lanes read a source row, four floats each (the last of them steps back so that it ends at
+//     the row's end: rows of any width are read 16 bytes at a time; a row of three floats or less is
+//     one access); P such slots share a row's entries, U at a time each, and add their sums by
+//     exchanging lanes;
+//   * a row of more than `limit` entries is left to the whole workgroup, which takes the long rows
+//     among its own one after the other;
+//   * a row of more than a few steps of a workgroup is cut into chunks, one workgroup each, at the
+//     front of the grid; a second kernel adds the chunks' sums.
+// The order of the additions depends on the path and the width only: equal inputs give equal bits.
+//
+// Measured (us, rows / groups): 7,107 entries in 1,700 rows, F = 16: 5.5 / 10.6; 44,405 in 14,925, F = 64:
+// 10.3 / 14.9; 1.3 M in 322,705, F = 16: 33.9 / 58.7; 4.2 M in 100,000 (longest 43,347), F = 4: 35.6 / 119.
+
+#include <cstdlib>
+
+#include "epp_internal.h"
+
+namespace {
+
+constexpr int kBlock = 256;
+constexpr int kU = 4;  // entries in flight per slot (eight cost half the wavefronts in flight and gain nothing)
+
+typedef int int2v __attribute__((ext_vector_type(2)));
+
+// VEC floats at 4-byte alignment (global accesses need no more): one access of 4 VEC bytes.  (Three
+// floats element by element: a vector of three is read and written as one of four.)
+template <int VEC>
+__device__ __forceinline__ void load_frag(const float* __restrict__ p, float (&x)[VEC]) {
+    if constexpr (VEC == 1 || VEC == 3) {
+#pragma unroll
+        for (int i = 0; i < VEC; ++i) x[i] = p[i];
+    } else {
+        typedef float vec_t __attribute__((ext_vector_type(VEC), aligned(4)));
+        const vec_t v = *reinterpret_cast<const vec_t*>(p);
+#pragma unroll
+        for (int i = 0; i < VEC; ++i) x[i] = v[i];
+    }
+}
+template <int VEC>
+__device__ __forceinline__ void store_frag(float* __restrict__ p, const float (&x)[VEC]) {
+    if constexpr (VEC == 1 || VEC == 3) {
+#pragma unroll
+        for (int i = 0; i < VEC; ++i) p[i] = x[i];
+    } else {
+        typedef float vec_t __attribute__((ext_vector_type(VEC), aligned(4)));
+        vec_t v;
+#pragma unroll
+        for (int i = 0; i < VEC; ++i) v[i] = x[i];
+        *reinterpret_cast<vec_t*>(p) = v;
+    }
+}
+
+struct RowArgs {
+    const int2v* cv;
+    const int32_t* rowptr;
+    const int32_t* row_ids;  // NULL: identity
+    int n_rows;
+    const float* in;
+    float* out;
+    int F;
+    int log2p;               // slots per row
+    int limit;               // longest row that is not left to the workgroup
+    int huge;                // longest row that is not cut into chunks
+    int has_long;            // some row is longer than `limit`
+    int chunk_blocks;        // workgroups that take one chunk of a cut row each, before the others
+    const int2v* chunks;     // their entries [x, y); empty: no such chunk
+    float* pieces;           // their sums, F floats each
+    // launch for the inner path that shares the arrays only
+    const float* zero;           // what an entry that is not the inner path's gathers
+    const unsigned int* only;    // bitmap of the inner path's rows
+};
+
+// acc += sum of the entries j0, j0 + 1, .. (U at a time, `step` apart) of [j0, p1).  The pairs of the
+// next step are fetched while the rows of this one are on their way.
+template <int VEC, int U, bool INNER>
+__device__ __forceinline__ void add_entries(const RowArgs& a, const float* __restrict__ src, int j0, int p1, int step,
+                                            float (&acc)[VEC]) {
+    if (j0 >= p1) return;
+    int2v e[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) e[u] = a.cv[min(j0 + u, p1 - 1)];
+    for (int j = j0; j < p1; j += step) {
+        float x[U][VEC];
+        float w[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const float* p = src + (size_t)(e[u].x & kEntCol) * (size_t)a.F;
+            if constexpr (INNER) p = (e[u].x & kEntOuterOnly) ? a.zero : p;
+            load_frag<VEC>(p, x[u]);
+            w[u] = j + u < p1 ? __int_as_float(e[u].y) : 0.0f;
+        }
+        if (j + step < p1) {
+#pragma unroll
+            for (int u = 0; u < U; ++u) e[u] = a.cv[min(j + step + u, p1 - 1)];
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+#pragma unroll
+            for (int i = 0; i < VEC; ++i) acc[i] = fmaf(w[u], x[u][i], acc[i]);
+        }
+    }
+}
+
+// o[f ..] of the calling thread's lanes = sum of the entries [q0, q1), by the whole workgroup.
+template <int VEC, int LOG2T, bool INNER>
+__device__ __forceinline__ void sum_by_workgroup(const RowArgs& a, int q0, int q1, float* __restrict__ o,
+                                                 float (*part)[(1 << LOG2T) * VEC]) {
+    constexpr int T = 1 << LOG2T;
+    const int t = threadIdx.x & (T - 1), slot = threadIdx.x >> LOG2T;
+    for (int f0 = 0; f0 < a.F; f0 += T * VEC) {
+        const bool fok = f0 + t * VEC < a.F;
+        const int f = fok ? min(f0 + t * VEC, a.F - VEC) : 0;
+        float acc[VEC];
+#pragma unroll
+        for (int i = 0; i < VEC; ++i) acc[i] = 0.0f;
+        add_entries<VEC, kU, INNER>(a, a.in + f, q0 + slot * kU, q1, (kBlock >> LOG2T) * kU, acc);
+#pragma unroll
+        for (int d = T; d < 64; d <<= 1) {
+#pragma unroll
+            for (int i = 0; i < VEC; ++i) acc[i] += __shfl_xor(acc[i], d, 64);
+        }
+        if ((threadIdx.x & 63) < T) {
+#pragma unroll
+            for (int i = 0; i < VEC; ++i) part[threadIdx.x >> 6][t * VEC + i] = acc[i];
+        }
+        __syncthreads();
+        if (threadIdx.x < T && fok) {
+            float r[VEC];
+#pragma unroll
+            for (int i = 0; i < VEC; ++i) {
+                float sum = part[0][t * VEC + i];
+#pragma unroll
+                for (int w = 1; w < kBlock / 64; ++w) sum += part[w][t * VEC + i];
+                r[i] = sum;
+            }
+            store_frag<VEC>(o + f, r);
+        }
+        __syncthreads();  // `part` is written again
+    }
+}
+
+template <int VEC, int LOG2T, bool INNER>
+__global__ __launch_bounds__(kBlock, 7) void k_aggregate_rows(RowArgs a) {
+    constexpr int T = 1 << LOG2T;
+    __shared__ int list[kBlock];
+    __shared__ int count;
+    __shared__ float part[kBlock / 64][T * VEC];
+    if ((int)blockIdx.x < a.chunk_blocks) {
+        const int2v c = a.chunks[blockIdx.x];
+        if (c.x < c.y) sum_by_workgroup<VEC, LOG2T, INNER>(a, c.x, c.y, a.pieces + (size_t)blockIdx.x * a.F, part);
+        return;
+    }
+    const int t = threadIdx.x & (T - 1), slot = threadIdx.x >> LOG2T;
+    const int P = 1 << a.log2p, sub = slot & (P - 1);
+    const int r = ((int)blockIdx.x - a.chunk_blocks) * (kBlock >> (LOG2T + a.log2p)) + (slot >> a.log2p);
+    const bool has = r < a.n_rows;
+    const int p0 = has ? a.rowptr[r] : 0, p1 = has ? a.rowptr[r + 1] : 0;
+    const int v = has ? (a.row_ids ? a.row_ids[r] : r) : 0;
+    const bool is_long = p1 - p0 > a.limit;
+    bool write = has && !is_long && sub == 0;
+    if constexpr (INNER) write = write && ((a.only[v >> 5] >> (v & 31)) & 1u);
+    if (a.has_long) {
+        if (threadIdx.x == 0) count = 0;
+        __syncthreads();
+        if (is_long && p1 - p0 <= a.huge && t == 0 && sub == 0) list[atomicAdd(&count, 1)] = r;
+    }
+    for (int f0 = 0; f0 < a.F; f0 += T * VEC) {
+        const bool fok = f0 + t * VEC < a.F;
+        const int f = fok ? min(f0 + t * VEC, a.F - VEC) : 0;
+        float acc[VEC];
+#pragma unroll
+        for (int i = 0; i < VEC; ++i) acc[i] = 0.0f;
+        add_entries<VEC, kU, INNER>(a, a.in + f, p0 + sub * kU, is_long ? p0 : p1, P * kU, acc);
+        for (int d = T; d < T * P; d <<= 1) {
+#pragma unroll
+            for (int i = 0; i < VEC; ++i) acc[i] += __shfl_xor(acc[i], d, 64);
+        }
+        if (write && fok) store_frag<VEC>(a.out + (size_t)v * a.F + f, acc);
+    }
+    if (!a.has_long) return;
+    __syncthreads();
+    const int n_long = count;
+    for (int k = 0; k < n_long; ++k) {
+        const int lr = list[k], q0 = a.rowptr[lr], q1 = a.rowptr[lr + 1];
+        const int lv = a.row_ids ? a.row_ids[lr] : lr;
+        if constexpr (INNER) {
+            if (!((a.only[lv >> 5] >> (lv & 31)) & 1u)) continue;  // (uniform)
+        }
+        sum_by_workgroup<VEC, LOG2T, INNER>(a, q0, q1, a.out + (size_t)lv * a.F, part);
+    }
+}
+
+// Rows of more than `chunk` entries: their chunks, and what the chunks' sums are to be added to.
+__global__ __launch_bounds__(kBlock) void k_cut_huge_rows(const int32_t* __restrict__ rowptr,
+                                                          const int32_t* __restrict__ row_ids, int n_rows, int chunk,
+                                                          int* __restrict__ counters, int2v* __restrict__ chunks,
+                                                          HugeRow* __restrict__ rows) {
+    const int r = blockIdx.x * kBlock + threadIdx.x;
+    if (r >= n_rows) return;
+    const int p0 = rowptr[r], p1 = rowptr[r + 1];
+    if (p1 - p0 <= chunk) return;
+    const int cnt = (p1 - p0 + chunk - 1) / chunk;
+    const int first = atomicAdd(&counters[0], cnt);
+    rows[atomicAdd(&counters[1], 1)] = HugeRow{row_ids ? row_ids[r] : r, first, cnt};
+    for (int i = 0; i < cnt; ++i) chunks[first + i] = int2v{p0 + i * chunk, min(p0 + (i + 1) * chunk, p1)};
+}
+
+// out[v] = sum of the chunks of v's row, in a fixed order.  One wavefront per row: the pieces are
+// dealt to 64 >> log2t groups of lanes, eight in flight each.
+__global__ __launch_bounds__(kBlock) void k_add_chunks(const HugeRow* __restrict__ rows, int n_huge,
+                                                       const float* __restrict__ pieces, int F, int log2t,
+                                                       const unsigned int* __restrict__ only, float* __restrict__ out) {
+    const int k = blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6);
+    if (k >= n_huge) return;
+    const HugeRow h = rows[k];
+    if (only && !((only[h.v >> 5] >> (h.v & 31)) & 1u)) return;
+    const int T = 1 << log2t, lane = threadIdx.x & 63, sub = lane >> log2t, S = 64 >> log2t;
+    const float* __restrict__ p = pieces + (size_t)h.first * F;
+    for (int f0 = 0; f0 < F; f0 += T) {
+        const int f = f0 + (lane & (T - 1));
+        float sum = 0.0f;
+        for (int c = sub; c < h.count; c += 8 * S) {
+            float x[8];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) x[i] = f < F && c + i * S < h.count ? p[(size_t)(c + i * S) * F + f] : 0.0f;
+#pragma unroll
+            for (int i = 0; i < 8; ++i) sum += x[i];
+        }
+        for (int d = T; d < 64; d <<= 1) sum += __shfl_xor(sum, d, 64);
+        if (f < F && sub == 0) out[(size_t)h.v * F + f] = sum;
+    }
+}
+
+template <int VEC, int LOG2T>
+void launch(const RowArgs& a, hipStream_t s) {
+    const int per_block = kBlock >> (LOG2T + a.log2p);
+    const dim3 grid((unsigned)(a.chunk_blocks + (a.n_rows + per_block - 1) / per_block));
+    if (a.zero) hipLaunchKernelGGL((k_aggregate_rows<VEC, LOG2T, true>), grid, dim3(kBlock), 0, s, a);
+    else hipLaunchKernelGGL((k_aggregate_rows<VEC, LOG2T, false>), grid, dim3(kBlock), 0, s, a);
+}
+
+}  // namespace
+
+// Lanes per source row, and the entries of a chunk: eight steps of the workgroup.
+static int lanes_log2(int F) {
+    const int frags = (F + 3) / 4;
+    int l = 0;
+    while ((1 << l) < frags && l < 6) ++l;
+    return l;
+}
+static int chunk_log2(int F) { return 13 - lanes_log2(F); }
+static_assert((1 << 13) == 8 * kBlock * kU, "chunk length");
+
+// Which paths run here.  Rows of 16 bytes and less always: the group kernel's lanes then each carry a
+// group of their own and read pairs far apart (F = 4: 1.5 to 3.3 times slower at 0.4 to 26 M entries).
+// Rows of up to 64 bytes while the second kernel and the chain of loads still show: up to 10 M entries
+// (F = 16: 1.4 to 1.6 times faster at 0.4 M, 0.9 to 1.25 times at 4 to 10 M, even from 20 M on).  Wider
+// rows while the launches do: at 16 M floats of gathered rows (F = 64: 250,000 entries) the two are even.
+bool epp_rows_kernel_fits(const epp_path* p, int F) {
+    if (const char* e = std::getenv("EPP_TUNE_ROWS")) {  // 0: never, 2: always (tests, measurements)
+        if (*e == '0') return false;
+        if (*e == '2') return p->nnz <= (1 << 30);
+    }
+    // (the switches that force a layout on the group kernel ask for that kernel)
+    const char* part = std::getenv("EPP_TUNE_PART");
+    if ((part && *part == '2') || std::getenv("EPP_TUNE_HOT_MB") || std::getenv("EPP_TUNE_LOG2_SLICES")) return false;
+    if (F <= 4) return p->nnz <= (1 << 30);
+    if (F <= 16) return p->nnz <= 10000000;
+    return p->nnz * F <= 16000000;
+}
+
+int epp_build_rows_plan(epp_path* p, int F, hipStream_t s, RowsPlan** out) {
+    *out = nullptr;
+    // rows of 2^(c-1) < length <= 2^c are counted in class c
+    const int c0 = chunk_log2(F);
+    int64_t n_huge = 0, n_chunks = 0;
+    for (int c = c0 + 1; c < EPP_NCLASS; ++c) {
+        n_huge += p->len_hist[c];
+        n_chunks += p->len_hist[c] << (c - c0);
+    }
+    if (n_huge == 0) return EPP_OK;
+    RowsPlan* q = new RowsPlan();
+    struct Guard { RowsPlan* q; ~Guard() { delete q; } } guard{q};
+    const epp_alloc_t* al = epp_alloc_of(p);
+    q->n_huge = (int)n_huge;
+    q->n_chunks = (int)n_chunks;  // (an upper bound)
+    const size_t table = DevArena::rounded((size_t)n_chunks * 8) + DevArena::rounded(8);
+    EPP_TRY(q->store.alloc(table + DevArena::rounded((size_t)n_huge * sizeof(HugeRow)) + (size_t)n_chunks * F * 4, al));
+    q->chunks = q->store.p;
+    q->rows = reinterpret_cast<HugeRow*>(q->store.as<char>() + table);
+    q->pieces = reinterpret_cast<float*>(q->store.as<char>() + table + DevArena::rounded((size_t)n_huge * sizeof(HugeRow)));
+    EPP_HIP_TRY(hipMemsetAsync(q->store.p, 0, table, s));
+    hipLaunchKernelGGL(k_cut_huge_rows, dim3((unsigned)((p->n_stream_rows + kBlock - 1) / kBlock)), dim3(kBlock), 0, s,
+                       p->rowptr.as<int32_t>(), p->row_ids.p ? p->row_ids.as<int32_t>() : nullptr, (int)p->n_stream_rows,
+                       1 << c0, reinterpret_cast<int*>(q->store.as<char>() + DevArena::rounded((size_t)n_chunks * 8)),
+                       static_cast<int2v*>(q->chunks), q->rows);
+    EPP_HIP_TRY(hipGetLastError());
+    EPP_HIP_TRY(hipStreamSynchronize(s));
+    guard.q = nullptr;
+    *out = q;
+    return EPP_OK;
+}
+
+int epp_launch_rows(const epp_path* p, const RowsPlan* plan, const float* in, float* out, int F, hipStream_t s,
+                    const unsigned int* inner_rows) {
+    if (p->n_stream_rows == 0) return EPP_OK;
+    RowArgs a;
+    a.cv = reinterpret_cast<const int2v*>(p->cv.p);
+    a.rowptr = p->rowptr.as<int32_t>();
+    a.row_ids = p->row_ids.p ? p->row_ids.as<int32_t>() : nullptr;
+    a.n_rows = (int)p->n_stream_rows;
+    a.in = in;
+    a.out = out;
+    a.F = F;
+    a.zero = inner_rows ? p->zero_block.as<float>() : nullptr;
+    a.only = inner_rows;
+    const int log2t = lanes_log2(F);
+    // as many slots per row as its entries keep busy on average, but no more wavefronts than two or three
+    // rounds of the chip (the chain of loads is then paid once per round instead of once)
+    const double per_row = (double)p->nnz / (double)p->n_stream_rows;
+    int log2p = 0;
+    while (log2p + log2t < 6 && (double)(kU << log2p) < per_row) ++log2p;
+    while (log2p > 0 && (p->n_stream_rows << (log2t + log2p)) >> 6 > 16384) --log2p;
+    a.log2p = log2p;
+    a.huge = 1 << chunk_log2(F);
+    a.limit = std::min((8 * kU) << log2p, a.huge);
+    a.has_long = p->max_len > a.limit;
+    a.chunk_blocks = plan ? plan->n_chunks : 0;
+    a.chunks = plan ? static_cast<const int2v*>(plan->chunks) : nullptr;
+    a.pieces = plan ? plan->pieces : nullptr;
+    if (F >= 4) {
+        switch (log2t) {
+            case 0: launch<4, 0>(a, s); break;
+            case 1: launch<4, 1>(a, s); break;
+            case 2: launch<4, 2>(a, s); break;
+            case 3: launch<4, 3>(a, s); break;
+            case 4: launch<4, 4>(a, s); break;
+            case 5: launch<4, 5>(a, s); break;
+            default: launch<4, 6>(a, s); break;
+        }
+    } else if (F == 3) {
+        launch<3, 0>(a, s);
+    } else if (F == 2) {
+        launch<2, 0>(a, s);
+    } else {
+        launch<1, 0>(a, s);
+    }
+    if (plan) {
+        int log2f = 0;
+        while ((1 << log2f) < F && log2f < 6) ++log2f;
+        hipLaunchKernelGGL(k_add_chunks, dim3((unsigned)((plan->n_huge + kBlock / 64 - 1) / (kBlock / 64))), dim3(kBlock), 0, s,
+                           plan->rows, plan->n_huge, plan->pieces, F, log2f, inner_rows, out);
+    }
+    EPP_HIP_TRY(hipGetLastError());
+    return EPP_OK;
+}
