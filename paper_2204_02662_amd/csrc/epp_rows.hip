@@ -260,8 +260,10 @@ static_assert((1 << 13) == 8 * kBlock * kU, "chunk length");
 // Which paths run here.  Rows of 16 bytes and less always: the group kernel's lanes then each carry a
 // group of their own and read pairs far apart (F = 4: 1.5 to 3.3 times slower at 0.4 to 26 M entries).
 // Rows of up to 64 bytes while the second kernel and the chain of loads still show: up to 10 M entries
-// (F = 16: 1.4 to 1.6 times faster at 0.4 M, 0.9 to 1.25 times at 4 to 10 M, even from 20 M on).  Wider
-// rows while the launches do: at 16 M floats of gathered rows (F = 64: 250,000 entries) the two are even.
+// (F = 16: 1.4 to 1.7 times faster at 0.4 M, 1.0 to 1.3 times at 4 to 10 M, even from 20 M on).  Wider
+// rows while the launches do: at 16 M floats of gathered rows (F = 64: 250,000 entries) the two are
+// even, at twice as many where the width is not a multiple of four (the group kernel then reads
+// four bytes a lane; F = 47: 771,515 entries in 46.7 / 50.4 us).
 bool epp_rows_kernel_fits(const epp_path* p, int F) {
     if (const char* e = std::getenv("EPP_TUNE_ROWS")) {  // 0: never, 2: always (tests, measurements)
         if (*e == '0') return false;
@@ -272,7 +274,7 @@ bool epp_rows_kernel_fits(const epp_path* p, int F) {
     if ((part && *part == '2') || std::getenv("EPP_TUNE_HOT_MB") || std::getenv("EPP_TUNE_LOG2_SLICES")) return false;
     if (F <= 4) return p->nnz <= (1 << 30);
     if (F <= 16) return p->nnz <= 10000000;
-    return p->nnz * F <= 16000000;
+    return p->nnz * F <= (F % 4 ? 32000000 : 16000000);
 }
 
 int epp_build_rows_plan(epp_path* p, int F, hipStream_t s, RowsPlan** out) {
@@ -321,12 +323,13 @@ int epp_launch_rows(const epp_path* p, const RowsPlan* plan, const float* in, fl
     a.zero = inner_rows ? p->zero_block.as<float>() : nullptr;
     a.only = inner_rows;
     const int log2t = lanes_log2(F);
-    // as many slots per row as its entries keep busy on average, but no more wavefronts than two or three
-    // rounds of the chip (the chain of loads is then paid once per round instead of once)
+    // as many slots per row as its entries keep busy on average, but no more wavefronts than a few rounds
+    // of the chip, more of them the less each gathers (a round costs the whole chain of loads; F = 64,
+    // 1.5 M entries: 62 us against 90 us with a wavefront per row, where one slot's chain would not be longer)
     const double per_row = (double)p->nnz / (double)p->n_stream_rows;
     int log2p = 0;
     while (log2p + log2t < 6 && (double)(kU << log2p) < per_row) ++log2p;
-    while (log2p > 0 && (p->n_stream_rows << (log2t + log2p)) >> 6 > 16384) --log2p;
+    while (log2p > 0 && (p->n_stream_rows << (log2t + log2p)) >> 6 > (262144 >> log2t)) --log2p;
     a.log2p = log2p;
     a.huge = 1 << chunk_log2(F);
     a.limit = std::min((8 * kU) << log2p, a.huge);
