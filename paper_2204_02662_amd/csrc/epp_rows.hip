@@ -259,11 +259,10 @@ static_assert((1 << 13) == 8 * kBlock * kU, "chunk length");
 
 // Which paths run here.  Rows of 16 bytes and less always: the group kernel's lanes then each carry a
 // group of their own and read pairs far apart (F = 4: 1.5 to 3.3 times slower at 0.4 to 26 M entries).
-// Rows of up to 64 bytes while the second kernel and the chain of loads still show: up to 10 M entries
-// (F = 16: 1.4 to 1.7 times faster at 0.4 M, 1.0 to 1.3 times at 4 to 10 M, even from 20 M on).  Wider
-// rows while the launches do: at 16 M floats of gathered rows (F = 64: 250,000 entries) the two are
-// even, at twice as many where the width is not a multiple of four (the group kernel then reads
-// four bytes a lane; F = 47: 771,515 entries in 46.7 / 50.4 us).
+// Rows of up to 32 and 64 bytes while the second kernel and the chain of loads still show: up to 10 and
+// 5 M entries (F = 16: 1.2 to 1.9 times faster at 0.2 to 1 M, 1.05 to 1.35 times at 4 M, 0.9 to 1.2 at 6 to
+// 10 M, where matrices no longer stay in the memory-side cache between calls).  Wider rows while
+// the launches do: at 16 M floats of gathered rows (F = 64: 250,000 entries) the two are even.
 bool epp_rows_kernel_fits(const epp_path* p, int F) {
     if (const char* e = std::getenv("EPP_TUNE_ROWS")) {  // 0: never, 2: always (tests, measurements)
         if (*e == '0') return false;
@@ -273,8 +272,8 @@ bool epp_rows_kernel_fits(const epp_path* p, int F) {
     const char* part = std::getenv("EPP_TUNE_PART");
     if ((part && *part == '2') || std::getenv("EPP_TUNE_HOT_MB") || std::getenv("EPP_TUNE_LOG2_SLICES")) return false;
     if (F <= 4) return p->nnz <= (1 << 30);
-    if (F <= 16) return p->nnz <= 10000000;
-    return p->nnz * F <= (F % 4 ? 32000000 : 16000000);
+    if (F <= 16) return p->nnz <= (F <= 8 ? 10000000 : 5000000);
+    return p->nnz * F <= 16000000;
 }
 
 int epp_build_rows_plan(epp_path* p, int F, hipStream_t s, RowsPlan** out) {
