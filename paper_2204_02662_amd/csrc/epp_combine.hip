@@ -5,7 +5,10 @@
 // list of N^k only: the rows are gathered (and, for Y', scattered) by vertex id, everything
 // else is a dense contraction and runs on the matrix cores in fp32 (v_mfma_f32_32x32x2_f32).
 //
-// Both kernels give a workgroup of four wavefronts, arranged WM x WN, an output tile of
+// Widths of up to 128 (every weight matrix of an ordinary model) have kernels of their own, further down:
+// the whole product of a pair of rows fits a wavefront's registers, so nothing but W goes through LDS.
+//
+// For wider ones both kernels give a workgroup of four wavefronts, arranged WM x WN, an output tile of
 // 32 WM BM x 32 WN BN, every wavefront BM x BN accumulator blocks of 32 x 32, and step through
 // the contraction 32 at a time: the operand tiles of the next step are fetched into registers
 // while the matrix cores work on the current ones in LDS.  The arrangement follows the matrix:
@@ -28,6 +31,7 @@ constexpr int kBlock = 256;
 constexpr int kStep = 32;   // contraction step
 constexpr int kMaxWidth = 4096;
 constexpr int kMinChunkRows = 256;
+constexpr int kOneWorkgroup = 1024;  // rows that one workgroup takes alone
 constexpr int64_t kNoChunkLimit = (int64_t)1 << 40;
 
 typedef float float4v __attribute__((ext_vector_type(4)));
@@ -207,22 +211,287 @@ __global__ __launch_bounds__(kBlock) void k_weight_gradient(const int32_t* __res
         }
 }
 
-// W'[e] = sum over chunks: 16 threads per element take every 16th chunk each, accumulate in
-// double, and are added in lane order (the result does not depend on timing).
-__global__ __launch_bounds__(kBlock) void k_weight_gradient_reduce(const float* __restrict__ partial, int64_t n_chunks,
+// ---------------------------------------------------------------- widths of up to 128
+// Loads of a lane's share of a row: BLOCKS floats, one for each 32-wide block of the width.  VEC: they
+// are consecutive (lane p holds BLOCKS p, BLOCKS p + 1, ..: one wide load; the blocks then interleave,
+// which only permutes the products' rows or columns and is undone when they are written); else
+// float 32 i + p of block i, element by element, for widths that BLOCKS does not divide.  Lanes past
+// the width read what is there: their products are never written.
+template <int BLOCKS, bool VEC>
+__device__ __forceinline__ void load_share(const float* __restrict__ row, int width, int p, float (&x)[BLOCKS]) {
+    if constexpr (VEC) {
+        typedef float vec_t __attribute__((ext_vector_type(BLOCKS), aligned(4)));
+        const vec_t v = *reinterpret_cast<const vec_t*>(row + (BLOCKS * p < width ? BLOCKS * p : 0));
+#pragma unroll
+        for (int i = 0; i < BLOCKS; ++i) x[i] = v[i];
+    } else {
+#pragma unroll
+        for (int i = 0; i < BLOCKS; ++i) x[i] = row[32 * i + p < width ? 32 * i + p : 0];
+    }
+}
+template <int BLOCKS, bool VEC>
+__device__ __forceinline__ int share_index(int block, int p) { return VEC ? BLOCKS * p + block : 32 * block + p; }
+
+// partial[chunk] = sum over the chunk's rows of Y[id, :]^T X'[id, :], widths of at most 32 MT and 32 NT.
+//
+// The contraction runs over the rows, and both operands of v_mfma_f32_32x32x2_f32 want lane l to hold
+// one feature (l % 32) of row l / 32 of a pair: which is how a row lies in memory.  So nothing goes through
+// LDS: every wavefront takes its own rows, loads its operands straight into registers (one 16-byte load
+// per lane and operand for a pair of rows of 128), D pairs ahead of the matrix core, and keeps the whole
+// F_in x F_out product in its accumulators.  The wavefronts of a workgroup add theirs in LDS, in a
+// fixed order, once at the end.  Bound by the matrix core at 128 x 128 (16 instructions of 64 cycles per
+// pair of loads; busy 86 % of the time, at 2.1 of its 2.4 GHz), by HBM where a width is 16 (4.9 TB/s).
+// Measured against tiles staged through LDS, partial sums included: 128 x 128, 4.6 M rows 1.51 -> 1.31 ms;
+// 128 x 16, 3.9 M rows 0.53 -> 0.46 ms; 16 x 41, 250,000 rows 55 -> 29 us; 16 x 3, 382 rows 16 -> 7 us.
+template <int MT, int NT, bool VA, bool VB, int WAVES>
+__global__ __launch_bounds__(64 * WAVES, MT * NT >= 16 ? 1 : (WAVES > 4 ? WAVES / 4 : 2)) void k_weight_gradient_rows(
+    const int32_t* __restrict__ ids, int64_t n_rows, int64_t rows_per_wave, const float* __restrict__ Y, int Fi,
+    const float* __restrict__ G, int Fo, float* __restrict__ out) {
+    // pairs of rows in flight (fewer where the registers would not hold them)
+    constexpr int D = WAVES > 4 && MT * NT >= 4 ? 4 : 8;
+    __shared__ float sums[WAVES / 2][MT * NT * 16 * 64];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, p = lane & 31, half = lane >> 5;
+    const int64_t first = ((int64_t)blockIdx.x * WAVES + wave) * rows_per_wave;
+    const int64_t last = std::min<int64_t>(first + rows_per_wave, n_rows);
+    floatx16 acc[MT][NT] = {};
+    // lane i (of the first 2 D) holds the vertex of row r + i; rows past the end repeat the last one
+    // (without `ids` the load is of something else and not used: a branch around it would make every
+    // step wait for all loads)
+    const int32_t* __restrict__ id_src = ids ? ids : reinterpret_cast<const int32_t*>(Y);
+    auto place = [&](int64_t r) -> int { return (int)std::min<int64_t>(r + (lane & (2 * D - 1)), last - 1); };
+    auto vertices = [&](int64_t r) -> int { return id_src[place(r)]; };
+    float a[D][MT], b[D][NT];
+    auto fetch = [&](int d, int v) {
+        const int v0 = __builtin_amdgcn_readlane(v, 2 * d), v1 = __builtin_amdgcn_readlane(v, 2 * d + 1);
+        const int64_t id = half ? v1 : v0;
+        load_share<MT, VA>(Y + id * Fi, Fi, p, a[d]);
+        load_share<NT, VB>(G + id * Fo, Fo, p, b[d]);
+    };
+    if (first < last) {
+        // (loads in the order in which the loop issues them, so that the loop's waits count the same
+        // loads whichever way it is entered)
+        const int v0 = vertices(first);
+        int v = vertices(first + 2 * D);
+        __builtin_amdgcn_sched_barrier(0);
+        const int now = ids ? v0 : place(first);
+#pragma unroll
+        for (int d = 0; d < D; ++d) {
+            fetch(d, now);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        for (int64_t r = first; r < last; r += 2 * D) {
+            if (r + 2 * D > last) {  // rows past the end count nothing: both factors zero
+#pragma unroll
+                for (int d = 0; d < D; ++d) {
+                    const bool in = r + 2 * d + half < last;
+#pragma unroll
+                    for (int i = 0; i < MT; ++i) a[d][i] = in ? a[d][i] : 0.0f;
+#pragma unroll
+                    for (int j = 0; j < NT; ++j) b[d][j] = in ? b[d][j] : 0.0f;
+                }
+            }
+            // a pair's registers are filled again as soon as the matrix core has taken them, so that a
+            // fetch has the products of D - 1 pairs to arrive in, and its address arithmetic hides
+            // behind those of its own (the last step fetches rows that are not used)
+            const int next = ids ? v : place(r + 2 * D);
+            v = vertices(r + 4 * D);
+#pragma unroll
+            for (int d = 0; d < D; ++d) {
+#pragma unroll
+                for (int i = 0; i < MT; ++i)
+#pragma unroll
+                    for (int j = 0; j < NT; ++j)
+                        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[d][i], b[d][j], acc[i][j], 0, 0, 0);
+                fetch(d, next);
+                __builtin_amdgcn_sched_barrier(0);  // (left alone, all products come first and all fetches last)
+            }
+        }
+    }
+    // the upper half of the wavefronts hands its sums to the lower half, until one is left
+#pragma unroll
+    for (int left = WAVES / 2; left >= 1; left /= 2) {
+        if (wave >= left && wave < 2 * left) {
+#pragma unroll
+            for (int i = 0; i < MT; ++i)
+#pragma unroll
+                for (int j = 0; j < NT; ++j)
+#pragma unroll
+                    for (int e = 0; e < 16; ++e) sums[wave - left][((i * NT + j) * 16 + e) * 64 + lane] = acc[i][j][e];
+        }
+        __syncthreads();
+        if (wave < left) {
+#pragma unroll
+            for (int i = 0; i < MT; ++i)
+#pragma unroll
+                for (int j = 0; j < NT; ++j)
+#pragma unroll
+                    for (int e = 0; e < 16; ++e) acc[i][j][e] += sums[wave][((i * NT + j) * 16 + e) * 64 + lane];
+        }
+        __syncthreads();
+    }
+    if (wave != 0) return;
+    float* __restrict__ mine = out + (int64_t)blockIdx.x * Fi * Fo;
+#pragma unroll
+    for (int i = 0; i < MT; ++i)
+#pragma unroll
+        for (int j = 0; j < NT; ++j) {
+            const int n = share_index<NT, VB>(j, p);
+#pragma unroll
+            for (int e = 0; e < 16; ++e) {
+                const int m = share_index<MT, VA>(i, 8 * (e / 4) + 4 * half + (e % 4));
+                if (m < Fi && n < Fo) mine[m * Fo + n] = acc[i][j][e];
+            }
+        }
+}
+
+// Y'[id, n] = sum_k X'[id, k] W[n, k], widths of at most 128 (F_out = k) and 32 NT (F_in = n).
+//
+// W stays in LDS for the whole launch, in the order in which the matrix core takes it: the workgroups
+// are persistent, each wavefront takes 32 rows at a time and loads them straight into registers, lane l
+// its own row l % 32, four floats at a time (lanes l and l + 32 alternate: the contraction's order is free as
+// long as both operands follow it), the next 32 rows while the matrix core works on these.  One
+// 16-byte LDS read feeds four instructions, and no barrier is left in the loop.  Bound by the matrix
+// core at 128 x 128 (busy 82 %), by HBM where a width is 16 (4.9 TB/s).
+// Measured against tiles of both operands staged through LDS: 128 x 128, 4.6 M rows 1.61 -> 1.35 ms;
+// 128 x 16, 3.9 M rows 0.55 -> 0.46 ms; 16 x 41, 250,000 rows 27 -> 21 us; 16 x 3, 382 rows 5.4 -> 3.0 us.
+template <int KC, int NT>  // KC: chunks of 8 floats of a row
+__global__ __launch_bounds__(kBlock, 2) void k_input_gradient_rows(const int32_t* __restrict__ ids, int64_t n_rows,
+                                                                   const float* __restrict__ G, int Fo,
+                                                                   const float* __restrict__ W, int Fi,
+                                                                   float* __restrict__ Yg) {
+    __shared__ float4v Ws[KC * 2 * NT * 32];  // [chunk][half][n]: W[n, 8 chunk + 4 half ..]
+    __shared__ float4v out_all[kBlock / 64][32 * 8];  // 32 rows x 32 columns of results, private to a wavefront
+    const int lane = threadIdx.x & 63, p = lane & 31, half = lane >> 5;
+    for (int i = threadIdx.x; i < KC * 2 * NT * 32; i += kBlock) {
+        const int n = i % (NT * 32), k = (i / (NT * 32)) * 4;
+        float4v w = {0.f, 0.f, 0.f, 0.f};
+        if (n < Fi) {
+#pragma unroll
+            for (int c = 0; c < 4; ++c)
+                if (k + c < Fo) w[c] = W[(int64_t)n * Fo + k + c];
+        }
+        Ws[i] = w;
+    }
+    __syncthreads();
+    typedef float vec_t __attribute__((ext_vector_type(4), aligned(4)));
+    const int64_t n_tiles = (n_rows + 31) / 32, step = (int64_t)gridDim.x * (kBlock / 64);
+    auto vertex = [&](int64_t tile) -> int {
+        const int64_t r = std::min<int64_t>(tile * 32 + p, n_rows - 1);
+        return ids ? ids[r] : (int)r;
+    };
+    auto fetch = [&](float4v (&x)[KC], int v) {
+        const float* __restrict__ row = G + (int64_t)v * Fo;
+#pragma unroll
+        for (int c = 0; c < KC; ++c) {
+            const int k = 8 * c + 4 * half;
+            if (k + 4 <= Fo) {
+                x[c] = *reinterpret_cast<const vec_t*>(row + k);
+            } else {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) x[c][i] = k + i < Fo ? row[k + i] : 0.0f;
+            }
+        }
+    };
+    auto process = [&](const float4v (&x)[KC], int64_t tile, int v) {
+        floatx16 acc[NT] = {};
+#pragma unroll
+        for (int c = 0; c < KC; ++c) {
+            float4v w[NT];
+#pragma unroll
+            for (int j = 0; j < NT; ++j) w[j] = Ws[((c * 2 + half) * NT + j) * 32 + p];
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+#pragma unroll
+                for (int j = 0; j < NT; ++j) acc[j] = __builtin_amdgcn_mfma_f32_32x32x2f32(x[c][i], w[j][i], acc[j], 0, 0, 0);
+            if (c % 2) __builtin_amdgcn_sched_barrier(0);  // (all of W read ahead would not fit the registers)
+        }
+        // 32 columns at a time through LDS, so that a store carries 16 bytes per lane and whole 128-byte
+        // lines: single floats are four times as many stores as the counter of outstanding accesses holds,
+        // and four columns of a lane's own row each are 32-byte pieces of lines (1.41 and 1.50 ms)
+        float4v* __restrict__ ov = out_all[threadIdx.x >> 6];
+        float* __restrict__ of = reinterpret_cast<float*>(ov);
+        int vr[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) vr[q] = __shfl(v, 8 * q + (lane >> 3), 64);
+#pragma unroll
+        for (int j = 0; j < NT; ++j) {
+            __builtin_amdgcn_wave_barrier();
+#pragma unroll
+            for (int e = 0; e < 16; ++e) of[(8 * (e / 4) + 4 * half + (e % 4)) * 32 + p] = acc[j][e];
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            const int n = 32 * j + 4 * (lane & 7);
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const float4v y = ov[64 * q + lane];
+                if (tile * 32 + 8 * q + (lane >> 3) >= n_rows) continue;
+                float* __restrict__ o = Yg + (int64_t)vr[q] * Fi + n;
+                if (n + 4 <= Fi) {
+                    *reinterpret_cast<vec_t*>(o) = y;
+                } else {
+#pragma unroll
+                    for (int i = 0; i < 4; ++i)
+                        if (n + i < Fi) o[i] = y[i];
+                }
+            }
+        }
+    };
+    int64_t tile = (int64_t)blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6);
+    if (tile >= n_tiles) return;
+    float4v x0[KC], x1[KC];
+    int v0 = vertex(tile), v1 = tile + step < n_tiles ? vertex(tile + step) : 0;
+    fetch(x0, v0);
+    for (;;) {
+        const bool more = tile + step < n_tiles;
+        int v2 = 0;
+        if (more) {
+            fetch(x1, v1);
+            if (tile + 2 * step < n_tiles) v2 = vertex(tile + 2 * step);
+        }
+        process(x0, tile, v0);
+        if (!more) break;
+        tile += step;
+        const bool again = tile + step < n_tiles;
+        int v3 = 0;
+        if (again) {
+            fetch(x0, v2);
+            if (tile + 2 * step < n_tiles) v3 = vertex(tile + 2 * step);
+        }
+        process(x1, tile, v1);
+        if (!again) break;
+        tile += step;
+        v0 = v2;
+        v1 = v3;
+    }
+}
+
+// W'[e] = sum over chunks: LANES threads per element take every LANES-th chunk each, accumulate in
+// double, and are added in lane order (the result does not depend on timing).  64 of them where the
+// product is small: a few hundred elements would leave the chip idle with long chains of loads
+// (16 x 41, 978 chunks: 19.5 us with 16).
+template <int LANES>
+__global__ __launch_bounds__(kBlock) void k_weight_gradient_reduce(const float* __restrict__ partial, int n_chunks,
                                                                    int64_t total, float* __restrict__ Wg) {
-    __shared__ double part[16][17];
-    const int el = threadIdx.x & 15, cl = threadIdx.x >> 4;
-    const int64_t e = (int64_t)blockIdx.x * 16 + el;
+    constexpr int E = kBlock / LANES;  // elements per workgroup
+    __shared__ double part[LANES][E + 1];
+    const int el = threadIdx.x % E, cl = threadIdx.x / E;
+    const int64_t e = (int64_t)blockIdx.x * E + el;
     double s = 0.0;
-    if (e < total)
-        for (int64_t c = cl; c < n_chunks; c += 16) s += (double)partial[c * total + e];
+    if (e < total) {
+        for (int c = cl; c < n_chunks; c += 8 * LANES) {
+            float x[8];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) x[i] = c + i * LANES < n_chunks ? partial[(c + i * LANES) * total + e] : 0.0f;
+#pragma unroll
+            for (int i = 0; i < 8; ++i) s += (double)x[i];
+        }
+    }
     part[cl][el] = s;
     __syncthreads();
     if (cl == 0 && e < total) {
         double sum = 0.0;
 #pragma unroll
-        for (int i = 0; i < 16; ++i) sum += part[i][el];
+        for (int i = 0; i < LANES; ++i) sum += part[i][el];
         Wg[e] = (float)sum;
     }
 }
@@ -234,15 +503,15 @@ bool aligned4(int Fa, int Fb, const void* a, const void* b) {
 
 // Output tile of a launch, by the extents of the two tiled dimensions (m is always "long" for the
 // input gradient, whose rows are the active vertices).
-enum TileShape { T128x128, T128x64, T64x128, T64x64, T128x32, T32x128 };
+enum TileShape { T128x128, T128x64, T64x128, T128x32, T32x128 };
 TileShape tile_shape(int m, int n) {
     if (n <= 32 && m > 32) return T128x32;
     if (m <= 32 && n > 32) return T32x128;
     if (m > 64) return n > 64 ? T128x128 : T128x64;
-    return n > 64 ? T64x128 : T64x64;
+    return T64x128;
 }
 void tile_dims(TileShape t, int* tm, int* tn) {
-    static const int dims[6][2] = {{128, 128}, {128, 64}, {64, 128}, {64, 64}, {128, 32}, {32, 128}};
+    static const int dims[5][2] = {{128, 128}, {128, 64}, {64, 128}, {128, 32}, {32, 128}};
     *tm = dims[t][0];
     *tn = dims[t][1];
 }
@@ -265,17 +534,72 @@ int row_set(const epp_paths* p, int k, const int32_t** ids, int64_t* count) {
     return epp_active_ids(p, k, ids, count);
 }
 
-// Rows per partial sum: enough chunks to fill the chip a few times over (at most `max_chunks`
-// of them), whole steps each.
-void chunking(int64_t n_rows, int Fi, int Fo, int64_t max_chunks, int64_t* rows_per_chunk, int64_t* n_chunks) {
+// Widths that the kernels without operand tiles take (and their number of 32-wide blocks).
+constexpr int kNarrow = 128;
+bool narrow(int Fi, int Fo) { return Fi <= kNarrow && Fo <= kNarrow; }
+int blocks_of(int F) { return F > 64 ? 4 : (F > 32 ? 2 : 1); }
+
+// How the rows are cut into partial sums (at most `max_chunks` of them).
+struct Chunks {
+    int64_t per;    // rows per chunk; narrow widths: rows per wavefront
+    int64_t count;  // partial sums
+    int waves;      // narrow widths: wavefronts per workgroup (= per partial sum)
+};
+Chunks chunking(int64_t n_rows, int Fi, int Fo, int64_t max_chunks) {
+    Chunks c;
+    if (narrow(Fi, Fo)) {
+        const int tiles = blocks_of(Fi) * blocks_of(Fo);
+        // A few rows: one workgroup of 16 wavefronts, whose sum is the result (as many as its registers
+        // allow: 16 accumulators of 32 x 32 fit one wavefront per SIMD only).
+        if (tiles <= 4 && n_rows <= kOneWorkgroup) {
+            c.waves = 16;
+            c.count = n_rows > 0 ? 1 : 0;
+            c.per = (n_rows + 15) / 16;
+            return c;
+        }
+        // Four wavefronts: two rounds of the chip where a wavefront fills its SIMD, else four; 64 rows
+        // per wavefront at least.
+        c.waves = 4;
+        const int64_t want = std::min<int64_t>(tiles >= 8 ? 512 : 1024, std::max<int64_t>(max_chunks, 1));
+        c.per = std::max<int64_t>((n_rows + 4 * want - 1) / (4 * want), 64);
+        c.per = (c.per + 1) / 2 * 2;
+        c.count = (n_rows + 4 * c.per - 1) / (4 * c.per);
+        return c;
+    }
+    // operand tiles: enough chunks to fill the chip a few times over, whole steps each
     int tm, tn;
     tile_dims(tile_shape(Fi, Fo), &tm, &tn);
     const int64_t tiles = (int64_t)((Fi + tm - 1) / tm) * ((Fo + tn - 1) / tn);
     const int64_t want = std::min(std::max<int64_t>(1, 2048 / tiles), std::max<int64_t>(max_chunks, 1));
-    int64_t per = std::max<int64_t>((n_rows + want - 1) / want, kMinChunkRows);
-    per = (per + kStep - 1) / kStep * kStep;
-    *rows_per_chunk = per;
-    *n_chunks = (n_rows + per - 1) / per;
+    c.waves = 4;
+    c.per = std::max<int64_t>((n_rows + want - 1) / want, kMinChunkRows);
+    c.per = (c.per + kStep - 1) / kStep * kStep;
+    c.count = (n_rows + c.per - 1) / c.per;
+    return c;
+}
+
+template <int MT, int NT, bool VA, bool VB>
+void launch_rows_wg(const Chunks& c, const int32_t* ids, int64_t n_rows, const float* Y, int Fi, const float* G, int Fo,
+                    float* out, hipStream_t s) {
+    if constexpr (MT * NT <= 4) {
+        if (c.waves == 16) {
+            hipLaunchKernelGGL((k_weight_gradient_rows<MT, NT, VA, VB, 16>), dim3((unsigned)c.count), dim3(1024), 0, s, ids,
+                               n_rows, c.per, Y, Fi, G, Fo, out);
+            return;
+        }
+    }
+    hipLaunchKernelGGL((k_weight_gradient_rows<MT, NT, VA, VB, 4>), dim3((unsigned)c.count), dim3(256), 0, s, ids, n_rows,
+                       c.per, Y, Fi, G, Fo, out);
+}
+template <int MT, bool VA>
+void launch_rows_wg_n(const Chunks& c, const int32_t* ids, int64_t n_rows, const float* Y, int Fi, const float* G, int Fo,
+                      float* out, hipStream_t s) {
+    const int nt = blocks_of(Fo);
+    if (nt == 1) launch_rows_wg<MT, 1, VA, false>(c, ids, n_rows, Y, Fi, G, Fo, out, s);
+    else if (nt == 2 && Fo % 2 == 0) launch_rows_wg<MT, 2, VA, true>(c, ids, n_rows, Y, Fi, G, Fo, out, s);
+    else if (nt == 2) launch_rows_wg<MT, 2, VA, false>(c, ids, n_rows, Y, Fi, G, Fo, out, s);
+    else if (Fo % 4 == 0) launch_rows_wg<MT, 4, VA, true>(c, ids, n_rows, Y, Fi, G, Fo, out, s);
+    else launch_rows_wg<MT, 4, VA, false>(c, ids, n_rows, Y, Fi, G, Fo, out, s);
 }
 
 }  // namespace
@@ -284,9 +608,8 @@ extern "C" int64_t epp_weight_gradient_workspace(const epp_paths_t* paths, int k
     if (!paths) { epp_set_error("NULL argument"); return EPP_ERR_INVALID_ARG; }
     if (k < -1 || k > paths->L) { epp_set_error("k=%d outside [-1, %d]", k, paths->L); return EPP_ERR_INVALID_ARG; }
     if (check_widths(F_in, F_out) != EPP_OK) return EPP_ERR_INVALID_ARG;
-    int64_t per, chunks;
-    chunking(k < 0 ? paths->n : paths->set_size[k], F_in, F_out, kNoChunkLimit, &per, &chunks);
-    return std::max<int64_t>(chunks, 1) * F_in * F_out * (int64_t)sizeof(float);
+    const Chunks c = chunking(k < 0 ? paths->n : paths->set_size[k], F_in, F_out, kNoChunkLimit);
+    return std::max<int64_t>(c.count, 1) * F_in * F_out * (int64_t)sizeof(float);
 }
 
 namespace {
@@ -298,9 +621,21 @@ int weight_gradient(const epp_paths* paths, int k, const float* Y, int F_in, con
     const int32_t* ids = nullptr;
     int64_t n_rows = 0;
     EPP_TRY(row_set(paths, k, &ids, &n_rows));
-    int64_t per, chunks;
-    chunking(n_rows, F_in, F_out, max_chunks, &per, &chunks);
-    if (chunks > 0) {
+    const Chunks c = chunking(n_rows, F_in, F_out, max_chunks);
+    const int64_t per = c.per, chunks = c.count;
+    if (chunks > 0 && narrow(F_in, F_out)) {
+        float* out = chunks == 1 ? grad_W : part;
+        const int mt = blocks_of(F_in);
+        if (mt == 1) launch_rows_wg_n<1, false>(c, ids, n_rows, Y, F_in, grad_X, F_out, out, s);
+        else if (mt == 2 && F_in % 2 == 0) launch_rows_wg_n<2, true>(c, ids, n_rows, Y, F_in, grad_X, F_out, out, s);
+        else if (mt == 2) launch_rows_wg_n<2, false>(c, ids, n_rows, Y, F_in, grad_X, F_out, out, s);
+        else if (F_in % 4 == 0) launch_rows_wg_n<4, true>(c, ids, n_rows, Y, F_in, grad_X, F_out, out, s);
+        else launch_rows_wg_n<4, false>(c, ids, n_rows, Y, F_in, grad_X, F_out, out, s);
+        if (chunks == 1) {
+            EPP_HIP_TRY(hipGetLastError());
+            return EPP_OK;
+        }
+    } else if (chunks > 0) {
         const TileShape shape = tile_shape(F_in, F_out);
         int tm, tn;
         tile_dims(shape, &tm, &tn);
@@ -319,15 +654,18 @@ int weight_gradient(const epp_paths* paths, int k, const float* Y, int F_in, con
             case T128x128: EPP_LAUNCH_WG(2, 2, 2, 2); break;
             case T128x64: EPP_LAUNCH_WG(2, 2, 2, 1); break;
             case T64x128: EPP_LAUNCH_WG(2, 2, 1, 2); break;
-            case T64x64: EPP_LAUNCH_WG(2, 2, 1, 1); break;
             case T128x32: EPP_LAUNCH_WG(4, 1, 1, 1); break;
             case T32x128: EPP_LAUNCH_WG(1, 4, 1, 1); break;
         }
 #undef EPP_LAUNCH_WG
     }
     const int64_t total = (int64_t)F_in * F_out;
-    hipLaunchKernelGGL(k_weight_gradient_reduce, dim3((unsigned)((total + 15) / 16)), dim3(kBlock), 0, s,
-                       static_cast<const float*>(part), chunks, total, grad_W);
+    if (total >= 4096)
+        hipLaunchKernelGGL(k_weight_gradient_reduce<16>, dim3((unsigned)((total + 15) / 16)), dim3(kBlock), 0, s,
+                           static_cast<const float*>(part), (int)chunks, total, grad_W);
+    else
+        hipLaunchKernelGGL(k_weight_gradient_reduce<64>, dim3((unsigned)((total + 3) / 4)), dim3(kBlock), 0, s,
+                           static_cast<const float*>(part), (int)chunks, total, grad_W);
     EPP_HIP_TRY(hipGetLastError());
     return EPP_OK;
 }
@@ -407,6 +745,32 @@ extern "C" int epp_input_gradient(epp_paths_t* paths, int k, const float* grad_X
     int64_t n_rows = 0;
     EPP_TRY(row_set(paths, k, &ids, &n_rows));
     if (n_rows == 0) return EPP_OK;
+    if (narrow(F_in, F_out)) {
+        // persistent workgroups, as many as the chip holds at once
+        const int64_t tiles = (n_rows + 31) / 32;
+        const int kc = (F_out + 7) / 8, nt = blocks_of(F_in);
+        const dim3 grid((unsigned)std::min<int64_t>((tiles + 3) / 4, kc > 8 ? 512 : 1024));
+#define EPP_LAUNCH_IGR(KC)                                                                                           \
+    do {                                                                                                             \
+        if (nt == 1)                                                                                                 \
+            hipLaunchKernelGGL((k_input_gradient_rows<KC, 1>), grid, dim3(kBlock), 0, s, ids, n_rows, grad_X, F_out, \
+                               W, F_in, grad_Y);                                                                     \
+        else if (nt == 2)                                                                                            \
+            hipLaunchKernelGGL((k_input_gradient_rows<KC, 2>), grid, dim3(kBlock), 0, s, ids, n_rows, grad_X, F_out, \
+                               W, F_in, grad_Y);                                                                     \
+        else                                                                                                         \
+            hipLaunchKernelGGL((k_input_gradient_rows<KC, 4>), grid, dim3(kBlock), 0, s, ids, n_rows, grad_X, F_out, \
+                               W, F_in, grad_Y);                                                                     \
+    } while (0)
+        if (kc <= 2) EPP_LAUNCH_IGR(2);
+        else if (kc <= 4) EPP_LAUNCH_IGR(4);
+        else if (kc <= 6) EPP_LAUNCH_IGR(6);
+        else if (kc <= 8) EPP_LAUNCH_IGR(8);
+        else EPP_LAUNCH_IGR(16);
+#undef EPP_LAUNCH_IGR
+        EPP_HIP_TRY(hipGetLastError());
+        return EPP_OK;
+    }
     // rows are the long dimension: 128 of them per tile
     const TileShape shape = tile_shape(1 << 20, F_in);
     int tm, tn;

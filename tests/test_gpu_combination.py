@@ -239,3 +239,31 @@ def test_backward_epoch_in_a_hip_graph():
         for l in range(L):
             assert torch.equal(Wgs[l], eager_w[l]), f"replay {rep} W' l={l}"
         assert torch.equal(Gs[0], eager_g0), f"replay {rep} gradient"
+
+
+@pytest.mark.parametrize("Fi,Fo", [(1, 1), (3, 16), (16, 7), (32, 33), (41, 47), (64, 64), (65, 31), (96, 128), (127, 128),
+                                   (128, 126), (128, 129), (130, 128)])
+@pytest.mark.parametrize("n_rows", [1, 31, 63, 1024, 1025, 5000])
+def test_narrow_products_at_the_edges_of_their_tiles(Fi, Fo, n_rows):
+    """Widths around the 32-wide blocks and at the limits of the kernels without operand tiles; row sets
+    around a tile of rows, a pair of rows and the most that one workgroup takes alone."""
+    n = 6000
+    g = graphgen.csr_from_edges(n, [(i, (i + 1) % n) for i in range(n)], self_loops=True)
+    train = np.random.default_rng(7).permutation(n)[:n_rows].astype(np.int32)
+    paths = gpu_prepare(g, train, 1)
+    member = np.zeros(n, bool)
+    member[train] = True
+    Y, W = _rand((n, Fi), 421), _rand((Fi, Fo), 423)
+    G = np.full((n, Fo), np.nan, np.float32)  # rows outside the set are never read
+    G[member] = _rand((n_rows, Fo), 422)
+    Gz = np.where(member[:, None], G, np.float32(0))
+    Yn = np.where(member[:, None], Y, np.float32(np.nan))
+    want_w, scale_w = oracle.weight_gradient(Y, Gz, member)
+    _close(_weight_gradient(paths, 0, Yn, G), want_w, scale_w, f"W' {Fi}x{Fo} rows {n_rows}")
+    want_y, scale_y = oracle.input_gradient(Gz, W)
+    d = dev()
+    out = torch.full((n, Fi), 9.0, device=d)
+    epp.epp_input_gradient(paths, 0, torch.from_numpy(G).to(d), torch.from_numpy(W).to(d), out)
+    got = out.cpu().numpy()
+    assert (got[~member] == 9.0).all()
+    _close(got[member], want_y[member], scale_y[member], f"Y' {Fi}x{Fo} rows {n_rows}")
