@@ -45,26 +45,23 @@ template <int VEC, class V> __device__ __forceinline__ float lane_get(const V& x
 }
 
 // ---------------------------------------------------------------- schedule construction
-// One thread per group: the row that holds the group's first entry (search in the row
-// pointer; streamed rows are non-empty, so the pointer is strictly increasing).  Bit 31
-// marks a group that starts inside a row.  A row cut by group boundaries is appended to
-// cut_rows once, by the first boundary inside it.
+// One thread per row (streamed rows are non-empty): it is the row of the first entry of every group that
+// starts inside it.  Bit 31 marks a group that starts past the row's beginning; a row with such a
+// group is cut, and listed once.  (A search of the row pointer for every group is a chain of
+// some twenty loads: 12 us where this takes 4.)
 __global__ __launch_bounds__(kBlock) void k_sched_groups(const int32_t* __restrict__ rowptr, int64_t n_rows, int gs,
-                                                         int64_t n_groups, int32_t* __restrict__ group_row,
-                                                         int32_t* __restrict__ cut_rows,
+                                                         int32_t* __restrict__ group_row, int32_t* __restrict__ cut_rows,
                                                          unsigned int* __restrict__ n_cut) {
-    int64_t g = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (g >= n_groups) return;
-    const int64_t first = g * gs;
-    int64_t lo = 0, hi = n_rows - 1;  // largest r with rowptr[r] <= first
-    while (lo < hi) {
-        int64_t mid = (lo + hi + 1) >> 1;
-        if (rowptr[mid] <= first) lo = mid; else hi = mid - 1;
+    const int64_t r = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+    if (r >= n_rows) return;
+    const int64_t p0 = rowptr[r], p1 = rowptr[r + 1];
+    bool cut = false;
+    for (int64_t g = (p0 + gs - 1) / gs; g * gs < p1; ++g) {
+        const bool inside = g * gs > p0;
+        group_row[g] = (int32_t)r | (inside ? kRowEnd : 0);
+        cut |= inside;
     }
-    const int64_t start = rowptr[lo];
-    const bool inside = start < first;
-    group_row[g] = (int32_t)lo | (inside ? kRowEnd : 0);
-    if (inside && start >= first - gs) cut_rows[atomicAdd(n_cut, 1u)] = (int32_t)lo;
+    if (cut) cut_rows[atomicAdd(n_cut, 1u)] = (int32_t)r;
 }
 
 // ------------------------------------------------------------------------- aggregation
@@ -648,20 +645,23 @@ int epp_build_schedule_over(const epp_path* p, const int32_t* rowptr, int64_t n_
     if (n_groups >= 0x7FFFFFFFll) { epp_set_error("too many groups"); return EPP_ERR_TOO_LARGE; }
     sc->n_groups = n_groups;
     const epp_alloc_t* al = epp_alloc_of(p);
-    EPP_TRY(sc->group_row.alloc((size_t)n_groups * 4, al));
-    EPP_TRY(sc->cut_rows.alloc((size_t)n_groups * 4, al));
+    // group rows | cut rows | their number
+    const size_t table = DevArena::rounded((size_t)n_groups * 4);
+    EPP_TRY(sc->store.alloc(2 * table + 256, al));
+    sc->group_row.view(sc->store.p, (size_t)n_groups * 4);
+    sc->cut_rows.view(sc->store.as<char>() + table, (size_t)n_groups * 4);
+    unsigned int* n_cut = reinterpret_cast<unsigned int*>(sc->store.as<char>() + 2 * table);
     if (n_groups > 0) {
-        DevBuf cnt;
-        EPP_TRY(cnt.alloc(sizeof(unsigned int), al));
-        EPP_HIP_TRY(hipMemsetAsync(cnt.p, 0, sizeof(unsigned int), s));
-        hipLaunchKernelGGL(k_sched_groups, dim3((unsigned)((n_groups + kBlock - 1) / kBlock)), dim3(kBlock), 0, s,
-                           rowptr, n_rows, gs, n_groups, sc->group_row.as<int32_t>(),
-                           sc->cut_rows.as<int32_t>(), cnt.as<unsigned int>());
+        PinnedWords host;
+        EPP_TRY(host.get(1));
+        EPP_HIP_TRY(hipMemsetAsync(n_cut, 0, sizeof(unsigned int), s));
+        hipLaunchKernelGGL(k_sched_groups, dim3((unsigned)((n_rows + kBlock - 1) / kBlock)), dim3(kBlock), 0, s, rowptr, n_rows,
+                           gs, sc->group_row.as<int32_t>(), sc->cut_rows.as<int32_t>(), n_cut);
         EPP_HIP_TRY(hipGetLastError());
-        unsigned int h = 0;
-        EPP_HIP_TRY(hipMemcpyAsync(&h, cnt.p, sizeof(h), hipMemcpyDeviceToHost, s));
+        host.p[0] = 0;
+        EPP_HIP_TRY(hipMemcpyAsync(host.p, n_cut, sizeof(unsigned int), hipMemcpyDeviceToHost, s));
         EPP_HIP_TRY(hipStreamSynchronize(s));
-        sc->n_split_rows = h;
+        sc->n_split_rows = (int64_t)host.p[0];  // (little endian)
     }
     guard.s = nullptr;
     *out = sc;

@@ -118,6 +118,7 @@ struct Schedule {
     int gs = 0;
     int64_t n_groups = 0;
     int64_t n_split_rows = 0;  // rows cut by a group boundary (summed from the groups' partial rows)
+    DevBuf store;              // the allocation behind the two tables
     DevBuf group_row;          // int32[n_groups] row holding the group's first entry; bit 31: starts inside it
     DevBuf cut_rows;           // int32[n_split_rows] (path-row indices)
     // Partial rows of the groups, per width F: float[n_groups][2][F].  Slot 0 of a group holds the
@@ -145,7 +146,7 @@ struct Schedule {
             if (pieces[i]->F == F) { delete pieces[i]; pieces.erase(pieces.begin() + i); return; }
     }
     size_t bytes() const {
-        size_t b = group_row.bytes + cut_rows.bytes;
+        size_t b = store.bytes;
         for (const Pieces* q : pieces) b += q->buf.bytes;
         return b;
     }

@@ -76,6 +76,51 @@ __global__ __launch_bounds__(kBlock) void k_mark_training(const int32_t* __restr
     atomicOr(&bitmap32[v >> 5], 1u << (v & 31));
 }
 
+// The same, with the ascending ids and their number, by one workgroup that keeps the bitmap in LDS: for up to
+// kSetVertices vertices and kSetIds training ids (marking, counting, scanning and listing are four
+// launches of 4.5 us otherwise, whatever they process).
+constexpr int kSetVertices = 524288, kSetIds = 65536;
+__global__ __launch_bounds__(1024) void k_training_set(const int32_t* __restrict__ ids, int n_ids, int n,
+                                                       unsigned long long* __restrict__ bitmap, int32_t* __restrict__ ids_out,
+                                                       long long* __restrict__ count, int* __restrict__ err) {
+    __shared__ unsigned long long bits[kSetVertices / 64];
+    __shared__ int wave_sum[16];
+    const int tid = threadIdx.x, wave = tid >> 6, lane = lane_id(), n_words = (n + 63) >> 6;
+    for (int w = tid; w < n_words; w += 1024) bits[w] = 0ull;
+    __syncthreads();
+    unsigned int* bits32 = reinterpret_cast<unsigned int*>(bits);
+    for (int i0 = tid; i0 < n_ids; i0 += 8 * 1024) {
+        int v[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) v[j] = i0 + j * 1024 < n_ids ? ids[i0 + j * 1024] : 0;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            if (i0 + j * 1024 >= n_ids) continue;
+            if (v[j] < 0 || v[j] >= n) atomicOr(err, kErrTrain);
+            else atomicOr(&bits32[v[j] >> 5], 1u << (v[j] & 31));
+        }
+    }
+    __syncthreads();
+    // consecutive words per thread, so that a scan of the threads' counts places every word
+    const int per = (n_words + 1023) / 1024, w0 = min(tid * per, n_words), w1 = min(w0 + per, n_words);
+    int mine = 0;
+    for (int w = w0; w < w1; ++w) mine += __popcll(bits[w]);
+    const int incl = wave_inclusive_scan(mine);
+    if (lane == 63) wave_sum[wave] = incl;
+    __syncthreads();
+    int at = incl - mine, all = 0;
+    for (int w = 0; w < 16; ++w) {
+        if (w < wave) at += wave_sum[w];
+        all += wave_sum[w];
+    }
+    for (int w = w0; w < w1; ++w) {
+        unsigned long long m = bits[w];
+        bitmap[w] = m;
+        for (; m; m &= m - 1ull) ids_out[at++] = w * 64 + __ffsll((long long)m) - 1;
+    }
+    if (tid == 0) *count = all;
+}
+
 struct MaskArgs {
     const int32_t* col;
     int64_t nnz, n_seg, n_tiles;
@@ -648,14 +693,13 @@ __global__ __launch_bounds__(kBlock) void k_export(const int2* __restrict__ cv, 
     }
 }
 
-// Flag the last entry of every (non-empty) row in bit 31 of its column id.  (The bounds only matter
-// for imported arrays, which are checked in the same stream of work.)
-__global__ __launch_bounds__(kBlock) void k_mark_row_ends(const int32_t* __restrict__ rowptr, int64_t n_rows, int64_t nnz,
+// Flag the last entry of every (non-empty) row in bit 31 of its column id.
+__global__ __launch_bounds__(kBlock) void k_mark_row_ends(const int32_t* __restrict__ rowptr, int64_t n_rows,
                                                           int2* __restrict__ cv) {
     int64_t r = (int64_t)blockIdx.x * kBlock + threadIdx.x;
     if (r >= n_rows) return;
     const int32_t end = rowptr[r + 1];
-    if (end > rowptr[r] && end > 0 && end <= nnz) cv[end - 1].x |= kEntRowEnd;
+    if (end > rowptr[r]) cv[end - 1].x |= kEntRowEnd;
 }
 
 // Bitmap of the vertices with a non-empty (invert = 0) or empty (invert = 1) list.
@@ -776,36 +820,90 @@ void launch_edge_mask(const epp_csr_t* g, int64_t n_seg, unsigned n_tiles, const
     }
 }
 
-// Row arrays of an imported path: copied, checked (an error bit if ids do not ascend, the pointer
-// decreases, a row is empty or the end points are wrong; another for an id outside [0, n)), counted
-// into the row-length statistics, and set in the bitmap of the row set.  Ids ascend, so neighbouring
-// lanes share bitmap words: the bits of a word are gathered by a segmented scan across the
-// wavefront and set by its last lane, one atomic per word instead of one per row.
-__global__ __launch_bounds__(kBlock) void k_import_rows(const int32_t* __restrict__ row_ids,
-                                                        const int32_t* __restrict__ rowptr, int64_t n_rows, int64_t nnz,
-                                                        int64_t n, int32_t* __restrict__ ids_out,
-                                                        int32_t* __restrict__ ptr_out, unsigned int* __restrict__ bitmap32,
-                                                        unsigned long long* __restrict__ stats, int* __restrict__ err) {
+// An imported path, copied and checked in one launch: the first row_blocks workgroups take the rows,
+// the others a tile of kImportTile entries each.
+//
+// Rows: an error bit if ids do not ascend, the pointer decreases, a row is empty or the end points are
+// wrong; another for an id outside [0, n).  They are counted into the row-length statistics and set in
+// the bitmap of the row set.  Ids ascend, so neighbouring lanes share bitmap words: the bits of a
+// word are gathered by a segmented scan across the wavefront and set by its last lane, one atomic per
+// word instead of one per row.
+//
+// Entries: columns in range, interleaved with the weights; the last entry of every row gets the
+// row-end flag.  A tile's first row is found by a search with 256 probes a step, and as no row is
+// empty at most kImportTile + 1 of them concern it (whatever an invalid pointer holds).
+struct ImportArgs {
+    const int32_t *row_ids, *rowptr, *col;
+    const float* val;
+    int64_t n_rows, nnz, n;
+    int32_t *ids_out, *ptr_out;
+    int2* cv;
+    unsigned int* bitmap32;
+    unsigned long long* stats;
+    int* err;
+    unsigned row_blocks;
+};
+constexpr int kImportTile = 2048;
+__global__ __launch_bounds__(kBlock) void k_import_path(ImportArgs a) {
     __shared__ int h[kHists * EPP_NCLASS];
     __shared__ int mx;
-    clear_lengths(h, &mx);
+    __shared__ unsigned int row_end[kImportTile / 32];
     const int lane = lane_id();
+    if (blockIdx.x >= a.row_blocks) {
+        const int64_t e0 = (int64_t)(blockIdx.x - a.row_blocks) * kImportTile;
+        constexpr int kPer = kImportTile / kBlock;
+        int2 x[kPer];
+#pragma unroll
+        for (int i = 0; i < kPer; ++i) {
+            const int64_t e = e0 + i * kBlock + threadIdx.x;
+            x[i] = e < a.nnz ? make_int2(a.col[e], __float_as_int(a.val[e])) : make_int2(0, 0);
+        }
+        if (threadIdx.x < kImportTile / 32) row_end[threadIdx.x] = 0u;
+        int64_t lo = 0, hi = a.n_rows;  // the row of entry e0: the last one that starts at or before it
+        while (hi - lo > 1) {
+            const int64_t step = (hi - lo + kBlock - 1) / kBlock, r = lo + (int64_t)threadIdx.x * step;
+            const int below = __syncthreads_count(r < hi && a.rowptr[r] <= e0);
+            lo += (int64_t)max(below - 1, 0) * step;
+            hi = std::min<int64_t>(lo + step, hi);
+        }
+        __syncthreads();
+        for (int64_t r = lo + threadIdx.x; r < std::min<int64_t>(lo + kImportTile + 1, a.n_rows); r += kBlock) {
+            const int64_t end = (int64_t)a.rowptr[r + 1] - 1 - e0;
+            if (end >= 0 && end < kImportTile) atomicOr(&row_end[end >> 5], 1u << (end & 31));
+        }
+        __syncthreads();
+        bool bad = false;
+#pragma unroll
+        for (int i = 0; i < kPer; ++i) {
+            const int t = i * kBlock + threadIdx.x;
+            if (e0 + t >= a.nnz) continue;
+            if (x[i].x < 0 || x[i].x >= a.n) {
+                bad = true;
+                x[i].x = 0;
+            }
+            if ((row_end[t >> 5] >> (t & 31)) & 1u) x[i].x |= kEntRowEnd;
+            a.cv[e0 + t] = x[i];
+        }
+        if (bad) atomicOr(a.err, kErrCol);
+        return;
+    }
+    clear_lengths(h, &mx);
     int my_max = 0, bad = 0;
-    const int64_t span = (int64_t)gridDim.x * kBlock;
+    const int64_t span = (int64_t)a.row_blocks * kBlock;
     // (one index past the rows, for the end of the pointer; whole wavefronts enter every iteration)
-    for (int64_t base = (int64_t)blockIdx.x * kBlock + (threadIdx.x & ~63); base <= n_rows; base += span) {
+    for (int64_t base = (int64_t)blockIdx.x * kBlock + (threadIdx.x & ~63); base <= a.n_rows; base += span) {
         const int64_t r = base + lane;
-        const bool row = r < n_rows;
-        const int p = r <= n_rows ? rowptr[r] : 0;
-        const int v = row ? row_ids[r] : -1;
-        const int prev = row && r > 0 ? row_ids[r - 1] : -1;
-        const int len = row ? rowptr[r + 1] - p : 0;
-        if (r <= n_rows) ptr_out[r] = p;
-        if ((r == 0 && p != 0) || (r == n_rows && p != nnz)) bad |= kErrRowptr;
+        const bool row = r < a.n_rows;
+        const int p = r <= a.n_rows ? a.rowptr[r] : 0;
+        const int v = row ? a.row_ids[r] : -1;
+        const int prev = row && r > 0 ? a.row_ids[r - 1] : -1;
+        const int len = row ? a.rowptr[r + 1] - p : 0;
+        if (r <= a.n_rows) a.ptr_out[r] = p;
+        if ((r == 0 && p != 0) || (r == a.n_rows && p != a.nnz)) bad |= kErrRowptr;
         bool in = false;
         if (row) {
-            ids_out[r] = v;
-            in = v >= 0 && v < n;
+            a.ids_out[r] = v;
+            in = v >= 0 && v < a.n;
             if (!in) bad |= kErrCol;
             if (prev >= v || len <= 0) bad |= kErrRowptr;
             my_max = max(my_max, len);
@@ -819,11 +917,31 @@ __global__ __launch_bounds__(kBlock) void k_import_rows(const int32_t* __restric
             if (lane >= d && other_word == word) b |= other;
         }
         const int next_word = __shfl_down(word, 1, 64);
-        if (in && (lane == 63 || next_word != word)) atomicOr(&bitmap32[word], b);
+        if (in && (lane == 63 || next_word != word)) atomicOr(&a.bitmap32[word], b);
         if (row && len > 0) add_length(h, len);
     }
-    if (bad) atomicOr(err, bad);
-    flush_lengths(h, &mx, my_max, stats, reinterpret_cast<int*>(stats + EPP_NCLASS));
+    if (bad) atomicOr(a.err, bad);
+    flush_lengths(h, &mx, my_max, a.stats, reinterpret_cast<int*>(a.stats + EPP_NCLASS));
+}
+
+// N^0 as a bitmap (cleared by the caller) and its ascending ids; *count receives their number.
+void launch_training_set(const int32_t* train_ids, int64_t n_train, int64_t n, const DevBuf& bitmap, void* ids_out,
+                         int* tile_cnt, int* tile_base, int* scan_tmp, long long* count, int* err, hipStream_t s) {
+    if (n_train == 0) return;
+    if (n > 0 && n <= kSetVertices && n_train <= kSetIds) {
+        hipLaunchKernelGGL(k_training_set, dim3(1), dim3(1024), 0, s, train_ids, (int)n_train, (int)n,
+                           bitmap.as<unsigned long long>(), static_cast<int32_t*>(ids_out), count, err);
+        return;
+    }
+    const int64_t n_words = (n + 63) / 64;
+    const unsigned tiles = grid_for(n_words, kWordsPerTile);
+    hipLaunchKernelGGL(k_mark_training, dim3(grid_for(n_train, kBlock)), dim3(kBlock), 0, s, train_ids, n_train, n,
+                       bitmap.as<unsigned int>(), err);
+    if (n == 0) return;
+    hipLaunchKernelGGL(k_bitmap_count, dim3(tiles), dim3(kBlock), 0, s, bitmap.as<unsigned long long>(), n_words, tile_cnt);
+    scan_counts(tile_cnt, tile_base, tiles, count, scan_tmp, s);
+    hipLaunchKernelGGL(k_bitmap_compact, dim3(tiles), dim3(kBlock), 0, s, bitmap.as<unsigned long long>(), n_words, tile_base,
+                       (const int*)nullptr, static_cast<int32_t*>(ids_out), (int32_t*)nullptr, (int64_t)0, 0);
 }
 
 // Message and code for the error bits raised by the input checks (bit 0 row pointer, bit 1 ids).
@@ -907,7 +1025,7 @@ int epp_path_finish(epp_path* p, hipStream_t s) {
     epp_path_set_stats(p, host);
     if (p->n_stream_rows > 0) {
         hipLaunchKernelGGL(k_mark_row_ends, dim3(grid_for(p->n_stream_rows, kBlock)), dim3(kBlock), 0, s,
-                           p->rowptr.as<int32_t>(), p->n_stream_rows, p->nnz, p->cv.as<int2>());
+                           p->rowptr.as<int32_t>(), p->n_stream_rows, p->cv.as<int2>());
         EPP_HIP_TRY(hipGetLastError());
     }
     return EPP_OK;  // the callers synchronise once, before they return the handle
@@ -997,19 +1115,9 @@ extern "C" int epp_prepare(const epp_csr_t* g, const int32_t* train_ids, int64_t
     EPP_HIP_TRY(hipMemsetAsync(levels.p, 0, level_bytes, s));
 
     // N^0 = V_t (Property 1) and its ascending ids (the other sets are the row ids of the paths)
-    if (n_train > 0) {
-        hipLaunchKernelGGL(k_mark_training, dim3(grid_for(n_train, kBlock)), dim3(kBlock), 0, s, train_ids, n_train, n,
-                           P->bitmaps[0].as<unsigned int>(), reinterpret_cast<int*>(d_levels + 2));
-        if (n > 0) {
-            hipLaunchKernelGGL(k_bitmap_count, dim3(word_tiles), dim3(kBlock), 0, s, P->bitmaps[0].as<unsigned long long>(),
-                               n_words, tile_cnt.as<int>());
-            scan_counts(tile_cnt.as<int>(), tile_base[0].as<int>(), word_tiles, d_levels + 5, scan_tmp.as<int>(), s);
-            hipLaunchKernelGGL(k_bitmap_compact, dim3(word_tiles), dim3(kBlock), 0, s,
-                               P->bitmaps[0].as<unsigned long long>(), n_words, tile_base[0].as<int>(), (const int*)nullptr,
-                               static_cast<int32_t*>(set0), (int32_t*)nullptr, (int64_t)0, 0);
-        }
-        EPP_HIP_TRY(hipGetLastError());
-    }
+    launch_training_set(train_ids, n_train, n, P->bitmaps[0], set0, tile_cnt.as<int>(), tile_base[0].as<int>(),
+                        scan_tmp.as<int>(), d_levels + 5, reinterpret_cast<int*>(d_levels + 2), s);
+    EPP_HIP_TRY(hipGetLastError());
 
     // Shared entries: the path of a level runs on the arrays of the next level's path if nearly
     // all of that path's entries are its own too (the extra entries are skipped one by one at
@@ -1272,18 +1380,8 @@ extern "C" int epp_paths_import(int64_t n, int L, const int32_t* train_ids, int6
     arena.take(&tile_cnt, tiles * 4);
     arena.take(&tile_base, tiles * 4);
     arena.take(&scan_tmp, scan_tmp_bytes(tiles));
-    if (n_train > 0) {
-        hipLaunchKernelGGL(k_mark_training, dim3(grid_for(n_train, kBlock)), dim3(kBlock), 0, s, train_ids, n_train, n,
-                           P->bitmaps[0].as<unsigned int>(), d_err);
-        if (n > 0) {
-            hipLaunchKernelGGL(k_bitmap_count, dim3((unsigned)tiles), dim3(kBlock), 0, s, P->bitmaps[0].as<unsigned long long>(),
-                               n_words, tile_cnt.as<int>());
-            scan_counts(tile_cnt.as<int>(), tile_base.as<int>(), (int64_t)tiles, d_res + 1, scan_tmp.as<int>(), s);
-            hipLaunchKernelGGL(k_bitmap_compact, dim3((unsigned)tiles), dim3(kBlock), 0, s,
-                               P->bitmaps[0].as<unsigned long long>(), n_words, tile_base.as<int>(), (const int*)nullptr,
-                               static_cast<int32_t*>(set0), (int32_t*)nullptr, (int64_t)0, 0);
-        }
-    }
+    launch_training_set(train_ids, n_train, n, P->bitmaps[0], set0, tile_cnt.as<int>(), tile_base.as<int>(),
+                        scan_tmp.as<int>(), d_res + 1, d_err, s);
     for (int l = L - 1; l >= 0; --l) {
         const epp_path_arrays_t& a = layers[l];
         const int k = L - l - 1;
@@ -1301,16 +1399,22 @@ extern "C" int epp_paths_import(int64_t n, int L, const int32_t* train_ids, int6
         p->row_ids.view(p->store.p, ids_bytes);
         p->rowptr.view(p->store.as<char>() + DevArena::rounded(ids_bytes), ptr_bytes);
         EPP_TRY(p->cv.alloc((size_t)a.nnz * sizeof(int2), al));
-        hipLaunchKernelGGL(k_import_rows, dim3(std::min(grid_for(a.n_rows + 1, kBlock), kStatBlocks)), dim3(kBlock), 0, s, a.row_ids,
-                           a.rowptr, a.n_rows, a.nnz, n, p->row_ids.as<int32_t>(), p->rowptr.as<int32_t>(),
-                           P->bitmaps[k + 1].as<unsigned int>(),
-                           reinterpret_cast<unsigned long long*>(d_res + 2 + (size_t)l * kStatWords), d_err);
-        if (a.nnz > 0) {
-            hipLaunchKernelGGL(k_interleave, dim3(grid_for(a.nnz, kBlock)), dim3(kBlock), 0, s, a.col, a.val, a.nnz, n,
-                               p->cv.as<int2>(), d_err);
-            hipLaunchKernelGGL(k_mark_row_ends, dim3(grid_for(a.n_rows, kBlock)), dim3(kBlock), 0, s,
-                               p->rowptr.as<int32_t>(), a.n_rows, a.nnz, p->cv.as<int2>());
-        }
+        ImportArgs q;
+        q.row_ids = a.row_ids;
+        q.rowptr = a.rowptr;
+        q.col = a.col;
+        q.val = a.val;
+        q.n_rows = a.n_rows;
+        q.nnz = a.nnz;
+        q.n = n;
+        q.ids_out = p->row_ids.as<int32_t>();
+        q.ptr_out = p->rowptr.as<int32_t>();
+        q.cv = p->cv.as<int2>();
+        q.bitmap32 = P->bitmaps[k + 1].as<unsigned int>();
+        q.stats = reinterpret_cast<unsigned long long*>(d_res + 2 + (size_t)l * kStatWords);
+        q.err = d_err;
+        q.row_blocks = std::min(grid_for(a.n_rows + 1, kBlock), kStatBlocks);
+        hipLaunchKernelGGL(k_import_path, dim3(q.row_blocks + grid_for(a.nnz, kImportTile)), dim3(kBlock), 0, s, q);
         EPP_HIP_TRY(hipGetLastError());
     }
     EPP_HIP_TRY(hipMemcpyAsync(hs.p, d_res, res_words * 8, hipMemcpyDeviceToHost, s));

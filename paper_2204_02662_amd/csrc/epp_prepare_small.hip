@@ -10,7 +10,7 @@
 // wait after, for the sizes.  Same results as the general construction, bit for bit (tested).
 //
 // Limits: n, |V_t| <= 65,536 and nnz <= 131,072 (one LDS word per 64 vertices and thread, two per
-// 64 entries and thread), L <= 32.
+// 64 entries and thread), L <= 32; of these, the graphs on which it is the faster of the two.
 
 #include <algorithm>
 #include <cstring>
@@ -25,6 +25,7 @@ constexpr int kMaxItems = 65536;           // vertices
 constexpr int kWords = kMaxItems / 64;     // = kThreads: one bitmap word per thread
 constexpr int kMaxEntries = 2 * kMaxItems;
 constexpr int kEntryWords = kMaxEntries / 64;  // = 2 * kThreads: two keep-mask words per thread
+constexpr int kHeldItems = 4096, kHeldEntries = 16384;  // whose row pointer and columns fit LDS beside the rest
 constexpr int kStatWords = EPP_NCLASS + 1; // histogram + longest row
 constexpr int kLevelWords = 3 + kStatWords; // kept entries, rows, "set did not change", statistics
 constexpr int kRowEnd = kEntRowEnd;
@@ -78,6 +79,11 @@ __device__ __forceinline__ int block_scan(int x, int* wave_sum /* LDS, kWaves + 
     return base + incl - x;
 }
 
+// Is it cheaper to look `items` items up one by one than to walk `words` words of which they are the bits?
+__device__ __forceinline__ bool by_item(int items, int words) {
+    return (items + kThreads - 1) / kThreads * 130 < (words + kWaves - 1) / kWaves * 25;
+}
+
 struct SmallArgs {
     int n, nnz, n_train, L;
     int cv_stride, ids_stride, ptr_stride, bm_stride;  // per-level strides of the output arrays, in elements
@@ -90,33 +96,91 @@ struct SmallArgs {
     int2* cv;                     // L x nnz
     int32_t* row_ids;             // L x n
     int32_t* out_rowptr;          // L x (n + 1)
-    int* newptr;                  // n + 1 (scratch)
     long long* result;            // pinned host words: [0] error bits, [1] |N^0|, then kLevelWords per level
 };
 
+// HELD: the row pointer and the columns fit LDS too (n <= kHeldItems, nnz <= kHeldEntries) and are read once;
+// what the levels still wait for in memory is the weights of the kept entries.  Bound by the
+// instructions of one CU's sixteen wavefronts (16 cycles for each), hence the care for their number.  A
+// citation graph of 2,708 vertices and 13,200 entries, two levels: 31 -> 26 us.
+template <bool HELD>
 __global__ __launch_bounds__(kThreads) void k_prepare_small(SmallArgs a) {
-    __shared__ unsigned long long bm_cur[kWords], bm_next[kWords], keep[kEntryWords];
+    __shared__ unsigned long long bm_cur[kWords + 1], bm_next[kWords], keep[kEntryWords];
+    __shared__ unsigned int ends[2 * kEntryWords];  // one bit per kept entry: the last of its row
     __shared__ int wpre[kEntryWords], rpre[kWords];
     __shared__ int wave_sum[kWaves + 1];
     __shared__ int hist[EPP_NCLASS];
     __shared__ int s_max, s_err, s_differs;
+    __shared__ int32_t held_ptr[HELD ? kHeldItems + 1 : 1], held_col[HELD ? kHeldEntries : 1];
+    __shared__ int32_t newptr[HELD ? kHeldItems + 1 : 1];  // filtered row pointer of every vertex
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int n_words = (a.n + 63) >> 6, n_seg = (a.nnz + 63) >> 6;
 
     bm_cur[tid] = 0ull;
-    if (tid == 0) s_err = 0;
+    if (tid == 0) {
+        bm_cur[kWords] = 0ull;  // what an id that is no vertex looks up
+        s_err = 0;
+    }
     __syncthreads();
     // N^0 = V_t (Property 1); the row pointer must rise from 0 to nnz
-    for (int i = tid; i < a.n_train; i += kThreads) {
-        const int v = a.train_ids[i];
-        if (v < 0 || v >= a.n) atomicOr(&s_err, 2);
-        else atomicOr(&bm_cur[v >> 6], 1ull << (v & 63));
+    // (the column ids are range-checked here where they are held, else where the first level loads them)
+    {
+        constexpr int kPtr = HELD ? kHeldItems / kThreads : 1, kCol = HELD ? kHeldEntries / kThreads : 1;
+        int pv[kPtr], cv[kCol];
+        if constexpr (HELD) {
+#pragma unroll
+            for (int i = 0; i < kPtr; ++i) pv[i] = tid + i * kThreads < a.n ? a.rowptr[tid + i * kThreads] : 0;
+#pragma unroll
+            for (int i = 0; i < kCol; ++i) cv[i] = tid + i * kThreads < a.nnz ? a.col[tid + i * kThreads] : 0;
+            if (tid == 0) held_ptr[a.n] = a.rowptr[a.n];
+        }
+        for (int i0 = tid; i0 < a.n_train; i0 += kThreads * kBatch) {
+            int v[kBatch];
+#pragma unroll
+            for (int i = 0; i < kBatch; ++i) v[i] = i0 + i * kThreads < a.n_train ? a.train_ids[i0 + i * kThreads] : 0;
+#pragma unroll
+            for (int i = 0; i < kBatch; ++i) {
+                if (i0 + i * kThreads >= a.n_train) continue;
+                if (v[i] < 0 || v[i] >= a.n) atomicOr(&s_err, 2);
+                else atomicOr(&bm_cur[v[i] >> 6], 1ull << (v[i] & 63));
+            }
+        }
+        if constexpr (HELD) {
+#pragma unroll
+            for (int i = 0; i < kPtr; ++i)
+                if (tid + i * kThreads < a.n) held_ptr[tid + i * kThreads] = pv[i];
+#pragma unroll
+            for (int i = 0; i < kCol; ++i) {
+                if (tid + i * kThreads >= a.nnz) continue;
+                if (cv[i] < 0 || cv[i] >= a.n) atomicOr(&s_err, 4);
+                held_col[tid + i * kThreads] = cv[i];
+            }
+            __syncthreads();
+        }
     }
-    for (int v = tid; v < a.n; v += kThreads) {
-        const int p0 = a.rowptr[v], p1 = a.rowptr[v + 1];
-        if (p0 < 0 || p1 < p0 || p1 > a.nnz || (v == 0 && p0 != 0) || (v == a.n - 1 && p1 != a.nnz)) atomicOr(&s_err, 1);
+    auto row_begin = [&](int v) -> int {
+        if constexpr (HELD) return held_ptr[v];
+        else return a.rowptr[v];
+    };
+    auto column = [&](int e) -> int {
+        if constexpr (HELD) return held_col[e];
+        else return a.col[e];
+    };
+    for (int v0 = tid; v0 < a.n; v0 += kThreads * kBatch) {
+        int p0[kBatch], p1[kBatch];
+#pragma unroll
+        for (int i = 0; i < kBatch; ++i) {
+            const int v = v0 + i * kThreads;
+            p0[i] = v < a.n ? row_begin(v) : 0;
+            p1[i] = v < a.n ? row_begin(v + 1) : 0;
+        }
+#pragma unroll
+        for (int i = 0; i < kBatch; ++i) {
+            const int v = v0 + i * kThreads;
+            if (v < a.n && (p0[i] < 0 || p1[i] < p0[i] || p1[i] > a.nnz || (v == 0 && p0[i] != 0) || (v == a.n - 1 && p1[i] != a.nnz)))
+                atomicOr(&s_err, 1);
+        }
     }
-    // (the column ids are range-checked where the first level loads them)
     __syncthreads();
     if (s_err) {  // uniform: nothing is indexed with unchecked values
         if (tid == 0) a.result[0] = s_err;
@@ -145,29 +209,44 @@ __global__ __launch_bounds__(kThreads) void k_prepare_small(SmallArgs a) {
         int32_t* __restrict__ orp = a.out_rowptr + (size_t)k * a.ptr_stride;
         __syncthreads();
         bm_next[tid] = 0ull;
+        for (int i = tid; i < 2 * n_seg; i += kThreads) ends[i] = 0u;
         if (tid < EPP_NCLASS) hist[tid] = 0;
         if (tid == 0) { s_max = 0; s_differs = 0; }
         // keep-mask of the entries: is the column in N^k?  (kMaskBatch words per step and wavefront:
         // the column loads of a step are issued together, their latency is paid once.)  An id
-        // outside [0, n) is never used as an index; the first level reports it.
-        bool bad = false;
+        // outside [0, n) finds a zero; the first level reports it.
+        unsigned int top = 0;
         const unsigned int* bm32 = reinterpret_cast<const unsigned int*>(bm_cur);  // (4-byte lookups: half the bank conflicts)
         for (int w0 = wave * kMaskBatch; w0 < n_seg; w0 += kWaves * kMaskBatch) {
             int c[kMaskBatch];
+            if ((w0 + kMaskBatch) * 64 <= a.nnz) {
+#pragma unroll
+                for (int i = 0; i < kMaskBatch; ++i) c[i] = column((w0 + i) * 64 + lane);
+                if (!HELD && k == 0) {
+#pragma unroll
+                    for (int i = 0; i < kMaskBatch; ++i) top = max(top, (unsigned int)c[i]);
+                }
+            } else {
+#pragma unroll
+                for (int i = 0; i < kMaskBatch; ++i) {
+                    const int e = (w0 + i) * 64 + lane;
+                    c[i] = kMaxItems;
+                    if (e < a.nnz) {
+                        c[i] = column(e);
+                        if (!HELD && k == 0) top = max(top, (unsigned int)c[i]);
+                    }
+                }
+            }
+            unsigned long long out = 0ull;
 #pragma unroll
             for (int i = 0; i < kMaskBatch; ++i) {
-                const int e = (w0 + i) * 64 + lane;
-                c[i] = e < a.nnz ? a.col[e] : -1;
+                const unsigned int x = min((unsigned int)c[i], (unsigned int)kMaxItems);
+                const unsigned long long m = __ballot((bm32[x >> 5] >> (x & 31)) & 1u);
+                if (lane == i) out = m;
             }
-#pragma unroll
-            for (int i = 0; i < kMaskBatch; ++i) {
-                const bool in_range = c[i] >= 0 && c[i] < a.n;
-                bad |= !in_range && (w0 + i) * 64 + lane < a.nnz;
-                const bool bit = in_range && ((bm32[c[i] >> 5] >> (c[i] & 31)) & 1u);
-                const unsigned long long m = __ballot(bit);
-                if (lane == 0 && w0 + i < n_seg) keep[w0 + i] = m;
-            }
+            if (lane < kMaskBatch && w0 + lane < n_seg) keep[w0 + lane] = out;
         }
+        const bool bad = top >= (unsigned int)a.n;
         if (k == 0 && bad) atomicOr(&s_err, 4);
         __syncthreads();
         if (k == 0 && s_err) {  // uniform
@@ -183,75 +262,99 @@ __global__ __launch_bounds__(kThreads) void k_prepare_small(SmallArgs a) {
             wpre[2 * tid + 1] = wbase + c0;
         }
         __syncthreads();
-        // stable compaction of (col, val), one kept entry per thread and step: slot j of the path
-        // belongs to the word whose prefix count is the last one not above j, and is that word's
-        // (j - prefix)-th set bit.  (Walking all words instead costs a load latency per word
-        // whatever it keeps; a small training set keeps a few hundred entries out of 10^5.)
-        for (int j0 = tid; j0 < kept; j0 += kThreads * kBatch) {
-            int e[kBatch];
-            int2 x[kBatch];
-#pragma unroll
-            for (int i = 0; i < kBatch; ++i) {
-                const int j = j0 + i * kThreads;
-                e[i] = -1;
-                if (j < kept) {
-                    const int w = last_not_above(wpre, n_seg, j);
-                    e[i] = w * 64 + select_bit(keep[w], j - wpre[w]);
-                }
-            }
-#pragma unroll
-            for (int i = 0; i < kBatch; ++i)
-                if (e[i] >= 0) x[i] = make_int2(a.col[e[i]], __float_as_int(a.val[e[i]]));
-#pragma unroll
-            for (int i = 0; i < kBatch; ++i)
-                if (e[i] >= 0) cv[j0 + i * kThreads] = x[i];
-        }
-        // filtered row pointer of every vertex; a vertex with a non-empty filtered list is in N^{k+1}
+        auto kept_before = [&](int p) -> int {
+            return p >= a.nnz ? kept : wpre[p >> 6] + __popcll(keep[p >> 6] & low_mask(p & 63));
+        };
+        // filtered list of every vertex; a vertex whose list is not empty is in N^{k+1}
         // (the 64 lanes of a wavefront hold the 64 vertices of one bitmap word: one ballot per word)
         int longest = 0;
-        for (int v0 = tid; v0 - lane < a.n; v0 += kThreads * kBatch) {
-            int p0[kBatch], p1[kBatch];
-#pragma unroll
-            for (int i = 0; i < kBatch; ++i) {
-                const int v = v0 + i * kThreads;
-                p0[i] = v < a.n ? a.rowptr[v] : a.nnz;
-                p1[i] = v < a.n ? a.rowptr[v + 1] : a.nnz;
+        auto count_row = [&](int v, int ra, int rb) {
+            const bool member = v < a.n && rb > ra;
+            const unsigned long long word = __ballot(member);
+            if (lane == 0 && (v >> 6) < n_words) bm_next[v >> 6] = word;
+            if (member) {
+                const int len = rb - ra;
+                atomicOr(&ends[(rb - 1) >> 5], 1u << ((rb - 1) & 31));
+                atomicAdd(&hist[length_class(len)], 1);
+                longest = max(longest, len);
             }
+        };
+        if constexpr (HELD) {
+            for (int v = tid; v <= a.n; v += kThreads) newptr[v] = kept_before(row_begin(v));
+            __syncthreads();
+            for (int v = tid; v - lane < a.n; v += kThreads)
+                count_row(v, v < a.n ? newptr[v] : 0, v < a.n ? newptr[v + 1] : 0);
+        } else {
+            for (int v0 = tid; v0 - lane < a.n; v0 += kThreads * kBatch) {
+                int p0[kBatch], p1[kBatch];
 #pragma unroll
-            for (int i = 0; i < kBatch; ++i) {
-                const int v = v0 + i * kThreads;
-                const int ra = p0[i] >= a.nnz ? kept : wpre[p0[i] >> 6] + __popcll(keep[p0[i] >> 6] & low_mask(p0[i] & 63));
-                const int rb = p1[i] >= a.nnz ? kept : wpre[p1[i] >> 6] + __popcll(keep[p1[i] >> 6] & low_mask(p1[i] & 63));
-                const bool member = v < a.n && rb > ra;
-                if (v < a.n) a.newptr[v] = ra;
-                const unsigned long long word = __ballot(member);
-                if (lane == 0 && (v >> 6) < n_words) bm_next[v >> 6] = word;
-                if (member) {
-                    const int len = rb - ra;
-                    atomicAdd(&hist[length_class(len)], 1);
-                    longest = max(longest, len);
+                for (int i = 0; i < kBatch; ++i) {
+                    const int v = v0 + i * kThreads;
+                    p0[i] = v < a.n ? row_begin(v) : a.nnz;
+                    p1[i] = v < a.n ? row_begin(v + 1) : a.nnz;
+                }
+#pragma unroll
+                for (int i = 0; i < kBatch; ++i) {
+                    if (v0 - lane + i * kThreads >= a.n) break;  // (uniform)
+                    count_row(v0 + i * kThreads, kept_before(p0[i]), kept_before(p1[i]));
                 }
             }
         }
 #pragma unroll
         for (int d = 32; d >= 1; d >>= 1) longest = max(longest, __shfl_xor(longest, d, 64));
         if (lane == 0 && longest > 0) atomicMax(&s_max, longest);
-        __syncthreads();  // bm_next, newptr and the compacted entries are complete
+        __syncthreads();  // bm_next and the row ends are complete
+        // Stable compaction of (col, val), word by word: a kept entry's place is its word's prefix count plus
+        // the kept ones before it in the word.  Where little is kept, entry by entry instead: slot j
+        // of the path belongs to the word whose prefix count is the last one not above j, and is that
+        // word's (j - prefix)-th set bit (some 130 instructions per entry and thread, against 14
+        // per word and wavefront, whose number this one workgroup is bound by).
+        if (by_item(kept, n_seg)) {
+            for (int j = tid; j < kept; j += kThreads) {
+                const int w = last_not_above(wpre, n_seg, j), e = w * 64 + select_bit(keep[w], j - wpre[w]);
+                const int flag = (ends[j >> 5] >> (j & 31)) & 1u ? kRowEnd : 0;
+                cv[j] = make_int2(column(e) | flag, __float_as_int(a.val[e]));
+            }
+        } else {
+            for (int w0 = wave; w0 < n_seg; w0 += kWaves * kBatch) {
+                unsigned long long m[kBatch];
+                int2 x[kBatch];
+#pragma unroll
+                for (int i = 0; i < kBatch; ++i) {
+                    const int w = w0 + i * kWaves;
+                    m[i] = w < n_seg ? keep[w] : 0ull;
+                    if ((m[i] >> lane) & 1ull) x[i] = make_int2(column(w * 64 + lane), __float_as_int(a.val[w * 64 + lane]));
+                }
+#pragma unroll
+                for (int i = 0; i < kBatch; ++i) {
+                    if (!((m[i] >> lane) & 1ull)) continue;
+                    const int j = wpre[w0 + i * kWaves] + __popcll(m[i] & low_mask(lane));
+                    if ((ends[j >> 5] >> (j & 31)) & 1u) x[i].x |= kRowEnd;
+                    cv[j] = x[i];
+                }
+            }
+        }
         int R;
         const int rbase = block_scan(tid < n_words ? __popcll(bm_next[tid]) : 0, wave_sum, &R);
         rpre[tid] = rbase;
         if (tid < n_words && bm_next[tid] != bm_cur[tid]) s_differs = 1;
         __syncthreads();
-        // rows of the path, one per thread and step (found like the entries above)
-        for (int r = tid; r < R; r += kThreads) {
-            const int w = last_not_above(rpre, n_words, r);
-            const int v = w * 64 + select_bit(bm_next[w], r - rpre[w]);
+        // rows of the path (in the same two ways)
+        auto put_row = [&](int r, int v) {
             row_ids[r] = v;
-            orp[r] = a.newptr[v];
-            // last entry of the row: one before the next vertex's first kept entry
-            const int p1 = a.rowptr[v + 1];
-            const int rb = p1 >= a.nnz ? kept : wpre[p1 >> 6] + __popcll(keep[p1 >> 6] & low_mask(p1 & 63));
-            cv[rb - 1].x |= kRowEnd;
+            if constexpr (HELD) orp[r] = newptr[v];
+            else orp[r] = kept_before(row_begin(v));
+        };
+        if (by_item(R, n_words)) {
+            for (int r = tid; r < R; r += kThreads) {
+                const int w = last_not_above(rpre, n_words, r);
+                put_row(r, w * 64 + select_bit(bm_next[w], r - rpre[w]));
+            }
+        } else {
+            for (int w = wave; w < n_words; w += kWaves) {
+                const unsigned long long m = bm_next[w];
+                if ((m >> lane) & 1ull) put_row(rpre[w] + __popcll(m & low_mask(lane)), w * 64 + lane);
+            }
         }
         long long* res = a.result + 2 + (size_t)k * kLevelWords;
         if (tid == 0) {
@@ -271,7 +374,11 @@ __global__ __launch_bounds__(kThreads) void k_prepare_small(SmallArgs a) {
 }  // namespace
 
 bool epp_prepare_small_fits(const epp_csr_t* g, int64_t n_train, int L) {
-    return g->n <= kMaxItems && g->nnz <= kMaxEntries && n_train <= kMaxItems && L <= 32 && g->n > 0;
+    // (one workgroup's time grows with the graph, the general construction's hardly does below a million
+    // entries: 83 to 103 us against 124 at 10,000 vertices and 64,000 entries, 103 to 131 against 122 at
+    // 10,000 and 117,000, 121 to 155 against 123 at 20,000 and 117,000, two levels each)
+    return g->n <= kMaxItems && g->nnz <= kMaxEntries && g->nnz + 3 * g->n <= 140000 && n_train <= kMaxItems && L <= 32 &&
+           g->n > 0;
 }
 
 int epp_prepare_small(const epp_csr_t* g, const int32_t* train_ids, int64_t n_train, int L, const epp_alloc_t* alloc,
@@ -293,16 +400,14 @@ int epp_prepare_small(const epp_csr_t* g, const int32_t* train_ids, int64_t n_tr
                  ids_bytes = (size_t)n * 4, ptr_bytes = (size_t)(n + 1) * 4;
     DevArena arena;
     EPP_TRY(arena.reserve((size_t)(L + 1) * DevArena::rounded(bm_bytes) + DevArena::rounded(ids_bytes) +
-                          (size_t)L * (DevArena::rounded(cv_bytes) + DevArena::rounded(ids_bytes) + DevArena::rounded(ptr_bytes)) +
-                          DevArena::rounded(ptr_bytes), al));
+                          (size_t)L * (DevArena::rounded(cv_bytes) + DevArena::rounded(ids_bytes) + DevArena::rounded(ptr_bytes)), al));
     // (every level's arrays start 256-byte aligned: the strides are the rounded sizes)
-    DevBuf bm_all, set0, cv_all, ids_all, ptr_all, newptr;
+    DevBuf bm_all, set0, cv_all, ids_all, ptr_all;
     arena.take(&bm_all, (size_t)(L + 1) * DevArena::rounded(bm_bytes));
     arena.take(&set0, ids_bytes);
     arena.take(&cv_all, (size_t)L * DevArena::rounded(cv_bytes));
     arena.take(&ids_all, (size_t)L * DevArena::rounded(ids_bytes));
     arena.take(&ptr_all, (size_t)L * DevArena::rounded(ptr_bytes));
-    arena.take(&newptr, ptr_bytes);
     PinnedWords pinned;
     EPP_TRY(pinned.get(result_words));
     long long* host = pinned.p;
@@ -325,9 +430,9 @@ int epp_prepare_small(const epp_csr_t* g, const int32_t* train_ids, int64_t n_tr
     a.cv = cv_all.as<int2>();
     a.row_ids = ids_all.as<int32_t>();
     a.out_rowptr = ptr_all.as<int32_t>();
-    a.newptr = newptr.as<int>();
     a.result = host;  // (the kernel writes a few dozen words there itself: a copy would be a launch of its own)
-    hipLaunchKernelGGL(k_prepare_small, dim3(1), dim3(kThreads), 0, s, a);
+    if (n <= kHeldItems && nnz <= kHeldEntries) hipLaunchKernelGGL(k_prepare_small<true>, dim3(1), dim3(kThreads), 0, s, a);
+    else hipLaunchKernelGGL(k_prepare_small<false>, dim3(1), dim3(kThreads), 0, s, a);
     EPP_HIP_TRY(hipGetLastError());
     EPP_HIP_TRY(hipStreamSynchronize(s));
     if (host[0] != 0) {
