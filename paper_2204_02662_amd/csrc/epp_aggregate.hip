@@ -45,23 +45,45 @@ template <int VEC, class V> __device__ __forceinline__ float lane_get(const V& x
 }
 
 // ---------------------------------------------------------------- schedule construction
-// One thread per row (streamed rows are non-empty): it is the row of the first entry of every group that
+// A thread per row (streamed rows are non-empty): it is the row of the first entry of every group that
 // starts inside it.  Bit 31 marks a group that starts past the row's beginning; a row with such a
-// group is cut, and listed once.  (A search of the row pointer for every group is a chain of
-// some twenty loads: 12 us where this takes 4.)
-__global__ __launch_bounds__(kBlock) void k_sched_groups(const int32_t* __restrict__ rowptr, int64_t n_rows, int gs,
-                                                         int32_t* __restrict__ group_row, int32_t* __restrict__ cut_rows,
-                                                         unsigned int* __restrict__ n_cut) {
-    const int64_t r = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (r >= n_rows) return;
-    const int64_t p0 = rowptr[r], p1 = rowptr[r + 1];
-    bool cut = false;
-    for (int64_t g = (p0 + gs - 1) / gs; g * gs < p1; ++g) {
-        const bool inside = g * gs > p0;
-        group_row[g] = (int32_t)r | (inside ? kRowEnd : 0);
-        cut |= inside;
+// group is cut, and listed once.  A workgroup takes kSchedRows rows and one place in the list for
+// all its cut rows together: an addition to the one counter costs 8 ns, whoever makes it.  (A search of
+// the row pointer for every group, the other way round, is a chain of some twenty loads.)
+constexpr int kSchedRows = 4096;
+__global__ __launch_bounds__(1024) void k_sched_groups(const int32_t* __restrict__ rowptr, int64_t n_rows, int gs,
+                                                       int32_t* __restrict__ group_row, int32_t* __restrict__ cut_rows,
+                                                       unsigned int* __restrict__ n_cut) {
+    __shared__ unsigned int count, place;
+    if (threadIdx.x == 0) count = 0;
+    __syncthreads();
+    constexpr int kPer = kSchedRows / 1024;
+    const int64_t r0 = (int64_t)blockIdx.x * kSchedRows + threadIdx.x;
+    const unsigned int step = (unsigned int)gs;
+    unsigned int p0[kPer], p1[kPer], at[kPer];
+#pragma unroll
+    for (int i = 0; i < kPer; ++i) {
+        const int64_t r = r0 + i * 1024;
+        p0[i] = r < n_rows ? (unsigned int)rowptr[r] : 0u;
+        p1[i] = r < n_rows ? (unsigned int)rowptr[r + 1] : 0u;
     }
-    if (cut) cut_rows[atomicAdd(n_cut, 1u)] = (int32_t)r;
+    bool cut[kPer];
+#pragma unroll
+    for (int i = 0; i < kPer; ++i) {
+        unsigned int g = (p0[i] + step - 1) / step;  // (32 bits: entries and group size are below 2^31)
+        cut[i] = false;
+        for (unsigned int j = g * step; j < p1[i] && j >= p0[i]; j += step, ++g) {
+            group_row[g] = (int32_t)(r0 + i * 1024) | (j > p0[i] ? kRowEnd : 0);
+            cut[i] |= j > p0[i];
+        }
+        at[i] = cut[i] ? atomicAdd(&count, 1u) : 0u;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0 && count) place = atomicAdd(n_cut, count);
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < kPer; ++i)
+        if (cut[i]) cut_rows[place + at[i]] = (int32_t)(r0 + i * 1024);
 }
 
 // ------------------------------------------------------------------------- aggregation
@@ -655,8 +677,8 @@ int epp_build_schedule_over(const epp_path* p, const int32_t* rowptr, int64_t n_
         PinnedWords host;
         EPP_TRY(host.get(1));
         EPP_HIP_TRY(hipMemsetAsync(n_cut, 0, sizeof(unsigned int), s));
-        hipLaunchKernelGGL(k_sched_groups, dim3((unsigned)((n_rows + kBlock - 1) / kBlock)), dim3(kBlock), 0, s, rowptr, n_rows,
-                           gs, sc->group_row.as<int32_t>(), sc->cut_rows.as<int32_t>(), n_cut);
+        hipLaunchKernelGGL(k_sched_groups, dim3((unsigned)((n_rows + kSchedRows - 1) / kSchedRows)), dim3(1024), 0, s, rowptr,
+                           n_rows, gs, sc->group_row.as<int32_t>(), sc->cut_rows.as<int32_t>(), n_cut);
         EPP_HIP_TRY(hipGetLastError());
         host.p[0] = 0;
         EPP_HIP_TRY(hipMemcpyAsync(host.p, n_cut, sizeof(unsigned int), hipMemcpyDeviceToHost, s));
