@@ -34,8 +34,9 @@ constexpr int kBlock = 256;
 constexpr int kRowEnd = kEntRowEnd, kCold = kEntCold, kOuterOnly = kEntOuterOnly, kColMask = kEntCol;
 
 typedef int int2v __attribute__((ext_vector_type(2)));
-typedef float float2v __attribute__((ext_vector_type(2)));
-typedef float float4v __attribute__((ext_vector_type(4)));
+// (at 4-byte alignment, all that global accesses need: a row of any width is read and written 16 bytes a lane)
+typedef float float2v __attribute__((ext_vector_type(2), aligned(4)));
+typedef float float4v __attribute__((ext_vector_type(4), aligned(4)));
 template <int VEC> struct VecT;
 template <> struct VecT<1> { typedef float type; };
 template <> struct VecT<2> { typedef float2v type; };
@@ -107,6 +108,7 @@ struct AggArgs {
     int64_t nnz;
     int64_t n_groups;
     int F;
+    int ld;                    // floats from one row of `in` to the next
     int gs;
     int log2ns;                // feature slices spread over the XCDs (1 << log2ns of them)
     int has_cold;              // some entries carry the cold flag (host-side kernel choice)
@@ -320,7 +322,11 @@ __global__ __launch_bounds__(kBlock, IFELSE ? ((COLD && VEC != 1) ? 4 : 5) : ((I
     for (int f0 = 0; f0 < a.F; f0 += (T * VEC) << a.log2ns) {
         const int f = f0 + (slice * T + t) * VEC;
         const bool fok = f < a.F;
-        const float* __restrict__ src = a.in + (fok ? f : 0);
+        // a lane of 16 bytes that would reach past the row's end steps back to it (its neighbour's features
+        // are computed twice, with equal results); so do the lanes past it, which never write
+        const int fl = std::min(f, a.F - VEC);
+        const int fw = VEC == 4 ? fl : f;  // (narrower lanes never reach past it)
+        const float* __restrict__ src = a.in + fl;
         // first 4T pairs of the group: issued before anything that depends on the group table,
         // so that the two load chains (pairs -> gathers, group row -> vertex id) overlap
         // (pairs past the end of the group are clamped loads; they are neutralised only when they
@@ -389,7 +395,7 @@ __global__ __launch_bounds__(kBlock, IFELSE ? ((COLD && VEC != 1) ? 4 : 5) : ((I
                 vec_t x[U];
 #pragma unroll
                 for (int u = 0; u < U; ++u) e[u] = stage[b + u];
-                // (lanes past the last feature read feature 0 and never write: the loads stay
+                // (lanes past the last feature read the last one's and never write: the loads stay
                 // unconditional, so that nothing but their own results is ever waited on)
                 bool act[U];
 #pragma unroll
@@ -401,7 +407,7 @@ __global__ __launch_bounds__(kBlock, IFELSE ? ((COLD && VEC != 1) ? 4 : 5) : ((I
                 for (int u = 0; u < U; ++u) {
                     if (act[u]) {
                         const int c = e[u].x & kColMask;
-                        gvec_ptr p = (gvec_ptr)(src + (size_t)c * (size_t)a.F);
+                        gvec_ptr p = (gvec_ptr)(src + (size_t)c * (size_t)a.ld);
                         if constexpr (INNER) p = (e[u].x & kOuterOnly) ? (gvec_ptr)a.zero : p;
                         if (COLD && (e[u].x & kCold)) {
                             // rarely referenced source: streamed, so that it does not evict hot rows from
@@ -439,13 +445,13 @@ __global__ __launch_bounds__(kBlock, IFELSE ? ((COLD && VEC != 1) ? 4 : 5) : ((I
                             // trace, so that it is not kept in registers across the whole loop)
                             unsigned gl = gi;
                             asm volatile("" : "+v"(gl));
-                            if (fok) write_row<VEC>(a.pieces + (size_t)(2 * gl) * (size_t)a.F + f, acc);
+                            if (fok) write_row<VEC>(a.pieces + (size_t)(2 * gl) * (size_t)a.F + fw, acc);
                         } else if (wr) {
                             // (a target >= n is one section's share of a cut row: it goes to the array of
                             // partial rows, addressed relative to `out` so that the store stays one instruction)
                             uintptr_t base = reinterpret_cast<uintptr_t>(a.out);
                             if constexpr (PART) base += v >= a.n ? a.part_delta : 0;
-                            write_row<VEC>(reinterpret_cast<float*>(base) + ((size_t)v * (size_t)a.F + f), acc);
+                            write_row<VEC>(reinterpret_cast<float*>(base) + ((size_t)v * (size_t)a.F + fw), acc);
                         }
 #pragma unroll
                         for (int i = 0; i < VEC; ++i) acc[i] = 0.0f;
@@ -474,8 +480,36 @@ __global__ __launch_bounds__(kBlock, IFELSE ? ((COLD && VEC != 1) ? 4 : 5) : ((I
         if (open && fok) {
             unsigned gl = gi;
             asm volatile("" : "+v"(gl));
-            write_row<VEC>(a.pieces + (size_t)(2 * gl + 1) * (size_t)a.F + f, acc);
+            write_row<VEC>(a.pieces + (size_t)(2 * gl + 1) * (size_t)a.F + fw, acc);
         }
+    }
+}
+
+// Copies the source rows, F floats each, to rows of 4 q floats (the rest zero).  Rows that are not in the
+// bitmap `sources` (NULL: all are) are left out.  One workgroup per word of the bitmap.  Bound by memory:
+// 197 K of 2.4 M rows of 47 floats in 53 us, 233 K of 233 K rows of 41, 83 MB moved, in 13.
+constexpr int kPackRows = 64;
+__global__ __launch_bounds__(kBlock) void k_pack_rows(const float* __restrict__ in, int64_t n, int F, int q, unsigned rcp_q,
+                                                      const unsigned long long* __restrict__ sources, float* __restrict__ out) {
+    const unsigned long long mine = sources ? sources[blockIdx.x] : ~0ull;
+    if (!mine) return;
+    const int64_t r0 = (int64_t)blockIdx.x * kPackRows;
+    const int items = (int)std::min<int64_t>(n - r0, kPackRows) * q;
+    const float* __restrict__ src = in + r0 * F;
+    float4v* __restrict__ dst = reinterpret_cast<float4v*>(out + r0 * (4 * q));
+    for (int i = threadIdx.x; i < items; i += kBlock) {
+        const int r = (int)__umulhi((unsigned)i, rcp_q), f = (i - r * q) * 4;  // i / q: exact, i < 64 q and 64 q^2 < 2^32
+        if (!((mine >> r) & 1)) continue;
+        const float* __restrict__ x = src + (int64_t)r * F + f;
+        float4v v = {0.0f, 0.0f, 0.0f, 0.0f};
+        if (f + 4 <= F) {
+            v = *reinterpret_cast<const float4v*>(x);
+        } else {
+            if (f < F) v.x = x[0];
+            if (f + 1 < F) v.y = x[1];
+            if (f + 2 < F) v.z = x[2];
+        }
+        dst[i] = v;
     }
 }
 
@@ -490,16 +524,20 @@ int ceil_log2(int x) {
     return l;
 }
 
-// Lanes per source row and floats per lane for width F.  (16-byte accesses at 4-byte
-// alignment for widths that are not a multiple of four were tried and measured no faster:
-// F = 41: 1.34 vs 1.45 ms, F = 47: 0.51 vs 0.48 ms; the plain per-float form is kept.)
-void row_shape(int F, bool aligned16, int* vec, int* log2T) {
-    int v = (F % 4 == 0) ? 4 : (F % 2 == 0 ? 2 : 1);
-    if (!aligned16) v = 1;
+// Lanes per source row and floats per lane for width F.  Rows of 16-byte multiples, packed rows and the
+// source-partitioned layout take 16 bytes a lane.  Rows of other widths are bound by the 128-byte lines
+// they straddle, whatever the lane width (F = 47, 140 M entries: 5.77 ms at 4, 5.83 at 16 bytes a lane),
+// up to where 4- or 8-byte lanes need a second pass over the row, which 16-byte lanes do not
+// (F = 65: 9.7 to 6.9 ms; F = 129: 17.5 to 12.1).
+void row_shape(int F, bool wide, int* vec, int* log2T) {
+    const int v = (F % 4 == 0 || F > 64 || (wide && F > 4)) ? 4 : (F % 2 == 0 ? 2 : 1);
     int frags = (F + v - 1) / v;
     *vec = v;
     *log2T = std::min(ceil_log2(frags), 6);
 }
+
+// Whether launches of this width make use of the cold flags (see epp_tune_locality).
+bool marks_pay(int F, int ld) { return F > 32 && (ld % 4 == 0 || F > 64); }
 
 template <int VEC, int LOG2T, int U, bool INNER>
 void launch_plain(dim3 grid, dim3 block, hipStream_t s, const AggArgs& a) {
@@ -593,11 +631,15 @@ __global__ __launch_bounds__(kBlock) void k_count_hist(const int* __restrict__ c
     if (threadIdx.x < kCountBins && h[threadIdx.x]) atomicAdd(&hist[threadIdx.x], (unsigned long long)h[threadIdx.x]);
 }
 
-// One bit per vertex: referenced at least `thr` times in the sample.
-__global__ __launch_bounds__(kBlock) void k_hot_bitmap(const int* __restrict__ cnt, int64_t n, int thr,
+// One bit per vertex: referenced at least `thr` times in the sample, or one of the share (in 65536ths) of
+// those referenced at least `part_thr` times, picked by a hash of the id (another one than deals the hot sources to the XCDs).
+struct HotLine { int thr, part_thr, share; };
+__global__ __launch_bounds__(kBlock) void k_hot_bitmap(const int* __restrict__ cnt, int64_t n, HotLine line,
                                                        unsigned long long* __restrict__ bits) {
     int64_t v = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    const unsigned long long b = __ballot(v < n && cnt[v] >= thr);
+    const int k = v < n ? cnt[v] : -1;
+    const bool picked = (int)(((unsigned)v * 0x85EBCA6Bu) >> 16) < line.share;
+    const unsigned long long b = __ballot(v < n && (k >= line.thr || (k >= line.part_thr && picked)));
     if ((threadIdx.x & 63) == 0 && (v >> 6) < ((n + 63) >> 6)) bits[v >> 6] = b;
 }
 
@@ -658,6 +700,35 @@ int epp_default_group_size(const epp_path* p, int F) {
     return 1 << e;
 }
 
+// 128-byte lines that a row of F floats touches on average where the rows are `ld` floats apart.
+static double lines_per_row(int F, int ld) {
+    int64_t lines = 0;
+    for (int64_t r = 0; r < 32; ++r) lines += (r * ld + F - 1) / 32 - r * ld / 32 + 1;  // (32 rows: the pattern repeats)
+    return (double)lines / 32;
+}
+
+// Packed source rows.  A launch on large matrices is bound by the 128-byte lines it gathers, and a row of
+// a width like 31 or 47 lies across one more of them than it would fill.  It pays to copy the source
+// rows once per launch to a stride that keeps them apart from the lines' ends (a power of two, beyond 16
+// floats a multiple of 16) where the lines saved by all entries cost more than the copy: about 60 G lines
+// a second come from memory, twice that where the copy (96 MB at most) stays in the memory-side cache,
+// and the copy costs its bytes at 3.7 TB/s (it also displaces cached rows), a launch and a workgroup per 64
+// vertices.  Measured
+// (plain -> packed): 114 M entries, 233 K sources, F = 17 / 31: 1214 -> 910 / 1803 -> 929 us; 140 M entries,
+// 2.4 M sources, F = 31 / 47 / 63: 4596 -> 2738 / 5773 -> 4912 / 7100 -> 5107 us; 37 M entries of as many sources,
+// F = 31 / 63: 1268 -> 951 / 1918 -> 1611 us, but F = 41 / 73, which the rule leaves alone: 1477 -> 1561 / 2160 -> 2320.
+int epp_packed_stride(const epp_path* p, int F) {
+    const int mode = env_int("EPP_TUNE_PACK", 1);  // 0: never, 1: where it pays, 2: always (tests)
+    if (mode == 0 || F < 5 || F > (1 << 13) || p->nnz == 0) return F;
+    const int ld = F <= 16 ? 1 << ceil_log2(F) : (F + 15) / 16 * 16;
+    if (ld == F) return F;
+    if (mode == 2) return ld;
+    const double copy_bytes = 4.0 * (double)p->n_src * (F + ld);
+    const double rate = (double)p->n_src * ld * 4 <= 96e6 ? 120e9 : 60e9;
+    const double saved = (lines_per_row(F, F) - lines_per_row(F, ld)) * (double)p->nnz / rate;
+    return saved > 6e-6 + 3e-12 * (double)p->n + 1.25 * copy_bytes / 3.7e12 ? ld : F;
+}
+
 int epp_build_schedule_over(const epp_path* p, const int32_t* rowptr, int64_t n_rows, int64_t nnz, int gs,
                             hipStream_t s, Schedule** out) {
     Schedule* sc = new Schedule();
@@ -710,14 +781,13 @@ int epp_zero_empty_rows(const epp_path* p, float* out, int F, hipStream_t s) {
 
 int epp_launch_aggregate(epp_path* p, Schedule* sc, int log2_slices, const float* in, float* out, int F, hipStream_t s,
                          const unsigned int* row_bits, const unsigned int* src_bits, const Partition* part,
-                         const unsigned int* inner_rows) {
+                         const unsigned int* inner_rows, float* packed, int ld, const unsigned long long* sources) {
     if (inner_rows && (row_bits || !p->has_inner || !p->zero_block.p)) {
         epp_set_error("the path's entries are not marked for an inner path");
         return EPP_ERR_INVALID_ARG;
     }
     int vec, log2T;
-    const bool aligned16 = ((reinterpret_cast<uintptr_t>(in) | reinterpret_cast<uintptr_t>(out)) & 15) == 0;
-    row_shape(F, aligned16, &vec, &log2T);
+    row_shape(F, (part && F > 32) || packed, &vec, &log2T);
     // feature slices over the XCDs: each slice keeps whole 128-byte lines of a row
     int log2ns = part ? 0 : std::min(std::max(log2_slices, 0), 3);
     while (log2ns > 0 && ((log2T - log2ns) < 0 || ((vec * 4) << (log2T - log2ns)) < 128)) --log2ns;
@@ -728,20 +798,26 @@ int epp_launch_aggregate(epp_path* p, Schedule* sc, int log2_slices, const float
     float* pieces = sc->pieces_for(F);
     if (sc->n_split_rows > 0 && !pieces) { epp_set_error("no partial-row buffer for F=%d", F); return EPP_ERR_INVALID_ARG; }
     if (!row_bits) EPP_TRY(epp_zero_empty_rows(p, out, F, s));
+    if (packed && sc->n_groups > 0) {
+        const int q = ld / 4;
+        hipLaunchKernelGGL(k_pack_rows, dim3((unsigned)((p->n + kPackRows - 1) / kPackRows)), dim3(kBlock), 0, s, in, p->n, F, q,
+                           (unsigned)((0x100000000ull + q - 1) / q), sources, packed);
+    }
     if (sc->n_groups > 0) {
         AggArgs a;
         a.cv = reinterpret_cast<const int2v*>(part ? part->cv2.p : p->cv.p);
         a.group_row = sc->group_row.as<int32_t>();
         a.row_ids = row_ids;
         a.n_rows = part ? part->n_vrows : p->n_stream_rows;
-        a.in = in;
+        a.in = packed ? packed : in;
         a.out = out;
         a.nnz = p->nnz;
         a.n_groups = sc->n_groups;
         a.F = F;
+        a.ld = packed ? ld : F;
         a.gs = sc->gs;
         a.log2ns = log2ns;
-        a.has_cold = p->cold_thr > 0 && (int64_t)F * 4 >= 256;  // narrow rows ignore the marks (bit 30 is masked)
+        a.has_cold = p->has_cold && marks_pay(F, packed ? ld : F);  // others ignore the marks (bit 30 is masked)
         a.pieces = pieces;
         a.row_bits = row_bits;
         a.src_bits = src_bits;
@@ -788,6 +864,17 @@ int epp_launch_aggregate(epp_path* p, Schedule* sc, int log2_slices, const float
     return EPP_OK;
 }
 
+// Share of the entries that lie in rows long enough to be cut into sections (96 entries and more), estimated from
+// the length classes (class c: 2^(c-1) < length <= 2^c).  With the share of the references that go to the
+// sources the L2s hold it tells, before anything is built, where the source-partitioned layout cannot
+// reach the score it is kept for, 0.12 = 0.75 * 0.16: below 0.11 the attempt is not made.
+constexpr double kMinEstimate = 0.11;
+static double long_row_share(const epp_path* p) {
+    double entries = 0.4 * 110.0 * (double)p->len_hist[7];
+    for (int c = 8; c < EPP_NCLASS; ++c) entries += 0.7 * (double)(1ll << c) * (double)p->len_hist[c];
+    return std::min(entries / (double)std::max<int64_t>(p->nnz, 1), 1.0);
+}
+
 // Cache-locality choices of one (path, width), made from how often the path references each
 // source.
 //
@@ -795,6 +882,8 @@ int epp_launch_aggregate(epp_path* p, Schedule* sc, int log2_slices, const float
 // XCD, 256 MB memory-side cache); with plain loads the rarely referenced rows keep evicting
 // the often referenced ones.  The most referenced sources, as many as fit the budget, stay
 // "hot"; all entries of the others get the cold flag and are gathered with streaming loads.
+// Budget of 64 / 80 / 96 / 128 MB, two layers each: 270 M entries, F = 128: 29.1 / 29.3 / 29.5 / 29.8 ms; 126 M
+// entries, F = 64: 9.47 / 9.25 / 9.26 / 9.48 ms.
 //
 // Source partition (epp_partition.hip).  The entries that reference the sources the eight L2s can
 // hold together are moved into one section per XCD; built where the counts say it pays.
@@ -806,21 +895,30 @@ int epp_launch_aggregate(epp_path* p, Schedule* sc, int log2_slices, const float
 // slicing, but not without, receive at least 6 % of all references (measured: R-MAT
 // configuration, 8 % -> 16.5 to 15.3 ms; Chung-Lu configuration, 4 % -> 4.3 to 4.6 ms, left off).
 int epp_tune_locality(epp_path* p, int F, int gs, hipStream_t s, int* log2_slices, Partition** part) {
-    const int64_t budget_mb = env_int("EPP_TUNE_HOT_MB", 96);
-    const int64_t rows_budget = budget_mb * (1ll << 20) / ((int64_t)F * 4);
+    const int64_t budget_mb = env_int("EPP_TUNE_HOT_MB", 80);
+    const int ld = epp_packed_stride(p, F);
+    const int64_t rows_budget = budget_mb * (1ll << 20) / ((int64_t)ld * 4);
     const int forced_slices = env_int("EPP_TUNE_LOG2_SLICES", -1);
     *log2_slices = forced_slices >= 0 ? forced_slices : 0;
     *part = nullptr;
-    // (measured useful for rows of 256 bytes and more; at F = 47 the extra branch costs 3 %)
+    // Cold marks: for rows of more than one 128-byte line read 16 bytes a lane (140 M entries, 2.4 M sources,
+    // F = 36 / 47, packed / 48: 4820 -> 4614 / 4958 -> 4737 / 4773 -> 4525 us; F = 32: 2566 -> 2555; with 4-byte lanes the
+    // extra branch costs 3 %).
+    // Source partition: for rows of more than one 128-byte line (114 M entries, 233 K sources, F = 36 / 48 / 64:
+    // 1908 -> 1515 / 1985 -> 1451 / 2141 -> 1425 us; rows of one line gain nothing, F = 32: 908 -> 1010).
     const int part_mode = env_int("EPP_TUNE_PART", 1);
-    if (p->nnz == 0 || ((int64_t)F * 4 < 256 && part_mode != 2)) return EPP_OK;
-    const int64_t part_rows = forced_slices >= 0 ? 0 : epp_partition_hot_rows(F);  // a forced slicing is a measurement
-    const bool want_cold = budget_mb > 0 && p->n_src > rows_budget && (int64_t)F * 4 >= 256;
-    // (in the automatic mode only where the source rows do not fit the eight L2s together; forced,
-    // for tests and measurements, at any width and size: on a graph whose narrow source rows all fit,
-    // it lifts the L2 hit rate from 62-76 % to 93 % and the time stays the same, because such
-    // launches are bound by the rate at which a CU's address unit and L1 take gather requests)
-    const bool want_part = part_rows > 0 && (part_mode == 2 || (part_mode == 1 && p->n_src > part_rows));
+    if (p->nnz == 0 || (F <= 32 && part_mode != 2)) return EPP_OK;
+    const int64_t part_rows = forced_slices >= 0 ? 0 : epp_partition_hot_rows(lines_per_row(F, ld));  // a forced slicing is a measurement
+    const bool want_cold = budget_mb > 0 && p->n_src > rows_budget && marks_pay(F, ld);
+    // (in the automatic mode only where the source rows do not fit the eight L2s together, or with 10 M entries
+    // and more where they fill three of them; forced, for tests and measurements, at any width and size.
+    // Measured, never -> always: 12 M entries of 60 K sources, F = 41 / 64 / 100, 12 to 24 MB of them: 233 -> 211 /
+    // 261 -> 212 / 572 -> 363 us; 41 M of 131 K, F = 36: 936 -> 638.  12 M of 30 K, 12 MB: 296 -> 294, 8 MB: 162 -> 192.
+    // 2 and 6 M of 40 K, F = 100, R-MAT: 67 -> 89 / 162 -> 177)
+    const int64_t l2_rows = (4ll << 20) / ((int64_t)ld * 4);
+    const int64_t min_src = p->nnz < 10'000'000 ? part_rows : std::min(part_rows, 3 * l2_rows);
+    const double long_share = long_row_share(p);  // the hot sections hold a part of these entries at most
+    const bool want_part = part_rows > 0 && (part_mode == 2 || (part_mode == 1 && p->n_src > min_src && long_share > kMinEstimate));
     if (!want_cold && !want_part) return EPP_OK;
 
     // sampled reference counts, their histogram, and two bitmaps, in one allocation
@@ -835,9 +933,13 @@ int epp_tune_locality(epp_path* p, int F, int gs, hipStream_t s, int* log2_slice
     arena.take(&part_hot, hot_bytes);
     EPP_HIP_TRY(hipMemsetAsync(cnt.p, 0, cnt.bytes, s));
     EPP_HIP_TRY(hipMemsetAsync(hist.p, 0, hist.bytes, s));
-    // at most ~16 M sampled entries
+    // The sample: 4 M entries rank the few sources that the L2s hold; the marks, whose line lies among sources
+    // referenced a few times each, take 7 entries per source, 16 M at most.  The counting is bound by the
+    // atomics, 10 to 20 G a second (16 / 8 / 4 M, 140 M entries of 2.4 M sources, F = 64: 4604 / 4712 / 4955 us a launch;
+    // 114 M entries of 233 K sources, F = 41: 1485 / 1470 / 1434 us a launch, 2.5 / 2.1 / 1.9 ms of preparation).
+    const int64_t wanted = want_cold ? std::min<int64_t>(std::max<int64_t>(7 * p->n_src, 4 << 20), 16 << 20) : 4 << 20;
     const int64_t n_seg = (p->nnz + 63) / 64;
-    const int64_t stride = std::max<int64_t>(1, n_seg / (1 << 18));
+    const int64_t stride = (p->nnz + wanted - 1) / wanted;
     const int64_t n_sampled_seg = (n_seg + stride - 1) / stride;
     hipLaunchKernelGGL(k_count_sources, dim3((unsigned)((n_sampled_seg + (kBlock / 64) - 1) / (kBlock / 64))),
                        dim3(kBlock), 0, s, reinterpret_cast<const int2v*>(p->cv.p), p->nnz, stride, cnt.as<int>());
@@ -847,47 +949,50 @@ int epp_tune_locality(epp_path* p, int F, int gs, hipStream_t s, int* log2_slice
     unsigned long long h[kCountBins];
     EPP_HIP_TRY(hipMemcpyAsync(h, hist.p, sizeof(h), hipMemcpyDeviceToHost, s));
     EPP_HIP_TRY(hipStreamSynchronize(s));
-    // smallest reference count of the sources kept when whole bins, most referenced first, are
-    // taken while they fit `budget` rows (sources the sample never met are never kept)
-    auto threshold_for = [&](int64_t budget) {
+    // the sources kept when bins, most referenced first, are taken while they fit `budget` rows, with a
+    // share of the first bin that does not (sources the sample never met are never kept)
+    auto line_for = [&](int64_t budget) {
         int64_t kept = 0;
         int c = kCountBins - 1;
-        for (; c >= 1; --c) {
-            if (kept + (int64_t)h[c] > budget) break;
-            kept += (int64_t)h[c];
-        }
-        return c < 1 ? 1 : bin_floor(c + 1 == 4 ? 8 : c + 1);  // bins 1..c are left out
+        for (; c >= 1 && kept + (int64_t)h[c] <= budget; --c) kept += (int64_t)h[c];
+        if (c < 1) return HotLine{1, 1, 0};
+        return HotLine{bin_floor(c + 1 == 4 ? 8 : c + 1), bin_floor(c), (int)(((budget - kept) << 16) / (int64_t)h[c])};
     };
 
     // One set of marks per path, shared by all its widths: it is the one chosen for the largest
     // prepared width that marks at all (a smaller budget in rows; narrower widths then stream a
     // few rows they could have kept).  The marks therefore depend on which widths have been
     // prepared, never on the order of the calls.
-    int new_thr = 0;  // > 0: the marks have to be set anew with this threshold
+    bool new_marks = false;
     if (want_cold && F > p->cold_F) {
         p->cold_F = F;
-        const int thr = threshold_for(rows_budget);
-        if (thr != p->cold_thr) {
-            new_thr = thr;
-            hipLaunchKernelGGL(k_hot_bitmap, dim3((unsigned)((p->n + kBlock - 1) / kBlock)), dim3(kBlock), 0, s,
-                               cnt.as<int>(), p->n, thr, hot.as<unsigned long long>());
-            EPP_HIP_TRY(hipGetLastError());
-        }
+        new_marks = true;
+        hipLaunchKernelGGL(k_hot_bitmap, dim3((unsigned)((p->n + kBlock - 1) / kBlock)), dim3(kBlock), 0, s,
+                           cnt.as<int>(), p->n, line_for(rows_budget), hot.as<unsigned long long>());
+        EPP_HIP_TRY(hipGetLastError());
     }
 
     if (want_part) {
-        const int thr = threshold_for(part_rows);
-        if (thr < 0x7FFFFFFF) {
+        // (all sources of a path that fit are hot, sampled or not)
+        const HotLine line = p->n_src <= part_rows ? HotLine{0, 0, 0} : line_for(part_rows);
+        double sampled = 0, of_hot = 0;
+        for (int c = 1; c < kCountBins; ++c) {
+            const double refs = 1.1 * (double)bin_floor(c) * (double)h[c];  // (a bin's mean, in quarter octaves)
+            sampled += refs;
+            if (bin_floor(c) >= line.thr) of_hot += refs;
+            else if (bin_floor(c) >= line.part_thr) of_hot += refs * line.share / 65536;
+        }
+        if (part_mode == 2 || of_hot * long_share > kMinEstimate * sampled) {
             hipLaunchKernelGGL(k_hot_bitmap, dim3((unsigned)((p->n + kBlock - 1) / kBlock)), dim3(kBlock), 0, s,
-                               cnt.as<int>(), p->n, thr, part_hot.as<unsigned long long>());
+                               cnt.as<int>(), p->n, line, part_hot.as<unsigned long long>());
             EPP_HIP_TRY(hipGetLastError());
             // (new marks are set by the copy itself, from the bitmap)
-            EPP_TRY(epp_build_partition(p, F, gs, part_hot.as<unsigned int>(), new_thr > 0 ? hot.as<unsigned int>() : nullptr,
+            EPP_TRY(epp_build_partition(p, F, gs, part_hot.as<unsigned int>(), new_marks ? hot.as<unsigned int>() : nullptr,
                                         s, part));
         }
     }
 
-    if (new_thr > 0) {
+    if (new_marks) {
         // The canonical array needs the new marks only if something will still read it: not when it
         // is given back right after this width is prepared (a rebuilt one takes the marks of the copy).
         if (!(*part && epp_canonical_unused(p, F))) {
@@ -896,14 +1001,13 @@ int epp_tune_locality(epp_path* p, int F, int gs, hipStream_t s, int* log2_slice
             EPP_HIP_TRY(hipGetLastError());
         }
         EPP_HIP_TRY(hipStreamSynchronize(s));
-        p->cold_thr = new_thr;
+        p->has_cold = true;
     }
 
     // (chosen whether or not the width has a partitioned layout: the if-else baseline never uses that layout)
     if (forced_slices < 0 && (int64_t)F * 4 >= 512) {
         // share of the references that goes to the sources ranked (rows one L2 holds) ..
         // (twice that), estimated from the bins (a bin's sources count as its lower bound)
-        const int64_t l2_rows = (4ll << 20) / ((int64_t)F * 4);
         double refs_between = 0.0;
         int64_t rank = 0;
         for (int b = kCountBins - 1; b >= 1; --b) {

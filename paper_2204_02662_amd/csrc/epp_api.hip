@@ -48,6 +48,14 @@ int prepare_width(epp_path* self, int F, hipStream_t s, epp_path::WidthCfg** out
         const int gs = w->forced_gs > 0 ? w->forced_gs : epp_default_group_size(p, F);
         Schedule* sc = find_schedule(p, gs);
         if (!sc) EPP_TRY(epp_build_schedule(p, gs, s, &sc));
+        w->packed = nullptr;
+        w->ld = epp_packed_stride(p, F);
+        if (w->ld > F) {
+            void* scratch = nullptr;
+            EPP_TRY(p->rows_pool->get((size_t)p->n * (size_t)w->ld * 4, epp_alloc_of(p), &scratch));
+            if (!p->rows_pool->accounted_by) p->rows_pool->accounted_by = p;
+            w->packed = static_cast<float*>(scratch);
+        }
         delete w->part;
         w->part = nullptr;
         EPP_TRY(epp_tune_locality(p, F, gs, s, &w->log2_slices, &w->part));
@@ -90,7 +98,8 @@ int aggregate(epp_path* self, const float* in, float* out, int F, hipStream_t s,
     }
     // (the if-else baseline walks the whole graph in its given order: no partitioned layout)
     return epp_launch_aggregate(p, w->sched, w->log2_slices, in, out, F, s, row_bits, src_bits,
-                                row_bits ? nullptr : w->part, self->outer ? self->inner_rows : nullptr);
+                                row_bits ? nullptr : w->part, self->outer ? self->inner_rows : nullptr,
+                                row_bits ? nullptr : w->packed, w->ld, self->sources);
 }
 
 }  // namespace
@@ -118,7 +127,8 @@ extern "C" int epp_path_info(const epp_path_t* p, epp_path_info_t* info) {
     for (const Schedule* s : p->scheds) bytes += s->bytes();
     for (const auto& w : p->widths)
         bytes += (w.part ? w.part->bytes() : 0) + (w.plan ? w.plan->store.bytes : 0);
-    if (p->pool->accounted_by == p) bytes += p->pool->bytes();  // shared by the handle's paths: reported once
+    for (const ScratchPool* pool : {p->pool, p->rows_pool})
+        if (pool->accounted_by == p) bytes += pool->bytes();  // shared by the handle's paths: reported once
     info->bytes = (int64_t)bytes;
     info->shares_entries = p->outer ? 1 : 0;
     // (a path that runs on the next outer path's arrays reports that path's tables as what it uses;

@@ -232,6 +232,7 @@ struct epp_path {
     int64_t n_rows = 0;  // R: rows of the path in canonical form (all-active graph: n)
     int64_t nnz = 0;
     int64_t n_src = 0;
+    const unsigned long long* sources = nullptr;  // bitmap of the source vertices (owned by the handle); NULL: all
     int64_t max_len = 0;
     int64_t len_hist[EPP_NCLASS] = {};
     bool all_rows = false;       // all-active graph (handle from epp_prepare_full)
@@ -252,11 +253,13 @@ struct epp_path {
     bool has_inner = false;               // set on the outer path: kEntOuterOnly marks are in place
     DevBuf zero_block;                    // outer path: 256 zero bytes, what a skipped entry gathers
     DevBuf inner_pos;                     // outer path: int32[ceil(nnz / 64)] entries of the inner path before every 64th entry
-    int cold_thr = 0;            // entries whose source is referenced fewer times than this carry the cold flag
+    bool has_cold = false;       // entries of rarely referenced sources carry the cold flag
     int cold_F = 0;              // width the cold flags were chosen for (the largest prepared width that marks)
     epp_alloc_t alloc = {nullptr, nullptr, nullptr};  // the caller's allocator (alloc == NULL: hipMalloc)
     ScratchPool own_pool;        // launch scratch of a path that belongs to no epp_paths handle
     ScratchPool* pool = &own_pool;  // the handle's pool for the paths of an epp_paths handle
+    ScratchPool own_rows;           // the same for packed source rows (needed together with the other's)
+    ScratchPool* rows_pool = &own_rows;
     // all-active graph only
     DevBuf full_rowptr;          // int32[n + 1] as given (for export)
     int64_t n_empty_rows = 0;
@@ -274,6 +277,8 @@ struct epp_path {
         Schedule* sched = nullptr;
         int log2_slices = 0;
         Partition* part = nullptr;
+        float* packed = nullptr;  // the launch first copies its source rows to this place, `ld` floats apart
+        int ld = 0;               // (NULL, F: it reads them where they are)
     };
     std::vector<WidthCfg> widths;
     int last_F = 0;
@@ -291,7 +296,7 @@ struct epp_paths {
     std::vector<epp_path*> path;    // index l; once the sets stop growing, deeper layers share one object
     DevBuf set0_ids;                // ascending ids of N^0 (the other sets are path rows)
     DevBuf store;                   // the allocation that the bitmaps (small graphs: all arrays) are views of
-    ScratchPool pool;               // launch scratch shared by the paths
+    ScratchPool pool, rows_pool;    // launch scratch shared by the paths
     epp_alloc_t alloc = {nullptr, nullptr, nullptr};
     ~epp_paths() {
         for (size_t i = 0; i < path.size(); ++i) {
@@ -336,7 +341,9 @@ int epp_build_schedule(epp_path* p, int gs, hipStream_t s, Schedule** out);
 // inner_rows != NULL: the launch serves the inner path that shares p's entries (bitmap of its rows)
 int epp_launch_aggregate(epp_path* p, Schedule* sc, int log2_slices, const float* in, float* out, int F, hipStream_t s,
                          const unsigned int* row_bits = nullptr, const unsigned int* src_bits = nullptr,
-                         const Partition* part = nullptr, const unsigned int* inner_rows = nullptr);
+                         const Partition* part = nullptr, const unsigned int* inner_rows = nullptr,
+                         float* packed = nullptr, int ld = 0, const unsigned long long* sources = nullptr);
+int epp_packed_stride(const epp_path* p, int F);  // floats from row to row of packed source rows; F: not packed
 // rows.hip: one launch that processes rows whole, for small paths
 bool epp_rows_kernel_fits(const epp_path* p, int F);
 int epp_build_rows_plan(epp_path* p, int F, hipStream_t s, RowsPlan** out);  // *out = NULL: none needed
@@ -349,7 +356,7 @@ int epp_zero_empty_rows(const epp_path* p, float* out, int F, hipStream_t s);
 int epp_tune_locality(epp_path* p, int F, int gs, hipStream_t s, int* log2_slices, Partition** part);
 
 // partition.hip
-int epp_partition_hot_rows(int F);  // source rows of width F the eight L2s hold together
+int epp_partition_hot_rows(double lines);  // source rows of width F the eight L2s hold together
 // source-partitioned layout of `p` for width F and group size gs, or *out = NULL where it does not pay
 // `unstreamed` (or NULL): bitmap of the sources whose entries stay unmarked in the last section; the
 // copy then sets the streamed-source marks itself, whatever the canonical array carries

@@ -375,10 +375,11 @@ int env_int(const char* name, int dflt) {
 
 }  // namespace
 
-int epp_partition_hot_rows(int F) {
-    // what the eight L2s hold together when each keeps 3.5 of its 4 MB for source rows
-    const int64_t kb_per_xcd = env_int("EPP_TUNE_PART_KB", 3584);
-    return (int)std::min<int64_t>(kHot * kb_per_xcd * 1024 / ((int64_t)F * 4), 1 << 30);
+// What the eight L2s hold together, of rows that touch so many 128-byte lines each.  (Budget per L2 of 3.5 / 3.75 /
+// 4 MB: 258 M entries, F = 128: 29.05 / 29.05 / 28.73 ms for two layers; 114 M entries, F = 99: 2928 / 2914 / 2885 us.)
+int epp_partition_hot_rows(double lines) {
+    const int64_t kb_per_xcd = env_int("EPP_TUNE_PART_KB", 4096);
+    return (int)std::min((double)(kHot * kb_per_xcd * 1024) / (128.0 * lines), 1073741824.0);
 }
 
 int epp_build_partition(epp_path* p, int F, int gs, const unsigned int* hot_bitmap, const unsigned int* unstreamed,
@@ -479,9 +480,11 @@ int epp_build_partition(epp_path* p, int F, int gs, const unsigned int* hot_bitm
     // once and read once.  Measured on an MI355X at 512-byte rows: a path with 42 % of its entries in
     // hot sections and 1.3 % as many partial rows as entries runs 14 % faster, one with 13 % / 0.9 %
     // gains 2 %, one with 28 % / 7 % loses 14 %.  The layout is built when the modelled saving,
-    // 0.75 hot - 2.5 partial rows (in gathers), exceeds a fifth of the entries.
+    // 0.75 hot - 2.5 partial rows (in gathers), exceeds 0.12 of the entries (88 M entries, 700 K sources:
+    // 0.20 at F = 64: 2931 -> 2527 us; 0.17 at F = 100: 5687 -> 4964; 0.15 at F = 128: 5563 -> 5097.
+    // 140 M entries, 2.4 M sources, 0.08 at F = 64: 4599 -> 4602).
     const double score = (0.75 * (double)hot_entries - 2.5 * (double)n_slots) / (double)nnz;
-    if (mode == 1 && score < 0.20) return EPP_OK;
+    if (mode == 1 && score < 0.12) return EPP_OK;
     if (p->n + n_slots >= 0x7FFFFFFFll) return EPP_OK;  // targets are 31-bit
 
     Partition* q = new Partition();

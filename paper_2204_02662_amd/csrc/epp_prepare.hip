@@ -1155,6 +1155,8 @@ extern "C" int epp_prepare(const epp_csr_t* g, const int32_t* train_ids, int64_t
         p->n = n;
         p->alloc = P->alloc;
         p->pool = &P->pool;
+        p->rows_pool = &P->rows_pool;
+        p->sources = P->bitmaps[k].as<unsigned long long>();
         long long* d_level = d_levels + (size_t)k * kLevelWords;
         if (edge_tiles) {
             const bool all = k > 0 && P->set_size[k] == n;
@@ -1390,6 +1392,8 @@ extern "C" int epp_paths_import(int64_t n, int L, const int32_t* train_ids, int6
         p->n = n;
         p->alloc = P->alloc;
         p->pool = &P->pool;
+        p->rows_pool = &P->rows_pool;
+        p->sources = P->bitmaps[k].as<unsigned long long>();
         p->n_rows = p->n_stream_rows = a.n_rows;
         p->nnz = a.nnz;
         P->set_size[k + 1] = a.n_rows;
