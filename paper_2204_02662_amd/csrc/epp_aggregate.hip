@@ -145,24 +145,33 @@ __device__ __forceinline__ void write_row(float* __restrict__ o, const float (&a
 
 // out[vertex(r), :] = sum of the partial rows of cut row r: the row starts in group g0 (whose
 // end-of-group slot holds its head), runs through whole groups (end-of-group slots) and ends in
-// group g1 (whose start-of-group slot holds its tail).  Fp lanes (a power of two >= min(F, 64)) add a
-// row's pieces in group order, eight loads in flight.  A row of more than kManyPieces is left to
-// the workgroup, whose 256 / Fp teams of lanes each take every so-manieth piece and are added in team
-// order: one team alone makes the longest row a chain of loads that nothing hides (340 pieces of a
-// 43,000-entry row: 24 of the launch's 24 us at F = 16; 7 us with the teams).  The order depends on
-// the table and the width only, never on timing.
+// group g1 (whose start-of-group slot holds its tail).  2^log2T lanes of VEC floats add a row's pieces in
+// group order, eight loads in flight; a lane that would reach past the row's end steps back to it.  A row of
+// more than kManyPieces is left to the workgroup, whose teams of lanes each take every so-manieth piece
+// and are added in team order: one team alone makes the longest row a chain of loads that nothing
+// hides (340 pieces of a 43,000-entry row: 24 of the launch's 24 us at F = 16; 7 us with the teams).  The
+// order depends on the table and the width only, never on timing.  Bound by the chain cut row -> entry
+// range -> pieces of rows that mostly have two or three of them: 123 K rows of 64 floats in 30 us (4-byte lanes and
+// 64-bit divisions: 82).
 constexpr int kManyPieces = 24;
+template <int VEC>
+__device__ __forceinline__ typename VecT<VEC>::type read_vec(const float* __restrict__ x) {
+    return *reinterpret_cast<const typename VecT<VEC>::type*>(x);
+}
+
+template <int VEC>
 __global__ __launch_bounds__(kBlock) void k_combine_cut_rows(const int32_t* __restrict__ cut_rows, int64_t n_cut,
                                                              const int32_t* __restrict__ rowptr,
                                                              const int32_t* __restrict__ row_ids, int gs, int F,
-                                                             int log2Fp, const float* __restrict__ pieces,
+                                                             int log2T, const float* __restrict__ pieces,
                                                              const unsigned int* __restrict__ only_bits,
                                                              float* __restrict__ out, int n,
                                                              float* __restrict__ vpart) {
+    typedef typename VecT<VEC>::type vec_t;
     __shared__ int32_t list[kBlock];
     __shared__ int count;
-    __shared__ float part[kBlock];
-    const int Fp = 1 << log2Fp, lane = threadIdx.x & (Fp - 1), team = threadIdx.x >> log2Fp;
+    __shared__ vec_t part[kBlock];
+    const int T = 1 << log2T, lane = threadIdx.x & (T - 1), team = threadIdx.x >> log2T;
     if (threadIdx.x == 0) count = 0;
     __syncthreads();
     // where cut row r goes (NULL: it is not a row of this launch -- if-else baseline, inner path on shared arrays)
@@ -172,51 +181,58 @@ __global__ __launch_bounds__(kBlock) void k_combine_cut_rows(const int32_t* __re
         if (only_bits && !((only_bits[v >> 5] >> (v & 31)) & 1u)) return nullptr;
         return out + (size_t)v * F;
     };
-    const int64_t k = ((int64_t)blockIdx.x * kBlock + threadIdx.x) >> log2Fp;
+    const int64_t row_step = (int64_t)2 * F;  // from a group's pieces to the next group's
+    const int64_t k = ((int64_t)blockIdx.x * kBlock + threadIdx.x) >> log2T;
     if (k < n_cut) {
         const int32_t r = cut_rows[k];
+        const unsigned p0 = (unsigned)rowptr[r], p1 = (unsigned)rowptr[r + 1] - 1u;
         float* __restrict__ o = target(r);
-        const int64_t g0 = rowptr[r] / gs, g1 = ((int64_t)rowptr[r + 1] - 1) / gs;
-        if (g1 - g0 >= kManyPieces) {
+        const int g0 = (int)(p0 / (unsigned)gs), m = (int)(p1 / (unsigned)gs) - g0;
+        if (m >= kManyPieces) {
             if (o && lane == 0) list[atomicAdd(&count, 1)] = r;
         } else if (o) {
-            for (int f = lane; f < F; f += Fp) {
-                float sum = 0.0f;
-                int64_t g = g0;
-                for (; g + 8 <= g1; g += 8) {
-                    float x[8];
+            for (int f0 = lane * VEC; f0 < F; f0 += T * VEC) {
+                const int f = std::min(f0, F - VEC);
+                const float* __restrict__ x0 = pieces + (int64_t)g0 * row_step + f;
+                vec_t sum = read_vec<VEC>(x0 + F);
+                const vec_t tail = read_vec<VEC>(x0 + m * row_step);
+                for (int g = 1; g < m; g += 8) {
+                    vec_t x[8];
 #pragma unroll
-                    for (int i = 0; i < 8; ++i) x[i] = pieces[((g + i) * 2 + 1) * F + f];
+                    for (int i = 0; i < 8; ++i) x[i] = read_vec<VEC>(x0 + std::min(g + i, m - 1) * row_step + F);
 #pragma unroll
-                    for (int i = 0; i < 8; ++i) sum += x[i];
+                    for (int i = 0; i < 8; ++i)
+                        if (g + i < m) sum += x[i];
                 }
-                for (; g < g1; ++g) sum += pieces[(g * 2 + 1) * F + f];
-                sum += pieces[(g1 * 2) * F + f];
-                o[f] = sum;
+                sum += tail;
+                *reinterpret_cast<vec_t*>(o + f) = sum;
             }
         }
     }
     __syncthreads();
-    const int n_long = count, teams = kBlock >> log2Fp;
+    const int n_long = count, teams = kBlock >> log2T;
     for (int i = 0; i < n_long; ++i) {
         const int32_t r = list[i];
         float* __restrict__ o = target(r);
-        const int64_t g0 = rowptr[r] / gs, g1 = ((int64_t)rowptr[r + 1] - 1) / gs;
-        for (int f0 = 0; f0 < F; f0 += Fp) {
-            const int f = f0 + lane;
-            float sum = 0.0f;
-            for (int64_t g = g0 + team; g < g1; g += 8 * teams) {
-                float x[8];
+        const int g0 = (int)((unsigned)rowptr[r] / (unsigned)gs), m = (int)(((unsigned)rowptr[r + 1] - 1u) / (unsigned)gs) - g0;
+        for (int base = 0; base < F; base += T * VEC) {
+            const int f0 = base + lane * VEC, f = std::min(f0, F - VEC);
+            const float* __restrict__ x0 = pieces + (int64_t)g0 * row_step + f;
+            vec_t sum = {};
+            for (int g = team; g < m; g += 8 * teams) {
+                vec_t x[8];
 #pragma unroll
-                for (int j = 0; j < 8; ++j) x[j] = f < F && g + j * teams < g1 ? pieces[((g + j * teams) * 2 + 1) * F + f] : 0.0f;
+                for (int j = 0; j < 8; ++j) x[j] = read_vec<VEC>(x0 + std::min(g + j * teams, m - 1) * row_step + F);
 #pragma unroll
-                for (int j = 0; j < 8; ++j) sum += x[j];
+                for (int j = 0; j < 8; ++j)
+                    if (g + j * teams < m) sum += x[j];
             }
             part[threadIdx.x] = sum;
             __syncthreads();
-            if (team == 0 && f < F) {
-                for (int j = 1; j < teams; ++j) sum += part[(j << log2Fp) + lane];
-                o[f] = sum + pieces[(g1 * 2) * F + f];
+            if (team == 0 && f0 < F) {
+                for (int j = 1; j < teams; ++j) sum += part[(j << log2T) + lane];
+                sum += read_vec<VEC>(x0 + m * row_step);
+                *reinterpret_cast<vec_t*>(o + f) = sum;
             }
             __syncthreads();  // `part` is written again
         }
@@ -224,26 +240,30 @@ __global__ __launch_bounds__(kBlock) void k_combine_cut_rows(const int32_t* __re
 }
 
 // Partitioned layout: out[vertex(m), :] = sum of the partial rows of split row m (one per section in
-// which it has entries), in section order.  Fp lanes per row.
+// which it has entries), in section order.  2^log2T lanes of VEC floats per row, as above.
+template <int VEC>
 __global__ __launch_bounds__(kBlock) void k_combine_sections(const int32_t* __restrict__ mvert,
                                                              const int32_t* __restrict__ mptr, int64_t n_split, int F,
-                                                             int log2Fp, const float* __restrict__ vpart,
+                                                             int log2T, const float* __restrict__ vpart,
                                                              const unsigned int* __restrict__ only_bits,
                                                              float* __restrict__ out) {
-    const int Fp = 1 << log2Fp;
-    const int64_t m = ((int64_t)blockIdx.x * kBlock + threadIdx.x) >> log2Fp;
+    typedef typename VecT<VEC>::type vec_t;
+    const int T = 1 << log2T;
+    const int64_t m = ((int64_t)blockIdx.x * kBlock + threadIdx.x) >> log2T;
     if (m >= n_split) return;
     const int32_t v = mvert[m];
-    if (only_bits && !((only_bits[v >> 5] >> (v & 31)) & 1u)) return;  // not a row of the inner path
     const int s0 = mptr[m], s1 = mptr[m + 1];
-    for (int f = threadIdx.x & (Fp - 1); f < F; f += Fp) {
-        float x[9];
+    if (only_bits && !((only_bits[v >> 5] >> (v & 31)) & 1u)) return;  // not a row of the inner path
+    for (int f0 = (threadIdx.x & (T - 1)) * VEC; f0 < F; f0 += T * VEC) {
+        const int f = std::min(f0, F - VEC);
+        vec_t x[9];
 #pragma unroll
-        for (int i = 0; i < 9; ++i) x[i] = s0 + i < s1 ? vpart[(size_t)(s0 + i) * F + f] : 0.0f;
-        float sum = x[0];
+        for (int i = 0; i < 9; ++i) x[i] = read_vec<VEC>(vpart + (size_t)std::min(s0 + i, s1 - 1) * F + f);
+        vec_t sum = x[0];
 #pragma unroll
-        for (int i = 1; i < 9; ++i) sum += x[i];
-        out[(size_t)v * F + f] = sum;
+        for (int i = 1; i < 9; ++i)
+            if (s0 + i < s1) sum += x[i];
+        *reinterpret_cast<vec_t*>(out + (size_t)v * F + f) = sum;
     }
 }
 
@@ -845,19 +865,20 @@ int epp_launch_aggregate(epp_path* p, Schedule* sc, int log2_slices, const float
         else if (vec == 2) launch_vec<2, 16>(log2T, s, a);
         else launch_vec<1, 16>(log2T, s, a);
     }
+    const int add_vec = F < 4 ? 1 : 4, add_log2T = std::min(ceil_log2((F + add_vec - 1) / add_vec), 6);
     if (sc->n_split_rows > 0) {
-        const int log2Fp = std::min(ceil_log2(F), 6);
-        const int64_t total = sc->n_split_rows << log2Fp;
-        hipLaunchKernelGGL(k_combine_cut_rows, dim3((unsigned)((total + kBlock - 1) / kBlock)), dim3(kBlock), 0, s,
+        const int64_t total = sc->n_split_rows << add_log2T;
+        auto kernel = add_vec == 4 ? k_combine_cut_rows<4> : k_combine_cut_rows<1>;
+        hipLaunchKernelGGL(kernel, dim3((unsigned)((total + kBlock - 1) / kBlock)), dim3(kBlock), 0, s,
                            sc->cut_rows.as<int32_t>(), sc->n_split_rows, rowptr, row_ids, sc->gs, F,
-                           log2Fp, pieces, row_bits ? row_bits : inner_rows, out, (int)p->n,
+                           add_log2T, pieces, row_bits ? row_bits : inner_rows, out, (int)p->n,
                            part ? part->vpart : (float*)nullptr);
     }
     if (part && part->n_split > 0) {
-        const int log2Fp = std::min(ceil_log2(F), 6);
-        const int64_t total = part->n_split << log2Fp;
-        hipLaunchKernelGGL(k_combine_sections, dim3((unsigned)((total + kBlock - 1) / kBlock)), dim3(kBlock), 0, s,
-                           part->mvert.as<int32_t>(), part->mptr.as<int32_t>(), part->n_split, F, log2Fp,
+        const int64_t total = part->n_split << add_log2T;
+        auto kernel = add_vec == 4 ? k_combine_sections<4> : k_combine_sections<1>;
+        hipLaunchKernelGGL(kernel, dim3((unsigned)((total + kBlock - 1) / kBlock)), dim3(kBlock), 0, s,
+                           part->mvert.as<int32_t>(), part->mptr.as<int32_t>(), part->n_split, F, add_log2T,
                            part->vpart, inner_rows, out);
     }
     EPP_HIP_TRY(hipGetLastError());
