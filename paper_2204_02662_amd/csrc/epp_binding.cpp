@@ -4,7 +4,11 @@
 // On a small graph such a call is all host work: a kernel of 4 us, and 7.5 us to check five arguments,
 // look up the stream and marshal the call from Python through ctypes.  Here the same steps take 1.5 us beside the
 // launch itself.  Messages and exceptions are those of the module that imports this one (__init__.py).
+//
+// What PyTorch's C++ throws (a tensor of unknown shape, as tracing makes them, asked for its sizes) leaves
+// every entry point as the Python exception it stands for: past a C function it would end the process.
 
+#include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/python_variable.h>
 
 #include <c10/core/impl/VirtualGuardImpl.h>
@@ -216,6 +220,14 @@ PyObject* input_gradient(PyObject*, PyObject* const* args, Py_ssize_t n, PyObjec
     return finish(rc);
 }
 
+typedef PyObject* (*Entry)(PyObject*, PyObject* const*, Py_ssize_t, PyObject*);
+template <Entry F>
+PyObject* guarded(PyObject* self, PyObject* const* args, Py_ssize_t n, PyObject* kw) {
+    HANDLE_TH_ERRORS
+    return F(self, args, n, kw);
+    END_HANDLE_TH_ERRORS
+}
+
 // init(error class, raw-stream function)
 PyObject* init(PyObject*, PyObject* const* args, Py_ssize_t n) {
     if (n != 2) {
@@ -229,7 +241,7 @@ PyObject* init(PyObject*, PyObject* const* args, Py_ssize_t n) {
     Py_RETURN_NONE;
 }
 
-#define EPP_FAST(f) reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)(void)>(f)), METH_FASTCALL | METH_KEYWORDS
+#define EPP_FAST(f) reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)(void)>(guarded<f>)), METH_FASTCALL | METH_KEYWORDS
 
 PyMethodDef methods[] = {
     {"init", reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)(void)>(init)), METH_FASTCALL, nullptr},
