@@ -77,7 +77,8 @@ struct RowArgs {
 };
 
 // acc += sum of the entries j0, j0 + 1, .. (U at a time, `step` apart) of [j0, p1).  The pairs of the
-// next step are fetched while the rows of this one are on their way.
+// next step are fetched while the rows of this one are on their way.  What a step reads past p1 (the last
+// entry again) counts nothing: both factors become zero, as zero times an infinity would not.
 template <int VEC, int U, bool INNER>
 __device__ __forceinline__ void add_entries(const RowArgs& a, const float* __restrict__ src, int j0, int p1, int step,
                                             float (&acc)[VEC]) {
@@ -91,9 +92,13 @@ __device__ __forceinline__ void add_entries(const RowArgs& a, const float* __res
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const float* p = src + (size_t)(e[u].x & kEntCol) * (size_t)a.F;
-            if constexpr (INNER) p = (e[u].x & kEntOuterOnly) ? a.zero : p;
+            bool mine = j + u < p1;
+            if constexpr (INNER) {
+                p = (e[u].x & kEntOuterOnly) ? a.zero : p;
+                mine = mine && !(e[u].x & kEntOuterOnly);
+            }
             load_frag<VEC>(p, x[u]);
-            w[u] = j + u < p1 ? __int_as_float(e[u].y) : 0.0f;
+            w[u] = mine ? __int_as_float(e[u].y) : 0.0f;
         }
         if (j + step < p1) {
 #pragma unroll
@@ -101,8 +106,9 @@ __device__ __forceinline__ void add_entries(const RowArgs& a, const float* __res
         }
 #pragma unroll
         for (int u = 0; u < U; ++u) {
+            const bool in = j + u < p1;
 #pragma unroll
-            for (int i = 0; i < VEC; ++i) acc[i] = fmaf(w[u], x[u][i], acc[i]);
+            for (int i = 0; i < VEC; ++i) acc[i] = fmaf(w[u], in ? x[u][i] : 0.0f, acc[i]);
         }
     }
 }
