@@ -223,9 +223,17 @@ PyObject* input_gradient(PyObject*, PyObject* const* args, Py_ssize_t n, PyObjec
 typedef PyObject* (*Entry)(PyObject*, PyObject* const*, Py_ssize_t, PyObject*);
 template <Entry F>
 PyObject* guarded(PyObject* self, PyObject* const* args, Py_ssize_t n, PyObject* kw) {
-    HANDLE_TH_ERRORS
-    return F(self, args, n, kw);
-    END_HANDLE_TH_ERRORS
+    // (PyTorch's own macro for this also buffers warnings: 0.2 us a call)
+    try {
+        return F(self, args, n, kw);
+    } catch (python_error& e) {
+        e.restore();
+    } catch (const c10::Error& e) {
+        PyErr_SetString(PyExc_RuntimeError, e.what_without_backtrace());
+    } catch (const std::exception& e) {
+        PyErr_SetString(PyExc_RuntimeError, e.what());
+    }
+    return nullptr;
 }
 
 // init(error class, raw-stream function)
