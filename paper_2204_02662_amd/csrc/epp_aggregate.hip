@@ -147,16 +147,36 @@ __device__ __forceinline__ void write_row(float* __restrict__ o, const float (&a
 // end-of-group slot holds its head), runs through whole groups (end-of-group slots) and ends in
 // group g1 (whose start-of-group slot holds its tail).  2^log2T lanes of VEC floats add a row's pieces in
 // group order, eight loads in flight; a lane that would reach past the row's end steps back to it.  A row of
-// more than kManyPieces is left to the workgroup, whose teams of lanes each take every so-manieth piece
-// and are added in team order: one team alone makes the longest row a chain of loads that nothing
-// hides (340 pieces of a 43,000-entry row: 24 of the launch's 24 us at F = 16; 7 us with the teams).  The
-// order depends on the table and the width only, never on timing.  Bound by the chain cut row -> entry
-// range -> pieces of rows that mostly have two or three of them: 123 K rows of 64 floats in 30 us (4-byte lanes and
-// 64-bit divisions: 82).
-constexpr int kManyPieces = 24;
+// more than kManyPieces is left to a wavefront, whose teams of lanes each take every so-manieth piece, and
+// one of more than kTeamPieces for each of those teams to the whole workgroup: one team alone makes the
+// longest row a chain of loads that nothing hides (340 pieces of a 43,000-entry row: 24 of the launch's
+// 24 us at F = 16).  The teams' sums are exchanged between lanes (adding them up one after the other from
+// LDS, 128 of them at F = 6, made every long row of a workgroup 6 us).  The order depends on the table and the
+// width only, never on timing.  Bound by the chain cut row -> entry range -> pieces of rows that mostly have two
+// or three of them: 123 K rows of 64 floats in 30 us (4-byte lanes and 64-bit divisions: 82).
+constexpr int kManyPieces = 24, kTeamPieces = 64;
 template <int VEC>
 __device__ __forceinline__ typename VecT<VEC>::type read_vec(const float* __restrict__ x) {
     return *reinterpret_cast<const typename VecT<VEC>::type*>(x);
+}
+
+template <int VEC>
+__device__ __forceinline__ void write_vec(float* __restrict__ o, typename VecT<VEC>::type x) {
+    *reinterpret_cast<typename VecT<VEC>::type*>(o) = x;
+}
+
+// Sum of x over the lanes of the wavefront that are 2^log2T, 2 * 2^log2T, .. apart, in every one of them.
+template <int VEC>
+__device__ __forceinline__ typename VecT<VEC>::type sum_of_teams(typename VecT<VEC>::type x, int log2T) {
+    for (int d = 1 << log2T; d < 64; d <<= 1) {
+        if constexpr (VEC == 1) {
+            x += __shfl_xor(x, d, 64);
+        } else {
+#pragma unroll
+            for (int i = 0; i < VEC; ++i) x[i] += __shfl_xor(x[i], d, 64);
+        }
+    }
+    return x;
 }
 
 template <int VEC>
@@ -168,10 +188,11 @@ __global__ __launch_bounds__(kBlock) void k_combine_cut_rows(const int32_t* __re
                                                              float* __restrict__ out, int n,
                                                              float* __restrict__ vpart) {
     typedef typename VecT<VEC>::type vec_t;
-    __shared__ int32_t list[kBlock];
+    struct Long { float* o; int g0, m; };  // a row that is left to a wavefront or to all of them
+    __shared__ Long list[kBlock];
     __shared__ int count;
-    __shared__ vec_t part[kBlock];
-    const int T = 1 << log2T, lane = threadIdx.x & (T - 1), team = threadIdx.x >> log2T;
+    __shared__ vec_t part[kBlock / 64][64];
+    const int T = 1 << log2T, lane = threadIdx.x & (T - 1);
     if (threadIdx.x == 0) count = 0;
     __syncthreads();
     // where cut row r goes (NULL: it is not a row of this launch -- if-else baseline, inner path on shared arrays)
@@ -189,7 +210,7 @@ __global__ __launch_bounds__(kBlock) void k_combine_cut_rows(const int32_t* __re
         float* __restrict__ o = target(r);
         const int g0 = (int)(p0 / (unsigned)gs), m = (int)(p1 / (unsigned)gs) - g0;
         if (m >= kManyPieces) {
-            if (o && lane == 0) list[atomicAdd(&count, 1)] = r;
+            if (o && lane == 0) list[atomicAdd(&count, 1)] = Long{o, g0, m};
         } else if (o) {
             for (int f0 = lane * VEC; f0 < F; f0 += T * VEC) {
                 const int f = std::min(f0, F - VEC);
@@ -205,36 +226,40 @@ __global__ __launch_bounds__(kBlock) void k_combine_cut_rows(const int32_t* __re
                         if (g + i < m) sum += x[i];
                 }
                 sum += tail;
-                *reinterpret_cast<vec_t*>(o + f) = sum;
+                write_vec<VEC>(o + f, sum);
             }
         }
     }
     __syncthreads();
-    const int n_long = count, teams = kBlock >> log2T;
+    const int n_long = count, wave = threadIdx.x >> 6;
     for (int i = 0; i < n_long; ++i) {
-        const int32_t r = list[i];
-        float* __restrict__ o = target(r);
-        const int g0 = (int)((unsigned)rowptr[r] / (unsigned)gs), m = (int)(((unsigned)rowptr[r + 1] - 1u) / (unsigned)gs) - g0;
+        const Long l = list[i];
+        const bool all = l.m > (kTeamPieces << 6) >> log2T;
+        if (!all && (i & (kBlock / 64 - 1)) != wave) continue;
+        const int team = (all ? (int)threadIdx.x : (int)(threadIdx.x & 63)) >> log2T, teams = (all ? kBlock : 64) >> log2T;
         for (int base = 0; base < F; base += T * VEC) {
             const int f0 = base + lane * VEC, f = std::min(f0, F - VEC);
-            const float* __restrict__ x0 = pieces + (int64_t)g0 * row_step + f;
+            const float* __restrict__ x0 = pieces + (int64_t)l.g0 * row_step + f;
+            const vec_t tail = read_vec<VEC>(x0 + l.m * row_step);
             vec_t sum = {};
-            for (int g = team; g < m; g += 8 * teams) {
+            for (int g = team; g < l.m; g += 8 * teams) {
                 vec_t x[8];
 #pragma unroll
-                for (int j = 0; j < 8; ++j) x[j] = read_vec<VEC>(x0 + std::min(g + j * teams, m - 1) * row_step + F);
+                for (int j = 0; j < 8; ++j) x[j] = read_vec<VEC>(x0 + std::min(g + j * teams, l.m - 1) * row_step + F);
 #pragma unroll
                 for (int j = 0; j < 8; ++j)
-                    if (g + j * teams < m) sum += x[j];
+                    if (g + j * teams < l.m) sum += x[j];
             }
-            part[threadIdx.x] = sum;
-            __syncthreads();
-            if (team == 0 && f0 < F) {
-                for (int j = 1; j < teams; ++j) sum += part[(j << log2T) + lane];
-                sum += read_vec<VEC>(x0 + m * row_step);
-                *reinterpret_cast<vec_t*>(o + f) = sum;
+            sum = sum_of_teams<VEC>(sum, log2T);
+            if (all) {  // (the same for every wavefront, like the barriers below)
+                if ((threadIdx.x & 63) < T) part[wave][lane] = sum;
+                __syncthreads();
+                if (wave == 0) {
+                    for (int w = 1; w < kBlock / 64; ++w) sum += part[w][lane];
+                }
+                __syncthreads();  // `part` is written again
             }
-            __syncthreads();  // `part` is written again
+            if (team == 0 && f0 < F) write_vec<VEC>(l.o + f, sum + tail);
         }
     }
 }
