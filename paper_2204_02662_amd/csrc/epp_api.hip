@@ -51,6 +51,7 @@ int prepare_width(epp_path* self, int F, hipStream_t s, epp_path::WidthCfg** out
         w->packed = nullptr;
         w->ld = epp_packed_stride(p, F);
         if (w->ld > F) {
+            EPP_TRY(epp_check_sources(p, s));  // (the launch copies the rows of `sources` only)
             void* scratch = nullptr;
             EPP_TRY(p->rows_pool->get((size_t)p->n * (size_t)w->ld * 4, epp_alloc_of(p), &scratch));
             if (!p->rows_pool->accounted_by) p->rows_pool->accounted_by = p;

@@ -233,6 +233,7 @@ struct epp_path {
     int64_t nnz = 0;
     int64_t n_src = 0;
     const unsigned long long* sources = nullptr;  // bitmap of the source vertices (owned by the handle); NULL: all
+    bool sources_checked = true;  // every column is in it (an imported path: not known before epp_check_sources)
     int64_t max_len = 0;
     int64_t len_hist[EPP_NCLASS] = {};
     bool all_rows = false;       // all-active graph (handle from epp_prepare_full)
@@ -325,6 +326,9 @@ int epp_path_finish(epp_path* p, hipStream_t s);
 void epp_path_set_stats(epp_path* p, const unsigned long long* host);
 // ascending vertex ids of N^k (device, owned by `p`); allocates nothing, never waits
 int epp_active_ids(const epp_paths* p, int k, const int32_t** ids, int64_t* count);
+
+// Whether an imported path's columns all lie in its source set; where they do not, `sources` is given up.  Once per path.
+int epp_check_sources(epp_path* p, hipStream_t s);
 
 // prepare_small.hip: the whole construction in one launch, for graphs of at most 65,536 vertices and 131,072 entries
 bool epp_prepare_small_fits(const epp_csr_t* g, int64_t n_train, int L);

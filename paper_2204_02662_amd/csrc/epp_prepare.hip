@@ -924,6 +924,24 @@ __global__ __launch_bounds__(kBlock) void k_import_path(ImportArgs a) {
     flush_lengths(h, &mx, my_max, a.stats, reinterpret_cast<int*>(a.stats + EPP_NCLASS));
 }
 
+// *outside = 1 if an entry's column is not in the bitmap.  Bound by the lookups, which come from L2 (250 G/s), eight in
+// flight per lane.
+constexpr int kCheckPer = 8;
+__global__ __launch_bounds__(kBlock) void k_columns_inside(const int2* __restrict__ cv, int64_t nnz,
+                                                           const unsigned int* __restrict__ bitmap32, int* __restrict__ outside) {
+    const int64_t e0 = (int64_t)blockIdx.x * (kBlock * kCheckPer) + threadIdx.x;
+    int c[kCheckPer];
+    unsigned int w[kCheckPer];
+#pragma unroll
+    for (int i = 0; i < kCheckPer; ++i) c[i] = cv[min(e0 + i * kBlock, nnz - 1)].x & kEntCol;
+#pragma unroll
+    for (int i = 0; i < kCheckPer; ++i) w[i] = bitmap32[c[i] >> 5];
+    unsigned int in = 1u;
+#pragma unroll
+    for (int i = 0; i < kCheckPer; ++i) in &= w[i] >> (c[i] & 31);
+    if (!(in & 1u)) *outside = 1;  // (every writer stores the same value)
+}
+
 // N^0 as a bitmap (cleared by the caller) and its ascending ids; *count receives their number.
 void launch_training_set(const int32_t* train_ids, int64_t n_train, int64_t n, const DevBuf& bitmap, void* ids_out,
                          int* tile_cnt, int* tile_base, int* scan_tmp, long long* count, int* err, hipStream_t s) {
@@ -1394,6 +1412,7 @@ extern "C" int epp_paths_import(int64_t n, int L, const int32_t* train_ids, int6
         p->pool = &P->pool;
         p->rows_pool = &P->rows_pool;
         p->sources = P->bitmaps[k].as<unsigned long long>();
+        p->sources_checked = false;
         p->n_rows = p->n_stream_rows = a.n_rows;
         p->nnz = a.nnz;
         P->set_size[k + 1] = a.n_rows;
@@ -1434,6 +1453,24 @@ extern "C" int epp_paths_import(int64_t n, int L, const int32_t* train_ids, int6
     }
     guard.p = nullptr;
     *out = P;
+    return EPP_OK;
+}
+
+int epp_check_sources(epp_path* p, hipStream_t s) {
+    if (p->sources_checked || !p->sources || p->nnz == 0) return EPP_OK;
+    PinnedWords host;
+    DevBuf outside;
+    EPP_TRY(host.get(1));
+    EPP_TRY(outside.alloc(sizeof(int), epp_alloc_of(p)));
+    EPP_HIP_TRY(hipMemsetAsync(outside.p, 0, sizeof(int), s));
+    hipLaunchKernelGGL(k_columns_inside, dim3(grid_for(p->nnz, kBlock * kCheckPer)), dim3(kBlock), 0, s, p->cv.as<int2>(),
+                       p->nnz, reinterpret_cast<const unsigned int*>(p->sources), outside.as<int>());
+    EPP_HIP_TRY(hipGetLastError());
+    host.p[0] = 0;
+    EPP_HIP_TRY(hipMemcpyAsync(host.p, outside.p, sizeof(int), hipMemcpyDeviceToHost, s));
+    EPP_HIP_TRY(hipStreamSynchronize(s));
+    if (host.p[0] != 0) p->sources = nullptr;  // any row may be gathered
+    p->sources_checked = true;
     return EPP_OK;
 }
 
