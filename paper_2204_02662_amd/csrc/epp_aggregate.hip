@@ -753,25 +753,34 @@ static double lines_per_row(int F, int ld) {
 }
 
 // Packed source rows.  A launch on large matrices is bound by the 128-byte lines it gathers, and a row of
-// a width like 31 or 47 lies across one more of them than it would fill.  It pays to copy the source
-// rows once per launch to a stride that keeps them apart from the lines' ends (a power of two, beyond 16
-// floats a multiple of 16) where the lines saved by all entries cost more than the copy: about 60 G lines
-// a second come from memory, twice that where the copy (96 MB at most) stays in the memory-side cache,
-// and the copy costs its bytes at 3.7 TB/s (it also displaces cached rows), a launch and a workgroup per 64
-// vertices.  Measured
-// (plain -> packed): 114 M entries, 233 K sources, F = 17 / 31: 1214 -> 910 / 1803 -> 929 us; 140 M entries,
-// 2.4 M sources, F = 31 / 47 / 63: 4596 -> 2738 / 5773 -> 4912 / 7100 -> 5107 us; 37 M entries of as many sources,
-// F = 31 / 63: 1268 -> 951 / 1918 -> 1611 us, but F = 41 / 73, which the rule leaves alone: 1477 -> 1561 / 2160 -> 2320.
+// a width like 31 or 47 lies across one more of them than it would fill.  The source rows can be copied once per
+// launch to a stride that keeps them apart from the lines' ends (a power of two, beyond 16 floats a multiple of 16).
+// It pays where
+//     entries * (cost of a plain row's gather - cost of a packed one's)
+// exceeds the copy (its bytes at 4 TB/s, a workgroup per 64 vertices, a launch).  What a gathered line costs depends
+// on where its matrix lives, and the packed one is up to 1.9 times as large: 6.5 ps where it fits an L2, rising by
+// 1.85 ps with every doubling to 15.75 ps at 128 MB and beyond (measured at 0.25 to 8 M sources, 20 to 230 M entries, both
+// graph models, all-active: 6.6 / 10.1 / 13.3 / 14.9 / 17.3 ps at 5 / 13 / 31 / 52 / 176 MB for Chung-Lu, 2 to 4 ps less
+// for R-MAT).  16 bytes a lane with 8 gathers in flight cannot go below 11.6 ps a row, nor 12.6 with two lanes a row:
+// rows of 5 to 8 floats that the caches hold are better read 4 or 8 bytes a lane (F = 5, 84 M entries of 250 K
+// sources: 653 us plain, 907 packed; F = 7, 227 M of 4 M: 4765, 4445).
+// Over 735 graphs and widths (F = 5 to 100, 2 to 230 M entries, 60 K to 8 M sources) the choice costs 0.3 % on average
+// against the better of the two, 18 % at worst (68 against 81 us).
 int epp_packed_stride(const epp_path* p, int F) {
     const int mode = env_int("EPP_TUNE_PACK", 1);  // 0: never, 1: where it pays, 2: always (tests)
     if (mode == 0 || F < 5 || F > (1 << 13) || p->nnz == 0) return F;
     const int ld = F <= 16 ? 1 << ceil_log2(F) : (F + 15) / 16 * 16;
     if (ld == F) return F;
     if (mode == 2) return ld;
-    const double copy_bytes = 4.0 * (double)p->n_src * (F + ld);
-    const double rate = (double)p->n_src * ld * 4 <= 96e6 ? 120e9 : 60e9;
-    const double saved = (lines_per_row(F, F) - lines_per_row(F, ld)) * (double)p->nnz / rate;
-    return saved > 6e-6 + 3e-12 * (double)p->n + 1.25 * copy_bytes / 3.7e12 ? ld : F;
+    const double rows = (double)p->n_src;
+    auto line_cost = [&](int stride) {  // of a matrix with rows that far apart
+        const double doublings = std::log2(std::max(4.0 * rows * stride, 1.0) / 4e6);
+        return 6.5e-12 + 1.85e-12 * std::min(std::max(doublings, 0.0), 5.0);
+    };
+    const double plain = lines_per_row(F, F) * line_cost(F);
+    const double packed = std::max(lines_per_row(F, ld) * line_cost(ld), 11.6e-12) + (ld == 8 ? 1e-12 : 0.0);
+    const double copy = 8e-6 + 3e-12 * (double)p->n + 4.0 * rows * (F + ld) / 4e12;
+    return (double)p->nnz * (plain - packed) > copy ? ld : F;
 }
 
 int epp_build_schedule_over(const epp_path* p, const int32_t* rowptr, int64_t n_rows, int64_t nnz, int gs,
