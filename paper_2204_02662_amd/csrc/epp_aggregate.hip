@@ -920,15 +920,35 @@ int epp_launch_aggregate(epp_path* p, Schedule* sc, int log2_slices, const float
 }
 
 // Share of the entries that lie in rows long enough to be cut into sections (96 entries and more), estimated from
-// the length classes (class c: 2^(c-1) < length <= 2^c).  With the share of the references that go to the
-// sources the L2s hold it tells, before anything is built, where the source-partitioned layout cannot
-// reach the score it is kept for, 0.12 = 0.75 * 0.16: below 0.11 the attempt is not made.
-constexpr double kMinEstimate = 0.11;
+// the length classes (class c: 2^(c-1) < length <= 2^c).
 static double long_row_share(const epp_path* p) {
     double entries = 0.4 * 110.0 * (double)p->len_hist[7];
     for (int c = 8; c < EPP_NCLASS; ++c) entries += 0.7 * (double)(1ll << c) * (double)p->len_hist[c];
     return std::min(entries / (double)std::max<int64_t>(p->nnz, 1), 1.0);
 }
+
+// Rows that are cut into sections, estimated in the same way.
+static double long_rows(const epp_path* p) {
+    double rows = 0.4 * (double)p->len_hist[7];
+    for (int c = 8; c < EPP_NCLASS; ++c) rows += (double)p->len_hist[c];
+    return rows;
+}
+
+// Share of the references that go to the `count` most referenced sources, estimated without counting any: as if the
+// sources were referenced as unequally as the rows are long (on a symmetric graph they are).
+static double estimated_share(const epp_path* p, double count) {
+    auto mean = [](int c) { return c == 0 ? 1.0 : 0.72 * (double)(1ll << c); };
+    double left = count * (double)p->n_stream_rows / (double)std::max<int64_t>(p->n_src, 1), got = 0.0, all = 0.0;
+    for (int c = EPP_NCLASS - 1; c >= 0; --c) {
+        const double rows = (double)p->len_hist[c], take = std::min(rows, left);
+        all += rows * mean(c);
+        got += take * mean(c);
+        left -= take;
+    }
+    return all > 0.0 ? got / all : 0.0;
+}
+
+constexpr double kMarkShare = 0.48, kMarkShareEnd = 0.93;
 
 // Cache-locality choices of one (path, width), made from how often the path references each
 // source.
@@ -937,8 +957,13 @@ static double long_row_share(const epp_path* p) {
 // XCD, 256 MB memory-side cache); with plain loads the rarely referenced rows keep evicting
 // the often referenced ones.  The most referenced sources, as many as fit the budget, stay
 // "hot"; all entries of the others get the cold flag and are gathered with streaming loads.
-// Budget of 64 / 80 / 96 / 128 MB, two layers each: 270 M entries, F = 128: 29.1 / 29.3 / 29.5 / 29.8 ms; 126 M
-// entries, F = 64: 9.47 / 9.25 / 9.26 / 9.48 ms.
+// It pays where the hot sources receive about half of the references or more: at 0.50 to 0.90 of them a launch takes
+// 0.95 to 0.98 of its time without marks, at 0.30 to 0.45 it takes 1.02 to 1.10 (Chung-Lu, 4 and 8 M sources, F = 36 to 100),
+// beyond 0.93 nothing is left to protect them from (12 to 230 M entries, 0.25 to 8 M sources, both models).  The marks are
+// set for widths of 64 and more, which repay them (1 to 2 ms at 100 M entries) within a few passes; narrower ones of
+// more than 128 bytes a row gain 4 % from marks that are there.
+// Budget of 64 / 80 / 96 / 128 MB: within 2 % of each other (270 M entries, F = 128: 29.1 / 29.3 / 29.5 / 29.8 ms for two
+// layers; 126 M entries, F = 64: 9.5 / 9.3 / 9.3 / 9.5 ms).
 //
 // Source partition (epp_partition.hip).  The entries that reference the sources the eight L2s can
 // hold together are moved into one section per XCD; built where the counts say it pays.
@@ -956,15 +981,16 @@ int epp_tune_locality(epp_path* p, int F, int gs, hipStream_t s, int* log2_slice
     const int forced_slices = env_int("EPP_TUNE_LOG2_SLICES", -1);
     *log2_slices = forced_slices >= 0 ? forced_slices : 0;
     *part = nullptr;
-    // Cold marks: for rows of more than one 128-byte line read 16 bytes a lane (140 M entries, 2.4 M sources,
-    // F = 36 / 47, packed / 48: 4820 -> 4614 / 4958 -> 4737 / 4773 -> 4525 us; F = 32: 2566 -> 2555; with 4-byte lanes the
-    // extra branch costs 3 %).
-    // Source partition: for rows of more than one 128-byte line (114 M entries, 233 K sources, F = 36 / 48 / 64:
-    // 1908 -> 1515 / 1985 -> 1451 / 2141 -> 1425 us; rows of one line gain nothing, F = 32: 908 -> 1010).
+    // Both are for rows of more than one 128-byte line, marks also for 16 bytes a lane: with 4-byte lanes the extra
+    // branch costs 3 %, and rows of one line gain nothing (F = 32, 140 M entries, 2.4 M sources: 2566 -> 2555 us marked;
+    // 114 M entries, 233 K sources: 908 -> 1010 partitioned, where F = 36 / 48 / 64 gain 1908 -> 1515 / 1985 -> 1451 /
+    // 2141 -> 1425).
     const int part_mode = env_int("EPP_TUNE_PART", 1);
     if (p->nnz == 0 || (F <= 32 && part_mode != 2)) return EPP_OK;
     const int64_t part_rows = forced_slices >= 0 ? 0 : epp_partition_hot_rows(lines_per_row(F, ld));  // a forced slicing is a measurement
-    const bool want_cold = budget_mb > 0 && p->n_src > rows_budget && marks_pay(F, ld);
+    const double hot_share = estimated_share(p, (double)rows_budget);
+    const bool want_cold = budget_mb > 0 && p->n_src > rows_budget && marks_pay(F, ld) &&
+                           (std::getenv("EPP_TUNE_HOT_MB") || (F >= 64 && hot_share >= kMarkShare && hot_share < kMarkShareEnd));
     // (in the automatic mode only where the source rows do not fit the eight L2s together, or with 10 M entries
     // and more where they fill three of them; forced, for tests and measurements, at any width and size.
     // Measured, never -> always: 12 M entries of 60 K sources, F = 41 / 64 / 100, 12 to 24 MB of them: 233 -> 211 /
@@ -972,8 +998,14 @@ int epp_tune_locality(epp_path* p, int F, int gs, hipStream_t s, int* log2_slice
     // 2 and 6 M of 40 K, F = 100, R-MAT: 67 -> 89 / 162 -> 177)
     const int64_t l2_rows = (4ll << 20) / ((int64_t)ld * 4);
     const int64_t min_src = p->nnz < 10'000'000 ? part_rows : std::min(part_rows, 3 * l2_rows);
-    const double long_share = long_row_share(p);  // the hot sections hold a part of these entries at most
-    const bool want_part = part_rows > 0 && (part_mode == 2 || (part_mode == 1 && p->n_src > min_src && long_share > kMinEstimate));
+    // What it can save is estimated from the length classes before anything is counted (eight partial rows for every
+    // cut row): within a tenth of the score of epp_build_partition on 60 graphs of both models.  Widths of 128 and more
+    // are counted in any case where they have enough long rows, as a graph's sources may be more unequal than its rows.
+    const double long_share = long_row_share(p), needed = epp_partition_score_needed(p);
+    const double estimate = 0.75 * estimated_share(p, (double)part_rows) * long_share -
+                            2.5 * 8.0 * long_rows(p) / (double)p->nnz;
+    const bool promising = F >= 128 ? long_share > needed : estimate > 0.9 * needed;
+    const bool want_part = part_rows > 0 && (part_mode == 2 || (part_mode == 1 && p->n_src > min_src && promising));
     if (!want_cold && !want_part) return EPP_OK;
 
     // sampled reference counts, their histogram, and two bitmaps, in one allocation
@@ -1001,8 +1033,10 @@ int epp_tune_locality(epp_path* p, int F, int gs, hipStream_t s, int* log2_slice
     hipLaunchKernelGGL(k_count_hist, dim3((unsigned)std::min<int64_t>((p->n + kBlock - 1) / kBlock, 2048)), dim3(kBlock), 0, s,
                        cnt.as<int>(), p->n, hist.as<unsigned long long>());
     EPP_HIP_TRY(hipGetLastError());
-    unsigned long long h[kCountBins];
-    EPP_HIP_TRY(hipMemcpyAsync(h, hist.p, sizeof(h), hipMemcpyDeviceToHost, s));
+    PinnedWords host;
+    EPP_TRY(host.get(kCountBins));
+    const unsigned long long* const h = reinterpret_cast<unsigned long long*>(host.p);
+    EPP_HIP_TRY(hipMemcpyAsync(host.p, hist.p, kCountBins * 8, hipMemcpyDeviceToHost, s));
     EPP_HIP_TRY(hipStreamSynchronize(s));
     // the sources kept when bins, most referenced first, are taken while they fit `budget` rows, with a
     // share of the first bin that does not (sources the sample never met are never kept)
@@ -1037,7 +1071,7 @@ int epp_tune_locality(epp_path* p, int F, int gs, hipStream_t s, int* log2_slice
             if (bin_floor(c) >= line.thr) of_hot += refs;
             else if (bin_floor(c) >= line.part_thr) of_hot += refs * line.share / 65536;
         }
-        if (part_mode == 2 || of_hot * long_share > kMinEstimate * sampled) {
+        if (part_mode == 2 || of_hot * long_share > needed * sampled) {
             hipLaunchKernelGGL(k_hot_bitmap, dim3((unsigned)((p->n + kBlock - 1) / kBlock)), dim3(kBlock), 0, s,
                                cnt.as<int>(), p->n, line, part_hot.as<unsigned long long>());
             EPP_HIP_TRY(hipGetLastError());

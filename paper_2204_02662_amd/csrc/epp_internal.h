@@ -361,6 +361,8 @@ int epp_tune_locality(epp_path* p, int F, int gs, hipStream_t s, int* log2_slice
 
 // partition.hip
 int epp_partition_hot_rows(double lines);  // source rows of width F the eight L2s hold together
+// share of the gathers it has to save (epp_build_partition)
+inline double epp_partition_score_needed(const epp_path* p) { return p->nnz < 5 * p->n_stream_rows ? 0.20 : 0.12; }
 // source-partitioned layout of `p` for width F and group size gs, or *out = NULL where it does not pay
 // `unstreamed` (or NULL): bitmap of the sources whose entries stay unmarked in the last section; the
 // copy then sets the streamed-source marks itself, whatever the canonical array carries

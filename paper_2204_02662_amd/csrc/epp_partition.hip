@@ -407,7 +407,9 @@ int epp_build_partition(epp_path* p, int F, int gs, const unsigned int* hot_bitm
     a1.take(&totals, 8 * sizeof(long long));
     EPP_HIP_TRY(hipMemsetAsync(totals.p, 0, totals.bytes, s));
     long long* d_tot = totals.as<long long>();
-    long long h_tot[8] = {};
+    PinnedWords host;
+    EPP_TRY(host.get(16));
+    long long* const h_tot = host.p;
     hipLaunchKernelGGL(k_part_flag_rows, dim3(grid_for(R, kBlock)), dim3(kBlock), 0, s, rowptr, R, min_len, flag.as<int>());
     epp_scan_exclusive(flag.as<int>(), midx.as<int>(), R, d_tot, scan_tmp.as<int>(), s);
     EPP_HIP_TRY(hipGetLastError());
@@ -482,13 +484,25 @@ int epp_build_partition(epp_path* p, int F, int gs, const unsigned int* hot_bitm
     // gains 2 %, one with 28 % / 7 % loses 14 %.  The layout is built when the modelled saving,
     // 0.75 hot - 2.5 partial rows (in gathers), exceeds 0.12 of the entries (88 M entries, 700 K sources:
     // 0.20 at F = 64: 2931 -> 2527 us; 0.17 at F = 100: 5687 -> 4964; 0.15 at F = 128: 5563 -> 5097.
-    // 140 M entries, 2.4 M sources, 0.08 at F = 64: 4599 -> 4602).
+    // 140 M entries, 2.4 M sources, 0.08 at F = 64: 4599 -> 4602), and 0.20 where rows have fewer than five
+    // entries on average: a launch is then bound by row ends as much as by gathers (31 M entries in 8.4 M rows,
+    // R-MAT, 0.15 at F = 36: 1187 -> 1256, 0.14 at F = 47: 1388 -> 1591, 0.12 at F = 128: 2652 -> 2761; 26 M in 4.2 M,
+    // 0.23 at F = 36: 906 -> 804).  What a copy costs (1.0 / 1.5 to 2.0 / 3 to 4.4 ms at 20 / 80 / 200 M entries) is
+    // repaid in 5 to 20 / 1 to 5 / 1 to 4 passes.
     const double score = (0.75 * (double)hot_entries - 2.5 * (double)n_slots) / (double)nnz;
-    if (mode == 1 && score < 0.12) return EPP_OK;
+    if (mode == 1 && score < epp_partition_score_needed(p)) return EPP_OK;
     if (p->n + n_slots >= 0x7FFFFFFFll) return EPP_OK;  // targets are 31-bit
 
     Partition* q = new Partition();
-    struct Guard { Partition* q; ~Guard() { delete q; } } guard{q};
+    struct Guard {  // (on an error: nothing may still be writing to what is given back)
+        Partition* q;
+        hipStream_t s;
+        ~Guard() {
+            if (!q) return;
+            (void)hipStreamSynchronize(s);
+            delete q;
+        }
+    } guard{q, s};
     q->n_vrows = n_vrows;
     q->n_split = M;
     q->n_slots = n_slots;
@@ -535,8 +549,8 @@ int epp_build_partition(epp_path* p, int F, int gs, const unsigned int* hot_bitm
                        m_of_row.as<int32_t>(), voff.as<int>(), unstreamed, reinterpret_cast<int2v*>(q->cv2.p),
                        q->whole_off.as<int>());
     EPP_HIP_TRY(hipGetLastError());
-    int h_sec[kSec];
-    EPP_HIP_TRY(hipMemcpyAsync(h_sec, sec_start.p, sizeof(h_sec), hipMemcpyDeviceToHost, s));
+    int* const h_sec = reinterpret_cast<int*>(host.p + 8);
+    EPP_HIP_TRY(hipMemcpyAsync(h_sec, sec_start.p, kSec * sizeof(int), hipMemcpyDeviceToHost, s));
     EPP_TRY(epp_build_schedule_over(p, q->vptr.as<int32_t>(), n_vrows, nnz, gs, s, &q->sched));  // synchronises
     EPP_TRY(q->sched->ensure_pieces(F, al));
     q->sec_g[0] = 0;
