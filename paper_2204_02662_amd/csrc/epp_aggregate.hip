@@ -974,9 +974,8 @@ constexpr double kMarkShare = 0.48, kMarkShareEnd = 0.93;
 // traffic: it is switched on when rows are at least 512 bytes and the sources that fit with
 // slicing, but not without, receive at least 6 % of all references (measured: R-MAT
 // configuration, 8 % -> 16.5 to 15.3 ms; Chung-Lu configuration, 4 % -> 4.3 to 4.6 ms, left off).
-int epp_tune_locality(epp_path* p, int F, int gs, hipStream_t s, int* log2_slices, Partition** part) {
+int epp_tune_locality(epp_path* p, int F, int ld, int gs, hipStream_t s, int* log2_slices, Partition** part) {
     const int64_t budget_mb = env_int("EPP_TUNE_HOT_MB", 80);
-    const int ld = epp_packed_stride(p, F);
     const int64_t rows_budget = budget_mb * (1ll << 20) / ((int64_t)ld * 4);
     const int forced_slices = env_int("EPP_TUNE_LOG2_SLICES", -1);
     *log2_slices = forced_slices >= 0 ? forced_slices : 0;
@@ -1012,8 +1011,8 @@ int epp_tune_locality(epp_path* p, int F, int gs, hipStream_t s, int* log2_slice
     DevArena arena;
     DevBuf cnt, hist, hot, part_hot;
     const size_t hot_bytes = (size_t)((p->n + 63) / 64) * 8;
-    EPP_TRY(arena.reserve(DevArena::rounded((size_t)p->n * 4) + DevArena::rounded(kCountBins * sizeof(unsigned long long)) +
-                          2 * DevArena::rounded(hot_bytes), epp_alloc_of(p)));
+    if (arena.reserve(DevArena::rounded((size_t)p->n * 4) + DevArena::rounded(kCountBins * sizeof(unsigned long long)) +
+                      2 * DevArena::rounded(hot_bytes), epp_alloc_of(p)) != EPP_OK) return EPP_OK;
     arena.take(&cnt, (size_t)p->n * 4);
     arena.take(&hist, kCountBins * sizeof(unsigned long long));
     arena.take(&hot, hot_bytes);
@@ -1076,8 +1075,9 @@ int epp_tune_locality(epp_path* p, int F, int gs, hipStream_t s, int* log2_slice
                                cnt.as<int>(), p->n, line, part_hot.as<unsigned long long>());
             EPP_HIP_TRY(hipGetLastError());
             // (new marks are set by the copy itself, from the bitmap)
-            EPP_TRY(epp_build_partition(p, F, gs, part_hot.as<unsigned int>(), new_marks ? hot.as<unsigned int>() : nullptr,
-                                        s, part));
+            const int rc = epp_build_partition(p, F, gs, part_hot.as<unsigned int>(),
+                                               new_marks ? hot.as<unsigned int>() : nullptr, s, part);
+            if (rc != EPP_ERR_ALLOC) EPP_TRY(rc);
         }
     }
 

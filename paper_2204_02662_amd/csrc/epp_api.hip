@@ -39,6 +39,8 @@ int prepare_width(epp_path* self, int F, hipStream_t s, epp_path::WidthCfg** out
         // small paths run without tables; a group size asked for is a group table asked for, and so is the
         // if-else baseline, which only the all-active handle serves
         w->rows = w->forced_gs <= 0 && epp_rows_kernel_fits(p, F);
+        delete w->plan;  // (left by a call that failed later on)
+        w->plan = nullptr;
         if (w->rows) EPP_TRY(epp_build_rows_plan(p, F, s, &w->plan));
         if (w->rows && !p->all_rows) {
             w->prepared = true;
@@ -53,13 +55,16 @@ int prepare_width(epp_path* self, int F, hipStream_t s, epp_path::WidthCfg** out
         if (w->ld > F) {
             EPP_TRY(epp_check_sources(p, s));  // (the launch copies the rows of `sources` only)
             void* scratch = nullptr;
-            EPP_TRY(p->rows_pool->get((size_t)p->n * (size_t)w->ld * 4, epp_alloc_of(p), &scratch));
-            if (!p->rows_pool->accounted_by) p->rows_pool->accounted_by = p;
-            w->packed = static_cast<float*>(scratch);
+            if (p->rows_pool->get((size_t)p->n * (size_t)w->ld * 4, epp_alloc_of(p), &scratch) == EPP_OK) {
+                if (!p->rows_pool->accounted_by) p->rows_pool->accounted_by = p;
+                w->packed = static_cast<float*>(scratch);
+            } else {
+                w->ld = F;  // no memory for the copy: the rows are read where they are
+            }
         }
         delete w->part;
         w->part = nullptr;
-        EPP_TRY(epp_tune_locality(p, F, gs, s, &w->log2_slices, &w->part));
+        EPP_TRY(epp_tune_locality(p, F, w->ld, gs, s, &w->log2_slices, &w->part));
         // partial rows of the plain group table: not needed where every launch uses the partitioned
         // layout (the all-active handle also serves the if-else baseline, which never does)
         if (!w->part || p->all_rows) EPP_TRY(sc->ensure_pieces(F, epp_alloc_of(p)));

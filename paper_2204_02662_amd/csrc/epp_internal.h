@@ -357,7 +357,8 @@ int epp_build_schedule_over(const epp_path* p, const int32_t* rowptr, int64_t n_
                             Schedule** out);
 int epp_default_group_size(const epp_path* p, int F);
 int epp_zero_empty_rows(const epp_path* p, float* out, int F, hipStream_t s);
-int epp_tune_locality(epp_path* p, int F, int gs, hipStream_t s, int* log2_slices, Partition** part);
+// ld: floats from one source row to the next.  Where the memory for it is missing, marks and partition are left out.
+int epp_tune_locality(epp_path* p, int F, int ld, int gs, hipStream_t s, int* log2_slices, Partition** part);
 
 // partition.hip
 int epp_partition_hot_rows(double lines);  // source rows of width F the eight L2s hold together
