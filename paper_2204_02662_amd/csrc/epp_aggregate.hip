@@ -47,7 +47,7 @@ template <int VEC, class V> __device__ __forceinline__ float lane_get(const V& x
 
 // ---------------------------------------------------------------- schedule construction
 // A thread per row (streamed rows are non-empty): it is the row of the first entry of every group that
-// starts inside it.  Bit 31 marks a group that starts past the row's beginning; a row with such a
+// starts inside it; the groups of a row with many are written by its wavefront.  Bit 31 marks a group that starts past the row's beginning; a row with such a
 // group is cut, and listed once.  A workgroup takes kSchedRows rows and one place in the list for
 // all its cut rows together: an addition to the one counter costs 8 ns, whoever makes it.  (A search of
 // the row pointer for every group, the other way round, is a chain of some twenty loads.)
@@ -71,12 +71,14 @@ __global__ __launch_bounds__(1024) void k_sched_groups(const int32_t* __restrict
     bool cut[kPer];
 #pragma unroll
     for (int i = 0; i < kPer; ++i) {
-        unsigned int g = (p0[i] + step - 1) / step;  // (32 bits: entries and group size are below 2^31)
-        cut[i] = false;
-        for (unsigned int j = g * step; j < p1[i] && j >= p0[i]; j += step, ++g) {
-            group_row[g] = (int32_t)(r0 + i * 1024) | (j > p0[i] ? kRowEnd : 0);
-            cut[i] |= j > p0[i];
-        }
+        // the groups that start in the row (32 bits: entries and group size are below 2^31); the first may start with it
+        const unsigned int g0 = (p0[i] + step - 1) / step, g1 = (p1[i] + step - 1) / step;
+        const int whole = g0 * step == p0[i] ? 1 : 0, mine = (int)(r0 + i * 1024);
+        if (g1 > g0) group_row[g0] = mine | (whole ? 0 : kRowEnd);
+        for_range_by_wave((int64_t)g0 + 1, g1, [&](int64_t g, int l) {
+            group_row[g] = (mine + l - (int)(threadIdx.x & 63)) | kRowEnd;
+        });
+        cut[i] = g1 > g0 + whole;
         at[i] = cut[i] ? atomicAdd(&count, 1u) : 0u;
     }
     __syncthreads();

@@ -20,6 +20,21 @@ constexpr int kEntOuterOnly = 0x20000000;      // not an entry of the inner path
 constexpr int kEntCol = 0x1FFFFFFF;
 constexpr long long kMaxVertices = 0x20000000ll;  // vertex ids must leave the flag bits free
 
+// f(i, lane) for the i of every lane's range [i0, i1): by the lane itself while they are few, else by the whole
+// wavefront (all lanes call this): one long row must not make one lane do the work of thousands.
+template <class F>
+__device__ __forceinline__ void for_range_by_wave(int64_t i0, int64_t i1, F f) {
+    const bool many = i1 - i0 > 8;
+    if (!many) {
+        for (int64_t i = i0; i < i1; ++i) f(i, (int)(threadIdx.x & 63));
+    }
+    for (unsigned long long todo = __ballot(many); todo; todo &= todo - 1ull) {
+        const int l = __ffsll((long long)todo) - 1;
+        const int64_t first = __shfl(i0, l, 64), last = __shfl(i1, l, 64);
+        for (int64_t i = first + (int)(threadIdx.x & 63); i < last; i += 64) f(i, l);
+    }
+}
+
 void epp_set_error(const char* fmt, ...);
 
 #define EPP_HIP_TRY(expr)                                                                           \

@@ -368,6 +368,19 @@ __global__ __launch_bounds__(1024) void k_scan_add_offsets(int* __restrict__ out
         if (i0 + j < n) out[i0 + j] += off;
 }
 
+// Members of a level's set N^{k+1} before a vertex: bitmap, and the members before every 256 vertices.
+struct Members {
+    const unsigned long long* bitmap;
+    const int* base;
+    __device__ __forceinline__ int before(int v, int n) const {
+        if (v >= n) v = n - 1;
+        const int w0 = (v >> 8) * 4, w = v >> 6;
+        int r = base[v >> 8];
+        for (int i = w0; i < w; ++i) r += __popcll(bitmap[i]);
+        return r + __popcll(bitmap[w] & low_mask(v & 63));
+    }
+};
+
 // Where the kept entries of a level go: mask, and the counts before a tile and inside it.
 struct Kept {
     const unsigned long long* mask;
@@ -382,18 +395,19 @@ struct Kept {
 // not keep get the kEntOuterOnly mark: the path of the level before will run on this array;
 // inner_pos[q / 64] then receives, for every 64th entry q, how many entries before it that level kept.
 //
-// The last kept entry of every row gets the row-end flag: a workgroup looks through the rows that
-// overlap its tile (tile_row[t]: the row of the tile's first entry) for those whose filtered list
-// ends in it, while its entries are in flight.  (A kernel of its own that set the flags in the
-// finished array took 0.1 ms for 2.4 M rows: a read and a write of 128 bytes for each.)
+// The last kept entry of every row gets the row-end flag: a workgroup looks through the path's rows that
+// overlap its tile (tile_row[t]: the vertex of the tile's first entry) for those that end in it, while its
+// entries are in flight.  They are 2,050 at most, as none of them is empty: the vertices in between can be
+// millions.  (A kernel of its own that set the flags in the finished array took 0.1 ms for 2.4 M rows:
+// a read and a write of 128 bytes for each.)
 //
 // Runs at the rate of a copy: 140 M entries in 0.42 ms.  (What concerns a segment is fetched by one lane
 // and read from there as a scalar; vector loads of it cost 0.45 ms more.)
 __global__ __launch_bounds__(kBlock) void k_edge_extract(const int32_t* __restrict__ col, const float* __restrict__ val,
                                                          int64_t n_seg, Kept outer, Kept inner,
                                                          int* __restrict__ inner_pos, const int* __restrict__ tile_row,
-                                                         const int* __restrict__ newptr, int n, int total,
-                                                         int2* __restrict__ cv) {
+                                                         Members members, int n, const int* __restrict__ ptr, int n_rows,
+                                                         int total, int2* __restrict__ cv) {
     constexpr int kPerWave = kSegsPerTile / 4;
     __shared__ unsigned int row_end[kSegsPerTile * 2];  // one bit per kept entry of the tile
     if (threadIdx.x < kSegsPerTile * 2) row_end[threadIdx.x] = 0u;
@@ -418,12 +432,14 @@ __global__ __launch_bounds__(kBlock) void k_edge_extract(const int32_t* __restri
     }
     const bool last_tile = blockIdx.x + 1 == gridDim.x;
     const int base = outer.tile_base[blockIdx.x], limit = last_tile ? total : outer.tile_base[blockIdx.x + 1];
-    const int v_last = last_tile ? n - 1 : tile_row[blockIdx.x + 1];
     __syncthreads();
     if (limit > base) {
-        for (int v = tile_row[blockIdx.x] + (int)threadIdx.x; v <= v_last; v += kBlock) {
-            const int a = newptr[v], b = newptr[v + 1];
-            if (b > a && b > base && b <= limit) atomicOr(&row_end[(b - 1 - base) >> 5], 1u << ((b - 1 - base) & 31));
+        // (the row of the next tile's first entry may end in this one, if that entry is not kept)
+        const int r0 = members.before(tile_row[blockIdx.x], n);
+        const int r1 = last_tile ? n_rows : min(members.before(tile_row[blockIdx.x + 1], n) + 1, n_rows);
+        for (int r = r0 + (int)threadIdx.x; r < r1; r += kBlock) {
+            const int b = ptr[r + 1];
+            if (b > base && b <= limit) atomicOr(&row_end[(b - 1 - base) >> 5], 1u << ((b - 1 - base) & 31));
         }
     }
     __syncthreads();
@@ -467,6 +483,7 @@ __global__ __launch_bounds__(kBlock) void k_row_flags(const int32_t* __restrict_
     int b = __shfl_down(a, 1, 64);
     if (lane == 63) b = kept_before(p1);
     bool flag = false;
+    int64_t t0 = 0, t1 = 0;  // tiles whose first entry is the row's
     if (v < n) {
         if (v == n - 1) p1 = rowptr[n];
         if (p0 < 0 || p1 < p0 || p1 > nnz || (v == 0 && p0 != 0) || (v == n - 1 && p1 != nnz))
@@ -476,9 +493,11 @@ __global__ __launch_bounds__(kBlock) void k_row_flags(const int32_t* __restrict_
         flag = b > a;
         if (tile_row && p0 >= 0 && p1 > p0 && p1 <= nnz) {  // (first level: the rows of the tiles' first entries)
             constexpr int kTile = kSegsPerTile * 64;
-            for (int64_t t = ((int64_t)p0 + kTile - 1) / kTile; t * kTile < p1; ++t) tile_row[t] = (int)v;
+            t0 = ((int64_t)p0 + kTile - 1) / kTile;
+            t1 = ((int64_t)p1 + kTile - 1) / kTile;
         }
     }
+    if (tile_row) for_range_by_wave(t0, t1, [&](int64_t t, int lane_of_row) { tile_row[t] = (int)(v - lane + lane_of_row); });
     const unsigned long long bal = __ballot(flag);
     if (lane == 0) {
         const bool in = v < n;
@@ -1104,9 +1123,9 @@ extern "C" int epp_prepare(const epp_csr_t* g, const int32_t* train_ids, int64_t
     EPP_HIP_TRY(hipMemsetAsync(P->bitmaps[0].p, 0, bm_bytes, s));  // (the others are written whole)
 
     // all temporaries of the construction come from one allocation
-    // (keep-mask, its counts and the filtered row pointer twice: the entries of a level are extracted once the next
-    // level has shown whether the two paths share them, so two levels' masks are alive at a time)
-    DevBuf mask[2], seg_off[2], tile_base[2], tile_cnt, row_cnt, row_base, scan_tmp, newptr[2], tile_row, levels;
+    // (keep-mask, its counts and the members before every 256 vertices twice: the entries of a level are extracted once
+    // the next level has shown whether the two paths share them, so two levels' masks are alive at a time)
+    DevBuf mask[2], seg_off[2], tile_base[2], tile_cnt, row_cnt, row_base[2], scan_tmp, newptr, tile_row, levels;
     const size_t cnt_bytes = (size_t)std::max(std::max(edge_tiles, word_tiles), 1u) * 4;
     const size_t row_bytes = (size_t)std::max(row_tiles, 1u) * 4;
     const size_t tmp_bytes = scan_tmp_bytes(std::max<int64_t>(edge_tiles, row_tiles));
@@ -1114,17 +1133,17 @@ extern "C" int epp_prepare(const epp_csr_t* g, const int32_t* train_ids, int64_t
     DevArena arena;
     EPP_TRY(arena.reserve(2 * (DevArena::rounded((size_t)n_seg * 8) + DevArena::rounded((size_t)n_seg * 2) +
                                DevArena::rounded(cnt_bytes)) +
-                          2 * DevArena::rounded(cnt_bytes) + 2 * DevArena::rounded(row_bytes) + DevArena::rounded(tmp_bytes) +
-                          2 * DevArena::rounded((size_t)(n + 1) * 4) + DevArena::rounded(level_bytes), al));
+                          2 * DevArena::rounded(cnt_bytes) + 3 * DevArena::rounded(row_bytes) + DevArena::rounded(tmp_bytes) +
+                          DevArena::rounded((size_t)(n + 1) * 4) + DevArena::rounded(level_bytes), al));
     for (int i = 0; i < 2; ++i) {
         arena.take(&mask[i], (size_t)n_seg * 8);
         arena.take(&seg_off[i], (size_t)n_seg * 2);
         arena.take(&tile_base[i], cnt_bytes);
-        arena.take(&newptr[i], (size_t)(n + 1) * 4);
+        arena.take(&row_base[i], row_bytes);
     }
+    arena.take(&newptr, (size_t)(n + 1) * 4);
     arena.take(&tile_cnt, cnt_bytes);
     arena.take(&row_cnt, row_bytes);
-    arena.take(&row_base, row_bytes);
     arena.take(&scan_tmp, tmp_bytes);
     arena.take(&tile_row, cnt_bytes);
     arena.take(&levels, level_bytes);
@@ -1145,11 +1164,12 @@ extern "C" int epp_prepare(const epp_csr_t* g, const int32_t* train_ids, int64_t
     // the inner path's.  Every other level at most: a path whose marks serve an inner path
     // keeps its own arrays.
     std::vector<epp_path*> built;  // in level order, for the statistics
-    struct { epp_path* p = nullptr; int slot = 0; } pending;  // path whose entries are not extracted yet
+    struct { epp_path* p = nullptr; int level = 0; } pending;  // path whose entries are not extracted yet
     auto kept_of = [&](int slot) {
         return Kept{mask[slot].as<unsigned long long>(), seg_off[slot].as<uint16_t>(), tile_base[slot].as<int>()};
     };
-    auto extract = [&](epp_path* q, int slot, bool marks_inner) -> int {
+    auto extract = [&](epp_path* q, int level, bool marks_inner) -> int {
+        const int slot = level & 1;
         // the entries in an allocation of their own (it can be given back once every prepared width
         // runs on a reconstructed copy)
         EPP_TRY(q->cv.alloc((size_t)q->nnz * sizeof(int2), al));
@@ -1157,7 +1177,9 @@ extern "C" int epp_prepare(const epp_csr_t* g, const int32_t* train_ids, int64_t
         if (edge_tiles) {
             hipLaunchKernelGGL(k_edge_extract, dim3(edge_tiles), dim3(kBlock), 0, s, g->col, g->val, n_seg, kept_of(slot),
                                marks_inner ? kept_of(slot ^ 1) : Kept{nullptr, nullptr, nullptr}, q->inner_pos.as<int>(),
-                               tile_row.as<int>(), newptr[slot].as<int>(), (int)n, (int)q->nnz, q->cv.as<int2>());
+                               tile_row.as<int>(),
+                               Members{P->bitmaps[level + 1].as<unsigned long long>(), row_base[slot].as<int>()}, (int)n,
+                               q->rowptr.as<int>(), (int)q->n_rows, (int)q->nnz, q->cv.as<int2>());
         }
         EPP_HIP_TRY(hipGetLastError());
         return EPP_OK;
@@ -1186,10 +1208,10 @@ extern "C" int epp_prepare(const epp_csr_t* g, const int32_t* train_ids, int64_t
         }
         if (n > 0) {
             hipLaunchKernelGGL(k_row_flags, dim3(row_tiles), dim3(kBlock), 0, s, g->rowptr, n, nnz, kept_of(slot), d_level,
-                               newptr[slot].as<int>(), P->bitmaps[k].as<unsigned long long>(),
+                               newptr.as<int>(), P->bitmaps[k].as<unsigned long long>(),
                                P->bitmaps[k + 1].as<unsigned long long>(), row_cnt.as<int>(),
                                k == 0 ? tile_row.as<int>() : (int*)nullptr);
-            scan_counts(row_cnt.as<int>(), row_base.as<int>(), (int64_t)row_tiles, d_level + 1, scan_tmp.as<int>(), s, d_level,
+            scan_counts(row_cnt.as<int>(), row_base[slot].as<int>(), (int64_t)row_tiles, d_level + 1, scan_tmp.as<int>(), s, d_level,
                         hs.p);
         } else {
             EPP_HIP_TRY(hipMemcpyAsync(hs.p, d_level, kLevelWords * sizeof(long long), hipMemcpyDeviceToHost, s));
@@ -1220,7 +1242,7 @@ extern "C" int epp_prepare(const epp_csr_t* g, const int32_t* train_ids, int64_t
         p->rowptr.view(base + DevArena::rounded(ids_bytes), ptr_bytes);
         if (n > 0) {
             hipLaunchKernelGGL(k_rows_compact, dim3(std::min(row_tiles, kStatBlocks)), dim3(kBlock), 0, s,
-                               P->bitmaps[k + 1].as<unsigned long long>(), n, row_base.as<int>(), newptr[slot].as<int>(),
+                               P->bitmaps[k + 1].as<unsigned long long>(), n, row_base[slot].as<int>(), newptr.as<int>(),
                                p->row_ids.as<int32_t>(), p->rowptr.as<int32_t>(), (int64_t)R, (int)kept,
                                d_stats + (size_t)k * kStatWords);
             EPP_HIP_TRY(hipGetLastError());
@@ -1234,12 +1256,12 @@ extern "C" int epp_prepare(const epp_csr_t* g, const int32_t* train_ids, int64_t
             p->has_inner = true;
             q->outer = p;
             q->inner_rows = P->bitmaps[k].as<unsigned int>();  // its rows are N^k
-            EPP_TRY(extract(p, slot, true));
+            EPP_TRY(extract(p, k, true));
             pending.p = nullptr;
         } else {
-            if (q) EPP_TRY(extract(q, pending.slot, false));
+            if (q) EPP_TRY(extract(q, pending.level, false));
             pending.p = p;
-            pending.slot = slot;
+            pending.level = k;
         }
         nested = next_nested;
         // Fixed point: N^{k+1} == N^k means every further set is the same set, so every deeper
@@ -1254,7 +1276,7 @@ extern "C" int epp_prepare(const epp_csr_t* g, const int32_t* train_ids, int64_t
             break;
         }
     }
-    if (pending.p) EPP_TRY(extract(pending.p, pending.slot, false));
+    if (pending.p) EPP_TRY(extract(pending.p, pending.level, false));
     EPP_HIP_TRY(hipMemcpyAsync(hs.p + kLevelWords, d_stats, (size_t)L * kStatWords * 8, hipMemcpyDeviceToHost, s));
     EPP_HIP_TRY(hipStreamSynchronize(s));
     for (size_t k = 0; k < built.size(); ++k)

@@ -223,13 +223,20 @@ __global__ __launch_bounds__(kBlock) void k_cut_huge_rows(const int32_t* __restr
                                                           int* __restrict__ counters, int2v* __restrict__ chunks,
                                                           HugeRow* __restrict__ rows) {
     const int r = blockIdx.x * kBlock + threadIdx.x;
-    if (r >= n_rows) return;
-    const int p0 = rowptr[r], p1 = rowptr[r + 1];
-    if (p1 - p0 <= chunk) return;
-    const int cnt = (p1 - p0 + chunk - 1) / chunk;
-    const int first = atomicAdd(&counters[0], cnt);
-    rows[atomicAdd(&counters[1], 1)] = HugeRow{row_ids ? row_ids[r] : r, first, cnt};
-    for (int i = 0; i < cnt; ++i) chunks[first + i] = int2v{p0 + i * chunk, min(p0 + (i + 1) * chunk, p1)};
+    const int p0 = r < n_rows ? rowptr[r] : 0, p1 = r < n_rows ? rowptr[r + 1] : 0;
+    int first = 0, cnt = 0;
+    if (p1 - p0 > chunk) {
+        cnt = (p1 - p0 + chunk - 1) / chunk;
+        first = atomicAdd(&counters[0], cnt);
+        rows[atomicAdd(&counters[1], 1)] = HugeRow{row_ids ? row_ids[r] : r, first, cnt};
+    }
+    // a row's chunks are written by its wavefront: there can be thousands
+    for (unsigned long long todo = __ballot(cnt > 0); todo; todo &= todo - 1ull) {
+        const int l = __ffsll((long long)todo) - 1;
+        const int begin = __shfl(p0, l, 64), end = __shfl(p1, l, 64), at = __shfl(first, l, 64), n = __shfl(cnt, l, 64);
+        for (int i = threadIdx.x & 63; i < n; i += 64)
+            chunks[at + i] = int2v{begin + i * chunk, min(begin + (i + 1) * chunk, end)};
+    }
 }
 
 // out[v] = sum of the chunks of v's row, in a fixed order.  One wavefront per row: the pieces are
