@@ -112,6 +112,7 @@ struct AggArgs {
     int F;
     int ld;                    // floats from one row of `in` to the next
     int gs;
+    int ragged;                // a group is not a whole number of batches of gathers (host-side: gs against U)
     int log2ns;                // feature slices spread over the XCDs (1 << log2ns of them)
     int has_cold;              // some entries carry the cold flag (host-side kernel choice)
     float* pieces;             // partial rows of the groups, [n_groups][2][F]
@@ -424,7 +425,10 @@ __global__ __launch_bounds__(kBlock, IFELSE ? ((COLD && VEC != 1) ? 4 : 5) : ((I
                     if (base + i * T + t >= len) pre[i] = int2v{kOuterOnly, 0};
                     else if (pre[i].x & kOuterOnly) { pre[i].x &= ~kCold; pre[i].y = 0; }
                 } else {
-                    if (base + i * T + t >= len) { pre[i].x &= kColMask; pre[i].y = 0; }  // no row end, weight 0
+                    if (base + i * T + t >= len) {  // no row end, weight 0; the baseline does not gather it either
+                        pre[i].x = IFELSE ? kColMask : pre[i].x & kColMask;
+                        pre[i].y = 0;
+                    }
                 }
                 stage[i * T + t] = pre[i];
             }
@@ -470,6 +474,15 @@ __global__ __launch_bounds__(kBlock, IFELSE ? ((COLD && VEC != 1) ? 4 : 5) : ((I
                         // the address stays live past both loads: a result register that overlapped it
                         // would make the second load wait for the first
                         if constexpr (COLD) asm volatile("" ::"v"(p));
+                    }
+                }
+                // what fills up a group that is cut inside a row would add 0 times the group's last source row to
+                // it, which is no zero where that row holds an infinity
+                if constexpr (!IFELSE && !INNER) {
+                    if (a.ragged) {
+#pragma unroll
+                        for (int u = 0; u < U; ++u)
+                            if (base + b + u >= len) x[u] = vec_t{};
                     }
                 }
 #pragma unroll
@@ -598,7 +611,8 @@ void launch_plain(dim3 grid, dim3 block, hipStream_t s, const AggArgs& a) {
 }
 
 template <int VEC, int LOG2T, int U>
-void launch_one(hipStream_t s, const AggArgs& a) {
+void launch_one(hipStream_t s, AggArgs a) {
+    a.ragged = a.gs % std::min(U, 4 << LOG2T) != 0;
     const int64_t per_block = kBlock >> LOG2T;
     const int64_t blocks_per_slice = (a.n_groups + per_block - 1) / per_block;
     const int64_t xcds_per_slice = 8 >> a.log2ns;

@@ -7,7 +7,7 @@ import torch
 import graphgen
 import oracle
 import paper_2204_02662_amd as epp
-from _util import ATOL, RTOL, dev, gpu_prepare, run_partial
+from _util import ATOL, RTOL, dev, gpu_prepare, gpu_prepare_full, run_full, run_ifelse, run_partial
 
 pytestmark = pytest.mark.gpu
 
@@ -71,3 +71,27 @@ def test_inner_path_does_not_meet_the_weights_of_the_outer_one(F, monkeypatch):
     want = oracle.path_aggregate(g.n, paths_o[1], X)
     got = run_partial(paths.path(1), X)
     assert np.all(np.abs(got - want) <= ATOL + RTOL * np.abs(want))
+
+
+@pytest.mark.parametrize("layout", ["plain", "packed", "partitioned", "marked"])
+@pytest.mark.parametrize("gs", [1, 3, 8, 24, 64])
+@pytest.mark.parametrize("F", [2, 7, 16, 41, 64])
+def test_groups_of_any_size(F, gs, layout, monkeypatch):
+    """Group ends inside rows, right behind an infinite source; if-else baseline as well."""
+    for k, v in {"EPP_TUNE_ROWS": "0", "EPP_TUNE_PACK": "2" if layout == "packed" else "0",
+                 "EPP_TUNE_PART": "2" if layout == "partitioned" else "0", "EPP_TUNE_PART_KB": "16",
+                 "EPP_TUNE_PART_MINLEN": "8", "EPP_TUNE_HOT_MB": "1" if layout == "marked" else "0"}.items():
+        monkeypatch.setenv(k, v)
+    g = graphgen.random_graph("rmat", 6_007, seed=51, raw_draws=60_000)  # (weights are positive)
+    train = graphgen.training_set(g.n, 2_000, 52)
+    sets_o, paths_o = oracle.prepare(g.n, g.rowptr, g.col, g.val, train, 1)
+    paths, full = gpu_prepare(g, train, 1), gpu_prepare_full(g)
+    src = np.flatnonzero(sets_o[0])
+    X = _with_infinities(graphgen.normal_rows(g.n, F, sets_o[0], 53), src[::40])
+    want = oracle.path_aggregate(g.n, paths_o[0], X)
+    for p in (paths.path(0), full):
+        p.set_group_size(F, gs)
+    rows = sets_o[1].astype(bool)
+    _assert_same(run_partial(paths.path(0), X)[rows], want[rows], f"F={F} gs={gs}")
+    _assert_same(run_ifelse(full, paths, 0, X)[rows], want[rows], f"if-else F={F} gs={gs}")
+    _assert_same(run_full(full, X), oracle.full_aggregate(g.n, g.rowptr, g.col, g.val, X), f"all-active F={F} gs={gs}")
