@@ -7,14 +7,19 @@
  * function aborts or throws across this boundary.  A handle (epp_paths_t / epp_path_t) must
  * not be used by two calls at the same time (calls on one stream, one after the other, are fine).
  *
- * Environment variables read when a schedule is built (measurement knobs; defaults in brackets):
+ * Environment variables read when paths or a width are prepared (measurement knobs; defaults in brackets):
  *   EPP_TUNE_GS           group size for every (path, F) that has none forced            [selector]
- *   EPP_TUNE_HOT_MB       budget of the hot source rows, 0 switches hot/cold marking off [96]
+ *   EPP_TUNE_ROWS         small paths and widths of at most 4 floats run on a kernel that takes rows whole and needs no
+ *                         group table: 0 never, 1 where it is faster, 2 always           [1]
+ *   EPP_TUNE_PACK         source rows copied to a wider stride by the launch: 0 never, 1 where it pays, 2 always  [1]
+ *   EPP_TUNE_HOT_MB       budget of the hot source rows (given: marks are set wherever the rows do not fit it), 0 switches
+ *                         hot/cold marking off                                           [80, where marks pay]
  *   EPP_TUNE_LOG2_SLICES  log2 of the XCD feature slices, 0..3                           [chosen per path]
- *   EPP_TUNE_SMALL_PREPARE  0: graphs of at most 65,536 vertices and 131,072 entries are prepared by the general
- *                         construction instead of the single-launch one                     [1]
+ *   EPP_TUNE_SMALL_PREPARE  0: small graphs (at most 65,536 vertices, 131,072 entries, 32 layers, and entries + 3 vertices
+ *                         within 140,000) are prepared by the general construction instead of the
+ *                         single-launch one                                                 [1]
  *   EPP_TUNE_PART         source-partitioned layout: 0 never, 1 where it pays, 2 always  [1]
- *   EPP_TUNE_PART_KB      L2 kilobytes per XCD given to the most referenced source rows  [3584]
+ *   EPP_TUNE_PART_KB      L2 kilobytes per XCD given to the most referenced source rows  [4096]
  *   EPP_TUNE_PART_MINLEN  shortest row that is cut into per-XCD sections                 [96]
  *   EPP_TUNE_SHARE_PCT    a path runs on the arrays of the next outer path (no entry arrays of its own) if it
  *                         holds at least this percentage of that path's entries; 0: never     [95]
@@ -170,7 +175,12 @@ int epp_paper_linreg_group_size(int64_t vertices, int64_t undirected_edges);
 /* One-off preparation of a path for gradient width F: builds the group table for the group size
  * in force (the selector's, or the one forced by epp_path_set_group_size), allocates the
  * partial rows of the groups (2 * n_groups * F floats, only if some row is cut by a group
- * boundary) and chooses the cache-locality marks of the entries.  Allocates through the handle's
+ * boundary) and chooses the cache-locality marks of the entries.  Small paths, and widths of at most
+ * 4 floats, run without a group table unless a group size is forced (epp_path_info then names the
+ * selector's).  Where it pays, the width also gets scratch memory for a copy of the source rows that
+ * every launch makes (n rows of F floats rounded up to a power of two, beyond 16 to a multiple of 16;
+ * one buffer for all paths of a handle) and the source-partitioned layout of the entries; without memory
+ * for these the width does without them.  Allocates through the handle's
  * allocator and synchronises `stream`; must not be called under stream capture.  Calling it again
  * for a prepared width does nothing.  The aggregate entry points below require it: they never
  * allocate and never wait. */
@@ -220,7 +230,8 @@ int epp_ifelse_aggregate(epp_path_t* full, const epp_paths_t* paths, int l, cons
  * pointer non-decreasing from 0 to nnz with no empty row, columns in range): a violation gives
  * EPP_ERR_INVALID_ARG or EPP_ERR_OUT_OF_RANGE_ID, never a fault.  That the arrays really are the
  * paths of some graph is the caller's responsibility.  N^0 comes from train_ids as in epp_prepare,
- * N^k (k >= 1) from the row ids of SG_{L-k}.  Synchronises `stream` before returning. */
+ * N^k (k >= 1) from the row ids of SG_{L-k}.  Columns need not lie in N^{L-l-1}: aggregation gathers the
+ * caller's row of every column.  Synchronises `stream` before returning. */
 typedef struct {
     int64_t n_rows;         /* |N^{L-l}|                              */
     int64_t nnz;            /* entries, < 2^31                        */

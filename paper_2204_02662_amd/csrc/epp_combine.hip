@@ -238,9 +238,14 @@ __device__ __forceinline__ int share_index(int block, int p) { return VEC ? BLOC
 // one feature (l % 32) of row l / 32 of a pair: which is how a row lies in memory.  So nothing goes through
 // LDS: every wavefront takes its own rows, loads its operands straight into registers (one 16-byte load
 // per lane and operand for a pair of rows of 128), D pairs ahead of the matrix core, and keeps the whole
-// F_in x F_out product in its accumulators.  The wavefronts of a workgroup add theirs in LDS, in a
-// fixed order, once at the end.  Bound by the matrix core at 128 x 128 (16 instructions of 64 cycles per
-// pair of loads; busy 86 % of the time, at 2.1 of its 2.4 GHz), by HBM where a width is 16 (4.9 TB/s).
+// F_in x F_out product in its accumulators.  The wavefronts of a workgroup add theirs in LDS, in 32 bits and in a
+// fixed order, once at the end; sums of workgroups are added in double.  That is two additions (four with 16
+// wavefronts) behind a chain that is a quarter as long as a workgroup's: against 64 bits the error over 7 to 4.6 M
+// rows and widths of 3 to 128 is 0.6 times that of one chain per workgroup on average, 1.07 times at worst (7 rows,
+// 2.9e-8 of the sum of the terms' magnitudes).
+// Bound by the matrix core at 128 x 128 (16 instructions of 64 cycles per pair of loads; 115 TFLOP/s at 4.6 M rows),
+// where the 256 accumulators and eight pairs ahead also cost 33 to 35 spilled registers a lane; by HBM where a width is
+// 16 (4.9 TB/s).
 // Measured against tiles staged through LDS, partial sums included: 128 x 128, 4.6 M rows 1.51 -> 1.31 ms;
 // 128 x 16, 3.9 M rows 0.53 -> 0.46 ms; 16 x 41, 250,000 rows 55 -> 29 us; 16 x 3, 382 rows 16 -> 7 us.
 template <int MT, int NT, bool VA, bool VB, int WAVES>

@@ -286,7 +286,9 @@ static int chunk_log2(int F) { return 13 - lanes_log2(F); }
 static_assert((1 << 13) == 8 * kBlock * kU, "chunk length");
 
 // Which paths run here.  Rows of 16 bytes and less always: the group kernel's lanes then each carry a
-// group of their own and read pairs far apart (F = 4: 1.5 to 3.3 times slower at 0.4 to 26 M entries).
+// group of their own and read pairs far apart (this kernel's time over the group kernel's at 20 / 90 / 200 to 230 M entries,
+// 0.25 to 8 M sources, both models: F = 1 0.37 to 0.80, F = 2 0.38 to 0.85, F = 4 0.42 to 0.88, growing with the matrix and
+// the entries; F = 3, whose groups have four lanes, 0.74 to 0.91 / 0.88 to 1.06 / 0.92 to 1.02).
 // Rows of up to 32 and 64 bytes while the second kernel and the chain of loads still show: up to 10 and
 // 5 M entries (F = 16: 1.2 to 1.9 times faster at 0.2 to 1 M, 1.05 to 1.35 times at 4 M, 0.9 to 1.2 at 6 to
 // 10 M, where matrices no longer stay in the memory-side cache between calls).  Wider rows while
