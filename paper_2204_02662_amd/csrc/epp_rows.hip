@@ -80,10 +80,10 @@ struct RowArgs {
 // next step are fetched while the rows of this one are on their way.
 //
 // A step that reaches past p1 gathers the last entry again, with weight zero, and one that belongs to the outer
-// path only gathers zeros.  That adds zero, or NaN where the row or the weight holds an infinity: a sum
-// that is not a number is therefore formed again from the slot's own entries alone, in the same order.  (A
-// selection of zeros in every step, or in the last one, costs a path of 7,000 entries 0.2 us of 4.1, this 0.06.)
-template <int VEC, int U, bool INNER>
+// path only gathers zeros.  That adds zero, or NaN where the row or the weight holds an infinity.  EXACT clears both
+// factors in the last step, which costs a path of 7,000 entries 0.2 us of 4.1; without it the caller looks at
+// the sums, and forms those that are not numbers again from the slot's own entries alone (add_own_entries).
+template <int VEC, int U, bool INNER, bool EXACT>
 __device__ __forceinline__ void add_entries(const RowArgs& a, const float* __restrict__ src, int j0, int p1, int step,
                                             float (&acc)[VEC]) {
 #pragma unroll
@@ -101,10 +101,19 @@ __device__ __forceinline__ void add_entries(const RowArgs& a, const float* __res
             if constexpr (INNER) p = (e[u].x & kEntOuterOnly) ? a.zero : p;
             load_frag<VEC>(p, x[u]);
             w[u] = j + u < p1 ? __int_as_float(e[u].y) : 0.0f;
+            if constexpr (INNER && EXACT) w[u] = (e[u].x & kEntOuterOnly) ? 0.0f : w[u];
         }
         if (j + step < p1) {
 #pragma unroll
             for (int u = 0; u < U; ++u) e[u] = a.cv[min(j + step + u, p1 - 1)];
+        }
+        if (EXACT && j + U > p1) {
+            asm volatile("");  // (keeps the branch)
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+#pragma unroll
+                for (int i = 0; i < VEC; ++i) x[u][i] = j + u < p1 ? x[u][i] : 0.0f;
+            }
         }
 #pragma unroll
         for (int u = 0; u < U; ++u) {
@@ -112,10 +121,11 @@ __device__ __forceinline__ void add_entries(const RowArgs& a, const float* __res
             for (int i = 0; i < VEC; ++i) acc[i] = fmaf(w[u], x[u][i], acc[i]);
         }
     }
-    bool bad = false;
-#pragma unroll
-    for (int i = 0; i < VEC; i += 2) bad |= (bool)__builtin_isunordered(acc[i], acc[i + 1 < VEC ? i + 1 : i]);
-    if (__builtin_expect(!bad, 1)) return;
+}
+
+template <int VEC, int U, bool INNER>
+__device__ __forceinline__ void add_own_entries(const RowArgs& a, const float* __restrict__ src, int j0, int p1, int step,
+                                                float (&acc)[VEC]) {
 #pragma unroll
     for (int i = 0; i < VEC; ++i) acc[i] = 0.0f;
     for (int j = j0; j < p1; j += step) {
@@ -132,6 +142,14 @@ __device__ __forceinline__ void add_entries(const RowArgs& a, const float* __res
     }
 }
 
+template <int VEC>
+__device__ __forceinline__ bool not_numbers(const float (&acc)[VEC]) {
+    bool bad = false;
+#pragma unroll
+    for (int i = 0; i < VEC; i += 2) bad |= (bool)__builtin_isunordered(acc[i], acc[i + 1 < VEC ? i + 1 : i]);
+    return bad;
+}
+
 // o[f ..] of the calling thread's lanes = sum of the entries [q0, q1), by the whole workgroup.
 template <int VEC, int LOG2T, bool INNER>
 __device__ __forceinline__ void sum_by_workgroup(const RowArgs& a, int q0, int q1, float* __restrict__ o,
@@ -142,7 +160,7 @@ __device__ __forceinline__ void sum_by_workgroup(const RowArgs& a, int q0, int q
         const bool fok = f0 + t * VEC < a.F;
         const int f = fok ? min(f0 + t * VEC, a.F - VEC) : 0;
         float acc[VEC];
-        add_entries<VEC, kU, INNER>(a, a.in + f, q0 + slot * kU, q1, (kBlock >> LOG2T) * kU, acc);
+        add_entries<VEC, kU, INNER, true>(a, a.in + f, q0 + slot * kU, q1, (kBlock >> LOG2T) * kU, acc);
 #pragma unroll
         for (int d = T; d < 64; d <<= 1) {
 #pragma unroll
@@ -193,16 +211,39 @@ __global__ __launch_bounds__(kBlock, 7) void k_aggregate_rows(RowArgs a) {
         __syncthreads();
         if (is_long && p1 - p0 <= a.huge && t == 0 && sub == 0) list[atomicAdd(&count, 1)] = r;
     }
+    bool bad = false;
     for (int f0 = 0; f0 < a.F; f0 += T * VEC) {
         const bool fok = f0 + t * VEC < a.F;
         const int f = fok ? min(f0 + t * VEC, a.F - VEC) : 0;
         float acc[VEC];
-        add_entries<VEC, kU, INNER>(a, a.in + f, p0 + sub * kU, is_long ? p0 : p1, P * kU, acc);
+        add_entries<VEC, kU, INNER, false>(a, a.in + f, p0 + sub * kU, is_long ? p0 : p1, P * kU, acc);
         for (int d = T; d < T * P; d <<= 1) {
 #pragma unroll
             for (int i = 0; i < VEC; ++i) acc[i] += __shfl_xor(acc[i], d, 64);
         }
+        bad |= not_numbers<VEC>(acc);  // (the same in all slots of the row)
         if (write && fok) store_frag<VEC>(a.out + (size_t)v * a.F + f, acc);
+    }
+    if (__builtin_expect(bad, 0)) {
+        // (a second look at everything, so that nothing of it is kept in registers through the loop above)
+        unsigned thread = threadIdx.x;
+        asm volatile("" : "+v"(thread));
+        const int ot = thread & (T - 1), os = thread >> LOG2T, osub = os & (P - 1);
+        const int orow = ((int)blockIdx.x - a.chunk_blocks) * (kBlock >> (LOG2T + a.log2p)) + (os >> a.log2p);
+        const int begin = a.rowptr[orow], end = a.rowptr[orow + 1], ov = a.row_ids ? a.row_ids[orow] : orow;
+        bool owrite = osub == 0;
+        if constexpr (INNER) owrite = owrite && ((a.only[ov >> 5] >> (ov & 31)) & 1u);
+        for (int f0 = 0; f0 < a.F; f0 += T * VEC) {
+            const bool fok = f0 + ot * VEC < a.F;
+            const int f = fok ? min(f0 + ot * VEC, a.F - VEC) : 0;
+            float acc[VEC];
+            add_own_entries<VEC, kU, INNER>(a, a.in + f, begin + osub * kU, end, P * kU, acc);
+            for (int d = T; d < T * P; d <<= 1) {
+#pragma unroll
+                for (int i = 0; i < VEC; ++i) acc[i] += __shfl_xor(acc[i], d, 64);
+            }
+            if (owrite && fok) store_frag<VEC>(a.out + (size_t)ov * a.F + f, acc);
+        }
     }
     if (!a.has_long) return;
     __syncthreads();
