@@ -31,7 +31,6 @@ constexpr int kBlock = 256;
 constexpr int kStep = 32;   // contraction step
 constexpr int kMaxWidth = 4096;
 constexpr int kMinChunkRows = 256;
-constexpr int kOneWorkgroup = 1024;  // rows that one workgroup takes alone
 constexpr int64_t kNoChunkLimit = (int64_t)1 << 40;
 
 typedef float float4v __attribute__((ext_vector_type(4)));
@@ -238,27 +237,28 @@ __device__ __forceinline__ int share_index(int block, int p) { return VEC ? BLOC
 // one feature (l % 32) of row l / 32 of a pair: which is how a row lies in memory.  So nothing goes through
 // LDS: every wavefront takes its own rows, loads its operands straight into registers (one 16-byte load
 // per lane and operand for a pair of rows of 128), D pairs ahead of the matrix core, and keeps the whole
-// F_in x F_out product in its accumulators.  The wavefronts of a workgroup add theirs in LDS, in 32 bits and in a
-// fixed order, once at the end; sums of workgroups are added in double.  That is two additions (four with 16
-// wavefronts) behind a chain that is a quarter as long as a workgroup's: against 64 bits the error over 7 to 4.6 M
-// rows and widths of 3 to 128 is 0.6 times that of one chain per workgroup on average, 1.07 times at worst (7 rows,
-// 2.9e-8 of the sum of the terms' magnitudes).
+// F_in x F_out product in its accumulators.  The wavefronts of a workgroup add theirs through LDS, in 32 bits, in pairs
+// and in a fixed order, once at the end; sums of workgroups are added in double.  That is two additions behind a chain
+// that is a quarter as long as a workgroup's: against 64 bits the error over 7 to 4.6 M rows and widths of 3 to 128 is
+// half that of one chain per workgroup on average, and nowhere larger.
 // Bound by the matrix core at 128 x 128 (16 instructions of 64 cycles per pair of loads; 115 TFLOP/s at 4.6 M rows),
-// where the 256 accumulators and eight pairs ahead also cost 33 to 35 spilled registers a lane; by HBM where a width is
+// where the 256 accumulators and eight pairs ahead also cost 17 to 21 spilled registers a lane; by HBM where a width is
 // 16 (4.9 TB/s).
 // Measured against tiles staged through LDS, partial sums included: 128 x 128, 4.6 M rows 1.51 -> 1.31 ms;
-// 128 x 16, 3.9 M rows 0.53 -> 0.46 ms; 16 x 41, 250,000 rows 55 -> 29 us; 16 x 3, 382 rows 16 -> 7 us.
-template <int MT, int NT, bool VA, bool VB, int WAVES>
-__global__ __launch_bounds__(64 * WAVES, MT * NT >= 16 ? 1 : (WAVES > 4 ? WAVES / 4 : 2)) void k_weight_gradient_rows(
+// 128 x 16, 3.9 M rows 0.53 -> 0.46 ms; 16 x 41, 250,000 rows 55 -> 29 us; 16 x 3, 400 rows 14.1 -> 6.4 us;
+// 96 x 96, 869 / 30,000 / 100,000 rows 26 -> 14.6 / 33 -> 29 / 53 -> 59 us.
+template <int MT, int NT, bool VA, bool VB>
+__global__ __launch_bounds__(kBlock, MT * NT >= 16 ? 1 : 2) void k_weight_gradient_rows(
     const int32_t* __restrict__ ids, int64_t n_rows, int64_t rows_per_wave, const float* __restrict__ Y, int Fi,
     const float* __restrict__ G, int Fo, float* __restrict__ out) {
-    // pairs of rows in flight (fewer where the registers would not hold them)
-    constexpr int D = WAVES > 4 && MT * NT >= 4 ? 4 : 8;
-    __shared__ float sums[WAVES / 2][MT * NT * 16 * 64];
+    constexpr int D = 8, WAVES = kBlock / 64;  // pairs of rows in flight, wavefronts
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, p = lane & 31, half = lane >> 5;
     const int64_t first = ((int64_t)blockIdx.x * WAVES + wave) * rows_per_wave;
     const int64_t last = std::min<int64_t>(first + rows_per_wave, n_rows);
-    floatx16 acc[MT][NT] = {};
+    // (one block leaves room for four sums, of every fourth pair each: as many chains as 16 wavefronts would have)
+    constexpr int CHAINS = MT * NT == 1 ? 4 : 1;
+    floatx16 chain[CHAINS][MT][NT] = {};
+    auto& acc = chain[0];
     // lane i (of the first 2 D) holds the vertex of row r + i; rows past the end repeat the last one
     // (without `ids` the load is of something else and not used: a branch around it would make every
     // step wait for all loads)
@@ -306,47 +306,79 @@ __global__ __launch_bounds__(64 * WAVES, MT * NT >= 16 ? 1 : (WAVES > 4 ? WAVES 
                 for (int i = 0; i < MT; ++i)
 #pragma unroll
                     for (int j = 0; j < NT; ++j)
-                        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[d][i], b[d][j], acc[i][j], 0, 0, 0);
+                        chain[d % CHAINS][i][j] =
+                            __builtin_amdgcn_mfma_f32_32x32x2f32(a[d][i], b[d][j], chain[d % CHAINS][i][j], 0, 0, 0);
                 fetch(d, next);
                 __builtin_amdgcn_sched_barrier(0);  // (left alone, all products come first and all fetches last)
             }
         }
     }
-    // the upper half of the wavefronts hands its sums to the lower half, until one is left
+    if constexpr (CHAINS == 4) acc[0][0] = (acc[0][0] + chain[1][0][0]) + (chain[2][0][0] + chain[3][0][0]);
+    // Each wavefront adds and writes its share of the blocks: wavefront o those numbered o kShare .. (o + 1) kShare - 1, row by row;
+    // the others hand theirs over through LDS, kPass blocks of every owner at a time.  (Handed on from one half of the
+    // wavefronts to the other until one has them all, and written by that one, 128 x 128 took 20 us more.)
+    static_assert(WAVES == 4, "added in pairs");
+    constexpr int B = MT * NT, kOwners = B < WAVES ? B : WAVES, kShare = B / kOwners, kPass = kShare > 2 ? 2 : 1;
+    __shared__ float4v sums[kOwners * kPass * (WAVES - 1)][4 * 64];
+    const int w = __builtin_amdgcn_readfirstlane(wave);
 #pragma unroll
-    for (int left = WAVES / 2; left >= 1; left /= 2) {
-        if (wave >= left && wave < 2 * left) {
+    for (int h = 0; h < kShare; h += kPass) {
+        if (h > 0) __syncthreads();  // `sums` is written again
 #pragma unroll
-            for (int i = 0; i < MT; ++i)
+        for (int o = 0; o < kOwners; ++o) {
+            if (w == o) continue;
 #pragma unroll
-                for (int j = 0; j < NT; ++j)
+            for (int g = 0; g < kPass; ++g) {
+                const floatx16& x = acc[(o * kShare + h + g) / NT][(o * kShare + h + g) % NT];
+                float4v* __restrict__ to = sums[(o * kPass + g) * (WAVES - 1) + (w < o ? w : w - 1)] + lane;
 #pragma unroll
-                    for (int e = 0; e < 16; ++e) sums[wave - left][((i * NT + j) * 16 + e) * 64 + lane] = acc[i][j][e];
-        }
-        __syncthreads();
-        if (wave < left) {
-#pragma unroll
-            for (int i = 0; i < MT; ++i)
-#pragma unroll
-                for (int j = 0; j < NT; ++j)
-#pragma unroll
-                    for (int e = 0; e < 16; ++e) acc[i][j][e] += sums[wave][((i * NT + j) * 16 + e) * 64 + lane];
-        }
-        __syncthreads();
-    }
-    if (wave != 0) return;
-    float* __restrict__ mine = out + (int64_t)blockIdx.x * Fi * Fo;
-#pragma unroll
-    for (int i = 0; i < MT; ++i)
-#pragma unroll
-        for (int j = 0; j < NT; ++j) {
-            const int n = share_index<NT, VB>(j, p);
-#pragma unroll
-            for (int e = 0; e < 16; ++e) {
-                const int m = share_index<MT, VA>(i, 8 * (e / 4) + 4 * half + (e % 4));
-                if (m < Fi && n < Fo) mine[m * Fo + n] = acc[i][j][e];
+                for (int q = 0; q < 4; ++q) to[q * 64] = float4v{x[4 * q], x[4 * q + 1], x[4 * q + 2], x[4 * q + 3]};
             }
         }
+        __syncthreads();
+#pragma unroll
+        for (int o = 0; o < kOwners; ++o) {
+            if (w != o) continue;
+#pragma unroll
+            for (int g = 0; g < kPass; ++g) {
+                floatx16& x = acc[(o * kShare + h + g) / NT][(o * kShare + h + g) % NT];
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const float4v* __restrict__ from = sums[(o * kPass + g) * (WAVES - 1)] + q * 64 + lane;
+                    const float4v y0 = from[0], y1 = from[4 * 64], y2 = from[2 * 4 * 64];
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) x[4 * q + c] = (x[4 * q + c] + y0[c]) + (y1[c] + y2[c]);
+                }
+            }
+        }
+    }
+    float* __restrict__ mine = out + (int64_t)blockIdx.x * Fi * Fo;
+#pragma unroll
+    for (int o = 0; o < kOwners; ++o) {
+        if (w != o) continue;
+        // (kShare divides NT: blocks of one row)
+        const int i = o * kShare / NT, j0 = o * kShare % NT;
+#pragma unroll
+        for (int e = 0; e < 16; ++e) {
+            const int m = share_index<MT, VA>(i, 8 * (e / 4) + 4 * half + (e % 4));
+            if (m >= Fi) continue;
+            float* __restrict__ row = mine + m * Fo;
+            if constexpr (VB && kShare > 1) {
+                typedef float vec_t __attribute__((ext_vector_type(kShare), aligned(4)));
+                vec_t v;
+#pragma unroll
+                for (int g = 0; g < kShare; ++g) v[g] = acc[i][j0 + g][e];
+                const int n = NT * p + j0;  // (Fo is a multiple of NT)
+                if (n < Fo) *reinterpret_cast<vec_t*>(row + n) = v;
+            } else {
+#pragma unroll
+                for (int g = 0; g < kShare; ++g) {
+                    const int n = share_index<NT, VB>(j0 + g, p);
+                    if (n < Fo) row[n] = acc[i][j0 + g][e];
+                }
+            }
+        }
+    }
 }
 
 // Y'[id, n] = sum_k X'[id, k] W[n, k], widths of at most 128 (F_out = k) and 32 NT (F_in = n).
@@ -358,7 +390,9 @@ __global__ __launch_bounds__(64 * WAVES, MT * NT >= 16 ? 1 : (WAVES > 4 ? WAVES 
 // 16-byte LDS read feeds four instructions, and no barrier is left in the loop.  Bound by the matrix
 // core at 128 x 128 (busy 82 %), by HBM where a width is 16 (4.9 TB/s).
 // Measured against tiles of both operands staged through LDS: 128 x 128, 4.6 M rows 1.61 -> 1.35 ms;
-// 128 x 16, 3.9 M rows 0.55 -> 0.46 ms; 16 x 41, 250,000 rows 27 -> 21 us; 16 x 3, 382 rows 5.4 -> 3.0 us.
+// 128 x 16, 3.9 M rows 0.55 -> 0.46 ms; 16 x 41, 250,000 rows 27 -> 21 us; 16 x 3, 382 rows 5.4 -> 3.0 us;
+// 96 x 96, 869 / 30,000 / 100,000 rows 11.9 -> 11.8 / 14.0 -> 14.0 / 38 -> 38 us (18.0 / 20.1 / 51 with W brought into
+// LDS a float and a row at a time, and 16 chunks for 12).
 template <int KC, int NT>  // KC: chunks of 8 floats of a row
 __global__ __launch_bounds__(kBlock, 2) void k_input_gradient_rows(const int32_t* __restrict__ ids, int64_t n_rows,
                                                                    const float* __restrict__ G, int Fo,
@@ -367,18 +401,43 @@ __global__ __launch_bounds__(kBlock, 2) void k_input_gradient_rows(const int32_t
     __shared__ float4v Ws[KC * 2 * NT * 32];  // [chunk][half][n]: W[n, 8 chunk + 4 half ..]
     __shared__ float4v out_all[kBlock / 64][32 * 8];  // 32 rows x 32 columns of results, private to a wavefront
     const int lane = threadIdx.x & 63, p = lane & 31, half = lane >> 5;
-    for (int i = threadIdx.x; i < KC * 2 * NT * 32; i += kBlock) {
-        const int n = i % (NT * 32), k = (i / (NT * 32)) * 4;
-        float4v w = {0.f, 0.f, 0.f, 0.f};
-        if (n < Fi) {
+    typedef float vec_t __attribute__((ext_vector_type(4), aligned(4)));
+    {   // W: a wavefront takes 16 rows x 16 columns at a time, so that a lane of four reads 64 bytes of a row and 16 of
+        // them write 256 bytes of LDS; all loads before the first write
+        constexpr int kSteps = (KC * NT + kBlock / 64 - 1) / (kBlock / 64);  // of KC NT such pieces
+        float4v w[kSteps];
+        const int top = std::max(Fo - 4, 0);
 #pragma unroll
-            for (int c = 0; c < 4; ++c)
-                if (k + c < Fo) w[c] = W[(int64_t)n * Fo + k + c];
+        for (int i = 0; i < kSteps; ++i) {
+            const int blk = i * (kBlock / 64) + (threadIdx.x >> 6);
+            const int k = 16 * (blk % (KC / 2)) + 4 * (lane & 3), n = 16 * (blk / (KC / 2)) + (lane >> 2);
+            const float* __restrict__ row = W + (int64_t)std::min(n, Fi - 1) * Fo;
+            if (Fo >= 4) {
+                w[i] = *reinterpret_cast<const vec_t*>(row + std::min(k, top));
+            } else {
+#pragma unroll
+                for (int c = 0; c < 4; ++c) w[i][c] = row[std::min(c, Fo - 1)];
+            }
         }
-        Ws[i] = w;
+#pragma unroll
+        for (int i = 0; i < kSteps; ++i) {
+            const int blk = i * (kBlock / 64) + (threadIdx.x >> 6);
+            const int k = 16 * (blk % (KC / 2)) + 4 * (lane & 3), n = 16 * (blk / (KC / 2)) + (lane >> 2);
+            // (the last columns of a row were read together with those before them)
+            const int late = k - std::min(k, top);
+            float4v x;
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                float y = w[i][c];
+                if (c < 3 && late == 1) y = w[i][c + 1];
+                if (c < 2 && late == 2) y = w[i][c + 2];
+                if (c < 1 && late == 3) y = w[i][c + 3];
+                x[c] = n < Fi && k + c < Fo ? y : 0.0f;
+            }
+            if (KC * NT % (kBlock / 64) == 0 || n < 32 * NT) Ws[(k / 4) * (NT * 32) + n] = x;
+        }
     }
     __syncthreads();
-    typedef float vec_t __attribute__((ext_vector_type(4), aligned(4)));
     const int64_t n_tiles = (n_rows + 31) / 32, step = (int64_t)gridDim.x * (kBlock / 64);
     auto vertex = [&](int64_t tile) -> int {
         const int64_t r = std::min<int64_t>(tile * 32 + p, n_rows - 1);
@@ -544,29 +603,40 @@ constexpr int kNarrow = 128;
 bool narrow(int Fi, int Fo) { return Fi <= kNarrow && Fo <= kNarrow; }
 int blocks_of(int F) { return F > 64 ? 4 : (F > 32 ? 2 : 1); }
 
+// Workgroups of k_input_gradient_rows<kc, nt> that a CU holds at once (by its registers; four at most, with which the
+// memory is busy).  More of them than the chip holds would run after the others, each for as long (96 x 39, 400,000
+// rows: 81 us with 1,024 workgroups, 72 with 768).
+int resident(int kc, int nt) {
+    if (kc >= 16) return 2;
+    if (kc == 12) return nt == 1 ? 3 : 2;
+    if (kc == 8) return nt == 4 ? 2 : 3;
+    return nt == 4 ? 3 : 4;
+}
+
 // How the rows are cut into partial sums (at most `max_chunks` of them).
 struct Chunks {
     int64_t per;    // rows per chunk; narrow widths: rows per wavefront
     int64_t count;  // partial sums
-    int waves;      // narrow widths: wavefronts per workgroup (= per partial sum)
 };
 Chunks chunking(int64_t n_rows, int Fi, int Fo, int64_t max_chunks) {
     Chunks c;
     if (narrow(Fi, Fo)) {
         const int tiles = blocks_of(Fi) * blocks_of(Fo);
-        // A few rows: one workgroup of 16 wavefronts, whose sum is the result (as many as its registers
-        // allow: 16 accumulators of 32 x 32 fit one wavefront per SIMD only).
-        if (tiles <= 4 && n_rows <= kOneWorkgroup) {
-            c.waves = 16;
-            c.count = n_rows > 0 ? 1 : 0;
-            c.per = (n_rows + 15) / 16;
-            return c;
+        // Four wavefronts.  Many rows: two rounds of the chip where a wavefront fills its SIMD, else four.  Up to 65,536:
+        // one round, 16 rows per wavefront at least (one batch of fetches), as what a launch takes is then the rows that
+        // follow each other in a wavefront, and what the partial sums cost to write and add (64 rows a wavefront, or
+        // 16 wavefronts for up to 1,024 rows -> this: 869 rows, 64 x 64 24.7 -> 7.5 us, 16 x 16 11.6 -> 6.6, 96 x 96
+        // 40.7 -> 14.6; 30,000 rows, 64 x 64 16.0 -> 15.2, 96 x 96 46 -> 29).  One block: half as many partial sums, until
+        // that is 64 rows a wavefront (32 x 32, 16,000 rows 9.1 -> 8.2 us), and up to 64 rows a single workgroup, which needs
+        // no launch to add them (60 rows 6.4 -> 4.0 us).  Up to four: 256 rows in 16 chains, for the sake of the sums.
+        if (n_rows <= 65536) {
+            const int64_t chains = tiles == 1 && n_rows <= 64 ? 4 : tiles <= 4 && n_rows <= 256 ? 16 : tiles == 1 ? 512 : 1024;
+            c.per = std::max<int64_t>((n_rows + chains - 1) / chains, chains <= 16 ? 2 : 16);
+            if (tiles == 1) c.per = std::min<int64_t>(c.per, 64);  // (256 partial sums at most, whatever the widths)
+        } else {
+            const int64_t want = std::min<int64_t>(tiles >= 8 ? 512 : 1024, std::max<int64_t>(max_chunks, 1));
+            c.per = std::max<int64_t>((n_rows + 4 * want - 1) / (4 * want), 64);
         }
-        // Four wavefronts: two rounds of the chip where a wavefront fills its SIMD, else four; 64 rows
-        // per wavefront at least.
-        c.waves = 4;
-        const int64_t want = std::min<int64_t>(tiles >= 8 ? 512 : 1024, std::max<int64_t>(max_chunks, 1));
-        c.per = std::max<int64_t>((n_rows + 4 * want - 1) / (4 * want), 64);
         c.per = (c.per + 1) / 2 * 2;
         c.count = (n_rows + 4 * c.per - 1) / (4 * c.per);
         return c;
@@ -576,7 +646,6 @@ Chunks chunking(int64_t n_rows, int Fi, int Fo, int64_t max_chunks) {
     tile_dims(tile_shape(Fi, Fo), &tm, &tn);
     const int64_t tiles = (int64_t)((Fi + tm - 1) / tm) * ((Fo + tn - 1) / tn);
     const int64_t want = std::min(std::max<int64_t>(1, 2048 / tiles), std::max<int64_t>(max_chunks, 1));
-    c.waves = 4;
     c.per = std::max<int64_t>((n_rows + want - 1) / want, kMinChunkRows);
     c.per = (c.per + kStep - 1) / kStep * kStep;
     c.count = (n_rows + c.per - 1) / c.per;
@@ -586,14 +655,7 @@ Chunks chunking(int64_t n_rows, int Fi, int Fo, int64_t max_chunks) {
 template <int MT, int NT, bool VA, bool VB>
 void launch_rows_wg(const Chunks& c, const int32_t* ids, int64_t n_rows, const float* Y, int Fi, const float* G, int Fo,
                     float* out, hipStream_t s) {
-    if constexpr (MT * NT <= 4) {
-        if (c.waves == 16) {
-            hipLaunchKernelGGL((k_weight_gradient_rows<MT, NT, VA, VB, 16>), dim3((unsigned)c.count), dim3(1024), 0, s, ids,
-                               n_rows, c.per, Y, Fi, G, Fo, out);
-            return;
-        }
-    }
-    hipLaunchKernelGGL((k_weight_gradient_rows<MT, NT, VA, VB, 4>), dim3((unsigned)c.count), dim3(256), 0, s, ids, n_rows,
+    hipLaunchKernelGGL((k_weight_gradient_rows<MT, NT, VA, VB>), dim3((unsigned)c.count), dim3(256), 0, s, ids, n_rows,
                        c.per, Y, Fi, G, Fo, out);
 }
 template <int MT, bool VA>
@@ -750,13 +812,18 @@ extern "C" int epp_input_gradient(epp_paths_t* paths, int k, const float* grad_X
     int64_t n_rows = 0;
     EPP_TRY(row_set(paths, k, &ids, &n_rows));
     if (n_rows == 0) return EPP_OK;
-    if (narrow(F_in, F_out)) {
+    const int kc = (F_out + 7) / 8, nt = blocks_of(F_in);
+    // (many rows of more than 48 floats onto one block of columns are left to the operand tiles: 16 x 64, 100,000 /
+    // 400,000 / 2 M rows 10.0 / 28 / 123 us against 11.9 / 32 / 169, 32 x 128, 60,000 rows 11.1 against 13.0; not so 16 x 41,
+    // 250,000 rows 27 against 21, nor 16 x 64, 30,000 rows 5.5 against 5.2)
+    if (narrow(F_in, F_out) && !(nt == 1 && F_out > 48 && n_rows >= 50000)) {
         // persistent workgroups, as many as the chip holds at once
         const int64_t tiles = (n_rows + 31) / 32;
-        const int kc = (F_out + 7) / 8, nt = blocks_of(F_in);
-        const dim3 grid((unsigned)std::min<int64_t>((tiles + 3) / 4, kc > 8 ? 512 : 1024));
+        dim3 grid;
+        auto blocks = [&](int at_once) { grid = dim3((unsigned)std::min<int64_t>((tiles + 3) / 4, at_once)); };
 #define EPP_LAUNCH_IGR(KC)                                                                                           \
     do {                                                                                                             \
+        blocks(256 * resident(KC, nt));                                                                              \
         if (nt == 1)                                                                                                 \
             hipLaunchKernelGGL((k_input_gradient_rows<KC, 1>), grid, dim3(kBlock), 0, s, ids, n_rows, grad_X, F_out, \
                                W, F_in, grad_Y);                                                                     \
@@ -771,6 +838,7 @@ extern "C" int epp_input_gradient(epp_paths_t* paths, int k, const float* grad_X
         else if (kc <= 4) EPP_LAUNCH_IGR(4);
         else if (kc <= 6) EPP_LAUNCH_IGR(6);
         else if (kc <= 8) EPP_LAUNCH_IGR(8);
+        else if (kc <= 12) EPP_LAUNCH_IGR(12);
         else EPP_LAUNCH_IGR(16);
 #undef EPP_LAUNCH_IGR
         EPP_HIP_TRY(hipGetLastError());

@@ -44,7 +44,7 @@ def test_scratch_memory(usage):
         for name, (scratch, _) in kernels.items():
             limit = 0
             if "k_weight_gradient_rowsILi4ELi4E" in name:
-                limit = 140  # 128 x 128: the product's 256 accumulators and eight pairs of rows ahead leave no room
+                limit = 84   # 128 x 128: the product's 256 accumulators and eight pairs of rows ahead leave no room
             elif "k_prepare_smallILb0E" in name:
                 limit = 132  # one workgroup, launched once per graph
             elif "k_prepare_smallILb1E" in name:
@@ -56,3 +56,16 @@ def test_wavefronts_of_the_row_kernel(usage):
     rows = {n: o for n, (_, o) in usage["epp_rows"].items() if "k_aggregate_rows" in n}
     assert len(rows) == 20  # ten shapes of a source row, with and without an inner path
     assert min(rows.values()) >= 8, rows
+
+
+def test_input_gradient_workgroups_at_once(usage):
+    """The launch starts as many workgroups as the chip holds at once, by this table (epp_combine.hip: resident)."""
+    at_once = {(2, 1): 4, (2, 2): 4, (2, 4): 3, (4, 1): 4, (4, 2): 4, (4, 4): 3, (6, 1): 4, (6, 2): 4, (6, 4): 3, (8, 1): 3,
+               (8, 2): 3, (8, 4): 2, (12, 1): 3, (12, 2): 2, (12, 4): 2, (16, 1): 2, (16, 2): 2, (16, 4): 2}
+    found = {}
+    for name, (_, waves) in usage["epp_combine"].items():
+        if m := re.search(r"k_input_gradient_rowsILi(\d+)ELi(\d)E", name):
+            found[int(m.group(1)), int(m.group(2))] = waves
+    assert set(found) == set(at_once)
+    for shape, n in at_once.items():
+        assert found[shape] >= n, (shape, found[shape])
