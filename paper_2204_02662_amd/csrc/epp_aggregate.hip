@@ -773,15 +773,20 @@ static double lines_per_row(int F, int ld) {
 // launch to a stride that keeps them apart from the lines' ends (a power of two, beyond 16 floats a multiple of 16).
 // It pays where
 //     entries * (cost of a plain row's gather - cost of a packed one's)
-// exceeds the copy (its bytes at 4 TB/s, a workgroup per 64 vertices, a launch).  What a gathered line costs depends
+// exceeds the copy (its bytes at 4 TB/s, a workgroup per 64 vertices, a launch; 13 ps for every vertex that is no source: 6.5
+// for the scan, the rest for rows that lie apart) and, where F is no multiple of four, 10 ps for each row's end, which
+// has four times fewer lanes to write it.  What a gathered line costs depends
 // on where its matrix lives, and the packed one is up to 1.9 times as large: 6.5 ps where it fits an L2, rising by
 // 1.85 ps with every doubling to 15.75 ps at 128 MB and beyond (measured at 0.25 to 8 M sources, 20 to 230 M entries, both
 // graph models, all-active: 6.6 / 10.1 / 13.3 / 14.9 / 17.3 ps at 5 / 13 / 31 / 52 / 176 MB for Chung-Lu, 2 to 4 ps less
 // for R-MAT).  16 bytes a lane with 8 gathers in flight cannot go below 11.6 ps a row, nor 12.6 with two lanes a row:
 // rows of 5 to 8 floats that the caches hold are better read 4 or 8 bytes a lane (F = 5, 84 M entries of 250 K
 // sources: 653 us plain, 907 packed; F = 7, 227 M of 4 M: 4765, 4445).
-// Over 735 graphs and widths (F = 5 to 100, 2 to 230 M entries, 60 K to 8 M sources) the choice costs 0.3 % on average
-// against the better of the two, 18 % at worst (68 against 81 us).
+// Over 735 all-active graphs and widths (F = 5 to 100, 2 to 230 M entries, 60 K to 8 M sources) the choice costs 0.4 % on
+// average against the better of the two, 18 % at worst (68 against 81 us); over 368 paths of 1 to 60 % of the vertices
+// (0.4 to 170 M entries) 0.9 % and 20 %, and 12 % at worst against not packing.  There, R-MAT's few sources are half in
+// the caches, which only counting would tell (8.4 M vertices, 335,544 sources, F = 31: 246 us plain, 348 packed; Chung-Lu,
+// 2.4 M and 195,922, F = 28: 350, 269).
 int epp_packed_stride(const epp_path* p, int F) {
     const int mode = env_int("EPP_TUNE_PACK", 1);  // 0: never, 1: where it pays, 2: always (tests)
     if (mode == 0 || F < 5 || F > (1 << 13) || p->nnz == 0) return F;
@@ -795,8 +800,9 @@ int epp_packed_stride(const epp_path* p, int F) {
     };
     const double plain = lines_per_row(F, F) * line_cost(F);
     const double packed = std::max(lines_per_row(F, ld) * line_cost(ld), 11.6e-12) + (ld == 8 ? 1e-12 : 0.0);
-    const double copy = 8e-6 + 3e-12 * (double)p->n + 4.0 * rows * (F + ld) / 4e12;
-    return (double)p->nnz * (plain - packed) > copy ? ld : F;
+    const double copy = 8e-6 + 3e-12 * rows + 13e-12 * ((double)p->n - rows) + 4.0 * rows * (F + ld) / 4e12;
+    const double ends = F % 4 ? 10e-12 * (double)p->n_stream_rows : 0.0;
+    return (double)p->nnz * (plain - packed) > copy + ends ? ld : F;
 }
 
 int epp_build_schedule_over(const epp_path* p, const int32_t* rowptr, int64_t n_rows, int64_t nnz, int gs,
