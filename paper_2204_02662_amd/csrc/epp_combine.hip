@@ -241,9 +241,9 @@ __device__ __forceinline__ int share_index(int block, int p) { return VEC ? BLOC
 // and in a fixed order, once at the end; sums of workgroups are added in double.  That is two additions behind a chain
 // that is a quarter as long as a workgroup's: against 64 bits the error over 7 to 4.6 M rows and widths of 3 to 128 is
 // half that of one chain per workgroup on average, and nowhere larger.
-// Bound by the matrix core at 128 x 128 (16 instructions of 64 cycles per pair of loads; 115 TFLOP/s at 4.6 M rows),
-// where the 256 accumulators and eight pairs ahead also cost 17 to 21 spilled registers a lane; by HBM where a width is
-// 16 (4.9 TB/s).
+// Bound by the matrix core at 128 x 128 (16 instructions of 64 cycles per pair of loads, busy 83 % of the cycles;
+// 113 TFLOP/s at 4.6 M rows), where the 256 accumulators and eight pairs ahead also cost 17 to 21 spilled registers a
+// lane; by HBM where a width is 16 (4.9 TB/s).
 // Measured against tiles staged through LDS, partial sums included: 128 x 128, 4.6 M rows 1.51 -> 1.31 ms;
 // 128 x 16, 3.9 M rows 0.53 -> 0.46 ms; 16 x 41, 250,000 rows 55 -> 29 us; 16 x 3, 400 rows 14.1 -> 6.4 us;
 // 96 x 96, 869 / 30,000 / 100,000 rows 26 -> 14.6 / 33 -> 29 / 53 -> 59 us.
@@ -314,9 +314,9 @@ __global__ __launch_bounds__(kBlock, MT * NT >= 16 ? 1 : 2) void k_weight_gradie
         }
     }
     if constexpr (CHAINS == 4) acc[0][0] = (acc[0][0] + chain[1][0][0]) + (chain[2][0][0] + chain[3][0][0]);
-    // Each wavefront adds and writes its share of the blocks: wavefront o those numbered o kShare .. (o + 1) kShare - 1, row by row;
-    // the others hand theirs over through LDS, kPass blocks of every owner at a time.  (Handed on from one half of the
-    // wavefronts to the other until one has them all, and written by that one, 128 x 128 took 20 us more.)
+    // Each wavefront adds and writes its share of the blocks: wavefront o those numbered o kShare .. (o + 1) kShare - 1, row
+    // by row; the others hand theirs over through LDS, kPass blocks of every owner at a time.  (Handed on from one half of
+    // the wavefronts to the other until one has them all, and written by that one, 128 x 128 took 20 us more.)
     static_assert(WAVES == 4, "added in pairs");
     constexpr int B = MT * NT, kOwners = B < WAVES ? B : WAVES, kShare = B / kOwners, kPass = kShare > 2 ? 2 : 1;
     __shared__ float4v sums[kOwners * kPass * (WAVES - 1)][4 * 64];
@@ -388,7 +388,7 @@ __global__ __launch_bounds__(kBlock, MT * NT >= 16 ? 1 : 2) void k_weight_gradie
 // its own row l % 32, four floats at a time (lanes l and l + 32 alternate: the contraction's order is free as
 // long as both operands follow it), the next 32 rows while the matrix core works on these.  One
 // 16-byte LDS read feeds four instructions, and no barrier is left in the loop.  Bound by the matrix
-// core at 128 x 128 (busy 82 %), by HBM where a width is 16 (4.9 TB/s).
+// core at 128 x 128 (busy 78 % of the cycles), by HBM where a width is 16 (4.9 TB/s).
 // Measured against tiles of both operands staged through LDS: 128 x 128, 4.6 M rows 1.61 -> 1.35 ms;
 // 128 x 16, 3.9 M rows 0.55 -> 0.46 ms; 16 x 41, 250,000 rows 27 -> 21 us; 16 x 3, 382 rows 5.4 -> 3.0 us;
 // 96 x 96, 869 / 30,000 / 100,000 rows 11.9 -> 11.8 / 14.0 -> 14.0 / 38 -> 38 us (18.0 / 20.1 / 51 with W brought into
