@@ -375,14 +375,14 @@ def l2model_study(args):
         return lru_hit_rate_irm(c, rows) * float(c.sum() / nnz)
 
     row_bytes = 4 * args.F
-    unstreamed = cnt[:(96 << 20) // row_bytes]
+    unstreamed = cnt[:(80 << 20) // row_bytes]
     for slices in (1, 2):
         rows = (4 << 20) * slices // row_bytes
         print(json.dumps({"config": args.config, "F": args.F, "xcd_feature_slices": slices, "rows_one_l2_holds": rows,
                           "share_of_references_to_that_many_top_rows": float(cnt[:rows].sum() / nnz),
                           "lru_hit_rate_all_sources_compete": lru_hit_rate(cnt, rows),
                           "lru_hit_rate_only_unstreamed_sources_compete": lru_hit_rate(unstreamed, rows)}), flush=True)
-    part_rows = 8 * (3584 << 10) // row_bytes
+    part_rows = 8 * (4 << 20) // row_bytes
     print(json.dumps({"config": args.config, "F": args.F, "rows_eight_l2s_hold_together": part_rows,
                       "share_of_references_to_that_many_top_rows": float(cnt[:part_rows].sum() / nnz)}), flush=True)
 
