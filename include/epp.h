@@ -103,7 +103,8 @@ typedef struct {
     int64_t n_groups;       /* ceil(nnz / gs)                                               */
     int64_t n_split_rows;   /* rows cut by a group boundary (summed from per-group pieces)  */
     /* source-partitioned layout of that width (all 0 if it is not in use): the entries of long rows
-       whose source is among the most referenced ones are kept in one section per XCD */
+       whose source is among the most referenced ones are kept in one section per XCD.  Where launches
+       of the width run on tiles of rows: the rows that are cut into parts, 0, and those parts */
     int64_t part_rows;          /* rows cut into per-section shares                          */
     int64_t part_hot_entries;   /* entries in the eight XCD sections                         */
     int64_t part_partial_rows;  /* partial rows of F floats written and added up per launch  */

@@ -762,7 +762,7 @@ int epp_default_group_size(const epp_path* p, int F) {
 }
 
 // 128-byte lines that a row of F floats touches on average where the rows are `ld` floats apart.
-static double lines_per_row(int F, int ld) {
+double epp_lines_per_row(int F, int ld) {
     int64_t lines = 0;
     for (int64_t r = 0; r < 32; ++r) lines += (r * ld + F - 1) / 32 - r * ld / 32 + 1;  // (32 rows: the pattern repeats)
     return (double)lines / 32;
@@ -798,8 +798,8 @@ int epp_packed_stride(const epp_path* p, int F) {
         const double doublings = std::log2(std::max(4.0 * rows * stride, 1.0) / 4e6);
         return 6.5e-12 + 1.85e-12 * std::min(std::max(doublings, 0.0), 5.0);
     };
-    const double plain = lines_per_row(F, F) * line_cost(F);
-    const double packed = std::max(lines_per_row(F, ld) * line_cost(ld), 11.6e-12) + (ld == 8 ? 1e-12 : 0.0);
+    const double plain = epp_lines_per_row(F, F) * line_cost(F);
+    const double packed = std::max(epp_lines_per_row(F, ld) * line_cost(ld), 11.6e-12) + (ld == 8 ? 1e-12 : 0.0);
     const double copy = 8e-6 + 3e-12 * rows + 13e-12 * ((double)p->n - rows) + 4.0 * rows * (F + ld) / 4e12;
     const double ends = F % 4 ? 10e-12 * (double)p->n_stream_rows : 0.0;
     return (double)p->nnz * (plain - packed) > copy + ends ? ld : F;
@@ -996,7 +996,7 @@ constexpr double kMarkShare = 0.48, kMarkShareEnd = 0.93;
 // traffic: it is switched on when rows are at least 512 bytes and the sources that fit with
 // slicing, but not without, receive at least 6 % of all references (measured: R-MAT
 // configuration, 8 % -> 16.5 to 15.3 ms; Chung-Lu configuration, 4 % -> 4.3 to 4.6 ms, left off).
-int epp_tune_locality(epp_path* p, int F, int ld, int gs, hipStream_t s, int* log2_slices, Partition** part) {
+int epp_tune_locality(epp_path* p, int F, int ld, int gs, bool may_partition, hipStream_t s, int* log2_slices, Partition** part) {
     const int64_t budget_mb = env_int("EPP_TUNE_HOT_MB", 80);
     const int64_t rows_budget = budget_mb * (1ll << 20) / ((int64_t)ld * 4);
     const int forced_slices = env_int("EPP_TUNE_LOG2_SLICES", -1);
@@ -1006,9 +1006,9 @@ int epp_tune_locality(epp_path* p, int F, int ld, int gs, hipStream_t s, int* lo
     // branch costs 3 %, and rows of one line gain nothing (F = 32, 140 M entries, 2.4 M sources: 2566 -> 2555 us marked;
     // 114 M entries, 233 K sources: 908 -> 1010 partitioned, where F = 36 / 48 / 64 gain 1908 -> 1515 / 1985 -> 1451 /
     // 2141 -> 1425).
-    const int part_mode = env_int("EPP_TUNE_PART", 1);
+    const int part_mode = may_partition ? env_int("EPP_TUNE_PART", 1) : 0;
     if (p->nnz == 0 || (F <= 32 && part_mode != 2)) return EPP_OK;
-    const int64_t part_rows = forced_slices >= 0 ? 0 : epp_partition_hot_rows(lines_per_row(F, ld));  // a forced slicing is a measurement
+    const int64_t part_rows = forced_slices >= 0 ? 0 : epp_partition_hot_rows(epp_lines_per_row(F, ld));  // a forced slicing is a measurement
     const double hot_share = estimated_share(p, (double)rows_budget);
     const bool want_cold = budget_mb > 0 && p->n_src > rows_budget && marks_pay(F, ld) &&
                            (std::getenv("EPP_TUNE_HOT_MB") || (F >= 64 && hot_share >= kMarkShare && hot_share < kMarkShareEnd));

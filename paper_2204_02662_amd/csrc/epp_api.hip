@@ -28,6 +28,37 @@ Schedule* find_schedule(epp_path* p, int gs) {
 epp_path* entries_of(epp_path* p) { return p->outer ? p->outer : p; }
 const epp_path* entries_of(const epp_path* p) { return p->outer ? p->outer : p; }
 
+// Tiles, where launches of the width run on them and there is memory for them.
+int prepare_tiles(epp_path* p, epp_path::WidthCfg* w, hipStream_t s) {
+    const int lanes = epp_tile_lanes(p, w->F);
+    if (!lanes) return EPP_OK;
+    const epp_alloc_t* al = epp_alloc_of(p);
+    TilePlan* q = nullptr;
+    for (TilePlan* t : p->tile_plans)
+        if (t->lanes == lanes) q = t;
+    if (!q) {
+        const int rc = epp_build_tiles(p, lanes, s, &q);
+        if (rc == EPP_ERR_ALLOC || (rc == EPP_OK && !q)) return EPP_OK;
+        EPP_TRY(rc);
+        p->tile_plans.push_back(q);
+    }
+    void *parts = nullptr, *packed = nullptr;
+    if (q->n_parts > 0) {
+        if (p->pool->get((size_t)q->n_parts * (size_t)w->F * 4, al, &parts) != EPP_OK) return EPP_OK;
+        if (!p->pool->accounted_by) p->pool->accounted_by = p;
+    }
+    if (const size_t bytes = epp_tile_packed_bytes(p, w->F, lanes)) {
+        EPP_TRY(epp_check_sources(p, s));  // (the launch copies the rows of `sources` only)
+        if (p->rows_pool->get(bytes, al, &packed) != EPP_OK) return EPP_OK;
+        if (!p->rows_pool->accounted_by) p->rows_pool->accounted_by = p;
+    }
+    w->tile_parts = static_cast<float*>(parts);
+    w->packed = static_cast<float*>(packed);
+    w->ld = w->F;
+    w->tiles = q;
+    return EPP_OK;
+}
+
 // One-off work of a (path, width): group table, partial rows, locality marks.  Allocates and
 // waits; the aggregate entry points only look the result up.
 int prepare_width(epp_path* self, int F, hipStream_t s, epp_path::WidthCfg** out) {
@@ -48,10 +79,20 @@ int prepare_width(epp_path* self, int F, hipStream_t s, epp_path::WidthCfg** out
             return EPP_OK;
         }
         const int gs = w->forced_gs > 0 ? w->forced_gs : epp_default_group_size(p, F);
+        delete w->part;
+        w->part = nullptr;
+        w->tiles = nullptr;
+        w->packed = nullptr;
+        if (w->forced_gs <= 0) EPP_TRY(prepare_tiles(p, w, s));
+        if (w->tiles && !p->all_rows) {
+            w->prepared = true;
+            if (out) *out = w;
+            return EPP_OK;
+        }
+        // (the all-active handle also serves the if-else baseline, which runs on the group table)
         Schedule* sc = find_schedule(p, gs);
         if (!sc) EPP_TRY(epp_build_schedule(p, gs, s, &sc));
-        w->packed = nullptr;
-        w->ld = epp_packed_stride(p, F);
+        if (!w->tiles) w->ld = epp_packed_stride(p, F);
         if (w->ld > F) {
             EPP_TRY(epp_check_sources(p, s));  // (the launch copies the rows of `sources` only)
             void* scratch = nullptr;
@@ -62,9 +103,7 @@ int prepare_width(epp_path* self, int F, hipStream_t s, epp_path::WidthCfg** out
                 w->ld = F;  // no memory for the copy: the rows are read where they are
             }
         }
-        delete w->part;
-        w->part = nullptr;
-        EPP_TRY(epp_tune_locality(p, F, w->ld, gs, s, &w->log2_slices, &w->part));
+        EPP_TRY(epp_tune_locality(p, F, w->ld, gs, !w->tiles, s, &w->log2_slices, &w->part));
         // partial rows of the plain group table: not needed where every launch uses the partitioned
         // layout (the all-active handle also serves the if-else baseline, which never does)
         if (!w->part || p->all_rows) EPP_TRY(sc->ensure_pieces(F, epp_alloc_of(p)));
@@ -102,6 +141,11 @@ int aggregate(epp_path* self, const float* in, float* out, int F, hipStream_t s,
         EPP_TRY(epp_zero_empty_rows(p, out, F, s));
         return epp_launch_rows(p, w->plan, in, out, F, s, self->outer ? self->inner_rows : nullptr);
     }
+    if (w->tiles && !row_bits) {
+        EPP_TRY(epp_zero_empty_rows(p, out, F, s));
+        return epp_launch_tiles(p, w->tiles, w->tile_parts, in, w->packed, out, F, s, self->sources,
+                                self->outer ? self->inner_rows : nullptr);
+    }
     // (the if-else baseline walks the whole graph in its given order: no partitioned layout)
     return epp_launch_aggregate(p, w->sched, w->log2_slices, in, out, F, s, row_bits, src_bits,
                                 row_bits ? nullptr : w->part, self->outer ? self->inner_rows : nullptr,
@@ -131,6 +175,7 @@ extern "C" int epp_path_info(const epp_path_t* p, epp_path_info_t* info) {
     size_t bytes = p->row_ids.bytes + p->rowptr.bytes + p->cv.bytes + p->full_rowptr.bytes + p->empty_rows.bytes;
     bytes += p->zero_block.bytes + p->inner_pos.bytes;
     for (const Schedule* s : p->scheds) bytes += s->bytes();
+    for (const TilePlan* t : p->tile_plans) bytes += t->store.bytes;
     for (const auto& w : p->widths)
         bytes += (w.part ? w.part->bytes() : 0) + (w.plan ? w.plan->store.bytes : 0);
     for (const ScratchPool* pool : {p->pool, p->rows_pool})
@@ -140,10 +185,14 @@ extern "C" int epp_path_info(const epp_path_t* p, epp_path_info_t* info) {
     // (a path that runs on the next outer path's arrays reports that path's tables as what it uses;
     // their bytes are part of the outer path's footprint)
     for (const auto& w : entries_of(p)->widths) {
-        if (w.F == p->last_F && w.rows) {  // (no table: no row is cut; the group size is the one the selector names)
+        if (w.F == p->last_F && (w.rows || w.tiles)) {  // (no table: no row is cut; the group size is the one the selector names)
             info->sched_F = w.F;
             info->group_size = epp_default_group_size(entries_of(p), w.F);
             info->n_groups = (entries_of(p)->nnz + info->group_size - 1) / info->group_size;
+            if (w.tiles) {
+                info->part_rows = w.tiles->n_cut;
+                info->part_partial_rows = w.tiles->n_parts;
+            }
         } else if (w.F == p->last_F && w.sched) {
             const Schedule* used = w.part ? w.part->sched : w.sched;
             info->sched_F = w.F;
@@ -192,6 +241,12 @@ extern "C" int epp_path_set_group_size(epp_path_t* self, int F, int gs, epp_stre
     w->plan = nullptr;
     delete w->part;
     w->part = nullptr;
+    w->tiles = nullptr;
+    for (size_t i = 0; i < p->tile_plans.size();) {
+        bool used = false;
+        for (const auto& x : p->widths) used |= (x.tiles == p->tile_plans[i]);
+        if (!used) { delete p->tile_plans[i]; p->tile_plans.erase(p->tile_plans.begin() + i); } else ++i;
+    }
     // drop cached tables that no width refers to any more
     for (size_t i = 0; i < p->scheds.size();) {
         bool used = false;

@@ -242,6 +242,22 @@ struct RowsPlan {
     int n_huge = 0, n_chunks = 0;
 };
 
+// Tiles of rows whose sums a launch keeps in LDS while it takes their entries in source order (epp_tiles.hip); serves
+// all widths that want the same lanes per source row.
+struct TilePlan {
+    DevBuf store;                    // the allocation behind the arrays
+    int lanes = 0;                   // per slot
+    int at_once = 0;                 // tiles that run at the same time, among which the rows are dealt
+    int n_tiles = 0, max_batches = 0, n_cut = 0;
+    int64_t n_parts = 0;
+    void* ent = nullptr;             // int2[64 * batches]
+    int32_t* first_batch = nullptr;  // [n_tiles + 1]
+    int32_t* target = nullptr;       // [n_tiles * rows of a tile]
+    int* longest = nullptr;          // [n_tiles]
+    unsigned int* care = nullptr;    // two bits per batch
+    void* cut = nullptr;             // rows that are cut into parts
+};
+
 struct epp_path {
     int64_t n = 0;       // vertices of the input graph
     int64_t n_rows = 0;  // R: rows of the path in canonical form (all-active graph: n)
@@ -281,6 +297,7 @@ struct epp_path {
     int64_t n_empty_rows = 0;
     DevBuf empty_rows;           // int32[n_empty_rows] vertices with empty lists
     std::vector<Schedule*> scheds;
+    std::vector<TilePlan*> tile_plans;
     // per-width choices
     // prepared: epp_path_prepare_width has been called; rows: launches run the row kernel, which needs no
     // group table (sched may be NULL then) and a plan only where some row is very long; slices: XCD feature slicing; part: source-partitioned layout
@@ -293,6 +310,8 @@ struct epp_path {
         Schedule* sched = nullptr;
         int log2_slices = 0;
         Partition* part = nullptr;
+        TilePlan* tiles = nullptr;    // launches run on tiles (no group table then, but for the if-else baseline's)
+        float* tile_parts = nullptr;  // sums of the cut rows' parts, in the handle's scratch pool
         float* packed = nullptr;  // the launch first copies its source rows to this place, `ld` floats apart
         int ld = 0;               // (NULL, F: it reads them where they are)
     };
@@ -300,6 +319,7 @@ struct epp_path {
     int last_F = 0;
     ~epp_path() {
         for (Schedule* s : scheds) delete s;
+        for (TilePlan* t : tile_plans) delete t;
         for (auto& w : widths) { delete w.part; delete w.plan; }
     }
 };
@@ -362,6 +382,7 @@ int epp_launch_aggregate(epp_path* p, Schedule* sc, int log2_slices, const float
                          const unsigned int* row_bits = nullptr, const unsigned int* src_bits = nullptr,
                          const Partition* part = nullptr, const unsigned int* inner_rows = nullptr,
                          float* packed = nullptr, int ld = 0, const unsigned long long* sources = nullptr);
+double epp_lines_per_row(int F, int ld);           // 128-byte lines that a row of F floats touches on average, rows ld floats apart
 int epp_packed_stride(const epp_path* p, int F);  // floats from row to row of packed source rows; F: not packed
 // rows.hip: one launch that processes rows whole, for small paths
 bool epp_rows_kernel_fits(const epp_path* p, int F);
@@ -373,7 +394,15 @@ int epp_build_schedule_over(const epp_path* p, const int32_t* rowptr, int64_t n_
 int epp_default_group_size(const epp_path* p, int F);
 int epp_zero_empty_rows(const epp_path* p, float* out, int F, hipStream_t s);
 // ld: floats from one source row to the next.  Where the memory for it is missing, marks and partition are left out.
-int epp_tune_locality(epp_path* p, int F, int ld, int gs, hipStream_t s, int* log2_slices, Partition** part);
+int epp_tune_locality(epp_path* p, int F, int ld, int gs, bool may_partition, hipStream_t s, int* log2_slices, Partition** part);
+
+// tiles.hip: lanes per source row of a launch on tiles (0: it runs on the group table), bytes of the copy of
+// the source rows that it makes (0: none)
+int epp_tile_lanes(const epp_path* p, int F);
+size_t epp_tile_packed_bytes(const epp_path* p, int F, int lanes);
+int epp_build_tiles(epp_path* p, int lanes, hipStream_t s, TilePlan** out);  // *out = NULL: not these entries
+int epp_launch_tiles(const epp_path* p, const TilePlan* q, float* parts, const float* in, float* packed, float* out, int F,
+                     hipStream_t s, const unsigned long long* sources, const unsigned int* inner_rows);
 
 // partition.hip
 int epp_partition_hot_rows(double lines);  // source rows of width F the eight L2s hold together

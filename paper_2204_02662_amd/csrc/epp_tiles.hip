@@ -1,0 +1,1103 @@
+// Gather-reduce in source order: tiles of rows whose sums stay in LDS (Alg. 2, aggregation loop), for paths whose
+// source rows do not fit the L2s.
+//
+// The group kernel (epp_aggregate.hip) takes entries row after row, so every XCD gathers from everywhere at any time and
+// an L2 of 4 MB serves next to nothing (2.4 M sources, F = 64: 11 % of the lines); the rest runs at the 60 G lines/s
+// that the fabric gives.  Here a wavefront owns a tile of up to 155 rows, whose sums lie in LDS, and takes the
+// tile's entries in the order of their sources.  The 256 wavefronts of an XCD therefore sweep the source matrix
+// together, and a source row that one of them has fetched is still in L2 when the others come to it.
+//
+//   * The rows are dealt to the tiles by length: tiles that run at the same time hold rows of nearly the same lengths, hence
+//     as many entries each, and keep abreast by themselves (a sweep that falls behind finds its lines in L2 and
+//     catches up).  It also puts the long rows into few tiles, which is where most entries share a sweep.  (2.4 M sources,
+//     F = 64: rows dealt at random 4.4 ms a launch, by length 2.8.)
+//   * A row of more than kSplitMax entries is cut into parts, each with every so-manieth kChunk entries, so that every
+//     part spans all sources; the parts' sums go to an array that a second kernel adds up.
+//   * 2^k lanes of 16 bytes read a source row's slice (a "slot"); a wavefront carries several slots, which share its
+//     tile.  A tile's list is cut into batches of 64 entries, each sorted by row and dealt to the slots so that
+//     one step of the wavefront never touches a row twice: then LDS is read, added to and written without atomics
+//     (ds_add_f32 takes 190 cycles a wavefront here), in an order that depends on the path alone.
+//   * Eight wavefronts of 155 rows fill a CU's LDS.  Sixteen of 75 drift apart (26 % instead of 46 % of the lines in
+//     L2: 3.9 ms), four are bound by the instructions of one wavefront per SIMD.
+//   * Wide rows are taken in slices, one after the other: the narrower the slice, the more rows fit LDS and the more sources L2,
+//     at the price of reading the entries once per slice.
+
+#include <cmath>
+#include <cstdlib>
+
+#include "epp_internal.h"
+
+namespace {
+
+constexpr int kTileWaves = 8;            // wavefronts of a workgroup, which fills a CU's LDS
+constexpr int kTilesAtOnce = 256 * kTileWaves;  // tiles of a generation, which run at the same time
+constexpr int kSplitMax = 512;           // longest row that is not cut into parts (and a part's entries, at most)
+constexpr int kPiece = 32;               // entries of a row (about) that are added up before their sum is added to the row's
+constexpr int kTileBins = 128;           // length classes by which rows are dealt
+constexpr unsigned kTogether = 64;       // consecutive tiles that are prepared on one XCD
+constexpr int kChunk = 4;                // entries of a cut row that stay together
+constexpr int kBuckets = 1024;           // source ranges into which a tile's entries are sorted
+constexpr int kRowsPerBlock = 4096, kListBlock = 256;
+constexpr int kColBits = 23;             // of an entry's first word; then 8 bits row of the tile, 1 bit "not the inner path's"
+constexpr unsigned kColMask23 = (1u << kColBits) - 1;
+
+typedef int int2v __attribute__((ext_vector_type(2)));
+typedef float float4v __attribute__((ext_vector_type(4)));
+typedef float float4u __attribute__((ext_vector_type(4), aligned(4)));  // global accesses need no more
+
+// LANES lanes of 16 bytes per slot: rows whose sums a wavefront keeps (one more takes what fills up a batch)
+constexpr int tile_rows(int lanes) { return lanes == 4 ? 255 : lanes == 8 ? 155 : 77; }
+// How a batch is taken, by its two bits of `care`: two steps at a time (0 turns), or one at a time in so many turns.
+constexpr int care_turns(int lanes, unsigned care) {
+    return lanes == 4 ? (care == 0 ? 1 : care == 1 ? 2 : care == 2 ? 4 : 16)
+                      : (care == 0 ? 0 : care == 1 ? 1 : care == 2 ? 2 : 64 / lanes);
+}
+// entries of one row that it may hold
+constexpr int care_limit(int lanes, unsigned care) {
+    return care_turns(lanes, care) == 0 ? lanes / 2 : care_turns(lanes, care) * lanes;
+}
+
+int env_int(const char* name, int dflt) {
+    const char* v = std::getenv(name);
+    return (v && *v) ? std::atoi(v) : dflt;
+}
+
+// Entries of part p of a row of `len` entries cut into `parts`: chunks p, p + parts, ..
+__host__ __device__ inline int parts_of(int len, int split) { return len <= split ? 1 : (len + split - 1) / split; }
+__host__ __device__ inline int part_len(int len, int parts, int p) {
+    const int chunks = (len + kChunk - 1) / kChunk;
+    const int mine = (chunks - p + parts - 1) / parts;
+    return mine * kChunk - ((chunks - 1) % parts == p ? chunks * kChunk - len : 0);
+}
+
+// Length class, the longest rows first: exact up to 32 entries, then eight classes per octave.
+__device__ __forceinline__ int tile_bin(int len) {
+    const int e = 31 - __clz(len);
+    const int up = len < 32 ? len : 32 + (e - 5) * 8 + ((len >> (e - 3)) & 7);
+    return kTileBins - 1 - min(up, kTileBins - 1);
+}
+
+// ------------------------------------------------------------------------------------------ preparation
+// Sums over the lanes up to this one (data moves between lanes without LDS).
+__device__ __forceinline__ int sum_up_to_lane(int x) {
+    x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xF, 0xF, false);  // row_shr:1
+    x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xF, 0xF, false);  // row_shr:2
+    x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xF, 0xF, false);  // row_shr:4
+    x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xF, 0xF, false);  // row_shr:8
+    x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xA, 0xF, false);  // row_bcast:15
+    x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xC, 0xF, false);  // row_bcast:31
+    return x;
+}
+
+// A workgroup takes kRowsPerBlock consecutive rows, a wavefront a quarter of them, 64 at a time: f(row's first entry,
+// its entries, its parts (0: no row), its vertex's index r) by every lane.
+template <class F>
+__device__ __forceinline__ void for_block_rows(const int32_t* __restrict__ rowptr, int64_t n_rows, int split, F f) {
+    constexpr int kPerWave = kRowsPerBlock / (kListBlock / 64);
+    const int64_t base = (int64_t)blockIdx.x * kRowsPerBlock + (threadIdx.x >> 6) * kPerWave + (threadIdx.x & 63);
+    for (int i = 0; i < kPerWave; i += 64) {
+        const int64_t r = base + i;
+        const int begin = r < n_rows ? rowptr[r] : 0, len = r < n_rows ? rowptr[r + 1] - begin : 0;
+        f(begin, len, len > 0 ? parts_of(len, split) : 0, r);
+    }
+}
+
+// f(entries, part, ..) for the parts of every lane's row, by its wavefront where they are many; `begin`, `parts` and `to`
+// are handed on as the row's lane has them.
+template <class F>
+__device__ __forceinline__ void for_parts(int len, int parts, int begin, int to, F f) {
+    for (int p = 0; p < (parts > 8 ? 0 : parts); ++p) f(part_len(len, parts, p), p, begin, parts, to);
+    for (unsigned long long todo = __ballot(parts > 8); todo; todo &= todo - 1ull) {
+        const int l = __ffsll((long long)todo) - 1;
+        const int its_len = __shfl(len, l, 64), its_parts = __shfl(parts, l, 64);
+        const int its_begin = __shfl(begin, l, 64), its_to = __shfl(to, l, 64);
+        for (int p = (int)(threadIdx.x & 63); p < its_parts; p += 64)
+            f(part_len(its_len, its_parts, p), p, its_begin, its_parts, its_to);
+    }
+}
+
+// Rows (parts of cut rows counted one by one) per length class, of every workgroup; totals: rows, parts of cut rows,
+// cut rows.
+__global__ __launch_bounds__(kListBlock) void k_tile_count(const int32_t* __restrict__ rowptr, int64_t n_rows, int split,
+                                                           unsigned int* __restrict__ block_hist,
+                                                           unsigned int* __restrict__ totals) {
+    __shared__ unsigned int h[kTileBins], t[3];
+    if (threadIdx.x < kTileBins) h[threadIdx.x] = 0;
+    if (threadIdx.x < 3) t[threadIdx.x] = 0;
+    __syncthreads();
+    for_block_rows(rowptr, n_rows, split, [&](int, int len, int parts, int64_t) {
+        for_parts(len, parts, 0, 0, [&](int m, int, int, int, int) { atomicAdd(&h[tile_bin(m)], 1u); });
+        if (parts > 0) atomicAdd(&t[0], (unsigned)parts);
+        if (parts > 1) {
+            atomicAdd(&t[1], (unsigned)parts);
+            atomicAdd(&t[2], 1u);
+        }
+    });
+    __syncthreads();
+    if (threadIdx.x < kTileBins) block_hist[blockIdx.x * kTileBins + threadIdx.x] = h[threadIdx.x];
+    if (threadIdx.x < 3 && t[threadIdx.x]) atomicAdd(&totals[threadIdx.x], t[threadIdx.x]);
+}
+
+// A workgroup per class: the class's rows before every workgroup of k_tile_count, and in all of them.
+__global__ __launch_bounds__(256) void k_tile_classes(unsigned int* __restrict__ block_hist, int n_blocks,
+                                                      unsigned int* __restrict__ hist) {
+    __shared__ unsigned int wave_sum[4];
+    const int bin = blockIdx.x, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    unsigned before = 0;
+    for (int b0 = 0; b0 < n_blocks; b0 += 256) {
+        const int b = b0 + (int)threadIdx.x;
+        const unsigned x = b < n_blocks ? block_hist[b * kTileBins + bin] : 0u;
+        const unsigned incl = (unsigned)sum_up_to_lane((int)x);
+        if (lane == 63) wave_sum[wave] = incl;
+        __syncthreads();
+        unsigned mine = before + incl - x;
+        for (int w = 0; w < 4; ++w) {
+            if (w < wave) mine += wave_sum[w];
+            before += wave_sum[w];
+        }
+        if (b < n_blocks) block_hist[b * kTileBins + bin] = mine;
+        __syncthreads();
+    }
+    if (threadIdx.x == 0) hist[bin] = before;
+}
+
+struct TileBins { unsigned first[kTileBins]; };  // rank of the first row of every class
+struct CutRow { int v, first, count; };          // vertex, its first part's place and their number
+// Of a rank: the row's first entry (-1: no row), which of its parts, where its sum goes, parts << 10 | entries of this one.
+struct Dealt { int first, part, target, parts_len; };
+
+// Rank of a tile's row.
+__device__ __forceinline__ int64_t dealt_at(int tile, int local, int tile_rows, int at_once) {
+    const int gen = tile / at_once;
+    return ((int64_t)gen * tile_rows + local) * at_once + (tile - gen * at_once);
+}
+
+// Deals the rows: rank k goes to tile k % at_once of its generation, so that the ranks of a tile lie at_once apart.
+// Within a class rows are ranked in their order (a wavefront counts its own; lanes that add to one counter are served in
+// their order), so that two handles of one path run the same additions.  Only where the parts' sums lie depends on timing.
+__global__ __launch_bounds__(kListBlock) void k_tile_deal(const int32_t* __restrict__ rowptr, const int32_t* __restrict__ row_ids,
+                                                          int64_t n_rows, int split, int n, TileBins bins,
+                                                          const unsigned int* __restrict__ block_hist,
+                                                          unsigned int* __restrict__ places,  // [0] parts, [1] cut rows
+                                                          Dealt* __restrict__ dealt, CutRow* __restrict__ cut) {
+    constexpr int kWaves = kListBlock / 64;
+    __shared__ unsigned int h[kWaves][kTileBins], t[2], place[2];
+    for (int i = threadIdx.x; i < kWaves * kTileBins; i += kListBlock) h[i / kTileBins][i % kTileBins] = 0;
+    if (threadIdx.x < 2) t[threadIdx.x] = 0;
+    __syncthreads();
+    unsigned int* __restrict__ mine = h[threadIdx.x >> 6];
+    for_block_rows(rowptr, n_rows, split, [&](int, int len, int parts, int64_t) {
+        for_parts(len, parts, 0, 0, [&](int m, int, int, int, int) { atomicAdd(&mine[tile_bin(m)], 1u); });
+        if (parts > 1) { atomicAdd(&t[0], (unsigned)parts); atomicAdd(&t[1], 1u); }
+    });
+    __syncthreads();
+    // (one place in each list for all of the workgroup's parts and cut rows together)
+    if (threadIdx.x < kTileBins) {
+        unsigned rank = bins.first[threadIdx.x] + block_hist[blockIdx.x * kTileBins + threadIdx.x];
+        for (int w = 0; w < kWaves; ++w) {
+            const unsigned m = h[w][threadIdx.x];
+            h[w][threadIdx.x] = rank;
+            rank += m;
+        }
+    }
+    if (threadIdx.x < 2) {
+        place[threadIdx.x] = t[threadIdx.x] ? atomicAdd(&places[threadIdx.x], t[threadIdx.x]) : 0u;
+        t[threadIdx.x] = 0;
+    }
+    __syncthreads();
+    for_block_rows(rowptr, n_rows, split, [&](int begin, int len, int parts, int64_t r) {
+        int to = len > 0 ? (row_ids ? row_ids[r] : (int)r) : 0;
+        if (parts > 1) {
+            const int first = (int)(place[0] + atomicAdd(&t[0], (unsigned)parts));
+            cut[place[1] + atomicAdd(&t[1], 1u)] = CutRow{to, first, parts};
+            to = n + first;
+        }
+        for_parts(len, parts, begin, to, [&](int m, int p, int its_begin, int its_parts, int its_to) {
+            dealt[atomicAdd(&mine[tile_bin(m)], 1u)] = Dealt{its_begin, p, its_to + p, its_parts << 10 | m};
+        });
+    });
+}
+
+// Batches of 64 entries per tile.
+__global__ __launch_bounds__(64) void k_tile_sizes(const Dealt* __restrict__ dealt, int tile_rows, int at_once, int n_tiles,
+                                                   int* __restrict__ batches) {
+    const int tile = (int)(blockIdx.x * 64 + threadIdx.x);
+    if (tile >= n_tiles) return;
+    const int64_t first = dealt_at(tile, 0, tile_rows, at_once);
+    int sum = 0;
+#pragma unroll 8
+    for (int i = 0; i < tile_rows; ++i) {
+        const Dealt r = dealt[first + (int64_t)i * at_once];
+        sum += r.first < 0 ? 0 : r.parts_len & 1023;
+    }
+    batches[tile] = (sum + 63) / 64;
+}
+
+// One workgroup per tile: its entries into the order of their sources (kBuckets ranges of them), then into batches.
+//
+// A tile of at most kSortMax entries is read once, into registers; a larger one is counted first, then taken in rounds,
+// each a range of the sources.  A wavefront takes its share of the rows 64 entries at a time and counts for itself; lanes that
+// add to one counter are served in their order.  A range's entries are therefore in the order of the rows, whatever the
+// timing, and so are the additions of a launch.  The entries that fill up the last batch have weight zero and a row of
+// their own.
+//
+// A batch's 64 entries are sorted by row and dealt to (step, slot): place i goes to step i % steps of slot i / steps.
+// Two entries of one row then share a step only if the row has more than `steps` entries in the batch; they lie fewer
+// than t slots apart if it has at most t * steps, and then a step is safe in t turns, of every t-th slot each.  Two steps
+// half as many apart share no row if none has more than half as many entries.  The launch learns from two bits of
+// `care` how it has to take the batch.
+//
+// *bad is set where that cannot be done: more than kSortMax entries of a tile in one range, or, in a tile that takes more
+// than one round, columns that do not ascend along a row.
+constexpr int kSortThreads = 512, kSortWaves = kSortThreads / 64;
+constexpr int kSortMax = 5632;
+constexpr int kSortPer = (kSortMax / kSortWaves + kSplitMax - 1 + 63) / 64;  // entries per lane: a wavefront's share and all of one row but one
+
+// Of a row (part): its first entry, from one chunk of it to the next, its entries, and the (negative) number of the
+// round's entries before it less those of it that are already taken.
+struct TileRow { int first, step, len, before; };
+
+__device__ __forceinline__ int tile_entry(const TileRow& r, int k) {
+    return r.first + (int)((unsigned)k / kChunk) * r.step + (int)((unsigned)k % kChunk);
+}
+
+template <int LANES>
+__global__ __launch_bounds__(kSortThreads, 4) void k_tile_sort(const int2v* __restrict__ cv, const Dealt* __restrict__ dealt, int at_once,
+                                                               const int32_t* __restrict__ first_batch, int fine_shift,
+                                                               int32_t* __restrict__ target, int* __restrict__ longest,
+                                                               int2v* __restrict__ ent, unsigned int* __restrict__ care,
+                                                               int* __restrict__ bad) {
+    constexpr int kRows = tile_rows(LANES), kSlots = 64 / LANES, kSteps = LANES;
+    static_assert(kRows < 256 && kRows < kSortThreads, "");
+    __shared__ int2v buf[kSortMax + 64];
+    // entries per range: of the round and of two wavefronts a word, 16 bits each, then their places; of the tile, up to the range's end
+    __shared__ unsigned count[kSortWaves / 2][kBuckets];
+    __shared__ int upto[kBuckets];
+    __shared__ TileRow row_of[kRows];
+    __shared__ int from[kRows], start[kRows + 1];    // first entry of the round, its place among the round's entries
+    __shared__ int wave_sum[kSortWaves];
+    __shared__ int row_count_all[kSortWaves][256];
+    // (consecutive tiles hold the parts of one row and read the same lines: kTogether of them run on one XCD)
+    const unsigned turn = blockIdx.x >> 3;
+    const int tile = (int)(((turn / kTogether) * 8 + (blockIdx.x & 7)) * kTogether + turn % kTogether);
+    const int b0 = first_batch[tile];
+    const int t = (int)threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
+    TileRow mine = {0, kChunk, 0, 0};
+    if (t < kRows) {
+        const Dealt r = dealt[dealt_at(tile, t, kRows, at_once)];
+        if (r.first >= 0) mine = TileRow{r.first + r.part * kChunk, (r.parts_len >> 10) * kChunk, r.parts_len & 1023, 0};
+        target[(size_t)tile * kRows + t] = r.target;
+        if (t == 0) longest[tile] = mine.len;  // (about: a tile's first row is of its highest length class)
+    }
+    // sums of x over the threads before this one and over all
+    auto scan = [&](int x, int& total) {
+        const int incl = sum_up_to_lane(x);
+        __syncthreads();  // (wave_sum may still be read)
+        if (lane == 63) wave_sum[wave] = incl;
+        __syncthreads();
+        int before = incl - x;
+        total = 0;
+        for (int w = 0; w < kSortWaves; ++w) {
+            if (w < wave) before += wave_sum[w];
+            total += wave_sum[w];
+        }
+        total = __builtin_amdgcn_readfirstlane(total);
+        return before;
+    };
+    // the row of the round's entry `pos`: the last one that starts at or before it and is not empty
+    auto row_at = [&](int pos, int lo, int hi) {
+        while (hi - lo > 1) {
+            const int mid = (lo + hi) >> 1;
+            if (start[mid] <= pos) lo = mid; else hi = mid;
+        }
+        return lo;
+    };
+    int all;
+    {
+        const int before = scan(mine.len, all);
+        mine.before = -before;
+        if (t < kRows) { start[t] = before; from[t] = 0; row_of[t] = mine; }
+        if (t == 0) start[kRows] = all;
+    }
+    __syncthreads();
+    if (all == 0) return;  // (its places have no rows)
+    const bool whole = all <= kSortMax;
+    // fewer and larger ranges where a batch spans several of them anyway
+    int buckets = kBuckets, shift = fine_shift;
+    while (buckets > 256 && buckets > all / 8) { buckets /= 2; ++shift; }
+    const int per = max(buckets / kSortThreads, 1), mine0 = min(t * per, buckets), mine1 = min(mine0 + per, buckets);
+    if (!whole) {
+        for (int i = t; i < buckets; i += kSortThreads) upto[i] = 0;
+        __syncthreads();
+        for (int pos = t; pos < all; pos += kSortThreads) {
+            const int r = row_at(pos, 0, kRows);
+            atomicAdd(&upto[(cv[tile_entry(row_of[r], pos + row_of[r].before)].x & kEntCol) >> shift], 1);
+        }
+        __syncthreads();
+        int sum = 0, total;
+#pragma unroll 1
+        for (int i = mine0; i < mine1; ++i) sum += upto[i];
+        int before = scan(sum, total);
+#pragma unroll 1
+        for (int i = mine0; i < mine1; ++i) { before += upto[i]; upto[i] = before; }
+        __syncthreads();
+    }
+    int lo_bucket = 0, carry = 0, done = b0, taken = 0;  // (the same in all threads)
+    while (true) {
+        int hi_bucket = buckets;
+        if (!whole) {  // as many ranges as fit
+            const int limit = (lo_bucket ? upto[lo_bucket - 1] : 0) + kSortMax;
+            int lo = lo_bucket, hi = buckets;
+            while (lo < hi) {
+                const int mid = (lo + hi) >> 1;
+                if (upto[mid] <= limit) lo = mid + 1; else hi = mid;
+            }
+            hi_bucket = __builtin_amdgcn_readfirstlane(lo);
+            if (hi_bucket == lo_bucket) {
+                if (t == 0) *bad = 1;
+                return;
+            }
+        }
+        const bool last = hi_bucket == buckets;
+        int begin = 0, end = mine.len;
+        if (!whole && t < kRows) {
+            begin = from[t];
+            if (!last) {
+                int lo = begin;
+                while (lo < end) {
+                    const int mid = (lo + end) >> 1;
+                    if (((cv[tile_entry(mine, mid)].x & kEntCol) >> shift) < hi_bucket) lo = mid + 1; else end = mid;
+                }
+            }
+        }
+        int here;
+        {
+            const int before = scan(t < kRows ? end - begin : 0, here);
+            if (t < kRows) { start[t] = before; row_of[t].before = begin - before; }
+            if (t == 0) start[kRows] = here;
+        }
+        for (int i = t; i < buckets; i += kSortThreads) {
+            for (int w = 0; w < kSortWaves / 2; ++w) count[w][i] = 0;
+        }
+        __syncthreads();
+        if (here > kSortMax) {  // (rows that do not ascend)
+            if (t == 0) *bad = 1;
+            return;
+        }
+        // the wavefront's rows: those that start in its share of the places
+        const int share = (here + kSortWaves - 1) / kSortWaves;
+        auto first_place = [&](int w) {  // of the first row that starts at or after place w * share
+            int lo = 0, hi = kRows;
+            while (lo < hi) {
+                const int mid = (lo + hi) >> 1;
+                if (start[mid] < w * share) lo = mid + 1; else hi = mid;
+            }
+            return __builtin_amdgcn_readfirstlane(lo);
+        };
+        const int r0 = first_place(wave), r1 = wave == kSortWaves - 1 ? kRows : first_place(wave + 1);
+        const int p0 = __builtin_amdgcn_readfirstlane(start[r0]), p1 = __builtin_amdgcn_readfirstlane(start[r1]);
+        unsigned* __restrict__ my_count = count[wave >> 1];
+        const int half = (wave & 1) * 16;
+        int2v e[kSortPer];
+        int at[kSortPer];  // row, then (also) the place inside the range
+#pragma unroll
+        for (int i = 0; i < kSortPer; ++i) {
+            const int pos = p0 + i * 64 + lane;
+            e[i] = int2v{0, 0};
+            at[i] = 0;
+            if (p0 + i * 64 < p1) {
+                const int r = row_at(min(pos, p1 - 1), r0, r1);
+                at[i] = r;
+                const TileRow row = row_of[r];
+                e[i] = cv[tile_entry(row, min(pos, p1 - 1) + row.before)];
+            }
+        }
+        bool out_of_range = false;
+#pragma unroll
+        for (int i = 0; i < kSortPer; ++i) {
+            if (p0 + i * 64 < p1) {
+                const bool valid = p0 + i * 64 + lane < p1;
+                const int bucket = (e[i].x & kEntCol) >> shift;
+                if (!whole) out_of_range |= bucket < lo_bucket || bucket >= hi_bucket;
+                unsigned place = 0;
+                if (valid) place = atomicAdd(&my_count[bucket], 1u << half);
+                at[i] = (at[i] << 16) | (int)((place >> half) & 0xFFFFu);
+            }
+        }
+        if (out_of_range) *bad = 1;
+        __syncthreads();
+        {
+            int sum = 0, total;
+#pragma unroll 1
+            for (int i = mine0; i < mine1; ++i) {
+                for (int w = 0; w < kSortWaves / 2; ++w) sum += (int)((count[w][i] & 0xFFFFu) + (count[w][i] >> 16));
+            }
+            unsigned before = (unsigned)(scan(sum, total) + carry);
+#pragma unroll 1
+            for (int i = mine0; i < mine1; ++i) {  // a range's entries in the order of the wavefronts
+                for (int w = 0; w < kSortWaves / 2; ++w) {
+                    const unsigned c = count[w][i], odd = before + (c & 0xFFFFu);
+                    count[w][i] = before | odd << 16;
+                    before = odd + (c >> 16);
+                }
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < kSortPer; ++i) {
+            if (p0 + i * 64 + lane < p1) {
+                int x = e[i].x;
+                asm volatile("" : "+v"(x));  // (formed again: columns and ranges kept since above would not fit the registers)
+                const unsigned col = (unsigned)(x & kEntCol);
+                buf[((my_count[col >> shift] >> half) & 0xFFFFu) + (at[i] & 0xFFFF)] =
+                    int2v{(int)(col | ((unsigned)(at[i] >> 16) << kColBits) | (x & kEntOuterOnly ? 0x80000000u : 0u)), e[i].y};
+            }
+        }
+        const int filled = carry + here;
+        const int batches = last ? (filled + 63) / 64 : filled / 64;
+        if (last && t < 64 && filled + t < batches * 64) {
+            const int2v any = cv[tile_entry(row_of[0], 0)];  // (a source that the launch reads anyway)
+            buf[filled + t] = int2v{(int)((unsigned)(any.x & kEntCol) | ((unsigned)kRows << kColBits) |
+                                          (any.x & kEntOuterOnly ? 0x80000000u : 0u)), 0};
+        }
+        __syncthreads();
+        for (int i = wave; i < batches; i += kSortWaves) {
+            const int2v x = buf[i * 64 + lane];
+            const unsigned row = ((unsigned)x.x >> kColBits) & 255u;
+            // entries per row, their places, and how many of its own row are before an entry
+            int* __restrict__ n_of = row_count_all[wave];
+            int4* __restrict__ quad = reinterpret_cast<int4*>(n_of) + lane;
+            __builtin_amdgcn_wave_barrier();
+            *quad = int4{0, 0, 0, 0};
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            const int before = atomicAdd(&n_of[row], 1);
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            const int4 n = *quad;
+            int most = max(max(n.x, n.y), n.z);
+            if (lane * 4 + 3 != kRows) most = max(most, n.w);
+            static_assert(kRows % 4 == 3 || kRows == 77, "");
+            if (kRows == 77 && lane == 19) most = n.x;
+            const int sum = n.x + n.y + n.z + n.w;
+            const int first = sum_up_to_lane(sum) - sum;
+            *quad = int4{first, first + n.x, first + n.x + n.y, first + n.x + n.y + n.z};
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            const int place = n_of[row] + before;
+            unsigned level = 0;
+#pragma unroll
+            for (unsigned c = 0; c < 3; ++c)
+                if (__ballot(most > care_limit(LANES, c))) level = c + 1;
+            const int b = done + i;
+            if (level && lane == 0) atomicOr(&care[b >> 4], level << (2 * (b & 15)));
+            __builtin_nontemporal_store(x, ent + (int64_t)b * 64 + (place % kSteps) * kSlots + place / kSteps);
+        }
+        if (last) return;
+        done += batches;
+        carry = filled - batches * 64;
+        taken += here;
+        lo_bucket = hi_bucket;
+        const int2v rest = t < carry ? buf[batches * 64 + t] : int2v{0, 0};
+        __syncthreads();
+        if (t < carry) buf[t] = rest;
+        if (t < kRows) from[t] = end;
+        __syncthreads();
+    }
+}
+
+// ------------------------------------------------------------------------------------------------ launch
+struct TileArgs {
+    const int2v* ent;
+    const int32_t* first_batch;   // per tile, then their number
+    const unsigned int* care;     // two bits per batch (k_tile_sort)
+    const int32_t* target;        // per row of a tile: vertex, n + place of a part's sum, or -1
+    const int* longest;           // per tile: entries of its rows, about at most
+    const float* in;
+    float* out;
+    float* parts;                 // sums of the cut rows' parts, F floats each
+    int n, F;
+    int lanes;                    // of a slot that hold part of a slice
+    int ld;                       // floats from one row of `in` to the next
+    int64_t slice_step;           // and from one slice of a row to the next
+    int blocks;                   // workgroups per slice
+    const float* zero;            // launch for the inner path that shares the arrays: 256 zero bytes
+    const unsigned int* inner_rows;
+};
+
+// Copies the source rows slice by slice: all rows of the first slice, `stride` quadruples apart, of which `q` are used
+// (zeros behind F), then those of the next.  Rows that are not in the bitmap `sources` (NULL: all are) are left
+// out.  One workgroup per word of the bitmap.
+__global__ __launch_bounds__(kListBlock) void k_pack_slices(const float* __restrict__ in, int64_t n, int F, int q, int stride,
+                                                            int slices, const unsigned long long* __restrict__ sources,
+                                                            float* __restrict__ out) {
+    const unsigned long long mine = sources ? sources[blockIdx.x] : ~0ull;
+    if (!mine) return;
+    const int64_t r0 = (int64_t)blockIdx.x * 64;
+    const int rows = (int)std::min<int64_t>(n - r0, 64);
+    for (int s = 0; s < slices; ++s) {
+        float4v* __restrict__ dst = reinterpret_cast<float4v*>(out) + ((int64_t)s * n + r0) * stride;
+        for (int i = threadIdx.x; i < rows * q; i += kListBlock) {
+            const int r = i / q, k = i - r * q, f = (s * q + k) * 4;
+            if (!((mine >> r) & 1)) continue;
+            const float* __restrict__ x = in + (r0 + r) * F + f;
+            float4v v = {0.0f, 0.0f, 0.0f, 0.0f};
+            if (f + 4 <= F) {
+                v = *reinterpret_cast<const float4u*>(x);
+            } else {
+#pragma unroll
+                for (int c = 0; c < 3; ++c)
+                    if (f + c < F) v[c] = x[c];
+            }
+            dst[r * stride + k] = v;
+        }
+    }
+}
+
+// A wavefront per tile and slice.  8 and 16 lanes a slot are bound by the lines that miss L2 (2.4 M sources, 140 M entries,
+// F = 64: 93 G lines/s, half of which miss; the group kernel's launch takes 4620 us, this one 3090): all gathers of a
+// batch go out together, then its sums are added up, and a wavefront drifts from the others by one batch at most.  With the
+// gathers of the next batch made step by step as registers come free, the same launch took 3300 us, and with two batches 3500:
+// wavefronts that run further ahead find less in L2.  Slots of 4 lanes read half a line or less at a time and wait for
+// latency instead: there the gathers do run kDepth batches ahead (114 M entries, 233 K sources, F = 16: 697 us without, 575
+// with one batch, 555 with two, 554 with three; the group kernel 920).
+//
+// A sum is formed in LDS over about kPiece entries at a time, and those sums in registers, where a lane has those of the rows
+// that it will write.  Its rounding error then grows like that of a sum of 32 + 16 terms, not of 512: over 20 all-active
+// launches (both models, 22 to 288 M entries, F = 16 to 128) it is 0.63 to 0.89 of the group kernel's against 64 bits; one
+// chain of 512 would be 0.99 to 1.6 of it.  Adding up in LDS alone would be no faster (within 3 %, the spread of the runs).
+template <int LANES, bool INNER>
+__global__ __launch_bounds__(kTileWaves * 64, 2) void k_aggregate_tiles(TileArgs a) {
+    constexpr int kRows = tile_rows(LANES), kSlots = 64 / LANES, kSteps = LANES, kDepth = LANES == 4 ? 2 : 0;
+    constexpr int kTakes = std::max(kDepth, 1);
+    typedef __attribute__((address_space(1))) const float4u* gvec_ptr;
+    __shared__ float4v sums_all[kTileWaves][(kRows + 1) * LANES];
+    __shared__ int2v stage_all[kTileWaves][64];
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int slot = lane / LANES, l = lane % LANES;
+    const int slice = blockIdx.x / a.blocks;
+    const int tile = (blockIdx.x - slice * a.blocks) * kTileWaves + wave;
+    float4v* __restrict__ sums = sums_all[wave];
+    int2v* __restrict__ stage = stage_all[wave];
+    const int f = l < a.lanes ? (slice * a.lanes + l) * 4 : a.F;  // (a lane without a share reads its neighbour's)
+    const int b0 = a.first_batch[tile], b1 = a.first_batch[tile + 1];
+    if (b0 == b1) return;  // (its places have no rows; nothing below waits for another wavefront)
+    for (int i = lane; i < (kRows + 1) * LANES; i += 64) sums[i] = float4v{};
+    const float* __restrict__ src = a.in + slice * a.slice_step + min(l, a.lanes - 1) * 4;
+    const unsigned ld = (unsigned)a.ld;
+    const int2v* __restrict__ ent = a.ent + (int64_t)b0 * 64 + lane;
+    const int last = b1 - b0 - 1, pieces = min((a.longest[tile] + kPiece - 1) / kPiece, last + 1);
+    // Gathers are kDepth batches ahead of the additions, entries and their two bits of `care` one batch more.  (Behind the end
+    // the last batch is gathered again, from L2.)
+    auto entries = [&](int b) { return __builtin_nontemporal_load(ent + min(b, last) * 64); };
+    auto cares = [&](int b) { return a.care[(b0 + min(b, last)) >> 4]; };
+    struct { float4u x[kSteps]; float w[kSteps]; unsigned at[kSteps]; unsigned care; } flight[kTakes];
+    int2v ahead = entries(0);
+    auto put = [&](int b) {  // the entries of batch b, and loads those of the next
+        __builtin_amdgcn_wave_barrier();
+        stage[lane] = ahead;
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        ahead = entries(b + 1);
+        __builtin_amdgcn_sched_barrier(0);  // (before the gathers that come next, so that waiting for it is not waiting for them)
+    };
+    auto gather = [&](auto& fl, int j, int2v e) {
+        fl.at[j] = (((unsigned)e.x >> kColBits) & 255u) * LANES + l;
+        // (32 bits: the number of vertices times ld is below 2^32)
+        const unsigned place = __umul24((unsigned)e.x & kColMask23, ld);
+        gvec_ptr p = (gvec_ptr)(src + place);
+        fl.w[j] = __int_as_float(e.y);
+        if constexpr (INNER) {
+            if (e.x < 0) { p = (gvec_ptr)(a.zero + l * 4); fl.w[j] = 0.0f; }
+        }
+        fl.x[j] = *p;
+    };
+    // (always in this order: the wait for one gather is then not for another that was made later)
+    auto gather_two = [&](auto& fl, int j, int2v e0, int2v e1) {
+        gather(fl, j, e0);
+        __builtin_amdgcn_sched_barrier(0x7);  // (arithmetic may cross)
+        gather(fl, j + kSteps / 2, e1);
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    // (in LDS a wavefront's operations execute in order)
+    auto add = [&](auto& fl, int j) {
+        float4v sum = sums[fl.at[j]];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) sum[i] = fmaf(fl.w[j], fl.x[j][i], sum[i]);
+        sums[fl.at[j]] = sum;
+    };
+    auto take = [&](int b, auto& fl) {
+        const unsigned how = __builtin_amdgcn_readfirstlane(fl.care >> (2 * ((b0 + b) & 15))) & 3u;
+        put(b + kDepth);
+        fl.care = cares(b + kTakes);
+        constexpr int kHalf = kSteps / 2;
+        if constexpr (kDepth == 0) {
+#pragma unroll
+            for (int j = 0; j < kHalf; ++j) {
+                gather(fl, j, stage[j * kSlots + slot]);
+                gather(fl, j + kHalf, stage[(j + kHalf) * kSlots + slot]);
+            }
+        }
+        const int turns = how == 0 ? 1 : how == 1 ? care_turns(LANES, 1) : how == 2 ? care_turns(LANES, 2) : care_turns(LANES, 3);
+        const int mine = slot & (turns - 1);
+        auto in_turns = [&](int j) {
+            for (int t = 0; t < turns; ++t) {
+                if (mine == t) add(fl, j);
+                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+                __builtin_amdgcn_wave_barrier();
+            }
+        };
+#pragma unroll
+        for (int j = 0; j < kHalf; ++j) {
+            int2v e0, e1;
+            if constexpr (kDepth > 0) { e0 = stage[j * kSlots + slot]; e1 = stage[(j + kHalf) * kSlots + slot]; }
+            if (how != 0) {
+                in_turns(j);
+                in_turns(j + kHalf);
+            } else if constexpr (care_turns(LANES, 0) == 1) {
+                add(fl, j);
+                add(fl, j + kHalf);
+            } else {
+                float4v s0 = sums[fl.at[j]], s1 = sums[fl.at[j + kHalf]];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) s0[i] = fmaf(fl.w[j], fl.x[j][i], s0[i]);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) s1[i] = fmaf(fl.w[j + kHalf], fl.x[j + kHalf][i], s1[i]);
+                sums[fl.at[j]] = s0;
+                sums[fl.at[j + kHalf]] = s1;
+            }
+            if constexpr (kDepth > 0) {
+                __builtin_amdgcn_sched_barrier(0);  // (the gathers go to the registers that this has freed)
+                gather_two(fl, j, e0, e1);
+            }
+        }
+    };
+#pragma unroll
+    for (int d = 0; d < kTakes; ++d) {
+        flight[d].care = cares(d);
+        if (kDepth == 0) continue;
+        put(d);
+#pragma unroll
+        for (int j = 0; j < kSteps / 2; ++j) gather_two(flight[d], j, stage[j * kSlots + slot], stage[(j + kSteps / 2) * kSlots + slot]);
+    }
+    constexpr int kOwn = (kRows + kSlots - 1) / kSlots;
+    float4v whole[kOwn];
+#pragma unroll
+    for (int i = 0; i < kOwn; ++i) whole[i] = float4v{};
+    int b = 0;
+    for (int piece = 1; piece <= pieces; ++piece) {
+        const int upto = (int)((int64_t)(last + 1) * piece / pieces);
+        for (; b < upto; b += kTakes) {
+#pragma unroll
+            for (int d = 0; d < kTakes; ++d)
+                if (d == 0 || b + d <= last) take(b + d, flight[d]);
+        }
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int i = 0; i < kOwn; ++i) {
+            if ((i + 1) * 64 > (kRows + 1) * LANES && lane + i * 64 >= (kRows + 1) * LANES) continue;
+            whole[i] += sums[lane + i * 64];
+            sums[lane + i * 64] = float4v{};
+        }
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+    }
+    // (all places are looked up at once: one after the other they would hold the sweep up)
+    int to[kOwn];
+#pragma unroll
+    for (int i = 0; i < kOwn; ++i) {
+        const int r = slot + i * kSlots;
+        to[i] = a.target[(size_t)tile * kRows + min(r, kRows - 1)];
+        if (r >= kRows || f >= a.F) to[i] = -1;
+    }
+    if constexpr (INNER) {
+#pragma unroll
+        for (int i = 0; i < kOwn; ++i)
+            if (to[i] >= 0 && to[i] < a.n && !((a.inner_rows[to[i] >> 5] >> (to[i] & 31)) & 1u)) to[i] = -1;
+    }
+#pragma unroll
+    for (int i = 0; i < kOwn; ++i) {
+        if (to[i] < 0) continue;
+        float* __restrict__ o = to[i] < a.n ? a.out + (size_t)to[i] * (size_t)a.F : a.parts + (size_t)(to[i] - a.n) * (size_t)a.F;
+        if (f + 4 <= a.F) {
+            __builtin_nontemporal_store((float4u)whole[i], reinterpret_cast<float4u*>(o + f));
+        } else {
+#pragma unroll
+            for (int c = 0; c < 3; ++c)
+                if (f + c < a.F) o[f + c] = whole[i][c];
+        }
+    }
+}
+
+// out[v, :] = sum of the parts of a cut row, in their order: 2^log2T lanes of 16 bytes a row, four loads in flight.
+// A row with more than kFewSums of them is left to a wavefront, whose teams of lanes take every so-manieth one and
+// exchange their sums between lanes, one with more than kManySums to the whole workgroup.  Bound by memory: 2.9 M sums of
+// 128 floats in 278 us.
+constexpr int kFewSums = 16, kManySums = 256;
+__global__ __launch_bounds__(kListBlock) void k_tile_add_parts(const CutRow* __restrict__ cut, int n_cut, int F, int log2T,
+                                                               const float* __restrict__ parts,
+                                                               const unsigned int* __restrict__ only_bits,
+                                                               float* __restrict__ out) {
+    constexpr int kWaves = kListBlock / 64;
+    __shared__ CutRow list[kListBlock];
+    __shared__ int n_long;
+    __shared__ float4v sum_of[kWaves][64];
+    const int T = 1 << log2T, lane = threadIdx.x & (T - 1), wave = threadIdx.x >> 6;
+    if (threadIdx.x == 0) n_long = 0;
+    __syncthreads();
+    const int at = (int)((blockIdx.x * kListBlock + threadIdx.x) >> log2T);
+    if (at < n_cut) {
+        const CutRow c = cut[at];
+        if (only_bits && !((only_bits[c.v >> 5] >> (c.v & 31)) & 1u)) {
+            // not a row of the inner path
+        } else if (c.count > kFewSums) {
+            if (lane == 0) list[atomicAdd(&n_long, 1)] = c;
+        } else {
+            for (int f0 = lane * 4; f0 < F; f0 += T * 4) {
+                const int f = min(f0, F - 4);
+                const float* __restrict__ x0 = parts + (size_t)c.first * F + f;
+                float4u s = *reinterpret_cast<const float4u*>(x0);
+                for (int p = 1; p < c.count; p += 4) {
+                    float4u x[4];
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) x[i] = *reinterpret_cast<const float4u*>(x0 + (size_t)min(p + i, c.count - 1) * F);
+#pragma unroll
+                    for (int i = 0; i < 4; ++i)
+                        if (p + i < c.count) s += x[i];
+                }
+                *reinterpret_cast<float4u*>(out + (size_t)c.v * F + f) = s;
+            }
+        }
+    }
+    __syncthreads();
+    const int longs = n_long;
+    for (int i = 0; i < longs; ++i) {
+        const CutRow c = list[i];
+        const bool all = c.count > kManySums;
+        if (!all && (i & (kWaves - 1)) != wave) continue;
+        const int team = (all ? (int)threadIdx.x : (int)(threadIdx.x & 63)) >> log2T, teams = (all ? kListBlock : 64) >> log2T;
+        for (int base = 0; base < F; base += T * 4) {
+            const int f0 = base + lane * 4, f = min(f0, F - 4);
+            float4u s = {0.0f, 0.0f, 0.0f, 0.0f};
+            for (int p = team; p < c.count; p += 8 * teams) {
+                float4u x[8];
+#pragma unroll
+                for (int j = 0; j < 8; ++j)
+                    x[j] = *reinterpret_cast<const float4u*>(parts + (size_t)(c.first + min(p + j * teams, c.count - 1)) * F + f);
+#pragma unroll
+                for (int j = 0; j < 8; ++j)
+                    if (p + j * teams < c.count) s += x[j];
+            }
+            for (int d = T; d < 64; d <<= 1) {
+#pragma unroll
+                for (int j = 0; j < 4; ++j) s[j] += __shfl_xor(s[j], d, 64);
+            }
+            if (all) {  // (the same for every wavefront, like the barriers below)
+                sum_of[wave][threadIdx.x & 63] = s;
+                __syncthreads();
+                if (wave == 0) {
+                    for (int w = 1; w < kWaves; ++w) s += sum_of[w][lane];
+                }
+                __syncthreads();  // `sum_of` is written again
+            }
+            if (team == 0 && f0 < F) *reinterpret_cast<float4u*>(out + (size_t)c.v * F + f) = s;
+        }
+    }
+}
+
+struct TileShape { int slices, quads, stride; bool packed; };
+
+unsigned blocks_for(int64_t items, int per) { return (unsigned)((items + per - 1) / per); }
+
+template <int LANES>
+void sort_tiles(TilePlan* q, const int2v* cv, const Dealt* dealt, int shift, int* bad, hipStream_t s) {
+    hipLaunchKernelGGL(k_tile_sort<LANES>, dim3((unsigned)q->n_tiles), dim3(kSortThreads), 0, s, cv, dealt, q->at_once,
+                       q->first_batch, shift, q->target, q->longest, reinterpret_cast<int2v*>(q->ent), q->care, bad);
+}
+
+template <int LANES>
+void launch_tiles(const TileArgs& a, int slices, hipStream_t s) {
+    const dim3 grid((unsigned)(a.blocks * slices)), block(kTileWaves * 64);
+    if (a.zero) hipLaunchKernelGGL((k_aggregate_tiles<LANES, true>), grid, block, 0, s, a);
+    else hipLaunchKernelGGL((k_aggregate_tiles<LANES, false>), grid, block, 0, s, a);
+}
+
+}  // namespace
+
+// How launches take rows of F floats: slices of `quads` quadruples, which lie `stride` quadruples apart where the rows
+// are copied first.  A slice should touch as few 128-byte lines as it can fill, so that all is copied that does not
+// lie that way already (F = 24, 274 M entries, 2.4 M sources: 2687 us copied, 4251 read across the lines' ends).
+static TileShape tile_shape(int F, int lanes) {
+    const int quads = (F + 3) / 4;
+    TileShape t;
+    t.slices = (quads + lanes - 1) / lanes;
+    t.quads = (quads + t.slices - 1) / t.slices;
+    t.stride = 1;
+    while (t.stride < t.quads) t.stride *= 2;
+    if (t.stride == 16 && t.quads <= 12) t.stride = 12;  // (two lines either way)
+    t.packed = F % 4 != 0 || t.slices * t.quads != quads || t.quads != t.stride;
+    return t;
+}
+
+size_t epp_tile_packed_bytes(const epp_path* p, int F, int lanes) {
+    const TileShape t = tile_shape(F, lanes);
+    return t.packed ? (size_t)p->n * t.slices * t.stride * 16 : 0;
+}
+
+// ------------------------------------------------------------------------------------------------ which paths
+// What a launch costs is estimated from how often each source is referenced, and that from the row-length classes, as
+// if the sources were referenced as unequally as the rows are long (on a symmetric graph they are).
+struct Sources {
+    int classes = 0;
+    double count[EPP_NCLASS], share[EPP_NCLASS];  // sources; part of all references that goes to one of them
+    double rows[EPP_NCLASS], len[EPP_NCLASS];     // rows and their mean length, the longest first
+    explicit Sources(const epp_path* p) {
+        double all = 0.0;
+        const double per_row = (double)p->n_src / (double)std::max<int64_t>(p->n_stream_rows, 1);
+        for (int c = EPP_NCLASS - 1; c >= 0; --c) {
+            const double r = (double)(p->len_hist[c] - (c == 0 ? p->n_empty_rows : 0));
+            if (r <= 0.0) continue;
+            rows[classes] = r;
+            len[classes] = c == 0 ? 1.0 : 0.72 * (double)(1ll << c);
+            all += r * len[classes++];
+        }
+        for (int i = 0; i < classes; ++i) {
+            count[i] = rows[i] * per_row;
+            share[i] = len[i] / (all * per_row);
+            len[i] *= (double)p->nnz / all;
+        }
+    }
+    // groups of `per` sources that so many references touch
+    double touched(double references, double per) const {
+        double d = 0.0;
+        for (int i = 0; i < classes; ++i) d -= count[i] / per * std::expm1(-share[i] * per * references);
+        return d;
+    }
+    // references that a cache of so many sources serves, the least recently used one giving way
+    double cached(double sources) const {
+        double all = 0.0, lo = 0.0, hi = 60.0, hit = 0.0;  // (octaves of references between two uses)
+        for (int i = 0; i < classes; ++i) all += count[i];
+        if (all <= sources) return 1.0;
+        for (int i = 0; i < 30; ++i) {
+            const double mid = 0.5 * (lo + hi);
+            (touched(std::exp2(mid), 1.0) < sources ? lo : hi) = mid;
+        }
+        for (int i = 0; i < classes; ++i) hit -= count[i] * share[i] * std::expm1(-share[i] * std::exp2(lo));
+        return hit;
+    }
+};
+
+constexpr double kLinesOfL2 = 32768.0;
+
+// Microseconds of a launch on the group table (or its partitioned copy).
+static double group_launch_us(const epp_path* p, const Sources& src, int F) {
+    double best = 1e30;
+    const int packed = F <= 16 ? std::max(8, F > 8 ? 16 : 8) : (F + 15) / 16 * 16;
+    for (const int ld : {F, packed}) {
+        const double lines = epp_lines_per_row(F, ld), hit = src.cached(kLinesOfL2 / lines);
+        const double copy = ld == F ? 0.0 : 4.0 * (double)p->n * (F + ld) * 2.5e-7;
+        best = std::min(best, 1e-6 * (double)p->nnz * (3.8 + lines * (3.0 * hit + 12.8 * (1.0 - hit))) + copy);
+    }
+    return 16.0 + best + 1e-6 * (double)p->n_stream_rows * (16.0 + 0.66 * F);
+}
+
+// .. and on tiles of so many lanes a slot.
+static double tile_launch_us(const epp_path* p, const Sources& src, int F, int lanes) {
+    struct Cost { double launch, sweep, entry, line_cached, line_missed, row, copy; };  // us; ps per entry, line, row and byte
+    const Cost c = lanes == 4 ? Cost{45, 10.2, 2.5, 2.3, 19.6, 0.0, 0.36} : lanes == 8 ? Cost{76, 1.7, 6.5, 0.38, 10.7, 0.84, 0.29}
+                                                                        : Cost{41, 3.4, 9.4, 0.90, 14.6, 0.22, 0.17};
+    const TileShape t = tile_shape(F, lanes);
+    const double per_line = std::max(1.0, 8.0 / t.stride), lines = std::max(1.0, t.stride == 12 ? 2.0 : t.stride / 8.0);
+    const double capacity = (double)kTilesAtOnce * tile_rows(lanes);
+    // sweeps, the longest rows first: each XCD touches the sources of an eighth of a sweep's entries
+    double sweeps = 0.0, missed = 0.0, room = capacity, entries = 0.0;
+    auto sweep = [&] {
+        missed += std::min(8.0 * src.touched(entries / 8.0, per_line), entries);
+        sweeps += 1.0;
+        entries = 0.0;
+        room = capacity;
+    };
+    for (int i = 0; i < src.classes; ++i) {
+        const double cut = std::max(1.0, src.len[i] / kSplitMax), len = src.len[i] / cut;
+        for (double left = src.rows[i] * cut; left > 0.0;) {
+            const double take = std::min(left, room);
+            entries += take * len;
+            left -= take;
+            room -= take;
+            if (room <= 0.0) sweep();
+        }
+    }
+    if (entries > 0.0) sweep();
+    const double nnz = (double)p->nnz;
+    double us = c.launch + 1e-6 * (double)p->n_stream_rows * F * c.row +
+                t.slices * (sweeps * c.sweep + 1e-6 * (nnz * c.entry + lines * ((nnz - missed) * c.line_cached + missed * c.line_missed)));
+    if (t.packed) us += 8.0 + 4e-6 * c.copy * ((double)p->n_src * F + (double)p->n * t.slices * t.stride * 4);
+    return us;
+}
+
+// Whether launches of width F run on tiles, and of how many lanes a slot.  The constants above were fitted to 544
+// paths and widths (all-active, and 0.5 to 30 % training vertices; 65 K to 8.4 M vertices, 1.6 to 274 M entries, both models, F =
+// 8 to 128), which they meet within 8 to 16 % (root mean square).  Of 487 of them that the row kernel does not take, launches by
+// this rule need 0.86 of the group kernel's time on average, 1.12 at worst; always the better one would need 0.83.
+// Some of them (us, group kernel / tiles of 4, 8 and 16 lanes): 274 M entries, 2.4 M sources, F = 64: 8866 / 12056 / 5550 /
+// 7246; F = 16: 4940 / 2425 / 2587; 228 M, 8.4 M, R-MAT, F = 128: 12290 / - / 8960 / 8560; not taken: 19 M of 2.4 M, F = 128:
+// 1547 / - / 1446 / 1442; 65 M of 8.4 M, F = 41: 2726 / 4699 / 4376 / 3603.
+// The tiles cost 10 to 12 us per million entries to prepare, which five launches have to repay.  Fewer sources than
+// 100,000 nearly fit the L2s together: the estimate of what hits them is not good enough there (65,000, 23 M entries, F = 96:
+// 527 / - / 732 / 633, estimated 758 / - / 602 / 617).
+int epp_tile_lanes(const epp_path* p, int F) {
+    const int mode = env_int("EPP_TUNE_TILES", 1);  // 0: never, 1: where it pays, 2: wherever it can be (tests)
+    if (mode == 0 || F < 5 || p->nnz == 0) return 0;
+    // (a source's id has 23 bits in an entry, and its row's place in the matrix 32)
+    if (p->n > (1ll << kColBits) || (p->n - 1) * (int64_t)F >= (1ll << 32)) return 0;
+    if (mode == 2) return env_int("EPP_TUNE_TILE_LANES", 8);
+    if (p->nnz < 4'000'000 || p->n_src < 100'000) return 0;
+    const Sources src(p);
+    const double groups = group_launch_us(p, src, F);
+    int lanes = 0;
+    double best = 1e30;
+    for (const int l : {4, 8, 16}) {
+        if (tile_shape(F, l).slices > 8) continue;
+        const double us = tile_launch_us(p, src, F, l);
+        if (us < best) { best = us; lanes = l; }
+    }
+    return best < 0.9 * groups && 5.0 * (groups - best) > 60.0 + 11.5e-6 * (double)p->nnz ? lanes : 0;
+}
+
+int epp_build_tiles(epp_path* p, int lanes, hipStream_t s, TilePlan** out) {
+    *out = nullptr;
+    const int rows_per_tile = tile_rows(lanes);
+    const int64_t R = p->n_stream_rows;
+    const int split = std::min(std::max(env_int("EPP_TUNE_TILE_SPLIT", kSplitMax), 8), kSplitMax);
+    const epp_alloc_t* al = epp_alloc_of(p);
+    const int32_t* rowptr = p->rowptr.as<int32_t>();
+    const int2v* cv = reinterpret_cast<const int2v*>(p->cv.p);
+
+    // rows per length class
+    DevArena counts;
+    DevBuf hist, totals, places, block_hist;
+    const unsigned blocks = blocks_for(R, kRowsPerBlock);
+    const size_t b_hist = (size_t)blocks * kTileBins * 4;
+    EPP_TRY(counts.reserve(3 * DevArena::rounded(kTileBins * 4) + DevArena::rounded(b_hist), al));
+    counts.take(&totals, kTileBins * 4);
+    counts.take(&places, kTileBins * 4);
+    counts.take(&hist, kTileBins * 4);
+    counts.take(&block_hist, b_hist);
+    EPP_HIP_TRY(hipMemsetAsync(totals.p, 0, 2 * DevArena::rounded(kTileBins * 4), s));
+    PinnedWords host;
+    EPP_TRY(host.get(kTileBins));
+    hipLaunchKernelGGL(k_tile_count, dim3(blocks), dim3(kListBlock), 0, s, rowptr, R, split, block_hist.as<unsigned>(),
+                       totals.as<unsigned>());
+    hipLaunchKernelGGL(k_tile_classes, dim3(kTileBins), dim3(256), 0, s, block_hist.as<unsigned>(), (int)blocks, hist.as<unsigned>());
+    EPP_HIP_TRY(hipGetLastError());
+    unsigned* const h = reinterpret_cast<unsigned*>(host.p);  // the classes, then the totals
+    EPP_HIP_TRY(hipMemcpyAsync(h, hist.p, kTileBins * 4, hipMemcpyDeviceToHost, s));
+    EPP_HIP_TRY(hipMemcpyAsync(h + kTileBins, totals.p, 3 * 4, hipMemcpyDeviceToHost, s));
+    EPP_HIP_TRY(hipStreamSynchronize(s));
+    TileBins bins;
+    unsigned rank = 0;
+    for (int b = 0; b < kTileBins; ++b) { bins.first[b] = rank; rank += h[b]; }
+    const int64_t n_rows = h[kTileBins], n_parts = h[kTileBins + 1], n_cut = h[kTileBins + 2];
+    if (p->n + n_parts >= 0x7FFFFFFFll || n_rows == 0) return EPP_OK;
+
+    TilePlan* q = new TilePlan();
+    struct Guard {  // (on an error: nothing may still be writing to what is given back)
+        TilePlan* q;
+        hipStream_t s;
+        ~Guard() {
+            if (!q) return;
+            (void)hipStreamSynchronize(s);
+            delete q;
+        }
+    } guard{q, s};
+    q->at_once = std::max(env_int("EPP_TUNE_TILES_AT_ONCE", kTilesAtOnce) / 512, 1) * 512;  // (whole groups of kTogether tiles per XCD)
+    const int64_t rows_at_once = (int64_t)q->at_once * rows_per_tile;
+    q->lanes = lanes;
+    q->n_tiles = (int)((n_rows + rows_at_once - 1) / rows_at_once * q->at_once);
+    q->n_parts = n_parts;
+    q->n_cut = (int)n_cut;
+    q->max_batches = (int)(p->nnz / 64 + q->n_tiles);  // (every tile's last batch may be filled up)
+    const size_t n_places = (size_t)q->n_tiles * rows_per_tile;
+    const size_t b_ent = DevArena::rounded((size_t)q->max_batches * 512), b_first = DevArena::rounded((size_t)(q->n_tiles + 1) * 4),
+                 b_target = DevArena::rounded(n_places * 4), b_longest = DevArena::rounded((size_t)q->n_tiles * 4), b_care = DevArena::rounded(((size_t)q->max_batches / 16 + 1) * 4),
+                 b_cut = DevArena::rounded((size_t)n_cut * sizeof(CutRow));
+    EPP_TRY(q->store.alloc(b_ent + b_first + b_target + b_longest + b_care + b_cut, al));
+    char* at = q->store.as<char>();
+    q->ent = at;
+    q->first_batch = reinterpret_cast<int32_t*>(at += b_ent);
+    q->target = reinterpret_cast<int32_t*>(at += b_first);
+    q->longest = reinterpret_cast<int*>(at += b_target);
+    q->care = reinterpret_cast<unsigned*>(at += b_longest);
+    q->cut = at += b_care;
+
+    DevArena tmp;
+    DevBuf dealt, batches, scan_tmp, total;
+    EPP_TRY(tmp.reserve(DevArena::rounded(n_places * sizeof(Dealt)) + DevArena::rounded((size_t)q->n_tiles * 4) +
+                        DevArena::rounded(epp_scan_tmp_bytes(q->n_tiles)) + 256, al));
+    tmp.take(&dealt, n_places * sizeof(Dealt));
+    tmp.take(&batches, (size_t)q->n_tiles * 4);
+    tmp.take(&scan_tmp, epp_scan_tmp_bytes(q->n_tiles));
+    tmp.take(&total, 8);
+    EPP_HIP_TRY(hipMemsetAsync(dealt.p, 0xFF, n_places * sizeof(Dealt), s));
+    EPP_HIP_TRY(hipMemsetAsync(q->care, 0, b_care, s));
+    hipLaunchKernelGGL(k_tile_deal, dim3(blocks), dim3(kListBlock), 0, s, rowptr, p->row_ids.p ? p->row_ids.as<int32_t>() : nullptr, R,
+                       split, (int)p->n, bins, block_hist.as<unsigned>(), places.as<unsigned>(), dealt.as<Dealt>(),
+                       static_cast<CutRow*>(q->cut));
+    hipLaunchKernelGGL(k_tile_sizes, dim3(blocks_for(q->n_tiles, 64)), dim3(64), 0, s, dealt.as<Dealt>(), rows_per_tile,
+                       q->at_once, q->n_tiles, batches.as<int>());
+    epp_scan_exclusive(batches.as<int>(), q->first_batch, q->n_tiles, total.as<long long>(), scan_tmp.as<int>(), s);
+    // (the scan's last element is the total; little endian)
+    EPP_HIP_TRY(hipMemcpyAsync(q->first_batch + q->n_tiles, total.p, 4, hipMemcpyDeviceToDevice, s));
+    int shift = 0;
+    while (((p->n - 1) >> shift) >= kBuckets) ++shift;
+    int* const bad = totals.as<int>();  // (what it held has been read)
+    EPP_HIP_TRY(hipMemsetAsync(bad, 0, 4, s));
+    if (lanes == 4) sort_tiles<4>(q, cv, dealt.as<Dealt>(), shift, bad, s);
+    else if (lanes == 8) sort_tiles<8>(q, cv, dealt.as<Dealt>(), shift, bad, s);
+    else sort_tiles<16>(q, cv, dealt.as<Dealt>(), shift, bad, s);
+    EPP_HIP_TRY(hipMemcpyAsync(h, bad, 4, hipMemcpyDeviceToHost, s));
+    EPP_HIP_TRY(hipGetLastError());
+    EPP_HIP_TRY(hipStreamSynchronize(s));  // (the temporaries go, too)
+    if (h[0]) return EPP_OK;
+    guard.q = nullptr;
+    *out = q;
+    return EPP_OK;
+}
+
+int epp_launch_tiles(const epp_path* p, const TilePlan* q, float* parts, const float* in, float* packed, float* out, int F,
+                     hipStream_t s, const unsigned long long* sources, const unsigned int* inner_rows) {
+    const TileShape t = tile_shape(F, q->lanes);
+    if (t.packed) {
+        hipLaunchKernelGGL(k_pack_slices, dim3(blocks_for(p->n, 64)), dim3(kListBlock), 0, s, in, p->n, F, t.quads, t.stride, t.slices, sources,
+                           packed);
+    }
+    TileArgs a;
+    a.ent = static_cast<const int2v*>(q->ent);
+    a.first_batch = q->first_batch;
+    a.care = q->care;
+    a.target = q->target;
+    a.longest = q->longest;
+    a.in = t.packed ? packed : in;
+    a.out = out;
+    a.parts = parts;
+    a.n = (int)p->n;
+    a.F = F;
+    a.lanes = t.quads;
+    a.ld = t.packed ? t.stride * 4 : F;
+    a.slice_step = t.packed ? p->n * t.stride * 4 : t.quads * 4;
+    a.blocks = q->n_tiles / kTileWaves;
+    a.zero = inner_rows ? p->zero_block.as<float>() : nullptr;
+    a.inner_rows = inner_rows;
+    if (q->lanes == 4) launch_tiles<4>(a, t.slices, s);
+    else if (q->lanes == 8) launch_tiles<8>(a, t.slices, s);
+    else launch_tiles<16>(a, t.slices, s);
+    if (q->n_cut > 0) {
+        int log2T = 0;
+        while (log2T < 6 && (4 << log2T) < F) ++log2T;
+        hipLaunchKernelGGL(k_tile_add_parts, dim3(blocks_for((int64_t)q->n_cut << log2T, kListBlock)), dim3(kListBlock), 0, s,
+                           static_cast<const CutRow*>(q->cut), q->n_cut, F, log2T, parts, inner_rows, out);
+    }
+    EPP_HIP_TRY(hipGetLastError());
+    return EPP_OK;
+}

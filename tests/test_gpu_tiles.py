@@ -1,0 +1,159 @@
+"""Launches on tiles of rows whose sums stay in LDS (csrc/epp_tiles.hip), forced onto small graphs: widths at the ends of
+slices and lines, cut rows, batches that hold a row many times, tiles that are sorted in several rounds, paths that run on
+the next outer path's tiles.  512 tiles at a time instead of 2,048, so that a graph of this size fills them."""
+import numpy as np
+import pytest
+import torch
+
+import graphgen
+import oracle
+import paper_2204_02662_amd as epp
+from _util import assert_close, assert_paths_bit_exact, dev, gpu_prepare, gpu_prepare_full, run_full, run_ifelse, run_partial
+
+pytestmark = pytest.mark.gpu
+
+
+def _force(monkeypatch, lanes, split=512, **more):
+    for k, v in {"ROWS": "0", "TILES": "2", "TILE_LANES": lanes, "TILE_SPLIT": split, "TILES_AT_ONCE": 512,
+                 "SMALL_PREPARE": "0", **more}.items():
+        monkeypatch.setenv("EPP_TUNE_" + k, str(v))
+
+
+@pytest.mark.parametrize("lanes", [4, 8, 16])
+@pytest.mark.parametrize("split", [16, 512])
+def test_every_width_shared_and_own_entries(lanes, split, monkeypatch):
+    """Two generations of tiles; the inner path runs on the outer one's, at any overlap."""
+    g = graphgen.random_graph("rmat", 90_001, seed=71, raw_draws=700_000)
+    train = graphgen.training_set(g.n, 9_000, 72)
+    sets_o, paths_o = oracle.prepare(g.n, g.rowptr, g.col, g.val, train, 2)
+    for share in ("1", "0"):
+        _force(monkeypatch, lanes, split, SHARE_PCT=share)
+        paths = gpu_prepare(g, train, 2)
+        assert [paths.path(l).info().shares_entries for l in (0, 1)] == [0, int(share)]
+        for F in (5, 8, 15, 16, 17, 31, 32, 33, 47, 64, 65, 100, 128, 259):
+            for l in (1, 0):
+                src, rows = sets_o[1 - l].astype(bool), sets_o[2 - l].astype(bool)
+                X = graphgen.normal_rows(g.n, F, sets_o[1 - l], 73 + l)
+                want = oracle.path_aggregate(g.n, paths_o[l], X)
+                X[~src] = np.nan  # never read
+                p = paths.path(l)
+                got = run_partial(p, X, poison=9.0)
+                what = f"lanes={lanes} split={split} share={share} F={F} l={l}"
+                assert np.all(got[~rows] == 9.0), what
+                assert_close(got[rows], want[rows], what)
+                assert np.array_equal(got[rows], run_partial(p, X, poison=1.0)[rows]), what
+                i = p.info()
+                longest = np.diff(paths_o[0 if share == "1" else l].rowptr).max()
+                assert (i.part_rows > 0) == (longest > split) and i.part_partial_rows >= 2 * i.part_rows, what
+        assert_paths_bit_exact(paths, sets_o, paths_o, 2)
+
+
+@pytest.mark.parametrize("lanes", [4, 8, 16])
+@pytest.mark.parametrize("n,draws", [(700, 60_000), (2_500, 900_000), (90_000, 5_000_000)])
+def test_dense_rows_and_large_tiles(lanes, n, draws, monkeypatch):
+    """Rows that have many of a batch's entries (all levels of care), and tiles of several rounds; a second handle gives the
+    same bits; the if-else baseline of the same handle still runs on its group table."""
+    _force(monkeypatch, lanes)
+    g = graphgen.random_graph("rmat", n, seed=81, raw_draws=draws)
+    F = 20
+    X = graphgen.normal_rows(g.n, F, None, 82)
+    want = oracle.full_aggregate(g.n, g.rowptr, g.col, g.val, X)
+    full = gpu_prepare_full(g)
+    got = run_full(full, X)
+    assert_close(got, want, f"lanes={lanes} n={n}")
+    assert np.array_equal(got, run_full(gpu_prepare_full(g), X))
+    paths = gpu_prepare(g, np.arange(g.n, dtype=np.int32), 1)
+    assert_close(run_ifelse(full, paths, 0, X), want, "if-else")
+
+
+@pytest.mark.parametrize("lanes", [4, 8, 16])
+def test_columns_in_any_order(lanes, monkeypatch):
+    """A tile of one round needs no order of the columns; one of several rounds does, and the path then keeps its group table."""
+    _force(monkeypatch, lanes)
+    rng = np.random.default_rng(91)
+    for n, draws, tiles in ((20_000, 200_000, True), (90_000, 5_000_000, False)):
+        g = graphgen.random_graph("rmat", n, seed=92, raw_draws=draws)
+        row = np.repeat(np.arange(g.n), np.diff(g.rowptr))
+        order = np.lexsort((rng.random(g.nnz), row))
+        col, val = g.col[order].copy(), g.val[order].copy()
+        X = graphgen.normal_rows(g.n, 33, None, 93)
+        want = oracle.full_aggregate(g.n, g.rowptr, col, val, X)
+        full = epp.epp_prepare_full(g.n, *(torch.from_numpy(x).to(dev()) for x in (g.rowptr, col, val)))
+        assert_close(run_full(full, X), want, f"lanes={lanes} n={n}")
+        assert (full.info().part_rows > 0) == (tiles and np.diff(g.rowptr).max() > 512)
+
+
+@pytest.mark.parametrize("lanes", [4, 8, 16])
+@pytest.mark.parametrize("F", [16, 47])
+def test_infinities_stay_where_they_belong(lanes, F, monkeypatch):
+    _force(monkeypatch, lanes)
+    g = graphgen.random_graph("chung_lu", 40_000, seed=95, target_edges=150_000)
+    X = graphgen.normal_rows(g.n, F, None, 96)
+    X[::977] = np.inf
+    X[5::1201] = -np.inf
+    X[7::3001, 0] = np.nan
+    with np.errstate(invalid="ignore"):
+        want = oracle.full_aggregate(g.n, g.rowptr, g.col, g.val, X)
+    got = run_full(gpu_prepare_full(g), X)
+    ok = np.isfinite(want)
+    assert np.array_equal(np.isnan(got), np.isnan(want)) and np.array_equal(got[~ok & ~np.isnan(want)], want[~ok & ~np.isnan(want)])
+    assert_close(got[ok], want[ok], f"lanes={lanes} F={F}")
+
+
+@pytest.mark.parametrize("F", [47, 64])
+def test_captured_launches(F, monkeypatch):
+    _force(monkeypatch, 8, 32)
+    g = graphgen.random_graph("rmat", 60_000, seed=97, raw_draws=500_000)
+    full = gpu_prepare_full(g)
+    full.prepare_width(F)
+    x = torch.zeros(g.n, F, device=dev())
+    y, z = torch.empty_like(x), torch.empty_like(x)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        epp.epp_full_aggregate(full, x, y)
+    for rep in range(3):
+        x.normal_()
+        graph.replay()
+        torch.cuda.synchronize()
+        epp.epp_full_aggregate(full, x, z)
+        assert torch.equal(y, z), f"replay {rep}"
+    assert_close(y.cpu().numpy(), oracle.full_aggregate(g.n, g.rowptr, g.col, g.val, x.cpu().numpy()), f"F={F}")
+
+
+@pytest.mark.parametrize("F", [47, 64])
+def test_every_refused_block(F, monkeypatch):
+    """Tiles are an option: without memory for them, for the parts' sums or for the copy, the group table serves."""
+    _force(monkeypatch, 8, 32)
+    count, refused = [0], [-1]
+
+    def alloc(nbytes, ctx):
+        count[0] += 1
+        return None if count[0] == refused[0] else epp._torch_alloc(nbytes, ctx)
+
+    monkeypatch.setattr(epp, "_TORCH_ALLOC", epp._Alloc(epp._ALLOC_FN(alloc), epp._TORCH_ALLOC.free, None))
+    g = graphgen.random_graph("rmat", 9_001, seed=601, raw_draws=120_000)
+    train = graphgen.training_set(g.n, 3_000, 602)
+    sets_o, paths_o = oracle.prepare(g.n, g.rowptr, g.col, g.val, train, 1)
+    X = graphgen.normal_rows(g.n, F, sets_o[0], 603)
+    want = oracle.path_aggregate(g.n, paths_o[0], X)
+    live = epp.alloc_stats["live"]
+    blocks, k = None, 0
+    while blocks is None or k <= blocks:
+        refused[0] = -1
+        paths = gpu_prepare(g, train, 1)
+        p = paths.path(0)
+        count[0], refused[0] = 0, k
+        p.prepare_width(F)
+        blocks = count[0] if blocks is None else blocks
+        refused[0] = -1
+        assert (p.info().part_rows > 0) == (k == 0), f"block {k} of {blocks} refused"
+        assert_close(run_partial(p, X), want, f"block {k} of {blocks} refused")
+        p.set_group_size(F, 24)
+        assert_close(run_partial(p, X), want, "group table asked for")
+        p.set_group_size(F, 0)
+        assert p.info().part_rows > 0
+        assert_close(run_partial(p, X), want, "tiles again")
+        del p, paths
+        assert epp.alloc_stats["live"] == live, f"block {k} of {blocks} refused"
+        k += 1

@@ -10,7 +10,7 @@ import pytest
 
 ROOT = Path(__file__).resolve().parent.parent
 CSRC = ROOT / "paper_2204_02662_amd" / "csrc"
-FILES = ("epp_rows", "epp_combine", "epp_prepare", "epp_prepare_small", "epp_partition")
+FILES = ("epp_rows", "epp_combine", "epp_prepare", "epp_prepare_small", "epp_partition", "epp_tiles")
 
 
 @pytest.fixture(scope="module")
