@@ -3,7 +3,7 @@
 //
 // The group kernel (epp_aggregate.hip) takes entries row after row, so every XCD gathers from everywhere at any time and
 // an L2 of 4 MB serves next to nothing (2.4 M sources, F = 64: 11 % of the lines); the rest runs at the 60 G lines/s
-// that the fabric gives.  Here a wavefront owns a tile of up to 155 rows, whose sums lie in LDS, and takes the
+// that the fabric gives.  Here a wavefront owns a tile of up to 159 rows, whose sums lie in LDS, and takes the
 // tile's entries in the order of their sources.  The 256 wavefronts of an XCD therefore sweep the source matrix
 // together, and a source row that one of them has fetched is still in L2 when the others come to it.
 //
@@ -17,13 +17,14 @@
 //     tile.  A tile's list is cut into batches of 64 entries, each sorted by row and dealt to the slots so that
 //     one step of the wavefront never touches a row twice: then LDS is read, added to and written without atomics
 //     (ds_add_f32 takes 190 cycles a wavefront here), in an order that depends on the path alone.
-//   * Eight wavefronts of 155 rows fill a CU's LDS.  Sixteen of 75 drift apart (26 % instead of 46 % of the lines in
+//   * Eight wavefronts of 159 rows fill a CU's LDS.  Sixteen of 79 drift apart (26 % instead of 46 % of the lines in
 //     L2: 3.9 ms), four are bound by the instructions of one wavefront per SIMD.
 //   * Wide rows are taken in slices, one after the other: the narrower the slice, the more rows fit LDS and the more sources L2,
 //     at the price of reading the entries once per slice.
 
 #include <cmath>
 #include <cstdlib>
+#include <type_traits>
 
 #include "epp_internal.h"
 
@@ -46,7 +47,7 @@ typedef float float4v __attribute__((ext_vector_type(4)));
 typedef float float4u __attribute__((ext_vector_type(4), aligned(4)));  // global accesses need no more
 
 // LANES lanes of 16 bytes per slot: rows whose sums a wavefront keeps (one more takes what fills up a batch)
-constexpr int tile_rows(int lanes) { return lanes == 4 ? 255 : lanes == 8 ? 155 : 77; }
+constexpr int tile_rows(int lanes) { return lanes == 4 ? 255 : lanes == 8 ? 159 : 79; }
 // How a batch is taken, by its two bits of `care`: two steps at a time (0 turns), or one at a time in so many turns.
 constexpr int care_turns(int lanes, unsigned care) {
     return lanes == 4 ? (care == 0 ? 1 : care == 1 ? 2 : care == 2 ? 4 : 16)
@@ -267,8 +268,8 @@ __global__ __launch_bounds__(kSortThreads, 4) void k_tile_sort(const int2v* __re
                                                                int32_t* __restrict__ target, int* __restrict__ longest,
                                                                int2v* __restrict__ ent, unsigned int* __restrict__ care,
                                                                int* __restrict__ bad) {
-    constexpr int kRows = tile_rows(LANES), kSlots = 64 / LANES, kSteps = LANES;
-    static_assert(kRows < 256 && kRows < kSortThreads, "");
+    constexpr int kRows = tile_rows(LANES);
+    static_assert(kRows < 256 && kRows < kSortThreads && kRows % 4 == 3, "");
     __shared__ int2v buf[kSortMax + 64];
     // entries per range: of the round and of two wavefronts a word, 16 bits each, then their places; of the tile, up to the range's end
     __shared__ unsigned count[kSortWaves / 2][kBuckets];
@@ -477,8 +478,6 @@ __global__ __launch_bounds__(kSortThreads, 4) void k_tile_sort(const int2v* __re
             const int4 n = *quad;
             int most = max(max(n.x, n.y), n.z);
             if (lane * 4 + 3 != kRows) most = max(most, n.w);
-            static_assert(kRows % 4 == 3 || kRows == 77, "");
-            if (kRows == 77 && lane == 19) most = n.x;
             const int sum = n.x + n.y + n.z + n.w;
             const int first = sum_up_to_lane(sum) - sum;
             *quad = int4{first, first + n.x, first + n.x + n.y, first + n.x + n.y + n.z};
@@ -491,7 +490,7 @@ __global__ __launch_bounds__(kSortThreads, 4) void k_tile_sort(const int2v* __re
                 if (__ballot(most > care_limit(LANES, c))) level = c + 1;
             const int b = done + i;
             if (level && lane == 0) atomicOr(&care[b >> 4], level << (2 * (b & 15)));
-            __builtin_nontemporal_store(x, ent + (int64_t)b * 64 + (place % kSteps) * kSlots + place / kSteps);
+            __builtin_nontemporal_store(x, ent + (int64_t)b * 64 + place);
         }
         if (last) return;
         done += batches;
@@ -568,17 +567,16 @@ __global__ __launch_bounds__(kListBlock) void k_pack_slices(const float* __restr
 // chain of 512 would be 0.99 to 1.6 of it.  Adding up in LDS alone would be no faster (within 3 %, the spread of the runs).
 template <int LANES, bool INNER>
 __global__ __launch_bounds__(kTileWaves * 64, 2) void k_aggregate_tiles(TileArgs a) {
-    constexpr int kRows = tile_rows(LANES), kSlots = 64 / LANES, kSteps = LANES, kDepth = LANES == 4 ? 2 : 0;
+    constexpr int kRows = tile_rows(LANES), kSlots = 64 / LANES, kSteps = LANES;
+    constexpr int kDepth = LANES == 4 ? 2 : 0;
     constexpr int kTakes = std::max(kDepth, 1);
     typedef __attribute__((address_space(1))) const float4u* gvec_ptr;
     __shared__ float4v sums_all[kTileWaves][(kRows + 1) * LANES];
-    __shared__ int2v stage_all[kTileWaves][64];
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     const int slot = lane / LANES, l = lane % LANES;
     const int slice = blockIdx.x / a.blocks;
     const int tile = (blockIdx.x - slice * a.blocks) * kTileWaves + wave;
     float4v* __restrict__ sums = sums_all[wave];
-    int2v* __restrict__ stage = stage_all[wave];
     const int f = l < a.lanes ? (slice * a.lanes + l) * 4 : a.F;  // (a lane without a share reads its neighbour's)
     const int b0 = a.first_batch[tile], b1 = a.first_batch[tile + 1];
     if (b0 == b1) return;  // (its places have no rows; nothing below waits for another wavefront)
@@ -593,13 +591,25 @@ __global__ __launch_bounds__(kTileWaves * 64, 2) void k_aggregate_tiles(TileArgs
     auto cares = [&](int b) { return a.care[(b0 + min(b, last)) >> 4]; };
     struct { float4u x[kSteps]; float w[kSteps]; unsigned at[kSteps]; unsigned care; } flight[kTakes];
     int2v ahead = entries(0);
+    int2v here;
     auto put = [&](int b) {  // the entries of batch b, and loads those of the next
-        __builtin_amdgcn_wave_barrier();
-        stage[lane] = ahead;
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
+        here = ahead;
         ahead = entries(b + 1);
         __builtin_amdgcn_sched_barrier(0);  // (before the gathers that come next, so that waiting for it is not waiting for them)
+    };
+    // Step j's entry of a lane's slot: the slot's lane j has it.  (Handed on through LDS, as both its words were at first, the
+    // entries took a place there that rows can use, and 2 to 9 % of a launch: 94 M entries, 250 K sources, F = 32, 8 lanes
+    // 830 -> 760 us; F = 64, 16 lanes 1305 -> 1225; 140 M, 2.4 M sources, F = 64: 3170 -> 3080.)
+    auto entry = [&](auto J) {
+        constexpr int j = decltype(J)::value;
+        auto word = [&](int x) {
+            if constexpr (LANES == 4) return __builtin_amdgcn_update_dpp(0, x, j * 0x55, 0xF, 0xF, true);  // quad_perm:[j,j,j,j]
+            else if constexpr (LANES == 8) {
+                const int low = __builtin_amdgcn_update_dpp(0, x, 0x150 + j, 0xF, 0xF, true);  // row_newbcast:j, then the upper half of a row
+                return __builtin_amdgcn_update_dpp(low, x, 0x158 + j, 0xF, 0xC, false);
+            } else return __builtin_amdgcn_update_dpp(0, x, 0x150 + j, 0xF, 0xF, true);
+        };
+        return int2v{word(here.x), word(here.y)};
     };
     auto gather = [&](auto& fl, int j, int2v e) {
         fl.at[j] = (((unsigned)e.x >> kColBits) & 255u) * LANES + l;
@@ -626,17 +636,27 @@ __global__ __launch_bounds__(kTileWaves * 64, 2) void k_aggregate_tiles(TileArgs
         for (int i = 0; i < 4; ++i) sum[i] = fmaf(fl.w[j], fl.x[j][i], sum[i]);
         sums[fl.at[j]] = sum;
     };
+    auto for_steps = [&](auto f) {  // for the first half of them, a constant each
+        f(std::integral_constant<int, 0>{});
+        f(std::integral_constant<int, 1>{});
+        if constexpr (kSteps >= 8) { f(std::integral_constant<int, 2>{}); f(std::integral_constant<int, 3>{}); }
+        if constexpr (kSteps >= 16) {
+            f(std::integral_constant<int, 4>{});
+            f(std::integral_constant<int, 5>{});
+            f(std::integral_constant<int, 6>{});
+            f(std::integral_constant<int, 7>{});
+        }
+    };
     auto take = [&](int b, auto& fl) {
         const unsigned how = __builtin_amdgcn_readfirstlane(fl.care >> (2 * ((b0 + b) & 15))) & 3u;
         put(b + kDepth);
         fl.care = cares(b + kTakes);
         constexpr int kHalf = kSteps / 2;
         if constexpr (kDepth == 0) {
-#pragma unroll
-            for (int j = 0; j < kHalf; ++j) {
-                gather(fl, j, stage[j * kSlots + slot]);
-                gather(fl, j + kHalf, stage[(j + kHalf) * kSlots + slot]);
-            }
+            for_steps([&](auto J) {
+                gather(fl, J, entry(J));
+                gather(fl, J + kHalf, entry(std::integral_constant<int, J + kHalf>{}));
+            });
         }
         const int turns = how == 0 ? 1 : how == 1 ? care_turns(LANES, 1) : how == 2 ? care_turns(LANES, 2) : care_turns(LANES, 3);
         const int mine = slot & (turns - 1);
@@ -647,10 +667,8 @@ __global__ __launch_bounds__(kTileWaves * 64, 2) void k_aggregate_tiles(TileArgs
                 __builtin_amdgcn_wave_barrier();
             }
         };
-#pragma unroll
-        for (int j = 0; j < kHalf; ++j) {
-            int2v e0, e1;
-            if constexpr (kDepth > 0) { e0 = stage[j * kSlots + slot]; e1 = stage[(j + kHalf) * kSlots + slot]; }
+        for_steps([&](auto J) {
+            constexpr int j = decltype(J)::value;
             if (how != 0) {
                 in_turns(j);
                 in_turns(j + kHalf);
@@ -668,19 +686,19 @@ __global__ __launch_bounds__(kTileWaves * 64, 2) void k_aggregate_tiles(TileArgs
             }
             if constexpr (kDepth > 0) {
                 __builtin_amdgcn_sched_barrier(0);  // (the gathers go to the registers that this has freed)
-                gather_two(fl, j, e0, e1);
+                gather_two(fl, j, entry(J), entry(std::integral_constant<int, j + kHalf>{}));
             }
-        }
+        });
     };
 #pragma unroll
     for (int d = 0; d < kTakes; ++d) {
         flight[d].care = cares(d);
         if (kDepth == 0) continue;
         put(d);
-#pragma unroll
-        for (int j = 0; j < kSteps / 2; ++j) gather_two(flight[d], j, stage[j * kSlots + slot], stage[(j + kSteps / 2) * kSlots + slot]);
+        for_steps([&](auto J) { gather_two(flight[d], J, entry(J), entry(std::integral_constant<int, J + kSteps / 2>{})); });
     }
-    constexpr int kOwn = (kRows + kSlots - 1) / kSlots;
+    constexpr int kOwn = (kRows + 1) / kSlots;
+    static_assert(kOwn * kSlots == kRows + 1, "");
     float4v whole[kOwn];
 #pragma unroll
     for (int i = 0; i < kOwn; ++i) whole[i] = float4v{};
@@ -696,7 +714,6 @@ __global__ __launch_bounds__(kTileWaves * 64, 2) void k_aggregate_tiles(TileArgs
         __builtin_amdgcn_wave_barrier();
 #pragma unroll
         for (int i = 0; i < kOwn; ++i) {
-            if ((i + 1) * 64 > (kRows + 1) * LANES && lane + i * 64 >= (kRows + 1) * LANES) continue;
             whole[i] += sums[lane + i * 64];
             sums[lane + i * 64] = float4v{};
         }
