@@ -83,7 +83,7 @@ int prepare_width(epp_path* self, int F, hipStream_t s, epp_path::WidthCfg** out
         w->part = nullptr;
         w->tiles = nullptr;
         w->packed = nullptr;
-        if (w->forced_gs <= 0) EPP_TRY(prepare_tiles(p, w, s));
+        if (w->forced_gs <= 0 && !w->rows) EPP_TRY(prepare_tiles(p, w, s));
         if (w->tiles && !p->all_rows) {
             w->prepared = true;
             if (out) *out = w;

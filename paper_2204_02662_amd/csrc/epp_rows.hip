@@ -14,8 +14,10 @@
 //     front of the grid; a second kernel adds the chunks' sums.
 // The order of the additions depends on the path and the width only: equal inputs give equal bits.
 //
-// Measured (us, rows / groups): 7,107 entries in 1,700 rows, F = 16: 5.5 / 10.6; 44,405 in 14,925, F = 64:
-// 10.3 / 14.9; 1.3 M in 322,705, F = 16: 33.9 / 58.7; 4.2 M in 100,000 (longest 43,347), F = 4: 35.6 / 119.
+// Bound by the address units where the sources lie in L2: a slot's pairs are therefore loaded by its lanes, one each, and handed
+// on between them; every lane used to load all four (us, before / now / groups: 1.3 M entries, 60,000 sources, F = 16: 27.6 /
+// 24.6 / 29.2, F = 32: 34.4 / 29.0 / 36.1; 7.1 M, 1.1 M sources, F = 16: 120 / 103 / 115; 13,938, 2,708 sources, F = 16:
+// 7.4 / 6.8 / 12.2; 4.6 M, 89,000, F = 4: 37 / 36 / 50).
 
 #include <cstdlib>
 
@@ -76,23 +78,49 @@ struct RowArgs {
     const unsigned int* only;    // bitmap of the inner path's rows
 };
 
+// Entry u of a step, of which every lane of a slot has loaded its share: lane i of the slot's first
+// four those numbered i, i + 4, ..
+template <int LOG2T, int N>
+__device__ __forceinline__ int2v step_entry(const int2v (&mine)[N], int u) {
+    if constexpr (LOG2T == 0) return mine[u];
+    else if constexpr (LOG2T == 1) {  // (two slots in four lanes)
+        const int2v e = mine[u >> 1];
+        return u & 1 ? int2v{__builtin_amdgcn_mov_dpp(e.x, 0xF5, 0xF, 0xF, true), __builtin_amdgcn_mov_dpp(e.y, 0xF5, 0xF, 0xF, true)}
+                     : int2v{__builtin_amdgcn_mov_dpp(e.x, 0xA0, 0xF, 0xF, true), __builtin_amdgcn_mov_dpp(e.y, 0xA0, 0xF, 0xF, true)};
+    } else {
+        const int2v e = mine[0];
+        switch (u) {  // quad_perm:[u,u,u,u]
+            case 0: return int2v{__builtin_amdgcn_mov_dpp(e.x, 0x00, 0xF, 0xF, true), __builtin_amdgcn_mov_dpp(e.y, 0x00, 0xF, 0xF, true)};
+            case 1: return int2v{__builtin_amdgcn_mov_dpp(e.x, 0x55, 0xF, 0xF, true), __builtin_amdgcn_mov_dpp(e.y, 0x55, 0xF, 0xF, true)};
+            case 2: return int2v{__builtin_amdgcn_mov_dpp(e.x, 0xAA, 0xF, 0xF, true), __builtin_amdgcn_mov_dpp(e.y, 0xAA, 0xF, 0xF, true)};
+            default: return int2v{__builtin_amdgcn_mov_dpp(e.x, 0xFF, 0xF, 0xF, true), __builtin_amdgcn_mov_dpp(e.y, 0xFF, 0xF, 0xF, true)};
+        }
+    }
+}
+
 // acc = sum of the entries j0, j0 + 1, .. (U at a time, `step` apart) of [j0, p1).  The pairs of the
-// next step are fetched while the rows of this one are on their way.
+// next step are fetched while the rows of this one are on their way, each by one lane of the slot, which hands it to the others.
 //
 // A step that reaches past p1 gathers the last entry again, with weight zero, and one that belongs to the outer
 // path only gathers zeros.  That adds zero, or NaN where the row or the weight holds an infinity.  EXACT clears both
 // factors in the last step, which costs a path of 7,000 entries 0.2 us of 4.1; without it the caller looks at
 // the sums, and forms those that are not numbers again from the slot's own entries alone (add_own_entries).
-template <int VEC, int U, bool INNER, bool EXACT>
+template <int VEC, int LOG2T, int U, bool INNER, bool EXACT>
 __device__ __forceinline__ void add_entries(const RowArgs& a, const float* __restrict__ src, int j0, int p1, int step,
                                             float (&acc)[VEC]) {
 #pragma unroll
     for (int i = 0; i < VEC; ++i) acc[i] = 0.0f;
     if (j0 >= p1) return;
-    int2v e[U];
+    constexpr int kSharers = LOG2T >= 2 ? 4 : 1 << LOG2T, kMine = U / kSharers;
+    static_assert(U == 4, "one step of a slot is what four lanes load");
+    const int q = (int)threadIdx.x & (kSharers - 1);
+    int2v mine[kMine];
 #pragma unroll
-    for (int u = 0; u < U; ++u) e[u] = a.cv[min(j0 + u, p1 - 1)];
+    for (int k = 0; k < kMine; ++k) mine[k] = a.cv[min(j0 + k * kSharers + q, p1 - 1)];
     for (int j = j0; j < p1; j += step) {
+        int2v e[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) e[u] = step_entry<LOG2T>(mine, u);
         float x[U][VEC];
         float w[U];
 #pragma unroll
@@ -105,7 +133,7 @@ __device__ __forceinline__ void add_entries(const RowArgs& a, const float* __res
         }
         if (j + step < p1) {
 #pragma unroll
-            for (int u = 0; u < U; ++u) e[u] = a.cv[min(j + step + u, p1 - 1)];
+            for (int k = 0; k < kMine; ++k) mine[k] = a.cv[min(j + step + k * kSharers + q, p1 - 1)];
         }
         if (EXACT && j + U > p1) {
             asm volatile("");  // (keeps the branch)
@@ -160,7 +188,7 @@ __device__ __forceinline__ void sum_by_workgroup(const RowArgs& a, int q0, int q
         const bool fok = f0 + t * VEC < a.F;
         const int f = fok ? min(f0 + t * VEC, a.F - VEC) : 0;
         float acc[VEC];
-        add_entries<VEC, kU, INNER, true>(a, a.in + f, q0 + slot * kU, q1, (kBlock >> LOG2T) * kU, acc);
+        add_entries<VEC, LOG2T, kU, INNER, true>(a, a.in + f, q0 + slot * kU, q1, (kBlock >> LOG2T) * kU, acc);
 #pragma unroll
         for (int d = T; d < 64; d <<= 1) {
 #pragma unroll
@@ -216,7 +244,7 @@ __global__ __launch_bounds__(kBlock, 7) void k_aggregate_rows(RowArgs a) {
         const bool fok = f0 + t * VEC < a.F;
         const int f = fok ? min(f0 + t * VEC, a.F - VEC) : 0;
         float acc[VEC];
-        add_entries<VEC, kU, INNER, false>(a, a.in + f, p0 + sub * kU, is_long ? p0 : p1, P * kU, acc);
+        add_entries<VEC, LOG2T, kU, INNER, false>(a, a.in + f, p0 + sub * kU, is_long ? p0 : p1, P * kU, acc);
         for (int d = T; d < T * P; d <<= 1) {
 #pragma unroll
             for (int i = 0; i < VEC; ++i) acc[i] += __shfl_xor(acc[i], d, 64);
@@ -330,10 +358,13 @@ static_assert((1 << 13) == 8 * kBlock * kU, "chunk length");
 // group of their own and read pairs far apart (this kernel's time over the group kernel's at 20 / 90 / 200 to 230 M entries,
 // 0.25 to 8 M sources, both models: F = 1 0.37 to 0.80, F = 2 0.38 to 0.85, F = 4 0.42 to 0.88, growing with the matrix and
 // the entries; F = 3, whose groups have four lanes, 0.74 to 0.91 / 0.88 to 1.06 / 0.92 to 1.02).
-// Rows of up to 32 and 64 bytes while the second kernel and the chain of loads still show: up to 10 and
-// 5 M entries (F = 16: 1.2 to 1.9 times faster at 0.2 to 1 M, 1.05 to 1.35 times at 4 M, 0.9 to 1.2 at 6 to
-// 10 M, where matrices no longer stay in the memory-side cache between calls).  Wider rows while
-// the launches do: at 16 M floats of gathered rows (F = 64: 250,000 entries) the two are even.
+// Rows of up to 64 bytes up to 10 (F <= 8) and 5 M entries, and where launches do not run on tiles (epp_tiles.hip) up to
+// 48 M, at 64 bytes, which the group kernel reads as whole half lines, up to 12 M (over the group kernel's time, 5 to 44 M entries, 0.1 to
+// 8.4 M vertices, both models: F = 7 0.68 to 1.04, F = 12 0.62 to 1.01, F = 16 0.63 to 0.91, at 13 to 20 M 0.75 to 1.11).
+// Rows of up to 256 bytes while the second kernel and the chain of loads still show: at 16 M floats of gathered rows in any
+// case; up to 100 M, where the source matrix of 110 MB still stays in the memory-side cache, if the group kernel has to read
+// rows across the ends of lines (F = 20 to 47: 0.66 to 1.02; at 3 to 7 M vertices' rows of 140 MB and more 0.9 to 1.3), and up
+// to 64 M of 40 MB if not (F = 32 and 64: 0.69 to 0.98; beyond 0.8 to 1.4).
 bool epp_rows_kernel_fits(const epp_path* p, int F) {
     if (const char* e = std::getenv("EPP_TUNE_ROWS")) {  // 0: never, 2: always (tests, measurements)
         if (*e == '0') return false;
@@ -343,8 +374,11 @@ bool epp_rows_kernel_fits(const epp_path* p, int F) {
     const char* part = std::getenv("EPP_TUNE_PART");
     if ((part && *part == '2') || std::getenv("EPP_TUNE_HOT_MB") || std::getenv("EPP_TUNE_LOG2_SLICES")) return false;
     if (F <= 4) return p->nnz <= (1 << 30);
-    if (F <= 16) return p->nnz <= (F <= 8 ? 10000000 : 5000000);
-    return p->nnz * F <= 16000000;
+    if (F <= 16 && p->nnz <= (F <= 8 ? 10000000 : 5000000)) return true;
+    if (F <= 16) return p->nnz <= (F < 16 ? 48000000 : 12000000) && epp_tile_lanes(p, F) == 0;
+    if (p->nnz * F <= 16000000) return true;
+    const bool whole = F % 16 == 0;
+    return F <= 64 && p->nnz * F <= (whole ? 64000000 : 100000000) && p->n_src * F <= (whole ? 10000000 : 28000000);
 }
 
 int epp_build_rows_plan(epp_path* p, int F, hipStream_t s, RowsPlan** out) {
