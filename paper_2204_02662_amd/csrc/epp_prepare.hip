@@ -401,24 +401,40 @@ struct Kept {
 // millions.  (A kernel of its own that set the flags in the finished array took 0.1 ms for 2.4 M rows:
 // a read and a write of 128 bytes for each.)
 //
-// Runs at the rate of a copy: 140 M entries in 0.42 ms.  (What concerns a segment is fetched by one lane
+// TWO: a second level's entries, without marks, from the same read of the columns and values.
+//
+// Runs at the rate of a copy: 140 M entries in 0.41 ms, with 19 M of another level 0.46 ms; those by themselves took 0.23 ms, as
+// nearly every line of the arrays holds some of them.  (What concerns a segment is fetched by one lane
 // and read from there as a scalar; vector loads of it cost 0.45 ms more.)
+struct Extracted {
+    Kept kept;
+    Members members;
+    const int* ptr;
+    int n_rows, total;
+    int2* cv;
+};
+template <bool TWO>
 __global__ __launch_bounds__(kBlock) void k_edge_extract(const int32_t* __restrict__ col, const float* __restrict__ val,
-                                                         int64_t n_seg, Kept outer, Kept inner,
-                                                         int* __restrict__ inner_pos, const int* __restrict__ tile_row,
-                                                         Members members, int n, const int* __restrict__ ptr, int n_rows,
-                                                         int total, int2* __restrict__ cv) {
+                                                         int64_t n_seg, Extracted a, Kept inner, int* __restrict__ inner_pos,
+                                                         Extracted b, const int* __restrict__ tile_row, int n) {
     constexpr int kPerWave = kSegsPerTile / 4;
-    __shared__ unsigned int row_end[kSegsPerTile * 2];  // one bit per kept entry of the tile
-    if (threadIdx.x < kSegsPerTile * 2) row_end[threadIdx.x] = 0u;
+    __shared__ unsigned int row_end[TWO ? 2 : 1][kSegsPerTile * 2];  // one bit per kept entry of the tile
+    if (threadIdx.x < kSegsPerTile * 2) {
+        row_end[0][threadIdx.x] = 0u;
+        if constexpr (TWO) row_end[1][threadIdx.x] = 0u;
+    }
     const int lane = lane_id();
     const int64_t seg0 = (int64_t)blockIdx.x * kSegsPerTile + (threadIdx.x >> 6) * kPerWave;
     // lane i fetches what concerns segment i; it is read from there as a scalar below
-    unsigned long long om = 0ull, im = 0ull;
-    int ob = 0, ib = 0;
+    unsigned long long am = 0ull, bm = 0ull, im = 0ull;
+    int ab = 0, bb = 0, ib = 0;
     if (lane < kPerWave && seg0 + lane < n_seg) {
-        om = outer.mask[seg0 + lane];
-        ob = outer.before_seg(seg0 + lane);
+        am = a.kept.mask[seg0 + lane];
+        ab = a.kept.before_seg(seg0 + lane);
+        if constexpr (TWO) {
+            bm = b.kept.mask[seg0 + lane];
+            bb = b.kept.before_seg(seg0 + lane);
+        }
         if (inner.mask) {
             im = inner.mask[seg0 + lane];
             ib = inner.before_seg(seg0 + lane);
@@ -428,35 +444,49 @@ __global__ __launch_bounds__(kBlock) void k_edge_extract(const int32_t* __restri
 #pragma unroll
     for (int i = 0; i < kPerWave; ++i) {
         const int64_t e = (seg0 + i) * 64 + lane;
-        if ((lane_word(om, i) >> lane) & 1ull) x[i] = make_int2(col[e], __float_as_int(val[e]));
+        if ((lane_word(TWO ? am | bm : am, i) >> lane) & 1ull) x[i] = make_int2(col[e], __float_as_int(val[e]));
     }
     const bool last_tile = blockIdx.x + 1 == gridDim.x;
-    const int base = outer.tile_base[blockIdx.x], limit = last_tile ? total : outer.tile_base[blockIdx.x + 1];
-    __syncthreads();
-    if (limit > base) {
-        // (the row of the next tile's first entry may end in this one, if that entry is not kept)
-        const int r0 = members.before(tile_row[blockIdx.x], n);
-        const int r1 = last_tile ? n_rows : min(members.before(tile_row[blockIdx.x + 1], n) + 1, n_rows);
-        for (int r = r0 + (int)threadIdx.x; r < r1; r += kBlock) {
-            const int b = ptr[r + 1];
-            if (b > base && b <= limit) atomicOr(&row_end[(b - 1 - base) >> 5], 1u << ((b - 1 - base) & 31));
-        }
+    const int a_base = a.kept.tile_base[blockIdx.x], a_limit = last_tile ? a.total : a.kept.tile_base[blockIdx.x + 1];
+    int b_base = 0, b_limit = 0;
+    if constexpr (TWO) {
+        b_base = b.kept.tile_base[blockIdx.x];
+        b_limit = last_tile ? b.total : b.kept.tile_base[blockIdx.x + 1];
     }
     __syncthreads();
+    auto ends = [&](const Extracted& o, int base, int limit, unsigned int* __restrict__ bits) {
+        if (limit <= base) return;
+        // (the row of the next tile's first entry may end in this one, if that entry is not kept)
+        const int r0 = o.members.before(tile_row[blockIdx.x], n);
+        const int r1 = last_tile ? o.n_rows : min(o.members.before(tile_row[blockIdx.x + 1], n) + 1, o.n_rows);
+        for (int r = r0 + (int)threadIdx.x; r < r1; r += kBlock) {
+            const int q = o.ptr[r + 1];
+            if (q > base && q <= limit) atomicOr(&bits[(q - 1 - base) >> 5], 1u << ((q - 1 - base) & 31));
+        }
+    };
+    ends(a, a_base, a_limit, row_end[0]);
+    if constexpr (TWO) ends(b, b_base, b_limit, row_end[1]);
+    __syncthreads();
+    auto put = [&](const Extracted& o, int base, const unsigned int* __restrict__ bits, int2 e, int q) {
+        if ((bits[(q - base) >> 5] >> ((q - base) & 31)) & 1u) e.x |= kEntRowEnd;
+        o.cv[q] = e;
+    };
 #pragma unroll
     for (int i = 0; i < kPerWave; ++i) {
-        const unsigned long long m = lane_word(om, i);
-        const int q = __builtin_amdgcn_readlane(ob, i) + __popcll(m & low_mask(lane));
+        const unsigned long long m = lane_word(am, i);
+        const int q = __builtin_amdgcn_readlane(ab, i) + __popcll(m & low_mask(lane));
+        if constexpr (TWO) {
+            const unsigned long long own = lane_word(bm, i);
+            if ((own >> lane) & 1ull)
+                put(b, b_base, row_end[TWO], x[i], __builtin_amdgcn_readlane(bb, i) + __popcll(own & low_mask(lane)));
+        }
         if (inner.mask) {  // (uniform)
             const unsigned long long in = lane_word(im, i);
             if (!((in >> lane) & 1ull)) x[i].x |= kEntOuterOnly;
             if (((m >> lane) & 1ull) && (q & 63) == 0)
                 inner_pos[q >> 6] = __builtin_amdgcn_readlane(ib, i) + __popcll(in & low_mask(lane));
         }
-        if ((m >> lane) & 1ull) {
-            if ((row_end[(q - base) >> 5] >> ((q - base) & 31)) & 1u) x[i].x |= kEntRowEnd;
-            cv[q] = x[i];
-        }
+        if ((m >> lane) & 1ull) put(a, a_base, row_end[0], x[i], q);
     }
 }
 
@@ -1123,19 +1153,20 @@ extern "C" int epp_prepare(const epp_csr_t* g, const int32_t* train_ids, int64_t
     EPP_HIP_TRY(hipMemsetAsync(P->bitmaps[0].p, 0, bm_bytes, s));  // (the others are written whole)
 
     // all temporaries of the construction come from one allocation
-    // (keep-mask, its counts and the members before every 256 vertices twice: the entries of a level are extracted once
-    // the next level has shown whether the two paths share them, so two levels' masks are alive at a time)
-    DevBuf mask[2], seg_off[2], tile_base[2], tile_cnt, row_cnt, row_base[2], scan_tmp, newptr, tile_row, levels;
+    // (keep-mask, its counts and the members before every 256 vertices three times: the entries of a level are extracted
+    // once the next level has shown whether the two paths share them, and then wait for the next extraction)
+    constexpr int kAlive = 3;
+    DevBuf mask[kAlive], seg_off[kAlive], tile_base[kAlive], tile_cnt, row_cnt, row_base[kAlive], scan_tmp, newptr, tile_row, levels;
     const size_t cnt_bytes = (size_t)std::max(std::max(edge_tiles, word_tiles), 1u) * 4;
     const size_t row_bytes = (size_t)std::max(row_tiles, 1u) * 4;
     const size_t tmp_bytes = scan_tmp_bytes(std::max<int64_t>(edge_tiles, row_tiles));
     const size_t level_bytes = (size_t)L * (kLevelWords + kStatWords) * 8;
     DevArena arena;
-    EPP_TRY(arena.reserve(2 * (DevArena::rounded((size_t)n_seg * 8) + DevArena::rounded((size_t)n_seg * 2) +
-                               DevArena::rounded(cnt_bytes)) +
-                          2 * DevArena::rounded(cnt_bytes) + 3 * DevArena::rounded(row_bytes) + DevArena::rounded(tmp_bytes) +
+    EPP_TRY(arena.reserve(kAlive * (DevArena::rounded((size_t)n_seg * 8) + DevArena::rounded((size_t)n_seg * 2) +
+                                    DevArena::rounded(cnt_bytes) + DevArena::rounded(row_bytes)) +
+                          2 * DevArena::rounded(cnt_bytes) + DevArena::rounded(row_bytes) + DevArena::rounded(tmp_bytes) +
                           DevArena::rounded((size_t)(n + 1) * 4) + DevArena::rounded(level_bytes), al));
-    for (int i = 0; i < 2; ++i) {
+    for (int i = 0; i < kAlive; ++i) {
         arena.take(&mask[i], (size_t)n_seg * 8);
         arena.take(&seg_off[i], (size_t)n_seg * 2);
         arena.take(&tile_base[i], cnt_bytes);
@@ -1164,23 +1195,34 @@ extern "C" int epp_prepare(const epp_csr_t* g, const int32_t* train_ids, int64_t
     // the inner path's.  Every other level at most: a path whose marks serve an inner path
     // keeps its own arrays.
     std::vector<epp_path*> built;  // in level order, for the statistics
-    struct { epp_path* p = nullptr; int level = 0; } pending;  // path whose entries are not extracted yet
+    struct Waiting { epp_path* p = nullptr; int level = 0; };
+    Waiting pending;  // path whose entries are not extracted yet
+    Waiting due;      // .. and have arrays of their own for certain: the next extraction takes them along
     auto kept_of = [&](int slot) {
         return Kept{mask[slot].as<unsigned long long>(), seg_off[slot].as<uint16_t>(), tile_base[slot].as<int>()};
     };
+    auto extracted = [&](const Waiting& w) {
+        const int slot = w.level % kAlive;
+        return Extracted{kept_of(slot), Members{P->bitmaps[w.level + 1].as<unsigned long long>(), row_base[slot].as<int>()},
+                         w.p->rowptr.as<int>(), (int)w.p->n_rows, (int)w.p->nnz, w.p->cv.as<int2>()};
+    };
     auto extract = [&](epp_path* q, int level, bool marks_inner) -> int {
-        const int slot = level & 1;
         // the entries in an allocation of their own (it can be given back once every prepared width
         // runs on a reconstructed copy)
         EPP_TRY(q->cv.alloc((size_t)q->nnz * sizeof(int2), al));
         if (marks_inner) EPP_TRY(q->inner_pos.alloc((size_t)((q->nnz + 63) / 64) * 4, al));
+        if (due.p) EPP_TRY(due.p->cv.alloc((size_t)due.p->nnz * sizeof(int2), al));
         if (edge_tiles) {
-            hipLaunchKernelGGL(k_edge_extract, dim3(edge_tiles), dim3(kBlock), 0, s, g->col, g->val, n_seg, kept_of(slot),
-                               marks_inner ? kept_of(slot ^ 1) : Kept{nullptr, nullptr, nullptr}, q->inner_pos.as<int>(),
-                               tile_row.as<int>(),
-                               Members{P->bitmaps[level + 1].as<unsigned long long>(), row_base[slot].as<int>()}, (int)n,
-                               q->rowptr.as<int>(), (int)q->n_rows, (int)q->nnz, q->cv.as<int2>());
+            const Extracted a = extracted(Waiting{q, level});
+            const Kept inner = marks_inner ? kept_of((level + kAlive - 1) % kAlive) : Kept{nullptr, nullptr, nullptr};
+            if (due.p)
+                hipLaunchKernelGGL(k_edge_extract<true>, dim3(edge_tiles), dim3(kBlock), 0, s, g->col, g->val, n_seg, a, inner,
+                                   q->inner_pos.as<int>(), extracted(due), tile_row.as<int>(), (int)n);
+            else
+                hipLaunchKernelGGL(k_edge_extract<false>, dim3(edge_tiles), dim3(kBlock), 0, s, g->col, g->val, n_seg, a, inner,
+                                   q->inner_pos.as<int>(), a, tile_row.as<int>(), (int)n);
         }
+        due = Waiting{};
         EPP_HIP_TRY(hipGetLastError());
         return EPP_OK;
     };
@@ -1188,7 +1230,7 @@ extern "C" int epp_prepare(const epp_csr_t* g, const int32_t* train_ids, int64_t
     bool nested = false;  // N^{k-1} lies in N^k
     for (int k = 0; k < L; ++k) {
         const int l = L - 1 - k;  // rows N^{k+1} = N^{L-l}, sources N^k = N^{L-l-1}
-        const int slot = k & 1;
+        const int slot = k % kAlive;
         epp_path* p = new epp_path();
         P->path[l] = p;
         built.push_back(p);
@@ -1201,7 +1243,7 @@ extern "C" int epp_prepare(const epp_csr_t* g, const int32_t* train_ids, int64_t
         if (edge_tiles) {
             const bool all = k > 0 && P->set_size[k] == n;
             launch_edge_mask(g, n_seg, edge_tiles, P->bitmaps[k].as<unsigned int>(),
-                             k > 0 && nested ? mask[slot ^ 1].as<unsigned long long>() : nullptr, all, k == 0,
+                             k > 0 && nested ? mask[(k + kAlive - 1) % kAlive].as<unsigned long long>() : nullptr, all, k == 0,
                              mask[slot].as<unsigned long long>(), seg_off[slot].as<uint16_t>(), tile_cnt.as<int>(),
                              reinterpret_cast<int*>(d_level + 2), s);
             scan_counts(tile_cnt.as<int>(), tile_base[slot].as<int>(), (int64_t)edge_tiles, d_level, scan_tmp.as<int>(), s);
@@ -1259,9 +1301,10 @@ extern "C" int epp_prepare(const epp_csr_t* g, const int32_t* train_ids, int64_t
             EPP_TRY(extract(p, k, true));
             pending.p = nullptr;
         } else {
-            if (q) EPP_TRY(extract(q, pending.level, false));
-            pending.p = p;
-            pending.level = k;
+            // (at most one is due: the next level extracts this one's entries, or its own that this one shares)
+            if (q && due.p) EPP_TRY(extract(q, pending.level, false));
+            else if (q) due = pending;
+            pending = Waiting{p, k};
         }
         nested = next_nested;
         // Fixed point: N^{k+1} == N^k means every further set is the same set, so every deeper
