@@ -17,6 +17,7 @@
 // alone yields the path's entries in canonical order.
 
 #include <algorithm>
+#include <cmath>
 #include <cstdlib>
 #include <cstring>
 #include <mutex>
@@ -146,8 +147,9 @@ struct MaskArgs {
 // entries of a co-purchase graph whose columns stream in 0.12 ms.  LDS serves a wavefront's 64
 // words in a few cycles.  So a workgroup first copies a window of the bitmap into LDS (WORDS words:
 // 1.28 M ids fit) and streams its tiles past it; where the graph has more vertices, one pass per
-// window, each adding its finds to the mask.  A pass re-reads the columns, so past three windows
-// the lookups through L2 (k_edge_mask_far) are no slower.  Same graph: 0.12 ms per pass.
+// window, each adding its finds to the mask.  A pass re-reads the columns (0.12 ms), so from three windows on
+// k_edge_mask_folded takes over where the set is sparse or dense enough, and past three the
+// lookups through L2 (k_edge_mask_far) otherwise.
 //
 // `known`: if N^{k-1} is a subset of N^k (always the case when every vertex has a self-loop), an
 // entry kept at the previous level has its column in N^{k-1}, hence in N^k, and is kept again.  The
@@ -229,6 +231,99 @@ __global__ __launch_bounds__(1024) void k_edge_mask(MaskArgs a) {
                 off = run;
             }
             run += __popcll(m);
+        }
+        store_tile(a, tile, mine, out, off, run);
+    }
+}
+
+// Bit g of `folded`: whether any of the 2^shift ids (4 or 8) from g 2^shift on is in the set, or (ALL_OF) all of them are.
+template <bool ALL_OF>
+__global__ __launch_bounds__(kBlock) void k_fold_bitmap(const unsigned int* __restrict__ bitmap, int words, int shift, int out_words,
+                                                        unsigned int* __restrict__ folded) {
+    const int i = (int)(blockIdx.x * kBlock + threadIdx.x);
+    if (i >= out_words) return;
+    unsigned int out = 0u;
+    for (int k = 0; k < 1 << shift; ++k) {
+        const int j = (i << shift) + k;
+        unsigned int x = j < words ? bitmap[j] : 0u;
+        if (ALL_OF) x = ~x;
+        for (int t = 0; t < shift; ++t) x |= x >> (1 << t);
+        // bits 0, 2^shift, .. to the front
+        if (shift == 2) {
+            x &= 0x11111111u;
+            x = (x | x >> 3) & 0x03030303u;
+            x = (x | x >> 6) & 0x000F000Fu;
+            x = (x | x >> 12) & 0x000000FFu;
+        } else {
+            x &= 0x01010101u;
+            x = (x | x >> 7) & 0x00030003u;
+            x = (x | x >> 14) & 0x0000000Fu;
+        }
+        out |= x << (k * (32 >> shift));
+    }
+    folded[i] = ALL_OF ? ~out : out;
+}
+
+// The same for graphs of three windows and more, in one pass: the folded bitmap in LDS settles most ids (none of a
+// group in the set, or, ALL_OF, all of them), the others are looked up through L2 while the columns stream in.  140 M entries
+// with 15 / 25 % of them looked up: 0.21 / 0.25 ms (two windows 0.24, all looked up 0.52).  Preparation of three layers, 284 M
+// entries, 8.4 M vertices: 4.36 -> 3.69 ms; 122 M, 4.5 M: 2.51 -> 1.95; of two, 76 M, 5 M: 1.48 -> 1.20.
+template <int WORDS, bool ALL_OF>
+__global__ __launch_bounds__(1024) void k_edge_mask_folded(MaskArgs a, const unsigned int* __restrict__ folded, int shift) {
+    __shared__ __attribute__((aligned(16))) unsigned int bits[WORDS];
+    const int wave = threadIdx.x >> 6, lane = lane_id();
+    const int words = (((a.n - 1) >> shift) >> 5) + 1;  // (at most WORDS; `folded` has room for whole quadruples)
+    for (int i = 4 * (int)threadIdx.x; i < words; i += 4 * 1024)
+        *reinterpret_cast<uint4*>(bits + i) = *reinterpret_cast<const uint4*>(folded + i);
+    __syncthreads();
+    const int64_t step = (int64_t)gridDim.x * 16;
+    for (int64_t tile = (int64_t)blockIdx.x * 16 + wave; tile < a.n_tiles; tile += step) {
+        const int64_t seg0 = tile * kSegsPerTile;
+        const bool mine = lane < kSegsPerTile && seg0 + lane < a.n_seg;
+        const unsigned long long known = (a.known && mine) ? a.known[seg0 + lane] : 0ull;
+        int c[kSegsPerTile];
+        const int32_t* __restrict__ col = a.col + seg0 * 64 + lane;
+        if ((seg0 + kSegsPerTile) * 64 <= a.nnz) {
+#pragma unroll
+            for (int i = 0; i < kSegsPerTile; ++i) c[i] = __builtin_nontemporal_load(col + i * 64);
+        } else {
+#pragma unroll
+            for (int i = 0; i < kSegsPerTile; ++i) c[i] = (seg0 + i) * 64 + lane < a.nnz ? col[i * 64] : -1;
+        }
+        if (a.check) {
+            unsigned int top = 0;
+#pragma unroll
+            for (int i = 0; i < kSegsPerTile; ++i)
+                top = max(top, (seg0 + i) * 64 + lane < a.nnz ? (unsigned int)c[i] : 0u);
+            if (top >= (unsigned int)a.n) atomicOr(a.err, kErrCol);
+        }
+        unsigned long long out = 0ull;
+        int off = 0, run = 0;
+        constexpr int kHalf = kSegsPerTile / 2;
+#pragma unroll
+        for (int h = 0; h < kSegsPerTile; h += kHalf) {
+            unsigned int in = 0u, open = 0u, w[kHalf];  // entries that are in the set; that are looked up
+#pragma unroll
+            for (int i = 0; i < kHalf; ++i) {
+                const int id = c[h + i];
+                const bool valid = (unsigned int)id < (unsigned int)a.n;
+                const unsigned int g = valid ? (unsigned int)id >> shift : 0u;
+                const bool bit = valid && ((bits[g >> 5] >> (g & 31)) & 1u);
+                const bool look = (ALL_OF ? valid && !bit : bit) && !((lane_word(known, h + i) >> lane) & 1ull);
+                if (ALL_OF && bit) in |= 1u << i;
+                if (look) open |= 1u << i;
+                w[i] = a.bitmap[look ? id >> 5 : 0];
+            }
+#pragma unroll
+            for (int i = 0; i < kHalf; ++i) {
+                const bool found = ((open >> i) & 1u) && ((w[i] >> (c[h + i] & 31)) & 1u);
+                const unsigned long long m = __ballot(found || ((in >> i) & 1u)) | lane_word(known, h + i);
+                if (lane == h + i) {
+                    out = m;
+                    off = run;
+                }
+                run += __popcll(m);
+            }
         }
         store_tile(a, tile, mine, out, off, run);
     }
@@ -828,11 +923,13 @@ int compact_bitmap(const DevBuf& bitmap, int64_t n, const int* newptr, int total
     return EPP_OK;
 }
 
+constexpr int kFoldedWords = 39936;
+
 // keep-mask of one level: windows of the bitmap in LDS, or lookups through L2 (see k_edge_mask).
 void launch_edge_mask(const epp_csr_t* g, int64_t n_seg, unsigned n_tiles, const unsigned int* bitmap,
-                      const unsigned long long* known, bool all, bool check, unsigned long long* mask, uint16_t* seg_off,
-                      int* tile_count, int* err, hipStream_t s) {
-    constexpr int kSmall = 8192, kLarge = 39936;  // words: 32 KB (two workgroups per CU), 156 KB (one)
+                      const unsigned long long* known, bool all, bool check, double share, double known_share, unsigned int* folded,
+                      unsigned long long* mask, uint16_t* seg_off, int* tile_count, int* err, hipStream_t s) {
+    constexpr int kSmall = 8192, kLarge = kFoldedWords;  // words: 32 KB (two workgroups per CU), 156 KB (one)
     MaskArgs a;
     a.col = g->col;
     a.nnz = g->nnz;
@@ -848,6 +945,27 @@ void launch_edge_mask(const epp_csr_t* g, int64_t n_seg, unsigned n_tiles, const
     a.err = err;
     const int64_t window = g->n <= kSmall * 32 ? kSmall * 32 : kLarge * 32;
     const int64_t passes = (g->n + window - 1) / window;
+    // (copying the folded bitmap into every CU's LDS takes as long as 6 M lookups through L2)
+    if (!all && (passes == 3 || (passes > 3 && g->nnz >= 6000000))) {
+        int shift = 2;
+        while (((g->n - 1) >> shift) >= (int64_t)kLarge * 32) ++shift;
+        const double any = 1.0 - std::pow(1.0 - share, 1 << shift), not_all = 1.0 - std::pow(share, 1 << shift);
+        // (as if an entry's column were any vertex, and its neighbours' membership nothing to do with its own)
+        const double looked_up = std::min(any, not_all);
+        if (shift <= 3 && looked_up < (passes > 3 ? 0.6 * (1.0 - known_share) : 0.4)) {
+            const bool all_of = not_all < any;
+            const int words = (int)((g->n + 31) >> 5), out_words = (int)(((((g->n - 1) >> shift) >> 5) + 4) & ~3ll);
+            hipLaunchKernelGGL(all_of ? k_fold_bitmap<true> : k_fold_bitmap<false>, dim3(grid_for(out_words, kBlock)), dim3(kBlock), 0, s,
+                               bitmap, words, shift, out_words, folded);
+            a.first_id = 0;
+            a.n_ids = a.n;
+            a.check = check;
+            a.count = 1;
+            hipLaunchKernelGGL((all_of ? k_edge_mask_folded<kLarge, true> : k_edge_mask_folded<kLarge, false>),
+                               dim3(std::min(grid_for(n_tiles, 16), 256u)), dim3(1024), 0, s, a, folded, shift);
+            return;
+        }
+    }
     if (all || passes > 3) {
         a.first_id = 0;
         a.n_ids = a.n;
@@ -1156,7 +1274,7 @@ extern "C" int epp_prepare(const epp_csr_t* g, const int32_t* train_ids, int64_t
     // (keep-mask, its counts and the members before every 256 vertices three times: the entries of a level are extracted
     // once the next level has shown whether the two paths share them, and then wait for the next extraction)
     constexpr int kAlive = 3;
-    DevBuf mask[kAlive], seg_off[kAlive], tile_base[kAlive], tile_cnt, row_cnt, row_base[kAlive], scan_tmp, newptr, tile_row, levels;
+    DevBuf mask[kAlive], seg_off[kAlive], tile_base[kAlive], folded, tile_cnt, row_cnt, row_base[kAlive], scan_tmp, newptr, tile_row, levels;
     const size_t cnt_bytes = (size_t)std::max(std::max(edge_tiles, word_tiles), 1u) * 4;
     const size_t row_bytes = (size_t)std::max(row_tiles, 1u) * 4;
     const size_t tmp_bytes = scan_tmp_bytes(std::max<int64_t>(edge_tiles, row_tiles));
@@ -1164,7 +1282,7 @@ extern "C" int epp_prepare(const epp_csr_t* g, const int32_t* train_ids, int64_t
     DevArena arena;
     EPP_TRY(arena.reserve(kAlive * (DevArena::rounded((size_t)n_seg * 8) + DevArena::rounded((size_t)n_seg * 2) +
                                     DevArena::rounded(cnt_bytes) + DevArena::rounded(row_bytes)) +
-                          2 * DevArena::rounded(cnt_bytes) + DevArena::rounded(row_bytes) + DevArena::rounded(tmp_bytes) +
+                          DevArena::rounded(kFoldedWords * 4) + 2 * DevArena::rounded(cnt_bytes) + DevArena::rounded(row_bytes) + DevArena::rounded(tmp_bytes) +
                           DevArena::rounded((size_t)(n + 1) * 4) + DevArena::rounded(level_bytes), al));
     for (int i = 0; i < kAlive; ++i) {
         arena.take(&mask[i], (size_t)n_seg * 8);
@@ -1172,6 +1290,7 @@ extern "C" int epp_prepare(const epp_csr_t* g, const int32_t* train_ids, int64_t
         arena.take(&tile_base[i], cnt_bytes);
         arena.take(&row_base[i], row_bytes);
     }
+    arena.take(&folded, kFoldedWords * 4);
     arena.take(&newptr, (size_t)(n + 1) * 4);
     arena.take(&tile_cnt, cnt_bytes);
     arena.take(&row_cnt, row_bytes);
@@ -1244,6 +1363,8 @@ extern "C" int epp_prepare(const epp_csr_t* g, const int32_t* train_ids, int64_t
             const bool all = k > 0 && P->set_size[k] == n;
             launch_edge_mask(g, n_seg, edge_tiles, P->bitmaps[k].as<unsigned int>(),
                              k > 0 && nested ? mask[(k + kAlive - 1) % kAlive].as<unsigned long long>() : nullptr, all, k == 0,
+                             (double)(k > 0 ? P->set_size[k] : std::min(n_train, n)) / (double)n,
+                             k > 0 && nested ? (double)built[k - 1]->nnz / (double)nnz : 0.0, folded.as<unsigned int>(),
                              mask[slot].as<unsigned long long>(), seg_off[slot].as<uint16_t>(), tile_cnt.as<int>(),
                              reinterpret_cast<int*>(d_level + 2), s);
             scan_counts(tile_cnt.as<int>(), tile_base[slot].as<int>(), (int64_t)edge_tiles, d_level, scan_tmp.as<int>(), s);
