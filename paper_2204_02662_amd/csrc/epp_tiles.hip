@@ -343,7 +343,7 @@ __global__ __launch_bounds__(kSortThreads, 4) void k_tile_sort(const int2v* __re
         for (int i = mine0; i < mine1; ++i) { before += upto[i]; upto[i] = before; }
         __syncthreads();
     }
-    int lo_bucket = 0, carry = 0, done = b0, taken = 0;  // (the same in all threads)
+    int lo_bucket = 0, carry = 0, done = b0;  // (the same in all threads)
     while (true) {
         int hi_bucket = buckets;
         if (!whole) {  // as many ranges as fit
@@ -495,7 +495,6 @@ __global__ __launch_bounds__(kSortThreads, 4) void k_tile_sort(const int2v* __re
         if (last) return;
         done += batches;
         carry = filled - batches * 64;
-        taken += here;
         lo_bucket = hi_bucket;
         const int2v rest = t < carry ? buf[batches * 64 + t] : int2v{0, 0};
         __syncthreads();
