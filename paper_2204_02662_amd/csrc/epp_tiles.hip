@@ -38,7 +38,7 @@ constexpr int kTileBins = 128;           // length classes by which rows are dea
 constexpr unsigned kTogether = 64;       // consecutive tiles that are prepared on one XCD
 constexpr int kChunk = 4;                // entries of a cut row that stay together
 constexpr int kBuckets = 1024;           // source ranges into which a tile's entries are sorted
-constexpr int kRowsPerBlock = 4096, kListBlock = 256;
+constexpr int kRowsPerBlock = 1024, kListBlock = 256;
 constexpr int kColBits = 23;             // of an entry's first word; then 8 bits row of the tile, 1 bit "not the inner path's"
 constexpr unsigned kColMask23 = (1u << kColBits) - 1;
 
@@ -306,12 +306,13 @@ __global__ __launch_bounds__(kSortThreads, 4) void k_tile_sort(const int2v* __re
         return before;
     };
     // the row of the round's entry `pos`: the last one that starts at or before it and is not empty
-    auto row_at = [&](int pos, int lo, int hi) {
-        while (hi - lo > 1) {
-            const int mid = (lo + hi) >> 1;
-            if (start[mid] <= pos) lo = mid; else hi = mid;
+    auto row_at = [&](int pos) {  // (a fixed number of steps, so that several searches run side by side)
+        int at = 0;
+#pragma unroll
+        for (int step = 128; step > 0; step >>= 1) {
+            if (at + step < kRows && start[at + step] <= pos) at += step;
         }
-        return lo;
+        return at;
     };
     int all;
     {
@@ -330,9 +331,18 @@ __global__ __launch_bounds__(kSortThreads, 4) void k_tile_sort(const int2v* __re
     if (!whole) {
         for (int i = t; i < buckets; i += kSortThreads) upto[i] = 0;
         __syncthreads();
-        for (int pos = t; pos < all; pos += kSortThreads) {
-            const int r = row_at(pos, 0, kRows);
-            atomicAdd(&upto[(cv[tile_entry(row_of[r], pos + row_of[r].before)].x & kEntCol) >> shift], 1);
+        constexpr int kAtOnce = 8;  // (with one search and load after the other the kernel took 15 % more)
+        for (int pos0 = t; pos0 < all; pos0 += kAtOnce * kSortThreads) {
+            int col[kAtOnce];
+#pragma unroll
+            for (int i = 0; i < kAtOnce; ++i) {
+                const int pos = min(pos0 + i * kSortThreads, all - 1);
+                const TileRow row = row_of[row_at(pos)];
+                col[i] = cv[tile_entry(row, pos + row.before)].x & kEntCol;
+            }
+#pragma unroll
+            for (int i = 0; i < kAtOnce; ++i)
+                if (pos0 + i * kSortThreads < all) atomicAdd(&upto[col[i] >> shift], 1);
         }
         __syncthreads();
         int sum = 0, total;
@@ -407,7 +417,7 @@ __global__ __launch_bounds__(kSortThreads, 4) void k_tile_sort(const int2v* __re
             e[i] = int2v{0, 0};
             at[i] = 0;
             if (p0 + i * 64 < p1) {
-                const int r = row_at(min(pos, p1 - 1), r0, r1);
+                const int r = row_at(min(pos, p1 - 1));
                 at[i] = r;
                 const TileRow row = row_of[r];
                 e[i] = cv[tile_entry(row, min(pos, p1 - 1) + row.before)];
@@ -895,7 +905,7 @@ struct Sources {
         double all = 0.0, lo = 0.0, hi = 60.0, hit = 0.0;  // (octaves of references between two uses)
         for (int i = 0; i < classes; ++i) all += count[i];
         if (all <= sources) return 1.0;
-        for (int i = 0; i < 30; ++i) {
+        for (int i = 0; i < 16; ++i) {
             const double mid = 0.5 * (lo + hi);
             (touched(std::exp2(mid), 1.0) < sources ? lo : hi) = mid;
         }
@@ -911,6 +921,7 @@ static double group_launch_us(const epp_path* p, const Sources& src, int F) {
     double best = 1e30;
     const int packed = F <= 16 ? std::max(8, F > 8 ? 16 : 8) : (F + 15) / 16 * 16;
     for (const int ld : {F, packed}) {
+        if (ld == packed && best < 1e30 && packed == F) break;
         const double lines = epp_lines_per_row(F, ld), hit = src.cached(kLinesOfL2 / lines);
         const double copy = ld == F ? 0.0 : 4.0 * (double)p->n * (F + ld) * 2.5e-7;
         best = std::min(best, 1e-6 * (double)p->nnz * (3.8 + lines * (3.0 * hit + 12.8 * (1.0 - hit))) + copy);
@@ -959,16 +970,17 @@ static double tile_launch_us(const epp_path* p, const Sources& src, int F, int l
 // Some of them (us, group kernel / tiles of 4, 8 and 16 lanes): 274 M entries, 2.4 M sources, F = 64: 8866 / 12056 / 5550 /
 // 7246; F = 16: 4940 / 2425 / 2587; 228 M, 8.4 M, R-MAT, F = 128: 12290 / - / 8960 / 8560; not taken: 19 M of 2.4 M, F = 128:
 // 1547 / - / 1446 / 1442; 65 M of 8.4 M, F = 41: 2726 / 4699 / 4376 / 3603.
-// The tiles cost 10 to 12 us per million entries to prepare, which five launches have to repay.  Fewer sources than
+// The tiles cost 9 to 11 us per million entries to prepare, which five launches have to repay.  Fewer sources than
 // 100,000 nearly fit the L2s together: the estimate of what hits them is not good enough there (65,000, 23 M entries, F = 96:
-// 527 / - / 732 / 633, estimated 758 / - / 602 / 617).
+// 527 / - / 732 / 633, estimated 758 / - / 602 / 617), but for rows of 64 bytes and less, which four lanes gather faster from L2
+// too (51,000, 30 M entries, F = 16: 269 / 181, estimated 230 / 202; 84,000, 118 M: 1085 / 691).
 int epp_tile_lanes(const epp_path* p, int F) {
     const int mode = env_int("EPP_TUNE_TILES", 1);  // 0: never, 1: where it pays, 2: wherever it can be (tests)
     if (mode == 0 || F < 5 || p->nnz == 0) return 0;
     // (a source's id has 23 bits in an entry, and its row's place in the matrix 32)
     if (p->n > (1ll << kColBits) || (p->n - 1) * (int64_t)F >= (1ll << 32)) return 0;
     if (mode == 2) return env_int("EPP_TUNE_TILE_LANES", 8);
-    if (p->nnz < 4'000'000 || p->n_src < 100'000) return 0;
+    if (p->nnz < 4'000'000 || p->n_src < (F <= 16 ? 40'000 : 100'000)) return 0;
     const Sources src(p);
     const double groups = group_launch_us(p, src, F);
     int lanes = 0;
@@ -978,7 +990,7 @@ int epp_tile_lanes(const epp_path* p, int F) {
         const double us = tile_launch_us(p, src, F, l);
         if (us < best) { best = us; lanes = l; }
     }
-    return best < 0.9 * groups && 5.0 * (groups - best) > 60.0 + 11.5e-6 * (double)p->nnz ? lanes : 0;
+    return best < 0.9 * groups && 5.0 * (groups - best) > 100.0 + 10e-6 * (double)p->nnz ? lanes : 0;
 }
 
 int epp_build_tiles(epp_path* p, int lanes, hipStream_t s, TilePlan** out) {
