@@ -970,10 +970,15 @@ static double tile_launch_us(const epp_path* p, const Sources& src, int F, int l
 // Some of them (us, group kernel / tiles of 4, 8 and 16 lanes): 274 M entries, 2.4 M sources, F = 64: 8866 / 12056 / 5550 /
 // 7246; F = 16: 4940 / 2425 / 2587; 228 M, 8.4 M, R-MAT, F = 128: 12290 / - / 8960 / 8560; not taken: 19 M of 2.4 M, F = 128:
 // 1547 / - / 1446 / 1442; 65 M of 8.4 M, F = 41: 2726 / 4699 / 4376 / 3603.
-// The tiles cost 9 to 11 us per million entries to prepare, which five launches have to repay.  Fewer sources than
+// The tiles cost 9 to 11 us per million entries to prepare, which five launches have to repay.  Rows of up to 32 floats have to save
+// kNarrowSaves a launch besides: beyond that width the group kernel prepares a partitioned copy, which costs as much as tiles, but here a
+// group table of 20 us, and a run that ends soon pays for the difference (import and one epoch, F = 5 / 32, 31 M entries: 422 us without
+// tiles, 891 with them; F = 32, 79 M: 1493, 2007; F = 16 / 41, 114 M: 1.1 ms more once, 0.37 ms less per epoch).  Fewer sources than
 // 100,000 nearly fit the L2s together: the estimate of what hits them is not good enough there (65,000, 23 M entries, F = 96:
 // 527 / - / 732 / 633, estimated 758 / - / 602 / 617), but for rows of 64 bytes and less, which four lanes gather faster from L2
 // too (51,000, 30 M entries, F = 16: 269 / 181, estimated 230 / 202; 84,000, 118 M: 1085 / 691).
+constexpr double kNarrowSaves = 400.0;  // us
+
 int epp_tile_lanes(const epp_path* p, int F) {
     const int mode = env_int("EPP_TUNE_TILES", 1);  // 0: never, 1: where it pays, 2: wherever it can be (tests)
     if (mode == 0 || F < 5 || p->nnz == 0) return 0;
@@ -990,7 +995,8 @@ int epp_tile_lanes(const epp_path* p, int F) {
         const double us = tile_launch_us(p, src, F, l);
         if (us < best) { best = us; lanes = l; }
     }
-    return best < 0.9 * groups && 5.0 * (groups - best) > 100.0 + 10e-6 * (double)p->nnz ? lanes : 0;
+    const double saved = groups - best;
+    return best < 0.9 * groups && 5.0 * saved > 100.0 + 10e-6 * (double)p->nnz && (F > 32 || saved > kNarrowSaves) ? lanes : 0;
 }
 
 int epp_build_tiles(epp_path* p, int lanes, hipStream_t s, TilePlan** out) {
