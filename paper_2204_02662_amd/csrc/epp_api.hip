@@ -31,7 +31,7 @@ const epp_path* entries_of(const epp_path* p) { return p->outer ? p->outer : p; 
 // Tiles, where launches of the width run on them and there is memory for them.
 int prepare_tiles(epp_path* p, epp_path::WidthCfg* w, hipStream_t s) {
     const int lanes = epp_tile_lanes(p, w->F);
-    if (!lanes) return EPP_OK;
+    if (!lanes || p->tile_order[tile_order_of(lanes)].unfit) return EPP_OK;
     const epp_alloc_t* al = epp_alloc_of(p);
     TilePlan* q = nullptr;
     for (TilePlan* t : p->tile_plans)

@@ -242,6 +242,12 @@ struct RowsPlan {
     int n_huge = 0, n_chunks = 0;
 };
 
+// What a build of tiles has shown about the order of a path's entries, whichever the width; per number of lanes.
+struct TileOrder {
+    bool unfit = false;  // they cannot be laid out
+};
+inline int tile_order_of(int lanes) { return lanes == 4 ? 0 : lanes == 8 ? 1 : 2; }
+
 // Tiles of rows whose sums a launch keeps in LDS while it takes their entries in source order (epp_tiles.hip); serves
 // all widths that want the same lanes per source row.
 struct TilePlan {
@@ -298,6 +304,7 @@ struct epp_path {
     DevBuf empty_rows;           // int32[n_empty_rows] vertices with empty lists
     std::vector<Schedule*> scheds;
     std::vector<TilePlan*> tile_plans;
+    TileOrder tile_order[3];
     // per-width choices
     // prepared: epp_path_prepare_width has been called; rows: launches run the row kernel, which needs no
     // group table (sched may be NULL then) and a plan only where some row is very long; slices: XCD feature slicing; part: source-partitioned layout
@@ -400,7 +407,7 @@ int epp_tune_locality(epp_path* p, int F, int ld, int gs, bool may_partition, hi
 // the source rows that it makes (0: none)
 int epp_tile_lanes(const epp_path* p, int F);
 size_t epp_tile_packed_bytes(const epp_path* p, int F, int lanes);
-int epp_build_tiles(epp_path* p, int lanes, hipStream_t s, TilePlan** out);  // *out = NULL: not these entries
+int epp_build_tiles(epp_path* p, int lanes, hipStream_t s, TilePlan** out);  // *out = NULL: not these entries (p->tile_order keeps that)
 int epp_launch_tiles(const epp_path* p, const TilePlan* q, float* parts, const float* in, float* packed, float* out, int F,
                      hipStream_t s, const unsigned long long* sources, const unsigned int* inner_rows);
 

@@ -249,7 +249,7 @@ __global__ __launch_bounds__(64) void k_tile_sizes(const Dealt* __restrict__ dea
 // `care` how it has to take the batch.
 //
 // *bad is set where that cannot be done: more than kSortMax entries of a tile in one range, or, in a tile that takes more
-// than one round, columns that do not ascend along a row.
+// than one round, columns that do not ascend along a row.  Workgroups that start after that do nothing.
 constexpr int kSortThreads = 512, kSortWaves = kSortThreads / 64;
 constexpr int kSortMax = 5632;
 constexpr int kSortPer = (kSortMax / kSortWaves + kSplitMax - 1 + 63) / 64;  // entries per lane: a wavefront's share and all of one row but one
@@ -278,11 +278,13 @@ __global__ __launch_bounds__(kSortThreads, 4) void k_tile_sort(const int2v* __re
     __shared__ int from[kRows], start[kRows + 1];    // first entry of the round, its place among the round's entries
     __shared__ int wave_sum[kSortWaves];
     __shared__ int row_count_all[kSortWaves][256];
+    __shared__ int stop;
     // (consecutive tiles hold the parts of one row and read the same lines: kTogether of them run on one XCD)
     const unsigned turn = blockIdx.x >> 3;
     const int tile = (int)(((turn / kTogether) * 8 + (blockIdx.x & 7)) * kTogether + turn % kTogether);
     const int b0 = first_batch[tile];
     const int t = (int)threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
+    if (t == 0) stop = __hip_atomic_load(bad, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     TileRow mine = {0, kChunk, 0, 0};
     if (t < kRows) {
         const Dealt r = dealt[dealt_at(tile, t, kRows, at_once)];
@@ -322,7 +324,7 @@ __global__ __launch_bounds__(kSortThreads, 4) void k_tile_sort(const int2v* __re
         if (t == 0) start[kRows] = all;
     }
     __syncthreads();
-    if (all == 0) return;  // (its places have no rows)
+    if (stop || all == 0) return;  // (its places have no rows)
     const bool whole = all <= kSortMax;
     // fewer and larger ranges where a batch spans several of them anyway
     int buckets = kBuckets, shift = fine_shift;
@@ -365,7 +367,7 @@ __global__ __launch_bounds__(kSortThreads, 4) void k_tile_sort(const int2v* __re
             }
             hi_bucket = __builtin_amdgcn_readfirstlane(lo);
             if (hi_bucket == lo_bucket) {
-                if (t == 0) *bad = 1;
+                if (t == 0) atomicOr(bad, 1);
                 return;
             }
         }
@@ -392,7 +394,7 @@ __global__ __launch_bounds__(kSortThreads, 4) void k_tile_sort(const int2v* __re
         }
         __syncthreads();
         if (here > kSortMax) {  // (rows that do not ascend)
-            if (t == 0) *bad = 1;
+            if (t == 0) atomicOr(bad, 1);
             return;
         }
         // the wavefront's rows: those that start in its share of the places
@@ -435,7 +437,7 @@ __global__ __launch_bounds__(kSortThreads, 4) void k_tile_sort(const int2v* __re
                 at[i] = (at[i] << 16) | (int)((place >> half) & 0xFFFFu);
             }
         }
-        if (out_of_range) *bad = 1;
+        if (out_of_range) atomicOr(bad, 1);
         __syncthreads();
         {
             int sum = 0, total;
@@ -1093,7 +1095,10 @@ int epp_build_tiles(epp_path* p, int lanes, hipStream_t s, TilePlan** out) {
     EPP_HIP_TRY(hipMemcpyAsync(h, bad, 4, hipMemcpyDeviceToHost, s));
     EPP_HIP_TRY(hipGetLastError());
     EPP_HIP_TRY(hipStreamSynchronize(s));  // (the temporaries go, too)
-    if (h[0]) return EPP_OK;
+    if (h[0]) {
+        p->tile_order[tile_order_of(lanes)].unfit = true;
+        return EPP_OK;
+    }
     guard.q = nullptr;
     *out = q;
     return EPP_OK;

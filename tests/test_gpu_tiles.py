@@ -84,6 +84,27 @@ def test_columns_in_any_order(lanes, monkeypatch):
 
 
 @pytest.mark.parametrize("lanes", [4, 8, 16])
+def test_entries_that_do_not_fit_are_laid_out_once(lanes, monkeypatch):
+    """Rows whose columns do not ascend, in tiles of several rounds: the first width finds out, the next one of the same lanes takes
+    no memory for tiles."""
+    _force(monkeypatch, lanes, PACK=0, PART=0)
+    g = graphgen.random_graph("rmat", 90_000, seed=92, raw_draws=5_000_000)
+    order = np.lexsort((np.random.default_rng(91).random(g.nnz), np.repeat(np.arange(g.n), np.diff(g.rowptr))))
+    col, val = g.col[order].copy(), g.val[order].copy()
+    paths = epp.epp_prepare(g.n, *(torch.from_numpy(x).to(dev()) for x in (g.rowptr, col, val)),
+                            torch.arange(g.n, dtype=torch.int32, device=dev()), 1)
+    taken = []
+    for F in (33, 47):
+        before = epp.alloc_stats["bytes"]
+        paths.path(0).prepare_width(F)
+        taken.append(epp.alloc_stats["bytes"] - before)
+        X = graphgen.normal_rows(g.n, F, None, 93)
+        assert_close(run_partial(paths.path(0), X)[np.diff(g.rowptr) > 0],
+                     oracle.full_aggregate(g.n, g.rowptr, col, val, X)[np.diff(g.rowptr) > 0], f"lanes={lanes} F={F}")
+    assert taken[0] > 8 * g.nnz > taken[1], taken
+
+
+@pytest.mark.parametrize("lanes", [4, 8, 16])
 @pytest.mark.parametrize("F", [16, 47])
 def test_infinities_stay_where_they_belong(lanes, F, monkeypatch):
     _force(monkeypatch, lanes)
