@@ -30,14 +30,17 @@ const epp_path* entries_of(const epp_path* p) { return p->outer ? p->outer : p; 
 
 // Tiles, where launches of the width run on them and there is memory for them.
 int prepare_tiles(epp_path* p, epp_path::WidthCfg* w, hipStream_t s) {
-    const int lanes = epp_tile_lanes(p, w->F);
-    if (!lanes || p->tile_order[tile_order_of(lanes)].unfit) return EPP_OK;
+    double max_delay;
+    const int lanes = epp_tile_lanes(p, w->F, &max_delay);
+    if (!lanes) return EPP_OK;
+    const TileOrder& order = p->tile_order[tile_order_of(lanes)];
+    if (order.unfit || order.delay > max_delay) return EPP_OK;
     const epp_alloc_t* al = epp_alloc_of(p);
     TilePlan* q = nullptr;
     for (TilePlan* t : p->tile_plans)
         if (t->lanes == lanes) q = t;
     if (!q) {
-        const int rc = epp_build_tiles(p, lanes, s, &q);
+        const int rc = epp_build_tiles(p, lanes, max_delay, s, &q);
         if (rc == EPP_ERR_ALLOC || (rc == EPP_OK && !q)) return EPP_OK;
         EPP_TRY(rc);
         p->tile_plans.push_back(q);

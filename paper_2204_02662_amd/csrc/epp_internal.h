@@ -244,7 +244,8 @@ struct RowsPlan {
 
 // What a build of tiles has shown about the order of a path's entries, whichever the width; per number of lanes.
 struct TileOrder {
-    bool unfit = false;  // they cannot be laid out
+    bool unfit = false;   // they cannot be laid out
+    double delay = -1.0;  // steps by which entries of one row delay a batch on average; -1: not known
 };
 inline int tile_order_of(int lanes) { return lanes == 4 ? 0 : lanes == 8 ? 1 : 2; }
 
@@ -403,11 +404,12 @@ int epp_zero_empty_rows(const epp_path* p, float* out, int F, hipStream_t s);
 // ld: floats from one source row to the next.  Where the memory for it is missing, marks and partition are left out.
 int epp_tune_locality(epp_path* p, int F, int ld, int gs, bool may_partition, hipStream_t s, int* log2_slices, Partition** part);
 
-// tiles.hip: lanes per source row of a launch on tiles (0: it runs on the group table), bytes of the copy of
-// the source rows that it makes (0: none)
-int epp_tile_lanes(const epp_path* p, int F);
+// tiles.hip: lanes per source row of a launch on tiles (0: it runs on the group table) and the longest delay of a batch
+// with which that pays, bytes of the copy of the source rows that it makes (0: none)
+int epp_tile_lanes(const epp_path* p, int F, double* max_delay);
 size_t epp_tile_packed_bytes(const epp_path* p, int F, int lanes);
-int epp_build_tiles(epp_path* p, int lanes, hipStream_t s, TilePlan** out);  // *out = NULL: not these entries (p->tile_order keeps that)
+// *out = NULL: these entries cannot be laid out, or their batches would be delayed by more than max_delay (p->tile_order keeps both)
+int epp_build_tiles(epp_path* p, int lanes, double max_delay, hipStream_t s, TilePlan** out);
 int epp_launch_tiles(const epp_path* p, const TilePlan* q, float* parts, const float* in, float* packed, float* out, int F,
                      hipStream_t s, const unsigned long long* sources, const unsigned int* inner_rows);
 

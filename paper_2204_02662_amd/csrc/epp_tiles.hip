@@ -22,6 +22,7 @@
 //   * Wide rows are taken in slices, one after the other: the narrower the slice, the more rows fit LDS and the more sources L2,
 //     at the price of reading the entries once per slice.
 
+#include <algorithm>
 #include <cmath>
 #include <cstdlib>
 #include <type_traits>
@@ -57,6 +58,10 @@ constexpr int care_turns(int lanes, unsigned care) {
 constexpr int care_limit(int lanes, unsigned care) {
     return care_turns(lanes, care) == 0 ? lanes / 2 : care_turns(lanes, care) * lanes;
 }
+
+// Steps that a wavefront makes one after the other for a batch, beyond those of a batch that needs no care.
+constexpr int care_steps(int lanes, unsigned care) { return care_turns(lanes, care) == 0 ? lanes / 2 : lanes * care_turns(lanes, care); }
+constexpr int care_delay(int lanes, unsigned care) { return care_steps(lanes, care) - care_steps(lanes, 0); }
 
 int env_int(const char* name, int dflt) {
     const char* v = std::getenv(name);
@@ -117,11 +122,89 @@ __device__ __forceinline__ void for_parts(int len, int parts, int begin, int to,
     }
 }
 
+// What the order of the ids will do to the batches of k_tile_sort: *delay is the sum of care_delay over kOrderSamples batches, each
+// that of a random entry.  Every workgroup counts 8,192 random entries per range of the sources (whole lines of 16), so that it knows
+// which ranges fill a batch of a tile between them.  A lane of one wavefront then draws an entry and looks up how many of its row (or part of
+// one) lie in the entry's batch, if all rows of the tile are as long.  Batches hold several rows, of which the one with the most
+// entries counts, so this is somewhat less than what the sort finds (mean delay, sort / sampled, 8 lanes: narrow band 60 / 59, communities
+// 58 / 48 and 6.5 / 3.0, by degree 12.3 / 10.4 and 4.0 / 3.0, random order 0.07 / 0.01).  Bound by latency, 35 to 40 us.
+constexpr int kOrderBlocks = 256, kOrderThreads = 1024, kOrderReads = 8;
+constexpr int kOrderSamples = kOrderBlocks * 64;  // (a wavefront each: more of them on a CU would wait for its address units)
+__host__ __device__ inline bool too_slow(unsigned delay, double max_delay) { return (double)delay > max_delay * kOrderSamples; }
+__device__ __forceinline__ unsigned scrambled(unsigned x) {
+    x = (x ^ (x >> 16)) * 0x7FEB352Du;
+    x = (x ^ (x >> 15)) * 0x846CA68Bu;
+    return x ^ (x >> 16);
+}
+template <int LANES>
+__global__ __launch_bounds__(kOrderThreads) void k_tile_order(const int2v* __restrict__ cv, int64_t nnz, const int32_t* __restrict__ rowptr,
+                                                              int64_t n_rows, int split, int shift, unsigned int* __restrict__ delay) {
+    static_assert(kBuckets == kOrderThreads, "a thread per range");
+    __shared__ int before[kBuckets], wave_sum[kOrderThreads / 64];
+    const int t = (int)threadIdx.x, lane = t & 63, wave = t >> 6;
+    before[t] = 0;
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < kOrderReads; ++i) {
+        const unsigned x = scrambled((blockIdx.x * kOrderReads + i) * (kOrderThreads / 16) + (t >> 4));
+        const int64_t e = (int64_t)(((unsigned long long)x * (unsigned long long)nnz) >> 32);
+        atomicAdd(&before[(cv[std::min<int64_t>((e & ~15ll) + (t & 15), nnz - 1)].x & kEntCol) >> shift], 1);
+    }
+    __syncthreads();
+    const int mine = before[t], incl = sum_up_to_lane(mine);
+    if (lane == 63) wave_sum[wave] = incl;
+    __syncthreads();
+    int sum = incl - mine;
+    for (int w = 0; w < wave; ++w) sum += wave_sum[w];
+    before[t] = sum;
+    __syncthreads();
+    if (wave > 0) return;
+    const unsigned x = scrambled(0x80000000u | (blockIdx.x * 64 + t));
+    const int64_t e = (int64_t)(((unsigned long long)x * (unsigned long long)nnz) >> 32);
+    int64_t lo = 0, hi = n_rows;  // the last row that begins at or before entry e
+    while (hi - lo > 1) {
+        const int64_t step = std::max<int64_t>((hi - lo) / 8, 1);
+        int past = 0;
+#pragma unroll
+        for (int i = 1; i < 8; ++i) past += lo + i * step < hi && rowptr[std::min(lo + i * step, hi - 1)] <= e;
+        if (past < 7) hi = std::min(hi, lo + (past + 1) * step);
+        lo += past * step;
+    }
+    const int begin = rowptr[lo], len = rowptr[lo + 1] - begin, parts = parts_of(len, split), at = (int)e - begin;
+    const int part = at / kChunk % parts, m = part_len(len, parts, part), here = at / kChunk / parts * kChunk + at % kChunk;
+    // batch of the part's entry k, if a tile's rows all have m entries
+    const float batches = (float)(tile_rows(LANES) * m) / (64.0f * kOrderThreads * kOrderReads);
+    auto batch_of = [&](int k) {
+        const int col = cv[begin + part * kChunk + k / kChunk * parts * kChunk + k % kChunk].x & kEntCol;
+        return (int)((float)before[col >> shift] * batches);
+    };
+    const int batch = batch_of(here);
+    int first = 0, top = here, low = here + 1, end = m;  // [first, top] and [low, end] hold the ends of its entries of that batch
+    while (first < top || low < end) {
+        const int mid0 = (first + top) >> 1, mid1 = (low + end) >> 1;
+        const int b0 = batch_of(min(mid0, m - 1)), b1 = batch_of(min(mid1, m - 1));
+        if (first < top) {
+            if (b0 < batch) first = mid0 + 1; else top = mid0;
+        }
+        if (low < end) {
+            if (b1 <= batch) low = mid1 + 1; else end = mid1;
+        }
+    }
+    const int most = end - first;
+    int steps = 0;
+#pragma unroll
+    for (unsigned c = 0; c < 3; ++c)
+        if (most > care_limit(LANES, c)) steps = care_delay(LANES, c + 1);
+    steps = sum_up_to_lane(steps);
+    if (lane == 63 && steps) atomicAdd(delay, (unsigned)steps);
+}
+
 // Rows (parts of cut rows counted one by one) per length class, of every workgroup; totals: rows, parts of cut rows,
-// cut rows.
+// cut rows; then the delay of k_tile_order, with which nothing is done if it is too long.
 __global__ __launch_bounds__(kListBlock) void k_tile_count(const int32_t* __restrict__ rowptr, int64_t n_rows, int split,
                                                            unsigned int* __restrict__ block_hist,
-                                                           unsigned int* __restrict__ totals) {
+                                                           unsigned int* __restrict__ totals, double max_delay) {
+    if (too_slow(totals[3], max_delay)) return;
     __shared__ unsigned int h[kTileBins], t[3];
     if (threadIdx.x < kTileBins) h[threadIdx.x] = 0;
     if (threadIdx.x < 3) t[threadIdx.x] = 0;
@@ -141,7 +224,9 @@ __global__ __launch_bounds__(kListBlock) void k_tile_count(const int32_t* __rest
 
 // A workgroup per class: the class's rows before every workgroup of k_tile_count, and in all of them.
 __global__ __launch_bounds__(256) void k_tile_classes(unsigned int* __restrict__ block_hist, int n_blocks,
-                                                      unsigned int* __restrict__ hist) {
+                                                      unsigned int* __restrict__ hist,
+                                                      const unsigned int* __restrict__ totals, double max_delay) {
+    if (too_slow(totals[3], max_delay)) return;
     __shared__ unsigned int wave_sum[4];
     const int bin = blockIdx.x, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     unsigned before = 0;
@@ -845,6 +930,12 @@ void sort_tiles(TilePlan* q, const int2v* cv, const Dealt* dealt, int shift, int
 }
 
 template <int LANES>
+void sample_order(const epp_path* p, int split, int shift, unsigned int* delay, hipStream_t s) {
+    hipLaunchKernelGGL(k_tile_order<LANES>, dim3(kOrderBlocks), dim3(kOrderThreads), 0, s, reinterpret_cast<const int2v*>(p->cv.p), p->nnz,
+                       p->rowptr.as<int32_t>(), p->n_stream_rows, split, shift, delay);
+}
+
+template <int LANES>
 void launch_tiles(const TileArgs& a, int slices, hipStream_t s) {
     const dim3 grid((unsigned)(a.blocks * slices)), block(kTileWaves * 64);
     if (a.zero) hipLaunchKernelGGL((k_aggregate_tiles<LANES, true>), grid, block, 0, s, a);
@@ -980,8 +1071,19 @@ static double tile_launch_us(const epp_path* p, const Sources& src, int F, int l
 // 527 / - / 732 / 633, estimated 758 / - / 602 / 617), but for rows of 64 bytes and less, which four lanes gather faster from L2
 // too (51,000, 30 M entries, F = 16: 269 / 181, estimated 230 / 202; 84,000, 118 M: 1085 / 691).
 constexpr double kNarrowSaves = 400.0;  // us
+// All of that is for ids in random order, where hardly a row has more than a few of a batch's 64 entries.  Where neighbours have
+// neighbouring ids, rows fill batches by themselves, and their additions wait for each other: a band of 500 ids, 50 M entries, 1 M
+// sources, F = 64: 1569 us on groups, 4677 on 8 lanes; communities of 20,000 ids with hubs, 116 M entries, F = 64: 3657 / 10191; ids by
+// degree, 114 M entries, 233,000 sources, F = 16: 950 / 1540, F = 128: 2902 / 3990.  So the build first samples the batches
+// (k_tile_order) and stops where their mean delay uses up what the launch would save.  Mean delay in steps, sampled: random order 0.01
+// at most; a band of 200,000 ids 0.1; 2.4 M vertices by degree 1.9 to 3; 233,000 by degree 6 to 10; the narrow band 55 to 60.
+// Such a step costs 35e-6 us a batch in the last case and 50 to 140e-6 in those before, where the estimates of the gathers are off,
+// too: with 60e-6 the F = 128 above would be taken, with 100e-6 no launch of 56 paths and widths in 14 orders took more than 1.04 of
+// the group kernel's time.
+constexpr double kStepUs = 1e-4;
 
-int epp_tile_lanes(const epp_path* p, int F) {
+int epp_tile_lanes(const epp_path* p, int F, double* max_delay) {
+    *max_delay = 1e30;
     const int mode = env_int("EPP_TUNE_TILES", 1);  // 0: never, 1: where it pays, 2: wherever it can be (tests)
     if (mode == 0 || F < 5 || p->nnz == 0) return 0;
     // (a source's id has 23 bits in an entry, and its row's place in the matrix 32)
@@ -997,11 +1099,14 @@ int epp_tile_lanes(const epp_path* p, int F) {
         const double us = tile_launch_us(p, src, F, l);
         if (us < best) { best = us; lanes = l; }
     }
-    const double saved = groups - best;
-    return best < 0.9 * groups && 5.0 * saved > 100.0 + 10e-6 * (double)p->nnz && (F > 32 || saved > kNarrowSaves) ? lanes : 0;
+    const double need = std::max({0.1 * groups, 20.0 + 2e-6 * (double)p->nnz, F > 32 ? 0.0 : kNarrowSaves});
+    const double spare = groups - need - best;
+    if (spare <= 0.0) return 0;
+    *max_delay = spare / (tile_shape(F, lanes).slices * (double)p->nnz / 64.0 * kStepUs);
+    return lanes;
 }
 
-int epp_build_tiles(epp_path* p, int lanes, hipStream_t s, TilePlan** out) {
+int epp_build_tiles(epp_path* p, int lanes, double max_delay, hipStream_t s, TilePlan** out) {
     *out = nullptr;
     const int rows_per_tile = tile_rows(lanes);
     const int64_t R = p->n_stream_rows;
@@ -1010,7 +1115,10 @@ int epp_build_tiles(epp_path* p, int lanes, hipStream_t s, TilePlan** out) {
     const int32_t* rowptr = p->rowptr.as<int32_t>();
     const int2v* cv = reinterpret_cast<const int2v*>(p->cv.p);
 
-    // rows per length class
+    int shift = 0;
+    while (((p->n - 1) >> shift) >= kBuckets) ++shift;
+
+    // rows per length class, and the order of the ids
     DevArena counts;
     DevBuf hist, totals, places, block_hist;
     const unsigned blocks = blocks_for(R, kRowsPerBlock);
@@ -1023,14 +1131,21 @@ int epp_build_tiles(epp_path* p, int lanes, hipStream_t s, TilePlan** out) {
     EPP_HIP_TRY(hipMemsetAsync(totals.p, 0, 2 * DevArena::rounded(kTileBins * 4), s));
     PinnedWords host;
     EPP_TRY(host.get(kTileBins));
+    if (lanes == 4) sample_order<4>(p, split, shift, totals.as<unsigned>() + 3, s);
+    else if (lanes == 8) sample_order<8>(p, split, shift, totals.as<unsigned>() + 3, s);
+    else sample_order<16>(p, split, shift, totals.as<unsigned>() + 3, s);
     hipLaunchKernelGGL(k_tile_count, dim3(blocks), dim3(kListBlock), 0, s, rowptr, R, split, block_hist.as<unsigned>(),
-                       totals.as<unsigned>());
-    hipLaunchKernelGGL(k_tile_classes, dim3(kTileBins), dim3(256), 0, s, block_hist.as<unsigned>(), (int)blocks, hist.as<unsigned>());
+                       totals.as<unsigned>(), max_delay);
+    hipLaunchKernelGGL(k_tile_classes, dim3(kTileBins), dim3(256), 0, s, block_hist.as<unsigned>(), (int)blocks, hist.as<unsigned>(),
+                       totals.as<unsigned>(), max_delay);
     EPP_HIP_TRY(hipGetLastError());
     unsigned* const h = reinterpret_cast<unsigned*>(host.p);  // the classes, then the totals
     EPP_HIP_TRY(hipMemcpyAsync(h, hist.p, kTileBins * 4, hipMemcpyDeviceToHost, s));
-    EPP_HIP_TRY(hipMemcpyAsync(h + kTileBins, totals.p, 3 * 4, hipMemcpyDeviceToHost, s));
+    EPP_HIP_TRY(hipMemcpyAsync(h + kTileBins, totals.p, 4 * 4, hipMemcpyDeviceToHost, s));
     EPP_HIP_TRY(hipStreamSynchronize(s));
+    TileOrder& order = p->tile_order[tile_order_of(lanes)];
+    order.delay = (double)h[kTileBins + 3] / kOrderSamples;
+    if (too_slow(h[kTileBins + 3], max_delay)) return EPP_OK;
     TileBins bins;
     unsigned rank = 0;
     for (int b = 0; b < kTileBins; ++b) { bins.first[b] = rank; rank += h[b]; }
@@ -1085,8 +1200,6 @@ int epp_build_tiles(epp_path* p, int lanes, hipStream_t s, TilePlan** out) {
     epp_scan_exclusive(batches.as<int>(), q->first_batch, q->n_tiles, total.as<long long>(), scan_tmp.as<int>(), s);
     // (the scan's last element is the total; little endian)
     EPP_HIP_TRY(hipMemcpyAsync(q->first_batch + q->n_tiles, total.p, 4, hipMemcpyDeviceToDevice, s));
-    int shift = 0;
-    while (((p->n - 1) >> shift) >= kBuckets) ++shift;
     int* const bad = totals.as<int>();  // (what it held has been read)
     EPP_HIP_TRY(hipMemsetAsync(bad, 0, 4, s));
     if (lanes == 4) sort_tiles<4>(q, cv, dealt.as<Dealt>(), shift, bad, s);
@@ -1096,7 +1209,7 @@ int epp_build_tiles(epp_path* p, int lanes, hipStream_t s, TilePlan** out) {
     EPP_HIP_TRY(hipGetLastError());
     EPP_HIP_TRY(hipStreamSynchronize(s));  // (the temporaries go, too)
     if (h[0]) {
-        p->tile_order[tile_order_of(lanes)].unfit = true;
+        order.unfit = true;
         return EPP_OK;
     }
     guard.q = nullptr;

@@ -178,3 +178,31 @@ def test_every_refused_block(F, monkeypatch):
         del p, paths
         assert epp.alloc_stats["live"] == live, f"block {k} of {blocks} refused"
         k += 1
+
+
+@pytest.mark.parametrize("order,tiles", [("random", True), ("band", False), ("degree", False)])
+def test_ids_in_an_order_stay_on_the_group_table(order, tiles, monkeypatch):
+    """By the library's own rule: 20 M entries among 400,000 vertices run on tiles where neighbours lie anywhere; not where rows have
+    theirs close together (within 300 ids; hubs in front), and the entries of a batch would wait for each other."""
+    monkeypatch.setenv("EPP_TUNE_SMALL_PREPARE", "0")
+    n, F, gen = 400_000, 64, torch.Generator(device="cuda").manual_seed(7)
+    u, v = ((torch.rand(13_000_000, generator=gen, device="cuda", dtype=torch.float64) ** 4 * n).long() for _ in range(2))
+    if order == "band":
+        v = (u + torch.randint(1, 300, u.shape, generator=gen, device="cuda")) % n
+    elif order == "random":
+        ids = torch.randperm(n, generator=gen, device="cuda")
+        u, v = ids[u], ids[v]
+    keys = torch.unique(torch.cat((u * n + v, v * n + u)))
+    row, col = keys // n, (keys % n).int()
+    rowptr = torch.zeros(n + 1, dtype=torch.int32, device="cuda")
+    rowptr[1:] = torch.cumsum(torch.bincount(row, minlength=n), 0)
+    val = torch.randn(col.shape, generator=gen, device="cuda")
+    path = epp.epp_prepare(n, rowptr, col, val, torch.arange(n, dtype=torch.int32, device="cuda"), 1).path(0)
+    X, Y = torch.randn(n, F, generator=gen, device="cuda"), torch.zeros(n, F, device="cuda")
+    path.prepare_width(F)
+    epp.epp_backward_aggregate(path, X, Y)
+    assert (path.info().n_split_rows == 0) == tiles  # (only the group table has groups that cut rows)
+    want = torch.sparse_csr_tensor(rowptr, col, val.double(), (n, n)) @ X.double()
+    most = torch.sparse_csr_tensor(rowptr, col, val.double().abs(), (n, n)) @ X.double().abs()
+    # chains of 512 additions, and at most n / 512 of their sums: each addition rounds by 2^-24
+    assert bool(((Y.double() - want).abs() <= (512 + n / 512) * 2.0 ** -24 * most).all())
