@@ -28,7 +28,16 @@ Schedule* find_schedule(epp_path* p, int gs) {
 epp_path* entries_of(epp_path* p) { return p->outer ? p->outer : p; }
 const epp_path* entries_of(const epp_path* p) { return p->outer ? p->outer : p; }
 
-// Tiles, where launches of the width run on them and there is memory for them.
+void drop_unused_tiles(epp_path* p) {
+    for (size_t i = 0; i < p->tile_plans.size();) {
+        bool used = false;
+        for (const auto& x : p->widths) used |= (x.tiles == p->tile_plans[i]);
+        if (!used) { delete p->tile_plans[i]; p->tile_plans.erase(p->tile_plans.begin() + i); } else ++i;
+    }
+}
+
+// Tiles, where launches of the width run on them and there is memory for them.  (What was taken for them in vain
+// goes back: the group table needs memory, too.)
 int prepare_tiles(epp_path* p, epp_path::WidthCfg* w, hipStream_t s) {
     double max_delay;
     const int lanes = epp_tile_lanes(p, w->F, &max_delay);
@@ -46,19 +55,52 @@ int prepare_tiles(epp_path* p, epp_path::WidthCfg* w, hipStream_t s) {
         p->tile_plans.push_back(q);
     }
     void *parts = nullptr, *packed = nullptr;
+    const size_t pooled = p->pool->bufs.size();
+    bool room = true;
     if (q->n_parts > 0) {
-        if (p->pool->get((size_t)q->n_parts * (size_t)w->F * 4, al, &parts) != EPP_OK) return EPP_OK;
-        if (!p->pool->accounted_by) p->pool->accounted_by = p;
+        room = p->pool->get((size_t)q->n_parts * (size_t)w->F * 4, al, &parts) == EPP_OK;
+        if (room && !p->pool->accounted_by) p->pool->accounted_by = p;
     }
-    if (const size_t bytes = epp_tile_packed_bytes(p, w->F, lanes)) {
-        EPP_TRY(epp_check_sources(p, s));  // (the launch copies the rows of `sources` only)
-        if (p->rows_pool->get(bytes, al, &packed) != EPP_OK) return EPP_OK;
-        if (!p->rows_pool->accounted_by) p->rows_pool->accounted_by = p;
+    const size_t bytes = epp_tile_packed_bytes(p, w->F, lanes);
+    if (room && bytes) {
+        const int rc = epp_check_sources(p, s);  // (the launch copies the rows of `sources` only)
+        room = rc == EPP_OK && p->rows_pool->get(bytes, al, &packed) == EPP_OK;
+        if (rc != EPP_OK && rc != EPP_ERR_ALLOC) return rc;
+        if (room && !p->rows_pool->accounted_by) p->rows_pool->accounted_by = p;
+    }
+    if (!room) {
+        p->pool->keep_first(pooled);
+        drop_unused_tiles(p);
+        return EPP_OK;
     }
     w->tile_parts = static_cast<float*>(parts);
     w->packed = static_cast<float*>(packed);
     w->ld = w->F;
     w->tiles = q;
+    return EPP_OK;
+}
+
+// Group table, partial rows, locality marks and partition of a width; with tiles, what the if-else baseline needs of it.
+int prepare_groups(epp_path* p, epp_path::WidthCfg* w, hipStream_t s) {
+    const int F = w->F, gs = w->forced_gs > 0 ? w->forced_gs : epp_default_group_size(p, F);
+    Schedule* sc = find_schedule(p, gs);
+    if (!sc) EPP_TRY(epp_build_schedule(p, gs, s, &sc));
+    if (!w->tiles) w->ld = epp_packed_stride(p, F);
+    if (w->ld > F) {
+        EPP_TRY(epp_check_sources(p, s));  // (the launch copies the rows of `sources` only)
+        void* scratch = nullptr;
+        if (p->rows_pool->get((size_t)p->n * (size_t)w->ld * 4, epp_alloc_of(p), &scratch) == EPP_OK) {
+            if (!p->rows_pool->accounted_by) p->rows_pool->accounted_by = p;
+            w->packed = static_cast<float*>(scratch);
+        } else {
+            w->ld = F;  // no memory for the copy: the rows are read where they are
+        }
+    }
+    EPP_TRY(epp_tune_locality(p, F, w->ld, gs, !w->tiles, s, &w->log2_slices, &w->part));
+    // partial rows of the plain group table: not needed where every launch uses the partitioned
+    // layout (the all-active handle also serves the if-else baseline, which never does)
+    if (!w->part || p->all_rows) EPP_TRY(sc->ensure_pieces(F, epp_alloc_of(p)));
+    w->sched = sc;
     return EPP_OK;
 }
 
@@ -81,11 +123,11 @@ int prepare_width(epp_path* self, int F, hipStream_t s, epp_path::WidthCfg** out
             if (out) *out = w;
             return EPP_OK;
         }
-        const int gs = w->forced_gs > 0 ? w->forced_gs : epp_default_group_size(p, F);
         delete w->part;
         w->part = nullptr;
         w->tiles = nullptr;
         w->packed = nullptr;
+        const size_t pooled = p->pool->bufs.size(), rows_pooled = p->rows_pool->bufs.size();
         if (w->forced_gs <= 0 && !w->rows) EPP_TRY(prepare_tiles(p, w, s));
         if (w->tiles && !p->all_rows) {
             w->prepared = true;
@@ -93,24 +135,16 @@ int prepare_width(epp_path* self, int F, hipStream_t s, epp_path::WidthCfg** out
             return EPP_OK;
         }
         // (the all-active handle also serves the if-else baseline, which runs on the group table)
-        Schedule* sc = find_schedule(p, gs);
-        if (!sc) EPP_TRY(epp_build_schedule(p, gs, s, &sc));
-        if (!w->tiles) w->ld = epp_packed_stride(p, F);
-        if (w->ld > F) {
-            EPP_TRY(epp_check_sources(p, s));  // (the launch copies the rows of `sources` only)
-            void* scratch = nullptr;
-            if (p->rows_pool->get((size_t)p->n * (size_t)w->ld * 4, epp_alloc_of(p), &scratch) == EPP_OK) {
-                if (!p->rows_pool->accounted_by) p->rows_pool->accounted_by = p;
-                w->packed = static_cast<float*>(scratch);
-            } else {
-                w->ld = F;  // no memory for the copy: the rows are read where they are
-            }
+        int rc = prepare_groups(p, w, s);
+        if (rc == EPP_ERR_ALLOC && w->tiles) {  // memory for one of the two
+            w->tiles = nullptr;
+            w->packed = nullptr;
+            p->pool->keep_first(pooled);
+            p->rows_pool->keep_first(rows_pooled);
+            drop_unused_tiles(p);
+            rc = prepare_groups(p, w, s);
         }
-        EPP_TRY(epp_tune_locality(p, F, w->ld, gs, !w->tiles, s, &w->log2_slices, &w->part));
-        // partial rows of the plain group table: not needed where every launch uses the partitioned
-        // layout (the all-active handle also serves the if-else baseline, which never does)
-        if (!w->part || p->all_rows) EPP_TRY(sc->ensure_pieces(F, epp_alloc_of(p)));
-        w->sched = sc;
+        EPP_TRY(rc);
         w->prepared = true;
         EPP_HIP_TRY(hipStreamSynchronize(s));
         epp_release_canonical_if_unused(p);
@@ -245,11 +279,7 @@ extern "C" int epp_path_set_group_size(epp_path_t* self, int F, int gs, epp_stre
     delete w->part;
     w->part = nullptr;
     w->tiles = nullptr;
-    for (size_t i = 0; i < p->tile_plans.size();) {
-        bool used = false;
-        for (const auto& x : p->widths) used |= (x.tiles == p->tile_plans[i]);
-        if (!used) { delete p->tile_plans[i]; p->tile_plans.erase(p->tile_plans.begin() + i); } else ++i;
-    }
+    drop_unused_tiles(p);
     // drop cached tables that no width refers to any more
     for (size_t i = 0; i < p->scheds.size();) {
         bool used = false;

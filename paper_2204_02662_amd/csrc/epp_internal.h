@@ -169,7 +169,8 @@ struct Schedule {
 
 // Scratch memory of a launch that the paths of one handle share: a handle is used by one call at
 // a time, so two of its paths never need their scratch at once.  Buffers only ever get added (a
-// captured HIP graph may hold the address of an older one); a request is served by the smallest
+// captured HIP graph may hold the address of an older one), unless the width they were added for has
+// not been prepared; a request is served by the smallest
 // buffer that is large enough, else by a new one, sized an eighth above the request at most so
 // that paths of nearly equal size end up on one buffer.
 struct ScratchPool {
@@ -189,6 +190,9 @@ struct ScratchPool {
         }
         *out = best->p;
         return EPP_OK;
+    }
+    void keep_first(size_t n) {
+        for (; bufs.size() > n; bufs.pop_back()) delete bufs.back();
     }
     size_t bytes() const {
         size_t b = 0;

@@ -12,6 +12,8 @@ from _util import assert_close, assert_paths_bit_exact, dev, gpu_prepare, gpu_pr
 
 pytestmark = pytest.mark.gpu
 
+_ALLOCATORS = []  # (handles that a failed test leaves behind give their memory back through them)
+
 
 def _force(monkeypatch, lanes, split=512, **more):
     for k, v in {"ROWS": "0", "TILES": "2", "TILE_LANES": lanes, "TILE_SPLIT": split, "TILES_AT_ONCE": 512,
@@ -206,3 +208,55 @@ def test_ids_in_an_order_stay_on_the_group_table(order, tiles, monkeypatch):
     most = torch.sparse_csr_tensor(rowptr, col, val.double().abs(), (n, n)) @ X.double().abs()
     # chains of 512 additions, and at most n / 512 of their sums: each addition rounds by 2^-24
     assert bool(((Y.double() - want).abs() <= (512 + n / 512) * 2.0 ** -24 * most).all())
+
+
+@pytest.mark.parametrize("F", [47, 64])
+@pytest.mark.parametrize("all_active", [False, True])
+def test_memory_for_the_group_table_is_enough(F, all_active, monkeypatch):
+    """Whatever lies between what the group table needs and what the tiles take: the width is prepared, and nothing is left over."""
+    sizes, live, peak, budget = {}, [0], [0], [1 << 60]
+
+    def alloc(nbytes, ctx):
+        p = epp._torch_alloc(nbytes, ctx) if live[0] + nbytes <= budget[0] else None
+        if p:
+            sizes[p] = nbytes
+            live[0] += nbytes
+            peak[0] = max(peak[0], live[0])
+        return p
+
+    def free(ptr, ctx):
+        live[0] -= sizes.pop(ptr)
+        epp._torch_free(ptr, ctx)
+
+    _ALLOCATORS.append(epp._Alloc(epp._ALLOC_FN(alloc), epp._FREE_FN(free), None))
+    monkeypatch.setattr(epp, "_TORCH_ALLOC", _ALLOCATORS[-1])
+    g = graphgen.random_graph("rmat", 40_001, seed=611, raw_draws=900_000)
+    train = np.arange(g.n, dtype=np.int32)
+    X = graphgen.normal_rows(g.n, F, None, 612)
+    want = oracle.full_aggregate(g.n, g.rowptr, g.col, g.val, X)
+    some = np.diff(g.rowptr) > 0
+
+    def prepared(tiles, limit):
+        """Bytes that preparing the width took at most, and whether it has tiles."""
+        _force(monkeypatch, 8, 32, TILES=tiles, PACK=0, PART=0)
+        handle = gpu_prepare_full(g) if all_active else gpu_prepare(g, train, 1)
+        p = handle if all_active else handle.path(0)
+        base = peak[0] = live[0]
+        budget[0] = base + limit
+        p.prepare_width(F)
+        budget[0] = 1 << 60
+        most, cut = peak[0] - base, p.info().part_rows
+        got = run_full(p, X) if all_active else run_partial(p, X)
+        assert_close(got[some], want[some], f"limit {limit}")
+        if all_active and limit < 1 << 50:
+            assert_close(run_ifelse(p, gpu_prepare(g, train, 1), 0, X)[some], want[some], f"if-else, limit {limit}")
+        del p, handle
+        assert live[0] == 0
+        return most, cut > 0
+
+    groups, with_tiles = prepared(0, 1 << 59)[0], prepared(2, 1 << 59)[0]
+    assert groups < with_tiles
+    limits = np.linspace(groups, with_tiles, 25).astype(np.int64).tolist()
+    assert [prepared(2, limit)[1] for limit in (limits[0], limits[-1])] == [False, True]
+    for limit in limits[1:-1]:
+        prepared(2, limit)
