@@ -11,6 +11,9 @@
  *   EPP_TUNE_GS           group size for every (path, F) that has none forced            [selector]
  *   EPP_TUNE_ROWS         small paths and widths of at most 4 floats run on a kernel that takes rows whole and needs no
  *                         group table: 0 never, 1 where it is faster, 2 always           [1]
+ *   EPP_TUNE_TILES        large paths run on tiles of rows whose sums stay on chip: 0 never, 1 where it is faster, 2 always [1]
+ *                         (large paths do not while EPP_TUNE_GS, EPP_TUNE_PACK, EPP_TUNE_HOT_MB, EPP_TUNE_LOG2_SLICES or
+ *                         EPP_TUNE_PART=2 asks for a choice that only the group table has)
  *   EPP_TUNE_PACK         source rows copied to a wider stride by the launch: 0 never, 1 where it pays, 2 always  [1]
  *   EPP_TUNE_HOT_MB       budget of the hot source rows (given: marks are set wherever the rows do not fit it), 0 switches
  *                         hot/cold marking off                                           [80, where marks pay]

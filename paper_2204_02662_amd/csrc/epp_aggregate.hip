@@ -761,6 +761,14 @@ int epp_default_group_size(const epp_path* p, int F) {
     return 1 << e;
 }
 
+bool epp_group_layout_asked() {
+    return env_int("EPP_TUNE_PART", 1) == 2 || std::getenv("EPP_TUNE_HOT_MB") || std::getenv("EPP_TUNE_LOG2_SLICES");
+}
+
+bool epp_group_table_asked() {
+    return epp_group_layout_asked() || env_int("EPP_TUNE_GS", 0) > 0 || env_int("EPP_TUNE_PACK", 1) != 1;
+}
+
 // 128-byte lines that a row of F floats touches on average where the rows are `ld` floats apart.
 double epp_lines_per_row(int F, int ld) {
     int64_t lines = 0;

@@ -395,6 +395,10 @@ int epp_launch_aggregate(epp_path* p, Schedule* sc, int log2_slices, const float
                          const Partition* part = nullptr, const unsigned int* inner_rows = nullptr,
                          float* packed = nullptr, int ld = 0, const unsigned long long* sources = nullptr);
 double epp_lines_per_row(int F, int ld);           // 128-byte lines that a row of F floats touches on average, rows ld floats apart
+// Whether a switch of the environment asks for what only the group kernel has: a layout of its entries; that, a group size or a
+// choice of the copied source rows.
+bool epp_group_layout_asked();
+bool epp_group_table_asked();
 int epp_packed_stride(const epp_path* p, int F);  // floats from row to row of packed source rows; F: not packed
 // rows.hip: one launch that processes rows whole, for small paths
 bool epp_rows_kernel_fits(const epp_path* p, int F);

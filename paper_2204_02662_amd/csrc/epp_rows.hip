@@ -370,14 +370,13 @@ bool epp_rows_kernel_fits(const epp_path* p, int F) {
         if (*e == '0') return false;
         if (*e == '2') return p->nnz <= (1 << 30);
     }
-    // (the switches that force a layout on the group kernel ask for that kernel)
-    const char* part = std::getenv("EPP_TUNE_PART");
-    if ((part && *part == '2') || std::getenv("EPP_TUNE_HOT_MB") || std::getenv("EPP_TUNE_LOG2_SLICES")) return false;
+    if (epp_group_layout_asked()) return false;
     if (F <= 4) return p->nnz <= (1 << 30);
     if (F <= 16 && p->nnz <= (F <= 8 ? 10000000 : 5000000)) return true;
+    if (F > 16 && p->nnz * F <= 16000000) return true;
+    if (epp_group_table_asked()) return false;
     double any_delay;
     if (F <= 16) return p->nnz <= (F < 16 ? 48000000 : 12000000) && epp_tile_lanes(p, F, &any_delay) == 0;
-    if (p->nnz * F <= 16000000) return true;
     const bool whole = F % 16 == 0;
     return F <= 64 && p->nnz * F <= (whole ? 64000000 : 100000000) && p->n_src * F <= (whole ? 10000000 : 28000000);
 }

@@ -1088,7 +1088,11 @@ int epp_tile_lanes(const epp_path* p, int F, double* max_delay) {
     if (mode == 0 || F < 5 || p->nnz == 0) return 0;
     // (a source's id has 23 bits in an entry, and its row's place in the matrix 32)
     if (p->n > (1ll << kColBits) || (p->n - 1) * (int64_t)F >= (1ll << 32)) return 0;
-    if (mode == 2) return env_int("EPP_TUNE_TILE_LANES", 8);
+    if (mode == 2) {
+        const int lanes = env_int("EPP_TUNE_TILE_LANES", 8);
+        return lanes == 4 || lanes == 16 ? lanes : 8;
+    }
+    if (epp_group_table_asked()) return 0;
     if (p->nnz < 4'000'000 || p->n_src < (F <= 16 ? 40'000 : 100'000)) return 0;
     const Sources src(p);
     const double groups = group_launch_us(p, src, F);

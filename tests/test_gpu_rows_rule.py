@@ -50,3 +50,13 @@ def test_rule_and_results(F, rows, monkeypatch):
     for mode, out in got.items():
         assert bool(((out.double() - want).abs() <= 128 * 2.0 ** -24 * most).all()), (F, mode)
     assert torch.equal(got[""][7], got["0"][7])
+
+
+@pytest.mark.parametrize("switch,value", [("GS", 24), ("PACK", 0), ("PACK", 2), ("HOT_MB", 1)])
+def test_switches_of_the_group_table_ask_for_it(switch, value, monkeypatch):
+    rowptr, col, val = (torch.from_numpy(a).to(dev()) for a in _regular_graph())
+    train = torch.arange(0, N, 1, dtype=torch.int32, device="cuda")
+    p = epp.epp_prepare(N, rowptr, col, val, train, 1).path(0)
+    monkeypatch.setenv(f"EPP_TUNE_{switch}", str(value))
+    p.prepare_width(24)
+    assert p.info().n_split_rows > 0 and (p.info().group_size == 24 or switch != "GS")

@@ -182,12 +182,10 @@ def test_every_refused_block(F, monkeypatch):
         k += 1
 
 
-@pytest.mark.parametrize("order,tiles", [("random", True), ("band", False), ("degree", False)])
-def test_ids_in_an_order_stay_on_the_group_table(order, tiles, monkeypatch):
-    """By the library's own rule: 20 M entries among 400,000 vertices run on tiles where neighbours lie anywhere; not where rows have
-    theirs close together (within 300 ids; hubs in front), and the entries of a batch would wait for each other."""
-    monkeypatch.setenv("EPP_TUNE_SMALL_PREPARE", "0")
-    n, F, gen = 400_000, 64, torch.Generator(device="cuda").manual_seed(7)
+def _ordered_graph(order):
+    """23 M entries among 400,000 vertices: hubs and their neighbours anywhere ("random") or in front ("degree"), or all neighbours
+    within 300 ids ("band")."""
+    n, gen = 400_000, torch.Generator(device="cuda").manual_seed(7)
     u, v = ((torch.rand(13_000_000, generator=gen, device="cuda", dtype=torch.float64) ** 4 * n).long() for _ in range(2))
     if order == "band":
         v = (u + torch.randint(1, 300, u.shape, generator=gen, device="cuda")) % n
@@ -200,6 +198,15 @@ def test_ids_in_an_order_stay_on_the_group_table(order, tiles, monkeypatch):
     rowptr[1:] = torch.cumsum(torch.bincount(row, minlength=n), 0)
     val = torch.randn(col.shape, generator=gen, device="cuda")
     path = epp.epp_prepare(n, rowptr, col, val, torch.arange(n, dtype=torch.int32, device="cuda"), 1).path(0)
+    return n, rowptr, col, val, path
+
+
+@pytest.mark.parametrize("order,tiles", [("random", True), ("band", False), ("degree", False)])
+def test_ids_in_an_order_stay_on_the_group_table(order, tiles):
+    """By the library's own rule, paths run on tiles where neighbours lie anywhere, but not where rows have theirs close together and
+    the entries of a batch would wait for each other."""
+    F, gen = 64, torch.Generator(device="cuda").manual_seed(8)
+    n, rowptr, col, val, path = _ordered_graph(order)
     X, Y = torch.randn(n, F, generator=gen, device="cuda"), torch.zeros(n, F, device="cuda")
     path.prepare_width(F)
     epp.epp_backward_aggregate(path, X, Y)
@@ -208,6 +215,17 @@ def test_ids_in_an_order_stay_on_the_group_table(order, tiles, monkeypatch):
     most = torch.sparse_csr_tensor(rowptr, col, val.double().abs(), (n, n)) @ X.double().abs()
     # chains of 512 additions, and at most n / 512 of their sums: each addition rounds by 2^-24
     assert bool(((Y.double() - want).abs() <= (512 + n / 512) * 2.0 ** -24 * most).all())
+
+
+@pytest.mark.parametrize("switch,value", [("GS", 96), ("PACK", 0), ("PACK", 2), ("PART", 2), ("HOT_MB", 1), ("LOG2_SLICES", 1)])
+def test_switches_of_the_group_table_ask_for_it(switch, value, monkeypatch):
+    monkeypatch.setenv(f"EPP_TUNE_{switch}", str(value))
+    path = _ordered_graph("random")[-1]
+    path.prepare_width(64)
+    i = path.info()
+    assert i.n_split_rows > 0
+    assert i.group_size == 96 or switch != "GS"
+    assert i.part_hot_entries > 0 or switch != "PART"
 
 
 @pytest.mark.parametrize("F", [47, 64])
