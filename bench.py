@@ -254,7 +254,7 @@ def run_config(config_id: int, args, detail: bool):
         layers.append({
             "l": l, "F": F, "rows": i.n_rows, "sources": i.n_src, "nnz": i.nnz, "max_len": i.max_len,
             "group_size": i.group_size, "groups": i.n_groups, "split_rows": i.n_split_rows,
-            # source-partitioned layout (zeros: not in use for this layer)
+            # source-partitioned layout (zeros: not in use for this layer); on tiles, rows cut into parts, 0, parts
             "partitioned_rows": i.part_rows, "entries_in_xcd_sections": i.part_hot_entries,
             "partial_rows": i.part_partial_rows,
             # 1: the path keeps no entry arrays and runs on those of layer l - 1 (skipping that path's extra entries)
@@ -272,7 +272,7 @@ def run_config(config_id: int, args, detail: bool):
     model_ms = (lines * ((1.0 - l2_hit) / GATHER_MISS_LINES_PER_S + l2_hit / GATHER_L2_LINES_PER_S) * 1e3
                 if l2_hit is not None else None)
     roofline = {
-        "bound": "hbm", "kernel": f"k_aggregate (layer l={dom['l']}, F={dom['F']})",
+        "bound": "hbm", "kernel": f"aggregation launch of layer l={dom['l']}, F={dom['F']}",
         "achieved": dom["roofline_GBs"], "peak": HBM_PEAK_GBS, "unit": "GB/s",
         "frac": dom["roofline_frac"], "traffic": traffic,
         # the same launch by the counters: HBM-side bytes actually moved per second (rises when caching gets

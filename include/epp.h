@@ -100,7 +100,9 @@ typedef struct {
     int64_t len_hist[32]; /* rows per length class c: len <= 1 -> 0, else ceil(log2(len))   */
     int64_t bytes;        /* device bytes held by the path (canonical arrays + schedules,
                              the per-group partial rows of every width used included)     */
-    /* schedule most recently used / built (0 if none yet) */
+    /* schedule most recently used / built (0 if none yet).  Launches that need no group table (small paths, and
+       large ones on tiles of rows) have no groups: group_size is then the one the selector names, n_groups what
+       it would make of the path, n_split_rows 0 */
     int32_t sched_F;        /* gradient width it was built for                              */
     int32_t group_size;     /* gs: entries per group (Sec. 2.2, Sec. 5)                     */
     int64_t n_groups;       /* ceil(nnz / gs)                                               */
@@ -179,12 +181,13 @@ int epp_paper_linreg_group_size(int64_t vertices, int64_t undirected_edges);
 /* One-off preparation of a path for gradient width F: builds the group table for the group size
  * in force (the selector's, or the one forced by epp_path_set_group_size), allocates the
  * partial rows of the groups (2 * n_groups * F floats, only if some row is cut by a group
- * boundary) and chooses the cache-locality marks of the entries.  Small paths, and widths of at most
- * 4 floats, run without a group table unless a group size is forced (epp_path_info then names the
- * selector's).  Where it pays, the width also gets scratch memory for a copy of the source rows that
+ * boundary) and chooses the cache-locality marks of the entries.  Small paths, widths of at most 4 floats, and
+ * large paths whose entries are laid out on tiles of rows (8 bytes per entry, F floats per part of a cut row) run without a
+ * group table unless a group size is forced (epp_path_info then names the selector's); all-active handles have one
+ * in any case.  Where it pays, the width also gets scratch memory for a copy of the source rows that
  * every launch makes (n rows of F floats rounded up to a power of two, beyond 16 to a multiple of 16;
- * one buffer for all paths of a handle) and the source-partitioned layout of the entries; without memory
- * for these the width does without them.  Allocates through the handle's
+ * one buffer for all paths of a handle) and, on the group table, the source-partitioned layout of the entries; without
+ * memory for these or for tiles the width does without them.  Allocates through the handle's
  * allocator and synchronises `stream`; must not be called under stream capture.  Calling it again
  * for a prepared width does nothing.  The aggregate entry points below require it: they never
  * allocate and never wait. */

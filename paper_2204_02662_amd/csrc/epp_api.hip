@@ -108,7 +108,7 @@ int prepare_groups(epp_path* p, epp_path::WidthCfg* w, hipStream_t s) {
 // waits; the aggregate entry points only look the result up.
 int prepare_width(epp_path* self, int F, hipStream_t s, epp_path::WidthCfg** out) {
     epp_path* p = entries_of(self);
-    self->last_F = F;
+    self->last_F = p->last_F = F;
     epp_path::WidthCfg* w = width_cfg(p, F);
     if (!w->prepared) {
         EPP_TRY(epp_ensure_canonical(p, s));  // (given back while all widths ran on reconstructed copies)
@@ -149,7 +149,6 @@ int prepare_width(epp_path* self, int F, hipStream_t s, epp_path::WidthCfg** out
         EPP_HIP_TRY(hipStreamSynchronize(s));
         epp_release_canonical_if_unused(p);
     }
-    p->last_F = F;
     if (out) *out = w;
     return EPP_OK;
 }

@@ -278,3 +278,13 @@ def test_memory_for_the_group_table_is_enough(F, all_active, monkeypatch):
     assert [prepared(2, limit)[1] for limit in (limits[0], limits[-1])] == [False, True]
     for limit in limits[1:-1]:
         prepared(2, limit)
+
+
+def test_report_of_a_path_that_was_prepared_through_its_inner_one(monkeypatch):
+    _force(monkeypatch, 8, SHARE_PCT=1)
+    g = graphgen.random_graph("rmat", 20_000, seed=621, raw_draws=200_000)
+    paths = gpu_prepare(g, graphgen.training_set(g.n, 4_000, 622), 2)
+    assert paths.path(1).info().shares_entries
+    paths.path(1).prepare_width(20)
+    assert [paths.path(l).info().sched_F for l in (0, 1)] == [20, 20]
+    assert paths.path(0).info().n_split_rows == 0 and paths.path(0).info().group_size == paths.path(0).select_group_size(20)
