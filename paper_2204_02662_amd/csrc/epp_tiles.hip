@@ -3,7 +3,7 @@
 //
 // The group kernel (epp_aggregate.hip) takes entries row after row, so every XCD gathers from everywhere at any time and
 // an L2 of 4 MB serves next to nothing (2.4 M sources, F = 64: 11 % of the lines); the rest runs at the 60 G lines/s
-// that the fabric gives.  Here a wavefront owns a tile of up to 159 rows, whose sums lie in LDS, and takes the
+// that the fabric gives.  Here a wavefront owns a tile of 79 to 255 rows, whose sums lie in LDS, and takes the
 // tile's entries in the order of their sources.  The 256 wavefronts of an XCD therefore sweep the source matrix
 // together, and a source row that one of them has fetched is still in L2 when the others come to it.
 //
@@ -34,7 +34,7 @@ namespace {
 constexpr int kTileWaves = 8;            // wavefronts of a workgroup, which fills a CU's LDS
 constexpr int kTilesAtOnce = 256 * kTileWaves;  // tiles of a generation, which run at the same time
 constexpr int kSplitMax = 512;           // longest row that is not cut into parts (and a part's entries, at most)
-constexpr int kPiece = 32;               // entries of a row (about) that are added up before their sum is added to the row's
+constexpr int kPiece = 32;               // entries of a row (on average) that are added up before their sum is added to the row's
 constexpr int kTileBins = 128;           // length classes by which rows are dealt
 constexpr unsigned kTogether = 64;       // consecutive tiles that are prepared on one XCD
 constexpr int kChunk = 4;                // entries of a cut row that stay together
@@ -657,10 +657,12 @@ __global__ __launch_bounds__(kListBlock) void k_pack_slices(const float* __restr
 // latency instead: there the gathers do run kDepth batches ahead (114 M entries, 233 K sources, F = 16: 697 us without, 575
 // with one batch, 555 with two, 554 with three; the group kernel 920).
 //
-// A sum is formed in LDS over about kPiece entries at a time, and those sums in registers, where a lane has those of the rows
-// that it will write.  Its rounding error then grows like that of a sum of 32 + 16 terms, not of 512: over 20 all-active
-// launches (both models, 22 to 288 M entries, F = 16 to 128) it is 0.63 to 0.89 of the group kernel's against 64 bits; one
-// chain of 512 would be 0.99 to 1.6 of it.  Adding up in LDS alone would be no faster (within 3 %, the spread of the runs).
+// A sum is formed in LDS over a part of the sweep at a time, and those sums in registers, where a lane has those of the rows that it
+// will write.  A part holds kPiece entries of a row whose sources lie anywhere; the rounding error then grows like that of a sum of
+// 32 + 16 terms, not of 512: over 20 all-active launches (both models, ids in random order, 22 to 288 M entries, F = 16 to 128) it is
+// 0.63 to 0.89 of the group kernel's against 64 bits.  A row whose sources all lie in one part is one chain of up to kSplitMax, 0.99 to
+// 1.6 of it; paths of such rows stay on the group table (k_tile_order).  Adding up in LDS alone would be no faster (within 3 %, the
+// spread of the runs).
 template <int LANES, bool INNER>
 __global__ __launch_bounds__(kTileWaves * 64, 2) void k_aggregate_tiles(TileArgs a) {
     constexpr int kRows = tile_rows(LANES), kSlots = 64 / LANES, kSteps = LANES;

@@ -288,3 +288,26 @@ def test_report_of_a_path_that_was_prepared_through_its_inner_one(monkeypatch):
     paths.path(1).prepare_width(20)
     assert [paths.path(l).info().sched_F for l in (0, 1)] == [20, 20]
     assert paths.path(0).info().n_split_rows == 0 and paths.path(0).info().group_size == paths.path(0).select_group_size(20)
+
+
+@pytest.mark.parametrize("lanes", [4, 8, 16])
+def test_sums_of_rows_with_neighbouring_sources(lanes, monkeypatch):
+    """600 rows of 500 consecutive columns among rows of 8 columns anywhere: all of a row's entries meet in one part of the sweep,
+    so that its sum is one chain of additions, the longest there can be."""
+    _force(monkeypatch, lanes)
+    n, F, rng = 30_000, 24, np.random.default_rng(631)
+    cols = [np.sort(rng.choice(n, 8, replace=False)) for _ in range(n)]
+    for r in rng.choice(n, 600, replace=False):
+        cols[r] = rng.integers(n - 500) + np.arange(500)
+    rowptr = np.zeros(n + 1, np.int32)
+    rowptr[1:] = np.cumsum([c.size for c in cols])
+    col = np.concatenate(cols).astype(np.int32)
+    val = rng.random(col.size).astype(np.float32)  # all positive, like the inputs: sums grow, the worst case for a chain
+    X = rng.random((n, F)).astype(np.float32)
+    full = epp.epp_prepare_full(n, *(torch.from_numpy(a).to(dev()) for a in (rowptr, col, val)))
+    got = run_full(full, X).astype(np.float64)
+    want = np.add.reduceat(val[:, None].astype(np.float64) * X[col], rowptr[:-1])
+    # each of the at most 512 + 16 additions (fused with its product) rounds by 2^-24 of what is there by then, at most the sum
+    assert (np.abs(got - want) <= 528 * 2.0 ** -24 * want).all()
+    # and the errors of a chain hardly ever add up: 2-norms, 2^-24 times sqrt(500 / 3) on average
+    assert np.linalg.norm(got - want) <= 4 * np.sqrt(500 / 3) * 2.0 ** -24 * np.linalg.norm(want)
