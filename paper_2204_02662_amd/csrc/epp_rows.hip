@@ -358,13 +358,17 @@ static_assert((1 << 13) == 8 * kBlock * kU, "chunk length");
 // group of their own and read pairs far apart (this kernel's time over the group kernel's at 20 / 90 / 200 to 230 M entries,
 // 0.25 to 8 M sources, both models: F = 1 0.37 to 0.80, F = 2 0.38 to 0.85, F = 4 0.42 to 0.88, growing with the matrix and
 // the entries; F = 3, whose groups have four lanes, 0.74 to 0.91 / 0.88 to 1.06 / 0.92 to 1.02).
-// Rows of up to 64 bytes up to 10 (F <= 8) and 5 M entries, and where launches do not run on tiles (epp_tiles.hip) up to
-// 48 M, at 64 bytes, which the group kernel reads as whole half lines, up to 12 M (over the group kernel's time, 5 to 44 M entries, 0.1 to
-// 8.4 M vertices, both models: F = 7 0.68 to 1.04, F = 12 0.62 to 1.01, F = 16 0.63 to 0.91, at 13 to 20 M 0.75 to 1.11).
+// Rows of up to 64 bytes up to 10 (F <= 8) and 5 M entries, and where launches do not run on tiles (epp_tiles.hip) as far as the
+// group kernel, which reads copies of 32 or 64 bytes instead, needs at least as long (over its time, 5 to 46 M entries, 0.02 to 6 M
+// vertices, both models): 8 floats 0.50 to 0.95 everywhere; 5 to 7 up to 30 M entries 0.67 to 0.98, beyond to 1.13; 9 and 10 up to 20 M
+// 0.76 to 1.03, beyond to 1.18; 11 to 13 up to 12 M 0.61 to 1.01, beyond to 1.30; 14 and 15 up to 8 M 0.79 to 1.03, beyond to 1.44; 16 up to
+// 12 M 0.59 to 0.94.
 // Rows of up to 256 bytes while the second kernel and the chain of loads still show: at 16 M floats of gathered rows in any
 // case; up to 100 M, where the source matrix of 110 MB still stays in the memory-side cache, if the group kernel has to read
-// rows across the ends of lines (F = 20 to 47: 0.66 to 1.02; at 3 to 7 M vertices' rows of 140 MB and more 0.9 to 1.3), and up
-// to 64 M of 40 MB if not (F = 32 and 64: 0.69 to 0.98; beyond 0.8 to 1.4).
+// rows across the ends of lines (F = 17 to 31: 0.63 to 1.10, at most 1.02 in nine of ten; above 32, if rows are no whole number of 16 bytes, 0.74
+// to 1.20 and 0.93 on average; at 3 to 7 M vertices' rows of 140 MB and more 0.9 to 1.3); up to 64 M of 40 MB at F = 32 (0.60 to 0.91) and
+// 48 M at F = 64 (0.73 to 0.94).  The group kernel's aligned loads are as fast or faster for other multiples of 4 (F = 36 to 60, 16 to
+// 100 M: 0.73 to 1.53).
 bool epp_rows_kernel_fits(const epp_path* p, int F) {
     if (const char* e = std::getenv("EPP_TUNE_ROWS")) {  // 0: never, 2: always (tests, measurements)
         if (*e == '0') return false;
@@ -376,9 +380,13 @@ bool epp_rows_kernel_fits(const epp_path* p, int F) {
     if (F > 16 && p->nnz * F <= 16000000) return true;
     if (epp_group_table_asked()) return false;
     double any_delay;
-    if (F <= 16) return p->nnz <= (F < 16 ? 48000000 : 12000000) && epp_tile_lanes(p, F, &any_delay) == 0;
-    const bool whole = F % 16 == 0;
-    return F <= 64 && p->nnz * F <= (whole ? 64000000 : 100000000) && p->n_src * F <= (whole ? 10000000 : 28000000);
+    if (F <= 16) {
+        const int64_t most = F <= 7 ? 30000000 : F == 8 ? 48000000 : F <= 10 ? 20000000 : F <= 13 || F == 16 ? 12000000 : 8000000;
+        return p->nnz <= most && epp_tile_lanes(p, F, &any_delay) == 0;
+    }
+    if (F > 64) return false;
+    if (F == 32 || F == 64) return p->nnz * F <= (F == 32 ? 64000000 : 48000000) && p->n_src * F <= 10000000;
+    return (F < 32 || F % 4 != 0) && p->nnz * F <= 100000000 && p->n_src * F <= 28000000;
 }
 
 int epp_build_rows_plan(epp_path* p, int F, hipStream_t s, RowsPlan** out) {

@@ -52,6 +52,28 @@ def test_rule_and_results(F, rows, monkeypatch):
     assert torch.equal(got[""][7], got["0"][7])
 
 
+@pytest.mark.parametrize("n,row,F,rows", [
+    (280_000, 30, 13, True), (280_000, 30, 14, False), (310_000, 40, 10, True), (310_000, 40, 13, False), (310_000, 40, 16, False),
+    (290_000, 40, 16, True), (510_000, 40, 7, True), (510_000, 40, 10, False), (760_000, 40, 8, True), (760_000, 40, 7, False),
+    (1_150_000, 3, 24, True), (1_200_000, 3, 24, False), (300_000, 6, 32, True), (320_000, 6, 32, False),
+    (100_000, 7, 64, True), (110_000, 7, 64, False), (20_000, 22, 36, True), (20_000, 24, 36, False), (20_000, 60, 37, True)])
+def test_limits(n, row, F, rows):
+    """Either side of every limit, of entries, of gathered floats and of source floats: `row` equally spaced columns in every row."""
+    r = torch.arange(n, device="cuda")[:, None]
+    col = ((r * 7_919 + torch.arange(row, device="cuda") * (n // row)) % n).sort(1).values.int().reshape(-1)
+    rowptr = torch.arange(0, n * row + 1, row, dtype=torch.int32, device="cuda")
+    gen = torch.Generator(device="cuda").manual_seed(F)
+    val = torch.randn(n * row, generator=gen, device="cuda")
+    p = epp.epp_prepare(n, rowptr, col, val, torch.arange(n, dtype=torch.int32, device="cuda"), 1).path(0)
+    p.prepare_width(F)
+    assert (p.info().n_split_rows == 0) == rows
+    X, Y = torch.randn(n, F, generator=gen, device="cuda"), torch.empty(n, F, device="cuda")
+    epp.epp_backward_aggregate(p, X, Y)
+    want = torch.sparse_csr_tensor(rowptr, col, val.double(), (n, n)) @ X.double()
+    most = torch.sparse_csr_tensor(rowptr, col, val.double().abs(), (n, n)) @ X.double().abs()
+    assert bool(((Y.double() - want).abs() <= (row + 2) * 2.0 ** -24 * most).all())
+
+
 @pytest.mark.parametrize("switch,value", [("GS", 24), ("PACK", 0), ("PACK", 2), ("HOT_MB", 1)])
 def test_switches_of_the_group_table_ask_for_it(switch, value, monkeypatch):
     rowptr, col, val = (torch.from_numpy(a).to(dev()) for a in _regular_graph())
