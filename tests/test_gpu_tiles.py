@@ -311,3 +311,28 @@ def test_sums_of_rows_with_neighbouring_sources(lanes, monkeypatch):
     assert (np.abs(got - want) <= 528 * 2.0 ** -24 * want).all()
     # and the errors of a chain hardly ever add up: 2-norms, 2^-24 times sqrt(500 / 3) on average
     assert np.linalg.norm(got - want) <= 4 * np.sqrt(500 / 3) * 2.0 ** -24 * np.linalg.norm(want)
+
+
+@pytest.mark.parametrize("n,tiles", [(1 << 23, True), (1 + (1 << 23), False)])
+def test_ids_of_more_than_23_bits_stay_on_the_group_table(n, tiles, monkeypatch):
+    """60,000 rows among the first and last ids, columns anywhere, the last id among them."""
+    _force(monkeypatch, 8)
+    F, gen = 20, torch.Generator(device="cuda").manual_seed(641)
+    rows = torch.cat((torch.arange(30_000, device="cuda"), torch.arange(n - 30_000, n, device="cuda")))
+    col = torch.randint(n, (60_000, 9), generator=gen, device="cuda")
+    col[:, 8] = n - 1
+    row, col = (x.reshape(-1) for x in torch.broadcast_tensors(rows[:, None], col))
+    keys = torch.unique(row * n + col)
+    row, col = keys // n, (keys % n).int()
+    rowptr = torch.zeros(n + 1, dtype=torch.int32, device="cuda")
+    rowptr[1:] = torch.cumsum(torch.bincount(row, minlength=n), 0)
+    val = torch.rand(col.shape, generator=gen, device="cuda")
+    path = epp.epp_prepare(n, rowptr, col, val, torch.arange(n, dtype=torch.int32, device="cuda"), 1).path(0)
+    X, Y = torch.rand(n, F, generator=gen, device="cuda"), torch.full((n, F), 7.0, device="cuda")
+    path.prepare_width(F)
+    assert (path.info().n_split_rows == 0) == tiles
+    epp.epp_backward_aggregate(path, X, Y)
+    want = torch.zeros(n, F, dtype=torch.float64, device="cuda").index_add_(0, row, val.double()[:, None] * X[col.long()].double())
+    assert bool((Y[30_000:n - 30_000] == 7.0).all())
+    # nine positive terms: eleven additions at most, each rounds by 2^-24 of what is there by then
+    assert bool(((Y.double() - want).abs() <= 11 * 2.0 ** -24 * want)[rows].all())
