@@ -1065,10 +1065,14 @@ static double tile_launch_us(const epp_path* p, const Sources& src, int F, int l
 // Some of them (us, group kernel / tiles of 4, 8 and 16 lanes): 274 M entries, 2.4 M sources, F = 64: 8866 / 12056 / 5550 /
 // 7246; F = 16: 4940 / 2425 / 2587; 228 M, 8.4 M, R-MAT, F = 128: 12290 / - / 8960 / 8560; not taken: 19 M of 2.4 M, F = 128:
 // 1547 / - / 1446 / 1442; 65 M of 8.4 M, F = 41: 2726 / 4699 / 4376 / 3603.
-// The tiles cost 9 to 11 us per million entries to prepare, which five launches have to repay.  Rows of up to 32 floats have to save
-// kNarrowSaves a launch besides: beyond that width the group kernel prepares a partitioned copy, which costs as much as tiles, but here a
-// group table of 20 us, and a run that ends soon pays for the difference (import and one epoch, F = 5 / 32, 31 M entries: 422 us without
-// tiles, 891 with them; F = 32, 79 M: 1493, 2007; F = 16 / 41, 114 M: 1.1 ms more once, 0.37 ms less per epoch).  Fewer sources than
+// Of 540 other paths and widths (ids in random order, 4 to 240 M entries, F = 5 to 160) 162 are taken, in 0.70 of the time on average,
+// 1.11 at worst (R-MAT, 165,000 sources, F = 88).
+// The tiles cost 9 to 11 us per million entries to prepare, which five launches have to repay.  Rows of up to 32 floats have to be
+// estimated to save kNarrowSaves a launch besides: beyond that width the group kernel prepares a partitioned copy of skewed graphs, which
+// costs as much as tiles, but here a group table of 20 us, and a run that ends soon pays for the difference (import and one epoch, F =
+// 5 / 32, 31 M entries: 422 us without tiles, 891 with them; F = 32, 79 M: 1493, 2007; F = 16 / 41, 114 M: 1.1 ms more once, 0.37 ms less
+// per epoch).  Preparation and one launch of the 162 run at 0.34 to 0.84 of the speed without tiles up to 32 floats, 0.71 to 2.0 up to
+// 64, 1.04 to 2.4 beyond; narrow ones are repaid by 1.3 to 5.3 launches.  Fewer sources than
 // 100,000 nearly fit the L2s together: the estimate of what hits them is not good enough there (65,000, 23 M entries, F = 96:
 // 527 / - / 732 / 633, estimated 758 / - / 602 / 617), but for rows of 64 bytes and less, which four lanes gather faster from L2
 // too (51,000, 30 M entries, F = 16: 269 / 181, estimated 230 / 202; 84,000, 118 M: 1085 / 691).
