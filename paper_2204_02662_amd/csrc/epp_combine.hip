@@ -7,6 +7,7 @@
 //
 // Widths of up to 128 (every weight matrix of an ordinary model) have kernels of their own, further down:
 // the whole product of a pair of rows fits a wavefront's registers, so nothing but W goes through LDS.
+// Two widths of 65 to 128 and many rows are left to epp_combine_split.hip.
 //
 // For wider ones both kernels give a workgroup of four wavefronts, arranged WM x WN, an output tile of
 // 32 WM BM x 32 WN BN, every wavefront BM x BN accumulator blocks of 32 x 32, and step through
@@ -241,11 +242,8 @@ __device__ __forceinline__ int share_index(int block, int p) { return VEC ? BLOC
 // and in a fixed order, once at the end; sums of workgroups are added in double.  That is two additions behind a chain
 // that is a quarter as long as a workgroup's: against 64 bits the error over 7 to 4.6 M rows and widths of 3 to 128 is
 // half that of one chain per workgroup on average, and nowhere larger.
-// Bound by the matrix core at 128 x 128 (16 instructions of 64 cycles per pair of loads, busy 83 % of the cycles;
-// 113 TFLOP/s at 4.6 M rows), where the 256 accumulators and eight pairs ahead also cost 17 to 21 spilled registers a
-// lane; by HBM where a width is 16 (4.9 TB/s).
-// Measured against tiles staged through LDS, partial sums included: 128 x 128, 4.6 M rows 1.51 -> 1.31 ms;
-// 128 x 16, 3.9 M rows 0.53 -> 0.46 ms; 16 x 41, 250,000 rows 55 -> 29 us; 16 x 3, 400 rows 14.1 -> 6.4 us;
+// Bound by HBM where a width is 16 (4.9 TB/s), by the launch with the few rows that 128 x 128 has here.
+// Measured against tiles staged through LDS, partial sums included: 128 x 16, 3.9 M rows 0.53 -> 0.46 ms; 16 x 41, 250,000 rows 55 -> 29 us; 16 x 3, 400 rows 14.1 -> 6.4 us;
 // 96 x 96, 869 / 30,000 / 100,000 rows 26 -> 14.6 / 33 -> 29 / 53 -> 59 us.
 template <int MT, int NT, bool VA, bool VB>
 __global__ __launch_bounds__(kBlock, MT * NT >= 16 ? 1 : 2) void k_weight_gradient_rows(
@@ -387,10 +385,9 @@ __global__ __launch_bounds__(kBlock, MT * NT >= 16 ? 1 : 2) void k_weight_gradie
 // are persistent, each wavefront takes 32 rows at a time and loads them straight into registers, lane l
 // its own row l % 32, four floats at a time (lanes l and l + 32 alternate: the contraction's order is free as
 // long as both operands follow it), the next 32 rows while the matrix core works on these.  One
-// 16-byte LDS read feeds four instructions, and no barrier is left in the loop.  Bound by the matrix
-// core at 128 x 128 (busy 78 % of the cycles), by HBM where a width is 16 (4.9 TB/s).
-// Measured against tiles of both operands staged through LDS: 128 x 128, 4.6 M rows 1.61 -> 1.35 ms;
-// 128 x 16, 3.9 M rows 0.55 -> 0.46 ms; 16 x 41, 250,000 rows 27 -> 21 us; 16 x 3, 382 rows 5.4 -> 3.0 us;
+// 16-byte LDS read feeds four instructions, and no barrier is left in the loop.  Bound by HBM where a width is 16
+// (4.9 TB/s).
+// Measured against tiles of both operands staged through LDS: 128 x 16, 3.9 M rows 0.55 -> 0.46 ms; 16 x 41, 250,000 rows 27 -> 21 us; 16 x 3, 382 rows 5.4 -> 3.0 us;
 // 96 x 96, 869 / 30,000 / 100,000 rows 11.9 -> 11.8 / 14.0 -> 14.0 / 38 -> 38 us (18.0 / 20.1 / 51 with W brought into
 // LDS a float and a row at a time, and 16 chunks for 12).
 template <int KC, int NT>  // KC: chunks of 8 floats of a row
@@ -690,7 +687,9 @@ int weight_gradient(const epp_paths* paths, int k, const float* Y, int F_in, con
     EPP_TRY(row_set(paths, k, &ids, &n_rows));
     const Chunks c = chunking(n_rows, F_in, F_out, max_chunks);
     const int64_t per = c.per, chunks = c.count;
-    if (chunks > 0 && narrow(F_in, F_out)) {
+    if (epp_split_weight_gradient(F_in, F_out, n_rows)) {
+        epp_launch_weight_gradient_split(chunks, 4 * per, ids, n_rows, Y, F_in, grad_X, F_out, part, s);
+    } else if (chunks > 0 && narrow(F_in, F_out)) {
         float* out = chunks == 1 ? grad_W : part;
         const int mt = blocks_of(F_in);
         if (mt == 1) launch_rows_wg_n<1, false>(c, ids, n_rows, Y, F_in, grad_X, F_out, out, s);
@@ -812,6 +811,11 @@ extern "C" int epp_input_gradient(epp_paths_t* paths, int k, const float* grad_X
     int64_t n_rows = 0;
     EPP_TRY(row_set(paths, k, &ids, &n_rows));
     if (n_rows == 0) return EPP_OK;
+    if (epp_split_input_gradient(F_in, F_out, n_rows)) {
+        epp_launch_input_gradient_split(ids, n_rows, grad_X, F_out, W, F_in, grad_Y, s);
+        EPP_HIP_TRY(hipGetLastError());
+        return EPP_OK;
+    }
     const int kc = (F_out + 7) / 8, nt = blocks_of(F_in);
     // (many rows of more than 48 floats onto one block of columns are left to the operand tiles: 16 x 64, 100,000 /
     // 400,000 / 2 M rows 10.0 / 28 / 123 us against 11.9 / 32 / 169, 32 x 128, 60,000 rows 11.1 against 13.0; not so 16 x 41,

@@ -1,0 +1,423 @@
+// The products of the combination stage (epp_combine.hip) for two widths of 65 to 128 and many rows, where
+// v_mfma_f32_32x32x2_f32 and not memory is the bound: on v_mfma_f32_32x32x16_bf16, which takes sixteen times the products
+// a cycle, with every float split into three bfloat16 parts.
+//
+// x = h + m + l with h = bf16(x), m = bf16(x - h), l = x - h - m: both differences are exact, and so is l as a bfloat16 (24 bits
+// less the 8 + 1 of each part before).  Of the nine products of two split floats six are formed; ml, lm and ll are below
+// 2^-26 of hh.  Sums are in 32 bits, in two chains: hh, and the five small ones, added at the end.  (In one chain the matrix
+// core drops the small products' low bits against a sum that has all of its own, always downwards: a bias of 2e-7 of a sum of 4,480
+// terms, which does not average out over thousands of such sums as errors do.)  Relative error of sums of 16 / 128 / 512 / 4,480
+// products of normal numbers against 64 bits: fp32 instruction 7.3 / 20 / 41 / 120 e-8, one chain 3.3 / 16 / 34 / 104, two 3.2 /
+// 6.5 / 13 / 42.
+//
+// What the parts cannot hold is formed again with the fp32 instruction, 32 rows of Y' or a wavefront's part of W' at a time.  The
+// operands' largest magnitudes tell, per row (column) that goes into a sum:
+//   * infinities (inf - inf is no part of one) and what may overflow: from 2^120 on, or where two multiply to 2^100;
+//   * parts or products below 2^-126, which the bf16 instruction takes as zero: where the largest of a row is below 2^-90, or two
+//     such multiply to less than 2^-100.  Above, what is lost is at most 2^-36 of the largest element, 2^-12 of its rounding.
+// (NaN become NaN, in the same rows and columns.)
+//
+// 4.6 M rows, W' with its reduction / Y': 128 x 128 1487 / 1449 -> 1356 / 1062 us, 96 x 96 1457 / 1075 -> 1058 / 740, 65 x 67 1450 / 1118 ->
+// 972 / 883.  What bounds them is the card's power: the matrix core is busy 44 % of the cycles of W' at 128 x 128, at 1.5 GHz (fp32
+// instruction 82 % at 1.9); without four of the six products it takes 964 us, with all of them on rows that are in cache 1057.
+
+// Operand layout of the 32x32x16 instruction: lane l supplies A[l % 32][8 (l / 32) ..] and B[8 (l / 32) ..][l % 32], eight
+// elements; its accumulator is that of 32x32x2.
+
+#include <algorithm>
+
+#include "epp_internal.h"
+
+namespace {
+
+typedef float floatx16 __attribute__((ext_vector_type(16)));
+typedef float float4v __attribute__((ext_vector_type(4)));
+typedef float float4u __attribute__((ext_vector_type(4), aligned(4)));  // global accesses need no more
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef unsigned uintx4 __attribute__((ext_vector_type(4)));
+
+constexpr float kLeast = 0x1p-90f, kLeastProduct = 0x1p-100f, kMost = 0x1p120f, kMostProduct = 0x1p100f;
+
+// Three parts of eight floats, two to a word.
+struct Parts { uintx4 h, m, l; };
+__device__ __forceinline__ bf16x8 operand(uintx4 x) { return __builtin_bit_cast(bf16x8, x); }
+__device__ __forceinline__ unsigned two_bf16(float x, float y) { return __builtin_bit_cast(unsigned, bf16x2{(__bf16)x, (__bf16)y}); }
+// x - one of two bfloat16, in one instruction (the product with the other is a zero, or NaN beside one that is not finite).  The factors
+// come from a register: as constants in the instruction they were taken for others.
+__device__ __forceinline__ float less(float x, unsigned w, unsigned factors) {
+    return __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, w), __builtin_bit_cast(bf16x2, factors), x, false);
+}
+template <class X>  // x(i): the i-th of eight floats; `most` becomes the largest magnitude so far (NaN are passed over)
+__device__ __forceinline__ Parts split(X x, float& most) {
+    Parts r;
+    unsigned low = 0x0000BF80u, high = 0xBF800000u;  // -1 for one of two
+    asm("" : "+s"(low), "+s"(high));
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const float a = x(2 * i), b = x(2 * i + 1);
+        asm("v_max3_f32 %0, |%1|, |%2|, %0" : "+v"(most) : "v"(a), "v"(b));
+        r.h[i] = two_bf16(a, b);
+        const float a1 = less(a, r.h[i], low), b1 = less(b, r.h[i], high);
+        r.m[i] = two_bf16(a1, b1);
+        r.l[i] = two_bf16(less(a1, r.m[i], low), less(b1, r.m[i], high));
+    }
+    return r;
+}
+__device__ __forceinline__ float least_of_wave(float x) {
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) x = fminf(x, __shfl_xor(x, d, 64));
+    return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(x)));
+}
+__device__ __forceinline__ float most_of_wave(float x) {
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) x = fmaxf(x, __shfl_xor(x, d, 64));
+    return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(x)));
+}
+// (zeros lose nothing)
+__device__ __forceinline__ float or_one(float x) { return x > 0.0f ? x : 1.0f; }
+// Whether the parts hold everything, from the least of the rows' (columns') largest magnitudes that are not zero, and the largest of
+// them, of both operands.
+__device__ __forceinline__ bool in_range(float least_a, float most_a, float least_b, float most_b) {
+    return least_a >= kLeast && least_b >= kLeast && least_a * least_b >= kLeastProduct && most_a < kMost && most_b < kMost &&
+           most_a * most_b < kMostProduct;
+}
+
+// The six products of N blocks: b's with a.
+template <int N>
+__device__ __forceinline__ void add_products(floatx16* sum, floatx16* small, const Parts (&a)[N], const Parts& b) {
+#define EPP_MFMA(to, x, y)  \
+    _Pragma("unroll") for (int j = 0; j < N; ++j) to[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(operand(a[j].x), operand(b.y), to[j], 0, 0, 0)
+    EPP_MFMA(small, l, h);
+    EPP_MFMA(sum, h, h);
+    EPP_MFMA(small, h, l);
+    EPP_MFMA(small, m, m);
+    EPP_MFMA(small, m, h);
+    EPP_MFMA(small, h, m);
+#undef EPP_MFMA
+}
+
+// partial[workgroup] = sum over the workgroup's rows of Y[id, :]^T X'[id, :].
+//
+// 16 rows at a time: a thread loads one feature of eight of them (256 consecutive bytes of a row per instruction, D steps ahead), splits
+// them, which is what the instruction wants of a lane, and leaves its parts in LDS; then every wavefront adds a quarter of
+// the product, 64 x 64.  A row is read and split once.  Sums of kSplitPiece rows at a time are formed, checked and added to the
+// workgroup's: the error of the chain then stays below that of the fp32 instruction also where all products have one sign.
+constexpr int kSplitPiece = 2304;
+__global__ __launch_bounds__(256, 2) void k_weight_gradient_split(const int32_t* __restrict__ ids, int n_rows, int rows_per_group,
+                                                                  const float* __restrict__ Y, int Fi, const float* __restrict__ G,
+                                                                  int Fo, float* __restrict__ out) {
+    constexpr int D = 3;  // steps of 16 rows in flight
+    __shared__ uintx4 parts[2][3][2][256];  // [step][part][half][feature of Y, then of X' from 128 on]
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), p = lane & 31, half = lane >> 5;
+    const int64_t group_first = (int64_t)blockIdx.x * rows_per_group;
+    if (group_first >= n_rows) return;
+    const int group_last = (int)std::min<int64_t>(group_first + rows_per_group, n_rows);
+    // what the thread loads: eight rows of every step, one feature of Y and one of X' (past the width the last one: its products
+    // are never written)
+    const int rows = 8 * (wave >> 1), feature = 64 * (wave & 1) + lane;
+    const int fa = std::min(feature, Fi - 1), fb = std::min(feature, Fo - 1);
+    // what it multiplies
+    const int m0 = 64 * (wave & 1), n0 = 64 * (wave >> 1);
+    float* __restrict__ mine = out + (int64_t)blockIdx.x * Fi * Fo;
+    // (without `ids` the load is of something else and not used: a branch around it would make a step wait for all loads)
+    const int32_t* __restrict__ id_src = ids ? ids : reinterpret_cast<const int32_t*>(Y);
+    for (int first = (int)group_first; first < group_last; first += kSplitPiece) {
+        const int last = std::min(first + kSplitPiece, group_last);
+        // Lane i (of eight) holds the vertex of the thread's i-th row of a step (rows past the end repeat the last one), from D steps before
+        // that row is loaded, so that the wait for it is not one for rows that were asked for later.
+        auto place = [&](int r) { return std::min(r + rows + (lane & 7), last - 1); };
+        float a[D][8], b[D][8];
+        auto fetch = [&](int d, int v) {
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                const int64_t id = __builtin_amdgcn_readlane(v, i);
+                a[d][i] = (Y + id * Fi)[fa];
+                b[d][i] = (G + id * Fo)[fb];
+            }
+        };
+        int vertex[D];
+        floatx16 sum[2][2] = {}, small[2][2] = {};  // [block of X'][block of Y]
+        float most_a = 0.0f, most_b = 0.0f;
+#pragma unroll
+        for (int d = 0; d < D; ++d) {
+            const int v = id_src[place(first + 16 * d)];
+            fetch(d, ids ? v : place(first + 16 * d));
+            vertex[d] = id_src[place(first + 16 * (d + D))];
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        int buffer = 0;
+        for (int r0 = first; r0 < last; r0 += 16 * D) {
+#pragma unroll
+            for (int d = 0; d < D; ++d) {
+                const int r = r0 + 16 * d;
+                if (r + 16 > last) {  // rows past the end count nothing
+#pragma unroll
+                    for (int i = 0; i < 8; ++i) {
+                        a[d][i] = r + rows + i < last ? a[d][i] : 0.0f;
+                        b[d][i] = r + rows + i < last ? b[d][i] : 0.0f;
+                    }
+                }
+                {
+                    const Parts x = split([&](int i) { return a[d][i]; }, most_a);
+                    parts[buffer][0][wave >> 1][feature] = x.h;
+                    parts[buffer][1][wave >> 1][feature] = x.m;
+                    parts[buffer][2][wave >> 1][feature] = x.l;
+                    const Parts z = split([&](int i) { return b[d][i]; }, most_b);
+                    parts[buffer][0][wave >> 1][128 + feature] = z.h;
+                    parts[buffer][1][wave >> 1][128 + feature] = z.m;
+                    parts[buffer][2][wave >> 1][128 + feature] = z.l;
+                }
+                __builtin_amdgcn_sched_barrier(0);
+                fetch(d, ids ? vertex[d] : place(r + 16 * D));
+                __builtin_amdgcn_sched_barrier(0);
+                vertex[d] = id_src[place(r + 16 * 2 * D)];
+                // (a wavefront writes to this buffer again only after the next step's barrier, behind which all have read it)
+                __syncthreads();
+                auto read = [&](int f) {
+                    return Parts{parts[buffer][0][half][f], parts[buffer][1][half][f], parts[buffer][2][half][f]};
+                };
+                const Parts x[2] = {read(m0 + p), read(m0 + 32 + p)};
+#pragma unroll
+                for (int j = 0; j < 2; ++j) add_products(sum[j], small[j], x, read(128 + n0 + 32 * j + p));
+                buffer ^= 1;
+            }
+        }
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+            for (int i = 0; i < 2; ++i) sum[j][i] += small[j][i];
+        __shared__ float most_of[2][256];  // [half][feature]
+        most_of[wave >> 1][feature] = most_a;
+        most_of[wave >> 1][128 + feature] = most_b;
+        __syncthreads();
+        const float ca = fmaxf(most_of[0][m0 + lane], most_of[1][m0 + lane]);
+        const float cb = fmaxf(most_of[0][128 + n0 + lane], most_of[1][128 + n0 + lane]);
+        __syncthreads();  // `most_of` is written again
+        if (!in_range(least_of_wave(or_one(ca)), most_of_wave(ca), least_of_wave(or_one(cb)), most_of_wave(cb))) {
+#pragma unroll
+            for (int i = 0; i < 2; ++i)
+#pragma unroll
+                for (int j = 0; j < 2; ++j) sum[j][i] = floatx16{};
+            for (int r = first; r < last; r += 2) {
+                const bool in = r + half < last;
+                const int at = in ? r + half : r;
+                const int64_t v = ids ? ids[at] : at;
+                float x[2], z[2];
+#pragma unroll
+                for (int u = 0; u < 2; ++u) {
+                    x[u] = in ? (Y + v * Fi)[std::min(m0 + 32 * u + p, Fi - 1)] : 0.0f;
+                    z[u] = in ? (G + v * Fo)[std::min(n0 + 32 * u + p, Fo - 1)] : 0.0f;
+                }
+#pragma unroll
+                for (int i = 0; i < 2; ++i)
+#pragma unroll
+                    for (int j = 0; j < 2; ++j) sum[j][i] = __builtin_amdgcn_mfma_f32_32x32x2f32(x[i], z[j], sum[j][i], 0, 0, 0);
+            }
+        }
+        int m1 = m0 + 4 * half;
+        asm volatile("" : "+v"(m1));  // (the places' offsets are not kept in registers through the loop)
+        auto element = [&](int i, int j, int e) {
+            return std::min(m1 + 32 * i + 8 * (e / 4) + e % 4, Fi - 1) * Fo + std::min(n0 + 32 * j + p, Fo - 1);
+        };
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+                if (first > (int)group_first) {
+                    float before[16];
+#pragma unroll
+                    for (int e = 0; e < 16; ++e) before[e] = mine[element(i, j, e)];
+#pragma unroll
+                    for (int e = 0; e < 16; ++e) sum[j][i][e] += before[e];
+                }
+#pragma unroll
+                for (int e = 0; e < 16; ++e)
+                    if (m1 + 32 * i + 8 * (e / 4) + e % 4 < Fi && n0 + 32 * j + p < Fo) mine[element(i, j, e)] = sum[j][i][e];
+            }
+    }
+}
+
+// Y'[id, n] = sum_k X'[id, k] W[n, k] for F_out of at most 16 KS (k), F_in of at most 32 NT (n).
+//
+// W's parts stay in LDS for the whole launch, in the order in which the matrix core takes them; a workgroup fills a CU and is
+// persistent.  A wavefront takes 32 rows at a time, of which a lane loads its own row l % 32, four floats at a time (lanes l
+// and l + 32 alternate), the next 32 rows' as soon as it has split these.  The rows are the columns of the instruction's
+// result, so that a lane has four consecutive floats of its row at a time; they go through LDS to be stored in whole lines.
+constexpr int kSplitThreads = 512, kSplitWaves = kSplitThreads / 64;
+// FULL: F_in is 32 NT.  (Stores under no condition: behind others the next rows' wait could not tell how many there are, and would be
+// for all of them.)
+template <int KS, int NT, bool FULL>
+__global__ __launch_bounds__(kSplitThreads, 2) void k_input_gradient_split(const int32_t* __restrict__ ids, int64_t n_rows,
+                                                                           const float* __restrict__ G, int Fo,
+                                                                           const float* __restrict__ W, int Fi,
+                                                                           float* __restrict__ Yg) {
+    constexpr int N = 32 * NT;
+    __shared__ uintx4 Ws[3][KS * 2 * N];  // [part][step][half][n]
+    __shared__ unsigned w_most[N];        // bits of the largest magnitude of W's row n (NaN are passed over)
+    __shared__ float4v out_all[kSplitWaves][32 * 8];  // 32 rows x 32 columns of results, private to a wavefront
+    const int lane = threadIdx.x & 63, p = lane & 31, half = lane >> 5;
+    // Element i (of four) of the quadruple that starts at k; the last ones of a row start at F_out - 4 and have what comes
+    // before k as zeros in W.
+    const int top = Fo - 4;
+    for (int n = threadIdx.x; n < N; n += kSplitThreads) w_most[n] = 0;
+    __syncthreads();
+    for (int i = threadIdx.x; i < KS * 2 * N; i += kSplitThreads) {
+        const int n = i / (KS * 2), s = i % (KS * 2) / 2, h = i % 2;
+        const float* __restrict__ row = W + (int64_t)std::min(n, Fi - 1) * Fo;
+        float x[8], most = 0.0f;
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            const int k = 16 * s + 8 * q + 4 * h, from = std::min(k, top);
+            const float4u w = *reinterpret_cast<const float4u*>(row + from);
+#pragma unroll
+            for (int c = 0; c < 4; ++c) x[4 * q + c] = n < Fi && k < Fo && from + c >= k ? w[c] : 0.0f;
+        }
+        const Parts w = split([&](int j) { return x[j]; }, most);
+        Ws[0][(s * 2 + h) * N + n] = w.h;
+        Ws[1][(s * 2 + h) * N + n] = w.m;
+        Ws[2][(s * 2 + h) * N + n] = w.l;
+        atomicMax(&w_most[n], __float_as_uint(most));
+    }
+    __syncthreads();
+    float least_w = 1.0f, most_w = 0.0f;
+#pragma unroll
+    for (int j = 0; j < NT; ++j) {
+        const float x = __uint_as_float(w_most[32 * j + p]);
+        least_w = fminf(least_w, or_one(x));
+        most_w = fmaxf(most_w, x);
+    }
+    least_w = least_of_wave(least_w);
+    most_w = most_of_wave(most_w);
+
+    const int64_t n_tiles = (n_rows + 31) / 32, step = (int64_t)gridDim.x * kSplitWaves;
+    auto vertex = [&](int64_t tile) -> int {
+        const int64_t r = std::min<int64_t>(tile * 32 + p, n_rows - 1);
+        return ids ? ids[r] : (int)r;
+    };
+    auto quad = [&](const float* __restrict__ row, int c) {  // (F_out is above 16 (KS - 2))
+        const int k = 8 * c + 4 * half;
+        return *reinterpret_cast<const float4u*>(row + (8 * c + 8 <= 16 * (KS - 2) ? k : std::min(k, top)));
+    };
+    int64_t tile = (int64_t)blockIdx.x * kSplitWaves + (threadIdx.x >> 6);
+    if (tile >= n_tiles) return;
+    float4v x[2 * KS];
+    int v = vertex(tile), next = vertex(std::min(tile + step, n_tiles - 1));
+    {
+        const float* __restrict__ row = G + (int64_t)v * Fo;
+#pragma unroll
+        for (int c = 0; c < 2 * KS; ++c) {
+            x[c] = quad(row, c);
+            __builtin_amdgcn_sched_barrier(0);  // (in the order of the loop's loads, whose waits then count the same ones)
+        }
+    }
+    for (; tile < n_tiles; tile += step) {
+        const float* __restrict__ next_row = G + (int64_t)next * Fo;
+        const int after = vertex(std::min(tile + 2 * step, n_tiles - 1));
+        floatx16 sum[NT] = {}, small[NT] = {};
+        float most = 0.0f;
+#pragma unroll
+        for (int s = 0; s < KS; ++s) {
+            const Parts b = split([&](int i) { return x[2 * s + i / 4][i % 4]; }, most);
+            // (behind the last tile these are read once more and not used)
+            x[2 * s] = quad(next_row, 2 * s);
+            x[2 * s + 1] = quad(next_row, 2 * s + 1);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int j = 0; j < NT; ++j) {
+                const int at = (s * 2 + half) * N + 32 * j + p;
+                const Parts w[1] = {{Ws[0][at], Ws[1][at], Ws[2][at]}};
+                add_products(sum + j, small + j, w, b);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+#pragma unroll
+        for (int j = 0; j < NT; ++j) sum[j] += small[j];
+        most = fmaxf(most, __shfl_xor(most, 32, 64));
+        if (__ballot(!in_range(or_one(most), most, least_w, most_w))) {
+#pragma unroll
+            for (int j = 0; j < NT; ++j) sum[j] = floatx16{};
+            const float* __restrict__ row = G + (int64_t)v * Fo;
+            for (int k = half; k < Fo + half; k += 2) {
+                const float g = k < Fo ? row[k] : 0.0f;
+#pragma unroll
+                for (int j = 0; j < NT; ++j) {
+                    const int n = 32 * j + p;
+                    const float w = k < Fo && n < Fi ? W[(int64_t)n * Fo + k] : 0.0f;
+                    sum[j] = __builtin_amdgcn_mfma_f32_32x32x2f32(w, g, sum[j], 0, 0, 0);
+                }
+            }
+        }
+        int t = threadIdx.x;
+        asm volatile("" : "+v"(t));  // (what follows from it is not kept in registers through the products)
+        float4v* __restrict__ ov = out_all[t >> 6];
+        const int l = t & 63, own = l & 31, upper = l >> 5;
+        int vr[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) vr[q] = __shfl(v, 8 * q + (l >> 3), 64);
+#pragma unroll
+        for (int j = 0; j < NT; ++j) {
+            __builtin_amdgcn_wave_barrier();
+            // (quadruple c of row r lies at place c ^ r % 8, so that the rows' accesses spread over the banks)
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                ov[own * 8 + ((2 * q + upper) ^ (own & 7))] = float4v{sum[j][4 * q], sum[j][4 * q + 1], sum[j][4 * q + 2], sum[j][4 * q + 3]};
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            const int n = 32 * j + 4 * (l & 7);
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int r = 8 * q + (l >> 3);
+                const float4v y = ov[r * 8 + ((l & 7) ^ (r & 7))];
+                // (rows past the end are the last one once more, and so are their results)
+                float* __restrict__ o = Yg + (int64_t)vr[q] * Fi + n;
+                if (FULL || n + 4 <= Fi) {
+                    *reinterpret_cast<float4u*>(o) = y;
+                } else {
+#pragma unroll
+                    for (int i = 0; i < 4; ++i)
+                        if (n + i < Fi) o[i] = y[i];
+                }
+            }
+        }
+        v = next;
+        next = after;
+    }
+}
+
+}  // namespace
+
+// One width of up to 64 leaves memory the bound (128 x 64: 12 instructions for 768 bytes), and fewer rows the launch: 10,000 / 17,000 /
+// 40,000 / 65,000 / 100,000 rows of 128 x 128, W' with its reduction 21.9 / 27 / 31.8 / 35.4 / 60 -> 21.8 / 22 / 27.3 / 32.0 / 47 us, Y'
+// (20,000 first) 16.7 / .. / 28.7 / 30.4 / 50 -> 18.4 / .. / 20.4 / 22.8 / 31; 65 x 67 20.1 / 27 / 31.4 / 34.7 / 61 -> 17.4 / 20 / 25.3 / 29.1
+// / 43 and 12.2 / .. / 19.6 / 21.8 / 37 -> 11.1 / .. / 12.3 / 13.8 / 21.
+static bool split_widths(int Fi, int Fo) { return Fi > 64 && Fo > 64 && Fi <= 128 && Fo <= 128; }
+bool epp_split_weight_gradient(int Fi, int Fo, int64_t n_rows) { return split_widths(Fi, Fo) && n_rows > 16384; }
+bool epp_split_input_gradient(int Fi, int Fo, int64_t n_rows) { return split_widths(Fi, Fo) && n_rows > 32768; }
+
+void epp_launch_weight_gradient_split(int64_t groups, int64_t rows_per_group, const int32_t* ids, int64_t n_rows, const float* Y,
+                                      int Fi, const float* G, int Fo, float* out, hipStream_t s) {
+    hipLaunchKernelGGL(k_weight_gradient_split, dim3((unsigned)groups), dim3(256), 0, s, ids, (int)n_rows, (int)rows_per_group, Y, Fi, G,
+                       Fo, out);
+}
+
+void epp_launch_input_gradient_split(const int32_t* ids, int64_t n_rows, const float* G, int Fo, const float* W, int Fi, float* Yg,
+                                     hipStream_t s) {
+    const int64_t tiles = (n_rows + 31) / 32;
+    const dim3 grid((unsigned)std::min<int64_t>((tiles + kSplitWaves - 1) / kSplitWaves, 256)), block(kSplitThreads);
+#define EPP_LAUNCH(KS, NT)                                                                                                      \
+    do {                                                                                                                        \
+        if (Fi == 32 * NT)                                                                                                      \
+            hipLaunchKernelGGL((k_input_gradient_split<KS, NT, true>), grid, block, 0, s, ids, n_rows, G, Fo, W, Fi, Yg);       \
+        else                                                                                                                    \
+            hipLaunchKernelGGL((k_input_gradient_split<KS, NT, false>), grid, block, 0, s, ids, n_rows, G, Fo, W, Fi, Yg);      \
+    } while (0)
+    if (Fo <= 96) {
+        if (Fi <= 96) EPP_LAUNCH(6, 3);
+        else EPP_LAUNCH(6, 4);
+    } else {
+        if (Fi <= 96) EPP_LAUNCH(8, 3);
+        else EPP_LAUNCH(8, 4);
+    }
+#undef EPP_LAUNCH
+}

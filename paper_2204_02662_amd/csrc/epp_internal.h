@@ -387,6 +387,15 @@ int epp_prepare_small(const epp_csr_t* g, const int32_t* train_ids, int64_t n_tr
 // no allocation).  Handles are created with the GPU current, so they resolve it up front.
 int epp_static_scratch(float** ptr);
 
+// combine_split.hip: whether these products are taken in bfloat16 parts; the launches (W': `groups` partial products of
+// rows_per_group rows each)
+bool epp_split_weight_gradient(int Fi, int Fo, int64_t n_rows);
+bool epp_split_input_gradient(int Fi, int Fo, int64_t n_rows);
+void epp_launch_weight_gradient_split(int64_t groups, int64_t rows_per_group, const int32_t* ids, int64_t n_rows, const float* Y,
+                                      int Fi, const float* G, int Fo, float* out, hipStream_t s);
+void epp_launch_input_gradient_split(const int32_t* ids, int64_t n_rows, const float* G, int Fo, const float* W, int Fi, float* Yg,
+                                     hipStream_t s);
+
 // aggregate.hip
 int epp_build_schedule(epp_path* p, int gs, hipStream_t s, Schedule** out);
 // inner_rows != NULL: the launch serves the inner path that shares p's entries (bitmap of its rows)
