@@ -25,7 +25,6 @@ constexpr int kMaxItems = 65536;           // vertices
 constexpr int kWords = kMaxItems / 64;     // = kThreads: one bitmap word per thread
 constexpr int kMaxEntries = 2 * kMaxItems;
 constexpr int kEntryWords = kMaxEntries / 64;  // = 2 * kThreads: two keep-mask words per thread
-constexpr int kHeldItems = 4096, kHeldEntries = 16384;  // whose row pointer and columns fit LDS beside the rest
 constexpr int kStatWords = EPP_NCLASS + 1; // histogram + longest row
 constexpr int kLevelWords = 3 + kStatWords; // kept entries, rows, "set did not change", statistics
 constexpr int kRowEnd = kEntRowEnd;
@@ -99,20 +98,18 @@ struct SmallArgs {
     long long* result;            // pinned host words: [0] error bits, [1] |N^0|, then kLevelWords per level
 };
 
-// HELD: the row pointer and the columns fit LDS too (n <= kHeldItems, nnz <= kHeldEntries) and are read once;
-// what the levels still wait for in memory is the weights of the kept entries.  Bound by the
-// instructions of one CU's sixteen wavefronts (16 cycles for each), hence the care for their number.  A
-// citation graph of 2,708 vertices and 13,200 entries, two levels: 31 -> 26 us.
+// HELD: for graphs of at most kHeldItems vertices and kHeldEntries entries.
 template <bool HELD>
-__global__ __launch_bounds__(kThreads) void k_prepare_small(SmallArgs a) {
+__global__ void k_prepare_small(SmallArgs a);
+
+template <>
+__global__ __launch_bounds__(kThreads) void k_prepare_small<false>(SmallArgs a) {
     __shared__ unsigned long long bm_cur[kWords + 1], bm_next[kWords], keep[kEntryWords];
     __shared__ unsigned int ends[2 * kEntryWords];  // one bit per kept entry: the last of its row
     __shared__ int wpre[kEntryWords], rpre[kWords];
     __shared__ int wave_sum[kWaves + 1];
     __shared__ int hist[EPP_NCLASS];
     __shared__ int s_max, s_err, s_differs;
-    __shared__ int32_t held_ptr[HELD ? kHeldItems + 1 : 1], held_col[HELD ? kHeldEntries : 1];
-    __shared__ int32_t newptr[HELD ? kHeldItems + 1 : 1];  // filtered row pointer of every vertex
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int n_words = (a.n + 63) >> 6, n_seg = (a.nnz + 63) >> 6;
 
@@ -123,17 +120,8 @@ __global__ __launch_bounds__(kThreads) void k_prepare_small(SmallArgs a) {
     }
     __syncthreads();
     // N^0 = V_t (Property 1); the row pointer must rise from 0 to nnz
-    // (the column ids are range-checked here where they are held, else where the first level loads them)
+    // (the column ids are range-checked where the first level loads them)
     {
-        constexpr int kPtr = HELD ? kHeldItems / kThreads : 1, kCol = HELD ? kHeldEntries / kThreads : 1;
-        int pv[kPtr], cv[kCol];
-        if constexpr (HELD) {
-#pragma unroll
-            for (int i = 0; i < kPtr; ++i) pv[i] = tid + i * kThreads < a.n ? a.rowptr[tid + i * kThreads] : 0;
-#pragma unroll
-            for (int i = 0; i < kCol; ++i) cv[i] = tid + i * kThreads < a.nnz ? a.col[tid + i * kThreads] : 0;
-            if (tid == 0) held_ptr[a.n] = a.rowptr[a.n];
-        }
         for (int i0 = tid; i0 < a.n_train; i0 += kThreads * kBatch) {
             int v[kBatch];
 #pragma unroll
@@ -145,34 +133,14 @@ __global__ __launch_bounds__(kThreads) void k_prepare_small(SmallArgs a) {
                 else atomicOr(&bm_cur[v[i] >> 6], 1ull << (v[i] & 63));
             }
         }
-        if constexpr (HELD) {
-#pragma unroll
-            for (int i = 0; i < kPtr; ++i)
-                if (tid + i * kThreads < a.n) held_ptr[tid + i * kThreads] = pv[i];
-#pragma unroll
-            for (int i = 0; i < kCol; ++i) {
-                if (tid + i * kThreads >= a.nnz) continue;
-                if (cv[i] < 0 || cv[i] >= a.n) atomicOr(&s_err, 4);
-                held_col[tid + i * kThreads] = cv[i];
-            }
-            __syncthreads();
-        }
     }
-    auto row_begin = [&](int v) -> int {
-        if constexpr (HELD) return held_ptr[v];
-        else return a.rowptr[v];
-    };
-    auto column = [&](int e) -> int {
-        if constexpr (HELD) return held_col[e];
-        else return a.col[e];
-    };
     for (int v0 = tid; v0 < a.n; v0 += kThreads * kBatch) {
         int p0[kBatch], p1[kBatch];
 #pragma unroll
         for (int i = 0; i < kBatch; ++i) {
             const int v = v0 + i * kThreads;
-            p0[i] = v < a.n ? row_begin(v) : 0;
-            p1[i] = v < a.n ? row_begin(v + 1) : 0;
+            p0[i] = v < a.n ? a.rowptr[v] : 0;
+            p1[i] = v < a.n ? a.rowptr[v + 1] : 0;
         }
 #pragma unroll
         for (int i = 0; i < kBatch; ++i) {
@@ -221,8 +189,8 @@ __global__ __launch_bounds__(kThreads) void k_prepare_small(SmallArgs a) {
             int c[kMaskBatch];
             if ((w0 + kMaskBatch) * 64 <= a.nnz) {
 #pragma unroll
-                for (int i = 0; i < kMaskBatch; ++i) c[i] = column((w0 + i) * 64 + lane);
-                if (!HELD && k == 0) {
+                for (int i = 0; i < kMaskBatch; ++i) c[i] = a.col[(w0 + i) * 64 + lane];
+                if (k == 0) {
 #pragma unroll
                     for (int i = 0; i < kMaskBatch; ++i) top = max(top, (unsigned int)c[i]);
                 }
@@ -232,8 +200,8 @@ __global__ __launch_bounds__(kThreads) void k_prepare_small(SmallArgs a) {
                     const int e = (w0 + i) * 64 + lane;
                     c[i] = kMaxItems;
                     if (e < a.nnz) {
-                        c[i] = column(e);
-                        if (!HELD && k == 0) top = max(top, (unsigned int)c[i]);
+                        c[i] = a.col[e];
+                        if (k == 0) top = max(top, (unsigned int)c[i]);
                     }
                 }
             }
@@ -279,25 +247,18 @@ __global__ __launch_bounds__(kThreads) void k_prepare_small(SmallArgs a) {
                 longest = max(longest, len);
             }
         };
-        if constexpr (HELD) {
-            for (int v = tid; v <= a.n; v += kThreads) newptr[v] = kept_before(row_begin(v));
-            __syncthreads();
-            for (int v = tid; v - lane < a.n; v += kThreads)
-                count_row(v, v < a.n ? newptr[v] : 0, v < a.n ? newptr[v + 1] : 0);
-        } else {
-            for (int v0 = tid; v0 - lane < a.n; v0 += kThreads * kBatch) {
-                int p0[kBatch], p1[kBatch];
+        for (int v0 = tid; v0 - lane < a.n; v0 += kThreads * kBatch) {
+            int p0[kBatch], p1[kBatch];
 #pragma unroll
-                for (int i = 0; i < kBatch; ++i) {
-                    const int v = v0 + i * kThreads;
-                    p0[i] = v < a.n ? row_begin(v) : a.nnz;
-                    p1[i] = v < a.n ? row_begin(v + 1) : a.nnz;
-                }
+            for (int i = 0; i < kBatch; ++i) {
+                const int v = v0 + i * kThreads;
+                p0[i] = v < a.n ? a.rowptr[v] : a.nnz;
+                p1[i] = v < a.n ? a.rowptr[v + 1] : a.nnz;
+            }
 #pragma unroll
-                for (int i = 0; i < kBatch; ++i) {
-                    if (v0 - lane + i * kThreads >= a.n) break;  // (uniform)
-                    count_row(v0 + i * kThreads, kept_before(p0[i]), kept_before(p1[i]));
-                }
+            for (int i = 0; i < kBatch; ++i) {
+                if (v0 - lane + i * kThreads >= a.n) break;  // (uniform)
+                count_row(v0 + i * kThreads, kept_before(p0[i]), kept_before(p1[i]));
             }
         }
 #pragma unroll
@@ -313,7 +274,7 @@ __global__ __launch_bounds__(kThreads) void k_prepare_small(SmallArgs a) {
             for (int j = tid; j < kept; j += kThreads) {
                 const int w = last_not_above(wpre, n_seg, j), e = w * 64 + select_bit(keep[w], j - wpre[w]);
                 const int flag = (ends[j >> 5] >> (j & 31)) & 1u ? kRowEnd : 0;
-                cv[j] = make_int2(column(e) | flag, __float_as_int(a.val[e]));
+                cv[j] = make_int2(a.col[e] | flag, __float_as_int(a.val[e]));
             }
         } else {
             for (int w0 = wave; w0 < n_seg; w0 += kWaves * kBatch) {
@@ -323,7 +284,7 @@ __global__ __launch_bounds__(kThreads) void k_prepare_small(SmallArgs a) {
                 for (int i = 0; i < kBatch; ++i) {
                     const int w = w0 + i * kWaves;
                     m[i] = w < n_seg ? keep[w] : 0ull;
-                    if ((m[i] >> lane) & 1ull) x[i] = make_int2(column(w * 64 + lane), __float_as_int(a.val[w * 64 + lane]));
+                    if ((m[i] >> lane) & 1ull) x[i] = make_int2(a.col[w * 64 + lane], __float_as_int(a.val[w * 64 + lane]));
                 }
 #pragma unroll
                 for (int i = 0; i < kBatch; ++i) {
@@ -342,8 +303,7 @@ __global__ __launch_bounds__(kThreads) void k_prepare_small(SmallArgs a) {
         // rows of the path (in the same two ways)
         auto put_row = [&](int r, int v) {
             row_ids[r] = v;
-            if constexpr (HELD) orp[r] = newptr[v];
-            else orp[r] = kept_before(row_begin(v));
+            orp[r] = kept_before(a.rowptr[v]);
         };
         if (by_item(R, n_words)) {
             for (int r = tid; r < R; r += kThreads) {
@@ -368,6 +328,229 @@ __global__ __launch_bounds__(kThreads) void k_prepare_small(SmallArgs a) {
         if (tid < n_words) a.bitmaps[(size_t)(k + 1) * a.bm_stride + tid] = bm_next[tid];
         __syncthreads();
         bm_cur[tid] = bm_next[tid];
+    }
+}
+
+// The same for graphs whose columns, weights and row pointer fit the registers: thread t of wavefront w holds entry t % 64 of the words
+// w, w + 16, .. of the entries, and the vertices t, t + 1024, .., which is where the keep-mask, the compaction and the rows want
+// them.  Every wavefront adds up the words' counts for itself, and what a level writes has two buffers, so that a level takes two
+// barriers.  Bound by the latency of what one level's LDS accesses and barriers wait for.
+//
+// A citation graph of 2,708 vertices and 13,200 entries, two levels: 26.4 us with columns and row pointer in LDS, twelve barriers a level
+// and the weights read per level, 14.5 us like this (prepared and one epoch 59.5 -> 47.7).  With twice the registers, for 8,192 vertices
+// and 32,768 entries, they no longer fit and it is the slower one (4,000 vertices, 28,000 entries 106 -> 110 us).
+constexpr int kHeldItems = 4096, kHeldEntries = 16384;
+constexpr int kHistCopies = 16;  // (64 lanes on a few counters would wait for each other)
+
+// Sum over the lanes up to this one; largest of all lanes, in lane 63 (data moves between lanes without LDS).
+template <class F>
+__device__ __forceinline__ int over_lanes(int x, F f) {
+    x = f(x, __builtin_amdgcn_update_dpp(0, x, 0x111, 0xF, 0xF, false));  // row_shr:1
+    x = f(x, __builtin_amdgcn_update_dpp(0, x, 0x112, 0xF, 0xF, false));  // row_shr:2
+    x = f(x, __builtin_amdgcn_update_dpp(0, x, 0x114, 0xF, 0xF, false));  // row_shr:4
+    x = f(x, __builtin_amdgcn_update_dpp(0, x, 0x118, 0xF, 0xF, false));  // row_shr:8
+    x = f(x, __builtin_amdgcn_update_dpp(0, x, 0x142, 0xA, 0xF, false));  // row_bcast:15
+    x = f(x, __builtin_amdgcn_update_dpp(0, x, 0x143, 0xC, 0xF, false));  // row_bcast:31
+    return x;
+}
+__device__ __forceinline__ int sum_up_to_lane(int x) { return over_lanes(x, [](int a, int b) { return a + b; }); }
+__device__ __forceinline__ int largest_of_lanes(int x) { return over_lanes(x, [](int a, int b) { return max(a, b); }); }  // (none is negative)
+
+// Bits before the words of N = 64 PER: lane l has those before the words PER l + wave % PER, of which a wavefront's words w, w + 16, ..
+// are some (word_at); all[word], if given, becomes those before every word.
+template <int PER>
+__device__ __forceinline__ int bits_before(const unsigned long long* words, int wave, int& mine, int* all) {
+    const int lane = threadIdx.x & 63;
+    int c[PER], sum = 0;
+#pragma unroll
+    for (int q = 0; q < PER; ++q) {
+        c[q] = sum;
+        sum += __popcll(words[PER * lane + q]);
+    }
+    const int incl = sum_up_to_lane(sum);
+#pragma unroll
+    for (int q = 0; q < PER; ++q) {
+        c[q] += incl - sum;
+        if (all) all[PER * lane + q] = c[q];
+        if (wave % PER == q) mine = c[q];
+    }
+    return __builtin_amdgcn_readlane(incl, 63);
+}
+template <int PER>
+__device__ __forceinline__ int word_at(int mine, int wave, int i) { return __builtin_amdgcn_readlane(mine, wave / PER + kWaves / PER * i); }
+// Set bits of m below this lane.
+__device__ __forceinline__ int bits_below(unsigned long long m) {
+    return __builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)m, 0));
+}
+
+template <>
+__global__ __launch_bounds__(kThreads) void k_prepare_small<true>(SmallArgs a) {
+    constexpr int COLS = kHeldEntries / kThreads, ROWS = kHeldItems / kThreads;  // words of entries and of vertices per wavefront
+    constexpr int kSegs = COLS * kWaves, kRowWords = ROWS * kWaves;
+    constexpr int kPerSeg = kSegs / 64, kPerRow = kRowWords / 64;
+    static_assert(kSegs % 64 == 0 && kRowWords % 64 == 0 && kWaves % kPerSeg == 0 && COLS <= 32, "");
+    __shared__ unsigned long long bm[2][kRowWords + 1];  // N^k and N^{k+1}, in turns; the last word stays empty
+    __shared__ unsigned long long keep[kSegs];
+    __shared__ unsigned int ends[2][2 * kSegs];  // one bit per kept entry: the last of its row
+    __shared__ int before[kSegs];                // kept entries before every word (each wavefront writes, and reads, all of them)
+    __shared__ int hist[2][kHistCopies][EPP_NCLASS + 1];
+    __shared__ int s_max[2], s_err;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int n_words = (a.n + 63) >> 6;
+
+    int c[COLS], p0[ROWS], p1[ROWS];
+    float val[COLS];
+#pragma unroll
+    for (int i = 0; i < COLS; ++i) c[i] = tid + i * kThreads < a.nnz ? a.col[tid + i * kThreads] : kRowWords * 64;
+#pragma unroll
+    for (int j = 0; j < ROWS; ++j) {
+        const int v = tid + j * kThreads;
+        p0[j] = v < a.n ? a.rowptr[v] : a.nnz;
+        p1[j] = v < a.n ? a.rowptr[v + 1] : a.nnz;
+    }
+    for (int i = tid; i < 2 * (kRowWords + 1); i += kThreads) (&bm[0][0])[i] = 0ull;
+    for (int i = tid; i < 2 * 2 * kSegs; i += kThreads) (&ends[0][0])[i] = 0u;
+    for (int i = tid; i < 2 * kHistCopies * (EPP_NCLASS + 1); i += kThreads) (&hist[0][0][0])[i] = 0;
+    if (tid < 2) s_max[tid] = 0;
+    if (tid == 0) s_err = 0;
+    __syncthreads();
+    // N^0 = V_t (Property 1); the row pointer must rise from 0 to nnz
+    for (int i0 = tid; i0 < a.n_train; i0 += kThreads * kBatch) {
+        int v[kBatch];
+#pragma unroll
+        for (int i = 0; i < kBatch; ++i) v[i] = i0 + i * kThreads < a.n_train ? a.train_ids[i0 + i * kThreads] : 0;
+#pragma unroll
+        for (int i = 0; i < kBatch; ++i) {
+            if (i0 + i * kThreads >= a.n_train) continue;
+            if (v[i] < 0 || v[i] >= a.n) atomicOr(&s_err, 2);
+            else atomicOr(&bm[0][v[i] >> 6], 1ull << (v[i] & 63));
+        }
+    }
+    int t = tid;
+    asm volatile("" : "+v"(t));  // (a register pair for each of the comparisons, kept from above, does not fit)
+#pragma unroll
+    for (int i = 0; i < COLS; ++i) val[i] = t + i * kThreads < a.nnz ? a.val[t + i * kThreads] : 0.0f;
+    int wrong = 0;
+    asm volatile("" : "+v"(t));
+#pragma unroll
+    for (int i = 0; i < COLS; ++i) wrong |= t + i * kThreads < a.nnz && (unsigned)c[i] >= (unsigned)a.n ? 4 : 0;
+#pragma unroll
+    for (int j = 0; j < ROWS; ++j) {
+        const int v = tid + j * kThreads;
+        if (v < a.n && (p0[j] < 0 || p1[j] < p0[j] || p1[j] > a.nnz || (v == 0 && p0[j] != 0) || (v == a.n - 1 && p1[j] != a.nnz)))
+            wrong |= 1;
+    }
+    if (wrong) atomicOr(&s_err, wrong);
+    __syncthreads();
+    if (s_err) {  // uniform: nothing is indexed with unchecked values
+        if (tid == 0) a.result[0] = s_err;
+        return;
+    }
+    {   // ascending ids of N^0
+        int base;
+        const int total = bits_before<kPerRow>(bm[0], wave, base, nullptr);
+#pragma unroll
+        for (int j = 0; j < ROWS; ++j) {
+            const unsigned long long m = bm[0][wave + j * kWaves];
+            const int at = word_at<kPerRow>(base, wave, j) + bits_below(m);
+            if ((m >> lane) & 1ull) a.set0_ids[at] = tid + j * kThreads;
+        }
+        if (tid < n_words) a.bitmaps[tid] = bm[0][tid];
+        if (tid == 0) {
+            a.result[0] = 0;
+            a.result[1] = total;
+        }
+    }
+
+    for (int k = 0; k < a.L; ++k) {
+        int2* __restrict__ cv = a.cv + (size_t)k * a.cv_stride;
+        int32_t* __restrict__ row_ids = a.row_ids + (size_t)k * a.ids_stride;
+        int32_t* __restrict__ orp = a.out_rowptr + (size_t)k * a.ptr_stride;
+        const int now = k & 1;
+        // (what follows from them is not kept in registers from level to level)
+#pragma unroll
+        for (int i = 0; i < COLS; ++i) asm volatile("" : "+v"(c[i]));
+#pragma unroll
+        for (int j = 0; j < ROWS; ++j) asm volatile("" : "+v"(p0[j]), "+v"(p1[j]));
+        // keep-mask of the entries: is the column in N^k?
+        const unsigned int* bm32 = reinterpret_cast<const unsigned int*>(bm[now]);  // (4-byte lookups: half the bank conflicts)
+        unsigned mine = 0u;  // bit i: the thread's i-th entry is kept
+#pragma unroll
+        for (int i = 0; i < COLS; ++i) {
+            const unsigned in = (bm32[c[i] >> 5] >> (c[i] & 31)) & 1u;
+            mine |= in << i;
+            const unsigned long long m = __ballot(in);
+            if (lane == 0) keep[wave + i * kWaves] = m;
+        }
+        __syncthreads();
+        int word_base;
+        const int kept = bits_before<kPerSeg>(keep, wave, word_base, before);
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        auto kept_before = [&](int p) -> int {
+            return p >= a.nnz ? kept : before[p >> 6] + __popcll(keep[p >> 6] & low_mask(p & 63));
+        };
+        // filtered list of every vertex; a vertex whose list is not empty is in N^{k+1}
+        int begin[ROWS], longest = 0;
+        unsigned member = 0u;  // bit j: the thread's j-th vertex is in N^{k+1}
+#pragma unroll
+        for (int j = 0; j < ROWS; ++j) {
+            begin[j] = kept_before(p0[j]);
+            const int end = kept_before(p1[j]), len = end - begin[j];
+            const unsigned long long m = __ballot(len > 0);
+            if (lane == 0) bm[now ^ 1][wave + j * kWaves] = m;
+            if (len > 0) {
+                member |= 1u << j;
+                atomicOr(&ends[now][(end - 1) >> 5], 1u << ((end - 1) & 31));
+                atomicAdd(&hist[now][lane & (kHistCopies - 1)][length_class(len)], 1);
+                longest = max(longest, len);
+            }
+        }
+        longest = largest_of_lanes(longest);
+        if (lane == 63 && longest > 0) atomicMax(&s_max[now], longest);
+        __syncthreads();
+        // stable compaction of (col, val): a kept entry's place is its word's count plus the kept ones before it in the word
+#pragma unroll
+        for (int i = 0; i < COLS; ++i) {
+            const bool in = (mine >> i) & 1u;
+            const int j = word_at<kPerSeg>(word_base, wave, i) + bits_below(__ballot(in));
+            if (in) cv[j] = make_int2(c[i] | ((ends[now][j >> 5] >> (j & 31)) & 1u ? kRowEnd : 0), __float_as_int(val[i]));
+        }
+        // rows of the path
+        int row_base;
+        const int R = bits_before<kPerRow>(bm[now ^ 1], wave, row_base, nullptr);
+#pragma unroll
+        for (int j = 0; j < ROWS; ++j) {
+            const bool in = (member >> j) & 1u;
+            const int r = word_at<kPerRow>(row_base, wave, j) + bits_below(__ballot(in));
+            if (in) {
+                row_ids[r] = tid + j * kThreads;
+                orp[r] = begin[j];
+            }
+        }
+        bool differs = false;
+#pragma unroll
+        for (int w = 0; w < kRowWords; w += 64) differs |= bm[0][w + lane] != bm[1][w + lane];
+        differs = __ballot(differs) != 0ull;
+        long long* res = a.result + 2 + (size_t)k * kLevelWords;
+        if (tid == 0) {
+            orp[R] = kept;
+            res[0] = kept;
+            res[1] = R;
+            res[2] = differs ? 0 : 1;
+            res[3 + EPP_NCLASS] = s_max[now];
+        }
+        if (tid < EPP_NCLASS) {
+            int sum = 0;
+#pragma unroll
+            for (int i = 0; i < kHistCopies; ++i) sum += hist[now][i][tid];
+            res[3 + tid] = sum;
+        }
+        if (tid < n_words) a.bitmaps[(size_t)(k + 1) * a.bm_stride + tid] = bm[now ^ 1][tid];
+        // for the next level (nobody reads these any more: all have been at the barrier behind this level's keep-mask)
+        for (int i = tid; i < 2 * kSegs; i += kThreads) ends[now ^ 1][i] = 0u;
+        for (int i = tid; i < kHistCopies * (EPP_NCLASS + 1); i += kThreads) (&hist[now ^ 1][0][0])[i] = 0;
+        if (tid == 0) s_max[now ^ 1] = 0;
     }
 }
 
