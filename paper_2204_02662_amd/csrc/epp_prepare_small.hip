@@ -96,11 +96,22 @@ struct SmallArgs {
     int32_t* row_ids;             // L x n
     int32_t* out_rowptr;          // L x (n + 1)
     long long* result;            // pinned host words: [0] error bits, [1] |N^0|, then kLevelWords per level
+    PinnedWords::Signal signal;   // .. that they, and everything else, are written
 };
 
 // HELD: for graphs of at most kHeldItems vertices and kHeldEntries entries.
 template <bool HELD>
 __global__ void k_prepare_small(SmallArgs a);
+
+// Everything that the workgroup has written is there, for the host and for kernels on any stream.
+__device__ __forceinline__ void all_written(const SmallArgs& a) {
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // (every wavefront's stores are in this XCD's L2)
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        __threadfence_system();
+        epp_raise(a.signal);
+    }
+}
 
 template <>
 __global__ __launch_bounds__(kThreads) void k_prepare_small<false>(SmallArgs a) {
@@ -152,6 +163,7 @@ __global__ __launch_bounds__(kThreads) void k_prepare_small<false>(SmallArgs a) 
     __syncthreads();
     if (s_err) {  // uniform: nothing is indexed with unchecked values
         if (tid == 0) a.result[0] = s_err;
+        all_written(a);
         return;
     }
     {   // ascending ids of N^0
@@ -219,6 +231,7 @@ __global__ __launch_bounds__(kThreads) void k_prepare_small<false>(SmallArgs a) 
         __syncthreads();
         if (k == 0 && s_err) {  // uniform
             if (tid == 0) a.result[0] = s_err;
+            all_written(a);
             return;
         }
         int kept;
@@ -329,6 +342,7 @@ __global__ __launch_bounds__(kThreads) void k_prepare_small<false>(SmallArgs a) 
         __syncthreads();
         bm_cur[tid] = bm_next[tid];
     }
+    all_written(a);
 }
 
 // The same for graphs whose columns, weights and row pointer fit the registers: thread t of wavefront w holds entry t % 64 of the words
@@ -444,6 +458,7 @@ __global__ __launch_bounds__(kThreads) void k_prepare_small<true>(SmallArgs a) {
     __syncthreads();
     if (s_err) {  // uniform: nothing is indexed with unchecked values
         if (tid == 0) a.result[0] = s_err;
+        all_written(a);
         return;
     }
     {   // ascending ids of N^0
@@ -552,6 +567,7 @@ __global__ __launch_bounds__(kThreads) void k_prepare_small<true>(SmallArgs a) {
         for (int i = tid; i < kHistCopies * (EPP_NCLASS + 1); i += kThreads) (&hist[now ^ 1][0][0])[i] = 0;
         if (tid == 0) s_max[now ^ 1] = 0;
     }
+    all_written(a);
 }
 
 }  // namespace
@@ -613,11 +629,12 @@ int epp_prepare_small(const epp_csr_t* g, const int32_t* train_ids, int64_t n_tr
     a.cv = cv_all.as<int2>();
     a.row_ids = ids_all.as<int32_t>();
     a.out_rowptr = ptr_all.as<int32_t>();
+    a.signal = pinned.signal();
     a.result = host;  // (the kernel writes a few dozen words there itself: a copy would be a launch of its own)
     if (n <= kHeldItems && nnz <= kHeldEntries) hipLaunchKernelGGL(k_prepare_small<true>, dim3(1), dim3(kThreads), 0, s, a);
     else hipLaunchKernelGGL(k_prepare_small<false>, dim3(1), dim3(kThreads), 0, s, a);
     EPP_HIP_TRY(hipGetLastError());
-    EPP_HIP_TRY(hipStreamSynchronize(s));
+    EPP_TRY(pinned.wait(s));
     if (host[0] != 0) {
         if (host[0] & 2) { epp_set_error("training id outside [0, %lld)", (long long)n); return EPP_ERR_OUT_OF_RANGE_ID; }
         if (host[0] & 4) { epp_set_error("a column id lies outside [0, %lld)", (long long)n); return EPP_ERR_OUT_OF_RANGE_ID; }

@@ -52,3 +52,35 @@ def test_mistakes_in_the_input(where, value):
     with pytest.raises(epp.EppError):
         gpu_prepare(g, train, 2)
     torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("busy", [0, 60])
+@pytest.mark.parametrize("n,nnz", [(3_000, 9_000), (9_000, 40_000), (60_000, 300_000)])
+def test_what_has_returned_is_there(n, nnz, busy):
+    """Paths made on one stream, behind other work or not, are used on another one as soon as the call is back (no wait in between)."""
+    g = _Random(n, nnz, 31)
+    train = np.arange(0, n, 5, dtype=np.int32)
+    sets_o, paths_o = oracle.prepare(g.n, g.rowptr, g.col, g.val, train, 2)
+    arrays = [torch.from_numpy(a).to(dev()) for a in (g.rowptr, g.col, g.val, train)]
+    X = torch.randn(n, 8, device=dev(), generator=torch.Generator(dev()).manual_seed(1))
+    work = torch.randn(4_096, 4_096, device=dev())
+    one, two = torch.cuda.Stream(), torch.cuda.Stream()
+    torch.cuda.synchronize()
+    for _ in range(5):
+        with torch.cuda.stream(one):
+            for _ in range(busy):
+                work = work @ work * 1e-3  # (about a millisecond each)
+            paths = epp.epp_prepare(n, *arrays, 2)
+            saved = [paths.path(l).export() for l in range(2)]
+            again = epp.epp_paths_import(n, arrays[3], saved)
+            for p in (paths, again):
+                p.path(0).prepare_width(8)
+        with torch.cuda.stream(two):
+            out = [torch.zeros_like(X) for _ in range(2)]
+            for p, o in zip((paths, again), out):
+                epp.epp_backward_aggregate(p.path(0), X, o)
+        torch.cuda.synchronize()
+        want = oracle.path_aggregate(n, paths_o[0], np.where(sets_o[1][:, None] != 0, X.cpu().numpy(), 0))
+        for o in out:
+            # (sums of at most 300 products of normal numbers in any order)
+            assert np.all(np.abs(o.cpu().numpy() - want) <= 1e-4 + 1e-5 * np.abs(want))
