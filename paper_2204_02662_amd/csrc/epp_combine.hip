@@ -526,14 +526,14 @@ __global__ __launch_bounds__(kBlock, 2) void k_input_gradient_rows(const int32_t
     }
 }
 
-// W'[e] = sum over chunks: LANES threads per element take every LANES-th chunk each, accumulate in
-// double, and are added in lane order (the result does not depend on timing).  64 of them where the
-// product is small: a few hundred elements would leave the chip idle with long chains of loads
-// (16 x 41, 978 chunks: 19.5 us with 16).
-template <int LANES>
-__global__ __launch_bounds__(kBlock) void k_weight_gradient_reduce(const float* __restrict__ partial, int n_chunks,
-                                                                   int64_t total, float* __restrict__ Wg) {
-    constexpr int E = kBlock / LANES;  // elements per workgroup
+// W'[e] = sum over chunks: LANES threads per element take every LANES-th chunk each, accumulate in double, and are added in a
+// fixed order (the result does not depend on timing).  What bounds it is the chain of loads that a thread waits for, eight at a
+// time, and then what a workgroup of E elements leaves of a line: a thousand partial sums want many lanes, large products wide
+// elements, small ones more workgroups.
+template <int E, int THREADS>
+__global__ __launch_bounds__(THREADS) void k_weight_gradient_reduce(const float* __restrict__ partial, int n_chunks,
+                                                                    int64_t total, float* __restrict__ Wg) {
+    constexpr int LANES = THREADS / E;
     __shared__ double part[LANES][E + 1];
     const int el = threadIdx.x % E, cl = threadIdx.x / E;
     const int64_t e = (int64_t)blockIdx.x * E + el;
@@ -549,12 +549,25 @@ __global__ __launch_bounds__(kBlock) void k_weight_gradient_reduce(const float* 
     }
     part[cl][el] = s;
     __syncthreads();
+    if (cl < 16) {  // (reads and writes no rows but those of its own remainder by 16)
+        double sum = 0.0;
+#pragma unroll
+        for (int i = 0; i < LANES / 16; ++i) sum += part[cl + 16 * i][el];
+        part[cl][el] = sum;
+    }
+    __syncthreads();
     if (cl == 0 && e < total) {
         double sum = 0.0;
 #pragma unroll
-        for (int i = 0; i < LANES; ++i) sum += part[i][el];
+        for (int i = 0; i < 16; ++i) sum += part[i][el];
         Wg[e] = (float)sum;
     }
+}
+template <int E, int THREADS>
+void launch_reduce(const float* part, int64_t chunks, int64_t total, float* Wg, hipStream_t s) {
+    static_assert(THREADS / E >= 16, "the last sum takes 16 lanes");
+    hipLaunchKernelGGL((k_weight_gradient_reduce<E, THREADS>), dim3((unsigned)((total + E - 1) / E)), dim3(THREADS), 0, s, part,
+                       (int)chunks, total, Wg);
 }
 
 // 16-byte row accesses need widths that are multiples of four and aligned bases.
@@ -726,12 +739,22 @@ int weight_gradient(const epp_paths* paths, int k, const float* Y, int F_in, con
 #undef EPP_LAUNCH_WG
     }
     const int64_t total = (int64_t)F_in * F_out;
-    if (total >= 4096)
-        hipLaunchKernelGGL(k_weight_gradient_reduce<16>, dim3((unsigned)((total + 15) / 16)), dim3(kBlock), 0, s,
-                           static_cast<const float*>(part), (int)chunks, total, grad_W);
-    else
-        hipLaunchKernelGGL(k_weight_gradient_reduce<64>, dim3((unsigned)((total + 3) / 4)), dim3(kBlock), 0, s,
-                           static_cast<const float*>(part), (int)chunks, total, grad_W);
+    // Up to 128 partial sums are one round of loads for workgroups of 256 threads.  More, in workgroups of 1,024 (4 or 16 elements by 256
+    // threads -> this): 250 of 41 x 41 / 64 x 64 / 128 x 128 4.5 / 6.2 / 7.6 -> 2.6 / 3.9 / 5.1 us; 1,021 of 16 x 16 / 16 x 41 / 64 x 16 / 64 x 47 /
+    // 64 x 64 6.8 / 7.3 / 7.8 / 15.2 / 18.4 -> 4.6 / 5.1 / 4.9 / 8.8 / 7.7; 512 of 96 x 96 / 128 x 128 14.6 / 16.2 -> 7.6 / 8.4 (4 TB/s).  The number of
+    // elements keeps about 128 to 512 workgroups in flight.
+    if (chunks <= 128) {
+        if (total >= 4096) launch_reduce<16, 256>(part, chunks, total, grad_W, s);
+        else launch_reduce<4, 256>(part, chunks, total, grad_W, s);
+    } else if (total >= 8192) {
+        launch_reduce<32, 1024>(part, chunks, total, grad_W, s);
+    } else if (total >= 4096) {
+        launch_reduce<16, 1024>(part, chunks, total, grad_W, s);
+    } else if (total >= 1024) {
+        launch_reduce<8, 1024>(part, chunks, total, grad_W, s);
+    } else {
+        launch_reduce<4, 1024>(part, chunks, total, grad_W, s);
+    }
     EPP_HIP_TRY(hipGetLastError());
     return EPP_OK;
 }
