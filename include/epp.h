@@ -127,7 +127,9 @@ typedef struct {
  *   train_ids  device, n_train entries; duplicates allowed (set semantics)
  *   L          number of layers, >= 1
  *   alloc      the caller's device allocator, or NULL (see epp_alloc_t)
- *   stream     work is enqueued here; the call synchronises the stream before returning
+ *   stream     work is enqueued here; the call synchronises the stream before returning (up to 65,536 vertices and 131,072
+ *              entries: all that was enqueued is done and may be used on any stream, but for some microseconds more
+ *              hipStreamQuery may answer that it is not)
  *   out        receives a handle owned by the library; release with epp_destroy_paths
  * Where the active sets are nested (always with self-loops) and the path of layer l holds nearly
  * all entries of the path of layer l - 1, it is stored as a view of that path: see

@@ -835,8 +835,10 @@ int epp_build_schedule_over(const epp_path* p, const int32_t* rowptr, int64_t n_
         hipLaunchKernelGGL(k_sched_groups, dim3((unsigned)((n_rows + kSchedRows - 1) / kSchedRows)), dim3(1024), 0, s, rowptr,
                            n_rows, gs, sc->group_row.as<int32_t>(), sc->cut_rows.as<int32_t>(), n_cut);
         EPP_HIP_TRY(hipGetLastError());
-        EPP_TRY(host.fetch(0, n_cut, 1, s));
-        sc->n_split_rows = (int64_t)(host.p[0] & 0xFFFFFFFFll);  // (the lower half; the store goes on behind it)
+        host.p[0] = 0;
+        EPP_HIP_TRY(hipMemcpyAsync(host.p, n_cut, sizeof(unsigned int), hipMemcpyDeviceToHost, s));
+        EPP_HIP_TRY(hipStreamSynchronize(s));
+        sc->n_split_rows = (int64_t)host.p[0];  // (little endian)
     }
     guard.s = nullptr;
     *out = sc;

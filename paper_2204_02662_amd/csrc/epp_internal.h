@@ -365,20 +365,19 @@ struct PinnedWords {
     PinnedWords& operator=(const PinnedWords&) = delete;
     int get(size_t need);
     ~PinnedWords();
-    // The wait for a kernel that raises this signal once everything before it on the stream is done and its words are written.  The host
-    // looks at a word of the block instead of asking the runtime, which takes 5 us more and 1.4 for every launch since it was last asked (1 /
-    // 4 / 16 kernels and hipStreamSynchronize 10.9 / 17.3 / 63 us, with a raised signal 6.1 / 13.3 / 42; with both 14.3 / 20.7 / 68: so
-    // what ends with a signal does not ask it at all).
+    // A kernel that is all that a call launches may raise this signal when everything that it writes is written, and the host then looks at
+    // a word of the block instead of asking the runtime, which knows 5 us later (prepared on 2,700 vertices 34.5 -> 29.2 us).
+    // Not for calls of several launches: these then wait, unknown to the runtime, for the next hipStreamSynchronize, which takes 20 us
+    // more from eight of them on (signals in export, import and the levels of a preparation: exported and synchronised 25 -> 32 us, prepared
+    // on 20,000 vertices and synchronised 122 -> 141, imported and one epoch over a group table 193 -> 211).
     struct Signal { long long* flag; long long ticket; };
     Signal signal();
     int wait(hipStream_t s);
-    // Words of device memory into the block from `at` on, and the wait for them and for all that the stream had to do.
-    int fetch(size_t at, const void* device, size_t words, hipStream_t s);
     long long ticket = 0;
+    struct Block { long long* words = nullptr; hipEvent_t mark = nullptr; int device = -1; } block;  // (mark: an event of that GPU)
 };
-int epp_wait(hipStream_t s);  // until all is done that the stream had to do
 __device__ __forceinline__ void epp_raise(PinnedWords::Signal g) {  // (by one thread, whose own words it releases)
-    if (g.flag) __hip_atomic_store(g.flag, g.ticket, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+    __hip_atomic_store(g.flag, g.ticket, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 // prepare.hip

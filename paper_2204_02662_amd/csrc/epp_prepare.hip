@@ -436,26 +436,16 @@ __device__ __forceinline__ int scan_chunk(const int* __restrict__ in, int* __res
     return all;
 }
 
-// Words for the host, in pinned memory, and the signal that they are there.  (Kernels before it on the stream are done when it starts.)
-__global__ __launch_bounds__(kBlock) void k_hand_over(const long long* __restrict__ from, int words, long long* to, PinnedWords::Signal signal) {
-    for (int i = threadIdx.x; i < words; i += kBlock) to[i] = from[i];
-    __threadfence_system();
-    __syncthreads();
-    if (threadIdx.x == 0) epp_raise(signal);
-}
-
 // With `level` (the numbers of a level, of which *total is one) and `host` (pinned): all of them are
-// handed to the host, which is told so.
+// handed to the host.
 __global__ __launch_bounds__(1024) void k_scan_counts(const int* __restrict__ in, int* __restrict__ out, int64_t n,
-                                                      long long* total, const long long* level, long long* host,
-                                                      PinnedWords::Signal signal) {
+                                                      long long* total, const long long* level, long long* host) {
     int carry = 0;
     for (int64_t base = 0; base < n; base += kScanChunk) carry += scan_chunk(in, out, n, base, carry);
     if (threadIdx.x == 0) {
         *total = carry;
         if (host) {
             for (int i = 0; i < kLevelWords; ++i) host[i] = level + i == total ? (long long)carry : level[i];
-            epp_raise(signal);
         }
     }
 }
@@ -875,17 +865,17 @@ inline int64_t scan_tmp_stride(int64_t n) { return ((n + kScanChunk - 1) / kScan
 inline size_t scan_tmp_bytes(int64_t n) { return (size_t)(2 * scan_tmp_stride(n)) * sizeof(int); }
 // `level`, `host`: see k_scan_counts.
 void scan_counts(const int* in, int* out, int64_t n, long long* total, int* tmp, hipStream_t s,
-                 const long long* level = nullptr, long long* host = nullptr, PinnedWords::Signal signal = {nullptr, 0}) {
+                 const long long* level = nullptr, long long* host = nullptr) {
     const int64_t chunks = (n + kScanChunk - 1) / kScanChunk;
     if (chunks <= 4) {
-        hipLaunchKernelGGL(k_scan_counts, dim3(1), dim3(1024), 0, s, in, out, n, total, (const long long*)level, host, signal);
+        hipLaunchKernelGGL(k_scan_counts, dim3(1), dim3(1024), 0, s, in, out, n, total, (const long long*)level, host);
         return;
     }
     int* chunk_sum = tmp;
     int* chunk_base = tmp + scan_tmp_stride(n);
     hipLaunchKernelGGL(k_scan_chunks, dim3((unsigned)chunks), dim3(1024), 0, s, in, out, n, chunk_sum);
     hipLaunchKernelGGL(k_scan_counts, dim3(1), dim3(1024), 0, s, (const int*)chunk_sum, chunk_base, chunks, total,
-                       level, host, signal);
+                       level, host);
     hipLaunchKernelGGL(k_scan_add_offsets, dim3((unsigned)chunks), dim3(1024), 0, s, out, n, (const int*)chunk_base);
 }
 
@@ -915,9 +905,9 @@ int compact_bitmap(const DevBuf& bitmap, int64_t n, const int* newptr, int total
         hipLaunchKernelGGL(k_bitmap_count, dim3(tiles), dim3(kBlock), 0, s, bitmap.as<unsigned long long>(), n_words,
                            tile_cnt.as<int>());
         hipLaunchKernelGGL(k_scan_counts, dim3(1), dim3(1024), 0, s, tile_cnt.as<int>(), tile_base.as<int>(),
-                           (int64_t)tiles, dev_total.as<long long>(), (const long long*)nullptr, (long long*)nullptr,
-                           PinnedWords::Signal{nullptr, 0});
-        EPP_TRY(hs.fetch(0, dev_total.p, 1, s));
+                           (int64_t)tiles, dev_total.as<long long>(), (const long long*)nullptr, (long long*)nullptr);
+        EPP_HIP_TRY(hipMemcpyAsync(hs.p, dev_total.p, sizeof(long long), hipMemcpyDeviceToHost, s));
+        EPP_HIP_TRY(hipStreamSynchronize(s));
         R = hs.p[0];
     }
     *count = R;
@@ -1161,15 +1151,16 @@ int input_error(int bits, int64_t n) {
 namespace {
 constexpr size_t kPinnedBlock = 4096, kIdlePinned = 16;
 std::mutex g_pinned_lock;
-long long* g_pinned_idle[kIdlePinned];
+PinnedWords::Block g_pinned_idle[kIdlePinned];
 size_t g_pinned_count = 0;
 }  // namespace
 
 int PinnedWords::get(size_t need) {
     if (need <= kPinnedBlock) {
         std::lock_guard<std::mutex> hold(g_pinned_lock);
-        if (g_pinned_count) p = g_pinned_idle[--g_pinned_count];
+        if (g_pinned_count) block = g_pinned_idle[--g_pinned_count];
     }
+    p = block.words;
     count = std::max(need, kPinnedBlock);
     // (behind the words the one that a signal is given by)
     if (!p && hipHostMalloc((void**)&p, (count + 1) * sizeof(long long), hipHostMallocPortable | hipHostMallocCoherent) != hipSuccess) {
@@ -1178,6 +1169,7 @@ int PinnedWords::get(size_t need) {
         epp_set_error("pinned host allocation failed");
         return EPP_ERR_ALLOC;
     }
+    block.words = p;
     return EPP_OK;
 }
 
@@ -1186,10 +1178,11 @@ PinnedWords::~PinnedWords() {
     if (count == kPinnedBlock) {
         std::lock_guard<std::mutex> hold(g_pinned_lock);
         if (g_pinned_count < kIdlePinned) {
-            g_pinned_idle[g_pinned_count++] = p;
+            g_pinned_idle[g_pinned_count++] = block;
             return;
         }
     }
+    if (block.mark) (void)hipEventDestroy(block.mark);
     (void)hipHostFree(p);
 }
 
@@ -1201,6 +1194,16 @@ PinnedWords::Signal PinnedWords::signal() {
 }
 
 int PinnedWords::wait(hipStream_t s) {
+    // (A hipStreamSynchronize soon after this would put such a mark on the stream itself, and wait for it: prepared and synchronised 41 us
+    // without, 33 with it, 38 with hipStreamSynchronize in place of the signal.  Without it nothing is wrong.)
+    int device = -1;
+    if (hipGetDevice(&device) == hipSuccess && (!block.mark || block.device != device)) {
+        if (block.mark) (void)hipEventDestroy(block.mark);
+        block.device = device;
+        if (hipEventCreateWithFlags(&block.mark, hipEventDisableTiming) != hipSuccess) block.mark = nullptr;
+    }
+    if (block.mark) (void)hipEventRecord(block.mark, s);
+    (void)hipGetLastError();
     // (not for ever: after 10 ms, or where no kernel will raise it, the runtime says what the stream does)
     const auto end = std::chrono::steady_clock::now() + std::chrono::milliseconds(10);
     do {
@@ -1209,20 +1212,12 @@ int PinnedWords::wait(hipStream_t s) {
             __builtin_ia32_pause();
         }
     } while (std::chrono::steady_clock::now() < end);
-    EPP_HIP_TRY(hipStreamSynchronize(s));
-    return EPP_OK;
-}
-
-int PinnedWords::fetch(size_t at, const void* device, size_t words, hipStream_t s) {
-    hipLaunchKernelGGL(k_hand_over, dim3(1), dim3(kBlock), 0, s, static_cast<const long long*>(device), (int)words, p + at, signal());
-    EPP_HIP_TRY(hipGetLastError());
-    return wait(s);
-}
-
-int epp_wait(hipStream_t s) {
-    PinnedWords none;
-    if (none.get(1) == EPP_OK) return none.fetch(0, nullptr, 0, s);
-    EPP_HIP_TRY(hipStreamSynchronize(s));
+    const hipError_t e = hipStreamSynchronize(s);
+    if (e != hipSuccess && block.mark) {  // (it may be part of a capture that this ended)
+        (void)hipEventDestroy(block.mark);
+        block.mark = nullptr;
+    }
+    EPP_HIP_TRY(e);
     return EPP_OK;
 }
 
@@ -1343,11 +1338,6 @@ extern "C" int epp_prepare(const epp_csr_t* g, const int32_t* train_ids, int64_t
     arena.take(&scan_tmp, tmp_bytes);
     arena.take(&tile_row, cnt_bytes);
     arena.take(&levels, level_bytes);
-    struct Idle {  // (a level's numbers arrive before its last kernel is done: on an error the temporaries wait for that)
-        hipStream_t s;
-        bool needed = true;
-        ~Idle() { if (needed) (void)hipStreamSynchronize(s); }
-    } idle{s};
     long long* const d_levels = levels.as<long long>();
     unsigned long long* const d_stats = reinterpret_cast<unsigned long long*>(d_levels + (size_t)L * kLevelWords);
     EPP_HIP_TRY(hipMemsetAsync(levels.p, 0, level_bytes, s));
@@ -1426,12 +1416,12 @@ extern "C" int epp_prepare(const epp_csr_t* g, const int32_t* train_ids, int64_t
                                P->bitmaps[k + 1].as<unsigned long long>(), row_cnt.as<int>(),
                                k == 0 ? tile_row.as<int>() : (int*)nullptr);
             scan_counts(row_cnt.as<int>(), row_base[slot].as<int>(), (int64_t)row_tiles, d_level + 1, scan_tmp.as<int>(), s, d_level,
-                        hs.p, hs.signal());
-            EPP_HIP_TRY(hipGetLastError());
-            EPP_TRY(hs.wait(s));
+                        hs.p);
         } else {
-            EPP_TRY(hs.fetch(0, d_level, kLevelWords, s));
+            EPP_HIP_TRY(hipMemcpyAsync(hs.p, d_level, kLevelWords * sizeof(long long), hipMemcpyDeviceToHost, s));
         }
+        EPP_HIP_TRY(hipGetLastError());
+        EPP_HIP_TRY(hipStreamSynchronize(s));
         if (hs.p[2] & kErrTrain) {
             epp_set_error("training id outside [0, %lld)", (long long)n);
             return EPP_ERR_OUT_OF_RANGE_ID;
@@ -1492,8 +1482,8 @@ extern "C" int epp_prepare(const epp_csr_t* g, const int32_t* train_ids, int64_t
         }
     }
     if (pending.p) EPP_TRY(extract(pending.p, pending.level, false));
-    EPP_TRY(hs.fetch(kLevelWords, d_stats, (size_t)L * kStatWords, s));
-    idle.needed = false;
+    EPP_HIP_TRY(hipMemcpyAsync(hs.p + kLevelWords, d_stats, (size_t)L * kStatWords * 8, hipMemcpyDeviceToHost, s));
+    EPP_HIP_TRY(hipStreamSynchronize(s));
     for (size_t k = 0; k < built.size(); ++k)
         epp_path_set_stats(built[k], reinterpret_cast<const unsigned long long*>(hs.p) + kLevelWords + k * kStatWords);
     guard.p = nullptr;
@@ -1677,7 +1667,8 @@ extern "C" int epp_paths_import(int64_t n, int L, const int32_t* train_ids, int6
         hipLaunchKernelGGL(k_import_path, dim3(q.row_blocks + grid_for(a.nnz, kImportTile)), dim3(kBlock), 0, s, q);
         EPP_HIP_TRY(hipGetLastError());
     }
-    EPP_TRY(hs.fetch(0, d_res, res_words, s));
+    EPP_HIP_TRY(hipMemcpyAsync(hs.p, d_res, res_words * 8, hipMemcpyDeviceToHost, s));
+    EPP_HIP_TRY(hipStreamSynchronize(s));
     const int herr = (int)hs.p[0];
     if (herr & (kErrCol | kErrTrain)) { epp_set_error("an id lies outside [0, %lld)", (long long)n); return EPP_ERR_OUT_OF_RANGE_ID; }
     if (herr) { epp_set_error("path arrays are not in canonical form"); return EPP_ERR_INVALID_ARG; }
@@ -1697,12 +1688,14 @@ int epp_check_sources(epp_path* p, hipStream_t s) {
     PinnedWords host;
     DevBuf outside;
     EPP_TRY(host.get(1));
-    EPP_TRY(outside.alloc(sizeof(long long), epp_alloc_of(p)));
-    EPP_HIP_TRY(hipMemsetAsync(outside.p, 0, sizeof(long long), s));
+    EPP_TRY(outside.alloc(sizeof(int), epp_alloc_of(p)));
+    EPP_HIP_TRY(hipMemsetAsync(outside.p, 0, sizeof(int), s));
     hipLaunchKernelGGL(k_columns_inside, dim3(grid_for(p->nnz, kBlock * kCheckPer)), dim3(kBlock), 0, s, p->cv.as<int2>(),
                        p->nnz, reinterpret_cast<const unsigned int*>(p->sources), outside.as<int>());
     EPP_HIP_TRY(hipGetLastError());
-    EPP_TRY(host.fetch(0, outside.p, 1, s));
+    host.p[0] = 0;
+    EPP_HIP_TRY(hipMemcpyAsync(host.p, outside.p, sizeof(int), hipMemcpyDeviceToHost, s));
+    EPP_HIP_TRY(hipStreamSynchronize(s));
     if (host.p[0] != 0) p->sources = nullptr;  // any row may be gathered
     p->sources_checked = true;
     return EPP_OK;
@@ -1738,7 +1731,7 @@ extern "C" int epp_path_export(const epp_path_t* p, int32_t* row_ids, int32_t* r
                                (const int*)nullptr, p->nnz, eb, col, val, ids, ptr, p->n_rows, row_ids, rowptr);
     }
     EPP_HIP_TRY(hipGetLastError());
-    EPP_TRY(epp_wait(s));
+    EPP_HIP_TRY(hipStreamSynchronize(s));
     // (an entry array that was rebuilt for this call only is given back again)
     epp_release_canonical_if_unused(p->outer ? p->outer : const_cast<epp_path*>(p));
     return EPP_OK;

@@ -415,7 +415,7 @@ int epp_build_rows_plan(epp_path* p, int F, hipStream_t s, RowsPlan** out) {
                        1 << c0, reinterpret_cast<int*>(q->store.as<char>() + DevArena::rounded((size_t)n_chunks * 8)),
                        static_cast<int2v*>(q->chunks), q->rows);
     EPP_HIP_TRY(hipGetLastError());
-    EPP_TRY(epp_wait(s));
+    EPP_HIP_TRY(hipStreamSynchronize(s));
     guard.q = nullptr;
     *out = q;
     return EPP_OK;
