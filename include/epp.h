@@ -255,7 +255,12 @@ int epp_paths_import(int64_t n, int L, const int32_t* train_ids, int64_t n_train
 /* Combination stage of the backward pass restricted to the active rows (Alg. 1, backward
  * loop: W'(l) = Y(l)^T (x) X'(l+1) and Y'(l) = X'(l+1) (x) W(l)^T; by Theorem 1 the rows of
  * X'(l+1) outside N^k, k = L-l-1, are zero and add nothing to either product).  Both run on
- * the matrix cores in fp32.
+ * the matrix cores in fp32; for two widths of 65 to 128 and more than 16,384 (W') or 32,768 (Y')
+ * rows with every operand in three bfloat16 parts and sums in fp32.  That is as close to the exact
+ * result as fp32 products are, for operands of any magnitude, denormal ones too, and closer for sums
+ * of many; a sum of a single product may be off by 2.1 x 2^-24 of it instead of 2^-24.  Infinities
+ * and NaN are where fp32 has them.  Sums with operands so large that the parts overflow (operands
+ * of 2^97, products of 2^66), and W' with NaN, are formed a second time in fp32 and take longer.
  *   k        which active set holds the non-zero rows of grad_X: 0..L, or -1 for all n rows
  *            (the unrestricted products)
  *   Y        device, n x F_in   forward aggregation result of the layer

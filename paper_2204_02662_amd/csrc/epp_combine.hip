@@ -3,11 +3,11 @@
 //     Y' = X' (x) W^T      (one row per vertex)
 // Theorem 1 makes every row of X' outside N^k zero, so both products run over the ascending id
 // list of N^k only: the rows are gathered (and, for Y', scattered) by vertex id, everything
-// else is a dense contraction and runs on the matrix cores in fp32 (v_mfma_f32_32x32x2_f32).
+// else is a dense contraction and runs on the matrix cores in fp32 (v_mfma_f32_32x32x2_f32; two
+// widths of 65 to 128 and many rows in bfloat16 parts, epp_combine_split.hip).
 //
 // Widths of up to 128 (every weight matrix of an ordinary model) have kernels of their own, further down:
 // the whole product of a pair of rows fits a wavefront's registers, so nothing but W goes through LDS.
-// Two widths of 65 to 128 and many rows are left to epp_combine_split.hip.
 //
 // For wider ones both kernels give a workgroup of four wavefronts, arranged WM x WN, an output tile of
 // 32 WM BM x 32 WN BN, every wavefront BM x BN accumulator blocks of 32 x 32, and step through

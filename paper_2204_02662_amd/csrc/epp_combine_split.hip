@@ -3,24 +3,22 @@
 // a cycle, with every float split into three bfloat16 parts.
 //
 // x = h + m + l with h = bf16(x), m = bf16(x - h), l = x - h - m: both differences are exact, and so is l as a bfloat16 (24 bits
-// less the 8 + 1 of each part before).  Of the nine products of two split floats six are formed; ml, lm and ll are below
-// 2^-26 of hh.  Sums are in 32 bits, in two chains: hh, and the five small ones, added at the end.  (In one chain the matrix
-// core drops the small products' low bits against a sum that has all of its own, always downwards: a bias of 2e-7 of a sum of 4,480
-// terms, which does not average out over thousands of such sums as errors do.)  Relative error of sums of 16 / 128 / 512 / 4,480
-// products of normal numbers against 64 bits: fp32 instruction 7.3 / 20 / 41 / 120 e-8, one chain 3.3 / 16 / 34 / 104, two 3.2 /
-// 6.5 / 13 / 42.
+// less the 8 + 1 of each part before).  The bf16 instruction takes parts and products below 2^-126 as zero.  So x is 2^23 times the operand,
+// by which every part of every float, denormal ones too, is above that, and every product that counts beside a result; sums go back
+// by 2^-46.
 //
-// What the parts cannot hold is formed again with the fp32 instruction, 32 rows of Y' or a wavefront's part of W' at a time.  The
-// operands' largest magnitudes tell, per row (column) that goes into a sum:
-//   * infinities (inf - inf is no part of one) and what may overflow: from 2^120 on, or where two multiply to 2^100;
-//   * parts or products below 2^-126, which the bf16 instruction takes as zero: where the largest of a row is below 2^-90, or two
-//     such multiply to less than 2^-100.  Above, what is lost is at most 2^-36 of the largest element, 2^-12 of its rounding.
-// (NaN become NaN, in the same rows and columns.)
+// Of the nine products of two split floats six are formed; ml, lm and ll are at most 2^-24 of the product together.  Sums are in 32 bits,
+// in two chains: hh, and the five small ones, added at the end.  (In one chain the matrix core drops the small products' low bits
+// against a sum that has all of its own, always downwards: a bias of 2e-7 of a sum of 4,480 terms, which does not average out over
+// thousands of such sums as errors do.)  Relative error of sums of 16 / 128 / 512 / 4,480 products of normal numbers against 64 bits (formed
+// in one piece for this): fp32 instruction 7.3 / 20 / 41 / 120 e-8, one chain 3.3 / 16 / 34 / 104, two 3.2 / 6.5 / 13 / 42.  It is as
+// large as the fp32 instruction's for W' where all products are positive (a million rows 3.05e-8, 2.94e-8), and larger in sums of one to
+// three products: for one at most 2.1 x 2^-24 of the result (measured 1.8; fp32 1), on average the same (2.60e-8, 2.53e-8).
 //
-// 4.6 M rows, W' with its reduction / Y': 128 x 128 1487 / 1449 -> 1356 / 1062 us, 96 x 96 1457 / 1075 -> 1058 / 740, 65 x 67 1450 / 1118 ->
-// 972 / 883.  What bounds them is the card's power: the matrix core is busy 44 % of the cycles of W' at 128 x 128, at 1.5 GHz (fp32
-// instruction 82 % at 1.9); without four of the six products it takes 964 us, with all of them on rows that are in cache 1057.
-
+// What overflows in this is formed again with the fp32 instruction, 32 rows of Y' or a wavefront's part of W' at a time: rows of Y' whose
+// largest magnitudes multiply to 2^66 or have 2^97 among them, parts of W' that came out infinite or NaN.  (So infinities are
+// where fp32 has them, and NaN in the same rows and columns.)
+//
 // Operand layout of the 32x32x16 instruction: lane l supplies A[l % 32][8 (l / 32) ..] and B[8 (l / 32) ..][l % 32], eight
 // elements; its accumulator is that of 32x32x2.
 
@@ -37,7 +35,8 @@ typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef unsigned uintx4 __attribute__((ext_vector_type(4)));
 
-constexpr float kLeast = 0x1p-90f, kLeastProduct = 0x1p-100f, kMost = 0x1p120f, kMostProduct = 0x1p100f;
+constexpr float kUp = 0x1p23f, kDown = 0x1p-46f;            // of both operands, of their products
+constexpr float kMost = 0x1p120f, kMostProduct = 0x1p112f;  // of scaled operands (128 such products are 2^119)
 
 // Three parts of eight floats, two to a word.
 struct Parts { uintx4 h, m, l; };
@@ -48,15 +47,15 @@ __device__ __forceinline__ unsigned two_bf16(float x, float y) { return __builti
 __device__ __forceinline__ float less(float x, unsigned w, unsigned factors) {
     return __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, w), __builtin_bit_cast(bf16x2, factors), x, false);
 }
-template <class X>  // x(i): the i-th of eight floats; `most` becomes the largest magnitude so far (NaN are passed over)
-__device__ __forceinline__ Parts split(X x, float& most) {
+template <class X>  // of x(i) kUp, x(i) the i-th of eight floats; `most`, if given, becomes the largest magnitude so far (NaN are passed over)
+__device__ __forceinline__ Parts split(X x, float* most = nullptr) {
     Parts r;
     unsigned low = 0x0000BF80u, high = 0xBF800000u;  // -1 for one of two
     asm("" : "+s"(low), "+s"(high));
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-        const float a = x(2 * i), b = x(2 * i + 1);
-        asm("v_max3_f32 %0, |%1|, |%2|, %0" : "+v"(most) : "v"(a), "v"(b));
+        const float a = x(2 * i) * kUp, b = x(2 * i + 1) * kUp;
+        if (most) asm("v_max3_f32 %0, |%1|, |%2|, %0" : "+v"(*most) : "v"(a), "v"(b));
         r.h[i] = two_bf16(a, b);
         const float a1 = less(a, r.h[i], low), b1 = less(b, r.h[i], high);
         r.m[i] = two_bf16(a1, b1);
@@ -64,23 +63,14 @@ __device__ __forceinline__ Parts split(X x, float& most) {
     }
     return r;
 }
-__device__ __forceinline__ float least_of_wave(float x) {
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) x = fminf(x, __shfl_xor(x, d, 64));
-    return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(x)));
-}
 __device__ __forceinline__ float most_of_wave(float x) {
 #pragma unroll
     for (int d = 1; d < 64; d <<= 1) x = fmaxf(x, __shfl_xor(x, d, 64));
     return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(x)));
 }
-// (zeros lose nothing)
-__device__ __forceinline__ float or_one(float x) { return x > 0.0f ? x : 1.0f; }
-// Whether the parts hold everything, from the least of the rows' (columns') largest magnitudes that are not zero, and the largest of
-// them, of both operands.
-__device__ __forceinline__ bool in_range(float least_a, float most_a, float least_b, float most_b) {
-    return least_a >= kLeast && least_b >= kLeast && least_a * least_b >= kLeastProduct && most_a < kMost && most_b < kMost &&
-           most_a * most_b < kMostProduct;
+// Whether nothing overflows, from the largest magnitudes of what is multiplied.
+__device__ __forceinline__ bool in_range(float most_a, float most_b) {
+    return most_a < kMost && most_b < kMost && most_a * most_b < kMostProduct;
 }
 
 // The six products of N blocks: b's with a.
@@ -122,6 +112,7 @@ __global__ __launch_bounds__(256, 2) void k_weight_gradient_split(const int32_t*
     float* __restrict__ mine = out + (int64_t)blockIdx.x * Fi * Fo;
     // (without `ids` the load is of something else and not used: a branch around it would make a step wait for all loads)
     const int32_t* __restrict__ id_src = ids ? ids : reinterpret_cast<const int32_t*>(Y);
+    int buffer = 0;  // (goes on from piece to piece)
     for (int first = (int)group_first; first < group_last; first += kSplitPiece) {
         const int last = std::min(first + kSplitPiece, group_last);
         // Lane i (of eight) holds the vertex of the thread's i-th row of a step (rows past the end repeat the last one), from D steps before
@@ -138,7 +129,6 @@ __global__ __launch_bounds__(256, 2) void k_weight_gradient_split(const int32_t*
         };
         int vertex[D];
         floatx16 sum[2][2] = {}, small[2][2] = {};  // [block of X'][block of Y]
-        float most_a = 0.0f, most_b = 0.0f;
 #pragma unroll
         for (int d = 0; d < D; ++d) {
             const int v = id_src[place(first + 16 * d)];
@@ -146,7 +136,6 @@ __global__ __launch_bounds__(256, 2) void k_weight_gradient_split(const int32_t*
             vertex[d] = id_src[place(first + 16 * (d + D))];
             __builtin_amdgcn_sched_barrier(0);
         }
-        int buffer = 0;
         for (int r0 = first; r0 < last; r0 += 16 * D) {
 #pragma unroll
             for (int d = 0; d < D; ++d) {
@@ -159,11 +148,11 @@ __global__ __launch_bounds__(256, 2) void k_weight_gradient_split(const int32_t*
                     }
                 }
                 {
-                    const Parts x = split([&](int i) { return a[d][i]; }, most_a);
+                    const Parts x = split([&](int i) { return a[d][i]; });
                     parts[buffer][0][wave >> 1][feature] = x.h;
                     parts[buffer][1][wave >> 1][feature] = x.m;
                     parts[buffer][2][wave >> 1][feature] = x.l;
-                    const Parts z = split([&](int i) { return b[d][i]; }, most_b);
+                    const Parts z = split([&](int i) { return b[d][i]; });
                     parts[buffer][0][wave >> 1][128 + feature] = z.h;
                     parts[buffer][1][wave >> 1][128 + feature] = z.m;
                     parts[buffer][2][wave >> 1][128 + feature] = z.l;
@@ -183,18 +172,16 @@ __global__ __launch_bounds__(256, 2) void k_weight_gradient_split(const int32_t*
                 buffer ^= 1;
             }
         }
+        bool finite = true;
 #pragma unroll
         for (int j = 0; j < 2; ++j)
 #pragma unroll
-            for (int i = 0; i < 2; ++i) sum[j][i] += small[j][i];
-        __shared__ float most_of[2][256];  // [half][feature]
-        most_of[wave >> 1][feature] = most_a;
-        most_of[wave >> 1][128 + feature] = most_b;
-        __syncthreads();
-        const float ca = fmaxf(most_of[0][m0 + lane], most_of[1][m0 + lane]);
-        const float cb = fmaxf(most_of[0][128 + n0 + lane], most_of[1][128 + n0 + lane]);
-        __syncthreads();  // `most_of` is written again
-        if (!in_range(least_of_wave(or_one(ca)), most_of_wave(ca), least_of_wave(or_one(cb)), most_of_wave(cb))) {
+            for (int i = 0; i < 2; ++i) {
+                sum[j][i] = (sum[j][i] + small[j][i]) * kDown;
+#pragma unroll
+                for (int e = 0; e < 16; ++e) finite &= fabsf(sum[j][i][e]) < INFINITY;
+            }
+        if (__ballot(!finite)) {
 #pragma unroll
             for (int i = 0; i < 2; ++i)
 #pragma unroll
@@ -254,18 +241,19 @@ __global__ __launch_bounds__(kSplitThreads, 2) void k_input_gradient_split(const
                                                                            float* __restrict__ Yg) {
     constexpr int N = 32 * NT;
     __shared__ uintx4 Ws[3][KS * 2 * N];  // [part][step][half][n]
-    __shared__ unsigned w_most[N];        // bits of the largest magnitude of W's row n (NaN are passed over)
+    __shared__ unsigned w_most;           // bits of W's largest magnitude (NaN are passed over)
     __shared__ float4v out_all[kSplitWaves][32 * 8];  // 32 rows x 32 columns of results, private to a wavefront
     const int lane = threadIdx.x & 63, p = lane & 31, half = lane >> 5;
     // Element i (of four) of the quadruple that starts at k; the last ones of a row start at F_out - 4 and have what comes
     // before k as zeros in W.
     const int top = Fo - 4;
-    for (int n = threadIdx.x; n < N; n += kSplitThreads) w_most[n] = 0;
+    if (threadIdx.x == 0) w_most = 0;
     __syncthreads();
+    float most_w = 0.0f;
     for (int i = threadIdx.x; i < KS * 2 * N; i += kSplitThreads) {
         const int n = i / (KS * 2), s = i % (KS * 2) / 2, h = i % 2;
         const float* __restrict__ row = W + (int64_t)std::min(n, Fi - 1) * Fo;
-        float x[8], most = 0.0f;
+        float x[8];
 #pragma unroll
         for (int q = 0; q < 2; ++q) {
             const int k = 16 * s + 8 * q + 4 * h, from = std::min(k, top);
@@ -273,22 +261,15 @@ __global__ __launch_bounds__(kSplitThreads, 2) void k_input_gradient_split(const
 #pragma unroll
             for (int c = 0; c < 4; ++c) x[4 * q + c] = n < Fi && k < Fo && from + c >= k ? w[c] : 0.0f;
         }
-        const Parts w = split([&](int j) { return x[j]; }, most);
+        const Parts w = split([&](int j) { return x[j]; }, &most_w);
         Ws[0][(s * 2 + h) * N + n] = w.h;
         Ws[1][(s * 2 + h) * N + n] = w.m;
         Ws[2][(s * 2 + h) * N + n] = w.l;
-        atomicMax(&w_most[n], __float_as_uint(most));
     }
-    __syncthreads();
-    float least_w = 1.0f, most_w = 0.0f;
-#pragma unroll
-    for (int j = 0; j < NT; ++j) {
-        const float x = __uint_as_float(w_most[32 * j + p]);
-        least_w = fminf(least_w, or_one(x));
-        most_w = fmaxf(most_w, x);
-    }
-    least_w = least_of_wave(least_w);
     most_w = most_of_wave(most_w);
+    if (lane == 0) atomicMax(&w_most, __float_as_uint(most_w));
+    __syncthreads();
+    most_w = __uint_as_float(__builtin_amdgcn_readfirstlane(w_most));
 
     const int64_t n_tiles = (n_rows + 31) / 32, step = (int64_t)gridDim.x * kSplitWaves;
     auto vertex = [&](int64_t tile) -> int {
@@ -318,7 +299,7 @@ __global__ __launch_bounds__(kSplitThreads, 2) void k_input_gradient_split(const
         float most = 0.0f;
 #pragma unroll
         for (int s = 0; s < KS; ++s) {
-            const Parts b = split([&](int i) { return x[2 * s + i / 4][i % 4]; }, most);
+            const Parts b = split([&](int i) { return x[2 * s + i / 4][i % 4]; }, &most);
             // (behind the last tile these are read once more and not used)
             x[2 * s] = quad(next_row, 2 * s);
             x[2 * s + 1] = quad(next_row, 2 * s + 1);
@@ -332,9 +313,8 @@ __global__ __launch_bounds__(kSplitThreads, 2) void k_input_gradient_split(const
             __builtin_amdgcn_sched_barrier(0);
         }
 #pragma unroll
-        for (int j = 0; j < NT; ++j) sum[j] += small[j];
-        most = fmaxf(most, __shfl_xor(most, 32, 64));
-        if (__ballot(!in_range(or_one(most), most, least_w, most_w))) {
+        for (int j = 0; j < NT; ++j) sum[j] = (sum[j] + small[j]) * kDown;
+        if (__ballot(!in_range(most, most_w))) {
 #pragma unroll
             for (int j = 0; j < NT; ++j) sum[j] = floatx16{};
             const float* __restrict__ row = G + (int64_t)v * Fo;
