@@ -17,7 +17,8 @@
 //
 // What overflows in this is formed again with the fp32 instruction, 32 rows of Y' or a wavefront's part of W' at a time: rows of Y' whose
 // largest magnitudes multiply to 2^66 or have 2^97 among them, parts of W' that came out infinite or NaN.  (So infinities are
-// where fp32 has them, and NaN in the same rows and columns.)
+// where fp32 has them, and NaN in the same rows and columns.)  These take about two and a half times as long as
+// the others: a million rows of 128 x 128 620 to 700 / 550 to 600 us.
 //
 // Operand layout of the 32x32x16 instruction: lane l supplies A[l % 32][8 (l / 32) ..] and B[8 (l / 32) ..][l % 32], eight
 // elements; its accumulator is that of 32x32x2.
@@ -186,20 +187,32 @@ __global__ __launch_bounds__(256, 2) void k_weight_gradient_split(const int32_t*
             for (int i = 0; i < 2; ++i)
 #pragma unroll
                 for (int j = 0; j < 2; ++j) sum[j][i] = floatx16{};
-            for (int r = first; r < last; r += 2) {
-                const bool in = r + half < last;
-                const int at = in ? r + half : r;
-                const int64_t v = ids ? ids[at] : at;
-                float x[2], z[2];
+            constexpr int P = 8;  // pairs of rows at a time
+            auto ids_of = [&](int r) { return id_src[std::min(r + (lane & (2 * P - 1)), last - 1)]; };
+            int ahead = ids_of(first);
+            for (int r = first; r < last; r += 2 * P) {
+                const int now = ahead;
+                ahead = ids_of(r + 2 * P);
+                float x[P][2], z[P][2];
 #pragma unroll
-                for (int u = 0; u < 2; ++u) {
-                    x[u] = in ? (Y + v * Fi)[std::min(m0 + 32 * u + p, Fi - 1)] : 0.0f;
-                    z[u] = in ? (G + v * Fo)[std::min(n0 + 32 * u + p, Fo - 1)] : 0.0f;
+                for (int q = 0; q < P; ++q) {
+                    const int at = std::min(r + 2 * q + half, last - 1);
+                    const int64_t v = ids ? (half ? __builtin_amdgcn_readlane(now, 2 * q + 1) : __builtin_amdgcn_readlane(now, 2 * q)) : at;
+#pragma unroll
+                    for (int u = 0; u < 2; ++u) {
+                        x[q][u] = (Y + v * Fi)[std::min(m0 + 32 * u + p, Fi - 1)];
+                        z[q][u] = (G + v * Fo)[std::min(n0 + 32 * u + p, Fo - 1)];
+                    }
                 }
 #pragma unroll
-                for (int i = 0; i < 2; ++i)
+                for (int q = 0; q < P; ++q) {
+                    const bool in = r + 2 * q + half < last;
 #pragma unroll
-                    for (int j = 0; j < 2; ++j) sum[j][i] = __builtin_amdgcn_mfma_f32_32x32x2f32(x[i], z[j], sum[j][i], 0, 0, 0);
+                    for (int i = 0; i < 2; ++i)
+#pragma unroll
+                        for (int j = 0; j < 2; ++j)
+                            sum[j][i] = __builtin_amdgcn_mfma_f32_32x32x2f32(in ? x[q][i] : 0.0f, in ? z[q][j] : 0.0f, sum[j][i], 0, 0, 0);
+                }
             }
         }
         int m1 = m0 + 4 * half;
@@ -318,13 +331,18 @@ __global__ __launch_bounds__(kSplitThreads, 2) void k_input_gradient_split(const
 #pragma unroll
             for (int j = 0; j < NT; ++j) sum[j] = floatx16{};
             const float* __restrict__ row = G + (int64_t)v * Fo;
-            for (int k = half; k < Fo + half; k += 2) {
-                const float g = k < Fo ? row[k] : 0.0f;
+            for (int k0 = 0; k0 < Fo; k0 += 8) {
+                const int k = k0 + 4 * half, from = std::min(k, top);
+                const float4u g = *reinterpret_cast<const float4u*>(row + from);
+                float4u w[NT];
 #pragma unroll
-                for (int j = 0; j < NT; ++j) {
-                    const int n = 32 * j + p;
-                    const float w = k < Fo && n < Fi ? W[(int64_t)n * Fo + k] : 0.0f;
-                    sum[j] = __builtin_amdgcn_mfma_f32_32x32x2f32(w, g, sum[j], 0, 0, 0);
+                for (int j = 0; j < NT; ++j) w[j] = *reinterpret_cast<const float4u*>(W + (int64_t)std::min(32 * j + p, Fi - 1) * Fo + from);
+#pragma unroll
+                for (int c = 0; c < 4; ++c) {
+                    const bool in = k < Fo && from + c >= k;
+#pragma unroll
+                    for (int j = 0; j < NT; ++j)  // (columns past F_in are not written)
+                        sum[j] = __builtin_amdgcn_mfma_f32_32x32x2f32(in ? w[j][c] : 0.0f, in ? g[c] : 0.0f, sum[j], 0, 0, 0);
                 }
             }
         }
