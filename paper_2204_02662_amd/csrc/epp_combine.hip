@@ -742,7 +742,7 @@ int weight_gradient(const epp_paths* paths, int k, const float* Y, int F_in, con
     // Up to 128 partial sums are one round of loads for workgroups of 256 threads.  More, in workgroups of 1,024 (4 or 16 elements by 256
     // threads -> this): 250 of 41 x 41 / 64 x 64 / 128 x 128 4.5 / 6.2 / 7.6 -> 2.6 / 3.9 / 5.1 us; 1,021 of 16 x 16 / 16 x 41 / 64 x 16 / 64 x 47 /
     // 64 x 64 6.8 / 7.3 / 7.8 / 15.2 / 18.4 -> 4.6 / 5.1 / 4.9 / 8.8 / 7.7; 512 of 96 x 96 / 128 x 128 14.6 / 16.2 -> 7.6 / 8.4 (4 TB/s).  The number of
-    // elements keeps about 128 to 512 workgroups in flight.
+    // elements makes 64 to 512 workgroups of 16 x 16 to 128 x 128.
     if (chunks <= 128) {
         if (total >= 4096) launch_reduce<16, 256>(part, chunks, total, grad_W, s);
         else launch_reduce<4, 256>(part, chunks, total, grad_W, s);

@@ -20,6 +20,11 @@
 // where fp32 has them, and NaN in the same rows and columns.)  These take about two and a half times as long as
 // the others: a million rows of 128 x 128 620 to 700 / 550 to 600 us.
 //
+// 4.6 M rows, fp32 kernels -> this, timed in turn, 20 calls in a row, W' with the sum of its partial sums / Y': 128 x 128 1335 / 1424 -> 1203 /
+// 1048 us, 96 x 96 1263 / 1039 -> 1091 / 744, 65 x 67 1230 / 1066 -> 996 / 700 (another card 1144 / 1015, 1039 / 727, 955 / 689).
+// What bounds them is the card's power: at 128 x 128 the matrix core is busy 42 / 50 % of the cycles, at 1.65 to 2.1 / 1.55 to 1.9 GHz (fp32
+// instruction 82 / 78 %, at 2.07).
+//
 // Operand layout of the 32x32x16 instruction: lane l supplies A[l % 32][8 (l / 32) ..] and B[8 (l / 32) ..][l % 32], eight
 // elements; its accumulator is that of 32x32x2.
 
@@ -385,10 +390,11 @@ __global__ __launch_bounds__(kSplitThreads, 2) void k_input_gradient_split(const
 
 }  // namespace
 
-// One width of up to 64 leaves memory the bound (128 x 64: 12 instructions for 768 bytes), and fewer rows the launch: 10,000 / 17,000 /
-// 40,000 / 65,000 / 100,000 rows of 128 x 128, W' with its reduction 21.9 / 27 / 31.8 / 35.4 / 60 -> 21.8 / 22 / 27.3 / 32.0 / 47 us, Y'
-// (20,000 first) 16.7 / .. / 28.7 / 30.4 / 50 -> 18.4 / .. / 20.4 / 22.8 / 31; 65 x 67 20.1 / 27 / 31.4 / 34.7 / 61 -> 17.4 / 20 / 25.3 / 29.1
-// / 43 and 12.2 / .. / 19.6 / 21.8 / 37 -> 11.1 / .. / 12.3 / 13.8 / 21.
+// One width of up to 64 leaves memory the bound (128 x 64: 12 instructions for 768 bytes), and fewer rows the launch.  fp32 kernels -> this
+// in us, W' with the sum of its partial sums: 128 x 128, 10,000 / 20,000 / 40,000 / 100,000 rows 21.9 -> 21.8, 29.0 -> 21.9, 32.5 -> 25.7,
+// 61 -> 43; 65 x 67 20.1 -> 17.4, 27.8 -> 18.7, 31.7 -> 24.2, 62 -> 39; 65 x 128, 16,400 rows 26.4 -> 19.5.  Y', 20,000 / 40,000 / 100,000:
+// 16.7 -> 18.4, 27.5 -> 19.0, 51 -> 31.6; 65 x 67 12.2 -> 11.1, 19.5 -> 12.1, 35.8 -> 21.5; 65 x 128, 33,000 rows 24.8 -> 15.4.  (W' of up to 65,536
+// rows is cut into 256 workgroups, as the fp32 kernel wants it; two fit a CU here, and 512 have not been tried.)
 static bool split_widths(int Fi, int Fo) { return Fi > 64 && Fo > 64 && Fi <= 128 && Fo <= 128; }
 bool epp_split_weight_gradient(int Fi, int Fo, int64_t n_rows) { return split_widths(Fi, Fo) && n_rows > 16384; }
 bool epp_split_input_gradient(int Fi, int Fo, int64_t n_rows) { return split_widths(Fi, Fo) && n_rows > 32768; }

