@@ -258,6 +258,8 @@ inline int tile_order_of(int lanes) { return lanes == 4 ? 0 : lanes == 8 ? 1 : 2
 struct TilePlan {
     DevBuf store;                    // the allocation behind the arrays
     int lanes = 0;                   // per slot
+    int ahead = 0;                   // how far a launch's gathers run ahead of its additions
+    bool far = false;                // launches take the addresses of far rows at any size (tests)
     int at_once = 0;                 // tiles that run at the same time, among which the rows are dealt
     int n_tiles = 0, max_batches = 0, n_cut = 0;
     int64_t n_parts = 0;

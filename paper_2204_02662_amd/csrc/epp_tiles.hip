@@ -611,6 +611,7 @@ struct TileArgs {
     const float* in;
     float* out;
     float* parts;                 // sums of the cut rows' parts, F floats each
+    unsigned records;             // bytes from a slice's first row to the end of its last one
     int n, F;
     int lanes;                    // of a slot that hold part of a slice
     int ld;                       // floats from one row of `in` to the next
@@ -619,6 +620,9 @@ struct TileArgs {
     const float* zero;            // launch for the inner path that shares the arrays: 256 zero bytes
     const unsigned int* inner_rows;
 };
+
+constexpr unsigned kNowhere = 0xFFFFFF00u;  // place of a source row that is not there: behind all that are
+constexpr int kRawBuffer = 0x00020000;      // a buffer of bytes, loads behind whose end give zero
 
 // Copies the source rows slice by slice: all rows of the first slice, `stride` quadruples apart, of which `q` are used
 // (zeros behind F), then those of the next.  Rows that are not in the bitmap `sources` (NULL: all are) are left
@@ -649,13 +653,16 @@ __global__ __launch_bounds__(kListBlock) void k_pack_slices(const float* __restr
     }
 }
 
-// A wavefront per tile and slice.  8 and 16 lanes a slot are bound by the lines that miss L2 (2.4 M sources, 140 M entries,
-// F = 64: 93 G lines/s, half of which miss; the group kernel's launch takes 4620 us, this one 3090): all gathers of a
-// batch go out together, then its sums are added up, and a wavefront drifts from the others by one batch at most.  With the
-// gathers of the next batch made step by step as registers come free, the same launch took 3300 us, and with two batches 3500:
-// wavefronts that run further ahead find less in L2.  Slots of 4 lanes read half a line or less at a time and wait for
-// latency instead: there the gathers do run kDepth batches ahead (114 M entries, 233 K sources, F = 16: 697 us without, 575
-// with one batch, 555 with two, 554 with three; the group kernel 920).
+// A wavefront per tile and slice.  Where the sources' lines miss L2, these bound it (2.4 M sources, 140 M entries, F = 64: 93 G
+// lines/s, half of which miss; the group kernel's launch takes 4620 us, this one 3080), and the further a wavefront runs ahead, the
+// less it finds there; where they hit, it waits for latency.  So its gathers go out AHEAD pairs of steps (of kSlots entries each) before
+// their additions, in a window that rolls over the batches (2 batches of 4 lanes), or, AHEAD = 0, a batch at a time.  tile_ahead
+// has the rule and the figures.
+//
+// What is formed per entry is what a step cannot share: the lanes of a slot hold its entries' weights and the places of their source
+// rows and sums, and the additions take them from there by DPP; the gathers are buffer loads with a 32-bit offset.  (Formed by every
+// lane for itself, with 64-bit addresses, a batch of 64 entries and 16 lanes a slot was 280 instructions instead of 206; 114 M entries,
+// 233 K sources, F = 41: 1390 -> 1310 us.)  FAR: rows that lie further apart than such an offset reaches.
 //
 // A sum is formed in LDS over a part of the sweep at a time, and those sums in registers, where a lane has those of the rows that it
 // will write.  A part holds kPiece entries of a row whose sources lie anywhere; the rounding error then grows like that of a sum of
@@ -663,11 +670,14 @@ __global__ __launch_bounds__(kListBlock) void k_pack_slices(const float* __restr
 // 0.63 to 0.89 of the group kernel's against 64 bits.  A row whose sources all lie in one part is one chain of up to kSplitMax, 0.99 to
 // 1.6 of it; paths of such rows stay on the group table (k_tile_order).  Adding up in LDS alone would be no faster (within 3 %, the
 // spread of the runs).
-template <int LANES, bool INNER>
+template <int LANES, int AHEAD, bool INNER, bool FAR>
 __global__ __launch_bounds__(kTileWaves * 64, 2) void k_aggregate_tiles(TileArgs a) {
     constexpr int kRows = tile_rows(LANES), kSlots = 64 / LANES, kSteps = LANES;
-    constexpr int kDepth = LANES == 4 ? 2 : 0;
-    constexpr int kTakes = std::max(kDepth, 1);
+    constexpr int kPairs = kSteps / 2;
+    constexpr int kTakes = LANES == 4 ? 2 : 1;  // batches in flight
+    static_assert(AHEAD == (LANES == 4 ? kTakes * kPairs : AHEAD) && AHEAD <= kTakes * kPairs, "a step's registers are those that it frees");
+    constexpr unsigned kNoRow = FAR ? ~0u : kNowhere;
+    constexpr int kShares = LANES == 8 ? 2 : 1;  // entries of a batch that a lane holds
     typedef __attribute__((address_space(1))) const float4u* gvec_ptr;
     __shared__ float4v sums_all[kTileWaves][(kRows + 1) * LANES];
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
@@ -679,121 +689,172 @@ __global__ __launch_bounds__(kTileWaves * 64, 2) void k_aggregate_tiles(TileArgs
     const int b0 = a.first_batch[tile], b1 = a.first_batch[tile + 1];
     if (b0 == b1) return;  // (its places have no rows; nothing below waits for another wavefront)
     for (int i = lane; i < (kRows + 1) * LANES; i += 64) sums[i] = float4v{};
-    const float* __restrict__ src = a.in + slice * a.slice_step + min(l, a.lanes - 1) * 4;
-    const unsigned ld = (unsigned)a.ld;
-    const int2v* __restrict__ ent = a.ent + (int64_t)b0 * 64 + lane;
+    const float* __restrict__ src = a.in + slice * a.slice_step;
+    const unsigned ld = (unsigned)a.ld * (FAR ? 1u : 4u), share = (unsigned)min(l, a.lanes - 1) * (FAR ? 4u : 16u);
+    const __amdgpu_buffer_rsrc_t rows = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(src), 0, (int)a.records, kRawBuffer);
+    // (8 lanes: the entries of steps 0 to 3, then of 4 to 7, in each of a slot's two quads)
+    const int2v* __restrict__ ent = a.ent + (int64_t)b0 * 64 + (LANES == 8 ? slot * 8 + (l & 3) : lane);
     const int last = b1 - b0 - 1, pieces = min((a.longest[tile] + kPiece - 1) / kPiece, last + 1);
-    // Gathers are kDepth batches ahead of the additions, entries and their two bits of `care` one batch more.  (Behind the end
-    // the last batch is gathered again, from L2.)
-    auto entries = [&](int b) { return __builtin_nontemporal_load(ent + min(b, last) * 64); };
+    // Entries and their two bits of `care` are loaded one batch before they are used.  (Behind the end the last batch is gathered
+    // again, from L2.)
+    struct Entries { int2v e[kShares]; };
+    auto entries = [&](int b) {
+        Entries x;
+#pragma unroll
+        for (int i = 0; i < kShares; ++i) x.e[i] = __builtin_nontemporal_load(ent + min(b, last) * 64 + i * 4);
+        return x;
+    };
     auto cares = [&](int b) { return a.care[(b0 + min(b, last)) >> 4]; };
-    struct { float4u x[kSteps]; float w[kSteps]; unsigned at[kSteps]; unsigned care; } flight[kTakes];
-    int2v ahead = entries(0);
-    int2v here;
-    auto put = [&](int b) {  // the entries of batch b, and loads those of the next
-        here = ahead;
+    // Of a batch in flight: what its gathers give, and of the entries that a lane holds the weight and the place of the row's sum.
+    struct Shares { float w[kShares]; int at[kShares]; };
+    struct { float4u x[kSteps]; Shares own; unsigned care; } flight[kTakes];
+    unsigned place[kShares];  // and of the source row, of the batch that is being gathered
+    Entries ahead = entries(0);
+    auto put = [&](int b, Shares& own) {  // the entries of batch b, and loads those of the next
+        const Entries here = ahead;
         ahead = entries(b + 1);
         __builtin_amdgcn_sched_barrier(0);  // (before the gathers that come next, so that waiting for it is not waiting for them)
-    };
-    // Step j's entry of a lane's slot: the slot's lane j has it.  (Handed on through LDS, as both its words were at first, the
-    // entries took a place there that rows can use, and 2 to 9 % of a launch: 94 M entries, 250 K sources, F = 32, 8 lanes
-    // 830 -> 760 us; F = 64, 16 lanes 1305 -> 1225; 140 M, 2.4 M sources, F = 64: 3170 -> 3080.)
-    auto entry = [&](auto J) {
-        constexpr int j = decltype(J)::value;
-        auto word = [&](int x) {
-            if constexpr (LANES == 4) return __builtin_amdgcn_update_dpp(0, x, j * 0x55, 0xF, 0xF, true);  // quad_perm:[j,j,j,j]
-            else if constexpr (LANES == 8) {
-                const int low = __builtin_amdgcn_update_dpp(0, x, 0x150 + j, 0xF, 0xF, true);  // row_newbcast:j, then the upper half of a row
-                return __builtin_amdgcn_update_dpp(low, x, 0x158 + j, 0xF, 0xC, false);
-            } else return __builtin_amdgcn_update_dpp(0, x, 0x150 + j, 0xF, 0xF, true);
-        };
-        return int2v{word(here.x), word(here.y)};
-    };
-    auto gather = [&](auto& fl, int j, int2v e) {
-        fl.at[j] = (((unsigned)e.x >> kColBits) & 255u) * LANES + l;
-        // (32 bits: the number of vertices times ld is below 2^32)
-        const unsigned place = __umul24((unsigned)e.x & kColMask23, ld);
-        gvec_ptr p = (gvec_ptr)(src + place);
-        fl.w[j] = __int_as_float(e.y);
-        if constexpr (INNER) {
-            if (e.x < 0) { p = (gvec_ptr)(a.zero + l * 4); fl.w[j] = 0.0f; }
+#pragma unroll
+        for (int i = 0; i < kShares; ++i) {
+            const int x = here.e[i].x;
+            own.at[i] = (int)(((unsigned)x >> kColBits) & 255u) * LANES * 16;
+            own.w[i] = __int_as_float(here.e[i].y);
+            place[i] = __umul24((unsigned)x & kColMask23, ld);
+            if constexpr (INNER) {
+                if (x < 0) { place[i] = kNoRow; own.w[i] = 0.0f; }
+            }
         }
-        fl.x[j] = *p;
+    };
+    // Step j's value of a lane's slot: one of the slot's lanes has it, and an addition or a product takes it from there.  (Handed
+    // on through LDS, as the words of an entry were at first, entries took a place there that rows can use, and 2 to 9 % of a launch.)
+    auto of_step = [&](auto J, const auto (&v)[kShares]) {
+        constexpr int j = decltype(J)::value;
+        const int x = __builtin_bit_cast(int, v[LANES == 8 ? j >> 2 : 0]);
+        int y;
+        if constexpr (LANES == 16) y = __builtin_amdgcn_update_dpp(0, x, 0x150 + j, 0xF, 0xF, true);  // row_newbcast:j
+        else y = __builtin_amdgcn_update_dpp(0, x, (j & 3) * 0x55, 0xF, 0xF, true);                   // quad_perm:[j,j,j,j]
+        return __builtin_bit_cast(std::remove_const_t<std::remove_reference_t<decltype(v[0])>>, y);
+    };
+    auto gather = [&](auto& fl, auto J) {
+        const unsigned at = of_step(J, place);
+        if constexpr (FAR) {
+            gvec_ptr p = (gvec_ptr)(src + (at + share));  // (32 bits: the number of vertices times ld is below 2^32)
+            if constexpr (INNER) p = at == kNoRow ? (gvec_ptr)(a.zero + l * 4) : p;
+            fl.x[J] = *p;
+        } else {
+            fl.x[J] = __builtin_bit_cast(float4u, __builtin_amdgcn_raw_buffer_load_b128(rows, (int)(at + share), 0, 0));
+        }
     };
     // (always in this order: the wait for one gather is then not for another that was made later)
-    auto gather_two = [&](auto& fl, int j, int2v e0, int2v e1) {
-        gather(fl, j, e0);
+    auto gather_two = [&](auto& fl, auto J, auto K) {
+        gather(fl, J);
         __builtin_amdgcn_sched_barrier(0x7);  // (arithmetic may cross)
-        gather(fl, j + kSteps / 2, e1);
+        gather(fl, K);
         __builtin_amdgcn_sched_barrier(0);
     };
-    // (in LDS a wavefront's operations execute in order)
-    auto add = [&](auto& fl, int j) {
-        float4v sum = sums[fl.at[j]];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) sum[i] = fmaf(fl.w[j], fl.x[j][i], sum[i]);
-        sums[fl.at[j]] = sum;
+    auto sum_at = [&](auto& fl, auto J) {
+        return reinterpret_cast<float4v*>(reinterpret_cast<char*>(sums) + (of_step(J, fl.own.at) + l * 16));
     };
-    auto for_steps = [&](auto f) {  // for the first half of them, a constant each
-        f(std::integral_constant<int, 0>{});
-        f(std::integral_constant<int, 1>{});
-        if constexpr (kSteps >= 8) { f(std::integral_constant<int, 2>{}); f(std::integral_constant<int, 3>{}); }
+    auto plus = [&](auto& fl, auto J, float4v& sum) {
+        const float w = of_step(J, fl.own.w);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) sum[i] = fmaf(w, fl.x[J][i], sum[i]);
+    };
+    auto for_steps = [&](auto f) {  // for the first half of them, a constant each, and that of the other half
+        auto g = [&](auto J) { f(J, std::integral_constant<int, decltype(J)::value + kSteps / 2>{}); };
+        g(std::integral_constant<int, 0>{});
+        g(std::integral_constant<int, 1>{});
+        if constexpr (kSteps >= 8) { g(std::integral_constant<int, 2>{}); g(std::integral_constant<int, 3>{}); }
         if constexpr (kSteps >= 16) {
-            f(std::integral_constant<int, 4>{});
-            f(std::integral_constant<int, 5>{});
-            f(std::integral_constant<int, 6>{});
-            f(std::integral_constant<int, 7>{});
+            g(std::integral_constant<int, 4>{});
+            g(std::integral_constant<int, 5>{});
+            g(std::integral_constant<int, 6>{});
+            g(std::integral_constant<int, 7>{});
         }
     };
     auto take = [&](int b, auto& fl) {
         const unsigned how = __builtin_amdgcn_readfirstlane(fl.care >> (2 * ((b0 + b) & 15))) & 3u;
-        put(b + kDepth);
         fl.care = cares(b + kTakes);
-        constexpr int kHalf = kSteps / 2;
-        if constexpr (kDepth == 0) {
-            for_steps([&](auto J) {
-                gather(fl, J, entry(J));
-                gather(fl, J + kHalf, entry(std::integral_constant<int, J + kHalf>{}));
+        Shares next;  // of the batch whose gathers go out meanwhile
+        if constexpr (AHEAD == 0) {
+            put(b, fl.own);
+            for_steps([&](auto J, auto K) {
+                gather(fl, J);
+                gather(fl, K);
             });
         }
+        auto refill = [&](auto J) {  // (the gathers go to registers that the additions have freed)
+            if constexpr (AHEAD > 0) {
+                constexpr int j = decltype(J)::value + AHEAD, q = j % kPairs;
+                __builtin_amdgcn_sched_barrier(0);
+                if constexpr (q == 0) put(b + kTakes, next);
+                gather_two(fl, std::integral_constant<int, q>{}, std::integral_constant<int, q + kPairs>{});
+            }
+        };
         const int turns = how == 0 ? 1 : how == 1 ? care_turns(LANES, 1) : how == 2 ? care_turns(LANES, 2) : care_turns(LANES, 3);
         const int mine = slot & (turns - 1);
-        auto in_turns = [&](int j) {
+        auto in_turns = [&](auto J) {
+            float4v* const p = sum_at(fl, J);
+            const float w = of_step(J, fl.own.w);
             for (int t = 0; t < turns; ++t) {
-                if (mine == t) add(fl, j);
+                if (mine == t) {
+                    float4v sum = *p;
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) sum[i] = fmaf(w, fl.x[J][i], sum[i]);
+                    *p = sum;
+                }
                 __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
                 __builtin_amdgcn_wave_barrier();
             }
         };
-        for_steps([&](auto J) {
-            constexpr int j = decltype(J)::value;
-            if (how != 0) {
-                in_turns(j);
-                in_turns(j + kHalf);
-            } else if constexpr (care_turns(LANES, 0) == 1) {
-                add(fl, j);
-                add(fl, j + kHalf);
+        // (in LDS a wavefront's operations execute in order)
+        auto add_two = [&](auto J, auto K) {
+            float4v* const p0 = sum_at(fl, J);
+            float4v* const p1 = sum_at(fl, K);
+            float4v s0 = *p0;
+            if constexpr (care_turns(LANES, 0) == 1) {
+                plus(fl, J, s0);
+                *p0 = s0;
+                float4v s1 = *p1;
+                plus(fl, K, s1);
+                *p1 = s1;
             } else {
-                float4v s0 = sums[fl.at[j]], s1 = sums[fl.at[j + kHalf]];
-#pragma unroll
-                for (int i = 0; i < 4; ++i) s0[i] = fmaf(fl.w[j], fl.x[j][i], s0[i]);
-#pragma unroll
-                for (int i = 0; i < 4; ++i) s1[i] = fmaf(fl.w[j + kHalf], fl.x[j + kHalf][i], s1[i]);
-                sums[fl.at[j]] = s0;
-                sums[fl.at[j + kHalf]] = s1;
+                float4v s1 = *p1;
+                plus(fl, J, s0);
+                plus(fl, K, s1);
+                *p0 = s0;
+                *p1 = s1;
             }
-            if constexpr (kDepth > 0) {
-                __builtin_amdgcn_sched_barrier(0);  // (the gathers go to the registers that this has freed)
-                gather_two(fl, j, entry(J), entry(std::integral_constant<int, j + kHalf>{}));
-            }
-        });
+        };
+        if constexpr (AHEAD > 0) {  // (one order of loads whichever way a batch is taken: the waits count them)
+            for_steps([&](auto J, auto K) {
+                if (how == 0) {
+                    add_two(J, K);
+                } else {
+                    in_turns(J);
+                    in_turns(K);
+                }
+                refill(J);
+            });
+        } else if (how == 0) {
+            for_steps([&](auto J, auto K) { add_two(J, K); });
+        } else {
+            for_steps([&](auto J, auto K) {
+                in_turns(J);
+                in_turns(K);
+            });
+        }
+        if constexpr (AHEAD > 0) fl.own = next;
     };
 #pragma unroll
     for (int d = 0; d < kTakes; ++d) {
         flight[d].care = cares(d);
-        if (kDepth == 0) continue;
-        put(d);
-        for_steps([&](auto J) { gather_two(flight[d], J, entry(J), entry(std::integral_constant<int, J + kSteps / 2>{})); });
+        if constexpr (AHEAD > 0) {
+            put(d, flight[d].own);
+            for_steps([&](auto J, auto K) {
+                if constexpr (decltype(J)::value < AHEAD) gather_two(flight[d], J, K);
+            });
+        }
     }
     constexpr int kOwn = (kRows + 1) / kSlots;
     static_assert(kOwn * kSlots == kRows + 1, "");
@@ -937,11 +998,17 @@ void sample_order(const epp_path* p, int split, int shift, unsigned int* delay, 
                        p->rowptr.as<int32_t>(), p->n_stream_rows, split, shift, delay);
 }
 
-template <int LANES>
+template <int LANES, int AHEAD>
 void launch_tiles(const TileArgs& a, int slices, hipStream_t s) {
     const dim3 grid((unsigned)(a.blocks * slices)), block(kTileWaves * 64);
-    if (a.zero) hipLaunchKernelGGL((k_aggregate_tiles<LANES, true>), grid, block, 0, s, a);
-    else hipLaunchKernelGGL((k_aggregate_tiles<LANES, false>), grid, block, 0, s, a);
+    const bool far = a.records == 0;
+    if (a.zero) {
+        if (far) hipLaunchKernelGGL((k_aggregate_tiles<LANES, AHEAD, true, true>), grid, block, 0, s, a);
+        else hipLaunchKernelGGL((k_aggregate_tiles<LANES, AHEAD, true, false>), grid, block, 0, s, a);
+    } else {
+        if (far) hipLaunchKernelGGL((k_aggregate_tiles<LANES, AHEAD, false, true>), grid, block, 0, s, a);
+        else hipLaunchKernelGGL((k_aggregate_tiles<LANES, AHEAD, false, false>), grid, block, 0, s, a);
+    }
 }
 
 }  // namespace
@@ -1025,18 +1092,15 @@ static double group_launch_us(const epp_path* p, const Sources& src, int F) {
 }
 
 // .. and on tiles of so many lanes a slot.
-static double tile_launch_us(const epp_path* p, const Sources& src, int F, int lanes) {
-    struct Cost { double launch, sweep, entry, line_cached, line_missed, row, copy; };  // us; ps per entry, line, row and byte
-    const Cost c = lanes == 4 ? Cost{45, 10.2, 2.5, 2.3, 19.6, 0.0, 0.36} : lanes == 8 ? Cost{76, 1.7, 6.5, 0.38, 10.7, 0.84, 0.29}
-                                                                        : Cost{41, 3.4, 9.4, 0.90, 14.6, 0.22, 0.17};
-    const TileShape t = tile_shape(F, lanes);
-    const double per_line = std::max(1.0, 8.0 / t.stride), lines = std::max(1.0, t.stride == 12 ? 2.0 : t.stride / 8.0);
+struct Sweeps { double count, missed; };  // and the source rows' lines that they fetch from beyond L2, a line a row
+static Sweeps tile_sweeps(const Sources& src, int lanes, double per_line) {
     const double capacity = (double)kTilesAtOnce * tile_rows(lanes);
-    // sweeps, the longest rows first: each XCD touches the sources of an eighth of a sweep's entries
-    double sweeps = 0.0, missed = 0.0, room = capacity, entries = 0.0;
+    // the longest rows first: each XCD touches the sources of an eighth of a sweep's entries
+    Sweeps s = {0.0, 0.0};
+    double room = capacity, entries = 0.0;
     auto sweep = [&] {
-        missed += std::min(8.0 * src.touched(entries / 8.0, per_line), entries);
-        sweeps += 1.0;
+        s.missed += std::min(8.0 * src.touched(entries / 8.0, per_line), entries);
+        s.count += 1.0;
         entries = 0.0;
         room = capacity;
     };
@@ -1051,6 +1115,34 @@ static double tile_launch_us(const epp_path* p, const Sources& src, int F, int l
         }
     }
     if (entries > 0.0) sweep();
+    return s;
+}
+
+// Pairs of steps that a launch's gathers are ahead of its additions (k_aggregate_tiles), by the part of its gathers that is expected to
+// miss L2, a line a row (us with 0 / 2 / 3 / 4 pairs; ids in random order, all-active;
+// sources, entries, missed):
+//   16 lanes, F = 64: 262 K sources, 60 M entries, 0.03 missed 752 / 881 / 733 / 712, F = 48 686 / 875 / 724 / 707; 233 K, 115 M, 0.03 1265 /
+//   1624 / 1337 / 1311; 1 M, 179 M, 0.07 2290 / 2626 / 2233 / 2257; 0.4 M, 44 M, 0.17 768 / 736 / 669 / 715; 4.2 M, 133 M, 0.21 2352 / 2450 /
+//   2232 / 2293; 8.4 M, 149 M, 0.31 3180 / 3208 / 3014 / 3128; 3 M, 270 M, 0.49 7084 / 6468 / 6653 / 7196; 5 M, 139 M, 0.70 4406 / 4247 / 4201 / 4397.
+//   8 lanes, F = 32: 262 K, 60 M, 0.024 439 / 527 / 422 / 409; 1 M, 179 M, 0.05 1301 / 1541 / 1252 / 1247; 0.4 M, 44 M, 0.11 384 / 418 / 369 / 372; 4.2 M, 0.16
+//   1201 / 1336 / 1198 / 1225; 1 M, 89 M, 0.21 809 / 857 / 806 / 851; 8.4 M, 0.25 1592 / 1709 / 1601 / 1640; 3 M, 0.37 2710 / 2746 / 2804 / 3064; 5 M,
+//   0.61 2044 / 1971 / 2018 / 2105; 2.4 M, 140 M,
+//   F = 64 3220 / 3082 / 3142 / 3431; dense ones, 1.1 M, 252 M, 0.12 1.09 to 1.15 of a batch at a time with 4.
+// 4 lanes need both batches in flight everywhere (114 M entries, 233 K sources, F = 16: 697 us without, 575 with one, 541 with two).
+static int tile_ahead(int lanes, double missed) {
+    if (lanes == 4) return 4;
+    if (lanes == 8) return missed < 0.10 ? 4 : missed < 0.33 ? 3 : 2;
+    return missed < 0.06 ? 0 : 3;
+}
+
+static double tile_launch_us(const epp_path* p, const Sources& src, int F, int lanes) {
+    struct Cost { double launch, sweep, entry, line_cached, line_missed, row, copy; };  // us; ps per entry, line, row and byte
+    const Cost c = lanes == 4 ? Cost{45, 10.2, 2.5, 2.3, 19.6, 0.0, 0.36} : lanes == 8 ? Cost{76, 1.7, 6.5, 0.38, 10.7, 0.84, 0.29}
+                                                                        : Cost{41, 3.4, 9.4, 0.90, 14.6, 0.22, 0.17};
+    const TileShape t = tile_shape(F, lanes);
+    const double per_line = std::max(1.0, 8.0 / t.stride), lines = std::max(1.0, t.stride == 12 ? 2.0 : t.stride / 8.0);
+    const Sweeps sw = tile_sweeps(src, lanes, per_line);
+    const double sweeps = sw.count, missed = sw.missed;
     const double nnz = (double)p->nnz;
     double us = c.launch + 1e-6 * (double)p->n_stream_rows * F * c.row +
                 t.slices * (sweeps * c.sweep + 1e-6 * (nnz * c.entry + lines * ((nnz - missed) * c.line_cached + missed * c.line_missed)));
@@ -1067,6 +1159,8 @@ static double tile_launch_us(const epp_path* p, const Sources& src, int F, int l
 // 1547 / - / 1446 / 1442; 65 M of 8.4 M, F = 41: 2726 / 4699 / 4376 / 3603.
 // Of 540 other paths and widths (ids in random order, 4 to 240 M entries, F = 5 to 160) 162 are taken, in 0.70 of the time on average,
 // 1.11 at worst (R-MAT, 165,000 sources, F = 88).
+// Among 8 and 16 lanes, slices of 33 to 48 floats on 16 (t.stride == 12), three quarters of whose lines they fill, take 0.92 of that: of 101
+// launches the choice is then 0.01 % behind the better one, 0.4 % without (2.4 M sources, 140 M entries, F = 47: 3640 on 8, 3440 on 16).
 // The tiles cost 9 to 11 us per million entries to prepare, which five launches have to repay.  Rows of up to 32 floats have to be
 // estimated to save kNarrowSaves a launch besides: beyond that width the group kernel prepares a partitioned copy of skewed graphs, which
 // costs as much as tiles, but here a group table of 20 us, and a run that ends soon pays for the difference (import and one epoch, F =
@@ -1103,11 +1197,13 @@ int epp_tile_lanes(const epp_path* p, int F, double* max_delay) {
     const Sources src(p);
     const double groups = group_launch_us(p, src, F);
     int lanes = 0;
-    double best = 1e30;
+    double best = 1e30, ranked = 1e30;
     for (const int l : {4, 8, 16}) {
-        if (tile_shape(F, l).slices > 8) continue;
-        const double us = tile_launch_us(p, src, F, l);
-        if (us < best) { best = us; lanes = l; }
+        const TileShape t = tile_shape(F, l);
+        if (t.slices > 8) continue;
+        const double us = tile_launch_us(p, src, F, l), rank = t.stride == 12 ? 0.92 * us : us;
+        best = std::min(best, us);
+        if (rank < ranked) { ranked = rank; lanes = l; }
     }
     const double need = std::max({0.1 * groups, 20.0 + 2e-6 * (double)p->nnz, F > 32 ? 0.0 : kNarrowSaves});
     const double spare = groups - need - best;
@@ -1175,6 +1271,8 @@ int epp_build_tiles(epp_path* p, int lanes, double max_delay, hipStream_t s, Til
     q->at_once = std::max(env_int("EPP_TUNE_TILES_AT_ONCE", kTilesAtOnce) / 512, 1) * 512;  // (whole groups of kTogether tiles per XCD)
     const int64_t rows_at_once = (int64_t)q->at_once * rows_per_tile;
     q->lanes = lanes;
+    q->ahead = env_int("EPP_TUNE_TILE_AHEAD", tile_ahead(lanes, tile_sweeps(Sources(p), lanes, 1.0).missed / (double)p->nnz));
+    q->far = env_int("EPP_TUNE_TILE_FAR", 0) != 0;
     q->n_tiles = (int)((n_rows + rows_at_once - 1) / rows_at_once * q->at_once);
     q->n_parts = n_parts;
     q->n_cut = (int)n_cut;
@@ -1249,11 +1347,18 @@ int epp_launch_tiles(const epp_path* p, const TilePlan* q, float* parts, const f
     a.ld = t.packed ? t.stride * 4 : F;
     a.slice_step = t.packed ? p->n * t.stride * 4 : t.quads * 4;
     a.blocks = q->n_tiles / kTileWaves;
+    const int64_t bytes = ((p->n - 1) * (int64_t)a.ld + t.quads * 4) * 4;
+    a.records = bytes <= (int64_t)kNowhere && !q->far ? (unsigned)bytes : 0u;
     a.zero = inner_rows ? p->zero_block.as<float>() : nullptr;
     a.inner_rows = inner_rows;
-    if (q->lanes == 4) launch_tiles<4>(a, t.slices, s);
-    else if (q->lanes == 8) launch_tiles<8>(a, t.slices, s);
-    else launch_tiles<16>(a, t.slices, s);
+    switch (q->lanes * 16 + q->ahead) {
+        case 4 * 16 + 4: launch_tiles<4, 4>(a, t.slices, s); break;
+        case 8 * 16 + 2: launch_tiles<8, 2>(a, t.slices, s); break;
+        case 8 * 16 + 3: launch_tiles<8, 3>(a, t.slices, s); break;
+        case 8 * 16 + 4: launch_tiles<8, 4>(a, t.slices, s); break;
+        case 16 * 16 + 3: launch_tiles<16, 3>(a, t.slices, s); break;
+        default: launch_tiles<16, 0>(a, t.slices, s); break;
+    }
     if (q->n_cut > 0) {
         int log2T = 0;
         while (log2T < 6 && (4 << log2T) < F) ++log2T;
