@@ -236,11 +236,12 @@ struct Partition {
 };
 
 // What the row kernel (epp_rows.hip) needs to know of the rows that one workgroup should not take alone:
-// they are cut into chunks, whose sums a second kernel adds.
-struct HugeRow { int v, first, count; };  // vertex, its first chunk and their number
+// they are cut into chunks, whose sums the last workgroup of the row's adds.
+struct HugeRow { int v, first, count; unsigned done; };  // vertex, its first chunk and their number; 0, during a launch how many it has summed
+struct RowChunk { int begin, end, row, unused; };        // entries; which of the cut rows
 struct RowsPlan {
     DevBuf store;
-    void* chunks = nullptr;   // entry range of every chunk
+    RowChunk* chunks = nullptr;
     HugeRow* rows = nullptr;
     float* pieces = nullptr;  // float[n_chunks][F]
     int n_huge = 0, n_chunks = 0;

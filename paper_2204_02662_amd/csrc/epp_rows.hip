@@ -11,7 +11,7 @@
 //   * a row of more than `limit` entries is left to the whole workgroup, which takes the long rows
 //     among its own one after the other;
 //   * a row of more than a few steps of a workgroup is cut into chunks, one workgroup each, at the
-//     front of the grid; a second kernel adds the chunks' sums.
+//     front of the grid, and the last of them to be done adds the chunks' sums.
 // The order of the additions depends on the path and the width only: equal inputs give equal bits.
 //
 // Bound by the address units where the sources lie in L2: a slot's pairs are therefore loaded by its lanes, one each, and handed
@@ -71,8 +71,9 @@ struct RowArgs {
     int huge;                // longest row that is not cut into chunks
     int has_long;            // some row is longer than `limit`
     int chunk_blocks;        // workgroups that take one chunk of a cut row each, before the others
-    const int2v* chunks;     // their entries [x, y); empty: no such chunk
-    float* pieces;           // their sums, F floats each
+    const RowChunk* chunks;  // empty: no such chunk
+    HugeRow* huge_rows;      // the cut rows
+    float* pieces;           // the chunks' sums, F floats each
     // launch for the inner path that shares the arrays only
     const float* zero;           // what an entry that is not the inner path's gathers
     const unsigned int* only;    // bitmap of the inner path's rows
@@ -178,17 +179,17 @@ __device__ __forceinline__ bool not_numbers(const float (&acc)[VEC]) {
     return bad;
 }
 
-// o[f ..] of the calling thread's lanes = sum of the entries [q0, q1), by the whole workgroup.
-template <int VEC, int LOG2T, bool INNER>
-__device__ __forceinline__ void sum_by_workgroup(const RowArgs& a, int q0, int q1, float* __restrict__ o,
-                                                 float (*part)[(1 << LOG2T) * VEC]) {
+// o[f ..] of the calling thread's lanes = sum of what the slots of the workgroup add up each: acc = add(f).  Only the first
+// wavefront writes, PIECE: past the L2, for workgroups on other XCDs.
+template <int VEC, int LOG2T, bool PIECE, class Add>
+__device__ __forceinline__ void sum_by_workgroup(const RowArgs& a, float* __restrict__ o, float (*part)[(1 << LOG2T) * VEC], Add add) {
     constexpr int T = 1 << LOG2T;
-    const int t = threadIdx.x & (T - 1), slot = threadIdx.x >> LOG2T;
+    const int t = threadIdx.x & (T - 1);
     for (int f0 = 0; f0 < a.F; f0 += T * VEC) {
         const bool fok = f0 + t * VEC < a.F;
         const int f = fok ? min(f0 + t * VEC, a.F - VEC) : 0;
         float acc[VEC];
-        add_entries<VEC, LOG2T, kU, INNER, true>(a, a.in + f, q0 + slot * kU, q1, (kBlock >> LOG2T) * kU, acc);
+        add(f, acc);
 #pragma unroll
         for (int d = T; d < 64; d <<= 1) {
 #pragma unroll
@@ -208,10 +209,60 @@ __device__ __forceinline__ void sum_by_workgroup(const RowArgs& a, int q0, int q
                 for (int w = 1; w < kBlock / 64; ++w) sum += part[w][t * VEC + i];
                 r[i] = sum;
             }
-            store_frag<VEC>(o + f, r);
+            if constexpr (PIECE) {
+#pragma unroll
+                for (int i = 0; i < VEC; ++i) __hip_atomic_store(o + f + i, r[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            } else {
+                store_frag<VEC>(o + f, r);
+            }
         }
         __syncthreads();  // `part` is written again
     }
+}
+
+// One chunk of a cut row.  The workgroup that is the last of the row's to be done adds the chunks' sums, in an order that depends on their
+// number alone (a launch of its own for that took 4 to 5 us and the gap before it: an epoch of 88,784 vertices, F = 16 / 39, and what
+// comes before it 177 -> 167 us, the backward loop of 1.1 M vertices, F = 16 / 41, 228.6 -> 223.1).  Sums are written and read past the
+// L2, of which every XCD has its own; the wait before the count is for the writes to have arrived.
+template <int VEC, int LOG2T, bool INNER>
+__device__ __forceinline__ void sum_chunk(const RowArgs& a, float (*part)[(1 << LOG2T) * VEC], int* was) {
+    const RowChunk c = a.chunks[blockIdx.x];
+    if (c.begin >= c.end) return;
+    const int slot = threadIdx.x >> LOG2T;
+    constexpr int kSlots = kBlock >> LOG2T, kAhead = 4;
+    sum_by_workgroup<VEC, LOG2T, true>(a, a.pieces + (size_t)blockIdx.x * a.F, part, [&](int f, float (&acc)[VEC]) {
+        add_entries<VEC, LOG2T, kU, INNER, true>(a, a.in + f, c.begin + slot * kU, c.end, kSlots * kU, acc);
+    });
+    HugeRow* const h = a.huge_rows + c.row;
+    const int count = h->count;
+    if (threadIdx.x < 64) {
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        if (threadIdx.x == 0) *was = (int)atomicInc(&h->done, (unsigned)count - 1u);  // (0 again behind the last one)
+    }
+    __syncthreads();
+    if (*was != count - 1) return;
+    if constexpr (INNER) {
+        if (!((a.only[h->v >> 5] >> (h->v & 31)) & 1u)) return;
+    }
+    const float* __restrict__ pieces = a.pieces + (size_t)h->first * a.F;
+    sum_by_workgroup<VEC, LOG2T, false>(a, a.out + (size_t)h->v * a.F, part, [&](int f, float (&acc)[VEC]) {
+#pragma unroll
+        for (int i = 0; i < VEC; ++i) acc[i] = 0.0f;
+        for (int p = slot; p < count; p += kAhead * kSlots) {
+            float x[kAhead][VEC];
+#pragma unroll
+            for (int u = 0; u < kAhead; ++u)
+#pragma unroll
+                for (int i = 0; i < VEC; ++i)
+                    x[u][i] = __hip_atomic_load(pieces + (size_t)min(p + u * kSlots, count - 1) * a.F + f + i, __ATOMIC_RELAXED,
+                                                __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+            for (int u = 0; u < kAhead; ++u)
+#pragma unroll
+                for (int i = 0; i < VEC; ++i)
+                    if (p + u * kSlots < count) acc[i] += x[u][i];
+        }
+    });
 }
 
 template <int VEC, int LOG2T, bool INNER>
@@ -221,8 +272,7 @@ __global__ __launch_bounds__(kBlock, 7) void k_aggregate_rows(RowArgs a) {
     __shared__ int count;
     __shared__ float part[kBlock / 64][T * VEC];
     if ((int)blockIdx.x < a.chunk_blocks) {
-        const int2v c = a.chunks[blockIdx.x];
-        if (c.x < c.y) sum_by_workgroup<VEC, LOG2T, INNER>(a, c.x, c.y, a.pieces + (size_t)blockIdx.x * a.F, part);
+        sum_chunk<VEC, LOG2T, INNER>(a, part, &count);
         return;
     }
     const int t = threadIdx.x & (T - 1), slot = threadIdx.x >> LOG2T;
@@ -282,55 +332,33 @@ __global__ __launch_bounds__(kBlock, 7) void k_aggregate_rows(RowArgs a) {
         if constexpr (INNER) {
             if (!((a.only[lv >> 5] >> (lv & 31)) & 1u)) continue;  // (uniform)
         }
-        sum_by_workgroup<VEC, LOG2T, INNER>(a, q0, q1, a.out + (size_t)lv * a.F, part);
+        sum_by_workgroup<VEC, LOG2T, false>(a, a.out + (size_t)lv * a.F, part, [&](int f, float (&acc)[VEC]) {
+            add_entries<VEC, LOG2T, kU, INNER, true>(a, a.in + f, q0 + slot * kU, q1, (kBlock >> LOG2T) * kU, acc);
+        });
     }
 }
 
 // Rows of more than `chunk` entries: their chunks, and what the chunks' sums are to be added to.
 __global__ __launch_bounds__(kBlock) void k_cut_huge_rows(const int32_t* __restrict__ rowptr,
                                                           const int32_t* __restrict__ row_ids, int n_rows, int chunk,
-                                                          int* __restrict__ counters, int2v* __restrict__ chunks,
+                                                          int* __restrict__ counters, RowChunk* __restrict__ chunks,
                                                           HugeRow* __restrict__ rows) {
     const int r = blockIdx.x * kBlock + threadIdx.x;
     const int p0 = r < n_rows ? rowptr[r] : 0, p1 = r < n_rows ? rowptr[r + 1] : 0;
-    int first = 0, cnt = 0;
+    int first = 0, cnt = 0, row = 0;
     if (p1 - p0 > chunk) {
         cnt = (p1 - p0 + chunk - 1) / chunk;
         first = atomicAdd(&counters[0], cnt);
-        rows[atomicAdd(&counters[1], 1)] = HugeRow{row_ids ? row_ids[r] : r, first, cnt};
+        row = atomicAdd(&counters[1], 1);
+        rows[row] = HugeRow{row_ids ? row_ids[r] : r, first, cnt, 0u};
     }
     // a row's chunks are written by its wavefront: there can be thousands
     for (unsigned long long todo = __ballot(cnt > 0); todo; todo &= todo - 1ull) {
         const int l = __ffsll((long long)todo) - 1;
         const int begin = __shfl(p0, l, 64), end = __shfl(p1, l, 64), at = __shfl(first, l, 64), n = __shfl(cnt, l, 64);
+        const int its_row = __shfl(row, l, 64);
         for (int i = threadIdx.x & 63; i < n; i += 64)
-            chunks[at + i] = int2v{begin + i * chunk, min(begin + (i + 1) * chunk, end)};
-    }
-}
-
-// out[v] = sum of the chunks of v's row, in a fixed order.  One wavefront per row: the pieces are
-// dealt to 64 >> log2t groups of lanes, eight in flight each.
-__global__ __launch_bounds__(kBlock) void k_add_chunks(const HugeRow* __restrict__ rows, int n_huge,
-                                                       const float* __restrict__ pieces, int F, int log2t,
-                                                       const unsigned int* __restrict__ only, float* __restrict__ out) {
-    const int k = blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6);
-    if (k >= n_huge) return;
-    const HugeRow h = rows[k];
-    if (only && !((only[h.v >> 5] >> (h.v & 31)) & 1u)) return;
-    const int T = 1 << log2t, lane = threadIdx.x & 63, sub = lane >> log2t, S = 64 >> log2t;
-    const float* __restrict__ p = pieces + (size_t)h.first * F;
-    for (int f0 = 0; f0 < F; f0 += T) {
-        const int f = f0 + (lane & (T - 1));
-        float sum = 0.0f;
-        for (int c = sub; c < h.count; c += 8 * S) {
-            float x[8];
-#pragma unroll
-            for (int i = 0; i < 8; ++i) x[i] = f < F && c + i * S < h.count ? p[(size_t)(c + i * S) * F + f] : 0.0f;
-#pragma unroll
-            for (int i = 0; i < 8; ++i) sum += x[i];
-        }
-        for (int d = T; d < 64; d <<= 1) sum += __shfl_xor(sum, d, 64);
-        if (f < F && sub == 0) out[(size_t)h.v * F + f] = sum;
+            chunks[at + i] = RowChunk{begin + i * chunk, min(begin + (i + 1) * chunk, end), its_row, 0};
     }
 }
 
@@ -404,16 +432,16 @@ int epp_build_rows_plan(epp_path* p, int F, hipStream_t s, RowsPlan** out) {
     const epp_alloc_t* al = epp_alloc_of(p);
     q->n_huge = (int)n_huge;
     q->n_chunks = (int)n_chunks;  // (an upper bound)
-    const size_t table = DevArena::rounded((size_t)n_chunks * 8) + DevArena::rounded(8);
+    const size_t table = DevArena::rounded((size_t)n_chunks * sizeof(RowChunk)) + DevArena::rounded(8);
     EPP_TRY(q->store.alloc(table + DevArena::rounded((size_t)n_huge * sizeof(HugeRow)) + (size_t)n_chunks * F * 4, al));
-    q->chunks = q->store.p;
+    q->chunks = q->store.as<RowChunk>();
     q->rows = reinterpret_cast<HugeRow*>(q->store.as<char>() + table);
     q->pieces = reinterpret_cast<float*>(q->store.as<char>() + table + DevArena::rounded((size_t)n_huge * sizeof(HugeRow)));
     EPP_HIP_TRY(hipMemsetAsync(q->store.p, 0, table, s));
     hipLaunchKernelGGL(k_cut_huge_rows, dim3((unsigned)((p->n_stream_rows + kBlock - 1) / kBlock)), dim3(kBlock), 0, s,
                        p->rowptr.as<int32_t>(), p->row_ids.p ? p->row_ids.as<int32_t>() : nullptr, (int)p->n_stream_rows,
-                       1 << c0, reinterpret_cast<int*>(q->store.as<char>() + DevArena::rounded((size_t)n_chunks * 8)),
-                       static_cast<int2v*>(q->chunks), q->rows);
+                       1 << c0, reinterpret_cast<int*>(q->store.as<char>() + DevArena::rounded((size_t)n_chunks * sizeof(RowChunk))),
+                       q->chunks, q->rows);
     EPP_HIP_TRY(hipGetLastError());
     EPP_HIP_TRY(hipStreamSynchronize(s));
     guard.q = nullptr;
@@ -447,7 +475,8 @@ int epp_launch_rows(const epp_path* p, const RowsPlan* plan, const float* in, fl
     a.limit = std::min((8 * kU) << log2p, a.huge);
     a.has_long = p->max_len > a.limit;
     a.chunk_blocks = plan ? plan->n_chunks : 0;
-    a.chunks = plan ? static_cast<const int2v*>(plan->chunks) : nullptr;
+    a.chunks = plan ? plan->chunks : nullptr;
+    a.huge_rows = plan ? plan->rows : nullptr;
     a.pieces = plan ? plan->pieces : nullptr;
     if (F >= 4) {
         switch (log2t) {
@@ -465,12 +494,6 @@ int epp_launch_rows(const epp_path* p, const RowsPlan* plan, const float* in, fl
         launch<2, 0>(a, s);
     } else {
         launch<1, 0>(a, s);
-    }
-    if (plan) {
-        int log2f = 0;
-        while ((1 << log2f) < F && log2f < 6) ++log2f;
-        hipLaunchKernelGGL(k_add_chunks, dim3((unsigned)((plan->n_huge + kBlock / 64 - 1) / (kBlock / 64))), dim3(kBlock), 0, s,
-                           plan->rows, plan->n_huge, plan->pieces, F, log2f, inner_rows, out);
     }
     EPP_HIP_TRY(hipGetLastError());
     return EPP_OK;
