@@ -249,6 +249,9 @@ template <int MT, int NT, bool VA, bool VB>
 __global__ __launch_bounds__(kBlock, MT * NT >= 16 ? 1 : 2) void k_weight_gradient_rows(
     const int32_t* __restrict__ ids, int64_t n_rows, int64_t rows_per_wave, const float* __restrict__ Y, int Fi,
     const float* __restrict__ G, int Fo, float* __restrict__ out) {
+    // columns of Y, hence rows of W', that are this workgroup's
+    const int m0 = blockIdx.y * 32 * MT, rows = std::min(Fi - m0, 32 * MT);
+    Y += m0;
     constexpr int D = 8, WAVES = kBlock / 64;  // pairs of rows in flight, wavefronts
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, p = lane & 31, half = lane >> 5;
     const int64_t first = ((int64_t)blockIdx.x * WAVES + wave) * rows_per_wave;
@@ -267,7 +270,7 @@ __global__ __launch_bounds__(kBlock, MT * NT >= 16 ? 1 : 2) void k_weight_gradie
     auto fetch = [&](int d, int v) {
         const int v0 = __builtin_amdgcn_readlane(v, 2 * d), v1 = __builtin_amdgcn_readlane(v, 2 * d + 1);
         const int64_t id = half ? v1 : v0;
-        load_share<MT, VA>(Y + id * Fi, Fi, p, a[d]);
+        load_share<MT, VA>(Y + id * Fi, rows, p, a[d]);
         load_share<NT, VB>(G + id * Fo, Fo, p, b[d]);
     };
     if (first < last) {
@@ -350,7 +353,7 @@ __global__ __launch_bounds__(kBlock, MT * NT >= 16 ? 1 : 2) void k_weight_gradie
             }
         }
     }
-    float* __restrict__ mine = out + (int64_t)blockIdx.x * Fi * Fo;
+    float* __restrict__ mine = out + ((int64_t)blockIdx.x * Fi + m0) * Fo;
 #pragma unroll
     for (int o = 0; o < kOwners; ++o) {
         if (w != o) continue;
@@ -359,7 +362,7 @@ __global__ __launch_bounds__(kBlock, MT * NT >= 16 ? 1 : 2) void k_weight_gradie
 #pragma unroll
         for (int e = 0; e < 16; ++e) {
             const int m = share_index<MT, VA>(i, 8 * (e / 4) + 4 * half + (e % 4));
-            if (m >= Fi) continue;
+            if (m >= rows) continue;
             float* __restrict__ row = mine + m * Fo;
             if constexpr (VB && kShare > 1) {
                 typedef float vec_t __attribute__((ext_vector_type(kShare), aligned(4)));
@@ -395,6 +398,9 @@ __global__ __launch_bounds__(kBlock, 2) void k_input_gradient_rows(const int32_t
                                                                    const float* __restrict__ G, int Fo,
                                                                    const float* __restrict__ W, int Fi,
                                                                    float* __restrict__ Yg) {
+    const int n0 = blockIdx.y * 32 * NT, cols = std::min(Fi - n0, 32 * NT);  // columns of Y' that are this workgroup's
+    W += (int64_t)n0 * Fo;
+    Yg += n0;
     __shared__ float4v Ws[KC * 2 * NT * 32];  // [chunk][half][n]: W[n, 8 chunk + 4 half ..]
     __shared__ float4v out_all[kBlock / 64][32 * 8];  // 32 rows x 32 columns of results, private to a wavefront
     const int lane = threadIdx.x & 63, p = lane & 31, half = lane >> 5;
@@ -408,7 +414,7 @@ __global__ __launch_bounds__(kBlock, 2) void k_input_gradient_rows(const int32_t
         for (int i = 0; i < kSteps; ++i) {
             const int blk = i * (kBlock / 64) + (threadIdx.x >> 6);
             const int k = 16 * (blk % (KC / 2)) + 4 * (lane & 3), n = 16 * (blk / (KC / 2)) + (lane >> 2);
-            const float* __restrict__ row = W + (int64_t)std::min(n, Fi - 1) * Fo;
+            const float* __restrict__ row = W + (int64_t)std::min(n, cols - 1) * Fo;
             if (Fo >= 4) {
                 w[i] = *reinterpret_cast<const vec_t*>(row + std::min(k, top));
             } else {
@@ -429,7 +435,7 @@ __global__ __launch_bounds__(kBlock, 2) void k_input_gradient_rows(const int32_t
                 if (c < 3 && late == 1) y = w[i][c + 1];
                 if (c < 2 && late == 2) y = w[i][c + 2];
                 if (c < 1 && late == 3) y = w[i][c + 3];
-                x[c] = n < Fi && k + c < Fo ? y : 0.0f;
+                x[c] = n < cols && k + c < Fo ? y : 0.0f;
             }
             if (KC * NT % (kBlock / 64) == 0 || n < 32 * NT) Ws[(k / 4) * (NT * 32) + n] = x;
         }
@@ -487,12 +493,12 @@ __global__ __launch_bounds__(kBlock, 2) void k_input_gradient_rows(const int32_t
                 const float4v y = ov[64 * q + lane];
                 if (tile * 32 + 8 * q + (lane >> 3) >= n_rows) continue;
                 float* __restrict__ o = Yg + (int64_t)vr[q] * Fi + n;
-                if (n + 4 <= Fi) {
+                if (n + 4 <= cols) {
                     *reinterpret_cast<vec_t*>(o) = y;
                 } else {
 #pragma unroll
                     for (int i = 0; i < 4; ++i)
-                        if (n + i < Fi) o[i] = y[i];
+                        if (n + i < cols) o[i] = y[i];
                 }
             }
         }
@@ -623,6 +629,18 @@ int resident(int kc, int nt) {
     return nt == 4 ? 3 : 4;
 }
 
+// Blocks of 32 columns of Y' (nt in all) that a workgroup of k_input_gradient_rows takes, 128 rows a round: fewer where the chip would
+// not be full.  A wavefront's products then follow each other in a chain a half or a quarter as long, and a workgroup brings that much
+// less of W into LDS (us, 1 / 2 / 4 blocks; 128 x 128, 11 rows 5.5 / 8.1 / 13.2, 2,000 6.3 / 9.0 / 14.5, 8,000 7.3 / 9.5 / 14.9, 12,000
+// 11.4 / 10.2 / 15.2, 16,000 12.2 / 11.0 / 15.8, 24,000 16.3 / 17.4 / 17.8, 32,000 23.5 / 18.4 / 18.6; 64 x 64, 2,000 4.2 / 5.5, 16,000 4.7 / 6.1,
+// 24,000 6.9 / 6.3).  Up to 16 floats a row leave a wavefront little to do but wait (128 x 16, 24,000 rows 5.3 / 5.7 / 5.8, 32,000 6.7 / 6.5 / 6.5).
+int columns_at_once(int64_t tiles, int kc, int nt) {
+    const int64_t blocks = (tiles + 3) / 4, most = kc <= 2 ? 768 : 256;
+    int per = 1;
+    while (per < nt && blocks * (nt / per) > most) per *= 2;
+    return per;
+}
+
 // How the rows are cut into partial sums (at most `max_chunks` of them).
 struct Chunks {
     int64_t per;    // rows per chunk; narrow widths: rows per wavefront
@@ -662,11 +680,22 @@ Chunks chunking(int64_t n_rows, int Fi, int Fo, int64_t max_chunks) {
     return c;
 }
 
+// Blocks of 32 columns of Y (mt in all) that a workgroup of k_weight_gradient_rows takes, for the same reason, while a wavefront has few
+// rows (us, 1 / 2 / 4 blocks, partial sums added; 128 x 128, 11 rows 4.6 / 6.0 / 10.5, 2,000 8.7 / 10.2 / 14.7, 8,000 15.4 / 15.8 / 19.9, 12,000 17.1 /
+// 18.0 / 20.2, 16,000 20.2 / 18.4 / 22.9; 64 x 128, 16,000 14.4 / 14.8, 50,000 21.9 / 19.4; 64 x 64, 2,000 6.5 / 7.4, 8,000 9.0 / 9.8, 12,000 9.4 /
+// 9.2; 128 x 16, 4,000 6.9 / 7.2 / 7.8, 12,000 8.7 / 8.8 / 8.2).
+int rows_at_once(const Chunks& c, int mt, int nt) {
+    const int64_t most = nt == 4 ? 768 : 256;
+    int at_once = c.per <= 16 ? 1 : mt;
+    while (at_once < mt && c.count * (mt / at_once) > most) at_once *= 2;
+    return at_once;
+}
+
 template <int MT, int NT, bool VA, bool VB>
 void launch_rows_wg(const Chunks& c, const int32_t* ids, int64_t n_rows, const float* Y, int Fi, const float* G, int Fo,
                     float* out, hipStream_t s) {
-    hipLaunchKernelGGL((k_weight_gradient_rows<MT, NT, VA, VB>), dim3((unsigned)c.count), dim3(256), 0, s, ids, n_rows,
-                       c.per, Y, Fi, G, Fo, out);
+    hipLaunchKernelGGL((k_weight_gradient_rows<MT, NT, VA, VB>), dim3((unsigned)c.count, (unsigned)((Fi + 32 * MT - 1) / (32 * MT))),
+                       dim3(256), 0, s, ids, n_rows, c.per, Y, Fi, G, Fo, out);
 }
 template <int MT, bool VA>
 void launch_rows_wg_n(const Chunks& c, const int32_t* ids, int64_t n_rows, const float* Y, int Fi, const float* G, int Fo,
@@ -704,7 +733,7 @@ int weight_gradient(const epp_paths* paths, int k, const float* Y, int F_in, con
         epp_launch_weight_gradient_split(chunks, 4 * per, ids, n_rows, Y, F_in, grad_X, F_out, part, s);
     } else if (chunks > 0 && narrow(F_in, F_out)) {
         float* out = chunks == 1 ? grad_W : part;
-        const int mt = blocks_of(F_in);
+        const int mt = rows_at_once(c, blocks_of(F_in), blocks_of(F_out));
         if (mt == 1) launch_rows_wg_n<1, false>(c, ids, n_rows, Y, F_in, grad_X, F_out, out, s);
         else if (mt == 2 && F_in % 2 == 0) launch_rows_wg_n<2, true>(c, ids, n_rows, Y, F_in, grad_X, F_out, out, s);
         else if (mt == 2) launch_rows_wg_n<2, false>(c, ids, n_rows, Y, F_in, grad_X, F_out, out, s);
@@ -846,15 +875,18 @@ extern "C" int epp_input_gradient(epp_paths_t* paths, int k, const float* grad_X
     if (narrow(F_in, F_out) && !(nt == 1 && F_out > 48 && n_rows >= 50000)) {
         // persistent workgroups, as many as the chip holds at once
         const int64_t tiles = (n_rows + 31) / 32;
+        // few rows: the columns in pieces of `per` blocks, a workgroup each
+        const int per = columns_at_once(tiles, kc, nt);
+        const unsigned pieces = (unsigned)((F_in + 32 * per - 1) / (32 * per));
         dim3 grid;
-        auto blocks = [&](int at_once) { grid = dim3((unsigned)std::min<int64_t>((tiles + 3) / 4, at_once)); };
+        auto blocks = [&](int at_once) { grid = dim3((unsigned)std::min<int64_t>((tiles + 3) / 4, at_once), pieces); };
 #define EPP_LAUNCH_IGR(KC)                                                                                           \
     do {                                                                                                             \
-        blocks(256 * resident(KC, nt));                                                                              \
-        if (nt == 1)                                                                                                 \
+        blocks(256 * resident(KC, per));                                                                             \
+        if (per == 1)                                                                                                \
             hipLaunchKernelGGL((k_input_gradient_rows<KC, 1>), grid, dim3(kBlock), 0, s, ids, n_rows, grad_X, F_out, \
                                W, F_in, grad_Y);                                                                     \
-        else if (nt == 2)                                                                                            \
+        else if (per == 2)                                                                                           \
             hipLaunchKernelGGL((k_input_gradient_rows<KC, 2>), grid, dim3(kBlock), 0, s, ids, n_rows, grad_X, F_out, \
                                W, F_in, grad_Y);                                                                     \
         else                                                                                                         \
