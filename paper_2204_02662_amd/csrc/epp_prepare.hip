@@ -83,12 +83,16 @@ __global__ __launch_bounds__(kBlock) void k_mark_training(const int32_t* __restr
 // kSetVertices vertices and kSetIds training ids (marking, counting, scanning and listing are four
 // launches of 4.5 us otherwise, whatever they process).
 constexpr int kSetVertices = 524288, kSetIds = 65536;
+constexpr size_t kSetClear = 262144;  // bytes
+//
+// It also clears the results of the kernels to come (`clear`; a memset is a launch of 5 us with the gap before it).
 __global__ __launch_bounds__(1024) void k_training_set(const int32_t* __restrict__ ids, int n_ids, int n,
                                                        unsigned long long* __restrict__ bitmap, int32_t* __restrict__ ids_out,
-                                                       long long* __restrict__ count, int* __restrict__ err) {
+                                                       long long* count, int* err, ulonglong2* clear, int clear_pairs) {
     __shared__ unsigned long long bits[kSetVertices / 64];
     __shared__ int wave_sum[16];
     const int tid = threadIdx.x, wave = tid >> 6, lane = lane_id(), n_words = (n + 63) >> 6;
+    for (int i = tid; i < clear_pairs; i += 1024) clear[i] = make_ulonglong2(0ull, 0ull);
     for (int w = tid; w < n_words; w += 1024) bits[w] = 0ull;
     __syncthreads();
     unsigned int* bits32 = reinterpret_cast<unsigned int*>(bits);
@@ -175,14 +179,17 @@ __device__ __forceinline__ void store_tile(const MaskArgs& a, int64_t tile, bool
     if (a.count && lane == 0) a.tile_count[tile] = run;
 }
 
-template <int WORDS>
-__global__ __launch_bounds__(1024) void k_edge_mask(MaskArgs a) {
+//
+// THREADS: 1,024, or 256 where the tiles are few and sixteen wavefronts would share one of a few CUs (0.5 M entries 9.3 -> 5.5 us, 4.2 M
+// 10.0 -> 9.6).
+template <int WORDS, int THREADS>
+__global__ __launch_bounds__(THREADS) void k_edge_mask(MaskArgs a) {
     __shared__ __attribute__((aligned(16))) unsigned int bits[WORDS + 4];
     const int wave = threadIdx.x >> 6, lane = lane_id();
     {
         const int words = (a.n_ids + 31) >> 5, total = ((a.n + 63) >> 6) * 2 - (a.first_id >> 5);
         const unsigned int* __restrict__ src = a.bitmap + (a.first_id >> 5);
-        for (int i = 4 * (int)threadIdx.x; i < words; i += 4 * 1024) {
+        for (int i = 4 * (int)threadIdx.x; i < words; i += 4 * THREADS) {
             uint4 x = make_uint4(0, 0, 0, 0);
             if (i + 4 <= total) {
                 x = *reinterpret_cast<const uint4*>(src + i);
@@ -196,8 +203,8 @@ __global__ __launch_bounds__(1024) void k_edge_mask(MaskArgs a) {
         if (threadIdx.x == 0) bits[WORDS] = 0u;  // what every id outside the window looks up
         __syncthreads();
     }
-    const int64_t step = (int64_t)gridDim.x * 16;
-    for (int64_t tile = (int64_t)blockIdx.x * 16 + wave; tile < a.n_tiles; tile += step) {
+    const int64_t step = (int64_t)gridDim.x * (THREADS / 64);
+    for (int64_t tile = (int64_t)blockIdx.x * (THREADS / 64) + wave; tile < a.n_tiles; tile += step) {
         const int64_t seg0 = tile * kSegsPerTile;
         const bool mine = lane < kSegsPerTile && seg0 + lane < a.n_seg;
         const unsigned long long known = (a.known && mine) ? a.known[seg0 + lane] : 0ull;
@@ -478,6 +485,28 @@ struct Members {
     }
 };
 
+// Copies of a path's statistics, which the workgroups are dealt to, so that no word is added to by more than 64 of them: atomics at one
+// address follow each other at 20 to 40 ns.  (k_rows_compact, one copy and 512 workgroups at most
+// -> 32 and 2,048: 89,000 vertices 8.6 -> 5.4 us, 1.1 M 16.0 -> 8.8.)
+// A copy: EPP_NCLASS counts, then the longest row.
+constexpr int kStatWords = EPP_NCLASS + 1;
+template <int COPIES>
+__device__ __forceinline__ unsigned long long* my_stats(unsigned long long* stats) { return stats + (blockIdx.x % COPIES) * kStatWords; }
+// The sum of the copies' word i; of the last word the largest.
+template <int COPIES>
+__host__ __device__ inline unsigned long long stat_word(const unsigned long long* __restrict__ stats, int i) {
+    unsigned long long x = 0ull;
+#pragma unroll
+    for (int c = 0; c < COPIES; ++c) {
+        const unsigned long long y = stats[c * kStatWords + i];
+        x = i < EPP_NCLASS ? x + y : std::max(x, y);
+    }
+    return x;
+}
+constexpr unsigned kRowBlocks = 2048;  // of k_rows_compact
+constexpr int kRowCopies = 32;
+constexpr int kImportCopies = 8;  // (they all go to the host)
+
 // Where the kept entries of a level go: mask, and the counts before a tile and inside it.
 struct Kept {
     const unsigned long long* mask;
@@ -500,6 +529,8 @@ struct Kept {
 //
 // TWO: a second level's entries, without marks, from the same read of the columns and values.
 //
+// The last one of a construction hands the levels' statistics to the host (pinned memory; a copy behind it is a launch of 6 us).
+//
 // Runs at the rate of a copy: 140 M entries in 0.41 ms, with 19 M of another level 0.46 ms; those by themselves took 0.23 ms, as
 // nearly every line of the arrays holds some of them.  (What concerns a segment is fetched by one lane
 // and read from there as a scalar; vector loads of it cost 0.45 ms more.)
@@ -513,7 +544,13 @@ struct Extracted {
 template <bool TWO>
 __global__ __launch_bounds__(kBlock) void k_edge_extract(const int32_t* __restrict__ col, const float* __restrict__ val,
                                                          int64_t n_seg, Extracted a, Kept inner, int* __restrict__ inner_pos,
-                                                         Extracted b, const int* __restrict__ tile_row, int n) {
+                                                         Extracted b, const int* __restrict__ tile_row, int n,
+                                                         const unsigned long long* __restrict__ stats, int levels,
+                                                         unsigned long long* __restrict__ host) {
+    if (blockIdx.x == 0) {  // (none where `levels` is 0)
+        for (int i = threadIdx.x; i < levels * kStatWords; i += kBlock)
+            host[i] = stat_word<kRowCopies>(stats + i / kStatWords * kRowCopies * kStatWords, i % kStatWords);
+    }
     constexpr int kPerWave = kSegsPerTile / 4;
     __shared__ unsigned int row_end[TWO ? 2 : 1][kSegsPerTile * 2];  // one bit per kept entry of the tile
     if (threadIdx.x < kSegsPerTile * 2) {
@@ -675,9 +712,7 @@ __device__ __forceinline__ void flush_lengths(const int* __restrict__ h, int* __
     if (threadIdx.x == 0 && *mx) atomicMax(max_len, *mx);
 }
 constexpr unsigned kStatBlocks = 512;
-
-// Ascending ids of N^{k+1}, compact row pointer and row-length statistics (EPP_NCLASS counts, then
-// the longest row); a workgroup takes 256 vertices at a time.
+// Ascending ids of N^{k+1}, compact row pointer and row-length statistics; a workgroup takes 256 vertices at a time.
 __global__ __launch_bounds__(kBlock) void k_rows_compact(const unsigned long long* __restrict__ bitmap, int64_t n,
                                                          const int* __restrict__ row_base, const int* __restrict__ newptr,
                                                          int32_t* __restrict__ ids, int32_t* __restrict__ ptr_out,
@@ -707,6 +742,7 @@ __global__ __launch_bounds__(kBlock) void k_rows_compact(const unsigned long lon
             add_length(h, len);
         }
     }
+    stats = my_stats<kRowCopies>(stats);
     flush_lengths(h, &mx, my_max, stats, reinterpret_cast<int*>(stats + EPP_NCLASS));
     if (blockIdx.x == 0 && threadIdx.x == 0) ptr_out[n_set] = total_nnz;
 }
@@ -982,10 +1018,12 @@ void launch_edge_mask(const epp_csr_t* g, int64_t n_seg, unsigned n_tiles, const
         a.check = check && w == 0;
         a.count = w == passes - 1;
         if (w > 0) a.known = mask;
-        if (window == kSmall * 32)
-            hipLaunchKernelGGL((k_edge_mask<kSmall>), dim3(std::min(grid_for(n_tiles, 16), 512u)), dim3(1024), 0, s, a);
+        if (window == kSmall * 32 && n_tiles <= 2048)
+            hipLaunchKernelGGL((k_edge_mask<kSmall, 256>), dim3(grid_for(n_tiles, 4)), dim3(256), 0, s, a);
+        else if (window == kSmall * 32)
+            hipLaunchKernelGGL((k_edge_mask<kSmall, 1024>), dim3(std::min(grid_for(n_tiles, 16), 512u)), dim3(1024), 0, s, a);
         else
-            hipLaunchKernelGGL((k_edge_mask<kLarge>), dim3(std::min(grid_for(n_tiles, 16), 256u)), dim3(1024), 0, s, a);
+            hipLaunchKernelGGL((k_edge_mask<kLarge, 1024>), dim3(std::min(grid_for(n_tiles, 16), 256u)), dim3(1024), 0, s, a);
     }
 }
 
@@ -1013,13 +1051,23 @@ struct ImportArgs {
     unsigned row_blocks;
 };
 constexpr int kImportTile = 2048;
-__global__ __launch_bounds__(kBlock) void k_import_path(ImportArgs a) {
+// The workgroups of several paths in one launch, each path's behind those of the one before.
+constexpr int kImportPaths = 4;
+struct ImportPaths {
+    ImportArgs path[kImportPaths];
+    unsigned end[kImportPaths];
+};
+__global__ __launch_bounds__(kBlock) void k_import_path(ImportPaths all) {
+    unsigned block = blockIdx.x;
+    int at = 0;
+    while (at < kImportPaths - 1 && blockIdx.x >= all.end[at]) block = blockIdx.x - all.end[at++];
+    const ImportArgs& a = all.path[at];
     __shared__ int h[kHists * EPP_NCLASS];
     __shared__ int mx;
     __shared__ unsigned int row_end[kImportTile / 32];
     const int lane = lane_id();
-    if (blockIdx.x >= a.row_blocks) {
-        const int64_t e0 = (int64_t)(blockIdx.x - a.row_blocks) * kImportTile;
+    if (block >= a.row_blocks) {
+        const int64_t e0 = (int64_t)(block - a.row_blocks) * kImportTile;
         constexpr int kPer = kImportTile / kBlock;
         int2 x[kPer];
 #pragma unroll
@@ -1060,7 +1108,7 @@ __global__ __launch_bounds__(kBlock) void k_import_path(ImportArgs a) {
     int my_max = 0, bad = 0;
     const int64_t span = (int64_t)a.row_blocks * kBlock;
     // (one index past the rows, for the end of the pointer; whole wavefronts enter every iteration)
-    for (int64_t base = (int64_t)blockIdx.x * kBlock + (threadIdx.x & ~63); base <= a.n_rows; base += span) {
+    for (int64_t base = (int64_t)block * kBlock + (threadIdx.x & ~63); base <= a.n_rows; base += span) {
         const int64_t r = base + lane;
         const bool row = r < a.n_rows;
         const int p = r <= a.n_rows ? a.rowptr[r] : 0;
@@ -1090,7 +1138,8 @@ __global__ __launch_bounds__(kBlock) void k_import_path(ImportArgs a) {
         if (row && len > 0) add_length(h, len);
     }
     if (bad) atomicOr(a.err, bad);
-    flush_lengths(h, &mx, my_max, a.stats, reinterpret_cast<int*>(a.stats + EPP_NCLASS));
+    unsigned long long* const stats = my_stats<kImportCopies>(a.stats);
+    flush_lengths(h, &mx, my_max, stats, reinterpret_cast<int*>(stats + EPP_NCLASS));
 }
 
 // *outside = 1 if an entry's column is not in the bitmap.  Bound by the lookups, which come from L2 (250 G/s), eight in
@@ -1111,24 +1160,30 @@ __global__ __launch_bounds__(kBlock) void k_columns_inside(const int2* __restric
     if (!(in & 1u)) *outside = 1;  // (every writer stores the same value)
 }
 
-// N^0 as a bitmap (cleared by the caller) and its ascending ids; *count receives their number.
-void launch_training_set(const int32_t* train_ids, int64_t n_train, int64_t n, const DevBuf& bitmap, void* ids_out,
-                         int* tile_cnt, int* tile_base, int* scan_tmp, long long* count, int* err, hipStream_t s) {
-    if (n_train == 0) return;
-    if (n > 0 && n <= kSetVertices && n_train <= kSetIds) {
+// N^0 as a bitmap and its ascending ids; *count receives their number.  `clear`, `clear_bytes`: what is cleared before (256 bytes
+// or a multiple, `count` and `err` among them, not the bitmap).
+int launch_training_set(const int32_t* train_ids, int64_t n_train, int64_t n, const DevBuf& bitmap, void* ids_out,
+                        int* tile_cnt, int* tile_base, int* scan_tmp, long long* count, int* err, void* clear, size_t clear_bytes,
+                        hipStream_t s) {
+    if (n_train > 0 && n > 0 && n <= kSetVertices && n_train <= kSetIds && clear_bytes <= kSetClear) {
         hipLaunchKernelGGL(k_training_set, dim3(1), dim3(1024), 0, s, train_ids, (int)n_train, (int)n,
-                           bitmap.as<unsigned long long>(), static_cast<int32_t*>(ids_out), count, err);
-        return;
+                           bitmap.as<unsigned long long>(), static_cast<int32_t*>(ids_out), count, err, static_cast<ulonglong2*>(clear),
+                           (int)(clear_bytes / sizeof(ulonglong2)));
+        return EPP_OK;
     }
+    EPP_HIP_TRY(hipMemsetAsync(clear, 0, clear_bytes, s));
+    EPP_HIP_TRY(hipMemsetAsync(bitmap.p, 0, bitmap.bytes, s));
+    if (n_train == 0) return EPP_OK;
     const int64_t n_words = (n + 63) / 64;
     const unsigned tiles = grid_for(n_words, kWordsPerTile);
     hipLaunchKernelGGL(k_mark_training, dim3(grid_for(n_train, kBlock)), dim3(kBlock), 0, s, train_ids, n_train, n,
                        bitmap.as<unsigned int>(), err);
-    if (n == 0) return;
+    if (n == 0) return EPP_OK;
     hipLaunchKernelGGL(k_bitmap_count, dim3(tiles), dim3(kBlock), 0, s, bitmap.as<unsigned long long>(), n_words, tile_cnt);
     scan_counts(tile_cnt, tile_base, tiles, count, scan_tmp, s);
     hipLaunchKernelGGL(k_bitmap_compact, dim3(tiles), dim3(kBlock), 0, s, bitmap.as<unsigned long long>(), n_words, tile_base,
                        (const int*)nullptr, static_cast<int32_t*>(ids_out), (int32_t*)nullptr, (int64_t)0, 0);
+    return EPP_OK;
 }
 
 // Message and code for the error bits raised by the input checks (bit 0 row pointer, bit 1 ids).
@@ -1283,7 +1338,6 @@ extern "C" int epp_prepare(const epp_csr_t* g, const int32_t* train_ids, int64_t
     const unsigned row_tiles = grid_for(n, kBlock);
 
     // pinned words: the numbers of the level being built, then every level's statistics
-    constexpr int kStatWords = EPP_NCLASS + 1;
     PinnedWords hs;
     EPP_TRY(hs.get(kLevelWords + (size_t)L * kStatWords));
     epp_paths* P = new epp_paths();
@@ -1309,7 +1363,6 @@ extern "C" int epp_prepare(const epp_csr_t* g, const int32_t* train_ids, int64_t
     EPP_TRY(P->store.alloc((size_t)(L + 1) * DevArena::rounded(bm_bytes) + DevArena::rounded(set0_bytes), al));
     for (int k = 0; k <= L; ++k) P->bitmaps[k].view(P->store.as<char>() + (size_t)k * DevArena::rounded(bm_bytes), bm_bytes);
     void* set0 = P->store.as<char>() + (size_t)(L + 1) * DevArena::rounded(bm_bytes);
-    EPP_HIP_TRY(hipMemsetAsync(P->bitmaps[0].p, 0, bm_bytes, s));  // (the others are written whole)
 
     // all temporaries of the construction come from one allocation
     // (keep-mask, its counts and the members before every 256 vertices three times: the entries of a level are extracted
@@ -1319,7 +1372,7 @@ extern "C" int epp_prepare(const epp_csr_t* g, const int32_t* train_ids, int64_t
     const size_t cnt_bytes = (size_t)std::max(std::max(edge_tiles, word_tiles), 1u) * 4;
     const size_t row_bytes = (size_t)std::max(row_tiles, 1u) * 4;
     const size_t tmp_bytes = scan_tmp_bytes(std::max<int64_t>(edge_tiles, row_tiles));
-    const size_t level_bytes = (size_t)L * (kLevelWords + kStatWords) * 8;
+    const size_t level_bytes = DevArena::rounded((size_t)L * (kLevelWords + kRowCopies * kStatWords) * 8);
     DevArena arena;
     EPP_TRY(arena.reserve(kAlive * (DevArena::rounded((size_t)n_seg * 8) + DevArena::rounded((size_t)n_seg * 2) +
                                     DevArena::rounded(cnt_bytes) + DevArena::rounded(row_bytes)) +
@@ -1340,11 +1393,10 @@ extern "C" int epp_prepare(const epp_csr_t* g, const int32_t* train_ids, int64_t
     arena.take(&levels, level_bytes);
     long long* const d_levels = levels.as<long long>();
     unsigned long long* const d_stats = reinterpret_cast<unsigned long long*>(d_levels + (size_t)L * kLevelWords);
-    EPP_HIP_TRY(hipMemsetAsync(levels.p, 0, level_bytes, s));
 
     // N^0 = V_t (Property 1) and its ascending ids (the other sets are the row ids of the paths)
-    launch_training_set(train_ids, n_train, n, P->bitmaps[0], set0, tile_cnt.as<int>(), tile_base[0].as<int>(),
-                        scan_tmp.as<int>(), d_levels + 5, reinterpret_cast<int*>(d_levels + 2), s);
+    EPP_TRY(launch_training_set(train_ids, n_train, n, P->bitmaps[0], set0, tile_cnt.as<int>(), tile_base[0].as<int>(),
+                                scan_tmp.as<int>(), d_levels + 5, reinterpret_cast<int*>(d_levels + 2), levels.p, level_bytes, s));
     EPP_HIP_TRY(hipGetLastError());
 
     // Shared entries: the path of a level runs on the arrays of the next level's path if nearly
@@ -1366,7 +1418,8 @@ extern "C" int epp_prepare(const epp_csr_t* g, const int32_t* train_ids, int64_t
         return Extracted{kept_of(slot), Members{P->bitmaps[w.level + 1].as<unsigned long long>(), row_base[slot].as<int>()},
                          w.p->rowptr.as<int>(), (int)w.p->n_rows, (int)w.p->nnz, w.p->cv.as<int2>()};
     };
-    auto extract = [&](epp_path* q, int level, bool marks_inner) -> int {
+    unsigned long long* const h_stats = reinterpret_cast<unsigned long long*>(hs.p) + kLevelWords;
+    auto extract = [&](epp_path* q, int level, bool marks_inner, bool last) -> int {
         // the entries in an allocation of their own (it can be given back once every prepared width
         // runs on a reconstructed copy)
         EPP_TRY(q->cv.alloc((size_t)q->nnz * sizeof(int2), al));
@@ -1377,10 +1430,10 @@ extern "C" int epp_prepare(const epp_csr_t* g, const int32_t* train_ids, int64_t
             const Kept inner = marks_inner ? kept_of((level + kAlive - 1) % kAlive) : Kept{nullptr, nullptr, nullptr};
             if (due.p)
                 hipLaunchKernelGGL(k_edge_extract<true>, dim3(edge_tiles), dim3(kBlock), 0, s, g->col, g->val, n_seg, a, inner,
-                                   q->inner_pos.as<int>(), extracted(due), tile_row.as<int>(), (int)n);
+                                   q->inner_pos.as<int>(), extracted(due), tile_row.as<int>(), (int)n, d_stats, last ? L : 0, h_stats);
             else
                 hipLaunchKernelGGL(k_edge_extract<false>, dim3(edge_tiles), dim3(kBlock), 0, s, g->col, g->val, n_seg, a, inner,
-                                   q->inner_pos.as<int>(), a, tile_row.as<int>(), (int)n);
+                                   q->inner_pos.as<int>(), a, tile_row.as<int>(), (int)n, d_stats, last ? L : 0, h_stats);
         }
         due = Waiting{};
         EPP_HIP_TRY(hipGetLastError());
@@ -1445,10 +1498,10 @@ extern "C" int epp_prepare(const epp_csr_t* g, const int32_t* train_ids, int64_t
         p->row_ids.view(base, ids_bytes);
         p->rowptr.view(base + DevArena::rounded(ids_bytes), ptr_bytes);
         if (n > 0) {
-            hipLaunchKernelGGL(k_rows_compact, dim3(std::min(row_tiles, kStatBlocks)), dim3(kBlock), 0, s,
+            hipLaunchKernelGGL(k_rows_compact, dim3(std::min(row_tiles, kRowBlocks)), dim3(kBlock), 0, s,
                                P->bitmaps[k + 1].as<unsigned long long>(), n, row_base[slot].as<int>(), newptr.as<int>(),
                                p->row_ids.as<int32_t>(), p->rowptr.as<int32_t>(), (int64_t)R, (int)kept,
-                               d_stats + (size_t)k * kStatWords);
+                               d_stats + (size_t)k * kRowCopies * kStatWords);
             EPP_HIP_TRY(hipGetLastError());
         } else {
             EPP_HIP_TRY(hipMemsetAsync(p->rowptr.p, 0, sizeof(int32_t), s));
@@ -1460,11 +1513,11 @@ extern "C" int epp_prepare(const epp_csr_t* g, const int32_t* train_ids, int64_t
             p->has_inner = true;
             q->outer = p;
             q->inner_rows = P->bitmaps[k].as<unsigned int>();  // its rows are N^k
-            EPP_TRY(extract(p, k, true));
+            EPP_TRY(extract(p, k, true, k + 1 == L || fixed_point));
             pending.p = nullptr;
         } else {
             // (at most one is due: the next level extracts this one's entries, or its own that this one shares)
-            if (q && due.p) EPP_TRY(extract(q, pending.level, false));
+            if (q && due.p) EPP_TRY(extract(q, pending.level, false, false));
             else if (q) due = pending;
             pending = Waiting{p, k};
         }
@@ -1481,11 +1534,11 @@ extern "C" int epp_prepare(const epp_csr_t* g, const int32_t* train_ids, int64_t
             break;
         }
     }
-    if (pending.p) EPP_TRY(extract(pending.p, pending.level, false));
-    EPP_HIP_TRY(hipMemcpyAsync(hs.p + kLevelWords, d_stats, (size_t)L * kStatWords * 8, hipMemcpyDeviceToHost, s));
+    if (pending.p) EPP_TRY(extract(pending.p, pending.level, false, true));
+    if (!edge_tiles) std::memset(h_stats, 0, (size_t)L * kStatWords * 8);  // (no entry, no row)
     EPP_HIP_TRY(hipStreamSynchronize(s));
     for (size_t k = 0; k < built.size(); ++k)
-        epp_path_set_stats(built[k], reinterpret_cast<const unsigned long long*>(hs.p) + kLevelWords + k * kStatWords);
+        epp_path_set_stats(built[k], h_stats + k * kStatWords);
     guard.p = nullptr;
     *out = P;
     return EPP_OK;
@@ -1589,9 +1642,9 @@ extern "C" int epp_paths_import(int64_t n, int L, const int32_t* train_ids, int6
         EPP_TRY(epp_static_scratch(&unused));
     }
     const int64_t n_words = (n + 63) / 64;
-    constexpr int kStatWords = EPP_NCLASS + 1;
     // words: [0] errors, [1] |N^0|, then every layer's statistics
-    const size_t res_words = 2 + (size_t)L * kStatWords;
+    constexpr size_t kLayerWords = kImportCopies * kStatWords;
+    const size_t res_words = 2 + (size_t)L * kLayerWords;
     PinnedWords hs;
     EPP_TRY(hs.get(res_words));
     epp_paths* P = new epp_paths();
@@ -1616,7 +1669,6 @@ extern "C" int epp_paths_import(int64_t n, int L, const int32_t* train_ids, int6
     const size_t tiles = std::max<size_t>(grid_for(n_words, kWordsPerTile), 1);
     const size_t clear_bytes = (size_t)(L + 1) * DevArena::rounded(bm_bytes) + DevArena::rounded(res_words * 8);
     EPP_TRY(P->store.alloc(clear_bytes + DevArena::rounded(set0_bytes), al));
-    EPP_HIP_TRY(hipMemsetAsync(P->store.p, 0, clear_bytes, s));
     for (int k = 0; k <= L; ++k) P->bitmaps[k].view(P->store.as<char>() + (size_t)k * DevArena::rounded(bm_bytes), bm_bytes);
     long long* d_res = reinterpret_cast<long long*>(P->store.as<char>() + (size_t)(L + 1) * DevArena::rounded(bm_bytes));
     void* set0 = P->store.as<char>() + clear_bytes;
@@ -1627,8 +1679,12 @@ extern "C" int epp_paths_import(int64_t n, int L, const int32_t* train_ids, int6
     arena.take(&tile_cnt, tiles * 4);
     arena.take(&tile_base, tiles * 4);
     arena.take(&scan_tmp, scan_tmp_bytes(tiles));
-    launch_training_set(train_ids, n_train, n, P->bitmaps[0], set0, tile_cnt.as<int>(), tile_base.as<int>(),
-                        scan_tmp.as<int>(), d_res + 1, d_err, s);
+    EPP_TRY(launch_training_set(train_ids, n_train, n, P->bitmaps[0], set0, tile_cnt.as<int>(), tile_base.as<int>(), scan_tmp.as<int>(),
+                                d_res + 1, d_err, P->store.as<char>() + DevArena::rounded(bm_bytes),
+                                clear_bytes - DevArena::rounded(bm_bytes), s));
+    ImportPaths all;
+    int held = 0;
+    unsigned blocks = 0;
     for (int l = L - 1; l >= 0; --l) {
         const epp_path_arrays_t& a = layers[l];
         const int k = L - l - 1;
@@ -1649,7 +1705,7 @@ extern "C" int epp_paths_import(int64_t n, int L, const int32_t* train_ids, int6
         p->row_ids.view(p->store.p, ids_bytes);
         p->rowptr.view(p->store.as<char>() + DevArena::rounded(ids_bytes), ptr_bytes);
         EPP_TRY(p->cv.alloc((size_t)a.nnz * sizeof(int2), al));
-        ImportArgs q;
+        ImportArgs& q = all.path[held];
         q.row_ids = a.row_ids;
         q.rowptr = a.rowptr;
         q.col = a.col;
@@ -1661,11 +1717,17 @@ extern "C" int epp_paths_import(int64_t n, int L, const int32_t* train_ids, int6
         q.ptr_out = p->rowptr.as<int32_t>();
         q.cv = p->cv.as<int2>();
         q.bitmap32 = P->bitmaps[k + 1].as<unsigned int>();
-        q.stats = reinterpret_cast<unsigned long long*>(d_res + 2 + (size_t)l * kStatWords);
+        q.stats = reinterpret_cast<unsigned long long*>(d_res + 2 + (size_t)l * kLayerWords);
         q.err = d_err;
         q.row_blocks = std::min(grid_for(a.n_rows + 1, kBlock), kStatBlocks);
-        hipLaunchKernelGGL(k_import_path, dim3(q.row_blocks + grid_for(a.nnz, kImportTile)), dim3(kBlock), 0, s, q);
+        blocks += q.row_blocks + grid_for(a.nnz, kImportTile);
+        all.end[held++] = blocks;
+        if (l > 0 && held < kImportPaths) continue;
+        for (int i = held; i < kImportPaths; ++i) all.end[i] = blocks;
+        hipLaunchKernelGGL(k_import_path, dim3(blocks), dim3(kBlock), 0, s, all);
         EPP_HIP_TRY(hipGetLastError());
+        held = 0;
+        blocks = 0;
     }
     EPP_HIP_TRY(hipMemcpyAsync(hs.p, d_res, res_words * 8, hipMemcpyDeviceToHost, s));
     EPP_HIP_TRY(hipStreamSynchronize(s));
@@ -1676,7 +1738,10 @@ extern "C" int epp_paths_import(int64_t n, int L, const int32_t* train_ids, int6
     P->set0_ids.view(set0, (size_t)hs.p[1] * 4);
     for (int l = 0; l < L; ++l) {
         P->path[l]->n_src = P->set_size[L - l - 1];
-        epp_path_set_stats(P->path[l], reinterpret_cast<const unsigned long long*>(hs.p) + 2 + (size_t)l * kStatWords);
+        const unsigned long long* const copies = reinterpret_cast<const unsigned long long*>(hs.p) + 2 + (size_t)l * kLayerWords;
+        unsigned long long stats[kStatWords];
+        for (int i = 0; i < kStatWords; ++i) stats[i] = stat_word<kImportCopies>(copies, i);
+        epp_path_set_stats(P->path[l], stats);
     }
     guard.p = nullptr;
     *out = P;
