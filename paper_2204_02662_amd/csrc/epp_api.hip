@@ -210,6 +210,7 @@ extern "C" int epp_path_info(const epp_path_t* p, epp_path_info_t* info) {
     for (int c = 0; c < EPP_NCLASS; ++c) info->len_hist[c] = p->len_hist[c];
     size_t bytes = p->row_ids.bytes + p->rowptr.bytes + p->cv.bytes + p->full_rowptr.bytes + p->empty_rows.bytes;
     bytes += p->zero_block.bytes + p->inner_pos.bytes;
+    if (p->long_rows.rows) bytes += (size_t)p->long_rows.first_place(EPP_NCLASS) * sizeof(LongRow);
     for (const Schedule* s : p->scheds) bytes += s->bytes();
     for (const TilePlan* t : p->tile_plans) bytes += t->store.bytes;
     for (const auto& w : p->widths)

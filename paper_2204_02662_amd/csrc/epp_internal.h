@@ -235,16 +235,54 @@ struct Partition {
     }
 };
 
-// What the row kernel (epp_rows.hip) needs to know of the rows that one workgroup should not take alone:
-// they are cut into chunks, whose sums the last workgroup of the row's adds.
-struct HugeRow { int v, first, count; unsigned done; };  // vertex, its first chunk and their number; 0, during a launch how many it has summed
-struct RowChunk { int begin, end, row, unused; };        // entries; which of the cut rows
+// A row that the row kernel (epp_rows.hip) may cut into chunks: vertex, entries; 0, during a launch how many chunks it has summed.
+struct LongRow { int v, begin, end; unsigned done; };
+// The rows of a path of `nnz` entries with more than 2^log2 of them, those of every length class (2^(c-1) < length <= 2^c) beside each
+// other, in any order, behind a place for every row that the shorter classes could have.
+struct LongRows {
+    LongRow* rows = nullptr;  // (NULL: not listed)
+    int* head = nullptr;      // per class, kLongApart ints apart: how many, first place (cleared before they are listed)
+    int log2 = 0, nnz = 0;
+    __host__ __device__ int first_place(int c) const {
+        int at = 0;
+        for (int i = log2 + 1; i < c; ++i) at += nnz >> (i - 1);
+        return at;
+    }
+};
+constexpr int kLongApart = 16;
+constexpr size_t kLongHeadBytes = EPP_NCLASS * kLongApart * sizeof(int);
+
+__device__ __forceinline__ int length_class(int len) { return len <= 1 ? 0 : 32 - __clz(len - 1); }
+
+// One row (or none, len = 0) of every thread of a workgroup, which all call this.  One atomic per workgroup and class: they follow each
+// other at 20 to 40 ns.  `found`: 2 EPP_NCLASS ints of LDS.  (No row gets a place that its class does not have, whatever the lengths.)
+__device__ __forceinline__ void list_long_rows(const LongRows& l, int v, int begin, int len, int* __restrict__ found) {
+    const bool is_long = len > (1 << l.log2);
+    if (!__syncthreads_or(is_long)) return;
+    if (threadIdx.x < EPP_NCLASS) found[threadIdx.x] = 0;
+    __syncthreads();
+    const int c = length_class(len), at = is_long ? atomicAdd(&found[c], 1) : 0;
+    __syncthreads();
+    if (threadIdx.x < EPP_NCLASS && found[threadIdx.x])
+        found[EPP_NCLASS + threadIdx.x] = atomicAdd(&l.head[threadIdx.x * kLongApart], found[threadIdx.x]);
+    __syncthreads();
+    if (!is_long) return;
+    const int first = l.first_place(c), place = found[EPP_NCLASS + c] + at;
+    if (place < l.nnz >> (c - 1)) l.rows[first + place] = LongRow{v, begin, begin + len, 0u};
+}
+// The first places, by one workgroup of those that list.
+__device__ __forceinline__ void place_long_rows(const LongRows& l) {
+    if (threadIdx.x < EPP_NCLASS) l.head[threadIdx.x * kLongApart + 1] = l.first_place((int)threadIdx.x);
+}
+
+// What the row kernel needs to know of the rows that one workgroup should not take alone: they are cut into chunks, whose sums the last
+// workgroup of the row's adds.
 struct RowsPlan {
-    DevBuf store;
-    RowChunk* chunks = nullptr;
-    HugeRow* rows = nullptr;
+    DevBuf store;  // the pieces, and the rows where the path has no list of them
+    LongRow* rows = nullptr;
+    const int* head = nullptr;
     float* pieces = nullptr;  // float[n_chunks][F]
-    int n_huge = 0, n_chunks = 0;
+    int n_chunks = 0;
 };
 
 // What a build of tiles has shown about the order of a path's entries, whichever the width; per number of lanes.
@@ -284,7 +322,8 @@ struct epp_path {
     bool all_rows = false;       // all-active graph (handle from epp_prepare_full)
     // Streamed form: only rows with at least one entry, in ascending vertex order.
     int64_t n_stream_rows = 0;
-    DevBuf store;                // one allocation behind row_ids, rowptr and cv where they are views of it
+    DevBuf store;                // one allocation behind row_ids, rowptr, long_rows and cv where they are views of it
+    LongRows long_rows;          // (a path of a construction or an import, where the row kernel may ask for it)
     DevBuf row_ids;              // int32[n_stream_rows] vertex of each streamed row; unset: identity
     DevBuf rowptr;               // int32[n_stream_rows + 1]
     DevBuf cv;                   // int2[nnz]: (column word, weight bits)
@@ -428,6 +467,9 @@ int epp_packed_stride(const epp_path* p, int F);  // floats from row to row of p
 // rows.hip: one launch that processes rows whole, for small paths
 bool epp_rows_kernel_fits(const epp_path* p, int F);
 int epp_build_rows_plan(epp_path* p, int F, hipStream_t s, RowsPlan** out);  // *out = NULL: none needed
+// rows.hip: the list of long rows that whoever builds a path of `nnz` entries makes along with it: which rows, where the classes lie (*l,
+// without memory); returns the bytes it takes, 0: none
+size_t epp_plan_long_rows(int64_t nnz, LongRows* l);
 int epp_launch_rows(const epp_path* p, const RowsPlan* plan, const float* in, float* out, int F, hipStream_t s, const unsigned int* inner_rows);
 // group table over any (row pointer, entry count); not registered with the path
 int epp_build_schedule_over(const epp_path* p, const int32_t* rowptr, int64_t n_rows, int64_t nnz, int gs, hipStream_t s,

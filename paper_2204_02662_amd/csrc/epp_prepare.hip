@@ -684,8 +684,6 @@ __global__ __launch_bounds__(kBlock) void k_row_flags(const int32_t* __restrict_
     }
 }
 
-__device__ __forceinline__ int length_class(int len) { return len <= 1 ? 0 : 32 - __clz(len - 1); }
-
 // Adds a row to the workgroup's histogram (one copy per wavefront, so that at most 64 lanes queue at
 // a counter).
 constexpr int kHists = kBlock / 64;
@@ -712,13 +710,13 @@ __device__ __forceinline__ void flush_lengths(const int* __restrict__ h, int* __
     if (threadIdx.x == 0 && *mx) atomicMax(max_len, *mx);
 }
 constexpr unsigned kStatBlocks = 512;
-// Ascending ids of N^{k+1}, compact row pointer and row-length statistics; a workgroup takes 256 vertices at a time.
+// Ascending ids of N^{k+1}, compact row pointer, row-length statistics and the list of long rows; a workgroup takes 256 vertices at a time.
 __global__ __launch_bounds__(kBlock) void k_rows_compact(const unsigned long long* __restrict__ bitmap, int64_t n,
                                                          const int* __restrict__ row_base, const int* __restrict__ newptr,
                                                          int32_t* __restrict__ ids, int32_t* __restrict__ ptr_out,
                                                          int64_t n_set, int total_nnz,
-                                                         unsigned long long* __restrict__ stats) {
-    __shared__ int h[kHists * EPP_NCLASS];
+                                                         unsigned long long* __restrict__ stats, LongRows list) {
+    __shared__ int h[kHists * EPP_NCLASS], found[2 * EPP_NCLASS];
     __shared__ int mx;
     const int lane = lane_id(), wave = threadIdx.x >> 6;
     clear_lengths(h, &mx);
@@ -734,17 +732,22 @@ __global__ __launch_bounds__(kBlock) void k_rows_compact(const unsigned long lon
             if (w == wave) m = x;
         }
         const int64_t v = t * kBlock + threadIdx.x;
+        int p = 0, len = 0;
         if ((m >> lane) & 1ull) {
-            const int r = at + __popcll(m & low_mask(lane)), p = newptr[v], len = newptr[v + 1] - p;
+            const int r = at + __popcll(m & low_mask(lane));
+            p = newptr[v];
+            len = newptr[v + 1] - p;
             ids[r] = (int32_t)v;
             ptr_out[r] = p;
             my_max = max(my_max, len);
             add_length(h, len);
         }
+        if (list.rows) list_long_rows(list, (int)v, p, len, found);
     }
     stats = my_stats<kRowCopies>(stats);
     flush_lengths(h, &mx, my_max, stats, reinterpret_cast<int*>(stats + EPP_NCLASS));
     if (blockIdx.x == 0 && threadIdx.x == 0) ptr_out[n_set] = total_nnz;
+    if (blockIdx.x == 0 && list.rows) place_long_rows(list);
 }
 
 __global__ __launch_bounds__(kBlock) void k_bitmap_count(const unsigned long long* __restrict__ bitmap, int64_t n_words,
@@ -1049,6 +1052,7 @@ struct ImportArgs {
     unsigned long long* stats;
     int* err;
     unsigned row_blocks;
+    LongRows list;
 };
 constexpr int kImportTile = 2048;
 // The workgroups of several paths in one launch, each path's behind those of the one before.
@@ -1062,7 +1066,7 @@ __global__ __launch_bounds__(kBlock) void k_import_path(ImportPaths all) {
     int at = 0;
     while (at < kImportPaths - 1 && blockIdx.x >= all.end[at]) block = blockIdx.x - all.end[at++];
     const ImportArgs& a = all.path[at];
-    __shared__ int h[kHists * EPP_NCLASS];
+    __shared__ int h[kHists * EPP_NCLASS], found[2 * EPP_NCLASS];
     __shared__ int mx;
     __shared__ unsigned int row_end[kImportTile / 32];
     const int lane = lane_id();
@@ -1107,9 +1111,9 @@ __global__ __launch_bounds__(kBlock) void k_import_path(ImportPaths all) {
     clear_lengths(h, &mx);
     int my_max = 0, bad = 0;
     const int64_t span = (int64_t)a.row_blocks * kBlock;
-    // (one index past the rows, for the end of the pointer; whole wavefronts enter every iteration)
-    for (int64_t base = (int64_t)block * kBlock + (threadIdx.x & ~63); base <= a.n_rows; base += span) {
-        const int64_t r = base + lane;
+    // (one index past the rows, for the end of the pointer; the whole workgroup enters every iteration)
+    for (int64_t base = (int64_t)block * kBlock; base <= a.n_rows; base += span) {
+        const int64_t r = base + threadIdx.x;
         const bool row = r < a.n_rows;
         const int p = r <= a.n_rows ? a.rowptr[r] : 0;
         const int v = row ? a.row_ids[r] : -1;
@@ -1136,8 +1140,10 @@ __global__ __launch_bounds__(kBlock) void k_import_path(ImportPaths all) {
         const int next_word = __shfl_down(word, 1, 64);
         if (in && (lane == 63 || next_word != word)) atomicOr(&a.bitmap32[word], b);
         if (row && len > 0) add_length(h, len);
+        if (a.list.rows) list_long_rows(a.list, v, p, row ? len : 0, found);
     }
     if (bad) atomicOr(a.err, bad);
+    if (block == 0 && a.list.rows) place_long_rows(a.list);
     unsigned long long* const stats = my_stats<kImportCopies>(a.stats);
     flush_lengths(h, &mx, my_max, stats, reinterpret_cast<int*>(stats + EPP_NCLASS));
 }
@@ -1190,6 +1196,21 @@ int launch_training_set(const int32_t* train_ids, int64_t n_train, int64_t n, co
 long long env_share_pct() {
     const char* e = std::getenv("EPP_TUNE_SHARE_PCT");
     return (e && *e) ? std::atoll(e) : 95;
+}
+
+// Memory of a path's rows, whose numbers are known: row ids | row pointer | list of long rows, each 256-byte aligned.  `head`: cleared, of that
+// list, and stays with it.
+int alloc_rows(epp_path* p, char* head, const epp_alloc_t* al) {
+    const size_t ids_bytes = (size_t)p->n_rows * 4, ptr_bytes = (size_t)(p->n_rows + 1) * 4, list_bytes = epp_plan_long_rows(p->nnz, &p->long_rows);
+    const size_t ptr_at = DevArena::rounded(ids_bytes), list_at = ptr_at + DevArena::rounded(ptr_bytes);
+    EPP_TRY(p->store.alloc(list_at + list_bytes, al));
+    p->row_ids.view(p->store.p, ids_bytes);
+    p->rowptr.view(p->store.as<char>() + ptr_at, ptr_bytes);
+    if (list_bytes) {
+        p->long_rows.rows = reinterpret_cast<LongRow*>(p->store.as<char>() + list_at);
+        p->long_rows.head = reinterpret_cast<int*>(head);
+    }
+    return EPP_OK;
 }
 
 int input_error(int bits, int64_t n) {
@@ -1357,10 +1378,11 @@ extern "C" int epp_prepare(const epp_csr_t* g, const int32_t* train_ids, int64_t
     P->bitmaps.resize(L + 1);
     P->set_size.assign(L + 1, 0);
     P->path.assign(L, nullptr);
-    // bitmaps of all sets and the ids of N^0 (at most one per training id) in one allocation
+    // bitmaps of all sets, the ids of N^0 (at most one per training id) and what the levels count in one allocation
     const size_t bm_bytes = (size_t)n_words * 8;
     const size_t set0_bytes = (size_t)std::min(n_train, n) * 4;
-    EPP_TRY(P->store.alloc((size_t)(L + 1) * DevArena::rounded(bm_bytes) + DevArena::rounded(set0_bytes), al));
+    const size_t level_bytes = DevArena::rounded((size_t)L * ((kLevelWords + kRowCopies * kStatWords) * 8 + kLongHeadBytes));
+    EPP_TRY(P->store.alloc((size_t)(L + 1) * DevArena::rounded(bm_bytes) + DevArena::rounded(set0_bytes) + level_bytes, al));
     for (int k = 0; k <= L; ++k) P->bitmaps[k].view(P->store.as<char>() + (size_t)k * DevArena::rounded(bm_bytes), bm_bytes);
     void* set0 = P->store.as<char>() + (size_t)(L + 1) * DevArena::rounded(bm_bytes);
 
@@ -1368,16 +1390,15 @@ extern "C" int epp_prepare(const epp_csr_t* g, const int32_t* train_ids, int64_t
     // (keep-mask, its counts and the members before every 256 vertices three times: the entries of a level are extracted
     // once the next level has shown whether the two paths share them, and then wait for the next extraction)
     constexpr int kAlive = 3;
-    DevBuf mask[kAlive], seg_off[kAlive], tile_base[kAlive], folded, tile_cnt, row_cnt, row_base[kAlive], scan_tmp, newptr, tile_row, levels;
+    DevBuf mask[kAlive], seg_off[kAlive], tile_base[kAlive], folded, tile_cnt, row_cnt, row_base[kAlive], scan_tmp, newptr, tile_row;
     const size_t cnt_bytes = (size_t)std::max(std::max(edge_tiles, word_tiles), 1u) * 4;
     const size_t row_bytes = (size_t)std::max(row_tiles, 1u) * 4;
     const size_t tmp_bytes = scan_tmp_bytes(std::max<int64_t>(edge_tiles, row_tiles));
-    const size_t level_bytes = DevArena::rounded((size_t)L * (kLevelWords + kRowCopies * kStatWords) * 8);
     DevArena arena;
     EPP_TRY(arena.reserve(kAlive * (DevArena::rounded((size_t)n_seg * 8) + DevArena::rounded((size_t)n_seg * 2) +
                                     DevArena::rounded(cnt_bytes) + DevArena::rounded(row_bytes)) +
                           DevArena::rounded(kFoldedWords * 4) + 2 * DevArena::rounded(cnt_bytes) + DevArena::rounded(row_bytes) + DevArena::rounded(tmp_bytes) +
-                          DevArena::rounded((size_t)(n + 1) * 4) + DevArena::rounded(level_bytes), al));
+                          DevArena::rounded((size_t)(n + 1) * 4), al));
     for (int i = 0; i < kAlive; ++i) {
         arena.take(&mask[i], (size_t)n_seg * 8);
         arena.take(&seg_off[i], (size_t)n_seg * 2);
@@ -1390,13 +1411,13 @@ extern "C" int epp_prepare(const epp_csr_t* g, const int32_t* train_ids, int64_t
     arena.take(&row_cnt, row_bytes);
     arena.take(&scan_tmp, tmp_bytes);
     arena.take(&tile_row, cnt_bytes);
-    arena.take(&levels, level_bytes);
-    long long* const d_levels = levels.as<long long>();
+    long long* const d_levels = reinterpret_cast<long long*>(static_cast<char*>(set0) + DevArena::rounded(set0_bytes));
     unsigned long long* const d_stats = reinterpret_cast<unsigned long long*>(d_levels + (size_t)L * kLevelWords);
+    char* const d_long = reinterpret_cast<char*>(d_stats + (size_t)L * kRowCopies * kStatWords);
 
     // N^0 = V_t (Property 1) and its ascending ids (the other sets are the row ids of the paths)
     EPP_TRY(launch_training_set(train_ids, n_train, n, P->bitmaps[0], set0, tile_cnt.as<int>(), tile_base[0].as<int>(),
-                                scan_tmp.as<int>(), d_levels + 5, reinterpret_cast<int*>(d_levels + 2), levels.p, level_bytes, s));
+                                scan_tmp.as<int>(), d_levels + 5, reinterpret_cast<int*>(d_levels + 2), d_levels, level_bytes, s));
     EPP_HIP_TRY(hipGetLastError());
 
     // Shared entries: the path of a level runs on the arrays of the next level's path if nearly
@@ -1491,17 +1512,12 @@ extern "C" int epp_prepare(const epp_csr_t* g, const int32_t* train_ids, int64_t
         p->n_rows = R;
         p->n_stream_rows = R;  // every row of a path has at least one entry
         P->set_size[k + 1] = R;
-        // row ids | row pointer in one allocation, each 256-byte aligned
-        const size_t ids_bytes = (size_t)R * 4, ptr_bytes = (size_t)(R + 1) * 4;
-        EPP_TRY(p->store.alloc(DevArena::rounded(ids_bytes) + DevArena::rounded(ptr_bytes), al));
-        char* base = p->store.as<char>();
-        p->row_ids.view(base, ids_bytes);
-        p->rowptr.view(base + DevArena::rounded(ids_bytes), ptr_bytes);
+        EPP_TRY(alloc_rows(p, d_long + (size_t)k * kLongHeadBytes, al));
         if (n > 0) {
             hipLaunchKernelGGL(k_rows_compact, dim3(std::min(row_tiles, kRowBlocks)), dim3(kBlock), 0, s,
                                P->bitmaps[k + 1].as<unsigned long long>(), n, row_base[slot].as<int>(), newptr.as<int>(),
                                p->row_ids.as<int32_t>(), p->rowptr.as<int32_t>(), (int64_t)R, (int)kept,
-                               d_stats + (size_t)k * kRowCopies * kStatWords);
+                               d_stats + (size_t)k * kRowCopies * kStatWords, p->long_rows);
             EPP_HIP_TRY(hipGetLastError());
         } else {
             EPP_HIP_TRY(hipMemsetAsync(p->rowptr.p, 0, sizeof(int32_t), s));
@@ -1664,13 +1680,14 @@ extern "C" int epp_paths_import(int64_t n, int L, const int32_t* train_ids, int6
     P->bitmaps.resize(L + 1);
     P->set_size.assign(L + 1, 0);
     P->path.assign(L, nullptr);
-    // bitmaps (cleared), ids of N^0 (at most one per training id), results (cleared)
+    // bitmaps (cleared), ids of N^0 (at most one per training id), results, counts of the long rows (cleared)
     const size_t bm_bytes = (size_t)n_words * 8, set0_bytes = (size_t)std::min(n_train, n) * 4;
     const size_t tiles = std::max<size_t>(grid_for(n_words, kWordsPerTile), 1);
-    const size_t clear_bytes = (size_t)(L + 1) * DevArena::rounded(bm_bytes) + DevArena::rounded(res_words * 8);
+    const size_t clear_bytes = (size_t)(L + 1) * DevArena::rounded(bm_bytes) + DevArena::rounded(res_words * 8 + (size_t)L * kLongHeadBytes);
     EPP_TRY(P->store.alloc(clear_bytes + DevArena::rounded(set0_bytes), al));
     for (int k = 0; k <= L; ++k) P->bitmaps[k].view(P->store.as<char>() + (size_t)k * DevArena::rounded(bm_bytes), bm_bytes);
     long long* d_res = reinterpret_cast<long long*>(P->store.as<char>() + (size_t)(L + 1) * DevArena::rounded(bm_bytes));
+    char* const d_long = reinterpret_cast<char*>(d_res + res_words);
     void* set0 = P->store.as<char>() + clear_bytes;
     int* d_err = reinterpret_cast<int*>(d_res);
     DevArena arena;
@@ -1699,11 +1716,8 @@ extern "C" int epp_paths_import(int64_t n, int L, const int32_t* train_ids, int6
         p->n_rows = p->n_stream_rows = a.n_rows;
         p->nnz = a.nnz;
         P->set_size[k + 1] = a.n_rows;
-        // row ids | row pointer in one allocation, the entries in one of their own (see epp_prepare)
-        const size_t ids_bytes = (size_t)a.n_rows * 4, ptr_bytes = (size_t)(a.n_rows + 1) * 4;
-        EPP_TRY(p->store.alloc(DevArena::rounded(ids_bytes) + DevArena::rounded(ptr_bytes), al));
-        p->row_ids.view(p->store.p, ids_bytes);
-        p->rowptr.view(p->store.as<char>() + DevArena::rounded(ids_bytes), ptr_bytes);
+        // (the entries in an allocation of their own: see epp_prepare)
+        EPP_TRY(alloc_rows(p, d_long + (size_t)l * kLongHeadBytes, al));
         EPP_TRY(p->cv.alloc((size_t)a.nnz * sizeof(int2), al));
         ImportArgs& q = all.path[held];
         q.row_ids = a.row_ids;
@@ -1720,6 +1734,7 @@ extern "C" int epp_paths_import(int64_t n, int L, const int32_t* train_ids, int6
         q.stats = reinterpret_cast<unsigned long long*>(d_res + 2 + (size_t)l * kLayerWords);
         q.err = d_err;
         q.row_blocks = std::min(grid_for(a.n_rows + 1, kBlock), kStatBlocks);
+        q.list = p->long_rows;
         blocks += q.row_blocks + grid_for(a.nnz, kImportTile);
         all.end[held++] = blocks;
         if (l > 0 && held < kImportPaths) continue;

@@ -68,11 +68,11 @@ struct RowArgs {
     int F;
     int log2p;               // slots per row
     int limit;               // longest row that is not left to the workgroup
-    int huge;                // longest row that is not cut into chunks
+    int log2_chunk;          // 2^: entries of a chunk, and the longest row that is not cut into chunks
     int has_long;            // some row is longer than `limit`
     int chunk_blocks;        // workgroups that take one chunk of a cut row each, before the others
-    const RowChunk* chunks;  // empty: no such chunk
-    HugeRow* huge_rows;      // the cut rows
+    LongRow* long_rows;
+    const int* long_head;
     float* pieces;           // the chunks' sums, F floats each
     // launch for the inner path that shares the arrays only
     const float* zero;           // what an entry that is not the inner path's gathers
@@ -226,15 +226,30 @@ __device__ __forceinline__ void sum_by_workgroup(const RowArgs& a, float* __rest
 // L2, of which every XCD has its own; the wait before the count is for the writes to have arrived.
 template <int VEC, int LOG2T, bool INNER>
 __device__ __forceinline__ void sum_chunk(const RowArgs& a, float (*part)[(1 << LOG2T) * VEC], int* was) {
-    const RowChunk c = a.chunks[blockIdx.x];
-    if (c.begin >= c.end) return;
+    const int b = (int)blockIdx.x;
+    // classes from the longest rows' down, as many workgroups for each row of one as its longest row has chunks
+    const int lane = threadIdx.x & 63, c = EPP_NCLASS - 1 - (lane & (EPP_NCLASS - 1));
+    const int rows_of_class = a.long_head[c * kLongApart], place_of_class = a.long_head[c * kLongApart + 1];
+    const int width = c > a.log2_chunk ? rows_of_class << (c - a.log2_chunk) : 0;
+    int upto = width;
+#pragma unroll
+    for (int d = 1; d < EPP_NCLASS; d <<= 1) {
+        const int below = __shfl_up(upto, d, EPP_NCLASS);
+        if ((lane & (EPP_NCLASS - 1)) >= d) upto += below;
+    }
+    const int k = __ffsll((long long)__ballot(b < upto)) - 1;
+    if (k < 0) return;
+    const int log2 = EPP_NCLASS - 1 - k - a.log2_chunk, j = b - __builtin_amdgcn_readlane(upto - width, k), q = j & ((1 << log2) - 1);
+    LongRow* const h = a.long_rows + __builtin_amdgcn_readlane(place_of_class, k) + (j >> log2);
+    const int row_begin = h->begin, row_end = h->end, v = h->v;
+    const int count = (row_end - row_begin + (1 << a.log2_chunk) - 1) >> a.log2_chunk;
+    if (q >= count) return;
+    const int begin = row_begin + (q << a.log2_chunk), end = min(begin + (1 << a.log2_chunk), row_end);
     const int slot = threadIdx.x >> LOG2T;
     constexpr int kSlots = kBlock >> LOG2T, kAhead = 4;
-    sum_by_workgroup<VEC, LOG2T, true>(a, a.pieces + (size_t)blockIdx.x * a.F, part, [&](int f, float (&acc)[VEC]) {
-        add_entries<VEC, LOG2T, kU, INNER, true>(a, a.in + f, c.begin + slot * kU, c.end, kSlots * kU, acc);
+    sum_by_workgroup<VEC, LOG2T, true>(a, a.pieces + (size_t)b * a.F, part, [&](int f, float (&acc)[VEC]) {
+        add_entries<VEC, LOG2T, kU, INNER, true>(a, a.in + f, begin + slot * kU, end, kSlots * kU, acc);
     });
-    HugeRow* const h = a.huge_rows + c.row;
-    const int count = h->count;
     if (threadIdx.x < 64) {
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         if (threadIdx.x == 0) *was = (int)atomicInc(&h->done, (unsigned)count - 1u);  // (0 again behind the last one)
@@ -242,10 +257,10 @@ __device__ __forceinline__ void sum_chunk(const RowArgs& a, float (*part)[(1 << 
     __syncthreads();
     if (*was != count - 1) return;
     if constexpr (INNER) {
-        if (!((a.only[h->v >> 5] >> (h->v & 31)) & 1u)) return;
+        if (!((a.only[v >> 5] >> (v & 31)) & 1u)) return;
     }
-    const float* __restrict__ pieces = a.pieces + (size_t)h->first * a.F;
-    sum_by_workgroup<VEC, LOG2T, false>(a, a.out + (size_t)h->v * a.F, part, [&](int f, float (&acc)[VEC]) {
+    const float* __restrict__ pieces = a.pieces + (size_t)(b - q) * a.F;
+    sum_by_workgroup<VEC, LOG2T, false>(a, a.out + (size_t)v * a.F, part, [&](int f, float (&acc)[VEC]) {
 #pragma unroll
         for (int i = 0; i < VEC; ++i) acc[i] = 0.0f;
         for (int p = slot; p < count; p += kAhead * kSlots) {
@@ -287,7 +302,7 @@ __global__ __launch_bounds__(kBlock, 7) void k_aggregate_rows(RowArgs a) {
     if (a.has_long) {
         if (threadIdx.x == 0) count = 0;
         __syncthreads();
-        if (is_long && p1 - p0 <= a.huge && t == 0 && sub == 0) list[atomicAdd(&count, 1)] = r;
+        if (is_long && p1 - p0 <= (1 << a.log2_chunk) && t == 0 && sub == 0) list[atomicAdd(&count, 1)] = r;
     }
     bool bad = false;
     for (int f0 = 0; f0 < a.F; f0 += T * VEC) {
@@ -338,28 +353,13 @@ __global__ __launch_bounds__(kBlock, 7) void k_aggregate_rows(RowArgs a) {
     }
 }
 
-// Rows of more than `chunk` entries: their chunks, and what the chunks' sums are to be added to.
-__global__ __launch_bounds__(kBlock) void k_cut_huge_rows(const int32_t* __restrict__ rowptr,
-                                                          const int32_t* __restrict__ row_ids, int n_rows, int chunk,
-                                                          int* __restrict__ counters, RowChunk* __restrict__ chunks,
-                                                          HugeRow* __restrict__ rows) {
+__global__ __launch_bounds__(kBlock) void k_list_long_rows(const int32_t* __restrict__ rowptr, const int32_t* __restrict__ row_ids,
+                                                           int n_rows, LongRows list) {
+    __shared__ int found[2 * EPP_NCLASS];
     const int r = blockIdx.x * kBlock + threadIdx.x;
     const int p0 = r < n_rows ? rowptr[r] : 0, p1 = r < n_rows ? rowptr[r + 1] : 0;
-    int first = 0, cnt = 0, row = 0;
-    if (p1 - p0 > chunk) {
-        cnt = (p1 - p0 + chunk - 1) / chunk;
-        first = atomicAdd(&counters[0], cnt);
-        row = atomicAdd(&counters[1], 1);
-        rows[row] = HugeRow{row_ids ? row_ids[r] : r, first, cnt, 0u};
-    }
-    // a row's chunks are written by its wavefront: there can be thousands
-    for (unsigned long long todo = __ballot(cnt > 0); todo; todo &= todo - 1ull) {
-        const int l = __ffsll((long long)todo) - 1;
-        const int begin = __shfl(p0, l, 64), end = __shfl(p1, l, 64), at = __shfl(first, l, 64), n = __shfl(cnt, l, 64);
-        const int its_row = __shfl(row, l, 64);
-        for (int i = threadIdx.x & 63; i < n; i += 64)
-            chunks[at + i] = RowChunk{begin + i * chunk, min(begin + (i + 1) * chunk, end), its_row, 0};
-    }
+    list_long_rows(list, r < n_rows && row_ids ? row_ids[r] : r, p0, p1 - p0, found);
+    if (blockIdx.x == 0) place_long_rows(list);
 }
 
 template <int VEC, int LOG2T>
@@ -417,33 +417,49 @@ bool epp_rows_kernel_fits(const epp_path* p, int F) {
     return (F < 32 || F % 4 != 0) && p->nnz * F <= 100000000 && p->n_src * F <= 28000000;
 }
 
+// The path's own list takes no launch of its own and no wait.  It goes down to the chunks that launches on this many entries have (see
+// above: over 48 M, none of more than 4 floats; 17 and 33 floats are the first of 16 and 32 bytes more a lane), since a place
+// for every row that there could be is 16 bytes for every 2^(log2 - 1) entries.  Import and first epoch of
+// the blog graph (4.2 M entries, F = 16 / 39): 153.5 us with the rows listed width by width, 120.2 with the path's own list.
+size_t epp_plan_long_rows(int64_t nnz, LongRows* l) {
+    *l = LongRows{};
+    if (nnz > 48000000) return 0;
+    l->log2 = nnz > 100000000 / 17 ? 11 : nnz > 100000000 / 33 ? 10 : 9;
+    l->nnz = (int)nnz;
+    return (size_t)l->first_place(EPP_NCLASS) * sizeof(LongRow);
+}
+
 int epp_build_rows_plan(epp_path* p, int F, hipStream_t s, RowsPlan** out) {
     *out = nullptr;
     // rows of 2^(c-1) < length <= 2^c are counted in class c
     const int c0 = chunk_log2(F);
-    int64_t n_huge = 0, n_chunks = 0;
-    for (int c = c0 + 1; c < EPP_NCLASS; ++c) {
-        n_huge += p->len_hist[c];
-        n_chunks += p->len_hist[c] << (c - c0);
-    }
-    if (n_huge == 0) return EPP_OK;
+    int64_t n_chunks = 0;
+    for (int c = c0 + 1; c < EPP_NCLASS; ++c) n_chunks += p->len_hist[c] << (c - c0);
+    if (n_chunks == 0) return EPP_OK;
     RowsPlan* q = new RowsPlan();
     struct Guard { RowsPlan* q; ~Guard() { delete q; } } guard{q};
-    const epp_alloc_t* al = epp_alloc_of(p);
-    q->n_huge = (int)n_huge;
-    q->n_chunks = (int)n_chunks;  // (an upper bound)
-    const size_t table = DevArena::rounded((size_t)n_chunks * sizeof(RowChunk)) + DevArena::rounded(8);
-    EPP_TRY(q->store.alloc(table + DevArena::rounded((size_t)n_huge * sizeof(HugeRow)) + (size_t)n_chunks * F * 4, al));
-    q->chunks = q->store.as<RowChunk>();
-    q->rows = reinterpret_cast<HugeRow*>(q->store.as<char>() + table);
-    q->pieces = reinterpret_cast<float*>(q->store.as<char>() + table + DevArena::rounded((size_t)n_huge * sizeof(HugeRow)));
-    EPP_HIP_TRY(hipMemsetAsync(q->store.p, 0, table, s));
-    hipLaunchKernelGGL(k_cut_huge_rows, dim3((unsigned)((p->n_stream_rows + kBlock - 1) / kBlock)), dim3(kBlock), 0, s,
-                       p->rowptr.as<int32_t>(), p->row_ids.p ? p->row_ids.as<int32_t>() : nullptr, (int)p->n_stream_rows,
-                       1 << c0, reinterpret_cast<int*>(q->store.as<char>() + DevArena::rounded((size_t)n_chunks * sizeof(RowChunk))),
-                       q->chunks, q->rows);
-    EPP_HIP_TRY(hipGetLastError());
-    EPP_HIP_TRY(hipStreamSynchronize(s));
+    LongRows list = p->long_rows;
+    size_t at = 0;
+    const bool listed = list.rows && list.log2 <= c0;
+    if (!listed) {
+        list.log2 = c0;
+        list.nnz = (int)p->nnz;
+        at = kLongHeadBytes + DevArena::rounded((size_t)list.first_place(EPP_NCLASS) * sizeof(LongRow));
+    }
+    EPP_TRY(q->store.alloc(at + (size_t)n_chunks * F * 4, epp_alloc_of(p)));
+    if (!listed) {
+        list.head = q->store.as<int>();
+        list.rows = reinterpret_cast<LongRow*>(q->store.as<char>() + kLongHeadBytes);
+        EPP_HIP_TRY(hipMemsetAsync(list.head, 0, kLongHeadBytes, s));
+        hipLaunchKernelGGL(k_list_long_rows, dim3((unsigned)((p->n_stream_rows + kBlock - 1) / kBlock)), dim3(kBlock), 0, s,
+                           p->rowptr.as<int32_t>(), p->row_ids.p ? p->row_ids.as<int32_t>() : nullptr, (int)p->n_stream_rows, list);
+        EPP_HIP_TRY(hipGetLastError());
+        EPP_HIP_TRY(hipStreamSynchronize(s));
+    }
+    q->rows = list.rows;
+    q->head = list.head;
+    q->pieces = reinterpret_cast<float*>(q->store.as<char>() + at);
+    q->n_chunks = (int)n_chunks;  // (an upper bound: a workgroup whose chunk its row does not have ends at once)
     guard.q = nullptr;
     *out = q;
     return EPP_OK;
@@ -471,12 +487,12 @@ int epp_launch_rows(const epp_path* p, const RowsPlan* plan, const float* in, fl
     while (log2p + log2t < 6 && (double)(kU << log2p) < per_row) ++log2p;
     while (log2p > 0 && (p->n_stream_rows << (log2t + log2p)) >> 6 > (262144 >> log2t)) --log2p;
     a.log2p = log2p;
-    a.huge = 1 << chunk_log2(F);
-    a.limit = std::min((8 * kU) << log2p, a.huge);
+    a.log2_chunk = chunk_log2(F);
+    a.limit = std::min((8 * kU) << log2p, 1 << a.log2_chunk);
     a.has_long = p->max_len > a.limit;
     a.chunk_blocks = plan ? plan->n_chunks : 0;
-    a.chunks = plan ? plan->chunks : nullptr;
-    a.huge_rows = plan ? plan->rows : nullptr;
+    a.long_rows = plan ? plan->rows : nullptr;
+    a.long_head = plan ? plan->head : nullptr;
     a.pieces = plan ? plan->pieces : nullptr;
     if (F >= 4) {
         switch (log2t) {
