@@ -10,6 +10,7 @@ The calls that a training loop makes on every layer of every pass come from the 
 from __future__ import annotations
 
 import ctypes
+from collections.abc import Mapping
 from dataclasses import dataclass
 from pathlib import Path
 
@@ -59,30 +60,33 @@ class _Alloc(ctypes.Structure):
     _fields_ = [("alloc", _ALLOC_FN), ("free", _FREE_FN), ("ctx", ctypes.c_void_p)]
 
 
+class _AllocStats(Mapping):
+    def __getitem__(self, what):
+        allocs, frees, nbytes = _alloc_counts()
+        return {"allocs": allocs, "frees": frees, "bytes": nbytes, "live": allocs - frees}[what]
+
+    def __iter__(self):
+        return iter(("allocs", "frees", "bytes", "live"))
+
+    def __len__(self):
+        return 4
+
+    def __repr__(self):
+        return repr(dict(self))
+
+
 #: calls and bytes that went through the PyTorch-backed allocator handed to the library
-alloc_stats = {"allocs": 0, "frees": 0, "bytes": 0, "live": 0}
+alloc_stats = _AllocStats()
 
 
-def _torch_alloc(nbytes, _ctx):
+def _torch_alloc(nbytes, ctx=None):
     """epp_alloc_t.alloc: a block of PyTorch's caching allocator on the current device and stream."""
-    try:
-        ptr = torch.cuda.caching_allocator_alloc(int(nbytes))
-    except Exception:  # out of memory: the library reports EPP_ERR_ALLOC
-        return None
-    alloc_stats["allocs"] += 1
-    alloc_stats["bytes"] += int(nbytes)
-    alloc_stats["live"] += 1
-    return ptr
+    return _TORCH_ALLOC_FN(int(nbytes), ctx)
 
 
-def _torch_free(ptr, _ctx):
+def _torch_free(ptr, ctx=None):
     """epp_alloc_t.free: the block goes back to the caching allocator (stream-ordered reuse)."""
-    alloc_stats["frees"] += 1
-    alloc_stats["live"] -= 1
-    torch.cuda.caching_allocator_delete(ptr)
-
-
-_TORCH_ALLOC = _Alloc(_ALLOC_FN(_torch_alloc), _FREE_FN(_torch_free), None)
+    _TORCH_FREE_FN(ptr, ctx)
 
 
 def _allocator(use_torch: bool):
@@ -328,13 +332,18 @@ def epp_weight_gradient_workspace(paths: Paths, k: int, F_in: int, F_out: int) -
 
 try:
     from ._binding import (epp_backward_aggregate, epp_full_aggregate, epp_input_gradient, epp_weight_gradient,
-                           epp_weight_gradient_static, init as _init_binding)
+                           epp_weight_gradient_static, alloc_counts as _alloc_counts, allocator as _native_allocator,
+                           init as _init_binding)
     _init_binding(EppError, _raw_stream)
+    _addresses = _native_allocator()
+    _TORCH_ALLOC_FN, _TORCH_FREE_FN = _ALLOC_FN(_addresses[0]), _FREE_FN(_addresses[1])
+    _TORCH_ALLOC = _Alloc(_TORCH_ALLOC_FN, _TORCH_FREE_FN, None)
 except ImportError as _e:  # not built yet: the package can be imported (to build it), these calls raise
     def _not_built(*_args, _why=str(_e), **_kw):
         raise FileNotFoundError(f"{PKG}/_binding is not usable ({_why}): run `python -m paper_2204_02662_amd.build`")
     epp_backward_aggregate = epp_full_aggregate = epp_input_gradient = _not_built
-    epp_weight_gradient = epp_weight_gradient_static = _not_built
+    epp_weight_gradient = epp_weight_gradient_static = _alloc_counts = _TORCH_ALLOC_FN = _TORCH_FREE_FN = _not_built
+    _TORCH_ALLOC = _Alloc()
 
 
 def epp_paths_import(n: int, train_ids: torch.Tensor, layers, torch_allocator: bool = True) -> Paths:

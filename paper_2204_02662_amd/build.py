@@ -2,6 +2,7 @@
 from __future__ import annotations
 
 import hashlib
+import shutil
 import subprocess
 import sysconfig
 import tempfile
@@ -51,7 +52,9 @@ def link_library(objects: list, verbose: bool = False) -> None:
 def binding_object(obj: Path, verbose: bool = False) -> None:
     import torch
     inc = Path(torch.__file__).parent / "include"
-    _run(["g++", "-O2", "-std=c++17", "-fPIC", "-Wall", f"-I{ROOT / 'include'}", f"-isystem{inc}",
+    rocm = Path(shutil.which("hipcc") or "/opt/rocm/bin/hipcc").resolve().parent.parent
+    _run(["g++", "-O2", "-std=c++17", "-fPIC", "-Wall", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM", f"-I{ROOT / 'include'}", f"-isystem{inc}",
+          f"-isystem{rocm / 'include'}",
           f"-isystem{inc / 'torch/csrc/api/include'}", f"-I{sysconfig.get_paths()['include']}", "-c", BINDING_SOURCE,
           "-o", obj], verbose)
 
@@ -60,7 +63,7 @@ def link_binding(obj: Path, verbose: bool = False) -> None:
     """Linked with libepp.so beside it and with the libraries of the PyTorch that runs it."""
     import torch
     lib = Path(torch.__file__).parent / "lib"
-    _run(["g++", "-shared", "-fPIC", obj, f"-L{PKG}", "-l:libepp.so", f"-L{lib}", "-ltorch_python", "-ltorch_cpu", "-lc10",
+    _run(["g++", "-shared", "-fPIC", obj, f"-L{PKG}", "-l:libepp.so", f"-L{lib}", "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip",
           "-Wl,--allow-shlib-undefined", "-Wl,-rpath,$ORIGIN", f"-Wl,-rpath,{lib}", "-o", BINDING], verbose)
 
 

@@ -12,6 +12,9 @@
 #include <torch/csrc/autograd/python_variable.h>
 
 #include <c10/core/impl/VirtualGuardImpl.h>
+#include <c10/hip/HIPCachingAllocator.h>
+
+#include <atomic>
 
 #include "epp.h"
 
@@ -236,6 +239,42 @@ PyObject* guarded(PyObject* self, PyObject* const* args, Py_ssize_t n, PyObject*
     return nullptr;
 }
 
+// epp_alloc_t of PyTorch's caching allocator, on the current device and stream; any host thread, with the interpreter's lock or without.
+// (As functions of the Python module, called back through ctypes, an allocation and its release took 4.3 us, and a construction or an
+// import makes about eight, some of them while the GPU waits for the next launch: constructed on 8,000 vertices 106 -> 88 us, imported
+// and one epoch on the blog graph 120 -> 112.)
+std::atomic<long long> g_allocs{0}, g_frees{0}, g_bytes{0};
+
+void* torch_alloc(size_t bytes, void*) {
+    try {
+        void* p = c10::hip::HIPCachingAllocator::raw_alloc(bytes);
+        if (!p) return nullptr;
+        g_allocs.fetch_add(1, std::memory_order_relaxed);
+        g_bytes.fetch_add((long long)bytes, std::memory_order_relaxed);
+        return p;
+    } catch (...) {  // out of memory: the library reports EPP_ERR_ALLOC
+        return nullptr;
+    }
+}
+void torch_free(void* p, void*) {
+    g_frees.fetch_add(1, std::memory_order_relaxed);
+    try {
+        c10::hip::HIPCachingAllocator::raw_delete(p);
+    } catch (...) {  // (nobody to tell: the handle goes)
+    }
+}
+
+// (address of the allocating function, of the releasing one)
+PyObject* allocator(PyObject*, PyObject*) {
+    return Py_BuildValue("KK", (unsigned long long)reinterpret_cast<uintptr_t>(&torch_alloc),
+                         (unsigned long long)reinterpret_cast<uintptr_t>(&torch_free));
+}
+// (allocations, releases, bytes) since the process began
+PyObject* alloc_counts(PyObject*, PyObject*) {
+    return Py_BuildValue("LLL", g_allocs.load(std::memory_order_relaxed), g_frees.load(std::memory_order_relaxed),
+                         g_bytes.load(std::memory_order_relaxed));
+}
+
 // init(error class, raw-stream function)
 PyObject* init(PyObject*, PyObject* const* args, Py_ssize_t n) {
     if (n != 2) {
@@ -267,6 +306,8 @@ PyMethodDef methods[] = {
     {"epp_input_gradient", EPP_FAST(input_gradient),
      "epp_input_gradient(paths, k, grad_X, W, grad_Y)\n\nY' = X' (x) W^T on the rows of N^k (k = -1: all rows); other rows "
      "of grad_Y are not touched."},
+    {"allocator", allocator, METH_NOARGS, nullptr},
+    {"alloc_counts", alloc_counts, METH_NOARGS, nullptr},
     {nullptr, nullptr, 0, nullptr}};
 
 PyModuleDef module = {PyModuleDef_HEAD_INIT, "_binding", nullptr, -1, methods, nullptr, nullptr, nullptr, nullptr};
