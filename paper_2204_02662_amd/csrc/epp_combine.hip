@@ -382,6 +382,59 @@ __global__ __launch_bounds__(kBlock, MT * NT >= 16 ? 1 : 2) void k_weight_gradie
     }
 }
 
+// W' of few rows in one launch: a workgroup of 16 wavefronts forms 32 x 32 of it from all rows, a sixteenth of them a wavefront, which has all its
+// operands on their way at once; the wavefronts' sums meet in LDS and are added in double.
+// Bound by the launch, the two loads behind each other and the lines that one CU gets through; partial sums need a second launch to add
+// them (us, 16 x 3 / 32 x 32 / 41 x 41 / 64 x 64 / 128 x 128; 8 rows 3.2 / 3.4 / 3.8 / 3.9 / 4.7 -> 2.5 / 2.5 / 2.6 / 2.6 / 2.7, 64 rows 3.0 / 3.3 / 6.1 / 6.0 /
+// 4.7 -> 3.0 / 3.0 / 3.1 / 3.2 / 3.3, 128 rows 5.4 / 5.7 / 6.1 / 6.0 / 7.0 -> 3.3 / 3.3 / 3.4 / 3.4 / 3.5, 384 rows 5.2 / 5.5 / 6.0 / 5.9 / 7.2 ->
+// 4.9 / 4.8 / 5.3 / 5.1 / 5.1; from 450 on not for every width: 5.2 / 5.6 / 6.0 / 5.9 / 7.3 against 5.6 / 5.6 / 5.8 / 5.7 / 5.7, 512 rows 5.2 against 5.8 at
+// 16 x 3).  Error against 64 bits 4e-8 to 7e-8 for 5e-8 to 9e-8.
+constexpr int kFewWaves = 16, kFewRows = 384;
+__global__ __launch_bounds__(64 * kFewWaves) void k_weight_gradient_few(const int32_t* __restrict__ ids, int n_rows, int rows_per_wave,
+                                                                        const float* __restrict__ Y, int Fi,
+                                                                        const float* __restrict__ G, int Fo, float* __restrict__ Wg) {
+    constexpr int PAIRS = kFewRows / kFewWaves / 2, CHAINS = 4;
+    __shared__ float part[kFewWaves][16 * 64];
+    const int m0 = blockIdx.x * 32, n0 = blockIdx.y * 32;
+    const int lane = threadIdx.x & 63, p = lane & 31, half = lane >> 5, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int first = wave * rows_per_wave, mine = std::min(rows_per_wave, n_rows - first);  // (0 or less: none)
+    // (lanes past a width read what is there: their products are never written)
+    const float* __restrict__ y = Y + (m0 + p < Fi ? m0 + p : 0);
+    const float* __restrict__ g = G + (n0 + p < Fo ? n0 + p : 0);
+    floatx16 chain[CHAINS] = {};
+    if (mine > 0) {
+        // lane i holds the vertex of row i; the row behind an odd number's last is that one again, with both factors zero
+        const int row = first + std::min(lane, mine - 1), v = ids ? ids[row] : row;
+        float a[PAIRS], b[PAIRS];
+#pragma unroll
+        for (int d = 0; d < PAIRS; ++d) {
+            a[d] = b[d] = 0.0f;
+            if (2 * d < mine) {
+                const int v0 = __builtin_amdgcn_readlane(v, 2 * d), v1 = __builtin_amdgcn_readlane(v, 2 * d + 1);
+                const int64_t id = half ? v1 : v0;
+                a[d] = y[id * Fi];
+                b[d] = g[id * Fo];
+            }
+        }
+#pragma unroll
+        for (int d = 0; d < PAIRS; ++d) {
+            if (2 * d >= mine) continue;
+            const bool in = 2 * d + half < mine;
+            chain[d % CHAINS] = __builtin_amdgcn_mfma_f32_32x32x2f32(in ? a[d] : 0.0f, in ? b[d] : 0.0f, chain[d % CHAINS], 0, 0, 0);
+        }
+    }
+    const floatx16 sum = (chain[0] + chain[1]) + (chain[2] + chain[3]);
+#pragma unroll
+    for (int e = 0; e < 16; ++e) part[wave][e * 64 + lane] = sum[e];
+    __syncthreads();
+    const int m = m0 + 8 * (wave / 4) + 4 * half + wave % 4, n = n0 + p;  // element `wave` of the accumulators
+    if (m >= Fi || n >= Fo) return;
+    double total = 0.0;
+#pragma unroll
+    for (int w = 0; w < kFewWaves; ++w) total += (double)part[w][threadIdx.x];
+    Wg[(int64_t)m * Fo + n] = (float)total;
+}
+
 // Y'[id, n] = sum_k X'[id, k] W[n, k], widths of at most 128 (F_out = k) and 32 NT (F_in = n).
 //
 // W stays in LDS for the whole launch, in the order in which the matrix core takes it: the workgroups
@@ -655,8 +708,8 @@ Chunks chunking(int64_t n_rows, int Fi, int Fo, int64_t max_chunks) {
         // follow each other in a wavefront, and what the partial sums cost to write and add (64 rows a wavefront, or
         // 16 wavefronts for up to 1,024 rows -> this: 869 rows, 64 x 64 24.7 -> 7.5 us, 16 x 16 11.6 -> 6.6, 96 x 96
         // 40.7 -> 14.6; 30,000 rows, 64 x 64 16.0 -> 15.2, 96 x 96 46 -> 29).  One block: half as many partial sums, until
-        // that is 64 rows a wavefront (32 x 32, 16,000 rows 9.1 -> 8.2 us), and up to 64 rows a single workgroup, which needs
-        // no launch to add them (60 rows 6.4 -> 4.0 us).  Up to four: 256 rows in 16 chains, for the sake of the sums.
+        // that is 64 rows a wavefront (32 x 32, 16,000 rows 9.1 -> 8.2 us).  (Up to kFewRows rows need no partial sums; callers still bring the
+        // workspace that this makes of them.)
         if (n_rows <= 65536) {
             const int64_t chains = tiles == 1 && n_rows <= 64 ? 4 : tiles <= 4 && n_rows <= 256 ? 16 : tiles == 1 ? 512 : 1024;
             c.per = std::max<int64_t>((n_rows + chains - 1) / chains, chains <= 16 ? 2 : 16);
@@ -681,7 +734,7 @@ Chunks chunking(int64_t n_rows, int Fi, int Fo, int64_t max_chunks) {
 }
 
 // Blocks of 32 columns of Y (mt in all) that a workgroup of k_weight_gradient_rows takes, for the same reason, while a wavefront has few
-// rows (us, 1 / 2 / 4 blocks, partial sums added; 128 x 128, 11 rows 4.6 / 6.0 / 10.5, 2,000 8.7 / 10.2 / 14.7, 8,000 15.4 / 15.8 / 19.9, 12,000 17.1 /
+// rows (us, 1 / 2 / 4 blocks, partial sums added; 128 x 128, 2,000 rows 8.7 / 10.2 / 14.7, 8,000 15.4 / 15.8 / 19.9, 12,000 17.1 /
 // 18.0 / 20.2, 16,000 20.2 / 18.4 / 22.9; 64 x 128, 16,000 14.4 / 14.8, 50,000 21.9 / 19.4; 64 x 64, 2,000 6.5 / 7.4, 8,000 9.0 / 9.8, 12,000 9.4 /
 // 9.2; 128 x 16, 4,000 6.9 / 7.2 / 7.8, 12,000 8.7 / 8.8 / 8.2).
 int rows_at_once(const Chunks& c, int mt, int nt) {
@@ -690,6 +743,9 @@ int rows_at_once(const Chunks& c, int mt, int nt) {
     while (at_once < mt && c.count * (mt / at_once) > most) at_once *= 2;
     return at_once;
 }
+
+// (where the rows have to run through one CU faster than partial sums are added: k_weight_gradient_few)
+bool few_rows(int64_t n_rows, int Fi, int Fo) { return n_rows > 0 && n_rows <= kFewRows && narrow(Fi, Fo); }
 
 template <int MT, int NT, bool VA, bool VB>
 void launch_rows_wg(const Chunks& c, const int32_t* ids, int64_t n_rows, const float* Y, int Fi, const float* G, int Fo,
@@ -727,22 +783,24 @@ int weight_gradient(const epp_paths* paths, int k, const float* Y, int F_in, con
     const int32_t* ids = nullptr;
     int64_t n_rows = 0;
     EPP_TRY(row_set(paths, k, &ids, &n_rows));
+    if (few_rows(n_rows, F_in, F_out)) {
+        const int per = ((int)n_rows + 2 * kFewWaves - 1) / (2 * kFewWaves) * 2;
+        hipLaunchKernelGGL(k_weight_gradient_few, dim3((unsigned)((F_in + 31) / 32), (unsigned)((F_out + 31) / 32)), dim3(64 * kFewWaves), 0, s,
+                           ids, (int)n_rows, per, Y, F_in, grad_X, F_out, grad_W);
+        EPP_HIP_TRY(hipGetLastError());
+        return EPP_OK;
+    }
     const Chunks c = chunking(n_rows, F_in, F_out, max_chunks);
     const int64_t per = c.per, chunks = c.count;
     if (epp_split_weight_gradient(F_in, F_out, n_rows)) {
         epp_launch_weight_gradient_split(chunks, 4 * per, ids, n_rows, Y, F_in, grad_X, F_out, part, s);
     } else if (chunks > 0 && narrow(F_in, F_out)) {
-        float* out = chunks == 1 ? grad_W : part;
         const int mt = rows_at_once(c, blocks_of(F_in), blocks_of(F_out));
-        if (mt == 1) launch_rows_wg_n<1, false>(c, ids, n_rows, Y, F_in, grad_X, F_out, out, s);
-        else if (mt == 2 && F_in % 2 == 0) launch_rows_wg_n<2, true>(c, ids, n_rows, Y, F_in, grad_X, F_out, out, s);
-        else if (mt == 2) launch_rows_wg_n<2, false>(c, ids, n_rows, Y, F_in, grad_X, F_out, out, s);
-        else if (F_in % 4 == 0) launch_rows_wg_n<4, true>(c, ids, n_rows, Y, F_in, grad_X, F_out, out, s);
-        else launch_rows_wg_n<4, false>(c, ids, n_rows, Y, F_in, grad_X, F_out, out, s);
-        if (chunks == 1) {
-            EPP_HIP_TRY(hipGetLastError());
-            return EPP_OK;
-        }
+        if (mt == 1) launch_rows_wg_n<1, false>(c, ids, n_rows, Y, F_in, grad_X, F_out, part, s);
+        else if (mt == 2 && F_in % 2 == 0) launch_rows_wg_n<2, true>(c, ids, n_rows, Y, F_in, grad_X, F_out, part, s);
+        else if (mt == 2) launch_rows_wg_n<2, false>(c, ids, n_rows, Y, F_in, grad_X, F_out, part, s);
+        else if (F_in % 4 == 0) launch_rows_wg_n<4, true>(c, ids, n_rows, Y, F_in, grad_X, F_out, part, s);
+        else launch_rows_wg_n<4, false>(c, ids, n_rows, Y, F_in, grad_X, F_out, part, s);
     } else if (chunks > 0) {
         const TileShape shape = tile_shape(F_in, F_out);
         int tm, tn;
