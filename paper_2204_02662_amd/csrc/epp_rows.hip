@@ -417,7 +417,7 @@ bool epp_rows_kernel_fits(const epp_path* p, int F) {
     return (F < 32 || F % 4 != 0) && p->nnz * F <= 100000000 && p->n_src * F <= 28000000;
 }
 
-// The path's own list takes no launch of its own and no wait.  It goes down to the chunks that launches on this many entries have (see
+// The path's own list takes no launch of its own.  It goes down to the chunks that launches on this many entries have (see
 // above: over 48 M, none of more than 4 floats; 17 and 33 floats are the first of 16 and 32 bytes more a lane), since a place
 // for every row that there could be is 16 bytes for every 2^(log2 - 1) entries.  Import and first epoch of
 // the blog graph (4.2 M entries, F = 16 / 39): 153.5 us with the rows listed width by width, 120.2 with the path's own list.
@@ -454,8 +454,9 @@ int epp_build_rows_plan(epp_path* p, int F, hipStream_t s, RowsPlan** out) {
         hipLaunchKernelGGL(k_list_long_rows, dim3((unsigned)((p->n_stream_rows + kBlock - 1) / kBlock)), dim3(kBlock), 0, s,
                            p->rowptr.as<int32_t>(), p->row_ids.p ? p->row_ids.as<int32_t>() : nullptr, (int)p->n_stream_rows, list);
         EPP_HIP_TRY(hipGetLastError());
-        EPP_HIP_TRY(hipStreamSynchronize(s));
     }
+    // (also where nothing was launched: launches may run on another stream than the one whose work the block of memory was last used by)
+    EPP_HIP_TRY(hipStreamSynchronize(s));
     q->rows = list.rows;
     q->head = list.head;
     q->pieces = reinterpret_cast<float*>(q->store.as<char>() + at);
