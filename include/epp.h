@@ -6,6 +6,10 @@
  * code; epp_last_error() then holds a human-readable message for the calling thread.  No
  * function aborts or throws across this boundary.  A handle (epp_paths_t / epp_path_t) must
  * not be used by two calls at the same time (calls on one stream, one after the other, are fine).
+ * What aggregations over one handle enqueue must not overlap on the GPU either (two streams: an
+ * event between them; a captured graph likewise): launches write scratch memory of the handle, which
+ * the paths of an epp_paths_t share.  (Different widths of paths that run without tables, see
+ * EPP_TUNE_ROWS, share none, and the products of the combination stage write none.)
  *
  * Environment variables read when paths or a width are prepared (measurement knobs; defaults in brackets):
  *   EPP_TUNE_GS           group size for every (path, F) that has none forced            [selector]

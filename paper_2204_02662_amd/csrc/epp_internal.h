@@ -235,8 +235,12 @@ struct Partition {
     }
 };
 
-// A row that the row kernel (epp_rows.hip) may cut into chunks: vertex, entries; 0, during a launch how many chunks it has summed.
-struct LongRow { int v, begin, end; unsigned done; };
+// A row that the row kernel (epp_rows.hip) may cut into chunks: vertex, entries; for each of the widths that may use the list, 0, and during
+// a launch how many chunks it has summed.  Every width counts for itself: widths cut a row into different numbers of chunks, and launches
+// of two of them may be in flight at once.
+constexpr int kLongUsers = 5;
+struct LongRow { int v, begin, end; unsigned done[kLongUsers]; };
+static_assert(sizeof(LongRow) == 32, "a row of the list lies in one line");
 // The rows of a path of `nnz` entries with more than 2^log2 of them, those of every length class (2^(c-1) < length <= 2^c) beside each
 // other, in any order, behind a place for every row that the shorter classes could have.
 struct LongRows {
@@ -268,7 +272,7 @@ __device__ __forceinline__ void list_long_rows(const LongRows& l, int v, int beg
     __syncthreads();
     if (!is_long) return;
     const int first = l.first_place(c), place = found[EPP_NCLASS + c] + at;
-    if (place < l.nnz >> (c - 1)) l.rows[first + place] = LongRow{v, begin, begin + len, 0u};
+    if (place < l.nnz >> (c - 1)) l.rows[first + place] = LongRow{v, begin, begin + len, {}};
 }
 // The first places, by one workgroup of those that list.
 __device__ __forceinline__ void place_long_rows(const LongRows& l) {
@@ -278,11 +282,14 @@ __device__ __forceinline__ void place_long_rows(const LongRows& l) {
 // What the row kernel needs to know of the rows that one workgroup should not take alone: they are cut into chunks, whose sums the last
 // workgroup of the row's adds.
 struct RowsPlan {
-    DevBuf store;  // the pieces, and the rows where the path has no list of them
+    DevBuf store;  // the pieces, and the rows where the path has no list of them, or none with a count to spare
     LongRow* rows = nullptr;
     const int* head = nullptr;
     float* pieces = nullptr;  // float[n_chunks][F]
     int n_chunks = 0;
+    int user = 0;             // which of a row's counts is this width's
+    unsigned* taken = nullptr;  // the path's list is used: the path's bits of the counts that are
+    ~RowsPlan() { if (taken) *taken &= ~(1u << user); }
 };
 
 // What a build of tiles has shown about the order of a path's entries, whichever the width; per number of lanes.
@@ -324,6 +331,7 @@ struct epp_path {
     int64_t n_stream_rows = 0;
     DevBuf store;                // one allocation behind row_ids, rowptr, long_rows and cv where they are views of it
     LongRows long_rows;          // (a path of a construction or an import, where the row kernel may ask for it)
+    unsigned long_rows_taken = 0;  // which of its rows' counts belong to a width
     DevBuf row_ids;              // int32[n_stream_rows] vertex of each streamed row; unset: identity
     DevBuf rowptr;               // int32[n_stream_rows + 1]
     DevBuf cv;                   // int2[nnz]: (column word, weight bits)

@@ -63,6 +63,7 @@ struct RowArgs {
     const int32_t* rowptr;
     const int32_t* row_ids;  // NULL: identity
     int n_rows;
+    int user;                // which of a cut row's counts is this width's
     const float* in;
     float* out;
     int F;
@@ -252,7 +253,7 @@ __device__ __forceinline__ void sum_chunk(const RowArgs& a, float (*part)[(1 << 
     });
     if (threadIdx.x < 64) {
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        if (threadIdx.x == 0) *was = (int)atomicInc(&h->done, (unsigned)count - 1u);  // (0 again behind the last one)
+        if (threadIdx.x == 0) *was = (int)atomicInc(&h->done[a.user], (unsigned)count - 1u);  // (0 again behind the last one)
     }
     __syncthreads();
     if (*was != count - 1) return;
@@ -440,7 +441,10 @@ int epp_build_rows_plan(epp_path* p, int F, hipStream_t s, RowsPlan** out) {
     struct Guard { RowsPlan* q; ~Guard() { delete q; } } guard{q};
     LongRows list = p->long_rows;
     size_t at = 0;
-    const bool listed = list.rows && list.log2 <= c0;
+    // (up to kLongUsers widths of a path take its list; the others each make one of their own)
+    while (q->user < kLongUsers && ((p->long_rows_taken >> q->user) & 1u)) ++q->user;
+    const bool listed = list.rows && list.log2 <= c0 && q->user < kLongUsers;
+    if (!listed) q->user = 0;
     if (!listed) {
         list.log2 = c0;
         list.nnz = (int)p->nnz;
@@ -460,6 +464,10 @@ int epp_build_rows_plan(epp_path* p, int F, hipStream_t s, RowsPlan** out) {
     q->rows = list.rows;
     q->head = list.head;
     q->pieces = reinterpret_cast<float*>(q->store.as<char>() + at);
+    if (listed) {
+        q->taken = &p->long_rows_taken;
+        p->long_rows_taken |= 1u << q->user;
+    }
     q->n_chunks = (int)n_chunks;  // (an upper bound: a workgroup whose chunk its row does not have ends at once)
     guard.q = nullptr;
     *out = q;
@@ -474,6 +482,7 @@ int epp_launch_rows(const epp_path* p, const RowsPlan* plan, const float* in, fl
     a.rowptr = p->rowptr.as<int32_t>();
     a.row_ids = p->row_ids.p ? p->row_ids.as<int32_t>() : nullptr;
     a.n_rows = (int)p->n_stream_rows;
+    a.user = plan ? plan->user : 0;
     a.in = in;
     a.out = out;
     a.F = F;
