@@ -1134,6 +1134,10 @@ static int tile_ahead(int lanes, double missed) {
     if (lanes == 8) return missed < 0.10 ? 4 : missed < 0.33 ? 3 : 2;
     return missed < 0.06 ? 0 : 3;
 }
+// Whether there is such a kernel (epp_launch_tiles): a switch of the environment may ask for any number.
+static bool tile_ahead_built(int lanes, int ahead) {
+    return lanes == 4 ? ahead == 4 : lanes == 8 ? ahead >= 2 && ahead <= 4 : ahead == 0 || ahead == 3;
+}
 
 static double tile_launch_us(const epp_path* p, const Sources& src, int F, int lanes) {
     struct Cost { double launch, sweep, entry, line_cached, line_missed, row, copy; };  // us; ps per entry, line, row and byte
@@ -1271,7 +1275,8 @@ int epp_build_tiles(epp_path* p, int lanes, double max_delay, hipStream_t s, Til
     q->at_once = std::max(env_int("EPP_TUNE_TILES_AT_ONCE", kTilesAtOnce) / 512, 1) * 512;  // (whole groups of kTogether tiles per XCD)
     const int64_t rows_at_once = (int64_t)q->at_once * rows_per_tile;
     q->lanes = lanes;
-    q->ahead = env_int("EPP_TUNE_TILE_AHEAD", tile_ahead(lanes, tile_sweeps(Sources(p), lanes, 1.0).missed / (double)p->nnz));
+    q->ahead = env_int("EPP_TUNE_TILE_AHEAD", -1);
+    if (!tile_ahead_built(lanes, q->ahead)) q->ahead = tile_ahead(lanes, tile_sweeps(Sources(p), lanes, 1.0).missed / (double)p->nnz);
     q->far = env_int("EPP_TUNE_TILE_FAR", 0) != 0;
     q->n_tiles = (int)((n_rows + rows_at_once - 1) / rows_at_once * q->at_once);
     q->n_parts = n_parts;
@@ -1351,13 +1356,14 @@ int epp_launch_tiles(const epp_path* p, const TilePlan* q, float* parts, const f
     a.records = bytes <= (int64_t)kNowhere && !q->far ? (unsigned)bytes : 0u;
     a.zero = inner_rows ? p->zero_block.as<float>() : nullptr;
     a.inner_rows = inner_rows;
-    switch (q->lanes * 16 + q->ahead) {
+    switch (q->lanes * 16 + q->ahead) {  // (all that tile_ahead_built lets through)
         case 4 * 16 + 4: launch_tiles<4, 4>(a, t.slices, s); break;
         case 8 * 16 + 2: launch_tiles<8, 2>(a, t.slices, s); break;
         case 8 * 16 + 3: launch_tiles<8, 3>(a, t.slices, s); break;
         case 8 * 16 + 4: launch_tiles<8, 4>(a, t.slices, s); break;
+        case 16 * 16 + 0: launch_tiles<16, 0>(a, t.slices, s); break;
         case 16 * 16 + 3: launch_tiles<16, 3>(a, t.slices, s); break;
-        default: launch_tiles<16, 0>(a, t.slices, s); break;
+        default: epp_set_error("no kernel for tiles of %d lanes, %d ahead", q->lanes, q->ahead); return EPP_ERR_INVALID_ARG;
     }
     if (q->n_cut > 0) {
         int log2T = 0;

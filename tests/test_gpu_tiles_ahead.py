@@ -44,3 +44,22 @@ def test_windows_and_addresses(lanes, aheads, F, monkeypatch):
                     assert_close(got[rows], want[rows], what)
                     first = got if first is None else first
                     assert np.array_equal(got, first), what
+
+
+@pytest.mark.parametrize("lanes,aheads", [(4, (-1, 0, 2, 3, 5, 196)), (8, (-1, 0, 1, 5, 128, 131)), (16, (-1, 1, 2, 4, 8))])
+def test_windows_that_do_not_exist(lanes, aheads, monkeypatch):
+    """A switch that asks for one leaves the choice as it is: a launch never runs a kernel made for other lanes than its plan's."""
+    for k, v in {"ROWS": 0, "TILES": 2, "TILE_LANES": lanes, "TILES_AT_ONCE": 512, "SMALL_PREPARE": 0}.items():
+        monkeypatch.setenv("EPP_TUNE_" + k, str(v))
+    g = graphgen.random_graph("rmat", 60_001, seed=171, raw_draws=500_000)
+    train, F = graphgen.training_set(g.n, 6_000, 172), 33
+    sets_o, paths_o = oracle.prepare(g.n, g.rowptr, g.col, g.val, train, 1)
+    X = graphgen.normal_rows(g.n, F, sets_o[0], 175)
+    want = oracle.path_aggregate(g.n, paths_o[0], X)
+    for ahead in aheads:
+        monkeypatch.setenv("EPP_TUNE_TILE_AHEAD", str(ahead))
+        p = gpu_prepare(g, train, 1).path(0)
+        p.prepare_width(F)
+        out = torch.zeros(g.n, F, device=dev())
+        epp.epp_backward_aggregate(p, torch.from_numpy(X).to(dev()), out)
+        assert_close(out.cpu().numpy(), want, f"lanes={lanes} ahead={ahead}")
