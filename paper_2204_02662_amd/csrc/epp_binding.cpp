@@ -269,10 +269,26 @@ PyObject* allocator(PyObject*, PyObject*) {
     return Py_BuildValue("KK", (unsigned long long)reinterpret_cast<uintptr_t>(&torch_alloc),
                          (unsigned long long)reinterpret_cast<uintptr_t>(&torch_free));
 }
-// (allocations, releases, bytes) since the process began
-PyObject* alloc_counts(PyObject*, PyObject*) {
-    return Py_BuildValue("LLL", g_allocs.load(std::memory_order_relaxed), g_frees.load(std::memory_order_relaxed),
-                         g_bytes.load(std::memory_order_relaxed));
+// alloc_news(dictionary): adds to its allocs, frees, bytes and live what has been counted since the last call.
+PyObject* alloc_news(PyObject*, PyObject* stats) {
+    if (!PyDict_Check(stats)) {
+        PyErr_SetString(PyExc_TypeError, "alloc_news(dictionary)");
+        return nullptr;
+    }
+    if (!g_allocs.load(std::memory_order_relaxed) && !g_frees.load(std::memory_order_relaxed)) Py_RETURN_NONE;
+    const long long allocs = g_allocs.exchange(0, std::memory_order_relaxed), frees = g_frees.exchange(0, std::memory_order_relaxed);
+    const struct { const char* key; long long more; } news[] = {
+        {"allocs", allocs}, {"frees", frees}, {"bytes", g_bytes.exchange(0, std::memory_order_relaxed)}, {"live", allocs - frees}};
+    for (const auto& x : news) {
+        PyObject* const had = PyDict_GetItemString(stats, x.key);  // (borrowed; none: taken for 0)
+        PyObject* const more = PyLong_FromLongLong(x.more);
+        PyObject* const sum = more && had ? PyNumber_Add(had, more) : more;
+        const bool done = sum && PyDict_SetItemString(stats, x.key, sum) == 0;
+        if (had) Py_XDECREF(more);
+        Py_XDECREF(sum);
+        if (!done) return nullptr;
+    }
+    Py_RETURN_NONE;
 }
 
 // init(error class, raw-stream function)
@@ -307,7 +323,7 @@ PyMethodDef methods[] = {
      "epp_input_gradient(paths, k, grad_X, W, grad_Y)\n\nY' = X' (x) W^T on the rows of N^k (k = -1: all rows); other rows "
      "of grad_Y are not touched."},
     {"allocator", allocator, METH_NOARGS, nullptr},
-    {"alloc_counts", alloc_counts, METH_NOARGS, nullptr},
+    {"alloc_news", alloc_news, METH_O, nullptr},
     {nullptr, nullptr, 0, nullptr}};
 
 PyModuleDef module = {PyModuleDef_HEAD_INIT, "_binding", nullptr, -1, methods, nullptr, nullptr, nullptr, nullptr};
