@@ -343,17 +343,34 @@ try:
     _init_binding(EppError, _raw_stream)
     _addresses = _native_allocator()
     _TORCH_ALLOC_FN, _TORCH_FREE_FN = _ALLOC_FN(_addresses[0]), _FREE_FN(_addresses[1])
-    _TORCH_ALLOC = _Alloc(_TORCH_ALLOC_FN, _TORCH_FREE_FN, None)
 except ImportError as _e:  # not built yet: the package can be imported (to build it), these calls raise
     def _not_built(*_args, _why=str(_e), **_kw):
         raise FileNotFoundError(f"{PKG}/_binding is not usable ({_why}): run `python -m paper_2204_02662_amd.build`")
     epp_backward_aggregate = epp_full_aggregate = epp_input_gradient = _not_built
-    epp_weight_gradient = epp_weight_gradient_static = _TORCH_ALLOC_FN = _TORCH_FREE_FN = _not_built
+    epp_weight_gradient = epp_weight_gradient_static = _not_built
 
+    # (what goes through ctypes runs all the same, and on PyTorch's memory: NULL functions would be hipMalloc's)
     def _alloc_news(stats):
         pass
 
-    _TORCH_ALLOC = _Alloc()
+    @_ALLOC_FN
+    def _TORCH_ALLOC_FN(nbytes, _ctx):
+        try:
+            ptr = torch.cuda.caching_allocator_alloc(int(nbytes))
+        except Exception:  # out of memory: the library reports EPP_ERR_ALLOC
+            return None
+        alloc_stats["allocs"] += 1
+        alloc_stats["bytes"] += int(nbytes)
+        alloc_stats["live"] += 1
+        return ptr
+
+    @_FREE_FN
+    def _TORCH_FREE_FN(ptr, _ctx):
+        alloc_stats["frees"] += 1
+        alloc_stats["live"] -= 1
+        torch.cuda.caching_allocator_delete(ptr)
+
+_TORCH_ALLOC = _Alloc(_TORCH_ALLOC_FN, _TORCH_FREE_FN, None)
 
 
 def epp_paths_import(n: int, train_ids: torch.Tensor, layers, torch_allocator: bool = True) -> Paths:
