@@ -694,7 +694,10 @@ int columns_at_once(int64_t tiles, int kc, int nt) {
     return per;
 }
 
-// How the rows are cut into partial sums (at most `max_chunks` of them).
+// (where the rows have to run through one CU faster than partial sums are added: k_weight_gradient_few)
+bool few_rows(int64_t n_rows, int Fi, int Fo) { return n_rows > 0 && n_rows <= kFewRows && narrow(Fi, Fo); }
+
+// How the rows are cut into partial sums (at most `max_chunks` of them); not for few rows.
 struct Chunks {
     int64_t per;    // rows per chunk; narrow widths: rows per wavefront
     int64_t count;  // partial sums
@@ -708,11 +711,10 @@ Chunks chunking(int64_t n_rows, int Fi, int Fo, int64_t max_chunks) {
         // follow each other in a wavefront, and what the partial sums cost to write and add (64 rows a wavefront, or
         // 16 wavefronts for up to 1,024 rows -> this: 869 rows, 64 x 64 24.7 -> 7.5 us, 16 x 16 11.6 -> 6.6, 96 x 96
         // 40.7 -> 14.6; 30,000 rows, 64 x 64 16.0 -> 15.2, 96 x 96 46 -> 29).  One block: half as many partial sums, until
-        // that is 64 rows a wavefront (32 x 32, 16,000 rows 9.1 -> 8.2 us).  (Up to kFewRows rows need no partial sums; callers still bring the
-        // workspace that this makes of them.)
+        // that is 64 rows a wavefront (32 x 32, 16,000 rows 9.1 -> 8.2 us).
         if (n_rows <= 65536) {
-            const int64_t chains = tiles == 1 && n_rows <= 64 ? 4 : tiles <= 4 && n_rows <= 256 ? 16 : tiles == 1 ? 512 : 1024;
-            c.per = std::max<int64_t>((n_rows + chains - 1) / chains, chains <= 16 ? 2 : 16);
+            const int64_t chains = tiles == 1 ? 512 : 1024;
+            c.per = std::max<int64_t>((n_rows + chains - 1) / chains, 16);
             if (tiles == 1) c.per = std::min<int64_t>(c.per, 64);  // (256 partial sums at most, whatever the widths)
         } else {
             const int64_t want = std::min<int64_t>(tiles >= 8 ? 512 : 1024, std::max<int64_t>(max_chunks, 1));
@@ -744,9 +746,6 @@ int rows_at_once(const Chunks& c, int mt, int nt) {
     return at_once;
 }
 
-// (where the rows have to run through one CU faster than partial sums are added: k_weight_gradient_few)
-bool few_rows(int64_t n_rows, int Fi, int Fo) { return n_rows > 0 && n_rows <= kFewRows && narrow(Fi, Fo); }
-
 template <int MT, int NT, bool VA, bool VB>
 void launch_rows_wg(const Chunks& c, const int32_t* ids, int64_t n_rows, const float* Y, int Fi, const float* G, int Fo,
                     float* out, hipStream_t s) {
@@ -770,8 +769,9 @@ extern "C" int64_t epp_weight_gradient_workspace(const epp_paths_t* paths, int k
     if (!paths) { epp_set_error("NULL argument"); return EPP_ERR_INVALID_ARG; }
     if (k < -1 || k > paths->L) { epp_set_error("k=%d outside [-1, %d]", k, paths->L); return EPP_ERR_INVALID_ARG; }
     if (check_widths(F_in, F_out) != EPP_OK) return EPP_ERR_INVALID_ARG;
-    const Chunks c = chunking(k < 0 ? paths->n : paths->set_size[k], F_in, F_out, kNoChunkLimit);
-    return std::max<int64_t>(c.count, 1) * F_in * F_out * (int64_t)sizeof(float);
+    const int64_t n_rows = k < 0 ? paths->n : paths->set_size[k];
+    const int64_t sums = few_rows(n_rows, F_in, F_out) ? 1 : std::max<int64_t>(chunking(n_rows, F_in, F_out, kNoChunkLimit).count, 1);
+    return sums * F_in * F_out * (int64_t)sizeof(float);
 }
 
 namespace {

@@ -38,3 +38,23 @@ def test_edges(rows, Fi, Fo):
         epp.epp_weight_gradient_static(paths, 0, Y, X, got)
         assert torch.equal(got[0], torch.where(X[ids[-1].long()] > 0, float("inf"), float("-inf")))
         assert torch.isfinite(got[1:]).all()
+
+
+@pytest.mark.parametrize("Fi,Fo", [(5, 4), (41, 64), (128, 128), (129, 16)])
+def test_workspace(Fi, Fo):
+    """One block of W', the least there is, where no partial sums are formed; as many as the rows make beyond, and at other widths."""
+    for rows in (0, 1, 60, 256, 384, 385, 2_000):
+        eye = torch.arange(2_001, dtype=torch.int32, device=dev())
+        paths = epp.epp_prepare(2_000, eye, eye[:2_000].clone(), torch.ones(2_000, device=dev()), eye[:rows].clone(), 1)
+        blocks, rest = divmod(epp.epp_weight_gradient_workspace(paths, 0, Fi, Fo), Fi * Fo * 4)
+        assert rest == 0 and (blocks == 1 if rows <= 384 and max(Fi, Fo) <= 128 else blocks >= 1), rows
+        if rows >= 385 and max(Fi, Fo) <= 128:
+            assert blocks == -(-rows // 64)
+        Y, X = torch.ones(2_000, Fi, device=dev()), torch.ones(2_000, Fo, device=dev())
+        need = blocks * Fi * Fo * 4
+        held = torch.full((need + 256,), 7, dtype=torch.uint8, device=dev())
+        got = torch.empty(Fi, Fo, device=dev())
+        epp.epp_weight_gradient(paths, 0, Y, X, got, held[:need])
+        assert torch.all(got == rows) and torch.all(held[need:] == 7), rows
+        with pytest.raises(epp.EppError):
+            epp.epp_weight_gradient(paths, 0, Y, X, got, held[:need - 16])
