@@ -398,6 +398,8 @@ static_assert((1 << 13) == 8 * kBlock * kU, "chunk length");
 // to 1.20 and 0.93 on average; at 3 to 7 M vertices' rows of 140 MB and more 0.9 to 1.3); up to 64 M of 40 MB at F = 32 (0.60 to 0.91) and
 // 48 M at F = 64 (0.73 to 0.94).  The group kernel's aligned loads are as fast or faster for other multiples of 4 (F = 36 to 60, 16 to
 // 100 M: 0.73 to 1.53).
+constexpr int64_t kMostNarrow = 48000000;   // entries: no path of more runs here at more than 4 floats a row, 8 floats having the most
+constexpr int64_t kMostGathered = 100000000;  // floats of gathered rows, at more than 16 floats a row
 bool epp_rows_kernel_fits(const epp_path* p, int F) {
     if (const char* e = std::getenv("EPP_TUNE_ROWS")) {  // 0: never, 2: always (tests, measurements)
         if (*e == '0') return false;
@@ -410,22 +412,24 @@ bool epp_rows_kernel_fits(const epp_path* p, int F) {
     if (epp_group_table_asked()) return false;
     double any_delay;
     if (F <= 16) {
-        const int64_t most = F <= 7 ? 30000000 : F == 8 ? 48000000 : F <= 10 ? 20000000 : F <= 13 || F == 16 ? 12000000 : 8000000;
+        const int64_t most = F <= 7 ? 30000000 : F == 8 ? kMostNarrow : F <= 10 ? 20000000 : F <= 13 || F == 16 ? 12000000 : 8000000;
         return p->nnz <= most && epp_tile_lanes(p, F, &any_delay) == 0;
     }
     if (F > 64) return false;
     if (F == 32 || F == 64) return p->nnz * F <= (F == 32 ? 64000000 : 48000000) && p->n_src * F <= 10000000;
-    return (F < 32 || F % 4 != 0) && p->nnz * F <= 100000000 && p->n_src * F <= 28000000;
+    return (F < 32 || F % 4 != 0) && p->nnz * F <= kMostGathered && p->n_src * F <= 28000000;
 }
 
-// The path's own list takes no launch of its own.  It goes down to the chunks that launches on this many entries have (see
-// above: over 48 M, none of more than 4 floats; 17 and 33 floats are the first of 16 and 32 bytes more a lane), since a place
-// for every row that there could be is 16 bytes for every 2^(log2 - 1) entries.  Import and first epoch of
+// The path's own list takes no launch of its own.  It goes down to the shortest chunks that launches on this many entries have, those
+// of the widest rows that the rule above lets run here, since a place for every row that there could be is 32 bytes for every
+// 2^(log2 - 1) entries; but not below 2^9: wider rows than 64 floats run here on up to 250,000 entries only, and list for themselves.  Import and first epoch of
 // the blog graph (4.2 M entries, F = 16 / 39): 153.5 us with the rows listed width by width, 120.2 with the path's own list.
 size_t epp_plan_long_rows(int64_t nnz, LongRows* l) {
     *l = LongRows{};
-    if (nnz > 48000000) return 0;
-    l->log2 = nnz > 100000000 / 17 ? 11 : nnz > 100000000 / 33 ? 10 : 9;
+    if (nnz > kMostNarrow) return 0;
+    int widest = 16;  // (in steps that change the chunks: one more lane a row)
+    while (widest < 64 && nnz * (widest + 1) <= kMostGathered) widest *= 2;
+    l->log2 = chunk_log2(widest);
     l->nnz = (int)nnz;
     return (size_t)l->first_place(EPP_NCLASS) * sizeof(LongRow);
 }
