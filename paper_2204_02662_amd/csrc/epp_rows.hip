@@ -223,8 +223,11 @@ __device__ __forceinline__ void sum_by_workgroup(const RowArgs& a, float* __rest
 
 // One chunk of a cut row.  The workgroup that is the last of the row's to be done adds the chunks' sums, in an order that depends on their
 // number alone (a launch of its own for that took 4 to 5 us and the gap before it: an epoch of 88,784 vertices, F = 16 / 39, and what
-// comes before it 177 -> 167 us, the backward loop of 1.1 M vertices, F = 16 / 41, 228.6 -> 223.1).  Sums are written and read past the
-// L2, of which every XCD has its own; the wait before the count is for the writes to have arrived.
+// comes before it 177 -> 167 us, the backward loop of 1.1 M vertices, F = 16 / 41, 228.6 -> 223.1).
+// Sums are written and read past the L2, of which every XCD has its own: relaxed atomics of agent scope, which this GPU's instructions do
+// that with (sc1), and a wait for the writes to have arrived before they are counted.  The language orders relaxed atomics of different
+// words by fences alone; a release here and an acquire by the last workgroup are the same order with the whole L2 written back and
+// dropped (223.9 -> 231.3 us of that loop, the blog graph's import and first epoch 112.6 -> 122.8).  A test reads the instructions.
 template <int VEC, int LOG2T, bool INNER>
 __device__ __forceinline__ void sum_chunk(const RowArgs& a, float (*part)[(1 << LOG2T) * VEC], int* was) {
     const int b = (int)blockIdx.x;

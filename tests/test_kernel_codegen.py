@@ -77,3 +77,28 @@ def test_gathers_of_a_batch_are_issued_back_to_back(compiled):
         assert waits <= 1, f"VEC={vec} LOG2T={log2t} if-else={ifelse} cold={cold} part={part} inner={inner}: {waits} full waits between gathers"
         checked += 1
     assert checked >= 120, checked
+
+
+def test_chunk_sums_of_cut_rows_go_past_the_l2(tmp_path):
+    """The row kernel's workgroups hand each other the sums of a cut row's chunks without fences: every sum has to be stored and loaded with
+    sc1 (past the L2 of one XCD), and the stores waited for before the one atomic that counts them."""
+    src = SRC.parent / "epp_rows.hip"
+    subprocess.run(["hipcc", "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+                    f"-I{ROOT / 'include'}", f"-I{SRC.parent}", "--cuda-device-only", "-S", str(src), "-o", "rows.s"], cwd=tmp_path, check=True,
+                   capture_output=True, timeout=900)
+    asm = (tmp_path / "rows.s").read_text()
+    checked = 0
+    for m in re.finditer(r"^(_ZN\S*k_aggregate_rowsILi(\d)ELi(\d)ELb([01])E\S*):(.*?)^\.Lfunc_end", asm, re.S | re.M):
+        vec, what = int(m.group(2)), f"VEC={m.group(2)} LOG2T={m.group(3)} inner={m.group(4)}"
+        lines = [x.strip() for x in m.group(5).split("\n") if x.strip() and not x.strip().startswith((";", "."))]
+        count = [i for i, x in enumerate(lines) if x.startswith("global_atomic_inc")]
+        assert len(count) == 1, what
+        stores = [i for i, x in enumerate(lines) if x.startswith("global_store") and x.endswith("sc1")]
+        loads = [i for i, x in enumerate(lines) if x.startswith("global_load") and x.endswith("sc1")]
+        widths = {"dword": 1, "dwordx2": 2, "dwordx3": 3, "dwordx4": 4}
+        floats = lambda at: sum(widths[re.match(r"global_(?:load|store)_(\w+)", lines[i]).group(1)] for i in at)
+        assert floats(stores) == vec and max(stores) < count[0], what
+        assert floats(loads) == 4 * vec and min(loads) > count[0], what  # four chunks on their way at once
+        assert any(re.match(r"s_waitcnt vmcnt\(0\)", x) for x in lines[max(stores) + 1:count[0]]), what
+        checked += 1
+    assert checked == 20, checked  # (4 floats on 1 to 64 lanes; 1, 2 and 3 floats), for a path and for an inner one
