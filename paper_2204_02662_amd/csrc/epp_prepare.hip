@@ -81,11 +81,10 @@ __global__ __launch_bounds__(kBlock) void k_mark_training(const int32_t* __restr
 
 // The same, with the ascending ids and their number, by one workgroup that keeps the bitmap in LDS: for up to
 // kSetVertices vertices and kSetIds training ids (marking, counting, scanning and listing are four
-// launches of 4.5 us otherwise, whatever they process).
+// launches of 4.5 us otherwise, whatever they process).  It also clears the results of the kernels to come (`clear`, up to kSetClear
+// bytes; a memset is a launch of 5 us with the gap before it).
 constexpr int kSetVertices = 524288, kSetIds = 65536;
-constexpr size_t kSetClear = 262144;  // bytes
-//
-// It also clears the results of the kernels to come (`clear`; a memset is a launch of 5 us with the gap before it).
+constexpr size_t kSetClear = 262144;
 __global__ __launch_bounds__(1024) void k_training_set(const int32_t* __restrict__ ids, int n_ids, int n,
                                                        unsigned long long* __restrict__ bitmap, int32_t* __restrict__ ids_out,
                                                        long long* count, int* err, ulonglong2* clear, int clear_pairs) {
@@ -179,7 +178,6 @@ __device__ __forceinline__ void store_tile(const MaskArgs& a, int64_t tile, bool
     if (a.count && lane == 0) a.tile_count[tile] = run;
 }
 
-//
 // THREADS: 1,024, or 256 where the tiles are few and sixteen wavefronts would share one of a few CUs (0.5 M entries 9.3 -> 5.5 us, 4.2 M
 // 10.0 -> 9.6).
 template <int WORDS, int THREADS>

@@ -1128,6 +1128,8 @@ static Sweeps tile_sweeps(const Sources& src, int lanes, double per_line) {
 //   1201 / 1336 / 1198 / 1225; 1 M, 89 M, 0.21 809 / 857 / 806 / 851; 8.4 M, 0.25 1592 / 1709 / 1601 / 1640; 3 M, 0.37 2710 / 2746 / 2804 / 3064; 5 M,
 //   0.61 2044 / 1971 / 2018 / 2105; 2.4 M, 140 M,
 //   F = 64 3220 / 3082 / 3142 / 3431; dense ones, 1.1 M, 252 M, 0.12 1.09 to 1.15 of a batch at a time with 4.
+// 16 lanes that hardly miss: a batch at a time is the fastest over the three launches below 0.06 together (2703; 3 pairs 2794, 4 pairs 2730),
+// not in each.  Two pairs, which only half of the gathers missing pays for (6468 of 6653), are no kernel for 16 lanes.
 // 4 lanes need both batches in flight everywhere (114 M entries, 233 K sources, F = 16: 697 us without, 575 with one, 541 with two).
 static int tile_ahead(int lanes, double missed) {
     if (lanes == 4) return 4;
