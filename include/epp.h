@@ -22,8 +22,8 @@
  *   EPP_TUNE_TILE_AHEAD   how far a launch on tiles gathers ahead of its additions: 4 with 4 lanes, 2 to 4 with 8, 0 or 3
  *                         with 16; anything else leaves the choice to the library      [chosen per path]
  *   EPP_TUNE_TILE_FAR     1: launches on tiles address source rows with 64 bits at any size of the matrix  [0]
- *   EPP_TUNE_TILE_SPLIT, EPP_TUNE_TILES_AT_ONCE   entries from which on a row is cut into parts, and tiles that share out
- *                         the rows, in multiples of 512                                 [chosen by the library]
+ *   EPP_TUNE_TILE_SPLIT   longest row that tiles do not cut into parts, 8 to 512       [512]
+ *   EPP_TUNE_TILES_AT_ONCE  tiles that the rows are dealt to at a time, a multiple of 512  [2048]
  *   EPP_TUNE_PACK         source rows copied to a wider stride by the launch: 0 never, 1 where it pays, 2 always  [1]
  *   EPP_TUNE_HOT_MB       budget of the hot source rows (given: marks are set wherever the rows do not fit it), 0 switches
  *                         hot/cold marking off                                           [80, where marks pay]
